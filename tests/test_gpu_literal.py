@@ -217,3 +217,57 @@ def test_decode_probs_over_many_chunks_and_schemes():
         else:
             assert np.abs(got - want).max() <= tol, (dtype, k_scheme)
         assert np.all(got[:, :, Ltot:] == 0.0)
+
+
+@pytest.mark.parametrize("P,B,Hq,N,n_out", [(1, 1, 1, 40, 1), (9, 2, 40, 100, 33), (8, 1, 70, 64, 64), (17, 3, 64, 131, 65), (10, 300, 2, 70, 70)])
+def test_rows_saliency_shapes(P, B, Hq, N, n_out):
+    """Columns around the edges of a workgroup's tile (32 and 64 columns), more heads than are
+    summed at once, row counts around a batch of rows; cells past a row's length hold NaN."""
+    g = torch.Generator().manual_seed(P * 1000 + Hq)
+    rows = torch.rand(P, B, Hq, N, generator=g)
+    row_len = torch.sort(torch.randint(1, N + 1, (P,), generator=g)).values.to(torch.int32)
+    seen = torch.arange(N)[None] < row_len[:, None].long()                       # [P, N]
+    rows = torch.where(seen[:, None, None], rows, torch.full((), float("nan")))
+    want = torch.where(seen[:, None, None], rows, torch.zeros(())).double().sum(0).mean(1)[:, :n_out]
+    cnt = seen.sum(0)[:n_out].double()
+    for normalize in (True, False):
+        ref = want / cnt.clamp(min=1) if normalize else want
+        got = zb.zc_rows_saliency(rows.to(DEV), row_len.to(DEV), n_out, normalize=normalize).cpu().double()
+        # P * Hq terms of at most 1 summed in fp32 in two chains
+        assert float((got - ref).abs().max()) <= 2.0 ** -24 * (P + Hq) * float(ref.max()) + 1e-12
+
+
+@pytest.mark.parametrize("bits_hi,bits_lo,d,dtype", [(4, 2, 128, torch.bfloat16), (8, 4, 64, torch.float16), (2, 8, 128, torch.float32)])
+def test_dequantize_cache_is_the_unpacked_cache_in_token_order(bits_hi, bits_lo, d, dtype):
+    """More segments than one launch takes, empty subsets, lengths around a block's edges, both
+    layouts; positions past the output are skipped, other rows are untouched."""
+    B, H = 2, 3
+    sizes = [(64, 64), (1, 0), (0, 1), (33, 65), (16, 15)] + [(5, 9)] * 9
+    cap = 64 * 20
+    g = torch.Generator().manual_seed(bits_hi)
+    total = sum(a + b for a, b in sizes)
+    X = torch.randn(B, H, total, d, generator=g).to(dtype).to(DEV)
+    for scheme, layout in (("channel", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP), ("token", zb.ZC_LAYOUT_ROW)):
+        p = zb.PackedTensor(B, H, d, cap, cap, bits_hi, bits_lo, scheme, layout, max_chunks=len(sizes), device=DEV)
+        n0 = 0
+        for k, r in sizes:
+            sal, reg = zb.zc_select_salient(torch.rand(B, k + r, generator=g).to(DEV), k)
+            zb.zc_quantize_pack(X[:, :, n0:n0 + k + r], sal, reg, p, pos_offset=n0)
+            n0 += k + r
+        Lout = total - 3
+        out = torch.full((B, H, Lout + 2, d), 7.0, dtype=dtype, device=DEV)
+        want = torch.full((B, total, H * d), 7.0, dtype=torch.float32, device=DEV)
+        for ci in range(len(sizes)):
+            for which in (0, 1):
+                n = p.chunks[ci][2 * which + 1]
+                if n == 0:
+                    continue
+                _, dq = zb.zc_unpack(p, which, ci)
+                begin = p.chunks[ci][2 * which]
+                pos = (p.pos_lo if which else p.pos_hi)[:, begin:begin + n].long()
+                for b in range(B):
+                    want[b, pos[b]] = dq[b]
+        zb.zc_dequantize_cache(p, out[:, :, :Lout])
+        want = want.to(dtype).view(B, total, H, d).permute(0, 2, 1, 3)
+        assert torch.equal(out[:, :, :Lout], want[:, :, :Lout])
+        assert float((out[:, :, Lout:].float() - 7.0).abs().max()) == 0.0
