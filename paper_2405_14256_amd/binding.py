@@ -1,13 +1,16 @@
-"""ctypes binding of libzipcache.so: argument marshalling only.
+"""Binding of libzipcache.so: argument marshalling only.
 
 Every function has the name of the C entry point it calls.  Tensors are torch
 tensors on the GPU (torch supplies device memory and the current HIP stream);
-no arithmetic of the method happens here.  If the library has not been built
-the import of any entry point fails loudly - there is no fallback path.
+no arithmetic of the method happens here.  The calls of a prompt and of a decode
+step are marshalled by native code (`csrc/host/marshal.cpp` -> `_zc_host.so`), the
+comparison helpers by ctypes.  If the libraries have not been built the import of
+any entry point fails loudly - there is no fallback path.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 from typing import Optional
 
@@ -16,6 +19,7 @@ import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libzipcache.so")
+HOST_PATH = os.path.join(_HERE, "_zc_host.so")
 
 ZC_OK = 0
 ZC_F32, ZC_F16, ZC_BF16 = 0, 1, 2
@@ -54,15 +58,17 @@ class ZipCacheError(RuntimeError):
 
 
 _lib = None
+_host = None
 
 
 def load() -> C.CDLL:
     """Loads the HIP library; raises if it has not been built."""
-    global _lib
+    global _lib, _host
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise ImportError(f"{LIB_PATH} is missing: run `python __graft_entry__.py` to build the HIP library")
+    for path in (LIB_PATH, HOST_PATH):
+        if not os.path.exists(path):
+            raise ImportError(f"{path} is missing: run `python __graft_entry__.py` to build the HIP library")
     lib = C.CDLL(LIB_PATH)
     P, I32, I64, F, SZ = C.c_void_p, C.c_int32, C.c_int64, C.c_float, C.c_size_t
     T4, PK = C.POINTER(zc_tensor4), C.POINTER(zc_packed)
@@ -110,8 +116,22 @@ def load() -> C.CDLL:
     lib.zc_status_string.argtypes = [C.c_int]
     lib.zc_version.restype = C.c_int
     lib.zc_version.argtypes = []
-    _lib = lib
+    if _host is None:
+        spec = importlib.util.spec_from_file_location("paper_2405_14256_amd._zc_host", HOST_PATH)
+        host = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(host)
+    else:
+        host = _host
+    host.bind(tuple(C.cast(getattr(lib, name), C.c_void_p).value for name in host.names()))
+    _lib, _host = lib, host
     return lib
+
+
+def _native():
+    """The native marshalling module, bound to the loaded library."""
+    if _lib is None:
+        load()
+    return _host
 
 
 def _check(fn: str, status: int) -> None:
@@ -132,21 +152,6 @@ def tensor4(t: torch.Tensor) -> zc_tensor4:
     assert t.dim() == 4 and t.stride(3) == 1, "need a 4-D tensor with contiguous last axis"
     return zc_tensor4(t.data_ptr(), _DTYPE[t.dtype], 0, t.shape[0], t.shape[1], t.shape[2], t.shape[3],
                       t.stride(0), t.stride(1), t.stride(2))
-
-
-_ws_cache = {}
-
-
-def _workspace(nbytes: int, device, tag: str = "scratch") -> torch.Tensor:
-    """A scratch tensor per device, operation and stream (calls issued on different
-    streams may run concurrently, so they must not share scratch memory), grown
-    on demand and reused across calls."""
-    key = (str(device), tag, _stream())
-    cur = _ws_cache.get(key)
-    if cur is None or cur.numel() < nbytes:
-        cur = torch.zeros(max(int(nbytes), 256), dtype=torch.uint8, device=device)
-        _ws_cache[key] = cur
-    return cur
 
 
 class PackedTensor:
@@ -211,19 +216,10 @@ def zc_probe_saliency(q: torch.Tensor, k: torch.Tensor, probe_pos: torch.Tensor,
                       probe_rows: Optional[torch.Tensor] = None, sm_scale: float = 0.0,
                       lse_ext: Optional[torch.Tensor] = None, scores: Optional[torch.Tensor] = None,
                       scores_per_head: Optional[torch.Tensor] = None, _entry: str = "zc_probe_saliency") -> torch.Tensor:
-    lib = load()
-    B, Hq, _, _ = q.shape
-    Lk = k.shape[2]
-    P = int(probe_pos.numel())
+    host = _native()
     if scores is None:
-        scores = torch.empty(B, Lk, dtype=torch.float32, device=q.device)
-    need = lib.zc_probe_saliency_workspace(B, Hq, Lk, P)
-    ws = _workspace(need, q.device)
-    tq, tk = tensor4(q), tensor4(k)
-    _check(_entry,
-           getattr(lib, _entry)(C.byref(tq), C.byref(tk), _ptr(probe_rows), _ptr(probe_pos), P, float(sm_scale),
-                                _ptr(lse_ext), _ptr(scores), _ptr(scores_per_head), ws.data_ptr(), ws.numel(),
-                                _stream()))
+        scores = torch.empty(q.shape[0], k.shape[2], dtype=torch.float32, device=q.device)
+    _check(_entry, host.probe(_entry == "zc_probe_accumulated", q, k, probe_rows, probe_pos, sm_scale, lse_ext, scores, scores_per_head))
     return scores
 
 
@@ -236,66 +232,39 @@ def zc_prefill_attention(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, sm_s
                          out: Optional[torch.Tensor] = None, lse: Optional[torch.Tensor] = None,
                          probe_pos: Optional[torch.Tensor] = None, lse_probe: Optional[torch.Tensor] = None):
     """(out [B, Hq, L, D], lse [B, Hq, L], lse_probe [B, Hq, P] or None)."""
-    lib = load()
-    B, Hq, L, _ = q.shape
+    host = _native()
     if out is None:
         out = torch.empty_like(q)
     if lse is None:
-        lse = torch.empty(B, Hq, L, dtype=torch.float32, device=q.device)
-    P = int(probe_pos.numel()) if probe_pos is not None else 0
-    if P and lse_probe is None:
-        lse_probe = torch.empty(B, Hq, P, dtype=torch.float32, device=q.device)
-    tq, tk, tv, to = tensor4(q), tensor4(k), tensor4(v), tensor4(out)
-    _check("zc_prefill_attention",
-           lib.zc_prefill_attention(C.byref(tq), C.byref(tk), C.byref(tv), float(sm_scale), C.byref(to), _ptr(lse),
-                                    _ptr(probe_pos) if P else None, P, _ptr(lse_probe) if P else None, _stream()))
+        lse = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
+    if lse_probe is None and probe_pos is not None and probe_pos.numel():
+        lse_probe = torch.empty(q.shape[0], q.shape[1], probe_pos.numel(), dtype=torch.float32, device=q.device)
+    _check("zc_prefill_attention", host.prefill(q, k, v, sm_scale, out, lse, probe_pos, lse_probe))
     return out, lse, lse_probe
 
 
 def zc_select_salient(scores: torch.Tensor, k: int, salient_idx: Optional[torch.Tensor] = None,
                       regular_idx: Optional[torch.Tensor] = None, mask: Optional[torch.Tensor] = None):
-    lib = load()
-    B, L = scores.shape
-    dev = scores.device
-    if salient_idx is None:
-        salient_idx = torch.empty(B, max(k, 0), dtype=torch.int32, device=dev)
-    if regular_idx is None:
-        regular_idx = torch.empty(B, max(L - k, 0), dtype=torch.int32, device=dev)
-    _check("zc_select_salient",
-           lib.zc_select_salient(scores.data_ptr(), B, L, k, _ptr(salient_idx), _ptr(regular_idx), _ptr(mask),
-                                 None, 0, _stream()))
+    host = _native()
+    if salient_idx is None or regular_idx is None:
+        B, L = scores.shape
+        if salient_idx is None:
+            salient_idx = torch.empty(B, max(k, 0), dtype=torch.int32, device=scores.device)
+        if regular_idx is None:
+            regular_idx = torch.empty(B, max(L - k, 0), dtype=torch.int32, device=scores.device)
+    _check("zc_select_salient", host.select(scores, k, salient_idx, regular_idx, mask))
     return salient_idx, regular_idx
 
 
 def zc_quantize_pack(x: torch.Tensor, salient_idx: torch.Tensor, regular_idx: torch.Tensor,
                      out: PackedTensor, pos_offset: int = 0) -> None:
-    lib = load()
-    B, H, _, D = x.shape
-    k = int(salient_idx.shape[1]) if salient_idx is not None else 0
-    n_reg = int(regular_idx.shape[1]) if regular_idx is not None else 0
-    need = lib.zc_quantize_pack_workspace(B, H, k + n_reg, D)
-    ws = _workspace(need, x.device, "quantize")
-    tx = tensor4(x)
-    _check("zc_quantize_pack",
-           lib.zc_quantize_pack(C.byref(tx), _ptr(salient_idx) if k else None, k,
-                                _ptr(regular_idx) if n_reg else None, n_reg, pos_offset,
-                                C.byref(out.c), ws.data_ptr(), ws.numel(), _stream()))
+    _check("zc_quantize_pack", _native().quantize(x, salient_idx, regular_idx, out.c, pos_offset))
 
 
 def zc_quantize_pack_kv(xk: torch.Tensor, xv: torch.Tensor, salient_idx: torch.Tensor, regular_idx: torch.Tensor,
                         outK: PackedTensor, outV: PackedTensor, pos_offset: int = 0) -> None:
     """Keys and values of one cache in the same launches (the four quantizer calls of Algorithm 2)."""
-    lib = load()
-    B, H, _, D = xk.shape
-    k = int(salient_idx.shape[1]) if salient_idx is not None else 0
-    n_reg = int(regular_idx.shape[1]) if regular_idx is not None else 0
-    need = lib.zc_quantize_pack_kv_workspace(B, H, k + n_reg, D)
-    ws = _workspace(need, xk.device, "quantize_kv")
-    tk, tv = tensor4(xk), tensor4(xv)
-    _check("zc_quantize_pack_kv",
-           lib.zc_quantize_pack_kv(C.byref(tk), C.byref(tv), _ptr(salient_idx) if k else None, k,
-                                   _ptr(regular_idx) if n_reg else None, n_reg, pos_offset,
-                                   C.byref(outK.c), C.byref(outV.c), ws.data_ptr(), ws.numel(), _stream()))
+    _check("zc_quantize_pack_kv", _native().quantize_kv(xk, xv, salient_idx, regular_idx, outK.c, outV.c, pos_offset))
 
 
 def zc_unpack(p: PackedTensor, which: int, chunk: int, codes: bool = True, dequant: bool = True):
@@ -317,22 +286,10 @@ def zc_decode_attention(q: torch.Tensor, Kp: PackedTensor, Vp: PackedTensor,
                         tail_len: int = 0, sm_scale: float = 0.0, out: Optional[torch.Tensor] = None,
                         lse_out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """q: [B, Hq, D] or [B, Hq, 1, D]."""
-    lib = load()
-    if q.dim() == 3:
-        q = q.unsqueeze(2)
-    B, Hq, _, D = q.shape
+    host = _native()
     if out is None:
-        out = torch.empty(B, Hq, D, dtype=q.dtype, device=q.device)
-    need = lib.zc_decode_attention_workspace(B, Hq, D)
-    ws = _workspace(need, q.device, "decode")
-    tq = tensor4(q)
-    ttk = tensor4(tail_k) if tail_len else None
-    ttv = tensor4(tail_v) if tail_len else None
-    _check("zc_decode_attention",
-           lib.zc_decode_attention(C.byref(tq), C.byref(Kp.c), C.byref(Vp.c),
-                                   C.byref(ttk) if tail_len else None, C.byref(ttv) if tail_len else None,
-                                   tail_len, float(sm_scale), out.data_ptr(), _ptr(lse_out),
-                                   ws.data_ptr(), ws.numel(), _stream()))
+        out = torch.empty(q.shape[0], q.shape[1], q.shape[-1], dtype=q.dtype, device=q.device)
+    _check("zc_decode_attention", host.decode(False, q, Kp.c, Vp.c, tail_k, tail_v, tail_len, sm_scale, out, lse_out))
     return out
 
 
@@ -342,53 +299,31 @@ def zc_decode_attention_static(q: torch.Tensor, Kp: PackedTensor, Vp: PackedTens
                                lse_out: Optional[torch.Tensor] = None) -> torch.Tensor:
     """zc_decode_attention on the library's own scratch buffer: nothing is allocated, here
     or in the library (`out` must be given)."""
-    lib = load()
-    if q.dim() == 3:
-        q = q.unsqueeze(2)
-    tq = tensor4(q)
-    ttk = tensor4(tail_k) if tail_len else None
-    ttv = tensor4(tail_v) if tail_len else None
     _check("zc_decode_attention_static",
-           lib.zc_decode_attention_static(C.byref(tq), C.byref(Kp.c), C.byref(Vp.c),
-                                          C.byref(ttk) if tail_len else None, C.byref(ttv) if tail_len else None,
-                                          tail_len, float(sm_scale), out.data_ptr(), _ptr(lse_out), _stream()))
+           _native().decode(True, q, Kp.c, Vp.c, tail_k, tail_v, tail_len, sm_scale, out, lse_out))
     return out
 
 
 def zc_decode_probs(q: torch.Tensor, Kp: PackedTensor, tail_k: Optional[torch.Tensor], tail_len: int, tail_pos0: int,
                     lse: torch.Tensor, probs_out: torch.Tensor, sm_scale: float = 0.0) -> torch.Tensor:
     """probs_out [B, Hq, N] (token order) of one decode step; lse from zc_decode_attention."""
-    lib = load()
-    if q.dim() == 3:
-        q = q.unsqueeze(2)
-    assert probs_out.dim() == 3 and probs_out.is_contiguous() and probs_out.dtype == torch.float32
-    tq = tensor4(q)
-    ttk = tensor4(tail_k) if tail_len else None
-    _check("zc_decode_probs",
-           lib.zc_decode_probs(C.byref(tq), C.byref(Kp.c), C.byref(ttk) if tail_len else None, tail_len, tail_pos0,
-                               float(sm_scale), lse.data_ptr(), probs_out.data_ptr(), probs_out.shape[2], _stream()))
+    _check("zc_decode_probs", _native().probs(q, Kp.c, tail_k, tail_len, tail_pos0, lse, probs_out, sm_scale))
     return probs_out
 
 
 def zc_rows_saliency(rows: torch.Tensor, row_len: torch.Tensor, n_out: int, normalize: bool = True,
                      scores: Optional[torch.Tensor] = None) -> torch.Tensor:
     """rows [P, B, Hq, N] float32, row_len int32 [P] -> scores [B, n_out]."""
-    lib = load()
-    P, B, Hq, N = rows.shape
-    assert rows.is_contiguous() and rows.dtype == torch.float32 and row_len.dtype == torch.int32
+    host = _native()
     if scores is None:
-        scores = torch.empty(B, n_out, dtype=torch.float32, device=rows.device)
-    _check("zc_rows_saliency",
-           lib.zc_rows_saliency(rows.data_ptr(), row_len.data_ptr(), P, B, Hq, N, n_out, int(normalize),
-                                scores.data_ptr(), _stream()))
+        scores = torch.empty(rows.shape[1], n_out, dtype=torch.float32, device=rows.device)
+    _check("zc_rows_saliency", host.rows_saliency(rows, row_len, n_out, normalize, scores))
     return scores
 
 
 def zc_dequantize_cache(p: PackedTensor, out: torch.Tensor) -> torch.Tensor:
     """Scatters x_hat of every token of `p` to out[b, h, position, :]."""
-    lib = load()
-    to = tensor4(out)
-    _check("zc_dequantize_cache", lib.zc_dequantize_cache(C.byref(p.c), C.byref(to), _stream()))
+    _check("zc_dequantize_cache", _native().dequantize(p.c, out))
     return out
 
 
