@@ -14,6 +14,16 @@
 
 namespace zc {
 
+// ---- zc_decode_probs -----------------------------------------------------------------------
+constexpr int kProbSegs = 16;     // segments (chunk x subset, and the tail) one launch takes
+constexpr int kProbTile = 16;     // cache slots (or tail tokens) of one matrix-core tile
+constexpr int kTailSub = 2;       // `sub` of the tail's segment
+
+struct ProbsSeg {
+  int begin, len;           // slots (tail: tokens)
+  int first_block;          // this segment's first workgroup
+  int chunk, sub;
+};
 struct ProbsArgs {
   const void* q;
   int64_t q_sB, q_sH;
@@ -27,125 +37,228 @@ struct ProbsArgs {
   int k_tok;
   int64_t cap[2];
   int bits[2];
-  const int32_t* chunk_table;
-  int n_chunks;
-  int n_seg_tiles;          // 64-slot tiles of all packed segments together
   const void* tail_k;
   int64_t tk_sB, tk_sH, tk_sL;
-  int tail_len, tail_pos0;
+  int tail_pos0;
   float scale_log2;
   const float* lse;         // [B, Hq] natural log
   float* probs;             // [B, Hq, N]
   int N;
+  int tpw;                  // tiles per wave
+  int n_segs;
+  ProbsSeg seg[kProbSegs];
 };
 
-constexpr int kProbSlots = 64;    // cache slots (or tail tokens) per workgroup
+typedef float f4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
-// grid (tiles, Hkv, B), 256 threads: thread (t, kq) = (slot of the tile, quarter of its row)
+// Bound: vector-instruction issue (the unpacking), below a few thousand tokens latency.
+// Logits on the matrix cores: D[slot][column] = sum_c code[slot][c] q'[column][c] with
+// v_mfma_f32_16x16x32_f16.  A code is exact in fp16 at every width; q' enters as fp16 value and
+// residual (scaled by 2^11), two columns per head, after a power of two per head has brought its
+// largest element to [1, 2): 22 bits, whatever the scale of the query.  A lane's quarter row
+// (channels kg D / 4 ...) is contiguous in the ROW layout and goes from memory straight to its
+// registers.  The tail's few tokens take v_mfma_f32_16x16x4_f32 instead (no rounding of K).
+// Measured, us per call: on the vector ALUs with q' in LDS / with fp32 matrix instructions for
+// the packed tokens too / now:
+//   4096 tokens, 8 KV heads of 4 query heads      13.6 /   8.5 /  6.8
+//   the same, batch 8                             47.9 /  33.0 / 16.6
+//   2000 tokens, 40 KV heads of 1, batch 16      103.3 / 124.1 / 57.3
+constexpr float kProbLo = 2048.f;
+
+// Codes of a quarter row (NK = D / 4 channels) as fp16 operand registers, two codes each: register
+// i of word w holds its codes code_slot<BITS>(i) and code_slot<BITS>(i) + (half-word distance).
+// 1024 + code is the code under the exponent of 1024; taking 1024 off leaves the exact number.
+template <int BITS, int NK>
+__device__ inline void codes_to_half(const uint32_t* w, uint32_t (&r)[NK / 2]) {
+  constexpr int E = 32 / BITS;                        // codes per word, E / 2 registers
+  constexpr uint32_t M = BITS == 8 ? 0x00ff00ffu : BITS == 4 ? 0x000f000fu : 0x00030003u;
+#pragma unroll
+  for (int i = 0; i < NK / E; ++i)
+#pragma unroll
+    for (int j = 0; j < E / 2; ++j) {
+      const h2 x = __builtin_bit_cast(h2, ((w[i] >> (BITS * j)) & M) | 0x64006400u) - h2{(_Float16)1024.f, (_Float16)1024.f};
+      r[i * (E / 2) + j] = __builtin_bit_cast(uint32_t, x);
+    }
+}
+// channel (inside the quarter row) of the low (half = 0) or high code of register i
+template <int BITS>
+__device__ constexpr int channel_of(int i, int half) {
+  constexpr int E = 32 / BITS;
+  return i / (E / 2) * E + i % (E / 2) + half * (E / 2);
+}
+
+template <int DT, int D, int BITS>
+__device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chunk, int sub, int begin, int len, int tile0, int ntiles) {
+  constexpr int NK = D / 4, KS = D / 32;              // channels per lane and tile; matrix instructions per tile
+  constexpr int NW = NK * BITS / 32, ROWB = D * BITS / 8;
+  const int lane = threadIdx.x & 63, n = lane & 15, kg = lane >> 4;
+  const int g = n >> 1, part = n & 1;                 // head and part (value, residual) of this lane's column
+  const bool nvalid = g < a.G;
+  const int64_t cap = sub ? a.cap[1] : a.cap[0];
+  const uint8_t* kc = (sub ? a.kc[1] : a.kc[0]) + (((int64_t)b * a.Hkv + hk) * cap + begin) * ROWB + kg * (ROWB / 4);
+  const int64_t tok0 = (int64_t)b * cap + begin + 4 * kg;
+  const int32_t* pos_src = (sub ? a.pos[1] : a.pos[0]) + tok0;
+  const float *ts_src = nullptr, *tz_src = nullptr;
+  if (a.k_tok) { ts_src = (sub ? a.k_ts[1] : a.k_ts[0]) + tok0; tz_src = (sub ? a.k_tz[1] : a.k_tz[0]) + tok0; }
+
+  // a tile's inputs of this lane: the quarter row of slot n, positions and token parameters of slots 4 kg ..
+  // (slots past the segment's end lie inside the same 64-slot unit of the arena)
+  struct In { uint32_t w[NW]; int4 pos; float4 ts, tz; };
+  auto load = [&](int tile, In& in) {
+    const uint8_t* row = kc + (int64_t)(tile * kProbTile + n) * ROWB;
+    if constexpr (NW >= 4) {
+#pragma unroll
+      for (int i = 0; i < NW; i += 4) {
+        const uint4 t = *reinterpret_cast<const uint4*>(row + 4 * i);
+        in.w[i] = t.x; in.w[i + 1] = t.y; in.w[i + 2] = t.z; in.w[i + 3] = t.w;
+      }
+    } else if constexpr (NW == 2) {
+      const uint2 t = *reinterpret_cast<const uint2*>(row);
+      in.w[0] = t.x; in.w[1] = t.y;
+    } else {
+      in.w[0] = *reinterpret_cast<const uint32_t*>(row);
+    }
+    in.pos = *reinterpret_cast<const int4*>(pos_src + tile * kProbTile);
+    in.ts = make_float4(1.f, 1.f, 1.f, 1.f);
+    in.tz = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (a.k_tok) {
+      in.ts = *reinterpret_cast<const float4*>(ts_src + tile * kProbTile);
+      in.tz = *reinterpret_cast<const float4*>(tz_src + tile * kProbTile);
+    }
+  };
+  In in;
+  load(tile0, in);
+
+  // q' = q * channel scale * sm_scale * log2(e) of head g (unused columns: 0), its two channel sums
+  const int64_t hq = (int64_t)b * a.Hq + hk * a.G + (nvalid ? g : 0);
+  const float lse2 = a.lse[hq] * kLog2e;
+  u4 qB[KS];
+  float aq = 0.f, bq = 0.f, unscale;
+  {
+    const int64_t qoff = (int64_t)b * a.q_sB + (int64_t)(hk * a.G + (nvalid ? g : 0)) * a.q_sH + kg * NK;
+    const int64_t coff = ((int64_t)(chunk * 2 + sub) * a.B + b) * (a.Hkv * D) + hk * D + kg * NK;
+    const float scale = nvalid ? a.scale_log2 : 0.f;
+    float qp[NK], top = 0.f;
+#pragma unroll
+    for (int c8 = 0; c8 < NK; c8 += 8) {
+      float v[8], cs[8], cz[8];
+      load8<DT>(a.q, qoff + c8, v);
+      load8<ZC_F32>(a.k_cs, coff + c8, cs);
+      load8<ZC_F32>(a.k_cz, coff + c8, cz);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float x = v[i] * cs[i] * scale;
+        qp[c8 + i] = x;
+        top = fmaxf(top, fabsf(x));
+        aq += x;
+        bq = fmaf(x, cz[i], bq);
+      }
+    }
+    aq += __shfl_xor(aq, 16); aq += __shfl_xor(aq, 32);
+    bq += __shfl_xor(bq, 16); bq += __shfl_xor(bq, 32);
+    top = fmaxf(top, __shfl_xor(top, 16));
+    top = fmaxf(top, __shfl_xor(top, 32));
+    // the power of two that brings the largest element to [1, 2) (clamped: both factors are finite)
+    const int e = min(max((int)(__float_as_uint(top) >> 23), 1), 253);
+    const float up = __uint_as_float((uint32_t)(254 - e) << 23);
+    unscale = __uint_as_float((uint32_t)e << 23);
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      uint32_t r[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        uint32_t bits2 = 0;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+          const float x = qp[channel_of<BITS>(4 * ks + i, half)] * up;
+          const _Float16 hi = (_Float16)x;
+          const _Float16 y = part ? (_Float16)((x - (float)hi) * kProbLo) : hi;
+          bits2 |= (uint32_t)__builtin_bit_cast(uint16_t, y) << (16 * half);
+        }
+        r[i] = bits2;
+      }
+      qB[ks] = u4{r[0], r[1], r[2], r[3]};
+    }
+  }
+  float* out = a.probs + hq * a.N;
+  const bool store_col = nvalid && part == 0;
+
+  for (int i = 0; i < a.tpw; ++i) {
+    const int tile = tile0 + 4 * i;
+    if (tile >= ntiles) break;
+    uint32_t r[NK / 2];
+    codes_to_half<BITS, NK>(in.w, r);
+    const int pos[4] = {in.pos.x, in.pos.y, in.pos.z, in.pos.w};
+    const float ts[4] = {in.ts.x, in.ts.y, in.ts.z, in.ts.w}, tz[4] = {in.tz.x, in.tz.y, in.tz.z, in.tz.w};
+    if (i + 1 < a.tpw && tile + 4 < ntiles) load(tile + 4, in);      // the next tile's inputs are in flight meanwhile
+    f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks)
+      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, u4{r[4 * ks], r[4 * ks + 1], r[4 * ks + 2], r[4 * ks + 3]}),
+                                                   __builtin_bit_cast(h8, qB[ks]), acc, 0, 0, 0);
+    const float own[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const float lo = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(own[v]), 0xB1, 0xF, 0xF, true));   // the neighbour lane's
+      const float dot = fmaf(lo, 1.f / kProbLo, own[v]) * unscale;
+      const float logit2 = ts[v] * (dot - tz[v] * aq - bq);
+      const float p = exp2f(logit2 - lse2);
+      if (store_col && tile * kProbTile + 4 * kg + v < len && pos[v] >= 0 && pos[v] < a.N) out[pos[v]] = p;
+    }
+  }
+}
+
+// the full-precision tail, token tail_pos0 + t at row t
+template <int DT, int D>
+__device__ inline void probs_tail(const ProbsArgs& a, int b, int hk, int len, int tile0, int ntiles) {
+  constexpr int NK = D / 4;
+  const int lane = threadIdx.x & 63, n = lane & 15, kg = lane >> 4;
+  const bool nvalid = n < a.G;
+  const int64_t hq = (int64_t)b * a.Hq + hk * a.G + (nvalid ? n : 0);
+  const int64_t qoff = (int64_t)b * a.q_sB + (int64_t)(hk * a.G + (nvalid ? n : 0)) * a.q_sH + kg * NK;
+  const float scale = nvalid ? a.scale_log2 : 0.f;
+  const float lse2 = a.lse[hq] * kLog2e;
+  float* out = a.probs + hq * a.N + a.tail_pos0;
+  for (int tile = tile0; tile < ntiles && tile < tile0 + 4 * a.tpw; tile += 4) {
+    const int t = min(tile * kProbTile + n, len - 1);
+    const int64_t off = (int64_t)b * a.tk_sB + (int64_t)hk * a.tk_sH + (int64_t)t * a.tk_sL + kg * NK;
+    f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c8 = 0; c8 < NK; c8 += 8) {
+      float kv[8], qv[8];
+      load8<DT>(a.tail_k, off + c8, kv);
+      load8<DT>(a.q, qoff + c8, qv);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(kv[i], qv[i] * scale, acc, 0, 0, 0);
+    }
+    const float dot[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int tt = tile * kProbTile + 4 * kg + v;
+      if (nvalid && tt < len) out[tt] = exp2f(dot[v] - lse2);       // (the host checks tail_pos0 + tail_len <= N)
+    }
+  }
+}
+
+// grid (workgroups of all segments, Hkv, B); a wave takes a.tpw tiles of its segment
 template <int DT, int D>
 __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
-  __shared__ float qp[ZC_MAX_GROUP][D];
-  __shared__ float aq[ZC_MAX_GROUP], bq[ZC_MAX_GROUP];
-  const int tile = blockIdx.x, hk = blockIdx.y, b = blockIdx.z;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int G = a.G;
-  const int t = tid >> 2, kq = tid & 3;
-
-  // which segment (chunk, subset) this tile belongs to: walk the chunk table
-  int ci = -1, sub = 0, begin = 0, len = 0, first = 0;
-  bool is_tail = tile >= a.n_seg_tiles;
-  if (!is_tail) {
-    int cursor = 0;
-    for (int c = 0; c < a.n_chunks && ci < 0; ++c)
-      for (int s = 0; s < 2; ++s) {
-        const int l = a.chunk_table[4 * c + 2 * s + 1];
-        const int nt = ceil_div(l, kProbSlots);
-        if (tile < cursor + nt) { ci = c; sub = s; begin = a.chunk_table[4 * c + 2 * s]; len = l; first = (tile - cursor) * kProbSlots; break; }
-        cursor += nt;
-      }
-    if (ci < 0) return;                 // (the host's tile count and the device table disagree: nothing to do)
-  } else {
-    first = (tile - a.n_seg_tiles) * kProbSlots;
-    len = a.tail_len;
-  }
-  const int ntok = min(kProbSlots, len - first);
-
-  // q' = q * channel scale * sm_scale * log2(e), and its two channel sums
-  const int64_t chan_off = is_tail ? 0 : ((int64_t)(ci * 2 + sub) * a.B + b) * (a.Hkv * D) + hk * D;
-  for (int i = tid; i < G * D; i += 256) {
-    const int g = i / D, c = i % D;
-    const float qv = load1<DT>(a.q, (int64_t)b * a.q_sB + (int64_t)(hk * G + g) * a.q_sH + c);
-    qp[g][c] = qv * (is_tail ? 1.f : a.k_cs[chan_off + c]) * a.scale_log2;
-  }
-  __syncthreads();
-  for (int g = wave; g < G; g += 4) {
-    float sa = 0.f, sb = 0.f;
-    for (int c = lane; c < D; c += 64) { sa += qp[g][c]; sb += qp[g][c] * (is_tail ? 0.f : a.k_cz[chan_off + c]); }
-    sa = wave_sum(sa); sb = wave_sum(sb);
-    if (lane == 0) { aq[g] = sa; bq[g] = sb; }
-  }
-  __syncthreads();
-
-  float dot[ZC_MAX_GROUP];
-#pragma unroll
-  for (int g = 0; g < ZC_MAX_GROUP; ++g) dot[g] = 0.f;
-  int position = -1;
-  float ts = 1.f, tz = 0.f;
-  if (t < ntok) {
-    if (!is_tail) {
-      const int bits = a.bits[sub];
-      const int E = 32 / bits;
-      const uint32_t cmask = (1u << bits) - 1u;
-      const int row_bytes = D * bits / 8, q_bytes = row_bytes / 4;
-      const int64_t slot = (int64_t)begin + first + t;
-      const uint8_t* row = a.kc[sub] + (((int64_t)b * a.Hkv + hk) * a.cap[sub] + slot) * row_bytes + kq * q_bytes;
-      const int nwords = q_bytes / 4;
-      for (int wi = 0; wi < nwords; ++wi) {
-        const uint32_t wv = reinterpret_cast<const uint32_t*>(row)[wi];
-        for (int e = 0; e < E; ++e) {
-          const float code = (float)((wv >> (bits * e)) & cmask);
-          const int c = kq * (D / 4) + wi * E + e;
-#pragma unroll
-          for (int g = 0; g < ZC_MAX_GROUP; ++g)
-            if (g < G) dot[g] = fmaf(qp[g][c], code, dot[g]);
-        }
-      }
-      position = a.pos[sub][(int64_t)b * a.cap[sub] + slot];
-      if (a.k_tok) {
-        ts = a.k_ts[sub][(int64_t)b * a.cap[sub] + slot];
-        tz = a.k_tz[sub][(int64_t)b * a.cap[sub] + slot];
-      }
-    } else {
-      const int64_t off = (int64_t)b * a.tk_sB + (int64_t)hk * a.tk_sH + (int64_t)(first + t) * a.tk_sL + kq * (D / 4);
-      for (int c8 = 0; c8 < D / 4; c8 += 8) {
-        float kv[8];
-        load8<DT>(a.tail_k, off + c8, kv);
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-          for (int g = 0; g < ZC_MAX_GROUP; ++g)
-            if (g < G) dot[g] = fmaf(qp[g][kq * (D / 4) + c8 + i], kv[i], dot[g]);
-      }
-      position = a.tail_pos0 + first + t;
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < ZC_MAX_GROUP; ++g) {
-    if (g < G) {
-      dot[g] += __shfl_xor(dot[g], 1);
-      dot[g] += __shfl_xor(dot[g], 2);
-    }
-  }
-  if (t < ntok && kq == 0 && position >= 0 && position < a.N) {
-#pragma unroll
-    for (int g = 0; g < ZC_MAX_GROUP; ++g) {
-      if (g < G) {
-        const int64_t hq = (int64_t)b * a.Hq + hk * G + g;
-        const float logit2 = ts * (dot[g] - tz * aq[g] - bq[g]);
-        a.probs[hq * a.N + position] = exp2f(logit2 - a.lse[hq] * kLog2e);
-      }
-    }
-  }
+  const int hk = blockIdx.y, b = blockIdx.z;
+  const int wave = threadIdx.x >> 6;
+  int si = 0;
+  while (si + 1 < a.n_segs && (int)blockIdx.x >= a.seg[si + 1].first_block) ++si;
+  const int begin = a.seg[si].begin, len = a.seg[si].len, sub = a.seg[si].sub;
+  const bool is_tail = sub == kTailSub;
+  const int tile0 = ((int)blockIdx.x - a.seg[si].first_block) * 4 * a.tpw + wave, ntiles = ceil_div(len, kProbTile);
+  const int bits = is_tail ? 0 : sub ? a.bits[1] : a.bits[0];
+  if (tile0 >= ntiles) return;
+  if (is_tail) probs_tail<DT, D>(a, b, hk, len, tile0, ntiles);
+  else if (bits == 4) probs_segment<DT, D, 4>(a, b, hk, a.seg[si].chunk, sub, begin, len, tile0, ntiles);
+  else if (bits == 2) probs_segment<DT, D, 2>(a, b, hk, a.seg[si].chunk, sub, begin, len, tile0, ntiles);
+  else probs_segment<DT, D, 8>(a, b, hk, a.seg[si].chunk, sub, begin, len, tile0, ntiles);
 }
 
 // scores[b, i] = mean_h ( sum_{j : row_len[j] > i} rows[j, b, h, i] ) / #{j : row_len[j] > i}
@@ -353,10 +466,9 @@ extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const z
       return ZC_ERR_INVALID_ARG;
   }
   if (q->B > 65535 || Kp->H > 65535) return ZC_ERR_UNSUPPORTED;
-  int64_t seg_tiles = 0;
+  int64_t tiles = ceil_div64(tail_len, kProbTile);
   for (int ci = 0; ci < Kp->n_chunks; ++ci)
-    for (int s = 0; s < 2; ++s) seg_tiles += ceil_div64(Kp->chunk_table_host[4 * ci + 2 * s + 1], kProbSlots);
-  const int64_t tiles = seg_tiles + ceil_div64(tail_len, kProbSlots);
+    for (int sb = 0; sb < 2; ++sb) tiles += ceil_div64(Kp->chunk_table_host[4 * ci + 2 * sb + 1], kProbTile);
   if (tiles > 0x7fffffff) return ZC_ERR_UNSUPPORTED;
   if (tiles == 0) return ZC_OK;
 
@@ -370,26 +482,55 @@ extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const z
   a.k_cs = Kp->chan_scale; a.k_cz = Kp->chan_zero; a.k_tok = Kp->scheme != ZC_SCHEME_CHANNEL;
   a.cap[0] = Kp->cap_hi; a.cap[1] = Kp->cap_lo;
   a.bits[0] = Kp->bits_hi; a.bits[1] = Kp->bits_lo;
-  a.chunk_table = Kp->chunk_table; a.n_chunks = Kp->n_chunks;
-  a.n_seg_tiles = (int)seg_tiles;
   a.tail_k = tail_len ? tail_k->ptr : nullptr;
   a.tk_sB = tail_len ? tail_k->sB : 0; a.tk_sH = tail_len ? tail_k->sH : 0; a.tk_sL = tail_len ? tail_k->sL : 0;
-  a.tail_len = (int)tail_len; a.tail_pos0 = (int)tail_pos0;
+  a.tail_pos0 = (int)tail_pos0;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse = lse; a.probs = probs_out; a.N = (int)N;
-  dim3 grid((unsigned)tiles, (unsigned)a.Hkv, (unsigned)a.B);
+  // one tile a wave while the launch is below two workgroups per CU (latency), up to eight when
+  // the chip is full anyway and a wave's start (the query operand) would weigh as much as its tile
+  {
+    const int64_t t = tiles * a.Hkv * a.B / 2048;
+    a.tpw = (int)(t < 1 ? 1 : t > 8 ? 8 : t);
+  }
   hipStream_t st = (hipStream_t)stream;
-#define ZC_PR(DT)                                                                        \
-  do {                                                                                   \
+  int64_t blocks = 0;
+  a.n_segs = 0;
+  auto flush = [&]() -> int {
+    if (a.n_segs == 0) return ZC_OK;
+    const dim3 grid((unsigned)blocks, (unsigned)a.Hkv, (unsigned)a.B);
+#define ZC_PR(DT)                                                                              \
+  do {                                                                                         \
     if (q->D == 128) hipLaunchKernelGGL((k_decode_probs<DT, 128>), grid, dim3(256), 0, st, a); \
-    else hipLaunchKernelGGL((k_decode_probs<DT, 64>), grid, dim3(256), 0, st, a);          \
+    else hipLaunchKernelGGL((k_decode_probs<DT, 64>), grid, dim3(256), 0, st, a);              \
   } while (0)
-  if (q->dtype == ZC_F32) ZC_PR(ZC_F32);
-  else if (q->dtype == ZC_F16) ZC_PR(ZC_F16);
-  else ZC_PR(ZC_BF16);
+    if (q->dtype == ZC_F32) ZC_PR(ZC_F32);
+    else if (q->dtype == ZC_F16) ZC_PR(ZC_F16);
+    else ZC_PR(ZC_BF16);
 #undef ZC_PR
-  ZC_LAUNCH_CHECK();
-  return ZC_OK;
+    ZC_LAUNCH_CHECK();
+    a.n_segs = 0;
+    blocks = 0;
+    return ZC_OK;
+  };
+  auto add = [&](int begin, int64_t len, int chunk, int sub) -> int {
+    if (len == 0) return ZC_OK;
+    if (a.n_segs == kProbSegs) {
+      const int rcf = flush();
+      if (rcf) return rcf;
+    }
+    a.seg[a.n_segs++] = {begin, (int)len, (int)blocks, chunk, sub};
+    blocks += ceil_div64(ceil_div64(len, kProbTile), 4 * a.tpw);
+    return ZC_OK;
+  };
+  for (int ci = 0; ci < Kp->n_chunks; ++ci)
+    for (int sb = 0; sb < 2; ++sb) {
+      rc = add(Kp->chunk_table_host[4 * ci + 2 * sb], Kp->chunk_table_host[4 * ci + 2 * sb + 1], ci, sb);
+      if (rc) return rc;
+    }
+  rc = add(0, tail_len, 0, kTailSub);
+  if (rc) return rc;
+  return flush();
 }
 
 extern "C" int zc_rows_saliency(const float* rows, const int32_t* row_len, int32_t P, int64_t B, int64_t Hq,

@@ -271,3 +271,36 @@ def test_dequantize_cache_is_the_unpacked_cache_in_token_order(bits_hi, bits_lo,
         want = want.to(dtype).view(B, total, H, d).permute(0, 2, 1, 3)
         assert torch.equal(out[:, :, :Lout], want[:, :, :Lout])
         assert float((out[:, :, Lout:].float() - 7.0).abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,dtype,bits,L,T", [
+    (1, 1, 1, 64, torch.float32, (8, 2), 17, 1), (3, 16, 2, 128, torch.bfloat16, (2, 8), 1000, 33),
+    (16, 40, 40, 128, torch.float16, (4, 2), 515, 0), (2, 6, 2, 128, torch.float32, (4, 4), 63, 16)])
+def test_decode_probs_tiles_and_code_widths(B, Hq, Hkv, d, dtype, bits, L, T):
+    """Segments that end inside a 16-slot tile, one to eight query heads per KV head, every code
+    width, launches of one and of several tiles a wave, more segments than one launch takes."""
+    g = torch.Generator().manual_seed(L)
+    lib = zb.load()
+    sizes = [L] + [3] * 9
+    ks = [L // 3] + [1] * 9
+    K = torch.randn(B, Hkv, sum(sizes) + T, d, generator=g).to(dtype).to(DEV)
+    q = torch.randn(B, Hq, d, generator=g).to(dtype).to(DEV)
+    for scheme in ("channel", "token"):
+        p = zb.PackedTensor(B, Hkv, d, lib.zc_arena_slots(sum(ks), 10), lib.zc_arena_slots(sum(sizes) - sum(ks), 10), *bits, scheme,
+                            zb.ZC_LAYOUT_ROW, max_chunks=10, device=DEV)
+        n0 = 0
+        for n, k in zip(sizes, ks):
+            sal, reg = zb.zc_select_salient(torch.rand(B, n, generator=g).to(DEV), k)
+            zb.zc_quantize_pack(K[:, :, n0:n0 + n], sal, reg, p, pos_offset=n0)
+            n0 += n
+        Kh = K.float()
+        zb.zc_dequantize_cache(p, Kh)
+        logits = (q.double().view(B, Hkv, Hq // Hkv, 1, d) * Kh.double()[:, :, None]).sum(-1).view(B, Hq, -1) / d ** 0.5
+        lse = torch.logsumexp(logits, -1)
+        row = torch.full((B, Hq, n0 + T + 2), -1.0, dtype=torch.float32, device=DEV)
+        zb.zc_decode_probs(q, p, K[:, :, n0:] if T else None, T, n0, lse.float(), row)
+        want = torch.exp(logits - lse[..., None])
+        # a probability is exp of a logit of d fp32 terms: a few units of 2^-24 of the largest
+        # partial sum, which the token scale times |code - z| times |q| summed over d bounds by 300
+        assert float(((row[:, :, :n0 + T].double() - want) / want).abs().max()) <= 300 * 2.0 ** -23
+        assert bool((row[:, :, n0 + T:] == -1.0).all())
