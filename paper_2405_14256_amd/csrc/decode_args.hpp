@@ -53,7 +53,7 @@ struct DecArgs {
   float* lse_out;  // [B, Hq] or null
 };
 
-// Defined in decode_mfma.hip: the matrix-core kernel for 2- and 4-bit caches.
+// Defined in decode_mfma.hip: the matrix-core kernel.
 int launch_decode_mfma(const DecArgs& a, int dtype, hipStream_t st);
 
 }  // namespace zc

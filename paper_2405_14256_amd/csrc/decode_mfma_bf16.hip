@@ -3,7 +3,7 @@
 #include "decode_mfma_kernel.hpp"
 
 namespace zc {
-int launch_decode_mfma_bf16(const DecArgs& a, hipStream_t st) { return launch_decode_mfma_dt<ZC_BF16>(a, st); }
+int launch_decode_mfma_bf16(const DecArgs& a, hipStream_t st) { return launch_decode_mfma_dt<ZC_BF16, false>(a, st); }
 }  // namespace zc
 
 #ifdef ZC_TRACE

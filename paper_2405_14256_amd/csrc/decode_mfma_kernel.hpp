@@ -1,5 +1,5 @@
-// Matrix-core kernel of zc_decode_attention for 2- and 4-bit caches (Eq. 4 over
-// the packed cache, Algorithm 3's attention line).
+// Matrix-core kernel of zc_decode_attention (Eq. 4 over the packed cache, Algorithm 3's
+// attention line).
 //
 // The packed cache is a cost line of half-blocks (32 slots: 512 B x D/32 of K
 // codes and as many of V codes, equal compute at either bit width) in which
@@ -19,7 +19,8 @@
 // Both products run on v_mfma_f32_16x16x32_f16 with the codes as one operand:
 //   logits  D[token][n]   = sum_c code[token][c] * q'[n][c]      (A = K codes, ROW layout)
 //   output  D[n][channel] = sum_t w[n][t] * code[t][channel]     (B = V codes, TGROUP layout)
-// A code enters as an fp16 subnormal: masking a packed word leaves the code's
+// A code of 2 or 4 bits enters as an fp16 subnormal (8-bit codes become exact fp16
+// integers, see unpack8): masking a packed word leaves the code's
 // bits somewhere in the low ten bits of each 16-bit half, which reads as
 // code * 2^pos * 2^-24 (the matrix cores keep subnormal inputs).  The bit
 // position pos differs from register to register; the other operand carries
@@ -129,20 +130,40 @@ __device__ inline u4 unpack2(uint32_t w, int half) {
   }
   return r;
 }
+// 8-bit codes, both tensor types: the exact fp16 number code - 128 (1024 + code is the code under
+// the exponent of 1024, one byte permute; one packed subtraction takes 1152 off).  Centring the
+// codes keeps what cancels against the zero points out of the accumulators; the sums of the other
+// operand take 128 off the zero points in turn.  Two registers, codes (0, 2) and (1, 3) of the word.
+constexpr float kCode8Bias = 128.f;
+__device__ inline uint2 unpack8(uint32_t w) {
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  const h2 bias = h2{(_Float16)1152.f, (_Float16)1152.f};
+  const uint32_t even = __builtin_amdgcn_perm(0x64646464u, w, 0x07020700u), odd = __builtin_amdgcn_perm(0x64646464u, w, 0x07030701u);
+  return make_uint2(__builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, even) - bias),
+                    __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, odd) - bias));
+}
 // The factor the other operand carries for operand register i (both halves).
 template <int BITS, bool SUBN> __device__ inline float code_comp(int i) {
-  if constexpr (!SUBN) return BITS == 4 ? 16.f : 4.f;
+  if constexpr (BITS == 8) return 64.f;
+  else if constexpr (!SUBN) return BITS == 4 ? 16.f : 4.f;
   else if constexpr (BITS == 4) return (i & 1) ? 1.f : 16.f;
   else return (float)(64 >> (2 * i));
 }
 template <int BITS, bool SUBN> __device__ inline int code_comp_log2(int i) {
-  if constexpr (!SUBN) return BITS == 4 ? 4 : 2;
+  if constexpr (BITS == 8) return 6;
+  else if constexpr (!SUBN) return BITS == 4 ? 4 : 2;
   else if constexpr (BITS == 4) return (i & 1) ? 0 : 4;
   else return 6 - 2 * i;
 }
 // product of a code and x, divided by what the matrix cores accumulate for it
 template <int BITS, bool SUBN> constexpr float code_unscale() {
-  return SUBN ? (float)(1 << (24 - (BITS == 4 ? 4 : 6))) : 1.f;
+  if constexpr (BITS == 8) return 1.f / 64.f;
+  else return SUBN ? (float)(1 << (24 - (BITS == 4 ? 4 : 6))) : 1.f;
+}
+
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+__device__ inline f4 mfma16_k16(uint2 a, uint2 b, f4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(h4, a), __builtin_bit_cast(h4, b), c, 0, 0, 0);
 }
 
 __device__ inline uint32_t pack_h2(_Float16 lo, _Float16 hi) {
@@ -229,7 +250,11 @@ __device__ inline void raw_to_float(const Raw8<DT>& r, float (&v)[8]) {
 // launches of at most one workgroup per CU, where only latency counts.
 // STG: the operand's inputs reach LDS by transfers of their own (see the segment): for waves
 // with short runs, where a segment's start is a large part of a wave's time.
-template <int DT, int D, bool KTOK, bool VTOK, int MINB, bool STG>
+// WIDE: a subset has 8-bit codes (kernels of their own: a third copy of the segment code in the
+// others would cost them registers).  One kernel for all widths instead of the vector-ALU one
+// that served such caches before (a code at a time, the logits of a block through LDS and three
+// barriers): 4 prompts of 7901 tokens at 8/4 bits, 8 KV heads of 4: 263 -> 14.7 us per call.
+template <int DT, int D, bool KTOK, bool VTOK, int MINB, bool STG, bool WIDE>
 __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   constexpr int KS = D / 32;     // k-steps of the logit product
   constexpr int NR = D / 64;     // 16-byte V loads per lane and block
@@ -381,7 +406,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   // logits, re-referenced here when the reference moves; rel[v] = base[v] - m_ref.
   float m_ref = nvalid ? 0.f : INFINITY;       // (unused columns: every relative logit -inf, weight 0)
   bool seen = false;                            // (wave-uniform) a half-block has been taken in
-  auto update_ref = [&](float lmax, float (&lg)[2][4], float (&rel)[4], const float (&base)[4], float (&a1)[4], f4 (*acc)[4],
+  auto update_ref = [&](float lmax, auto& lg, float (&rel)[4], const float (&base)[4], float (&a1)[4], f4 (*acc)[4],
                         f4& acc1) {
     if (!seen || __builtin_amdgcn_ballot_w64(lmax > 0.f)) {
       float delta = grp_max(lmax);
@@ -409,7 +434,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
 #pragma unroll
       for (int v = 0; v < 4; ++v) rel[v] = base[v] - m_ref;
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
+      for (int jj = 0; jj < (int)(sizeof(lg) / sizeof(lg[0])); ++jj)
 #pragma unroll
         for (int v = 0; v < 4; ++v) lg[jj][v] -= delta;
       seen = true;
@@ -456,12 +481,13 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
           cz8[ks0][2 * i] = cza[i]; cz8[ks0][2 * i + 1] = czb[i];
         }
       } else {
-        // MODE 4: slots (i, half) are channels base + i + 4 half; MODE 0: base + 2 i + half
-        const int base = (MODE == 4) ? grp * (D / 4) + 8 * ks0 : 32 * ks0 + 8 * grp;
+        // MODE 4: slots (i, half) are channels base + i + 4 half; MODE 8: base + 4 (i / 2) + i % 2 + 2 half;
+        // MODE 0: base + 2 i + half
+        const int base = (MODE != 0) ? grp * (D / 4) + 8 * ks0 : 32 * ks0 + 8 * grp;
         float qa[8];
         load8<DT>(qsrc, qoff + base, qa);
         float ca[8] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f}, za[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-        if constexpr (MODE == 4) {
+        if constexpr (MODE != 0) {
           const float4 c0 = *reinterpret_cast<const float4*>(kcs + base), c1 = *reinterpret_cast<const float4*>(kcs + base + 4);
           const float4 z0 = *reinterpret_cast<const float4*>(kcz + base), z1 = *reinterpret_cast<const float4*>(kcz + base + 4);
           ca[0] = c0.x; ca[1] = c0.y; ca[2] = c0.z; ca[3] = c0.w; ca[4] = c1.x; ca[5] = c1.y; ca[6] = c1.z; ca[7] = c1.w;
@@ -471,7 +497,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         for (int i = 0; i < 4; ++i)
 #pragma unroll
           for (int half = 0; half < 2; ++half) {
-            const int e = (MODE == 4) ? i + 4 * half : 2 * i + half;
+            const int e = (MODE == 4) ? i + 4 * half : (MODE == 8) ? 4 * (i >> 1) + (i & 1) + 2 * half : 2 * i + half;
             q8[ks0][2 * i + half] = qa[e]; cs8[ks0][2 * i + half] = ca[e]; cz8[ks0][2 * i + half] = za[e];
           }
       }
@@ -501,11 +527,13 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
           regs[i] = part ? lo2 : hi2;
           if constexpr (SUBN) {
             sq += qn0 + qn1;
+            if constexpr (MODE == 8 && !KTOK) { cz8[ks0][2 * i] -= kCode8Bias; cz8[ks0][2 * i + 1] -= kCode8Bias; }
             sqz = fmaf(qn0, cz8[ks0][2 * i], fmaf(qn1, cz8[ks0][2 * i + 1], sqz));
           } else {
             const float inv_comp = 1.f / comp;      // a power of two
             const float r0 = (h0 + half_lo_to_float(lo2)) * inv_comp, r1 = (h1 + half_hi_to_float(lo2)) * inv_comp;
             sq += r0 + r1;
+            if constexpr (MODE == 8 && !KTOK) { cz8[ks0][2 * i] -= kCode8Bias; cz8[ks0][2 * i + 1] -= kCode8Bias; }
             sqz = fmaf(r0, cz8[ks0][2 * i], fmaf(r1, cz8[ks0][2 * i + 1], sqz));
           }
         } else {
@@ -515,7 +543,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         }
       }
       qB[ks0].x = regs[0]; qB[ks0].y = regs[1]; qB[ks0].z = regs[2]; qB[ks0].w = regs[3];
-      if constexpr (!SUBN && MODE != 0) {
+      if constexpr (!SUBN && MODE != 0 && MODE != 8) {
         sum_k[ks0] = grp_sum(sq - sq_before);
         sumcz_k[ks0] = grp_sum(sqz - sqz_before);
       } else {
@@ -766,7 +794,10 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   // ---------------- packed segments --------------------------------------------------
   auto segment = [&](auto bits_c, int ci, int sub, int begin, int len, int lo, int hi) {
     constexpr int BITS = decltype(bits_c)::value;
-    constexpr int TB = 4 * (32 / BITS), NH = TB / 32;   // slots and half-blocks per block
+    constexpr int TB = 4 * (32 / BITS);                 // slots per block
+    constexpr int HS = BITS == 8 ? 16 : 32, NH = TB / HS;   // slots per half-block (an 8-bit block is one of 16), half-blocks per block
+    constexpr int NJ = HS / 16;                         // 16-slot tiles of a half-block
+    constexpr bool PLAIN = SUBN || BITS == 8;           // the operand is the code itself (no "1" terms)
     constexpr int KW = D * BITS / 128;                  // 32-bit words of K codes per lane and token
     constexpr int ROWB = D * BITS / 8;                  // bytes of one K row
     constexpr float UNSCALE = code_unscale<BITS, SUBN>();
@@ -840,13 +871,18 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     // range check does not see, so for the last block of an arena that is full to its
     // capacity those lanes would otherwise read past the end of the array.)
     const int tok_lane = (4 * lane) | ((TB < 64 && lane >= TB) ? (int)0xFFFFF000u : 0);
+    // (8-bit rows are 128 or 64 bytes: read as they lie, sixteen lanes would meet in two or four bank
+    // groups, so lane l fetches another piece of its row and piece c of row n lies at c ^ kswz(n))
+    constexpr int CPR = ROWB / 16;
+    const int k16 = BITS == 8 ? 16 * ((lane & ~(CPR - 1)) | ((lane ^ ((lane / 16) & (CPR - 1))) & (CPR - 1))) : 16 * lane;
     auto issue = [&](uint32_t dst, int bi, bool live) {
       const int ko = (int)((uint32_t)(begin + bi * TB) * (uint32_t)ROWB);          // = block index * D * 16
       const int to = (int)((uint32_t)(begin + bi * TB) * 4u);
       const int oob = live ? 0 : (int)0xFFFFF000u;     // per-lane offsets beyond any buffer the host admits
       const int v16 = (16 * lane) | oob, v4 = tok_lane | oob;
-      dma16<0>(dst, rs_k, v16, ko);
-      if constexpr (KCH == 2) dma16<1024>(dst, rs_k, v16, ko);
+      const int vk = k16 | oob;
+      dma16<0>(dst, rs_k, vk, ko);
+      if constexpr (KCH == 2) dma16<1024>(dst, rs_k, BITS == 8 ? (k16 ^ 64) | oob : vk, ko);   // (rows 8 ..: piece c at c ^ 4 ^ ...)
       dma16<0>(dst + kCodeBytes, rs_v, v16, ko);
       if constexpr (KCH == 2) dma16<1024>(dst + kCodeBytes, rs_v, v16, ko);
       if constexpr (VTOK) {
@@ -917,12 +953,12 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     // error when sum(q') is large (queries with a common component, a large token scale).
     //   corr_c[ks] + tz corr_s[ks], in accumulator units; value column only (the residual
     //   column is added to it afterwards)
-    const float kconst = SUBN ? -sumqcz : 0.f;
+    const float kconst = PLAIN ? -sumqcz : 0.f;
     float corr_c[KS], corr_s[KS];
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks) {
-      corr_c[ks] = (SUBN || part) ? 0.f : -(SC * Aq_k[ks] + sumqcz_k[ks]) * (1.f / UNSCALE);
-      corr_s[ks] = (SUBN || part) ? 0.f : -Aq_k[ks] * (1.f / UNSCALE);
+      corr_c[ks] = (PLAIN || part) ? 0.f : -(SC * Aq_k[ks] + sumqcz_k[ks]) * (1.f / UNSCALE);
+      corr_s[ks] = (PLAIN || part) ? 0.f : -Aq_k[ks] * (1.f / UNSCALE);
     }
     // factor of operand register v of the weights.  When the weights are not split,
     // the second row of a head carries p instead of w = p ts: its product with the
@@ -945,7 +981,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     // B operand that sums the weights: 1 / factor of each operand register
     // (normalized codes: plain ones, the sum then carries SC and is also the "1" term of the output product)
     u4 ones;
-    if constexpr (!SUBN) ones = u4{0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
+    if constexpr (BITS == 8) ones = u4{0x24002400u, 0x24002400u, 0u, 0u};                          // 1/64
+    else if constexpr (!SUBN) ones = u4{0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
     else if constexpr (BITS == 4) ones = u4{0x2C002C00u, 0x3C003C00u, 0x2C002C00u, 0x3C003C00u};   // 1/16, 1, 1/16, 1
     else ones = u4{0x24002400u, 0x2C002C00u, 0x34003400u, 0x3C003C00u};                            // 1/64, 1/16, 1/4, 1
 
@@ -959,7 +996,9 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
 
     // this lane's addresses in the current stage (they move with the ring, once per
     // block); the half-block adds constants
-    const uint8_t* kbase = ring_gen + n * ROWB + grp * (KW * 4);
+    // (8-bit rows: the 16-byte pieces of a row sit in a swizzled order, see k16, and kbase is the row)
+    const int kswz = (n / (256 / ROWB)) % (ROWB / 16);
+    const uint8_t* kbase = ring_gen + n * ROWB + (BITS == 8 ? 0 : grp * (KW * 4));
     const uint8_t* vbase = ring_gen + kCodeBytes + grp * (D * 4) + 16 * n;
     const uint8_t* tbase = ring_gen + 2 * kCodeBytes + 16 * grp;
     const uint8_t* tsbase = (!WSPLIT && part) ? ring_gen + kOnesOff : tbase;
@@ -967,11 +1006,17 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
       constexpr int SB = 0;
       constexpr int h = decltype(h_c)::value;
       // operands of this half-block from the staging buffer
-      struct { uint32_t kw[2][KW]; u4 vw[NR]; u4 kts[2], ktz[2], vts[2], vtz[2]; } bf;
+      struct { uint32_t kw[NJ][KW]; u4 vw[NR]; u4 kts[NJ], ktz[NJ], vts[NJ], vtz[NJ]; } bf;
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
+      for (int jj = 0; jj < NJ; ++jj) {
         const uint8_t* kp = kbase + SB + 16 * (2 * h + jj) * ROWB;
-        if constexpr (KW == 4) { const u4 t = *reinterpret_cast<const u4*>(kp); bf.kw[jj][0] = t.x; bf.kw[jj][1] = t.y; bf.kw[jj][2] = t.z; bf.kw[jj][3] = t.w; }
+        if constexpr (BITS == 8) {
+#pragma unroll
+          for (int i = 0; i < KW; i += 4) {
+            const u4 t = *reinterpret_cast<const u4*>(kp + (((grp * (KW / 4) + i / 4) ^ kswz) << 4));
+            bf.kw[jj][i] = t.x; bf.kw[jj][i + 1] = t.y; bf.kw[jj][i + 2] = t.z; bf.kw[jj][i + 3] = t.w;
+          }
+        } else if constexpr (KW == 4) { const u4 t = *reinterpret_cast<const u4*>(kp); bf.kw[jj][0] = t.x; bf.kw[jj][1] = t.y; bf.kw[jj][2] = t.z; bf.kw[jj][3] = t.w; }
         else if constexpr (KW == 2) { const uint2 t = *reinterpret_cast<const uint2*>(kp); bf.kw[jj][0] = t.x; bf.kw[jj][1] = t.y; }
         else { bf.kw[jj][0] = *reinterpret_cast<const uint32_t*>(kp); }
         const uint8_t* tp = tbase + SB + 64 * (2 * h + jj);
@@ -983,19 +1028,22 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
       }
 #pragma unroll
       for (int r = 0; r < NR; ++r) bf.vw[r] = *reinterpret_cast<const u4*>(vbase + SB + 256 * r);
-      const int ntok = len - 32 * hb;                  // slots of this half-block inside the segment, >= 1
-      const bool masked = ntok < 32;                   // only the last half-block of a segment
-      float lg[2][4], vts[2][4], vtz[2][4];
+      const int ntok = len - HS * hb;                  // slots of this half-block inside the segment, >= 1
+      const bool masked = ntok < HS;                   // only the last half-block of a segment
+      float lg[NJ][4], vts[NJ][4], vtz[NJ][4];
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj) {
+      for (int jj = 0; jj < NJ; ++jj) {
         const float kts[4] = {__uint_as_float(bf.kts[jj].x), __uint_as_float(bf.kts[jj].y), __uint_as_float(bf.kts[jj].z), __uint_as_float(bf.kts[jj].w)};
         const float ktz[4] = {__uint_as_float(bf.ktz[jj].x), __uint_as_float(bf.ktz[jj].y), __uint_as_float(bf.ktz[jj].z), __uint_as_float(bf.ktz[jj].w)};
         f4 sacc = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
-          if constexpr (BITS == 4) sacc = mfma16(unpack4<SUBN>(bf.kw[jj][ks]), qB[ks], sacc);
+          if constexpr (BITS == 8) {
+            const uint2 c0 = unpack8(bf.kw[jj][2 * ks]), c1 = unpack8(bf.kw[jj][2 * ks + 1]);
+            sacc = mfma16(u4{c0.x, c0.y, c1.x, c1.y}, qB[ks], sacc);
+          } else if constexpr (BITS == 4) sacc = mfma16(unpack4<SUBN>(bf.kw[jj][ks]), qB[ks], sacc);
           else sacc = mfma16(unpack2<SUBN>(bf.kw[jj][ks >> 1], ks & 1), qB[ks], sacc);
-          if constexpr (!SUBN) {
+          if constexpr (!PLAIN) {
             if constexpr (KTOK) {
               sacc.x += fmaf(ktz[0], corr_s[ks], corr_c[ks]); sacc.y += fmaf(ktz[1], corr_s[ks], corr_c[ks]);
               sacc.z += fmaf(ktz[2], corr_s[ks], corr_c[ks]); sacc.w += fmaf(ktz[3], corr_s[ks], corr_c[ks]);
@@ -1013,7 +1061,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         for (int v = 0; v < 4; ++v) {
           float x;
           const float dot = QSPLIT ? own[v] + xor1(own[v]) : own[v];     // value + residual column
-          if constexpr (KTOK && !SUBN) x = fmaf(kts[v], dot * UNSCALE, rel[v]);        // already centred
+          if constexpr (KTOK && BITS == 8) x = fmaf(kts[v], fmaf(kCode8Bias - ktz[v], Aq, fmaf(dot, UNSCALE, kconst)), rel[v]);
+          else if constexpr (KTOK && !SUBN) x = fmaf(kts[v], dot * UNSCALE, rel[v]);        // already centred
           else if constexpr (KTOK) x = fmaf(kts[v], fmaf(-ktz[v], Aq, fmaf(dot, UNSCALE, kconst)), rel[v]);
           else x = fmaf(dot, UNSCALE, rel[v]);
           lg[jj][v] = x;
@@ -1023,7 +1072,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         // slots past the end of the segment: no weight, and their per-token
         // parameters were never written
 #pragma unroll
-        for (int jj = 0; jj < 2; ++jj)
+        for (int jj = 0; jj < NJ; ++jj)
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
             const bool live = 16 * jj + 4 * grp + v < ntok;
@@ -1032,13 +1081,16 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
             vtz[jj][v] = live ? vtz[jj][v] : 0.f;
           }
       }
-      const float lmax = fmaxf(fmaxf(fmaxf(fmaxf(lg[0][0], lg[0][1]), lg[0][2]), fmaxf(fmaxf(lg[0][3], lg[1][0]), lg[1][1])),
-                               fmaxf(lg[1][2], lg[1][3]));       // three v_max3 and one v_max
+      float lmax;
+      if constexpr (NJ == 2)
+        lmax = fmaxf(fmaxf(fmaxf(fmaxf(lg[0][0], lg[0][1]), lg[0][2]), fmaxf(fmaxf(lg[0][3], lg[NJ - 1][0]), lg[NJ - 1][1])),
+                     fmaxf(lg[NJ - 1][2], lg[NJ - 1][3]));       // three v_max3 and one v_max
+      else lmax = fmaxf(fmaxf(lg[0][0], lg[0][1]), fmaxf(lg[0][2], lg[0][3]));
       update_ref(lmax, lg, rel, base, a1, acc, acc1);
       // weights w = p ts and the A operand of the output product
-      float w2[2][4];
+      float w2[NJ][4];
 #pragma unroll
-      for (int jj = 0; jj < 2; ++jj)
+      for (int jj = 0; jj < NJ; ++jj)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
           const float p = fast_exp2(lg[jj][v]);              // 0 for masked slots and unused columns
@@ -1050,15 +1102,31 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
           if constexpr (WSPLIT) { z_part += p; w2[jj][v] = w * wcomp[v]; }
           else w2[jj][v] = w;
         }
+      if constexpr (BITS == 8) {
+        // 16 slots: one k = 16 instruction per output tile; a V word holds the codes of slots 4 grp ..
+        uint2 p8;
+        if constexpr (WSPLIT) p8 = make_uint2(pack_h2(split_part(w2[0][0], part), split_part(w2[0][2], part)),
+                                              pack_h2(split_part(w2[0][1], part), split_part(w2[0][3], part)));
+        else p8 = make_uint2(pack_f2(w2[0][0], w2[0][2]), pack_f2(w2[0][1], w2[0][3]));
+        acc1 = mfma16_k16(p8, make_uint2(ones.x, ones.y), acc1);
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+          const uint32_t ww[4] = {bf.vw[r].x, bf.vw[r].y, bf.vw[r].z, bf.vw[r].w};
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[r][j] = mfma16_k16(p8, unpack8(ww[j]), acc[r][j]);
+        }
+        return;
+      }
       u4 pA;
-      if constexpr (WSPLIT) {
-        pA.x = pack_h2(split_part(w2[0][0], part), split_part(w2[1][0], part));
-        pA.y = pack_h2(split_part(w2[0][1], part), split_part(w2[1][1], part));
-        pA.z = pack_h2(split_part(w2[0][2], part), split_part(w2[1][2], part));
-        pA.w = pack_h2(split_part(w2[0][3], part), split_part(w2[1][3], part));
+      if constexpr (BITS == 8) pA = u4{0u, 0u, 0u, 0u};
+      else if constexpr (WSPLIT) {
+        pA.x = pack_h2(split_part(w2[0][0], part), split_part(w2[NJ - 1][0], part));
+        pA.y = pack_h2(split_part(w2[0][1], part), split_part(w2[NJ - 1][1], part));
+        pA.z = pack_h2(split_part(w2[0][2], part), split_part(w2[NJ - 1][2], part));
+        pA.w = pack_h2(split_part(w2[0][3], part), split_part(w2[NJ - 1][3], part));
       } else {
-        pA.x = pack_f2(w2[0][0], w2[1][0]); pA.y = pack_f2(w2[0][1], w2[1][1]);
-        pA.z = pack_f2(w2[0][2], w2[1][2]); pA.w = pack_f2(w2[0][3], w2[1][3]);
+        pA.x = pack_f2(w2[0][0], w2[NJ - 1][0]); pA.y = pack_f2(w2[0][1], w2[NJ - 1][1]);
+        pA.z = pack_f2(w2[0][2], w2[NJ - 1][2]); pA.w = pack_f2(w2[0][3], w2[NJ - 1][3]);
       }
       acc1 = mfma16(pA, ones, acc1);
 #pragma unroll
@@ -1104,8 +1172,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     //   (value + residual / 2^11 when the weights are split)
     const float r0 = WSPLIT ? acc1.x + acc1.y * kLoInv : acc1.x;
     const float r1 = WSPLIT ? acc1.z + acc1.w * kLoInv : acc1.z;
-    const float sw0 = SUBN ? r0 : r0 * (1.f / SC), sw1 = SUBN ? r1 : r1 * (1.f / SC);
-    const float bias0 = SUBN ? 0.f : r0, bias1 = SUBN ? 0.f : r1;
+    const float sw0 = PLAIN ? r0 : r0 * (1.f / SC), sw1 = PLAIN ? r1 : r1 * (1.f / SC);
+    const float bias0 = PLAIN ? 0.f : r0, bias1 = PLAIN ? 0.f : r1;
     if constexpr (!WSPLIT) { Zrun0 += acc1.y; Zrun1 += acc1.w; }
     float a10 = 0.f, a11 = 0.f;
     if constexpr (VTOK) {
@@ -1115,6 +1183,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
       a1s = grp_sum(a1s);                          // (the same in every row)
       head_columns(a1s, a10, a11);
     }
+    if constexpr (BITS == 8) { a10 = fmaf(-kCode8Bias, sw0, a10); a11 = fmaf(-kCode8Bias, sw1, a11); }
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       const float4 vcs4 = *reinterpret_cast<const float4*>(&svc[wave][4 * (n + 16 * r)]);
@@ -1148,13 +1217,15 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         int bits;
         if constexpr (STG) bits = arg32(offsetof(DecArgs, bits) + 4 * (size_t)sub);
         else bits = sub ? a.bits[1] : a.bits[0];
-        const int TB = 4 * (32 / bits);
-        const int nb = ceil_div(len, 32);          // half-blocks of 32 slots (equal compute at either width)
+        const int nb = WIDE && bits == 8 ? ceil_div(len, 16) : ceil_div(len, 32);   // half-blocks of 32 slots (8 bits: 16), equal compute at any width
         if (nb == 0) continue;
         const int seg0 = cursor + kSegCost;        // the segment's half-blocks sit after its start-up slots
         cursor = seg0 + nb;
         const int lo = max(u0 - seg0, 0), hi = min(u1 - seg0, nb);
         if (lo >= hi) continue;
+        if constexpr (WIDE) {
+          if (bits == 8) { segment(std::integral_constant<int, 8>{}, ci, sub, begin, len, lo, hi); continue; }
+        }
         if (bits == 4) segment(std::integral_constant<int, 4>{}, ci, sub, begin, len, lo, hi);
         else segment(std::integral_constant<int, 2>{}, ci, sub, begin, len, lo, hi);
       }
@@ -1246,28 +1317,28 @@ __global__ __launch_bounds__(D) void k_decode_reduce(const float* __restrict__ p
   if (c == 0) ZC_MARK(2);                       // end
 }
 
-template <int DT>
+template <int DT, bool WIDE>
 static int launch_decode_mfma_dt(const DecArgs& a, hipStream_t st) {
   dim3 grid(a.S, a.Hkv, a.B), block(256);
   const bool small = (int64_t)a.S * a.Hkv * a.B <= a.n_cu;
-  const bool staged = small || a.pw_q < kStagedRun;          // cost units per packed wave
-#define ZC_L(KT, VT)                                                                                          \
-  do {                                                                                                        \
-    if (a.D == 128) {                                                                                         \
-      if (small) hipLaunchKernelGGL((k_decode_mfma<DT, 128, KT, VT, 1, true>), grid, block, 0, st, a);        \
-      else if (staged) hipLaunchKernelGGL((k_decode_mfma<DT, 128, KT, VT, 2, true>), grid, block, 0, st, a);  \
-      else hipLaunchKernelGGL((k_decode_mfma<DT, 128, KT, VT, 2, false>), grid, block, 0, st, a);             \
-    } else {                                                                                                  \
-      if (small) hipLaunchKernelGGL((k_decode_mfma<DT, 64, KT, VT, 1, true>), grid, block, 0, st, a);         \
-      else if (staged) hipLaunchKernelGGL((k_decode_mfma<DT, 64, KT, VT, 2, true>), grid, block, 0, st, a);   \
-      else hipLaunchKernelGGL((k_decode_mfma<DT, 64, KT, VT, 2, false>), grid, block, 0, st, a);              \
-    }                                                                                                         \
+  const bool staged = small || (!WIDE && a.pw_q < kStagedRun);          // cost units per packed wave
+#define ZC_LD(DD, KT, VT)                                                                                       \
+  do {                                                                                                          \
+    if (small) hipLaunchKernelGGL((k_decode_mfma<DT, DD, KT, VT, 1, true, WIDE>), grid, block, 0, st, a);       \
+    else if (staged) hipLaunchKernelGGL((k_decode_mfma<DT, DD, KT, VT, 2, !WIDE, WIDE>), grid, block, 0, st, a); \
+    else hipLaunchKernelGGL((k_decode_mfma<DT, DD, KT, VT, 2, false, WIDE>), grid, block, 0, st, a);            \
+  } while (0)
+#define ZC_L(KT, VT)                  \
+  do {                                \
+    if (a.D == 128) ZC_LD(128, KT, VT); \
+    else ZC_LD(64, KT, VT);           \
   } while (0)
   if (a.k_tok && a.v_tok) ZC_L(true, true);
   else if (a.k_tok) ZC_L(true, false);
   else if (a.v_tok) ZC_L(false, true);
   else ZC_L(false, false);
 #undef ZC_L
+#undef ZC_LD
   ZC_LAUNCH_CHECK();
   if (a.S > 1) {
 #define ZC_R(DD, NM) hipLaunchKernelGGL((k_decode_reduce<DT, DD, NM>), dim3(a.Hq, a.B), dim3(DD), 0, st, a.part_m, a.part_z, a.part_o, a.S, a.out, a.lse_out)

@@ -1,0 +1,6 @@
+// Instantiates the matrix-core decode kernel for caches with 8-bit codes and f32 queries.
+#include "decode_mfma_kernel.hpp"
+
+namespace zc {
+int launch_decode_wide_f32(const DecArgs& a, hipStream_t st) { return launch_decode_mfma_dt<ZC_F32, true>(a, st); }
+}  // namespace zc
