@@ -4,19 +4,16 @@
 // turn a logit into a probability, so zc_probe_saliency given them (lse_ext) runs its
 // column sweep only.
 //
-// One workgroup per 128 query rows of a (batch, query head), a wave per 32 of them;
-// 64-key tiles of K and V stream through LDS, long row blocks are launched first.
+// A wave owns 32 query rows of a (batch, query head); 64-key tiles of K and V stream
+// through LDS for all waves of a workgroup, long row blocks are launched first.
 //   logits  D[key][query]     = sum_c K[key][c] Q[query][c]        (A = K tile, B = Q rows in registers)
 //   output  D[channel][query] = sum_key Vt[channel][key] P[query][key]   (A = V tile transposed, B = P)
-// Both results put a query in a lane (column r = lane & 31): the running maximum, the
+// Both results put a query in a lane (column r = lane & 31): the running reference, the
 // sum and the rescaling of a row are lane-local (one exchange between the two
 // half-waves, which hold different keys of the same query), and the probabilities a
 // lane has just computed are, converted in place, exactly the B operand of the
 // second product - the order of the keys inside a matrix instruction's k index is
-// free as long as both operands use the same one, and the transposed V tile is
-// written to LDS in the order the logit accumulators imply.
-// K tiles go global -> LDS directly; V tiles pass through registers, where four
-// consecutive keys of eight (four) channels are transposed before they are stored.
+// free as long as both operands use the same one.
 #include <type_traits>
 
 #include "mfma_tiles.hpp"
@@ -30,29 +27,14 @@ struct PrefillArgs {
   int B, Hq, Hkv, G, L;
   float scale_log2;
   float* lse;   // [B, Hq, L] natural log, or null
+  int group;    // query heads an XCD works on at a time (prefill_block)
 };
 
-constexpr int kPfRows = 128;   // query rows per workgroup
+constexpr int kPfRows = 128;   // query rows per workgroup of the fp32 kernel
 constexpr int kPfKeys = 64;    // keys per tile
 
-// The transposed V tile in LDS: one row per channel, the tile's 64 keys along it.
-template <int DT>
-struct VtLayout {
-  static constexpr int EB = (DT == ZC_F32) ? 4 : 2;
-  static constexpr int ROWB = kPfKeys * EB + 16;   // (+16: consecutive channels start four banks apart)
-  // Keys a lane feeds to one matrix-instruction chunk: the accumulators v = VPC * s ..
-  // VPC * (s + 1) - 1 of a 32-key logit tile, i.e. for 16-bit types the keys
-  // 16 s + {4 kh .. 4 kh + 3, 8 + 4 kh .. 8 + 4 kh + 3} of half-wave kh, for fp32 the
-  // keys 8 s + 4 kh .. + 3.  A row stores them contiguously per half-wave.
-  static constexpr int VPC = (DT == ZC_F32) ? 4 : 8;
-  // byte offset inside a row of the four consecutive keys 4 g .. 4 g + 3
-  __device__ static int key4_offset(int g) {
-    if constexpr (DT == ZC_F32) return g * 16;
-    else return (16 * (g >> 2) + 8 * (g & 1) + 4 * ((g >> 1) & 1)) * 2;
-  }
-  // byte offset of the operand chunk of half-wave kh for chunk pc of the tile
-  __device__ static int chunk_offset(int pc, int kh) { return (2 * VPC * pc + VPC * kh) * EB; }
-};
+// The transposed V tile of the fp32 kernel in LDS: one row per channel, the tile's 64 keys along it.
+constexpr int kVtRowB = kPfKeys * 4 + 16;   // (+16: consecutive channels start four banks apart)
 
 template <int DT>
 __device__ inline uint32_t pack_pair(float lo, float hi) {
@@ -66,27 +48,58 @@ __device__ inline uint32_t pack_pair(float lo, float hi) {
   }
 }
 
-template <int DT, int D>
-__global__ __launch_bounds__(256, (DT == ZC_F32) ? 1 : 2) void k_prefill_attention(PrefillArgs a) {
-  using T = Tile<DT, D>;
-  using VT = VtLayout<DT>;
-  constexpr int EB = T::EB;
+// Workgroup -> (batch, query head, first row).  Row blocks go from the longest to the
+// shortest, and inside one length over the heads of a group, so that the last workgroups to
+// start are short ones (a head after the other, the last head's long blocks start when the
+// chip is already draining).  Where the heads divide over the 8 XCDs every XCD keeps its own
+// heads, in groups just large enough for two rounds of its slots: the workgroups in flight
+// then read few K and V heads through its L2.
+__device__ inline void prefill_block(const PrefillArgs& a, int rows, int* b, int* hq, int* q0) {
+  const int nqb = ceil_div(a.L, rows), heads = a.B * a.Hq;
+  int id = blockIdx.x, head, qb;
+  if (heads & 7) {
+    qb = id / heads;
+    head = id % heads;
+  } else {
+    const int hpx = heads >> 3, rank = id >> 3;
+    const int g = rank / (a.group * nqb), rem = rank % (a.group * nqb);
+    const int size = min(a.group, hpx - g * a.group);
+    qb = rem / size;
+    head = (id & 7) * hpx + g * a.group + rem % size;
+  }
+  *q0 = (nqb - 1 - qb) * rows;
+  *b = head / a.Hq;
+  *hq = head % a.Hq;
+}
+
+// Chunk slot permutation of a V tile row: the transposing load reads 64 bytes of four
+// consecutive keys per half-wave (32 bytes per 16 lanes); these land in different banks.
+template <int D>
+__device__ inline int v_swizzle(int key) {
+  return D == 128 ? 4 * (key & 3) ^ (key & 2) : 2 * (key & 2) ^ 2 * (key & 1);
+}
+
+// ---- fp32 ---------------------------------------------------------------------------
+// One workgroup per 128 query rows.  K tiles go global -> LDS directly; V tiles pass through
+// registers, where four consecutive keys of four channels are transposed before they are
+// stored.  Bound by the fp32 matrix instructions (a sixteenth of the 16-bit rate).
+template <int D>
+__global__ __launch_bounds__(256, 1) void k_prefill_attention(PrefillArgs a) {
+  using T = Tile<ZC_F32, D>;
+  constexpr int EB = 4;
   constexpr int KTILE_B = kPfKeys * T::ROWB;
-  constexpr int VTILE_B = D * VT::ROWB;
+  constexpr int VTILE_B = D * kVtRowB;
   constexpr int NI = kPfKeys / T::RPI / 4;       // K transfers per wave and tile
   constexpr int CT = D / 32;                     // 32-channel tiles of the output
-  constexpr int VPC = VT::VPC;
-  constexpr int NPC = 16 / VPC;                  // operand chunks per 32-key logit tile
+  constexpr int NPC = 4;                         // operand chunks per 32-key logit tile: keys 8 s + 4 kh .. + 3 of half-wave kh
   constexpr int VU = 16 * T::CPR;                // V load units of a tile: 4 keys x one 16-byte chunk
   constexpr int VUPT = (VU + 255) / 256;         // units per thread
   __shared__ __align__(16) uint8_t Ks[2][KTILE_B];
   __shared__ __align__(16) uint8_t Vt[2][VTILE_B];
 
-  // logical order: row block fastest (the longest first), then query head, then batch
-  const int nqb = ceil_div(a.L, kPfRows);
-  int j = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int q0 = (nqb - 1 - j % nqb) * kPfRows; j /= nqb;
-  const int hq = j % a.Hq, b = j / a.Hq, hk = hq / a.G;
+  int hq, b, q0;
+  prefill_block(a, kPfRows, &b, &hq, &q0);
+  const int hk = hq / a.G;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)hq * a.q_sH) * EB;
@@ -140,31 +153,16 @@ __global__ __launch_bounds__(256, (DT == ZC_F32) ? 1 : 2) void k_prefill_attenti
       const int u = tid + 256 * uu;
       if (u >= VU) continue;
       const int g4 = u & 15, cc = u >> 4;
-      uint8_t* base = &Vt[buf][0] + VT::key4_offset(g4);
-      if constexpr (DT == ZC_F32) {
-        // chunk cc: channels 4 cc .. 4 cc + 3 of the four keys
-        const uint32_t k0[4] = {vr.x[uu][0].x, vr.x[uu][0].y, vr.x[uu][0].z, vr.x[uu][0].w};
-        const uint32_t k1[4] = {vr.x[uu][1].x, vr.x[uu][1].y, vr.x[uu][1].z, vr.x[uu][1].w};
-        const uint32_t k2[4] = {vr.x[uu][2].x, vr.x[uu][2].y, vr.x[uu][2].z, vr.x[uu][2].w};
-        const uint32_t k3[4] = {vr.x[uu][3].x, vr.x[uu][3].y, vr.x[uu][3].z, vr.x[uu][3].w};
+      uint8_t* base = &Vt[buf][0] + g4 * 16;
+      // chunk cc: channels 4 cc .. 4 cc + 3 of the four keys
+      const uint32_t k0[4] = {vr.x[uu][0].x, vr.x[uu][0].y, vr.x[uu][0].z, vr.x[uu][0].w};
+      const uint32_t k1[4] = {vr.x[uu][1].x, vr.x[uu][1].y, vr.x[uu][1].z, vr.x[uu][1].w};
+      const uint32_t k2[4] = {vr.x[uu][2].x, vr.x[uu][2].y, vr.x[uu][2].z, vr.x[uu][2].w};
+      const uint32_t k3[4] = {vr.x[uu][3].x, vr.x[uu][3].y, vr.x[uu][3].z, vr.x[uu][3].w};
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          u32x4 o; o.x = k0[e]; o.y = k1[e]; o.z = k2[e]; o.w = k3[e];
-          *reinterpret_cast<u32x4*>(base + (4 * cc + e) * VT::ROWB) = o;
-        }
-      } else {
-        // chunk cc: channels 8 cc .. 8 cc + 7; word jw of a key holds channels 2 jw (low half) and 2 jw + 1
-        const uint32_t k0[4] = {vr.x[uu][0].x, vr.x[uu][0].y, vr.x[uu][0].z, vr.x[uu][0].w};
-        const uint32_t k1[4] = {vr.x[uu][1].x, vr.x[uu][1].y, vr.x[uu][1].z, vr.x[uu][1].w};
-        const uint32_t k2[4] = {vr.x[uu][2].x, vr.x[uu][2].y, vr.x[uu][2].z, vr.x[uu][2].w};
-        const uint32_t k3[4] = {vr.x[uu][3].x, vr.x[uu][3].y, vr.x[uu][3].z, vr.x[uu][3].w};
-#pragma unroll
-        for (int jw = 0; jw < 4; ++jw) {
-          const uint2 even = make_uint2((k0[jw] & 0xffffu) | (k1[jw] << 16), (k2[jw] & 0xffffu) | (k3[jw] << 16));
-          const uint2 odd = make_uint2((k0[jw] >> 16) | (k1[jw] & 0xffff0000u), (k2[jw] >> 16) | (k3[jw] & 0xffff0000u));
-          *reinterpret_cast<uint2*>(base + (8 * cc + 2 * jw) * VT::ROWB) = even;
-          *reinterpret_cast<uint2*>(base + (8 * cc + 2 * jw + 1) * VT::ROWB) = odd;
-        }
+      for (int e = 0; e < 4; ++e) {
+        u32x4 o; o.x = k0[e]; o.y = k1[e]; o.z = k2[e]; o.w = k3[e];
+        *reinterpret_cast<u32x4*>(base + (4 * cc + e) * kVtRowB) = o;
       }
     }
   };
@@ -206,7 +204,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32) ? 1 : 2) void k_prefill_attenti
 #pragma unroll
       for (int jt = 0; jt < 2; ++jt) {
         const u32x4 af = *reinterpret_cast<const u32x4*>(&Ks[cur][T::slot(32 * jt + r, 2 * kc + kh)]);
-        mma_chunk<DT>(sacc[jt], af, qf[kc]);
+        mma_chunk<ZC_F32>(sacc[jt], af, qf[kc]);
       }
     }
     // ---- online softmax: a lane owns one row and 32 of the tile's keys ----
@@ -251,18 +249,13 @@ __global__ __launch_bounds__(256, (DT == ZC_F32) ? 1 : 2) void k_prefill_attenti
 #pragma unroll
       for (int sp = 0; sp < NPC; ++sp) {
         u32x4 pb;
-        if constexpr (DT == ZC_F32) {
-          pb.x = __float_as_uint(s[jt][4 * sp]); pb.y = __float_as_uint(s[jt][4 * sp + 1]);
-          pb.z = __float_as_uint(s[jt][4 * sp + 2]); pb.w = __float_as_uint(s[jt][4 * sp + 3]);
-        } else {
-          pb.x = pack_pair<DT>(s[jt][8 * sp], s[jt][8 * sp + 1]); pb.y = pack_pair<DT>(s[jt][8 * sp + 2], s[jt][8 * sp + 3]);
-          pb.z = pack_pair<DT>(s[jt][8 * sp + 4], s[jt][8 * sp + 5]); pb.w = pack_pair<DT>(s[jt][8 * sp + 6], s[jt][8 * sp + 7]);
-        }
-        const int coff = VT::chunk_offset(jt * NPC + sp, kh);
+        pb.x = __float_as_uint(s[jt][4 * sp]); pb.y = __float_as_uint(s[jt][4 * sp + 1]);
+        pb.z = __float_as_uint(s[jt][4 * sp + 2]); pb.w = __float_as_uint(s[jt][4 * sp + 3]);
+        const int coff = (8 * (jt * NPC + sp) + 4 * kh) * EB;
 #pragma unroll
         for (int ct = 0; ct < CT; ++ct) {
-          const u32x4 vf = *reinterpret_cast<const u32x4*>(&Vt[cur][(32 * ct + r) * VT::ROWB + coff]);
-          mma_chunk<DT>(oacc[ct], vf, pb);
+          const u32x4 vf = *reinterpret_cast<const u32x4*>(&Vt[cur][(32 * ct + r) * kVtRowB + coff]);
+          mma_chunk<ZC_F32>(oacc[ct], vf, pb);
         }
       }
   };
@@ -283,12 +276,257 @@ __global__ __launch_bounds__(256, (DT == ZC_F32) ? 1 : 2) void k_prefill_attenti
 #pragma unroll
       for (int v4 = 0; v4 < 4; ++v4) {
         const int c = 32 * ct + acc_row(4 * v4, kh);        // four consecutive channels
-        const float o0 = oacc[ct][4 * v4] * inv, o1 = oacc[ct][4 * v4 + 1] * inv, o2 = oacc[ct][4 * v4 + 2] * inv, o3 = oacc[ct][4 * v4 + 3] * inv;
-        if constexpr (DT == ZC_F32) {
-          *reinterpret_cast<float4*>(orow + c * 4) = make_float4(o0, o1, o2, o3);
-        } else {
-          *reinterpret_cast<uint2*>(orow + c * 2) = make_uint2(pack_pair<DT>(o0, o1), pack_pair<DT>(o2, o3));
-        }
+        *reinterpret_cast<float4*>(orow + c * 4) =
+            make_float4(oacc[ct][4 * v4] * inv, oacc[ct][4 * v4 + 1] * inv, oacc[ct][4 * v4 + 2] * inv, oacc[ct][4 * v4 + 3] * inv);
+      }
+    if (a.lse && kh == 0) a.lse[((int64_t)b * a.Hq + hq) * a.L + qpos] = (m + log2f(l_tot)) * kLn2;
+  }
+}
+
+// ---- 16-bit types -------------------------------------------------------------------
+// One workgroup per 32 * NW query rows, a wave per 32 of them, two waves on a SIMD.  Keys
+// go by halves of a 64-key tile, and a wave's diagonal falls on exactly one half, so no
+// wave multiplies a half it cannot see.  Both tiles come global -> LDS directly; the V
+// operand is read with the transposing LDS load, in row-major tiles as they arrived.
+//
+// Bound by the matrix cores and the power they draw: a half is 16 matrix instructions of 32
+// cycles (d = 128) and about 300 cycles of vector instructions, so the two have to run at the
+// same time.  The logits of half h + 1 are multiplied while the exponentials of half h are
+// taken, and the operands of each product are requested one phase before.  32 heads of 32768
+// rows, bf16: 9.07 -> 7.46 ms (1.18 PFLOP/s; matrix cores busy 61 % of the cycles at the 1.6
+// GHz the chip holds then; a large library product reaches 1.21 PFLOP/s); 2 x 32 heads of
+// 3001 rows, fp16: 225 -> 159 us.  Scheduling barriers between the slices of the first
+// product, or a raised wave priority around the second, cost 3 to 5 %.
+//
+// A row's reference m only has to keep the exponentials in range; it need not be the
+// maximum.  It is taken from the first half and moved when a sum shows that some logit lies
+// far above it (then the half is done again, exactly): no maximum in the common path.  Weights
+// stay below 2^14, which fp16 holds, and at least one of a row's weights has been 1.
+template <int DT, int D, int NW>
+__global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs a) {
+  using T = Tile<DT, D>;
+  constexpr int TILE_B = kPfKeys * T::ROWB;
+  constexpr int NI = kPfKeys / T::RPI / NW;      // transfers per wave, tile and tensor
+  constexpr int CT = D / 32;                     // 32-channel tiles of the output
+  constexpr int EPS = 16 / T::NKC;               // logits per slice
+  constexpr int VS = T::NKC / 4;                 // the slice that requests the first V operand
+  static_assert(NI >= 1, "a wave moves whole transfers");
+  __shared__ __align__(1024) uint8_t Ks[2][TILE_B];
+  __shared__ __align__(1024) uint8_t Vs[2][TILE_B];
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+  int hq, b, q0;
+  prefill_block(a, 32 * NW, &b, &hq, &q0);
+  const int hk = hq / a.G;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)hq * a.q_sH) * 2;
+  const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)hk * a.k_sH) * 2;
+  const uint8_t* vb = reinterpret_cast<const uint8_t*>(a.v) + ((int64_t)b * a.v_sB + (int64_t)hk * a.v_sH) * 2;
+  const uint32_t q_rowb = (uint32_t)(a.q_sL * 2), k_rowb = (uint32_t)(a.k_sL * 2), v_rowb = (uint32_t)(a.v_sL * 2);
+  const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.L - 1) * q_rowb + T::ROWB, kBufFlags);
+  const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.L - 1) * k_rowb + T::ROWB, kBufFlags);
+  const auto rs_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(vb), 0, (uint32_t)(a.L - 1) * v_rowb + T::ROWB, kBufFlags);
+
+  const int ntiles = (min(q0 + 32 * NW, a.L) - 1) / kPfKeys + 1;     // key tiles the workgroup can see
+  const int wq0 = q0 + 32 * w;                                        // first row of this wave
+  const int qpos = wq0 + r;                                           // this lane's row
+  const int nh = wq0 < a.L ? wq0 / 32 + 1 : 0;                        // halves this wave can see: the last is its diagonal
+
+  const uint32_t ks_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&Ks[0][0];
+  const uint32_t vs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&Vs[0][0];
+  int kvoff[NI], vvoff[NI];
+#pragma unroll
+  for (int jj = 0; jj < NI; ++jj) {
+    const int row = (w + NW * jj) * T::RPI + lane / T::CPR;
+    kvoff[jj] = (int)(row * k_rowb) + (((lane % T::CPR) ^ T::swz(row)) << 4);
+    vvoff[jj] = (int)(row * v_rowb) + (((lane % T::CPR) ^ v_swizzle<D>(row)) << 4);
+  }
+  // (the tile's offset is part of the per-lane offset, which the range check sees: rows
+  // past the end arrive as zeros)
+  auto k_issue = [&](int t) {
+    const int toff = (int)((uint32_t)t * kPfKeys * k_rowb);
+#pragma unroll
+    for (int jj = 0; jj < NI; ++jj) dma16<0>(ks_lds + (t & 1) * TILE_B + (w + NW * jj) * 1024, rs_k, kvoff[jj] + toff, 0);
+  };
+  auto v_issue = [&](int t) {
+    const int toff = (int)((uint32_t)t * kPfKeys * v_rowb);
+#pragma unroll
+    for (int jj = 0; jj < NI; ++jj) dma16<0>(vs_lds + (t & 1) * TILE_B + (w + NW * jj) * 1024, rs_v, vvoff[jj] + toff, 0);
+  };
+
+  k_issue(0);
+  v_issue(0);
+  if (ntiles > 1) k_issue(1);
+  // this wave's query rows, straight into operand registers (rows past the end: zeros)
+  u32x4 qf[T::NKC];
+  {
+    const int voff = qpos < a.L ? (int)((uint32_t)qpos * q_rowb) + kh * 16 : kOutOfRange;
+#pragma unroll
+    for (int kc = 0; kc < T::NKC; ++kc) qf[kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_q, voff + kc * 32, 0, 0);
+  }
+
+  // ---- operands from LDS -----------------------------------------------------------------
+  struct KFrag { u32x4 x[T::NKC]; };
+  // (LDS addresses: one register per lane and chunk pattern, tile and half in the offset of
+  // the instruction; the empty assembly keeps the compiler from holding a register for each)
+  typedef __attribute__((address_space(3))) const uint8_t* lds_ptr;
+  uint32_t kaddr = ks_lds + T::slot(r, kh);           // chunk 2 kc + kh sits at kaddr ^ (32 kc)
+  asm volatile("" : "+v"(kaddr));
+  auto k_read = [&](int half, KFrag& f) {
+#pragma unroll
+    for (int kc = 0; kc < T::NKC; ++kc)
+      f.x[kc] = *(__attribute__((address_space(3))) const u32x4*)((lds_ptr)(uintptr_t)(kaddr ^ (32 * kc)) + half * 32 * T::ROWB);
+  };
+  // The transposing load: in every 16 lanes, lanes 4 i .. 4 i + 3 name the 16 channels of key
+  // i, and lane c receives channel c of the four keys.  A lane's 8 k-indices of operand chunk
+  // s are the keys its logit accumulators 8 s .. 8 s + 7 stand for: 16 s + 4 kh + {0 .. 3} and
+  // 16 s + 8 + 4 kh + {0 .. 3}.
+  const int vkey = 4 * kh + ((lane & 15) >> 2);
+  const int vsub = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);         // 16-byte chunk inside a 32-channel tile
+  uint32_t vaddr[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    vaddr[ct] = vs_lds + vkey * T::ROWB + (((4 * ct + vsub) ^ v_swizzle<D>(vkey)) << 4) + (lane & 1) * 8;
+    asm volatile("" : "+v"(vaddr[ct]));
+  }
+  auto v_read = [&](int half, int s, int ct, u32x4& f) {
+    // (the swizzle depends on the key's lowest two bits only)
+    const lds_ptr base = (lds_ptr)(uintptr_t)vaddr[ct] + (half * 32 + 16 * s) * T::ROWB;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)base);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(base + 8 * T::ROWB));
+    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+    f.x = l2.x; f.y = l2.y; f.z = h2.x; f.w = h2.y;
+  };
+
+  v16f oacc[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[ct][i] = 0.f;
+  float m = -INFINITY, l = 0.f;       // the row's reference (log2 units) and this half-wave's share of the sum
+  KFrag kf;
+  v16f s0, s1;
+
+  wait_all_loads();
+  __syncthreads();
+  k_read(0, kf);
+  s0 = v16f{};
+#pragma unroll
+  for (int kc = 0; kc < T::NKC; ++kc) mma_chunk<DT>(s0, kf.x[kc], qf[kc]);
+  k_read(1, kf);
+  kaddr += TILE_B;                                   // the K operands of a step are read one tile ahead
+
+  // One half: weights of the logits sc, output += V^T P; NEXT: the logits of the half after it
+  // (operands in kf) meanwhile, and the request of the operands of the half after that.
+  auto step = [&](auto last_c, int half, v16f& sc, v16f& sn) {
+    constexpr bool LAST = decltype(last_c)::value;
+    u32x4 vf[2][CT];
+    if constexpr (LAST) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (acc_row(v, kh) > r) sc[v] = -INFINITY;
+    }
+    uint32_t pw[8];                                  // the weights, two to a word
+    float psum = 0.f;
+    const float nm = -m;
+    if constexpr (!LAST) sn = v16f{};
+#pragma unroll
+    for (int kc = 0; kc < T::NKC; ++kc) {
+      if constexpr (!LAST) mma_chunk<DT>(sn, kf.x[kc], qf[kc]);
+      if (kc >= VS && kc < VS + CT) v_read(half, 0, kc - VS, vf[0][kc - VS]);     // (into registers kf has left)
+#pragma unroll
+      for (int e = kc * EPS; e < (kc + 1) * EPS; e += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[e], a.scale_log2, nm));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], a.scale_log2, nm));
+        psum += p0;
+        psum += p1;
+        pw[e >> 1] = pack_pair<DT>(p0, p1);
+        asm volatile("" : "+v"(pw[e >> 1]));         // (packed here, not after the branch below)
+      }
+    }
+    // a sum out of range (the first half, where m is -inf; a logit far above m; a NaN)
+    if (__builtin_amdgcn_ballot_w64(!(psum < 16384.f))) {
+      float tmax = sc[0];
+#pragma unroll
+      for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, sc[v]);
+      tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+      const float m_new = fmaxf(m, tmax * a.scale_log2);
+      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+      l *= alpha;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[ct][i] *= alpha;
+      m = m_new;
+      psum = 0.f;
+#pragma unroll
+      for (int e = 0; e < 16; e += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[e], a.scale_log2, -m));      // (m is finite: key 0 is visible to every row)
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], a.scale_log2, -m));
+        psum += p0;
+        psum += p1;
+        pw[e >> 1] = pack_pair<DT>(p0, p1);
+      }
+    }
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) v_read(half, 1, ct, vf[1][ct]);
+    if constexpr (!LAST) k_read(half, kf);
+    u32x4 pb[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) { pb[s].x = pw[4 * s]; pb[s].y = pw[4 * s + 1]; pb[s].z = pw[4 * s + 2]; pb[s].w = pw[4 * s + 3]; }
+    l += psum;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) mma_chunk<DT>(oacc[ct], vf[s][ct], pb[s]);
+  };
+  // Tile t's barrier: K(t + 1) and V(t) are complete in LDS, and nobody still reads K(t)
+  // (its second half was requested before) or V(t - 1), whose buffers are filled next.
+  auto top = [&](int t) {
+    wait_all_loads();
+    __syncthreads();
+    if (t + 1 < ntiles) v_issue(t + 1);
+    if (t + 2 < ntiles) k_issue(t + 2);
+  };
+  int turn = TILE_B;
+  auto next_buffers = [&]() {                        // tile t + 1: V from the other buffer, K (of t + 2) too
+    kaddr -= turn;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) vaddr[ct] += turn;
+    turn = -turn;
+  };
+  const int t_full = nh > 0 ? (nh - 1) / 2 : 0;      // tiles both of whose halves lie before the wave's diagonal
+  int t = 0;
+  for (; t < t_full; ++t) {
+    top(t);
+    step(std::false_type{}, 0, s0, s1);
+    step(std::false_type{}, 1, s1, s0);
+    next_buffers();
+  }
+  if (nh > 0) {                                      // the tile of the diagonal (t < ntiles: the wave has rows)
+    top(t++);
+    if (nh & 1) {
+      step(std::true_type{}, 0, s0, s1);
+    } else {
+      step(std::false_type{}, 0, s0, s1);
+      step(std::true_type{}, 1, s1, s0);
+    }
+  }
+  for (; t < ntiles; ++t) top(t);                    // the other waves' tiles: their transfers and barriers
+
+  // ---- normalise and store: lane = row, accumulator v of tile ct = channel 32 ct + acc_row(v, kh) ----
+  const float l_tot = l + __shfl_xor(l, 32);
+  if (qpos < a.L) {
+    const float inv = 1.f / l_tot;
+    uint8_t* orow = reinterpret_cast<uint8_t*>(a.o) + ((int64_t)b * a.o_sB + (int64_t)hq * a.o_sH + (int64_t)qpos * a.o_sL) * 2;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+      for (int v4 = 0; v4 < 4; ++v4) {
+        const int c = 32 * ct + acc_row(4 * v4, kh);        // four consecutive channels
+        *reinterpret_cast<uint2*>(orow + c * 2) =
+            make_uint2(pack_pair<DT>(oacc[ct][4 * v4] * inv, oacc[ct][4 * v4 + 1] * inv), pack_pair<DT>(oacc[ct][4 * v4 + 2] * inv, oacc[ct][4 * v4 + 3] * inv));
       }
     if (a.lse && kh == 0) a.lse[((int64_t)b * a.Hq + hq) * a.L + qpos] = (m + log2f(l_tot)) * kLn2;
   }
@@ -306,9 +544,20 @@ __global__ void k_gather_lse(const float* __restrict__ lse, const int32_t* __res
 }
 
 template <int DT, int D>
-static int launch_prefill(const PrefillArgs& a, hipStream_t st) {
-  const int64_t grid = (int64_t)ceil_div(a.L, kPfRows) * a.Hq * a.B;
-  hipLaunchKernelGGL((k_prefill_attention<DT, D>), dim3((unsigned)grid), dim3(256), 0, st, a);
+static int launch_prefill(PrefillArgs a, hipStream_t st) {
+  // Eight waves per workgroup read a K and V tile once for 256 rows; four where that leaves
+  // the chip fewer than two workgroups a CU, whose lengths then cannot even out (16 heads of
+  // 4096 rows of 64 channels, 256 against 512 workgroups: 68 against 51 us; 32 heads of 128
+  // channels, 512 against 1024: 133 against 144 us).
+  const int64_t heads = (int64_t)a.B * a.Hq;
+  const bool wide = DT != ZC_F32 && ceil_div(a.L, 256) * heads >= 512;
+  const int rows = wide ? 256 : 128, slots = wide ? 32 : 64;       // workgroups an XCD holds at a time
+  const int nqb = ceil_div(a.L, rows);
+  a.group = a.G * ceil_div(2 * slots, nqb * a.G);
+  const dim3 grid((unsigned)(nqb * heads));
+  if constexpr (DT == ZC_F32) hipLaunchKernelGGL((k_prefill_attention<D>), grid, dim3(256), 0, st, a);
+  else if (wide) hipLaunchKernelGGL((k_prefill_attention16<DT, D, 8>), grid, dim3(512), 0, st, a);
+  else hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), grid, dim3(256), 0, st, a);
   ZC_LAUNCH_CHECK();
   return ZC_OK;
 }

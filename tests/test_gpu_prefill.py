@@ -101,3 +101,34 @@ def test_probe_saliency_from_the_prefill_normalisers():
     s1, _ = zb.zc_select_salient(one, w.k_salient)
     from tests.pipeline_check import check_index_sets
     check_index_sets(ref[0], s1[0].cpu().numpy(), w.k_salient, "split on one-sweep scores")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp16"])
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,rise", [
+    (1, 2, 1, 128, 1, 0.0), (1, 3, 3, 64, 31, 0.0), (1, 4, 2, 128, 33, 0.0), (1, 2, 2, 64, 64, 0.0), (1, 8, 2, 128, 65, 0.0),
+    (2, 12, 4, 128, 257, 0.0),              # heads that do not divide over the XCDs
+    (8, 64, 64, 64, 97, 0.0),               # 512 workgroups: eight waves each, fewer rows than waves
+    (4, 32, 8, 128, 1025, 0.0), (4, 32, 4, 64, 1057, 0.0),      # the same with many tiles, one row past a block and one wave more
+    (1, 4, 2, 128, 700, 40.0), (4, 32, 8, 128, 1025, 40.0),     # logits that climb by 2^40 and more: the reference of a row moves
+])
+def test_prefill_tiles_and_reference(dtype, B, Hq, Hkv, d, L, rise):
+    """Edges of row blocks, waves and key halves, and rows whose largest logit keeps growing."""
+    dt = {"bf16": torch.bfloat16, "fp16": torch.float16}[dtype]
+    g = torch.Generator().manual_seed(L + d + Hq)
+    Q = torch.randn(B, Hq, L, d, generator=g)
+    K = torch.randn(B, Hkv, L, d, generator=g)
+    V = torch.randn(B, Hkv, L, d, generator=g)
+    if rise:
+        Q[..., 0] = 4.0
+        K[..., 0] = torch.linspace(0, rise * d ** 0.5 / 4.0, L)
+    Q, K, V = Q.to(dt), K.to(dt), V.to(dt)
+    out, lse, _ = zb.zc_prefill_attention(Q.to(DEV), K.to(DEV), V.to(DEV))
+    G = Hq // Hkv
+    # each weight is rounded once to the type (unit u), and so is the result: both are at most u / 2 of max |V|
+    u = 2.0 ** (-8 if dtype == "bf16" else -11)
+    for b, h in {(0, 0), (B - 1, Hq - 1), (B // 2, Hq // 2)}:
+        O_o, lse_o = zo.prefill_attention(*(t.double().numpy() for t in (Q[b:b + 1, h:h + 1], K[b:b + 1, h // G:h // G + 1], V[b:b + 1, h // G:h // G + 1])))
+        vmax = float(V[b, h // G].abs().max())
+        assert np.abs(out[b, h].double().cpu().numpy() - O_o[0, 0]).max() <= u * vmax + 1e-5 * vmax
+        # fp32 sums of d products: a logit is off by about d 2^-24 of the sum of magnitudes
+        assert np.abs(lse[b, h].double().cpu().numpy() - lse_o[0, 0]).max() <= 1e-4 + 2e-5 * rise
