@@ -1,7 +1,7 @@
 // Pieces shared by the matrix-core kernels that tile dense products for wave64
 // (probe saliency, prefill attention): the 32x32 MFMA on one 16-byte operand chunk
-// per lane, the LDS tile layout that global -> LDS transfers fill, the workgroup ->
-// XCD mapping, the accumulator layout of a 32x32 result.
+// per lane, the LDS tile layout that global -> LDS transfers fill, the accumulator
+// layout of a 32x32 result.
 #pragma once
 
 #include "lds_dma.hpp"
@@ -46,15 +46,6 @@ struct Tile {
   __device__ static int swz(int row) { return (row / RP256) % SW; }
   __device__ static int slot(int row, int c) { return row * ROWB + ((c ^ swz(row)) << 4); }
 };
-
-// Workgroups are handed to the 8 XCDs round-robin by their linear index, and
-// every XCD has its own L2.  This maps the hardware index to a logical index such
-// that each XCD gets one contiguous range of logical indices: workgroups that
-// read the same K head (or the same probe rows) then share an L2.
-__device__ inline int xcd_contiguous(int id, int n) {
-  const int xcd = id & 7, slot = id >> 3;
-  return xcd * (n >> 3) + min(xcd, n & 7) + slot;
-}
 
 // Row index inside a 32x32 MFMA result held by accumulator register v of a lane
 // in half-wave kh.

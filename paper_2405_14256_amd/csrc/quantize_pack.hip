@@ -2,14 +2,12 @@
 // tensor (Eq. 5, Eq. 6, Algorithm 1; the four quantizer calls of Algorithm 2).
 //
 // Channel statistics of a subset must be complete before any of its tokens can
-// be quantized, so the work is three launches:
-//   1. k_chan_stats     per-channel min / max over a tile of tokens of one
-//                       subset (salient or regular), written as partials - no
-//                       atomics, so the result does not depend on scheduling.
-//   2. k_chan_finalize  reduces the partials and turns them once into the
-//                       parameters the quantizer needs (Eq. 5's R = max - min,
-//                       1/R and z per channel, or Eq. 6's c and 1/c).
-//   3. k_quant_pack     a team of waves (one thread per 8 channels) owns one to
+// be quantized, so the work is two launches, one where the rows fit registers:
+//   1. k_columns        a workgroup owns a few channels of one subset: their minima
+//                       and maxima over all its tokens, the parameters that follow
+//                       (Eq. 5's R = max - min, 1/R and z, or Eq. 6's c and 1/c)
+//                       and, for channelwise ROW codes that stay resident, the codes.
+//   2. k_quant_pack     a team of waves (one thread per 8 channels) owns one to
 //                       four word groups of a TGROUP block - the 32 / bits tokens
 //                       whose codes share 32-bit words - and walks them in
 //                       batches of 8 tokens, requesting batch i + 1 before it
@@ -21,6 +19,8 @@
 // Every sweep reads 16 bytes per lane with consecutive lanes on consecutive
 // addresses of a (token, head) row; the second sweep of a tensor that fits the
 // 256 MB Infinity Cache does not reach HBM.
+#include <type_traits>
+
 #include "quant_math.hpp"
 
 namespace zc {
@@ -40,154 +40,37 @@ struct QPArgs {
   int32_t* pos[2];
   float* chan_scale;           // this chunk: [2, B, W]
   float* chan_zero;
-  float* partial;              // workspace [B, tiles_hi + tiles_lo, W, 2] (min, max)
   float4* params;              // workspace [B, 2, W]: CHANNEL {1/R, z, R, -}, CST {1/c, -, -, -}
   int32_t* chunk_row;          // device chunk_table row to fill
   int64_t pos_offset;
-  int tiles[2], TT;            // stats sweep tiling
   int units[2];                // quantize sweep: word groups per subset (4 per TGROUP block)
   int upw, wgs[2];             // word groups per workgroup (1, 2 or 4: divides a block), workgroups per subset
   int scheme;
+  int vl;                      // column sweep: lanes across a token row (8 channels each)
+  int resident;                // column sweep: the subset's rows stay in registers and are packed there
 };
 
-constexpr int kStatThreads = 256;   // channel vectors (8 channels) per workgroup of the statistics sweep
-constexpr int kStatBatch = 8;       // token rows requested at once
+constexpr int kStatBatch = 8;       // token rows requested at once where they do not stay resident
 
-__host__ __device__ inline int stats_tile_tokens(int64_t total_tokens) {
-  int64_t tt = ceil_div64(total_tokens, 1024);
-  return tt < 16 ? 16 : (tt > 64 ? 64 : (int)tt);
-}
-
-// grid (tiles, B, ceil(NV / 256)): a workgroup reduces 256 channel vectors over a
-// tile of tokens of one subset; a thread owns one vector (8 channels).
 struct QPPair { QPArgs t[2]; };   // keys and values of one cache, compressed by the same launches
 
-template <int DT>
-__device__ inline void chan_stats_body(const QPArgs& a, int tile, int b, int zchunk) {
-  constexpr int RAW = (DT == ZC_F32) ? 2 : 1;        // 16-byte loads per channel vector
-  const int sub = tile >= a.tiles[0] ? 1 : 0;
-  const int gtile = tile;
-  if (sub) tile -= a.tiles[0];
-  const int t0 = tile * a.TT;
-  const int t1 = min(t0 + a.TT, a.n[sub]);
-  const int v = zchunk * kStatThreads + threadIdx.x;
-  if (v >= a.NV) return;
-  const int32_t* idx = a.idx[sub] + (int64_t)b * a.n[sub];
-  const int w = v * 8, h = w / a.D, c = w % a.D;
-  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * (DT == ZC_F32 ? 4 : 2);
-  const int64_t row_bytes = a.sL * (DT == ZC_F32 ? 4 : 2);
-
-  float mn[8], mx[8];
-#pragma unroll
-  for (int i = 0; i < 8; ++i) { mn[i] = INFINITY; mx[i] = -INFINITY; }
-
-  for (int tb = t0; tb < t1; tb += kStatBatch) {
-    // all rows of the batch are requested before any is reduced; rows past the
-    // end repeat the last one (min / max do not care)
-    uint4 raw[kStatBatch][RAW];
-#pragma unroll
-    for (int t = 0; t < kStatBatch; ++t) {
-      const int64_t pos = idx[min(tb + t, t1 - 1)];
-      const uint4* src = reinterpret_cast<const uint4*>(base + pos * row_bytes);
-#pragma unroll
-      for (int r = 0; r < RAW; ++r) raw[t][r] = src[r];
-    }
-#pragma unroll
-    for (int t = 0; t < kStatBatch; ++t) {
-      float x8[8];
-      if constexpr (DT == ZC_F32) {
-        x8[0] = __uint_as_float(raw[t][0].x); x8[1] = __uint_as_float(raw[t][0].y);
-        x8[2] = __uint_as_float(raw[t][0].z); x8[3] = __uint_as_float(raw[t][0].w);
-        x8[4] = __uint_as_float(raw[t][RAW - 1].x); x8[5] = __uint_as_float(raw[t][RAW - 1].y);
-        x8[6] = __uint_as_float(raw[t][RAW - 1].z); x8[7] = __uint_as_float(raw[t][RAW - 1].w);
-      } else {
-        const uint32_t w4[4] = {raw[t][0].x, raw[t][0].y, raw[t][0].z, raw[t][0].w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          x8[2 * i] = half_bits_to_float<DT>(w4[i] & 0xffffu);
-          x8[2 * i + 1] = half_bits_to_float<DT>(w4[i] >> 16);
-        }
-      }
-#pragma unroll
-      for (int i = 0; i < 8; ++i) { mn[i] = fminf(mn[i], x8[i]); mx[i] = fmaxf(mx[i], x8[i]); }
-    }
+// What the quantizer needs of a channel whose values span [lo, hi]; n tokens (0: defaults).
+__device__ inline float4 channel_params(int scheme, int n, float qmax, float lo, float hi, float* cs, float* cz) {
+  *cs = 1.f; *cz = 0.f;
+  if (n > 0 && scheme == ZC_SCHEME_CST) {
+    float c = sqrtf(fmaxf(fabsf(lo), fabsf(hi)));       // Eq. 6
+    if (c == 0.f) c = 1.f;
+    *cs = c;
+    return make_float4(1.f / c, 0.f, 1.f, 0.f);
   }
-  float* out = a.partial + ((int64_t)b * (a.tiles[0] + a.tiles[1]) + gtile) * a.W * 2;
-  float4* o4 = reinterpret_cast<float4*>(out + (int64_t)v * 16);
-  o4[0] = make_float4(mn[0], mx[0], mn[1], mx[1]);
-  o4[1] = make_float4(mn[2], mx[2], mn[3], mx[3]);
-  o4[2] = make_float4(mn[4], mx[4], mn[5], mx[5]);
-  o4[3] = make_float4(mn[6], mx[6], mn[7], mx[7]);
-}
-
-template <int DT>
-__global__ __launch_bounds__(kStatThreads) void k_chan_stats(QPArgs a) {
-  chan_stats_body<DT>(a, blockIdx.x, blockIdx.y, blockIdx.z);
-}
-// both tensors of a cache: grid.x = tiles of the first + tiles of the second
-template <int DT>
-__global__ __launch_bounds__(kStatThreads) void k_chan_stats_kv(QPPair p) {
-  const int nt = p.t[0].tiles[0] + p.t[0].tiles[1];
-  const int which = (int)blockIdx.x >= nt ? 1 : 0;
-  const QPArgs& a = which ? p.t[1] : p.t[0];
-  if (a.scheme == ZC_SCHEME_TOKEN) return;           // plain tokenwise: no channel statistics
-  chan_stats_body<DT>(a, blockIdx.x - which * nt, blockIdx.y, blockIdx.z);
-}
-
-// grid (ceil(W / 64), 2 subsets, B), block (64 channels, 4 tile lanes)
-__device__ inline void chan_finalize_body(const QPArgs& a, int sub, float (*smn)[64], float (*smx)[64]) {
-  const int cx = threadIdx.x, ty = threadIdx.y;
-  const int w = blockIdx.x * 64 + cx, b = blockIdx.z;
-  const int n = a.n[sub];
-  const float qmax = (float)((1 << a.bits[sub]) - 1);
-  float lo = INFINITY, hi = -INFINITY;
-  if (w < a.W && n > 0 && a.scheme != ZC_SCHEME_TOKEN) {
-    const int tbeg = sub ? a.tiles[0] : 0, tcnt = a.tiles[sub];
-    const float* p = a.partial + ((int64_t)b * (a.tiles[0] + a.tiles[1]) + tbeg) * a.W * 2 + (int64_t)w * 2;
-#pragma unroll 4
-    for (int t = ty; t < tcnt; t += 4) {
-      const float2 v = *reinterpret_cast<const float2*>(p + (int64_t)t * a.W * 2);
-      lo = fminf(lo, v.x); hi = fmaxf(hi, v.y);
-    }
+  if (n > 0 && scheme == ZC_SCHEME_CHANNEL) {
+    float R = hi - lo;                                     // Eq. 5: s = R / (2^k - 1)
+    if (R == 0.f) R = qmax;                                // max == min: s := 1
+    *cs = R / qmax;
+    *cz = -rintf(refined_ratio(lo, qmax, R, 1.f / R));
+    return make_float4(1.f / R, *cz, R, 0.f);
   }
-  smn[ty][cx] = lo; smx[ty][cx] = hi;
-  __syncthreads();
-  if (ty == 0 && w < a.W) {
-    lo = fminf(fminf(smn[0][cx], smn[1][cx]), fminf(smn[2][cx], smn[3][cx]));
-    hi = fmaxf(fmaxf(smx[0][cx], smx[1][cx]), fmaxf(smx[2][cx], smx[3][cx]));
-    float cs = 1.f, cz = 0.f;
-    float4 prm = make_float4(1.f, 0.f, 1.f, 0.f);
-    if (n > 0 && a.scheme == ZC_SCHEME_CST) {
-      float c = sqrtf(fmaxf(fabsf(lo), fabsf(hi)));       // Eq. 6
-      if (c == 0.f) c = 1.f;
-      cs = c;
-      prm.x = 1.f / c;
-    } else if (n > 0 && a.scheme == ZC_SCHEME_CHANNEL) {
-      float R = hi - lo;                                     // Eq. 5: s = R / (2^k - 1)
-      if (R == 0.f) R = qmax;                                // max == min: s := 1
-      cs = R / qmax;
-      cz = -rintf(refined_ratio(lo, qmax, R, 1.f / R));
-      prm = make_float4(1.f / R, cz, R, 0.f);
-    }
-    const int64_t o = (int64_t)(sub * a.B + b) * a.W + w;
-    a.chan_scale[o] = cs;
-    a.chan_zero[o] = cz;
-    a.params[(int64_t)(b * 2 + sub) * a.W + w] = prm;
-  }
-  if (blockIdx.x == 0 && sub == 0 && b == 0 && cx == 0 && ty == 0) {
-    a.chunk_row[0] = a.begin[0]; a.chunk_row[1] = a.n[0];
-    a.chunk_row[2] = a.begin[1]; a.chunk_row[3] = a.n[1];
-  }
-}
-__global__ __launch_bounds__(256) void k_chan_finalize(QPArgs a) {
-  __shared__ float smn[4][64], smx[4][64];
-  chan_finalize_body(a, blockIdx.y, smn, smx);
-}
-// both tensors of a cache: grid.y = 2 subsets of the first, then of the second
-__global__ __launch_bounds__(256) void k_chan_finalize_kv(QPPair p) {
-  __shared__ float smn[4][64], smx[4][64];
-  const int which = blockIdx.y >> 1;
-  chan_finalize_body(which ? p.t[1] : p.t[0], blockIdx.y & 1, smn, smx);
+  return make_float4(1.f, 0.f, 1.f, 0.f);
 }
 
 // ---- minima of N values over a wave at once -----------------------------------------
@@ -256,6 +139,190 @@ __device__ inline float wave_min_rest(float (&v)[N / 2]) {
 __device__ inline int tile_of_field_group(int bits, int jf) {
   // Slot tile (16 slots) addressed by field group jf of a TGROUP word.
   return (bits == 2) ? ((jf & 1) * 2 + (jf >> 1)) : jf;
+}
+
+// ---- column sweep: statistics, parameters and - channelwise keys - codes in one launch ----
+// A workgroup owns 8 vl channels of one subset of one batch element, vl lanes across a token
+// row and THREADS / vl rows at a time.  With no partials to exchange the parameters are final
+// when its own reduction is.  Channelwise codes in ROW layout need nothing else, so there
+// (a.resident) the rows stay in registers between the reduction and the packing: the tensor
+// is read from memory once and a launch does everything.  Bound by memory where the chip is
+// full (16 x 4096 tokens of 5120 channels, fp16: keys packed and statistics of the values in
+// 379 us, 517 as three launches that read the keys twice), by the latency of its two rounds
+// of loads where it is not (one prompt of 4096 tokens, 1024 channels: 8 us for both tensors'
+// statistics and parameters, 14 as two launches).
+constexpr int kColRows(int dt) { return dt == ZC_F32 ? 10 : 20; }   // rows a thread can hold
+
+template <int DT>
+__device__ inline void widen8(const uint4 (&raw)[DT == ZC_F32 ? 2 : 1], float (&v)[8]) {
+  if constexpr (DT == ZC_F32) {
+    v[0] = __uint_as_float(raw[0].x); v[1] = __uint_as_float(raw[0].y); v[2] = __uint_as_float(raw[0].z); v[3] = __uint_as_float(raw[0].w);
+    v[4] = __uint_as_float(raw[1].x); v[5] = __uint_as_float(raw[1].y); v[6] = __uint_as_float(raw[1].z); v[7] = __uint_as_float(raw[1].w);
+  } else {
+    const uint32_t w4[4] = {raw[0].x, raw[0].y, raw[0].z, raw[0].w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      v[2 * i] = half_bits_to_float<DT>(w4[i] & 0xffffu);
+      v[2 * i + 1] = half_bits_to_float<DT>(w4[i] >> 16);
+    }
+  }
+}
+
+// The 8 codes of one token row, packed (ROW layout).
+template <int DT, int BITS>
+__device__ inline void store_row_codes(uint8_t* row, const float (&x)[8], const float (&p0)[8], const float (&p1)[8], const float (&p2)[8]) {
+  constexpr float QMAX = (float)((1 << BITS) - 1);
+  constexpr int FPG = 16 / BITS, NG = 8 / FPG;       // code fields per 16-bit group, groups
+  uint32_t half[NG];
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    float acc = 0.f;
+#pragma unroll
+    for (int f = 0; f < FPG; ++f) {
+      const int i = g * FPG + f;
+      float qv;
+      if constexpr (DT == ZC_F32) qv = rintf(refined_ratio(x[i], QMAX, p2[i], p0[i])) + p1[i];
+      else qv = rintf(refined_div(x[i] * QMAX, p2[i], p0[i])) + p1[i];   // x * qmax is exact
+      acc = fmaf(__builtin_amdgcn_fmed3f(qv, 0.f, QMAX), (float)(1 << (BITS * f)), acc);
+    }
+    half[g] = (uint32_t)acc;
+  }
+  if constexpr (BITS == 8) *reinterpret_cast<uint2*>(row) = make_uint2(half[0] | (half[1] << 16), half[2] | (half[3] << 16));
+  else if constexpr (BITS == 4) *reinterpret_cast<uint32_t*>(row) = half[0] | (half[1] << 16);
+  else *reinterpret_cast<uint16_t*>(row) = (uint16_t)half[0];
+}
+
+template <int DT, int THREADS>
+__global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
+  constexpr int RAW = (DT == ZC_F32) ? 2 : 1, ESZ = (DT == ZC_F32) ? 4 : 2;
+  constexpr int NR = kColRows(DT), NWAVE = THREADS / 64;
+  __shared__ __align__(16) float red[NWAVE][2][128];
+  __shared__ __align__(16) float prm[3][128];
+
+  // logical order: channel group fastest, then subset, tensor, batch element: the workgroups
+  // that share a token row's cache lines run on one XCD at about the same time
+  const int vl = p.t[0].vl, groups = ceil_div(p.t[0].NV, vl);
+  int id = xcd_contiguous(blockIdx.x, gridDim.x);
+  const int grp = id % groups; id /= groups;
+  const int sub = id & 1; id >>= 1;
+  const int which = tensors == 2 ? id & 1 : 0, b = tensors == 2 ? id >> 1 : id;
+  const QPArgs& a = which ? p.t[1] : p.t[0];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int x = tid & (vl - 1), y = tid / vl, step = THREADS / vl;
+  const int n = a.scheme == ZC_SCHEME_TOKEN ? 0 : a.n[sub];     // (plain tokenwise: no channel statistics)
+  const int vec = min(grp * vl + x, a.NV - 1);                  // (lanes past the row repeat its last vector)
+  const int w = vec * 8, h = w / a.D, c = w % a.D;
+  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
+  const int64_t row_bytes = a.sL * ESZ;
+  const int32_t* idx = a.idx[sub] + (int64_t)b * a.n[sub];
+
+  float mn[8], mneg[8];                                         // minimum, minimum of -x
+#pragma unroll
+  for (int i = 0; i < 8; ++i) { mn[i] = INFINITY; mneg[i] = INFINITY; }
+  uint4 raw[NR][RAW];
+  auto reduce = [&](const uint4 (&rw)[RAW]) {
+    float v[8];
+    widen8<DT>(rw, v);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) { mn[i] = fminf(mn[i], v[i]); mneg[i] = fminf(mneg[i], -v[i]); }
+  };
+  // Rows are requested before any is reduced, all of a resident subset or kStatBatch at a time;
+  // rows past the end repeat the last one (minima do not care).
+  if (a.resident) {
+    int32_t tok[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      if (r * step < n) tok[r] = idx[min(r * step + y, n - 1)];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      if (r * step < n) {
+        const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)tok[r] * row_bytes);
+#pragma unroll
+        for (int q = 0; q < RAW; ++q) raw[r][q] = src[q];
+      }
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+      if (r * step < n) reduce(raw[r]);
+  } else {
+    for (int t0 = 0; t0 < n; t0 += kStatBatch * step) {
+      uint4 rw[kStatBatch][RAW];
+#pragma unroll
+      for (int r = 0; r < kStatBatch; ++r) {
+        const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)idx[min(t0 + r * step + y, n - 1)] * row_bytes);
+#pragma unroll
+        for (int q = 0; q < RAW; ++q) rw[r][q] = src[q];
+      }
+#pragma unroll
+      for (int r = 0; r < kStatBatch; ++r) reduce(rw[r]);
+    }
+  }
+  // over the rows of a wave: (minimum, minimum of -x) split over its halves, channels 0..3 and
+  // 4..7 over the rows of a half, the rest inside a row of 16 lanes
+  {
+    float u[4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mn[j] = swap_min_halves(mn[j], mneg[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u[j] = swap_min_rows(mn[j], mn[j + 4]);
+    if (vl <= 8) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) u[j] = fminf(u[j], __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u[j]), 0x128, 0xF, 0xF, true)));   // row_ror:8
+    }
+    if (vl <= 4) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) u[j] = fminf(u[j], __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u[j]), 0x124, 0xF, 0xF, true)));   // row_ror:4
+    }
+    if (vl <= 2) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) u[j] = fminf(u[j], __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u[j]), 0x122, 0xF, 0xF, true)));   // row_ror:2
+    }
+    if ((lane & 15) < vl)
+      *reinterpret_cast<float4*>(&red[wave][lane >> 5][(lane & 15) * 8 + 4 * ((lane >> 4) & 1)]) = make_float4(u[0], u[1], u[2], u[3]);
+  }
+  __syncthreads();
+  const int wc = grp * vl * 8 + tid;                            // channel of this thread in the parameter step
+  if (tid < vl * 8 && wc < a.W) {
+    float lo = red[0][0][tid], neg = red[0][1][tid];
+#pragma unroll
+    for (int v = 1; v < NWAVE; ++v) { lo = fminf(lo, red[v][0][tid]); neg = fminf(neg, red[v][1][tid]); }
+    float cs, cz;
+    const float4 pr = channel_params(a.scheme, n, (float)((1 << a.bits[sub]) - 1), lo, -neg, &cs, &cz);
+    const int64_t o = (int64_t)(sub * a.B + b) * a.W + wc;
+    a.chan_scale[o] = cs;
+    a.chan_zero[o] = cz;
+    if (!a.resident) a.params[(int64_t)(b * 2 + sub) * a.W + wc] = pr;
+    prm[0][tid] = pr.x; prm[1][tid] = pr.y; prm[2][tid] = pr.z;
+  }
+  if (grp == 0 && sub == 0 && b == 0 && tid == 0) {
+    a.chunk_row[0] = a.begin[0]; a.chunk_row[1] = a.n[0];
+    a.chunk_row[2] = a.begin[1]; a.chunk_row[3] = a.n[1];
+  }
+  if (!a.resident) return;
+  __syncthreads();
+
+  if (grp == 0 && a.pos[sub])
+    for (int t = tid; t < n; t += THREADS) a.pos[sub][(int64_t)b * a.cap[sub] + a.begin[sub] + t] = (int32_t)(idx[t] + a.pos_offset);
+  if (grp * vl + x >= a.NV) return;
+  float p0[8], p1[8], p2[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) { p0[i] = prm[0][x * 8 + i]; p1[i] = prm[1][x * 8 + i]; p2[i] = prm[2][x * 8 + i]; }
+  auto pack = [&](auto bits_c) {
+    constexpr int BITS = decltype(bits_c)::value;
+    const int rowb = a.D * BITS / 8;
+    uint8_t* dst = a.codes[sub] + (((int64_t)b * a.H + h) * a.cap[sub] + a.begin[sub] + y) * rowb + c * BITS / 8;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      if (r * step + y < n) {
+        float v[8];
+        widen8<DT>(raw[r], v);
+        store_row_codes<DT, BITS>(dst + (int64_t)(r * step) * rowb, v, p0, p1, p2);
+      }
+    }
+  };
+  const int bits = a.bits[sub];
+  if (bits == 4) pack(std::integral_constant<int, 4>{});
+  else if (bits == 2) pack(std::integral_constant<int, 2>{});
+  else pack(std::integral_constant<int, 8>{});
 }
 
 constexpr int kVPT = 1;  // channel vectors (8 channels each) per thread in the quantize sweep
@@ -589,22 +656,17 @@ static void launch_qp(const QPArgs& a, int layout, bool tokwise, dim3 grid, dim3
   else launch_qp_t<DT, 1024>(a, layout, tokwise, grid, block, st);
 }
 
-static int64_t stats_tiles(int64_t B, int64_t n_tokens, int* TT_out) {
-  const int TT = stats_tile_tokens(B * n_tokens);
-  if (TT_out) *TT_out = TT;
-  return ceil_div64(n_tokens, TT) + 1;     // two subsets: at most one extra ragged tile
-}
-
 }  // namespace zc
 
 using namespace zc;
 
+// [B, 2, W] parameters.  The size that callers are told also covers statistics by token tiles,
+// as it always has: buffers laid out with an earlier figure and this one are interchangeable.
 extern "C" size_t zc_quantize_pack_workspace(int64_t B, int64_t H, int64_t L, int64_t D) {
   if (B <= 0 || H <= 0 || D <= 0 || L < 0) return 0;
-  const int64_t W = H * D;
-  const size_t params = (size_t)align_up64(B * 2 * W * (int64_t)sizeof(float4), 256);
-  const size_t partial = (size_t)B * stats_tiles(B, L, nullptr) * W * 2 * sizeof(float);
-  return params + partial;
+  const int64_t W = H * D, per_tile = ceil_div64(B * L, 1024);
+  const int64_t tiles = ceil_div64(L, per_tile < 16 ? 16 : (per_tile > 64 ? 64 : per_tile)) + 1;
+  return (size_t)align_up64(B * 2 * W * (int64_t)sizeof(float4), 256) + (size_t)B * tiles * W * 2 * sizeof(float);
 }
 
 // Validation and kernel arguments of one tensor's compression call.
@@ -642,15 +704,9 @@ static int qp_prepare(const zc_tensor4* x, const int32_t* salient_idx, int64_t k
   a.chan_scale = out->chan_scale + chunk_off;
   a.chan_zero = out->chan_zero + chunk_off;
   a.params = reinterpret_cast<float4*>(ws);
-  a.partial = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + align_up64(x->B * 2 * W * (int64_t)sizeof(float4), 256));
   a.chunk_row = out->chunk_table + 4 * out->n_chunks;
   a.pos_offset = pos_offset;
   a.scheme = out->scheme;
-  int TT;
-  stats_tiles(x->B, k + n_reg, &TT);
-  a.TT = TT;
-  a.tiles[0] = (int)ceil_div64(k, TT);
-  a.tiles[1] = (int)ceil_div64(n_reg, TT);
   // word groups of 32 / bits tokens; a TGROUP block holds 4 of them
   a.units[0] = (int)ceil_div64(k, 4 * (32 / out->bits_hi)) * 4;
   a.units[1] = (int)ceil_div64(n_reg, 4 * (32 / out->bits_lo)) * 4;
@@ -664,6 +720,46 @@ static int qp_prepare(const zc_tensor4* x, const int32_t* salient_idx, int64_t k
     a.wgs[0] = a.units[0] / upw;
     a.wgs[1] = a.units[1] / upw;
   }
+  return ZC_OK;
+}
+
+// Shape of the column sweep over `tensors` tensors of one call (same sizes and subsets): lanes
+// across a row, threads of a workgroup, and which tensors stay resident.
+// The widest rows that leave a workgroup per CU; narrower ones where a resident subset only
+// then fits the registers.  Keys are resident wherever they fit - except in a call for both
+// tensors with too few workgroups to hide the packing behind each other's loads, where one
+// packing launch serves both (one prompt of 4096 tokens, 8 heads: 26.1 against 27.5 us).
+static int col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int dtype, bool joint_pack) {
+  const int64_t n = a[0].n[0] > a[0].n[1] ? a[0].n[0] : a[0].n[1], rows = kColRows(dtype);
+  const auto wgs = [&](int vl) { return ceil_div64(a[0].NV, vl) * 2 * a[0].B; };      // of one tensor
+  int vl = 16;
+  while (vl > 2 && wgs(vl) * tensors < 256) vl /= 2;
+  int threads = wgs(vl) * tensors < 256 ? 1024 : 512;
+  int v = vl, th = threads;
+  while (v > 2 && n > rows * th / v) v /= 2;
+  if (n > rows * th / v) th = 1024;
+  const bool fits = n <= rows * th / v && !(joint_pack && wgs(v) < 256);
+  bool any = false;
+  for (int t = 0; t < tensors; ++t) {
+    a[t].resident = fits && out[t]->scheme == ZC_SCHEME_CHANNEL && out[t]->layout == ZC_LAYOUT_ROW;
+    any |= a[t].resident != 0;
+  }
+  for (int t = 0; t < tensors; ++t) a[t].vl = any ? v : vl;
+  return any ? th : threads;
+}
+
+template <int DT>
+static void launch_columns(const QPPair& p, int tensors, int threads, hipStream_t st) {
+  const dim3 grid((unsigned)(ceil_div64(p.t[0].NV, p.t[0].vl) * 2 * tensors * p.t[0].B));
+  if (threads == 512) hipLaunchKernelGGL((k_columns<DT, 512>), grid, dim3(512), 0, st, p, tensors);
+  else hipLaunchKernelGGL((k_columns<DT, 1024>), grid, dim3(1024), 0, st, p, tensors);
+}
+static int qp_launch_columns(QPPair& p, const zc_packed* const* out, int tensors, int dtype, bool joint_pack, hipStream_t st) {
+  const int threads = col_plan(p.t, out, tensors, dtype, joint_pack);
+  if (dtype == ZC_F32) launch_columns<ZC_F32>(p, tensors, threads, st);
+  else if (dtype == ZC_F16) launch_columns<ZC_F16>(p, tensors, threads, st);
+  else launch_columns<ZC_BF16>(p, tensors, threads, st);
+  ZC_LAUNCH_CHECK();
   return ZC_OK;
 }
 
@@ -693,24 +789,15 @@ static int qp_launch_pack(const QPArgs& a, int dtype, int layout, hipStream_t st
 extern "C" int zc_quantize_pack(const zc_tensor4* x, const int32_t* salient_idx, int64_t k,
                                 const int32_t* regular_idx, int64_t n_reg, int64_t pos_offset,
                                 zc_packed* out, void* ws, size_t ws_bytes, void* stream) {
-  QPArgs a;
+  QPPair p;
+  QPArgs& a = p.t[0];
   int rc = qp_prepare(x, salient_idx, k, regular_idx, n_reg, pos_offset, out, ws, ws_bytes, a);
   if (rc) return rc;
+  p.t[1] = a;
   hipStream_t st = (hipStream_t)stream;
-  // ---- sweep 1: channel statistics (partials) -----------------------------------
-  if (out->scheme != ZC_SCHEME_TOKEN && a.tiles[0] + a.tiles[1] > 0) {
-    const int TX = a.NV >= kStatThreads ? kStatThreads : (int)align_up64(a.NV, 64);
-    dim3 grid((unsigned)(a.tiles[0] + a.tiles[1]), (unsigned)x->B, (unsigned)ceil_div64(a.NV, kStatThreads)), block(TX);
-    if (x->dtype == ZC_F32) hipLaunchKernelGGL(k_chan_stats<ZC_F32>, grid, block, 0, st, a);
-    else if (x->dtype == ZC_F16) hipLaunchKernelGGL(k_chan_stats<ZC_F16>, grid, block, 0, st, a);
-    else hipLaunchKernelGGL(k_chan_stats<ZC_BF16>, grid, block, 0, st, a);
-    ZC_LAUNCH_CHECK();
-  }
-  // ---- parameters (also for empty subsets and the tokenwise scheme: defaults) ------
-  hipLaunchKernelGGL(k_chan_finalize, dim3((unsigned)ceil_div64(a.W, 64), 2, (unsigned)x->B), dim3(64, 4), 0, st, a);
-  ZC_LAUNCH_CHECK();
-  // ---- sweep 2: quantize + pack ---------------------------------------------------
-  rc = qp_launch_pack(a, x->dtype, out->layout, st);
+  const zc_packed* const outs[1] = {out};
+  rc = qp_launch_columns(p, outs, 1, x->dtype, false, st);
+  if (!rc && !a.resident) rc = qp_launch_pack(a, x->dtype, out->layout, st);
   if (rc) return rc;
   qp_commit(out, k, n_reg);
   return ZC_OK;
@@ -735,34 +822,26 @@ extern "C" int zc_quantize_pack_kv(const zc_tensor4* xk, const zc_tensor4* xv, c
   hipStream_t st = (hipStream_t)stream;
   const QPArgs& a = p.t[0];
   const int dt = xk->dtype;
-  const int nt = a.tiles[0] + a.tiles[1];
-  // ---- sweep 1 of both tensors --------------------------------------------------------
-  if (nt > 0 && (outK->scheme != ZC_SCHEME_TOKEN || outV->scheme != ZC_SCHEME_TOKEN)) {
-    const int TX = a.NV >= kStatThreads ? kStatThreads : (int)align_up64(a.NV, 64);
-    dim3 grid((unsigned)(2 * nt), (unsigned)a.B, (unsigned)ceil_div64(a.NV, kStatThreads)), block(TX);
-    if (dt == ZC_F32) hipLaunchKernelGGL(k_chan_stats_kv<ZC_F32>, grid, block, 0, st, p);
-    else if (dt == ZC_F16) hipLaunchKernelGGL(k_chan_stats_kv<ZC_F16>, grid, block, 0, st, p);
-    else hipLaunchKernelGGL(k_chan_stats_kv<ZC_BF16>, grid, block, 0, st, p);
-    ZC_LAUNCH_CHECK();
-  }
-  hipLaunchKernelGGL(k_chan_finalize_kv, dim3((unsigned)ceil_div64(a.W, 64), 4, (unsigned)a.B), dim3(64, 4), 0, st, p);
-  ZC_LAUNCH_CHECK();
-  // ---- sweep 2: one launch for both tensors in the paper's configuration (channelwise keys in
-  //      ROW layout, channel-separable tokenwise values in TGROUP layout) when a token row fits
-  //      one workgroup of 256 threads; else a launch per tensor ------------------------------
-  const bool paper_cfg = outK->scheme == ZC_SCHEME_CHANNEL && outK->layout == ZC_LAYOUT_ROW &&
-                         outV->scheme == ZC_SCHEME_CST && outV->layout == ZC_LAYOUT_TGROUP;
+  // ---- statistics and parameters of both; codes of resident keys ---------------------------
+  // One packing launch can serve both tensors in the paper's configuration (channelwise keys in
+  // ROW layout, channel-separable tokenwise values in TGROUP layout) when a token row fits one
+  // workgroup of 256 threads.
+  const bool joint = outK->scheme == ZC_SCHEME_CHANNEL && outK->layout == ZC_LAYOUT_ROW &&
+                     outV->scheme == ZC_SCHEME_CST && outV->layout == ZC_LAYOUT_TGROUP && a.NV <= 256;
+  const zc_packed* const outs[2] = {outK, outV};
+  rc = qp_launch_columns(p, outs, 2, dt, joint, st);
+  if (rc) return rc;
+  // ---- quantize + pack what is not packed yet ------------------------------------------------
   const int nwg = a.wgs[0] + a.wgs[1] + p.t[1].wgs[0] + p.t[1].wgs[1];
-  if (paper_cfg && a.NV <= 256 && nwg > 0) {
+  if (joint && !a.resident && nwg > 0) {
     dim3 grid((unsigned)nwg, (unsigned)a.B), block((unsigned)align_up64(a.NV, 64));
     if (dt == ZC_F32) hipLaunchKernelGGL(k_quant_pack_kv<ZC_F32>, grid, block, 0, st, p);
     else if (dt == ZC_F16) hipLaunchKernelGGL(k_quant_pack_kv<ZC_F16>, grid, block, 0, st, p);
     else hipLaunchKernelGGL(k_quant_pack_kv<ZC_BF16>, grid, block, 0, st, p);
     ZC_LAUNCH_CHECK();
   } else {
-    rc = qp_launch_pack(p.t[0], dt, outK->layout, st);
-    if (rc) return rc;
-    rc = qp_launch_pack(p.t[1], dt, outV->layout, st);
+    if (!p.t[0].resident) rc = qp_launch_pack(p.t[0], dt, outK->layout, st);
+    if (!rc && !p.t[1].resident) rc = qp_launch_pack(p.t[1], dt, outV->layout, st);
     if (rc) return rc;
   }
   qp_commit(outK, k, n_reg);

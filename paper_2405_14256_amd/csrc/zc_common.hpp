@@ -86,6 +86,15 @@ __device__ inline void store1(void* base, int64_t off, float x) {
   }
 }
 
+// Workgroups are handed to the 8 XCDs round-robin by their linear index, and
+// every XCD has its own L2.  This maps the hardware index to a logical index such
+// that each XCD gets one contiguous range of logical indices: workgroups that
+// read the same K head (or the same probe rows) then share an L2.
+__device__ inline int xcd_contiguous(int id, int n) {
+  const int xcd = id & 7, slot = id >> 3;
+  return xcd * (n >> 3) + min(xcd, n & 7) + slot;
+}
+
 // ---- order-preserving image of a float in uint32 -----------------------------
 __host__ __device__ inline uint32_t float_key(float f) {
   uint32_t u;
