@@ -43,6 +43,7 @@ struct ProbeArgs {
   float2* lse_part;      // [B, Hq, P, nsplit] (running maximum in log2 units, sum) when nsplit > 1
   int nsplit;            // column ranges a row block's sweep 1 is split into
   float* per_head;       // [B, Hq, Lk]
+  int small;             // 1: few probe rows, sweep 2 and the mean in one launch
   int normalize;         // 1: divide a column's sum by the number of probes that see it (Eq. 8); 0: Eq. 7
 };
 
@@ -406,6 +407,78 @@ __global__ __launch_bounds__(256) void k_probe_mean(const float* __restrict__ pe
   if (gy == 0 && i < Lk) scores[(int64_t)b * Lk + i] = (((part[0][cx] + part[1][cx]) + part[2][cx]) + part[3][cx]) / (float)Hq;
 }
 
+// ---- few probe rows ----------------------------------------------------------------------
+// Sweep 2 and the mean over heads in one launch: a workgroup owns 32 columns of a batch element
+// for all heads, a wave a run of consecutive heads; rows and columns go straight from memory to
+// operand registers (each is used once, LDS would only add a trip).  Bound by what the loads of
+// one CU bring in, 32 cache lines an instruction: 8 heads of 64 channels, 256 tokens, 26 rows,
+// fp32: 8 us, 11 as two launches with a 64-row tile per head.
+constexpr int kSmallRows = 32;        // most probe rows
+constexpr int kSmallTable = 4096;     // most log-sum-exps of a batch element (heads x rows)
+constexpr int small_threads(int dt, int d) { return dt == ZC_F32 && d == 128 ? 512 : 1024; }
+
+template <int DT, int D>
+__global__ __launch_bounds__(small_threads(DT, D)) void k_probe_small(ProbeArgs a, float* __restrict__ scores) {
+  using T = Tile<DT, D>;
+  constexpr int NT = small_threads(DT, D), NW = NT / 64;
+  __shared__ float slse[kSmallTable];
+  __shared__ int spos[kSmallRows], srow[kSmallRows];
+  __shared__ float part[NW][32];
+  const int b = blockIdx.y, col0 = blockIdx.x * 32;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int ntab = a.Hq * a.P;
+  const float* lse_src = (a.lse_in ? a.lse_in : a.lse2) + (int64_t)b * ntab;
+  const float unit = a.lse_in ? kLog2e : 1.f;        // an external log-sum-exp is in natural units
+  for (int i = tid; i < ntab; i += NT) slse[i] = lse_src[i] * unit;
+  if (tid < a.P) {
+    const int pos = a.probe_pos[tid];
+    spos[tid] = pos;
+    srow[tid] = a.probe_rows ? a.probe_rows[tid] : pos;
+  }
+  __syncthreads();
+
+  const uint32_t k_rowb = (uint32_t)(a.k_sL * T::EB), q_rowb = (uint32_t)(a.q_sL * T::EB);
+  const int col = col0 + r;
+  const int koff = col < a.Lk ? (int)((uint32_t)col * k_rowb) + kh * 16 : kOutOfRange;     // (columns past the end: zeros)
+  float sum = 0.f;
+  // consecutive heads to a wave: one load of K serves those that share it
+  const int per = ceil_div(a.Hq, NW), h_end = min((w + 1) * per, a.Hq);
+  u32x4 kf[T::NKC];
+  for (int h = w * per; h < h_end; ++h) {
+    const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)h * a.q_sH) * T::EB;
+    const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)(h / a.G) * a.k_sH) * T::EB;
+    const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.Lq - 1) * q_rowb + T::ROWB, kBufFlags);
+    const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.Lk - 1) * k_rowb + T::ROWB, kBufFlags);
+    if (h == w * per || h % a.G == 0) {
+#pragma unroll
+      for (int kc = 0; kc < T::NKC; ++kc) kf[kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_k, koff + kc * 32, 0, 0);
+    }
+    const int qoff = r < a.P ? (int)((uint32_t)srow[r] * q_rowb) + kh * 16 : kOutOfRange;
+    v16f acc = {};
+#pragma unroll
+    for (int kc = 0; kc < T::NKC; ++kc)
+      mma_chunk<DT>(acc, __builtin_amdgcn_raw_buffer_load_b128(rs_q, qoff + kc * 32, 0, 0), kf[kc]);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int p = acc_row(v, kh), pc = min(p, a.P - 1);
+      const float e = __builtin_amdgcn_exp2f(fmaf(acc[v], a.scale_log2, -slse[h * a.P + pc]));
+      sum += (p < a.P && col <= spos[pc]) ? e : 0.f;
+    }
+  }
+  sum += __shfl_xor(sum, 32);
+  if (kh == 0) part[w][r] = sum;
+  __syncthreads();
+  if (tid < 32 && col0 + tid < a.Lk) {
+    float total = 0.f;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) total += part[v][tid];
+    const int cnt = a.P - lower_bound_pos(spos, a.P, col0 + tid);
+    if (a.normalize) total = cnt > 0 ? total / (float)cnt : 0.f;
+    scores[(int64_t)b * a.Lk + col0 + tid] = total / (float)a.Hq;
+  }
+}
+
 template <int DT, int D>
 static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStream_t st) {
   if (need_lse) {
@@ -416,6 +489,11 @@ static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStr
       hipLaunchKernelGGL(k_probe_lse_merge, dim3((unsigned)ceil_div64(rows, 256)), dim3(256), 0, st, a.lse_part, a.lse2, rows, a.nsplit);
       ZC_LAUNCH_CHECK();
     }
+  }
+  if (a.small) {
+    hipLaunchKernelGGL((k_probe_small<DT, D>), dim3((unsigned)ceil_div(a.Lk, 32), (unsigned)a.B), dim3(small_threads(DT, D)), 0, st, a, scores);
+    ZC_LAUNCH_CHECK();
+    return ZC_OK;
   }
   hipLaunchKernelGGL((k_probe_colsum<DT, D>), dim3((unsigned)((int64_t)ceil_div(a.Lk, 128) * a.Hq * a.B)), dim3(256), 0, st, a);
   ZC_LAUNCH_CHECK();
@@ -439,6 +517,17 @@ static int probe_splits(int64_t B, int64_t Hq, int64_t P, int64_t Lk) {
   if (even > 4) even = 4;
   const int64_t ns = fill > even ? fill : even;
   return (int)(ns < 1 ? 1 : (ns > kMaxProbeSplit ? kMaxProbeSplit : ns));
+}
+// Whether few probe rows are served by one launch: a block of 32, and no more bytes per
+// workgroup than its CU's loads bring in within the time the other path's two launches take
+// (8 heads of 64 channels, 256 tokens, 26 rows, fp32, 119 KB: 8 against 11 us; 2 x 16 heads of
+// 128 channels, 300 tokens, 30 rows, 16 bit, 254 KB: 10.5 against 9.7); twice that where
+// the columns fill half the chip (16 x 32 heads, 256 tokens, 26 rows, 344 KB: 14.9 against 18.9).
+static bool probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P, int64_t row_bytes) {
+  if (P > kSmallRows || Hq * P > kSmallTable) return false;
+  const int64_t segments = Hkv > 16 ? Hkv : (Hq < 16 ? Hq : 16);        // K loads: by waves and KV heads
+  const int64_t limit = B * ceil_div64(Lk, 32) >= 128 ? 384 * 1024 : 192 * 1024;
+  return (segments * 32 + Hq * P) * row_bytes <= limit;
 }
 static size_t lse_bytes(int64_t B, int64_t Hq, int64_t P) { return (size_t)align_up64(B * Hq * P * (kMaxProbeSplit * (int64_t)sizeof(float2) + 4), 256); }
 
@@ -488,6 +577,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
     return ZC_ERR_UNSUPPORTED;
   a.per_head = scores_per_head ? scores_per_head : ws_ph;
   a.normalize = normalize ? 1 : 0;
+  a.small = !scores_per_head && probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));
 
   hipStream_t st = (hipStream_t)stream;
   const bool need_lse = lse_ext == nullptr;

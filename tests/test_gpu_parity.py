@@ -882,3 +882,23 @@ def test_quantize_column_sweep_edges(B, H, D, n_reg, dtype):
                 total += r["n_codes"]
                 mism += r["n_mismatch"]
     assert mism <= 1e-4 * total, (mism, total)      # fp32 quotients next to a rounding boundary (the budget of the randomized shapes)
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,Lk,P,dtype", [
+    (1, 8, 8, 64, 256, 26, torch.float32), (1, 1, 1, 64, 1, 1, torch.bfloat16), (2, 18, 6, 64, 33, 32, torch.float16),
+    (3, 17, 17, 64, 100, 10, torch.bfloat16), (1, 12, 4, 128, 65, 31, torch.float32), (130, 24, 8, 128, 31, 9, torch.float16)])
+def test_probe_few_rows(B, Hq, Hkv, d, Lk, P, dtype):
+    """At most 32 probe rows (one launch for sums and mean) against the oracle and against the
+    general path, which per-head scores ask for: heads that do not divide over the waves, a
+    row block that is full and one that is not, columns one past a block."""
+    g = torch.Generator().manual_seed(Lk + P)
+    Q = torch.randn(B, Hq, Lk, d, generator=g).to(dtype)
+    K = torch.randn(B, Hkv, Lk, d, generator=g).to(dtype)
+    pos = torch.randperm(Lk, generator=g)[:P].sort().values.to(torch.int32)
+    few = zb.zc_probe_saliency(Q.to(DEV), K.to(DEV), pos.to(DEV))
+    ph = torch.empty(B, Hq, Lk, dtype=torch.float32, device=DEV)
+    general = zb.zc_probe_saliency(Q.to(DEV), K.to(DEV), pos.to(DEV), scores_per_head=ph)
+    # the same products and exponentials, added in another order: at most P * Hq terms of one sign
+    assert float((few - general).abs().max()) <= 1e-6 * float(general.abs().max())
+    ref, _ = zo.saliency_scores(Q[:1].double().numpy(), K[:1].double().numpy(), pos.numpy())
+    assert np.abs(few[:1].cpu().double().numpy() - ref).max() <= 1e-4 * np.abs(ref).max()
