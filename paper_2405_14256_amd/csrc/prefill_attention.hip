@@ -4,8 +4,7 @@
 // turn a logit into a probability, so zc_probe_saliency given them (lse_ext) runs its
 // column sweep only.
 //
-// A wave owns 32 query rows of a (batch, query head); 64-key tiles of K and V stream
-// through LDS for all waves of a workgroup, long row blocks are launched first.
+// A wave owns 32 query rows of a (batch, query head); long row blocks are launched first.
 //   logits  D[key][query]     = sum_c K[key][c] Q[query][c]        (A = K tile, B = Q rows in registers)
 //   output  D[channel][query] = sum_key Vt[channel][key] P[query][key]   (A = V tile transposed, B = P)
 // Both results put a query in a lane (column r = lane & 31): the running reference, the
@@ -30,11 +29,7 @@ struct PrefillArgs {
   int group;    // query heads an XCD works on at a time (prefill_block)
 };
 
-constexpr int kPfRows = 128;   // query rows per workgroup of the fp32 kernel
 constexpr int kPfKeys = 64;    // keys per tile
-
-// The transposed V tile of the fp32 kernel in LDS: one row per channel, the tile's 64 keys along it.
-constexpr int kVtRowB = kPfKeys * 4 + 16;   // (+16: consecutive channels start four banks apart)
 
 template <int DT>
 __device__ inline uint32_t pack_pair(float lo, float hi) {
@@ -80,148 +75,76 @@ __device__ inline int v_swizzle(int key) {
 }
 
 // ---- fp32 ---------------------------------------------------------------------------
-// One workgroup per 128 query rows.  K tiles go global -> LDS directly; V tiles pass through
-// registers, where four consecutive keys of four channels are transposed before they are
-// stored.  Bound by the fp32 matrix instructions (a sixteenth of the 16-bit rate).
-template <int D>
-__global__ __launch_bounds__(256, 1) void k_prefill_attention(PrefillArgs a) {
+// One workgroup per 32 query rows; its NW waves share the keys, a wave every NW-th block of 32,
+// each with a reference, sum and output of its own that are joined in LDS at the end.  Both
+// operands go straight from memory to registers: a lane's V words are 32 consecutive channels
+// of a key, which is the transposed operand as it stands (one fp32 word per k index).
+// Bound by the fp32 matrix instructions, a sixteenth of the 16-bit rate, and in small calls by
+// the chain of a row block's key blocks, which the split shortens: 8 heads of 64 channels, 256
+// rows: 22.8 -> 11 us; 1024 rows: 76 -> 27 us; 32 heads of 128 channels, 4096 rows: 1114 ->
+// 1053 us (against 128 rows a workgroup with 64-key tiles in LDS, V transposed on the way).
+// Requesting the next K block under the second product costs a wave per SIMD: 26 % slower there.
+template <int D, int NW>
+__global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs a) {
   using T = Tile<ZC_F32, D>;
-  constexpr int EB = 4;
-  constexpr int KTILE_B = kPfKeys * T::ROWB;
-  constexpr int VTILE_B = D * kVtRowB;
-  constexpr int NI = kPfKeys / T::RPI / 4;       // K transfers per wave and tile
-  constexpr int CT = D / 32;                     // 32-channel tiles of the output
-  constexpr int NPC = 4;                         // operand chunks per 32-key logit tile: keys 8 s + 4 kh .. + 3 of half-wave kh
-  constexpr int VU = 16 * T::CPR;                // V load units of a tile: 4 keys x one 16-byte chunk
-  constexpr int VUPT = (VU + 255) / 256;         // units per thread
-  __shared__ __align__(16) uint8_t Ks[2][KTILE_B];
-  __shared__ __align__(16) uint8_t Vt[2][VTILE_B];
+  constexpr int CT = D / 32;
+  constexpr int OROW = D + 4;                    // floats of a row in the joining stage
+  __shared__ __align__(16) float so[32 * OROW];
+  __shared__ float sm[NW][32], sl[NW][32];
 
   int hq, b, q0;
-  prefill_block(a, kPfRows, &b, &hq, &q0);
+  prefill_block(a, 32, &b, &hq, &q0);
   const int hk = hq / a.G;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)hq * a.q_sH) * EB;
-  const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)hk * a.k_sH) * EB;
-  const uint8_t* vb = reinterpret_cast<const uint8_t*>(a.v) + ((int64_t)b * a.v_sB + (int64_t)hk * a.v_sH) * EB;
-  const uint32_t q_rowb = (uint32_t)(a.q_sL * EB), k_rowb = (uint32_t)(a.k_sL * EB), v_rowb = (uint32_t)(a.v_sL * EB);
+  const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)hq * a.q_sH) * 4;
+  const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)hk * a.k_sH) * 4;
+  const uint8_t* vb = reinterpret_cast<const uint8_t*>(a.v) + ((int64_t)b * a.v_sB + (int64_t)hk * a.v_sH) * 4;
+  const uint32_t q_rowb = (uint32_t)(a.q_sL * 4), k_rowb = (uint32_t)(a.k_sL * 4), v_rowb = (uint32_t)(a.v_sL * 4);
   const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.L - 1) * q_rowb + T::ROWB, kBufFlags);
   const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.L - 1) * k_rowb + T::ROWB, kBufFlags);
   const auto rs_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(vb), 0, (uint32_t)(a.L - 1) * v_rowb + T::ROWB, kBufFlags);
+  const int qpos = q0 + r;
 
-  const int q_last = min(q0 + kPfRows, a.L) - 1;        // last real row of the block
-  const int ntiles = q_last / kPfKeys + 1;               // key tiles it can see
-  const int wq0 = q0 + 32 * w;                           // first row of this wave
-  const int qpos = wq0 + r;                              // this lane's row
-
-  // ---- K tile: global -> LDS directly, every wave a quarter of the transfers ----------
-  const uint32_t ks_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&Ks[0][0];
-  int kvoff[NI];
-#pragma unroll
-  for (int jj = 0; jj < NI; ++jj) {
-    const int row = (w + 4 * jj) * T::RPI + lane / T::CPR;
-    kvoff[jj] = (int)(row * k_rowb) + (((lane % T::CPR) ^ T::swz(row)) << 4);
-  }
-  // (the tile's offset is part of the per-lane offset, which the range check sees: rows
-  // past the end of K arrive as zeros)
-  auto k_issue = [&](int t, int buf) {
-    const int toff = (int)((uint32_t)t * kPfKeys * k_rowb);
-#pragma unroll
-    for (int jj = 0; jj < NI; ++jj) dma16<0>(ks_lds + buf * KTILE_B + (w + 4 * jj) * 1024, rs_k, kvoff[jj] + toff, 0);
-  };
-  // ---- V tile: into registers (four consecutive keys of one 16-byte chunk per unit;
-  //      consecutive lanes take consecutive key groups, so that the transposed stores of
-  //      a wave fill whole rows of the LDS tile) ------------------------------------------
-  struct VRegs { u32x4 x[VUPT][4]; };
-  auto v_issue = [&](int t, VRegs& vr) {
-#pragma unroll
-    for (int uu = 0; uu < VUPT; ++uu) {
-      const int u = tid + 256 * uu;
-      const int g4 = u & 15, cc = u >> 4;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int key = t * kPfKeys + 4 * g4 + i;
-        const int voff = (u < VU && key < a.L) ? (int)((uint32_t)key * v_rowb) + cc * 16 : kOutOfRange;
-        vr.x[uu][i] = __builtin_amdgcn_raw_buffer_load_b128(rs_v, voff, 0, 0);
-      }
-    }
-  };
-  auto v_store = [&](int buf, const VRegs& vr) {
-#pragma unroll
-    for (int uu = 0; uu < VUPT; ++uu) {
-      const int u = tid + 256 * uu;
-      if (u >= VU) continue;
-      const int g4 = u & 15, cc = u >> 4;
-      uint8_t* base = &Vt[buf][0] + g4 * 16;
-      // chunk cc: channels 4 cc .. 4 cc + 3 of the four keys
-      const uint32_t k0[4] = {vr.x[uu][0].x, vr.x[uu][0].y, vr.x[uu][0].z, vr.x[uu][0].w};
-      const uint32_t k1[4] = {vr.x[uu][1].x, vr.x[uu][1].y, vr.x[uu][1].z, vr.x[uu][1].w};
-      const uint32_t k2[4] = {vr.x[uu][2].x, vr.x[uu][2].y, vr.x[uu][2].z, vr.x[uu][2].w};
-      const uint32_t k3[4] = {vr.x[uu][3].x, vr.x[uu][3].y, vr.x[uu][3].z, vr.x[uu][3].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        u32x4 o; o.x = k0[e]; o.y = k1[e]; o.z = k2[e]; o.w = k3[e];
-        *reinterpret_cast<u32x4*>(base + (4 * cc + e) * kVtRowB) = o;
-      }
-    }
-  };
-
-  VRegs vr;
-  k_issue(0, 0);
-  v_issue(0, vr);
-  // this wave's query rows, straight into operand registers (rows past the end: zeros)
+  // (rows past the end, of any tensor, arrive as zeros)
   u32x4 qf[T::NKC];
   {
     const int voff = qpos < a.L ? (int)((uint32_t)qpos * q_rowb) + kh * 16 : kOutOfRange;
 #pragma unroll
     for (int kc = 0; kc < T::NKC; ++kc) qf[kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_q, voff + kc * 32, 0, 0);
   }
-
   v16f oacc[CT];
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) oacc[ct][i] = 0.f;
+  for (int ct = 0; ct < CT; ++ct) oacc[ct] = v16f{};
   float m = -INFINITY, l = 0.f;       // running maximum (log2 units) and this half-wave's share of the sum
 
-  auto tile = [&](auto masked_c, int t) {
-    constexpr bool MASKED = decltype(masked_c)::value;
-    const int cur = t & 1;
-    wait_all_loads();                 // K tile t (this wave's transfers) and V tile t (registers) have landed
-    v_store(cur, vr);
-    __syncthreads();                  // tile t is complete in LDS; nobody still reads the other buffers
-    if (t + 1 < ntiles) { k_issue(t + 1, cur ^ 1); v_issue(t + 1, vr); }
-    const int key0 = t * kPfKeys;
-    if (key0 > wq0 + 31) return;      // none of this tile's keys is visible to the wave's rows
-
-    // ---- logits of 64 keys x 32 rows ----
-    v16f sacc[2];
+  const int nblk = q0 / 32 + 1;                  // blocks of 32 keys the rows see: the last is the diagonal
+  for (int blk = w; blk < nblk; blk += NW) {
+    const int key0 = blk * 32;
+    const int koff = (int)((uint32_t)(key0 + r) * k_rowb) + kh * 16;
+    u32x4 kf[T::NKC];
 #pragma unroll
-    for (int i = 0; i < 16; ++i) { sacc[0][i] = 0.f; sacc[1][i] = 0.f; }
+    for (int kc = 0; kc < T::NKC; ++kc) kf[kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_k, koff + kc * 32, 0, 0);
+    float vf[CT][16];                            // [channel tile][accumulator of the logits]: key acc_row(v, kh), channel 32 ct + r
 #pragma unroll
-    for (int kc = 0; kc < T::NKC; ++kc) {
+    for (int v = 0; v < 16; ++v) {
+      const int voff = (int)((uint32_t)(key0 + acc_row(v, kh)) * v_rowb) + r * 4;
 #pragma unroll
-      for (int jt = 0; jt < 2; ++jt) {
-        const u32x4 af = *reinterpret_cast<const u32x4*>(&Ks[cur][T::slot(32 * jt + r, 2 * kc + kh)]);
-        mma_chunk<ZC_F32>(sacc[jt], af, qf[kc]);
-      }
+      for (int ct = 0; ct < CT; ++ct) vf[ct][v] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_v, voff + ct * 128, 0, 0));
     }
-    // ---- online softmax: a lane owns one row and 32 of the tile's keys ----
+    v16f s = {};
+#pragma unroll
+    for (int kc = 0; kc < T::NKC; ++kc) mma_chunk<ZC_F32>(s, kf[kc], qf[kc]);
+    if (blk == nblk - 1) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v)
+        if (acc_row(v, kh) > r) s[v] = -INFINITY;
+    }
     // (the maximum is taken over the raw products - the scale is positive - and the scale
     // enters with the subtraction of the reference: one fused multiply-add per logit)
-    float tmax = -INFINITY;
-    if constexpr (MASKED) {
+    float tmax = s[0];
 #pragma unroll
-      for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          if (key0 + 32 * jt + acc_row(v, kh) > qpos) sacc[jt][v] = -INFINITY;
-    }
-#pragma unroll
-    for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, sacc[jt][v]);
+    for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, s[v]);
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     const float m_new = fmaxf(m, tmax * a.scale_log2);
     if (__builtin_amdgcn_ballot_w64(m_new > m)) {
@@ -233,59 +156,73 @@ __global__ __launch_bounds__(256, 1) void k_prefill_attention(PrefillArgs a) {
         for (int i = 0; i < 16; ++i) oacc[ct][i] *= alpha;
       m = m_new;
     }
-    float s[2][16];
     float psum = 0.f;
 #pragma unroll
-    for (int jt = 0; jt < 2; ++jt)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        s[jt][v] = __builtin_amdgcn_exp2f(fmaf(sacc[jt][v], a.scale_log2, -m));   // (m is finite: key 0 is visible to every row)
-        psum += s[jt][v];
-      }
+    for (int v = 0; v < 16; ++v) {
+      s[v] = __builtin_amdgcn_exp2f(fmaf(s[v], a.scale_log2, -m));
+      psum += s[v];
+    }
     l += psum;
-    // ---- output += V^T P: the probabilities are the B operand as they stand ----
 #pragma unroll
-    for (int jt = 0; jt < 2; ++jt)
+    for (int v = 0; v < 16; ++v)
 #pragma unroll
-      for (int sp = 0; sp < NPC; ++sp) {
-        u32x4 pb;
-        pb.x = __float_as_uint(s[jt][4 * sp]); pb.y = __float_as_uint(s[jt][4 * sp + 1]);
-        pb.z = __float_as_uint(s[jt][4 * sp + 2]); pb.w = __float_as_uint(s[jt][4 * sp + 3]);
-        const int coff = (8 * (jt * NPC + sp) + 4 * kh) * EB;
-#pragma unroll
-        for (int ct = 0; ct < CT; ++ct) {
-          const u32x4 vf = *reinterpret_cast<const u32x4*>(&Vt[cur][(32 * ct + r) * kVtRowB + coff]);
-          mma_chunk<ZC_F32>(oacc[ct], vf, pb);
-        }
-      }
-  };
-  // Tiles all of whose keys every row of this wave sees need no mask: they run a copy of the
-  // tile code without the position compares (the waves of a workgroup reach their diagonal at
-  // different tiles, but every wave passes one barrier per tile either way).
-  const int t_full = min(ntiles, (wq0 + 1) / kPfKeys);
-  for (int t = 0; t < t_full; ++t) tile(std::false_type{}, t);
-  for (int t = t_full; t < ntiles; ++t) tile(std::true_type{}, t);
-
-  // ---- normalise and store: lane = row, accumulator v of tile ct = channel 32 ct + acc_row(v, kh) ----
-  const float l_tot = l + __shfl_xor(l, 32);
-  if (qpos < a.L) {
-    const float inv = 1.f / l_tot;
-    uint8_t* orow = reinterpret_cast<uint8_t*>(a.o) + ((int64_t)b * a.o_sB + (int64_t)hq * a.o_sH + (int64_t)qpos * a.o_sL) * EB;
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-      for (int v4 = 0; v4 < 4; ++v4) {
-        const int c = 32 * ct + acc_row(4 * v4, kh);        // four consecutive channels
-        *reinterpret_cast<float4*>(orow + c * 4) =
-            make_float4(oacc[ct][4 * v4] * inv, oacc[ct][4 * v4 + 1] * inv, oacc[ct][4 * v4 + 2] * inv, oacc[ct][4 * v4 + 3] * inv);
-      }
-    if (a.lse && kh == 0) a.lse[((int64_t)b * a.Hq + hq) * a.L + qpos] = (m + log2f(l_tot)) * kLn2;
+      for (int ct = 0; ct < CT; ++ct) oacc[ct] = __builtin_amdgcn_mfma_f32_32x32x2f32(vf[ct][v], s[v], oacc[ct], 0, 0, 0);
   }
+
+  if constexpr (NW == 1) {            // nothing to join: lane = row, accumulator v of tile ct = channel 32 ct + acc_row(v, kh)
+    const float l_tot = l + __shfl_xor(l, 32);
+    if (qpos < a.L) {
+      const float inv = 1.f / l_tot;
+      float* orow = reinterpret_cast<float*>(a.o) + (int64_t)b * a.o_sB + (int64_t)hq * a.o_sH + (int64_t)qpos * a.o_sL;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4)
+          *reinterpret_cast<float4*>(orow + 32 * ct + acc_row(4 * v4, kh)) =
+              make_float4(oacc[ct][4 * v4] * inv, oacc[ct][4 * v4 + 1] * inv, oacc[ct][4 * v4 + 2] * inv, oacc[ct][4 * v4 + 3] * inv);
+      if (a.lse && kh == 0) a.lse[((int64_t)b * a.Hq + hq) * a.L + qpos] = (m + log2f(l_tot)) * kLn2;
+    }
+    return;
+  }
+  // ---- join the waves: a common reference and sum, then the outputs one wave after the other ----
+  // (a wave without keys has m = -inf, l = 0 and zeros; wave 0 always has the block of key 0)
+  const float l_wave = l + __shfl_xor(l, 32);
+  if (kh == 0) { sm[w][r] = m; sl[w][r] = l_wave; }
+  __syncthreads();
+  float M = sm[0][r];
+#pragma unroll
+  for (int v = 1; v < NW; ++v) M = fmaxf(M, sm[v][r]);
+  float l_tot = 0.f;
+#pragma unroll
+  for (int v = 0; v < NW; ++v) l_tot += sm[v][r] == -INFINITY ? 0.f : sl[v][r] * __builtin_amdgcn_exp2f(sm[v][r] - M);
+  const float mine = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M) / l_tot;
+  const int used = min(NW, nblk);
+  for (int v = used - 1; v >= 0; --v) {
+    if (w == v) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+          float4* p = reinterpret_cast<float4*>(&so[r * OROW + 32 * ct + acc_row(4 * v4, kh)]);       // four consecutive channels
+          float4 o = make_float4(oacc[ct][4 * v4] * mine, oacc[ct][4 * v4 + 1] * mine, oacc[ct][4 * v4 + 2] * mine, oacc[ct][4 * v4 + 3] * mine);
+          if (v < used - 1) { const float4 t = *p; o.x += t.x; o.y += t.y; o.z += t.z; o.w += t.w; }
+          *p = o;
+        }
+    }
+    __syncthreads();
+  }
+  for (int i = tid; i < 32 * (D / 4); i += 64 * NW) {
+    const int row = i / (D / 4), c = (i % (D / 4)) * 4;
+    if (q0 + row < a.L)
+      *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.o) + (int64_t)b * a.o_sB + (int64_t)hq * a.o_sH + (int64_t)(q0 + row) * a.o_sL + c) =
+          *reinterpret_cast<const float4*>(&so[row * OROW + c]);
+  }
+  if (a.lse && w == 0 && kh == 0 && qpos < a.L) a.lse[((int64_t)b * a.Hq + hq) * a.L + qpos] = (M + log2f(l_tot)) * kLn2;
 }
 
 // ---- 16-bit types -------------------------------------------------------------------
-// One workgroup per 32 * NW query rows, a wave per 32 of them, two waves on a SIMD.  Keys
-// go by halves of a 64-key tile, and a wave's diagonal falls on exactly one half, so no
+// One workgroup per 32 * NW query rows, a wave per 32 of them, two waves on a SIMD; 64-key
+// tiles of K and V stream through LDS for all of them.  Keys go by halves of a 64-key tile, and a wave's diagonal falls on exactly one half, so no
 // wave multiplies a half it cannot see.  Both tiles come global -> LDS directly; the V
 // operand is read with the transposing LDS load, in row-major tiles as they arrived.
 //
@@ -543,21 +480,38 @@ __global__ void k_gather_lse(const float* __restrict__ lse, const int32_t* __res
   out[i] = (pos >= 0 && pos < L) ? lse[h * L + pos] : 0.f;
 }
 
+// Query heads an XCD works on at a time: whole KV heads, at least two rounds of its slots, and
+// groups of one size (a small last group would start its long blocks when the chip drains).
+static int head_group(const PrefillArgs& a, int nqb, int slots) {
+  const int hpx = (a.B * a.Hq) >> 3, least = a.G * ceil_div(2 * slots, nqb * a.G);
+  const int groups = hpx / least;
+  return groups > 1 ? a.G * ceil_div(hpx, groups * a.G) : hpx > 0 ? hpx : 1;
+}
+
 template <int DT, int D>
 static int launch_prefill(PrefillArgs a, hipStream_t st) {
-  // Eight waves per workgroup read a K and V tile once for 256 rows; four where that leaves
-  // the chip fewer than two workgroups a CU, whose lengths then cannot even out (16 heads of
-  // 4096 rows of 64 channels, 256 against 512 workgroups: 68 against 51 us; 32 heads of 128
-  // channels, 512 against 1024: 133 against 144 us).
   const int64_t heads = (int64_t)a.B * a.Hq;
-  const bool wide = DT != ZC_F32 && ceil_div(a.L, 256) * heads >= 512;
-  const int rows = wide ? 256 : 128, slots = wide ? 32 : 64;       // workgroups an XCD holds at a time
-  const int nqb = ceil_div(a.L, rows);
-  a.group = a.G * ceil_div(2 * slots, nqb * a.G);
-  const dim3 grid((unsigned)(nqb * heads));
-  if constexpr (DT == ZC_F32) hipLaunchKernelGGL((k_prefill_attention<D>), grid, dim3(256), 0, st, a);
-  else if (wide) hipLaunchKernelGGL((k_prefill_attention16<DT, D, 8>), grid, dim3(512), 0, st, a);
-  else hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), grid, dim3(256), 0, st, a);
+  const auto blocks = [&](int rows, int slots) {          // slots: workgroups an XCD holds at a time
+    const int nqb = ceil_div(a.L, rows);
+    a.group = head_group(a, nqb, slots);
+    return dim3((unsigned)(nqb * heads));
+  };
+  if constexpr (DT == ZC_F32) {
+    // The keys of a row block are split while that evens out the chip: a SIMD's share of all
+    // blocks is heads (n + 1) / 2048 times the n of the longest row block.  One wave or two, at
+    // 2.1: 88 / 94 and 335 / 331 us, at 2.0: 579 / 549; two or four, at 1.6: 232 / 261, at 1.1: 264 / 237.
+    const int64_t share = heads * (ceil_div(a.L, 32) + 1);
+    if (share >= 4300) hipLaunchKernelGGL((k_prefill_attention32<D, 1>), blocks(32, 256), dim3(64), 0, st, a);
+    else if (share >= 3100) hipLaunchKernelGGL((k_prefill_attention32<D, 2>), blocks(32, 128), dim3(128), 0, st, a);
+    else hipLaunchKernelGGL((k_prefill_attention32<D, 4>), blocks(32, 64), dim3(256), 0, st, a);
+  } else {
+    // Eight waves per workgroup read a K and V tile once for 256 rows; four where that leaves
+    // the chip fewer than two workgroups a CU, whose lengths then cannot even out (16 heads of
+    // 4096 rows of 64 channels, 256 against 512 workgroups: 68 against 51 us; 32 heads of 128
+    // channels, 512 against 1024: 133 against 144 us).
+    if (ceil_div(a.L, 256) * heads >= 512) hipLaunchKernelGGL((k_prefill_attention16<DT, D, 8>), blocks(256, 32), dim3(512), 0, st, a);
+    else hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), blocks(128, 64), dim3(256), 0, st, a);
+  }
   ZC_LAUNCH_CHECK();
   return ZC_OK;
 }
@@ -593,7 +547,7 @@ extern "C" int zc_prefill_attention(const zc_tensor4* q, const zc_tensor4* k, co
         (v->L + 128) * v->sL * eb >= 0xFFFFF000ll)
       return ZC_ERR_UNSUPPORTED;
   }
-  const int64_t grid = ceil_div64(q->L, kPfRows) * q->H * q->B;
+  const int64_t grid = ceil_div64(q->L, 32) * q->H * q->B;         // (the smallest row blocks)
   if (grid > 0x7fffffff) return ZC_ERR_UNSUPPORTED;
 
   PrefillArgs a;

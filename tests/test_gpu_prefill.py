@@ -132,3 +132,20 @@ def test_prefill_tiles_and_reference(dtype, B, Hq, Hkv, d, L, rise):
         assert np.abs(out[b, h].double().cpu().numpy() - O_o[0, 0]).max() <= u * vmax + 1e-5 * vmax
         # fp32 sums of d products: a logit is off by about d 2^-24 of the sum of magnitudes
         assert np.abs(lse[b, h].double().cpu().numpy() - lse_o[0, 0]).max() <= 1e-4 + 2e-5 * rise
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,d,L", [
+    (1, 4, 2, 64, 31), (1, 3, 1, 128, 33), (2, 12, 4, 64, 129), (1, 8, 2, 128, 161),    # a row block's keys over four waves: one to six blocks of them
+    (5, 32, 8, 64, 640), (5, 32, 8, 128, 609),                                          # over two
+    (5, 32, 8, 64, 865), (5, 32, 4, 128, 833)])                                         # not split
+def test_prefill_fp32_key_splits(B, Hq, Hkv, d, L):
+    g = torch.Generator().manual_seed(L + d)
+    Q, K, V = (torch.randn(B, H, L, d, generator=g) for H in (Hq, Hkv, Hkv))
+    K[..., 0] += torch.linspace(0, 20, L)                # the largest logits of a row are not all in one wave's blocks
+    out, lse, _ = zb.zc_prefill_attention(Q.to(DEV), K.to(DEV), V.to(DEV))
+    G = Hq // Hkv
+    for b, h in {(0, 0), (B - 1, Hq - 1)}:
+        O_o, lse_o = zo.prefill_attention(*(t.double().numpy() for t in (Q[b:b + 1, h:h + 1], K[b:b + 1, h // G:h // G + 1], V[b:b + 1, h // G:h // G + 1])))
+        # a logit of magnitude 2^5 is off by a few of its units 2^-19, a weight by as much relatively, |V| stays below 2^3
+        assert np.abs(out[b, h].double().cpu().numpy() - O_o[0, 0]).max() <= 1e-4
+        assert np.abs(lse[b, h].double().cpu().numpy() - lse_o[0, 0]).max() <= 1e-4
