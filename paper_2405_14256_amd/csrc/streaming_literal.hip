@@ -349,11 +349,21 @@ __device__ inline void store8(void* base, int64_t off, const float (&v)[8]) {
     p[0] = make_float4(v[0], v[1], v[2], v[3]);
     p[1] = make_float4(v[4], v[5], v[6], v[7]);
   } else {
-    uint16_t h[8];
+    // (two to an instruction, rounding to nearest even: 8000 tokens of two prompts re-compressed
+    // in bf16 91.6 -> 88.0 us against rounding by integer arithmetic)
+    uint32_t h[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) store1<DT>(h, i, v[i]);
-    *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(base) + off) =
-        make_uint4(h[0] | (uint32_t)h[1] << 16, h[2] | (uint32_t)h[3] << 16, h[4] | (uint32_t)h[5] << 16, h[6] | (uint32_t)h[7] << 16);
+    for (int i = 0; i < 4; ++i) {
+      typedef float f2 __attribute__((ext_vector_type(2)));
+      if constexpr (DT == ZC_F16) {
+        typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+        h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{v[2 * i], v[2 * i + 1]}), h2));
+      } else {
+        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+        h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{v[2 * i], v[2 * i + 1]}), b2));
+      }
+    }
+    *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(base) + off) = make_uint4(h[0], h[1], h[2], h[3]);
   }
 }
 
