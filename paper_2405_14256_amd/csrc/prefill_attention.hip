@@ -235,10 +235,10 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
 // 3001 rows, fp16: 225 -> 159 us.  Scheduling barriers between the slices of the first
 // product, or a raised wave priority around the second, cost 3 to 5 %.
 //
-// A row's reference m only has to keep the exponentials in range; it need not be the
-// maximum.  It is taken from the first half and moved when a sum shows that some logit lies
-// far above it (then the half is done again, exactly): no maximum in the common path.  Weights
-// stay below 2^14, which fp16 holds, and at least one of a row's weights has been 1.
+// The running maximum of a half is taken beside the second product of the half before.  (A
+// reference that moves only when a sum leaves its range spares most of that and of the
+// rescaling, 3 %, but a row's largest weight is then rounded like the others instead of being
+// 1: the distance to 64-bit results grows by 17 %.)
 template <int DT, int D, int NW>
 __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs a) {
   using T = Tile<DT, D>;
@@ -341,7 +341,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[ct][i] = 0.f;
-  float m = -INFINITY, l = 0.f;       // the row's reference (log2 units) and this half-wave's share of the sum
+  float m = -INFINITY, l = 0.f;       // the row's running maximum (log2 units) and this half-wave's share of the sum
   KFrag kf;
   v16f s0, s1;
 
@@ -354,8 +354,21 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
   k_read(1, kf);
   kaddr += TILE_B;                                   // the K operands of a step are read one tile ahead
 
-  // One half: weights of the logits sc, output += V^T P; NEXT: the logits of the half after it
-  // (operands in kf) meanwhile, and the request of the operands of the half after that.
+  // Largest logit (log2 units) of a half in either half-wave.  (The maximum is taken over the raw
+  // products - the scale is positive - and the scale enters the weights with the subtraction of
+  // the reference: one fused multiply-add per logit.)
+  auto half_max = [&](const v16f& sc) {
+    float t = sc[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) t = fmaxf(t, sc[v]);
+    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+    return fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1])) * a.scale_log2;
+  };
+  float tmax = half_max(s0);                         // of the half whose weights are taken next
+
+  // One half: weights of the logits sc, output += V^T P; unless it is the wave's LAST, the logits
+  // of the half after it (operands in kf) meanwhile, their maximum, and the request of the
+  // operands of the half after that.
   auto step = [&](auto last_c, int half, v16f& sc, v16f& sn) {
     constexpr bool LAST = decltype(last_c)::value;
     u32x4 vf[2][CT];
@@ -363,10 +376,21 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
 #pragma unroll
       for (int v = 0; v < 16; ++v)
         if (acc_row(v, kh) > r) sc[v] = -INFINITY;
+      tmax = half_max(sc);
+    }
+    const float m_new = fmaxf(m, tmax);
+    if (__builtin_amdgcn_ballot_w64(m_new > m)) {
+      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+      l *= alpha;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[ct][i] *= alpha;
+      m = m_new;
     }
     uint32_t pw[8];                                  // the weights, two to a word
     float psum = 0.f;
-    const float nm = -m;
+    const float nm = -m;                             // (finite: key 0 is visible to every row)
     if constexpr (!LAST) sn = v16f{};
 #pragma unroll
     for (int kc = 0; kc < T::NKC; ++kc) {
@@ -379,44 +403,20 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
         psum += p0;
         psum += p1;
         pw[e >> 1] = pack_pair<DT>(p0, p1);
-        asm volatile("" : "+v"(pw[e >> 1]));         // (packed here, not after the branch below)
       }
     }
-    // a sum out of range (the first half, where m is -inf; a logit far above m; a NaN)
-    if (__builtin_amdgcn_ballot_w64(!(psum < 16384.f))) {
-      float tmax = sc[0];
-#pragma unroll
-      for (int v = 1; v < 16; ++v) tmax = fmaxf(tmax, sc[v]);
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
-      const float m_new = fmaxf(m, tmax * a.scale_log2);
-      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
-      l *= alpha;
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct)
-#pragma unroll
-        for (int i = 0; i < 16; ++i) oacc[ct][i] *= alpha;
-      m = m_new;
-      psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 16; e += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[e], a.scale_log2, -m));      // (m is finite: key 0 is visible to every row)
-        const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], a.scale_log2, -m));
-        psum += p0;
-        psum += p1;
-        pw[e >> 1] = pack_pair<DT>(p0, p1);
-      }
-    }
+    l += psum;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) v_read(half, 1, ct, vf[1][ct]);
     if constexpr (!LAST) k_read(half, kf);
     u32x4 pb[2];
 #pragma unroll
     for (int s = 0; s < 2; ++s) { pb[s].x = pw[4 * s]; pb[s].y = pw[4 * s + 1]; pb[s].z = pw[4 * s + 2]; pb[s].w = pw[4 * s + 3]; }
-    l += psum;
 #pragma unroll
     for (int s = 0; s < 2; ++s)
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct) mma_chunk<DT>(oacc[ct], vf[s][ct], pb[s]);
+    if constexpr (!LAST) tmax = half_max(sn);        // (beside the second product, which leaves the vector units idle)
   };
   // Tile t's barrier: K(t + 1) and V(t) are complete in LDS, and nobody still reads K(t)
   // (its second half was requested before) or V(t - 1), whose buffers are filled next.
