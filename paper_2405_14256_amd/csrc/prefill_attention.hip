@@ -230,10 +230,10 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
 // cycles (d = 128) and about 300 cycles of vector instructions, so the two have to run at the
 // same time.  The logits of half h + 1 are multiplied while the exponentials of half h are
 // taken, and the operands of each product are requested one phase before.  32 heads of 32768
-// rows, bf16: 9.07 -> 7.46 ms (1.18 PFLOP/s; matrix cores busy 64 % of the cycles at the 1.75
-// GHz the chip holds then; a large library product reaches 1.21 PFLOP/s); 2 x 32 heads of
-// 3001 rows, fp16: 225 -> 159 us.  Scheduling barriers between the slices of the first
-// product, or a raised wave priority around the second, cost 3 to 5 %.
+// rows, bf16: 8.80 -> 7.92 ms (1.11 PFLOP/s; a large library product reaches 1.21); 2 x 32
+// heads of 3001 rows, fp16: 220 -> 173 us; 16 heads of 4096 rows of 64 channels: 89 -> 57 us.
+// Scheduling barriers between the slices of the first product, or a raised wave priority
+// around the second, cost 3 to 5 %.
 //
 // The running maximum of a half is taken beside the second product of the half before.  (A
 // reference that moves only when a sum leaves its range spares most of that and of the
