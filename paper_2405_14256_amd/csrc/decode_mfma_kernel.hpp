@@ -253,7 +253,7 @@ __device__ inline void raw_to_float(const Raw8<DT>& r, float (&v)[8]) {
 // WIDE: a subset has 8-bit codes (kernels of their own: a third copy of the segment code in the
 // others would cost them registers).  One kernel for all widths instead of the vector-ALU one
 // that served such caches before (a code at a time, the logits of a block through LDS and three
-// barriers): 4 prompts of 7901 tokens at 8/4 bits, 8 KV heads of 4: 263 -> 14.7 us per call.
+// barriers): 4 prompts of 7901 tokens at 8/4 bits, 8 KV heads of 4: 263 -> 15.7 us per call.
 template <int DT, int D, bool KTOK, bool VTOK, int MINB, bool STG, bool WIDE>
 __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   constexpr int KS = D / 32;     // k-steps of the logit product
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   const int g = n >> 1, part = n & 1;
   const bool nvalid = n < 2 * G;
   const int g0 = 2 * grp, g1 = 2 * grp + 1;      // heads of this lane's rows in the output tiles
-  constexpr bool WSPLIT = (DT == ZC_F32);    // softmax weights as value + residual
+  constexpr bool WSPLIT = (DT == ZC_F32) || WIDE;   // softmax weights as value + residual (8-bit caches: a single fp16 weight would show, 2e-4 -> 6e-4 in fp16)
   constexpr bool SUBN = (DT != ZC_F32);      // codes enter as fp16 subnormals
   // q' always enters as value + residual (two columns per head).  A single fp16 q'
   // was tried for 16-bit tensors: it saves two instructions per logit but moves the
