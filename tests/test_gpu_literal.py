@@ -237,6 +237,46 @@ def test_rows_saliency_shapes(P, B, Hq, N, n_out):
         assert float((got - ref).abs().max()) <= 2.0 ** -24 * (P + Hq) * float(ref.max()) + 1e-12
 
 
+def _unpacked(p, total, dtype):
+    """x_hat of the cache `p` of `total` tokens in token order [B, H, total, d], rounded to dtype:
+    fp16 from the exact product of the scales' fp32 product and the level, in one rounding."""
+    want = torch.zeros(p.B, total, p.H * p.D, dtype=torch.float64 if dtype == torch.float16 else torch.float32, device=DEV)
+    for ci, row in enumerate(p.chunks):
+        for which in (0, 1):
+            begin, n = row[2 * which:2 * which + 2]
+            if n == 0:
+                continue
+            codes, x = zb.zc_unpack(p, which, ci)
+            if dtype == torch.float16:
+                scale, level = p.chan_scale[ci, which][:, None], codes.float() - p.chan_zero[ci, which][:, None]
+                if p.scheme != "channel":
+                    scale = scale * (p.tok_scale_lo if which else p.tok_scale_hi)[:, begin:begin + n, None]
+                    level = level - (p.tok_zero_lo if which else p.tok_zero_hi)[:, begin:begin + n, None]
+                x = scale.double() * level.double()
+            pos = (p.pos_lo if which else p.pos_hi)[:, begin:begin + n].long()
+            for b in range(p.B):
+                want[b, pos[b]] = x[b]
+    if dtype == torch.float16:         # (torch converts float64 to float16 through float32; numpy does not)
+        want = torch.from_numpy(want.cpu().numpy().astype(np.float16)).to(DEV)
+    return want.to(dtype).view(p.B, total, p.H, p.D).permute(0, 2, 1, 3)
+
+
+@pytest.mark.parametrize("scheme,layout", [("channel", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP)])
+def test_dequantize_cache_rounds_fp16_once(scheme, layout):
+    """Enough 4-bit channels that some products (R / 15 times 3, 5, 6, 9, 10 or 12) lie within an
+    fp32 unit of an fp16 midpoint, where a product rounded to fp32 first ends on the other side."""
+    B, H, d, L, k = 2, 24, 128, 3000, 2000
+    g = torch.Generator().manual_seed(15)
+    x = torch.randn(B, H, L, d, generator=g).to(torch.float16).to(DEV)
+    p = zb.PackedTensor(B, H, d, 2048, 1024, 4, 2, scheme, layout, max_chunks=1, device=DEV)
+    sal, reg = zb.zc_select_salient(torch.rand(B, L, generator=g).to(DEV), k)
+    zb.zc_quantize_pack(x, sal, reg, p)
+    out = torch.zeros_like(x)
+    zb.zc_dequantize_cache(p, out)
+    want = _unpacked(p, L, torch.float16)
+    assert x.numel() > 10**7 and int((out != want).sum()) == 0
+
+
 @pytest.mark.parametrize("bits_hi,bits_lo,d,dtype", [(4, 2, 128, torch.bfloat16), (8, 4, 64, torch.float16), (2, 8, 128, torch.float32)])
 def test_dequantize_cache_is_the_unpacked_cache_in_token_order(bits_hi, bits_lo, d, dtype):
     """More segments than one launch takes, empty subsets, lengths around a block's edges, both
@@ -256,19 +296,8 @@ def test_dequantize_cache_is_the_unpacked_cache_in_token_order(bits_hi, bits_lo,
             n0 += k + r
         Lout = total - 3
         out = torch.full((B, H, Lout + 2, d), 7.0, dtype=dtype, device=DEV)
-        want = torch.full((B, total, H * d), 7.0, dtype=torch.float32, device=DEV)
-        for ci in range(len(sizes)):
-            for which in (0, 1):
-                n = p.chunks[ci][2 * which + 1]
-                if n == 0:
-                    continue
-                _, dq = zb.zc_unpack(p, which, ci)
-                begin = p.chunks[ci][2 * which]
-                pos = (p.pos_lo if which else p.pos_hi)[:, begin:begin + n].long()
-                for b in range(B):
-                    want[b, pos[b]] = dq[b]
+        want = _unpacked(p, total, dtype)
         zb.zc_dequantize_cache(p, out[:, :, :Lout])
-        want = want.to(dtype).view(B, total, H, d).permute(0, 2, 1, 3)
         assert torch.equal(out[:, :, :Lout], want[:, :, :Lout])
         assert float((out[:, :, Lout:].float() - 7.0).abs().max()) == 0.0
 
