@@ -19,8 +19,8 @@
 // Both products run on v_mfma_f32_16x16x32_f16 with the codes as one operand:
 //   logits  D[token][n]   = sum_c code[token][c] * q'[n][c]      (A = K codes, ROW layout)
 //   output  D[n][channel] = sum_t w[n][t] * code[t][channel]     (B = V codes, TGROUP layout)
-// A code of 2 or 4 bits enters as an fp16 subnormal (8-bit codes become exact fp16
-// integers, see unpack8): masking a packed word leaves the code's
+// A code of a cache of 2- and 4-bit codes in 16-bit tensors enters as an fp16 subnormal
+// (the other encodings are below, at CodeForm): masking a packed word leaves the code's
 // bits somewhere in the low ten bits of each 16-bit half, which reads as
 // code * 2^pos * 2^-24 (the matrix cores keep subnormal inputs).  The bit
 // position pos differs from register to register; the other operand carries
@@ -30,8 +30,9 @@
 // The 16 columns n hold the Hq/Hkv query heads of the KV head twice: the fp16
 // value of the operand (n even) and its rounding residual times 2^11 (n odd), so
 // the fp32 q keeps about 21 bits; the softmax weights are split the same way for
-// fp32 tensors and are single fp16 numbers for 16-bit tensors.  The sum of the
-// weights comes from one more MFMA against the constants 2^(pos - P).
+// fp32 tensors and for caches with 8-bit codes, and are single fp16 numbers for 16-bit
+// tensors over 2- and 4-bit codes.  The sum of the weights comes from one more MFMA
+// against the constants 2^(pos - P).
 // The packed layouts are chosen so that the 8 codes a lane feeds to one MFMA are
 // contiguous bits of one 32-bit word, and so that the lane that holds a logit is
 // the lane that must supply the corresponding softmax weight to the second MFMA.
@@ -83,7 +84,7 @@ __device__ inline f4 mfma16(u4 a, u4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
 
-// Two encodings of a code as an fp16 operand element.
+// Three encodings of a code as an fp16 operand element.
 //  * subnormal (16-bit tensors): the masked bits of the packed word, read as
 //    code * 2^pos * 2^-24; the other operand carries 2^(P - pos).  The matrix
 //    cores align the products of one instruction by their nominal exponents, so a
@@ -92,73 +93,96 @@ __device__ inline f4 mfma16(u4 a, u4 b, f4 c) {
 //  * normalized (fp32 tensors): 1 + code / SC, the code OR-ed into the top mantissa
 //    bits of 1.0 (SC = 16 or 4); the other operand carries SC and the "1" terms are
 //    removed with the sum of the other operand.  Exact to the accumulator's 24 bits.
+//  * centred (caches in which a subset has 8-bit codes, every type and width): the exact
+//    normal fp16 number (code - bias) * 2^pos * 2^-9 (8 bits: code - bias), bias = half the
+//    range: the masked bits, a subnormal number, through one packed multiply-add (8 bits: under
+//    the exponent of 1024, one packed subtraction).  The other operand carries 64 / 2^pos, and
+//    the sums of it take the bias off the zero points.  Nothing that cancels against the zero
+//    points reaches the accumulators.  (With the other two encodings for the
+//    2- and 4-bit subset of such a cache the log-sum-exp of 16-bit tensors was off by 4e-5 at
+//    8/4 and 1.4e-4 at 8/2 bits, against 2e-6 on the vector ALUs, and fp32 results were 1.2
+//    to 1.7 times as far from 64-bit ones.)
 // Register i of unpack4 holds code i (low half) and code i + 4 (high half);
-// register i of unpack2 holds codes (i, i + 8) for half 0, (4 + i, 12 + i) for half 1.
-template <bool SUBN>
+// register i of unpack2 holds codes (i, i + 8) for half 0, (4 + i, 12 + i) for half 1;
+// the two registers of unpack8 hold codes (0, 2) and (1, 3).
+enum class CodeForm { kSubnormal, kNormalized, kCentred };
+template <int BITS> constexpr float code_bias() { return (float)(1 << (BITS - 1)); }
+
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t centred(uint32_t masked, int bias) {      // bias: of the masked field
+  const h2 up = h2{(_Float16)32768.f, (_Float16)32768.f}, off = h2{(_Float16)(bias / 512.f), (_Float16)(bias / 512.f)};
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(__builtin_bit_cast(h2, masked), up, -off));
+}
+template <CodeForm F>
 __device__ inline u4 unpack4(uint32_t w) {
   u4 r;
-  if constexpr (SUBN) {
+  if constexpr (F == CodeForm::kSubnormal) {
     const uint32_t t = w >> 8;
     r.x = w & 0x000F000Fu;
     r.y = w & 0x00F000F0u;
     r.z = t & 0x000F000Fu;
     r.w = t & 0x00F000F0u;
-  } else {
+  } else if constexpr (F == CodeForm::kNormalized) {
     const uint32_t M = 0x03C003C0u, E = 0x3C003C00u;
     r.x = ((w << 6) & M) | E;
     r.y = ((w << 2) & M) | E;
     r.z = ((w >> 2) & M) | E;
     r.w = ((w >> 6) & M) | E;
+  } else {
+    const uint32_t t = w >> 8;
+    r.x = centred(w & 0x000F000Fu, 8);
+    r.y = centred(w & 0x00F000F0u, 8 << 4);
+    r.z = centred(t & 0x000F000Fu, 8);
+    r.w = centred(t & 0x00F000F0u, 8 << 4);
   }
   return r;
 }
-template <bool SUBN>
+template <CodeForm F>
 __device__ inline u4 unpack2(uint32_t w, int half) {
   if (half) w >>= 8;
   u4 r;
-  if constexpr (SUBN) {
+  if constexpr (F == CodeForm::kSubnormal) {
     r.x = w & 0x00030003u;
     r.y = w & 0x000C000Cu;
     r.z = w & 0x00300030u;
     r.w = w & 0x00C000C0u;
-  } else {
+  } else if constexpr (F == CodeForm::kNormalized) {
     const uint32_t M = 0x03000300u, E = 0x3C003C00u;
     r.x = ((w << 8) & M) | E;
     r.y = ((w << 6) & M) | E;
     r.z = ((w << 4) & M) | E;
     r.w = ((w << 2) & M) | E;
+  } else {
+    r.x = centred(w & 0x00030003u, 2);
+    r.y = centred(w & 0x000C000Cu, 2 << 2);
+    r.z = centred(w & 0x00300030u, 2 << 4);
+    r.w = centred(w & 0x00C000C0u, 2 << 6);
   }
   return r;
 }
-// 8-bit codes, both tensor types: the exact fp16 number code - 128 (1024 + code is the code under
-// the exponent of 1024, one byte permute; one packed subtraction takes 1152 off).  Centring the
-// codes keeps what cancels against the zero points out of the accumulators; the sums of the other
-// operand take 128 off the zero points in turn.  Two registers, codes (0, 2) and (1, 3) of the word.
-constexpr float kCode8Bias = 128.f;
+// 8-bit codes: 1024 + code is the code under the exponent of 1024, one byte permute.
 __device__ inline uint2 unpack8(uint32_t w) {
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-  const h2 bias = h2{(_Float16)1152.f, (_Float16)1152.f};
+  const h2 off = h2{(_Float16)1152.f, (_Float16)1152.f};
   const uint32_t even = __builtin_amdgcn_perm(0x64646464u, w, 0x07020700u), odd = __builtin_amdgcn_perm(0x64646464u, w, 0x07030701u);
-  return make_uint2(__builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, even) - bias),
-                    __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, odd) - bias));
+  return make_uint2(__builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, even) - off),
+                    __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, odd) - off));
 }
 // The factor the other operand carries for operand register i (both halves).
-template <int BITS, bool SUBN> __device__ inline float code_comp(int i) {
+template <int BITS, CodeForm F> __device__ inline float code_comp(int i) {
   if constexpr (BITS == 8) return 64.f;
-  else if constexpr (!SUBN) return BITS == 4 ? 16.f : 4.f;
-  else if constexpr (BITS == 4) return (i & 1) ? 1.f : 16.f;
-  else return (float)(64 >> (2 * i));
+  else if constexpr (F == CodeForm::kNormalized) return BITS == 4 ? 16.f : 4.f;
+  else if constexpr (BITS == 2) return (float)(64 >> (2 * i));
+  else if constexpr (F == CodeForm::kCentred) return (i & 1) ? 4.f : 64.f;
+  else return (i & 1) ? 1.f : 16.f;
 }
-template <int BITS, bool SUBN> __device__ inline int code_comp_log2(int i) {
-  if constexpr (BITS == 8) return 6;
-  else if constexpr (!SUBN) return BITS == 4 ? 4 : 2;
-  else if constexpr (BITS == 4) return (i & 1) ? 0 : 4;
+template <int BITS> __device__ inline int subnormal_comp_log2(int i) {      // of the subnormal encoding's
+  if constexpr (BITS == 4) return (i & 1) ? 0 : 4;
   else return 6 - 2 * i;
 }
 // product of a code and x, divided by what the matrix cores accumulate for it
-template <int BITS, bool SUBN> constexpr float code_unscale() {
-  if constexpr (BITS == 8) return 1.f / 64.f;
-  else return SUBN ? (float)(1 << (24 - (BITS == 4 ? 4 : 6))) : 1.f;
+template <int BITS, CodeForm F> constexpr float code_unscale() {
+  if constexpr (F == CodeForm::kCentred) return BITS == 8 ? 1.f / 64.f : 8.f;
+  else return F == CodeForm::kSubnormal ? (float)(1 << (24 - (BITS == 4 ? 4 : 6))) : 1.f;
 }
 
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
@@ -176,7 +200,6 @@ __device__ inline uint32_t pack_h2(_Float16 lo, _Float16 hi) {
 // Two floats rounded to fp16 in one register (v_cvt_pk_f16_f32).
 __device__ inline uint32_t pack_f2(float lo, float hi) {
   typedef float f2 __attribute__((ext_vector_type(2)));
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(f2{lo, hi}, h2));
 }
 
@@ -188,11 +211,9 @@ __device__ inline _Float16 split_part(float x, int part) {
   return part ? lo : hi;
 }
 __device__ inline float half_lo_to_float(uint32_t w) {
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
   return (float)__builtin_bit_cast(h2, w).x;
 }
 __device__ inline float half_hi_to_float(uint32_t w) {
-  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
   return (float)__builtin_bit_cast(h2, w).y;
 }
 
@@ -253,7 +274,8 @@ __device__ inline void raw_to_float(const Raw8<DT>& r, float (&v)[8]) {
 // WIDE: a subset has 8-bit codes (kernels of their own: a third copy of the segment code in the
 // others would cost them registers).  One kernel for all widths instead of the vector-ALU one
 // that served such caches before (a code at a time, the logits of a block through LDS and three
-// barriers): 4 prompts of 7901 tokens at 8/4 bits, 8 KV heads of 4: 263 -> 15.7 us per call.
+// barriers): 4 prompts of 7901 tokens at 8/4 bits, 8 KV heads of 4: 263 -> 17.4 us per call
+// (15.6 with subnormal 4-bit codes, at the accuracy given at CodeForm).
 template <int DT, int D, bool KTOK, bool VTOK, int MINB, bool STG, bool WIDE>
 __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   constexpr int KS = D / 32;     // k-steps of the logit product
@@ -286,7 +308,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   const bool nvalid = n < 2 * G;
   const int g0 = 2 * grp, g1 = 2 * grp + 1;      // heads of this lane's rows in the output tiles
   constexpr bool WSPLIT = (DT == ZC_F32) || WIDE;   // softmax weights as value + residual (8-bit caches: a single fp16 weight would show, 2e-4 -> 6e-4 in fp16)
-  constexpr bool SUBN = (DT != ZC_F32);      // codes enter as fp16 subnormals
+  constexpr CodeForm FORM = WIDE ? CodeForm::kCentred : DT == ZC_F32 ? CodeForm::kNormalized : CodeForm::kSubnormal;
+  static_assert(WSPLIT || FORM == CodeForm::kSubnormal, "unsplit weights carry the subnormal encoding's factors");
   // q' always enters as value + residual (two columns per head).  A single fp16 q'
   // was tried for 16-bit tensors: it saves two instructions per logit but moves the
   // log-sum-exp by up to 3e-3, which the streaming saliency scores inherit.
@@ -444,7 +467,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   // The query operand of a segment.  Every wave builds its own (all k-steps): the
   // waves of a workgroup then share nothing until the final merge, so each can
   // work through its own run of segments without a barrier.
-  // MODE 4 / 2: codes of that width, q' = q cs sm_scale log2(e) times the factor of
+  // MODE 8 / 4 / 2: codes of that width, q' = q cs sm_scale log2(e) times the factor of
   // its operand register, in the channel order the unpacked K words have; MODE 0:
   // the tail, q itself in natural order.
   // Returns the operand registers and sum(q'), sum(q' cz) over all channels, and the same
@@ -517,7 +540,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
       uint32_t regs[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float comp = (MODE == 0) ? 1.f : code_comp<MODE == 0 ? 4 : MODE, SUBN>(i);
+        const float comp = (MODE == 0) ? 1.f : code_comp<MODE == 0 ? 4 : MODE, FORM>(i);
         const float qn0 = q8[ks0][2 * i] * lane_scale * cs8[ks0][2 * i], qn1 = q8[ks0][2 * i + 1] * lane_scale * cs8[ks0][2 * i + 1];
         const float qv0 = qn0 * comp, qv1 = qn1 * comp;
         if constexpr (QSPLIT) {
@@ -525,15 +548,17 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
           const float h0 = half_lo_to_float(hi2), h1 = half_hi_to_float(hi2);
           const uint32_t lo2 = pack_f2(qv0 - h0, qv1 - h1);             // the residuals (exact differences), rounded
           regs[i] = part ? lo2 : hi2;
-          if constexpr (SUBN) {
+          // (channelwise keys, centred codes: the bias comes off the zero points, which are integers)
+          if constexpr (FORM == CodeForm::kCentred && MODE != 0 && !KTOK) {
+            cz8[ks0][2 * i] -= code_bias<MODE == 0 ? 4 : MODE>(); cz8[ks0][2 * i + 1] -= code_bias<MODE == 0 ? 4 : MODE>();
+          }
+          if constexpr (DT != ZC_F32) {
             sq += qn0 + qn1;
-            if constexpr (MODE == 8 && !KTOK) { cz8[ks0][2 * i] -= kCode8Bias; cz8[ks0][2 * i + 1] -= kCode8Bias; }
             sqz = fmaf(qn0, cz8[ks0][2 * i], fmaf(qn1, cz8[ks0][2 * i + 1], sqz));
           } else {
             const float inv_comp = 1.f / comp;      // a power of two
             const float r0 = (h0 + half_lo_to_float(lo2)) * inv_comp, r1 = (h1 + half_hi_to_float(lo2)) * inv_comp;
             sq += r0 + r1;
-            if constexpr (MODE == 8 && !KTOK) { cz8[ks0][2 * i] -= kCode8Bias; cz8[ks0][2 * i + 1] -= kCode8Bias; }
             sqz = fmaf(r0, cz8[ks0][2 * i], fmaf(r1, cz8[ks0][2 * i + 1], sqz));
           }
         } else {
@@ -543,7 +568,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         }
       }
       qB[ks0].x = regs[0]; qB[ks0].y = regs[1]; qB[ks0].z = regs[2]; qB[ks0].w = regs[3];
-      if constexpr (!SUBN && MODE != 0 && MODE != 8) {
+      if constexpr (FORM == CodeForm::kNormalized && MODE != 0) {
         sum_k[ks0] = grp_sum(sq - sq_before);
         sumcz_k[ks0] = grp_sum(sqz - sqz_before);
       } else {
@@ -797,10 +822,12 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     constexpr int TB = 4 * (32 / BITS);                 // slots per block
     constexpr int HS = BITS == 8 ? 16 : 32, NH = TB / HS;   // slots per half-block (an 8-bit block is one of 16), half-blocks per block
     constexpr int NJ = HS / 16;                         // 16-slot tiles of a half-block
-    constexpr bool PLAIN = SUBN || BITS == 8;           // the operand is the code itself (no "1" terms)
+    constexpr bool CENTRED = FORM == CodeForm::kCentred;
+    constexpr bool PLAIN = FORM != CodeForm::kNormalized;    // no "1" terms
+    static_assert(BITS != 8 || CENTRED, "8-bit codes have one encoding");
     constexpr int KW = D * BITS / 128;                  // 32-bit words of K codes per lane and token
     constexpr int ROWB = D * BITS / 8;                  // bytes of one K row
-    constexpr float UNSCALE = code_unscale<BITS, SUBN>();
+    constexpr float UNSCALE = code_unscale<BITS, FORM>();
     constexpr float SC = (BITS == 4) ? 16.f : 4.f;     // normalized encoding: 1 + code / SC
     const int64_t chan_off = ((int64_t)(ci * 2 + sub) * p_B + b) * (p_Hkv * D) + hk * D;
     // lo, hi: this wave's range of the segment in half-blocks (not empty)
@@ -946,7 +973,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     }
     ZC_MARK(2);                                 // the segment's query operand is built
     // Subnormal codes: the logit is ts (dot - tz sum(q') - sum(q' cz)), the two sums taken off
-    // after the matrix instructions.  Normalized codes (fp32 tensors) add SC sum(q') to the
+    // after the matrix instructions; centred ones likewise, the bias off tz or cz.  Normalized codes (fp32 tensors) add SC sum(q') to the
     // accumulator on top; there everything that is taken off is taken off k-step by k-step,
     // between the matrix instructions, so that the accumulator never holds more than one
     // k-step's worth of what cancels: with fp64 as the yardstick a quarter of the rounding
@@ -965,7 +992,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     // constants below is the sum of p (the softmax denominator), at no VALU cost
     float wcomp[4];
 #pragma unroll
-    for (int v = 0; v < 4; ++v) wcomp[v] = code_comp<BITS, SUBN>(v);
+    for (int v = 0; v < 4; ++v) wcomp[v] = code_comp<BITS, FORM>(v);
     // Unsplit weights: that factor (a power of two) is folded into the logit, so exp2
     // delivers p times the factor; the running maximum is then the maximum of the
     // shifted logits, which is as good a reference point as the true one.
@@ -974,7 +1001,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     float base[4], rel[4];
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const float lshift = WSPLIT ? 0.f : (float)code_comp_log2<BITS, SUBN>(v);
+      float lshift = 0.f;
+      if constexpr (!WSPLIT) lshift = (float)subnormal_comp_log2<BITS>(v);
       base[v] = KTOK ? lshift : kconst + lshift;
       rel[v] = base[v] - m_ref;
     }
@@ -982,7 +1010,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     // (normalized codes: plain ones, the sum then carries SC and is also the "1" term of the output product)
     u4 ones;
     if constexpr (BITS == 8) ones = u4{0x24002400u, 0x24002400u, 0u, 0u};                          // 1/64
-    else if constexpr (!SUBN) ones = u4{0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
+    else if constexpr (!PLAIN) ones = u4{0x3C003C00u, 0x3C003C00u, 0x3C003C00u, 0x3C003C00u};
+    else if constexpr (BITS == 4 && CENTRED) ones = u4{0x24002400u, 0x34003400u, 0x24002400u, 0x34003400u};   // 1/64, 1/4, 1/64, 1/4
     else if constexpr (BITS == 4) ones = u4{0x2C002C00u, 0x3C003C00u, 0x2C002C00u, 0x3C003C00u};   // 1/16, 1, 1/16, 1
     else ones = u4{0x24002400u, 0x2C002C00u, 0x34003400u, 0x3C003C00u};                            // 1/64, 1/16, 1/4, 1
 
@@ -1041,8 +1070,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
           if constexpr (BITS == 8) {
             const uint2 c0 = unpack8(bf.kw[jj][2 * ks]), c1 = unpack8(bf.kw[jj][2 * ks + 1]);
             sacc = mfma16(u4{c0.x, c0.y, c1.x, c1.y}, qB[ks], sacc);
-          } else if constexpr (BITS == 4) sacc = mfma16(unpack4<SUBN>(bf.kw[jj][ks]), qB[ks], sacc);
-          else sacc = mfma16(unpack2<SUBN>(bf.kw[jj][ks >> 1], ks & 1), qB[ks], sacc);
+          } else if constexpr (BITS == 4) sacc = mfma16(unpack4<FORM>(bf.kw[jj][ks]), qB[ks], sacc);
+          else sacc = mfma16(unpack2<FORM>(bf.kw[jj][ks >> 1], ks & 1), qB[ks], sacc);
           if constexpr (!PLAIN) {
             if constexpr (KTOK) {
               sacc.x += fmaf(ktz[0], corr_s[ks], corr_c[ks]); sacc.y += fmaf(ktz[1], corr_s[ks], corr_c[ks]);
@@ -1061,8 +1090,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         for (int v = 0; v < 4; ++v) {
           float x;
           const float dot = QSPLIT ? own[v] + xor1(own[v]) : own[v];     // value + residual column
-          if constexpr (KTOK && BITS == 8) x = fmaf(kts[v], fmaf(kCode8Bias - ktz[v], Aq, fmaf(dot, UNSCALE, kconst)), rel[v]);
-          else if constexpr (KTOK && !SUBN) x = fmaf(kts[v], dot * UNSCALE, rel[v]);        // already centred
+          if constexpr (KTOK && CENTRED) x = fmaf(kts[v], fmaf(code_bias<BITS>() - ktz[v], Aq, fmaf(dot, UNSCALE, kconst)), rel[v]);
+          else if constexpr (KTOK && !PLAIN) x = fmaf(kts[v], dot * UNSCALE, rel[v]);        // the sums are off already
           else if constexpr (KTOK) x = fmaf(kts[v], fmaf(-ktz[v], Aq, fmaf(dot, UNSCALE, kconst)), rel[v]);
           else x = fmaf(dot, UNSCALE, rel[v]);
           lg[jj][v] = x;
@@ -1104,10 +1133,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         }
       if constexpr (BITS == 8) {
         // 16 slots: one k = 16 instruction per output tile; a V word holds the codes of slots 4 grp ..
-        uint2 p8;
-        if constexpr (WSPLIT) p8 = make_uint2(pack_h2(split_part(w2[0][0], part), split_part(w2[0][2], part)),
-                                              pack_h2(split_part(w2[0][1], part), split_part(w2[0][3], part)));
-        else p8 = make_uint2(pack_f2(w2[0][0], w2[0][2]), pack_f2(w2[0][1], w2[0][3]));
+        const uint2 p8 = make_uint2(pack_h2(split_part(w2[0][0], part), split_part(w2[0][2], part)),
+                                    pack_h2(split_part(w2[0][1], part), split_part(w2[0][3], part)));
         acc1 = mfma16_k16(p8, make_uint2(ones.x, ones.y), acc1);
 #pragma unroll
         for (int r = 0; r < NR; ++r) {
@@ -1134,8 +1161,8 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
         const uint32_t ww[4] = {bf.vw[r].x, bf.vw[r].y, bf.vw[r].z, bf.vw[r].w};
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          if constexpr (BITS == 4) acc[r][j] = mfma16(pA, unpack4<SUBN>(ww[j]), acc[r][j]);
-          else acc[r][j] = mfma16(pA, unpack2<SUBN>(ww[j], h), acc[r][j]);
+          if constexpr (BITS == 4) acc[r][j] = mfma16(pA, unpack4<FORM>(ww[j]), acc[r][j]);
+          else acc[r][j] = mfma16(pA, unpack2<FORM>(ww[j], h), acc[r][j]);
         }
       }
     };
@@ -1168,6 +1195,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
     dma_reuse_fence();                           // the ring is reused (next segment, merge)
     // ---- fold the segment into O ----
     //   subnormal codes:   sum_t w code = acc 2^(24 - P),  sum_t w = acc1
+    //   centred codes:     sum_t w (code - bias) = acc * UNSCALE,  sum_t w = acc1
     //   normalized codes:  sum_t w code = acc - acc1,         sum_t w = acc1 / SC
     //   (value + residual / 2^11 when the weights are split)
     const float r0 = WSPLIT ? acc1.x + acc1.y * kLoInv : acc1.x;
@@ -1183,7 +1211,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
       a1s = grp_sum(a1s);                          // (the same in every row)
       head_columns(a1s, a10, a11);
     }
-    if constexpr (BITS == 8) { a10 = fmaf(-kCode8Bias, sw0, a10); a11 = fmaf(-kCode8Bias, sw1, a11); }
+    if constexpr (CENTRED) { a10 = fmaf(-code_bias<BITS>(), sw0, a10); a11 = fmaf(-code_bias<BITS>(), sw1, a11); }
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       const float4 vcs4 = *reinterpret_cast<const float4*>(&svc[wave][4 * (n + 16 * r)]);
