@@ -56,7 +56,10 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 // Bound: vector-instruction issue (the unpacking), below a few thousand tokens latency.
 // Logits on the matrix cores: D[slot][column] = sum_c code[slot][c] q'[column][c] with
-// v_mfma_f32_16x16x32_f16.  A code is exact in fp16 at every width; q' enters as fp16 value and
+// v_mfma_f32_16x16x32_f16.  A code enters exactly at every width, less half the range (what cancels
+// against the zero points stays out of the accumulators; the sums of q' take that bias off the
+// zero points: 8-bit keys with token scales 8.3e-6 -> 1.3e-6 relative error of a probability, 6.7e-6
+// on the vector ALUs); q' enters as fp16 value and
 // residual (scaled by 2^11), two columns per head, after a power of two per head has brought its
 // largest element to [1, 2): 22 bits, whatever the scale of the query.  A lane's quarter row
 // (channels kg D / 4 ...) is contiguous in the ROW layout and goes from memory straight to its
@@ -70,16 +73,18 @@ constexpr float kProbLo = 2048.f;
 
 // Codes of a quarter row (NK = D / 4 channels) as fp16 operand registers, two codes each: register
 // i of word w holds its codes code_slot<BITS>(i) and code_slot<BITS>(i) + (half-word distance).
-// 1024 + code is the code under the exponent of 1024; taking 1024 off leaves the exact number.
+// 1024 + code is the code under the exponent of 1024; one packed subtraction leaves code - bias.
+template <int BITS> constexpr float code_bias() { return (float)(1 << (BITS - 1)); }
 template <int BITS, int NK>
 __device__ inline void codes_to_half(const uint32_t* w, uint32_t (&r)[NK / 2]) {
   constexpr int E = 32 / BITS;                        // codes per word, E / 2 registers
   constexpr uint32_t M = BITS == 8 ? 0x00ff00ffu : BITS == 4 ? 0x000f000fu : 0x00030003u;
+  const h2 off = h2{(_Float16)(1024.f + code_bias<BITS>()), (_Float16)(1024.f + code_bias<BITS>())};
 #pragma unroll
   for (int i = 0; i < NK / E; ++i)
 #pragma unroll
     for (int j = 0; j < E / 2; ++j) {
-      const h2 x = __builtin_bit_cast(h2, ((w[i] >> (BITS * j)) & M) | 0x64006400u) - h2{(_Float16)1024.f, (_Float16)1024.f};
+      const h2 x = __builtin_bit_cast(h2, ((w[i] >> (BITS * j)) & M) | 0x64006400u) - off;
       r[i * (E / 2) + j] = __builtin_bit_cast(uint32_t, x);
     }
 }
@@ -137,6 +142,7 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
   const float lse2 = a.lse[hq] * kLog2e;
   u4 qB[KS];
   float aq = 0.f, bq = 0.f, unscale;
+  const float tok_bias = a.k_tok ? code_bias<BITS>() : 0.f, chan_bias = code_bias<BITS>() - tok_bias;   // off the zero points in use, which are integers
   {
     const int64_t qoff = (int64_t)b * a.q_sB + (int64_t)(hk * a.G + (nvalid ? g : 0)) * a.q_sH + kg * NK;
     const int64_t coff = ((int64_t)(chunk * 2 + sub) * a.B + b) * (a.Hkv * D) + hk * D + kg * NK;
@@ -154,7 +160,7 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
         qp[c8 + i] = x;
         top = fmaxf(top, fabsf(x));
         aq += x;
-        bq = fmaf(x, cz[i], bq);
+        bq = fmaf(x, cz[i] - chan_bias, bq);
       }
     }
     aq += __shfl_xor(aq, 16); aq += __shfl_xor(aq, 32);
@@ -204,7 +210,7 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
     for (int v = 0; v < 4; ++v) {
       const float lo = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(own[v]), 0xB1, 0xF, 0xF, true));   // the neighbour lane's
       const float dot = fmaf(lo, 1.f / kProbLo, own[v]) * unscale;
-      const float logit2 = ts[v] * (dot - tz[v] * aq - bq);
+      const float logit2 = ts[v] * (dot - (tz[v] - tok_bias) * aq - bq);
       const float p = exp2f(logit2 - lse2);
       if (store_col && tile * kProbTile + 4 * kg + v < len && pos[v] >= 0 && pos[v] < a.N) out[pos[v]] = p;
     }
