@@ -322,7 +322,7 @@ __global__ __launch_bounds__(kRowThreads) void k_rows_saliency(const float* __re
 }
 
 // ---- zc_dequantize_cache -------------------------------------------------------------------
-constexpr int kDqSegs = 24;        // segments (chunk x subset) one launch takes
+constexpr int kDqSegs = 8;         // segments (a chunk's subsets, in pieces where they are huge) one launch takes
 constexpr int kDqThreads = 256;
 
 struct DequantSeg {
@@ -394,7 +394,8 @@ __device__ inline void store8(void* base, int64_t off, const float (&s)[8], cons
 //           words: the codes of 4 consecutive slots), one store per slot; a thread per whole word
 //           group (8 to 16 stores) left half the chip without one.
 // Consecutive threads take consecutive channels of a row.
-// All segments (chunk x subset) share one launch: workgroup ranges per segment travel in the arguments.
+// The two subsets of a chunk share one launch: workgroup ranges per segment travel in the arguments.
+// Chunks go one after the other: where two hold the same position, the later one's row stays.
 template <int DT, int BITS>
 __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg sg, int unit, int b) {
   constexpr int E = 32 / BITS, TB = 4 * E;
@@ -622,7 +623,9 @@ extern "C" int zc_dequantize_cache(const zc_packed* p, const zc_tensor4* out, vo
   const int64_t vpr = p->D / 8;
   int64_t most = (1ll << 30) / (p->H * vpr) / ZC_SLOT_ALIGN * ZC_SLOT_ALIGN;
   if (most < ZC_SLOT_ALIGN) most = ZC_SLOT_ALIGN;
-  for (int chunk = 0; chunk < p->n_chunks; ++chunk)
+  for (int chunk = 0; chunk < p->n_chunks; ++chunk) {
+    rc = flush();                // (the chunk before this one)
+    if (rc) return rc;
     for (int which = 0; which < 2; ++which) {
       const int32_t* row = p->chunk_table_host + 4 * chunk;
       for (int64_t done = 0, len = row[2 * which + 1]; done < len; done += most) {
@@ -638,5 +641,6 @@ extern "C" int zc_dequantize_cache(const zc_packed* p, const zc_tensor4* out, vo
         blocks += n;
       }
     }
+  }
   return flush();
 }

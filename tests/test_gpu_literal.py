@@ -302,6 +302,28 @@ def test_dequantize_cache_is_the_unpacked_cache_in_token_order(bits_hi, bits_lo,
         assert float((out[:, :, Lout:].float() - 7.0).abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("scheme,layout", [("channel", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP)])
+def test_dequantize_cache_later_chunks_replace_earlier_ones(scheme, layout):
+    """Three chunks compressed without a position offset hold the same positions: every row is the
+    last chunk's that holds it, each time."""
+    B, H, d = 1, 8, 128
+    g = torch.Generator().manual_seed(3)
+    lens = (6000, 4000, 1000)
+    p = zb.PackedTensor(B, H, d, 7040, 7040, 4, 2, scheme, layout, max_chunks=3, device=DEV)
+    want = torch.zeros(B, H, lens[0], d, dtype=torch.bfloat16, device=DEV)
+    for L in lens:
+        x = torch.randn(B, H, L, d, generator=g).to(torch.bfloat16).to(DEV)
+        sal, reg = zb.zc_select_salient(torch.rand(B, L, generator=g).to(DEV), L // 2)
+        zb.zc_quantize_pack(x, sal, reg, p)
+        one = zb.PackedTensor(B, H, d, 3072, 3072, 4, 2, scheme, layout, max_chunks=1, device=DEV)
+        zb.zc_quantize_pack(x, sal, reg, one)
+        zb.zc_dequantize_cache(one, want)
+    for _ in range(5):
+        out = torch.zeros_like(want)
+        zb.zc_dequantize_cache(p, out)
+        assert torch.equal(out, want)
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,d,dtype,bits,L,T", [
     (1, 1, 1, 64, torch.float32, (8, 2), 17, 1), (3, 16, 2, 128, torch.bfloat16, (2, 8), 1000, 33),
     (16, 40, 40, 128, torch.float16, (4, 2), 515, 0), (2, 6, 2, 128, torch.float32, (4, 4), 63, 16)])
