@@ -324,6 +324,7 @@ __global__ __launch_bounds__(kRowThreads) void k_rows_saliency(const float* __re
 // ---- zc_dequantize_cache -------------------------------------------------------------------
 constexpr int kDqSegs = 8;         // segments (a chunk's subsets, in pieces where they are huge) one launch takes
 constexpr int kDqThreads = 256;
+constexpr int64_t kDqBlocks = (1ll << 32) / kDqThreads - 1;     // most workgroups of a launch: its threads are counted in 32 bits
 
 struct DequantSeg {
   int begin, len;        // slots
@@ -633,7 +634,7 @@ extern "C" int zc_dequantize_cache(const zc_packed* p, const zc_tensor4* out, vo
         // a unit is 8 channels of a slot (ROW) or of 4 slots (TGROUP: 32 / bits such groups per block of 4 * 32 / bits slots)
         const int64_t per_head = p->layout == ZC_LAYOUT_ROW ? part : ceil_div64(part, 4 * (32 / a.bits[which])) * (32 / a.bits[which]);
         const int64_t n = ceil_div64(per_head * p->H * vpr, kDqThreads);
-        if (a.n_segs == kDqSegs || blocks + n > 0x7fffffff) {
+        if (a.n_segs == kDqSegs || blocks + n > kDqBlocks) {
           rc = flush();
           if (rc) return rc;
         }

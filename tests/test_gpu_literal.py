@@ -324,6 +324,22 @@ def test_dequantize_cache_later_chunks_replace_earlier_ones(scheme, layout):
         assert torch.equal(out, want)
 
 
+def test_dequantize_cache_of_millions_of_tokens():
+    """More threads than one launch counts (8192 channels, 4.3 million tokens): the rows of the last
+    positions, which the first and the last tokens hold, arrive."""
+    H, d, n = 64, 128, 4_300_032
+    p = zb.PackedTensor(1, H, d, n, 0, 2, 2, "channel", zb.ZC_LAYOUT_ROW, max_chunks=1, device=DEV)
+    p.chan_scale.fill_(1.0)
+    p.chan_zero.fill_(-1.0)
+    p.pos_hi[0, :4] = torch.arange(4)
+    p.pos_hi[0, -4:] = torch.arange(4, 8)
+    p.chunk_table_host[0] = (0, n, 0, 0)
+    p.c.n_chunks, p.c.n_hi = 1, n
+    out = torch.zeros(1, H, 9, d, dtype=torch.float16, device=DEV)
+    zb.zc_dequantize_cache(p, out)
+    assert bool((out[:, :, :8] == 1.0).all()) and bool((out[:, :, 8] == 0.0).all())
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,d,dtype,bits,L,T", [
     (1, 1, 1, 64, torch.float32, (8, 2), 17, 1), (3, 16, 2, 128, torch.bfloat16, (2, 8), 1000, 33),
     (16, 40, 40, 128, torch.float16, (4, 2), 515, 0), (2, 6, 2, 128, torch.float32, (4, 4), 63, 16)])
