@@ -288,7 +288,9 @@ __global__ __launch_bounds__(kRowThreads) void k_rows_saliency(const float* __re
   __shared__ float part[kRowHeads][COLS];
   const int cx = threadIdx.x % COLS, g = threadIdx.x / COLS;
   const int b = blockIdx.y, B = gridDim.y;
-  const int i = blockIdx.x * COLS + cx;
+  const int64_t col0 = ((int64_t)blockIdx.z * gridDim.x + blockIdx.x) * COLS;
+  if (col0 >= n_out) return;
+  const int i = (int)min(col0 + cx, (int64_t)0x7fffffff);
   const int ic = min(i, n_out - 1);                  // (columns past the end repeat the last one and are not stored)
   const int64_t row_pitch = (int64_t)B * Hq * row_stride;
   float total = 0.f;
@@ -573,7 +575,9 @@ extern "C" int zc_rows_saliency(const float* rows, const int32_t* row_len, int32
   if (n_out == 0) return ZC_OK;
   // 32 columns (whole 128-byte lines) a workgroup while 64 would leave compute units without one
   const bool narrow = ceil_div64(n_out, 64) * B < 256;
-  const dim3 grid((unsigned)ceil_div64(n_out, narrow ? 32 : 64), (unsigned)B);
+  const int64_t tiles = ceil_div64(n_out, narrow ? 32 : 64);
+  const int64_t per_z = tiles < (1 << 21) ? tiles : 1 << 21;        // (a grid counts the threads of a dimension in 32 bits)
+  const dim3 grid((unsigned)per_z, (unsigned)B, (unsigned)ceil_div64(tiles, per_z));
   hipStream_t st = (hipStream_t)stream;
   if (narrow)
     hipLaunchKernelGGL(k_rows_saliency<32>, grid, dim3(kRowThreads), 0, st, rows, row_len, (int)P, (int)Hq, row_stride, (int)n_out,

@@ -237,6 +237,13 @@ def test_rows_saliency_shapes(P, B, Hq, N, n_out):
         assert float((got - ref).abs().max()) <= 2.0 ** -24 * (P + Hq) * float(ref.max()) + 1e-12
 
 
+def test_rows_saliency_of_more_columns_than_a_grid_dimension_counts():
+    n = (1 << 28) + 65              # tiles of 64 columns, 1024 threads each: one and a remainder past 2^32 threads
+    rows = torch.rand(1, 1, 1, n, device=DEV, generator=torch.Generator(DEV).manual_seed(1))
+    got = zb.zc_rows_saliency(rows, torch.tensor([n], dtype=torch.int32, device=DEV), n, scores=torch.zeros(1, n, device=DEV))
+    assert torch.equal(got, rows[0, 0])
+
+
 def _unpacked(p, total, dtype):
     """x_hat of the cache `p` of `total` tokens in token order [B, H, total, d], rounded to dtype:
     fp16 from the exact product of the scales' fp32 product and the level, in one rounding."""
