@@ -363,26 +363,23 @@ __device__ inline uint16_t mul_to_half(float s, float x) {
   return h;
 }
 
-// Eight consecutive products s x stored in DT (16-byte aligned).
+// Eight consecutive elements rounded to DT and stored (16-byte aligned).
 template <int DT>
-__device__ inline void store8(void* base, int64_t off, const float (&s)[8], const float (&x)[8]) {
+__device__ inline void store8(void* base, int64_t off, const float (&v)[8]) {
   if constexpr (DT == ZC_F32) {
     float4* p = reinterpret_cast<float4*>(reinterpret_cast<float*>(base) + off);
-    p[0] = make_float4(s[0] * x[0], s[1] * x[1], s[2] * x[2], s[3] * x[3]);
-    p[1] = make_float4(s[4] * x[4], s[5] * x[5], s[6] * x[6], s[7] * x[7]);
+    p[0] = make_float4(v[0], v[1], v[2], v[3]);
+    p[1] = make_float4(v[4], v[5], v[6], v[7]);
   } else {
+    // (two to an instruction, rounding to nearest even: 8000 tokens of two prompts re-compressed
+    // in bf16 91.6 -> 88.0 us against rounding by integer arithmetic)
+    static_assert(DT == ZC_BF16, "fp16 elements are rounded where they are multiplied");
     uint32_t h[4];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
-      if constexpr (DT == ZC_F16) {
-        h[i] = mul_to_half(s[2 * i], x[2 * i]) | (uint32_t)mul_to_half(s[2 * i + 1], x[2 * i + 1]) << 16;
-      } else {
-        // (two to an instruction, rounding to nearest even: 8000 tokens of two prompts re-compressed
-        // in bf16 91.6 -> 88.0 us against rounding by integer arithmetic)
-        typedef float f2 __attribute__((ext_vector_type(2)));
-        typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-        h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{s[2 * i] * x[2 * i], s[2 * i + 1] * x[2 * i + 1]}), b2));
-      }
+      typedef float f2 __attribute__((ext_vector_type(2)));
+      typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+      h[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2{v[2 * i], v[2 * i + 1]}), b2));
     }
     *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(base) + off) = make_uint4(h[0], h[1], h[2], h[3]);
   }
@@ -420,10 +417,19 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
   const int64_t obase = (int64_t)b * a.o_sB + (int64_t)h * a.o_sH + c;
   auto expand = [&](int position, float ts, float tz, auto code_of) {
     if (position < 0 || position >= a.out_L) return;
-    float s[8], x[8];
+    const int64_t off = obase + (int64_t)position * a.o_sL;
+    if constexpr (DT == ZC_F16) {
+      uint32_t h[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) { s[i] = cs[i] * ts; x[i] = (float)code_of(i) - tz - cz[i]; }
-    store8<DT>(a.out, obase + (int64_t)position * a.o_sL, s, x);
+      for (int i = 0; i < 8; ++i) h[i] = mul_to_half(cs[i] * ts, (float)code_of(i) - tz - cz[i]);
+      *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(a.out) + off) =
+          make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+    } else {
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = cs[i] * ts * ((float)code_of(i) - tz - cz[i]);
+      store8<DT>(a.out, off, v);
+    }
   };
   if (row_layout) {
     const int64_t slot = (int64_t)sg.begin + r, ti = (int64_t)b * cap + slot;
