@@ -202,7 +202,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
   // logical order: channel group fastest, then subset, tensor, batch element: the workgroups
   // that share a token row's cache lines run on one XCD at about the same time
   const int vl = p.t[0].vl, groups = ceil_div(p.t[0].NV, vl);
-  int id = xcd_contiguous(blockIdx.x, gridDim.x);
+  int id = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int grp = id % groups; id /= groups;
   const int sub = id & 1; id >>= 1;
   const int which = tensors == 2 ? id & 1 : 0, b = tensors == 2 ? id >> 1 : id;
@@ -750,7 +750,8 @@ static int col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int dty
 
 template <int DT>
 static void launch_columns(const QPPair& p, int tensors, int threads, hipStream_t st) {
-  const dim3 grid((unsigned)(ceil_div64(p.t[0].NV, p.t[0].vl) * 2 * tensors * p.t[0].B));
+  // (a grid counts the threads of a dimension in 32 bits: the batch has one of its own)
+  const dim3 grid((unsigned)(ceil_div64(p.t[0].NV, p.t[0].vl) * 2 * tensors), (unsigned)p.t[0].B);
   if (threads == 512) hipLaunchKernelGGL((k_columns<DT, 512>), grid, dim3(512), 0, st, p, tensors);
   else hipLaunchKernelGGL((k_columns<DT, 1024>), grid, dim3(1024), 0, st, p, tensors);
 }

@@ -884,6 +884,27 @@ def test_quantize_column_sweep_edges(B, H, D, n_reg, dtype):
     assert mism <= 1e-4 * total, (mism, total)      # fp32 quotients next to a rounding boundary (the budget of the randomized shapes)
 
 
+def test_quantize_of_the_largest_batches():
+    """Channel groups, subsets, tensors and batch elements together take more than 2^32 threads: every
+    batch element (all read the same two tokens) gets the parameters and codes of a call of its own."""
+    B, H, D, L = 33000, 64, 128, 2
+    g = torch.Generator().manual_seed(9)
+    x = torch.randn(1, H, L, D, generator=g).to(torch.bfloat16).to(DEV)
+    idx = torch.arange(L, dtype=torch.int32, device=DEV)[None]
+    none = torch.empty(B, 0, dtype=torch.int32, device=DEV)
+
+    def packed(n):
+        mk = lambda s, layout: zb.PackedTensor(n, H, D, 64, 0, 4, 2, s, layout, max_chunks=1, device=DEV, store_pos=False)
+        Kp, Vp = mk("channel", zb.ZC_LAYOUT_ROW), mk("cst", zb.ZC_LAYOUT_TGROUP)
+        xb = x.expand(n, H, L, D)
+        zb.zc_quantize_pack_kv(xb, xb, idx.expand(n, L).contiguous(), none[:n], Kp, Vp)
+        return Kp, Vp
+    for one, many in zip(packed(1), packed(B)):
+        assert bool((many.codes_hi.view(B, -1) == one.codes_hi).all())
+        assert bool((many.chan_scale[0, 0] == one.chan_scale[0, 0]).all()) and bool((many.chan_zero[0, 0] == one.chan_zero[0, 0]).all())
+        assert bool((many.tok_scale_hi[:, :L] == one.tok_scale_hi[:, :L]).all())
+
+
 @pytest.mark.parametrize("B,Hq,Hkv,d,Lk,P,dtype", [
     (1, 8, 8, 64, 256, 26, torch.float32), (1, 1, 1, 64, 1, 1, torch.bfloat16), (2, 18, 6, 64, 33, 32, torch.float16),
     (3, 17, 17, 64, 100, 10, torch.bfloat16), (1, 12, 4, 128, 65, 31, torch.float32), (130, 24, 8, 128, 31, 9, torch.float16)])
