@@ -7,6 +7,8 @@
 //                       and maxima over all its tokens, the parameters that follow
 //                       (Eq. 5's R = max - min, 1/R and z, or Eq. 6's c and 1/c)
 //                       and, for channelwise ROW codes that stay resident, the codes.
+//                       Long subsets of few channels are cut into token ranges, whose
+//                       minima k_column_params joins in a launch between the two.
 //   2. k_quant_pack     a team of waves (one thread per 8 channels) owns one to
 //                       four word groups of a TGROUP block - the 32 / bits tokens
 //                       whose codes share 32-bit words - and walks them in
@@ -40,7 +42,8 @@ struct QPArgs {
   int32_t* pos[2];
   float* chan_scale;           // this chunk: [2, B, W]
   float* chan_zero;
-  float4* params;              // workspace [B, 2, W]: CHANNEL {1/R, z, R, -}, CST {1/c, -, -, -}
+  float4* params;              // workspace [B, 2, W]: CHANNEL {1/R, z, R, -}, CST {1/c, -, -, -}; behind it the column
+                               // sweep's [B, 2, split, W] (minimum, minimum of -x) where it goes by token ranges
   int32_t* chunk_row;          // device chunk_table row to fill
   int64_t pos_offset;
   int units[2];                // quantize sweep: word groups per subset (4 per TGROUP block)
@@ -51,6 +54,10 @@ struct QPArgs {
 };
 
 constexpr int kStatBatch = 8;       // token rows requested at once where they do not stay resident
+constexpr int kSplitLanes = 16, kSplitThreads = 512;      // shape of the split column sweep's workgroups
+constexpr int kSplitRows = 16;      // least rows a thread of it takes
+
+__device__ inline float2* range_minima(const QPArgs& a) { return reinterpret_cast<float2*>(a.params + (int64_t)a.B * 2 * a.W); }
 
 struct QPPair { QPArgs t[2]; };   // keys and values of one cache, compressed by the same launches
 
@@ -192,8 +199,8 @@ __device__ inline void store_row_codes(uint8_t* row, const float (&x)[8], const 
   else *reinterpret_cast<uint16_t*>(row) = (uint16_t)half[0];
 }
 
-template <int DT, int THREADS>
-__global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
+template <int DT, int THREADS, bool SPLIT = false>       // SPLIT: `split` token ranges per subset, only their minima
+__global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, int split) {
   constexpr int RAW = (DT == ZC_F32) ? 2 : 1, ESZ = (DT == ZC_F32) ? 4 : 2;
   constexpr int NR = kColRows(DT), NWAVE = THREADS / 64;
   __shared__ __align__(16) float red[NWAVE][2][128];
@@ -204,6 +211,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
   const int vl = p.t[0].vl, groups = ceil_div(p.t[0].NV, vl);
   int id = xcd_contiguous(blockIdx.y * gridDim.x + blockIdx.x, gridDim.x * gridDim.y);
   const int grp = id % groups; id /= groups;
+  int part = 0;
+  if constexpr (SPLIT) { part = id % split; id /= split; }
   const int sub = id & 1; id >>= 1;
   const int which = tensors == 2 ? id & 1 : 0, b = tensors == 2 ? id >> 1 : id;
   const QPArgs& a = which ? p.t[1] : p.t[0];
@@ -228,7 +237,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
   };
   // Rows are requested before any is reduced, all of a resident subset or kStatBatch at a time;
   // rows past the end repeat the last one (minima do not care).
-  if (a.resident) {
+  if (!SPLIT && a.resident) {
     int32_t tok[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
@@ -244,11 +253,17 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
     for (int r = 0; r < NR; ++r)
       if (r * step < n) reduce(raw[r]);
   } else {
-    for (int t0 = 0; t0 < n; t0 += kStatBatch * step) {
+    int first = 0, n1 = n;
+    if constexpr (SPLIT) {
+      const int per = ceil_div(n, split);
+      first = part * per;
+      n1 = min(n, first + per);
+    }
+    for (int t0 = first; t0 < n1; t0 += kStatBatch * step) {
       uint4 rw[kStatBatch][RAW];
 #pragma unroll
       for (int r = 0; r < kStatBatch; ++r) {
-        const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)idx[min(t0 + r * step + y, n - 1)] * row_bytes);
+        const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)idx[min(t0 + r * step + y, n1 - 1)] * row_bytes);
 #pragma unroll
         for (int q = 0; q < RAW; ++q) rw[r][q] = src[q];
       }
@@ -285,6 +300,10 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
     float lo = red[0][0][tid], neg = red[0][1][tid];
 #pragma unroll
     for (int v = 1; v < NWAVE; ++v) { lo = fminf(lo, red[v][0][tid]); neg = fminf(neg, red[v][1][tid]); }
+    if constexpr (SPLIT) {
+      range_minima(a)[((int64_t)(b * 2 + sub) * split + part) * a.W + wc] = make_float2(lo, neg);
+      return;
+    }
     float cs, cz;
     const float4 pr = channel_params(a.scheme, n, (float)((1 << a.bits[sub]) - 1), lo, -neg, &cs, &cz);
     const int64_t o = (int64_t)(sub * a.B + b) * a.W + wc;
@@ -293,6 +312,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
     if (!a.resident) a.params[(int64_t)(b * 2 + sub) * a.W + wc] = pr;
     prm[0][tid] = pr.x; prm[1][tid] = pr.y; prm[2][tid] = pr.z;
   }
+  if constexpr (SPLIT) return;
   if (grp == 0 && sub == 0 && b == 0 && tid == 0) {
     a.chunk_row[0] = a.begin[0]; a.chunk_row[1] = a.n[0];
     a.chunk_row[2] = a.begin[1]; a.chunk_row[3] = a.n[1];
@@ -323,6 +343,36 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors) {
   if (bits == 4) pack(std::integral_constant<int, 4>{});
   else if (bits == 2) pack(std::integral_constant<int, 2>{});
   else pack(std::integral_constant<int, 8>{});
+}
+
+// Parameters from the minima of a subset's token ranges, a thread per channel; also those of the
+// plain tokenwise scheme, which has no statistics (1 and 0).
+// grid (ceil(W / 256), 2 subsets x tensors, B)
+__global__ __launch_bounds__(256) void k_column_params(QPPair p, int split) {
+  const QPArgs& a = blockIdx.y >> 1 ? p.t[1] : p.t[0];
+  const int sub = blockIdx.y & 1, b = blockIdx.z, w = blockIdx.x * 256 + threadIdx.x;
+  if (w >= a.W) return;
+  float lo = INFINITY, neg = INFINITY;
+  if (a.scheme != ZC_SCHEME_TOKEN) {
+    const float2* src = range_minima(a) + (int64_t)(b * 2 + sub) * split * a.W + w;
+    for (int t0 = 0; t0 < split; t0 += 16) {
+      float2 v[16];
+#pragma unroll
+      for (int t = 0; t < 16; ++t) v[t] = src[(int64_t)min(t0 + t, split - 1) * a.W];
+#pragma unroll
+      for (int t = 0; t < 16; ++t) { lo = fminf(lo, v[t].x); neg = fminf(neg, v[t].y); }
+    }
+  }
+  float cs, cz;
+  const float4 pr = channel_params(a.scheme, a.n[sub], (float)((1 << a.bits[sub]) - 1), lo, -neg, &cs, &cz);
+  const int64_t o = (int64_t)(sub * a.B + b) * a.W + w;
+  a.chan_scale[o] = cs;
+  a.chan_zero[o] = cz;
+  a.params[(int64_t)(b * 2 + sub) * a.W + w] = pr;
+  if (sub == 0 && b == 0 && w == 0) {
+    a.chunk_row[0] = a.begin[0]; a.chunk_row[1] = a.n[0];
+    a.chunk_row[2] = a.begin[1]; a.chunk_row[3] = a.n[1];
+  }
 }
 
 constexpr int kVPT = 1;  // channel vectors (8 channels each) per thread in the quantize sweep
@@ -660,13 +710,20 @@ static void launch_qp(const QPArgs& a, int layout, bool tokwise, dim3 grid, dim3
 
 using namespace zc;
 
-// [B, 2, W] parameters.  The size that callers are told also covers statistics by token tiles,
-// as it always has: buffers laid out with an earlier figure and this one are interchangeable.
+// Token ranges per subset of the split column sweep: enough for three workgroups a CU, and at
+// least kSplitRows rows a thread.  (n: tokens of the longer subset; a call for two tensors
+// cuts less.)
+static int64_t col_splits(int64_t B, int64_t NV, int64_t n, int tensors) {
+  const int64_t by_chip = 768 / (ceil_div64(NV, kSplitLanes) * 2 * tensors * B), by_rows = n * kSplitLanes / (kSplitThreads * kSplitRows);
+  const int64_t s = by_chip < by_rows ? by_chip : by_rows;
+  return s < 1 ? 1 : s;
+}
+
+// [B, 2, W] parameters, and the minima of the split column sweep.
 extern "C" size_t zc_quantize_pack_workspace(int64_t B, int64_t H, int64_t L, int64_t D) {
   if (B <= 0 || H <= 0 || D <= 0 || L < 0) return 0;
-  const int64_t W = H * D, per_tile = ceil_div64(B * L, 1024);
-  const int64_t tiles = ceil_div64(L, per_tile < 16 ? 16 : (per_tile > 64 ? 64 : per_tile)) + 1;
-  return (size_t)align_up64(B * 2 * W * (int64_t)sizeof(float4), 256) + (size_t)B * tiles * W * 2 * sizeof(float);
+  const int64_t W = H * D, split = col_splits(B, W / 8, L, 1);
+  return (size_t)align_up64(B * 2 * W * (int64_t)sizeof(float4), 256) + (split > 1 ? (size_t)B * 2 * split * W * sizeof(float2) : 0);
 }
 
 // Validation and kernel arguments of one tensor's compression call.
@@ -707,6 +764,7 @@ static int qp_prepare(const zc_tensor4* x, const int32_t* salient_idx, int64_t k
   a.chunk_row = out->chunk_table + 4 * out->n_chunks;
   a.pos_offset = pos_offset;
   a.scheme = out->scheme;
+  a.resident = 0;
   // word groups of 32 / bits tokens; a TGROUP block holds 4 of them
   a.units[0] = (int)ceil_div64(k, 4 * (32 / out->bits_hi)) * 4;
   a.units[1] = (int)ceil_div64(n_reg, 4 * (32 / out->bits_lo)) * 4;
@@ -729,7 +787,8 @@ static int qp_prepare(const zc_tensor4* x, const int32_t* salient_idx, int64_t k
 // then fits the registers.  Keys are resident wherever they fit - except in a call for both
 // tensors with too few workgroups to hide the packing behind each other's loads, where one
 // packing launch serves both (one prompt of 4096 tokens, 8 heads: 26.1 against 27.5 us).
-static int col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int dtype, bool joint_pack) {
+struct ColPlan { int threads, split; };
+static ColPlan col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int dtype, bool joint_pack) {
   const int64_t n = a[0].n[0] > a[0].n[1] ? a[0].n[0] : a[0].n[1], rows = kColRows(dtype);
   const auto wgs = [&](int vl) { return ceil_div64(a[0].NV, vl) * 2 * a[0].B; };      // of one tensor
   int vl = 16;
@@ -745,22 +804,46 @@ static int col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int dty
     any |= a[t].resident != 0;
   }
   for (int t = 0; t < tensors; ++t) a[t].vl = any ? v : vl;
-  return any ? th : threads;
+  if (any) return {th, 1};
+  // Few channels over many tokens leave most of the chip idle, each workgroup with a long chain
+  // of rows: token ranges and one more launch pay where a thread would have more than 16 rows
+  // (8 of fp32), or 32 where the workgroups fill the chip as they are.  131072 tokens of one head of 128
+  // channels in bf16: 137 us whole, 55 in ranges; of 8 heads 203 and 130; 12000 tokens of 4 heads
+  // in fp32: 29.5 and 23.7, but 3000 tokens of 32 heads (14 rows, 256 workgroups) 30.0 and 32.9.
+  const int64_t most = wgs(vl) * tensors >= 256 ? 32 : dtype == ZC_F32 ? 8 : 16;
+  if (n * vl > most * threads) {
+    const int64_t split = col_splits(a[0].B, a[0].NV, n, tensors);
+    if (split > 1) {
+      for (int t = 0; t < tensors; ++t) a[t].vl = kSplitLanes;
+      return {kSplitThreads, (int)split};
+    }
+  }
+  return {threads, 1};
 }
 
 template <int DT>
-static void launch_columns(const QPPair& p, int tensors, int threads, hipStream_t st) {
+static void launch_columns(const QPPair& p, int tensors, ColPlan c, hipStream_t st) {
   // (a grid counts the threads of a dimension in 32 bits: the batch has one of its own)
-  const dim3 grid((unsigned)(ceil_div64(p.t[0].NV, p.t[0].vl) * 2 * tensors), (unsigned)p.t[0].B);
-  if (threads == 512) hipLaunchKernelGGL((k_columns<DT, 512>), grid, dim3(512), 0, st, p, tensors);
-  else hipLaunchKernelGGL((k_columns<DT, 1024>), grid, dim3(1024), 0, st, p, tensors);
+  const dim3 grid((unsigned)(ceil_div64(p.t[0].NV, p.t[0].vl) * c.split * 2 * tensors), (unsigned)p.t[0].B);
+  if (c.split > 1) hipLaunchKernelGGL((k_columns<DT, kSplitThreads, true>), grid, dim3(kSplitThreads), 0, st, p, tensors, c.split);
+  else if (c.threads == 512) hipLaunchKernelGGL((k_columns<DT, 512>), grid, dim3(512), 0, st, p, tensors, c.split);
+  else hipLaunchKernelGGL((k_columns<DT, 1024>), grid, dim3(1024), 0, st, p, tensors, c.split);
 }
 static int qp_launch_columns(QPPair& p, const zc_packed* const* out, int tensors, int dtype, bool joint_pack, hipStream_t st) {
-  const int threads = col_plan(p.t, out, tensors, dtype, joint_pack);
-  if (dtype == ZC_F32) launch_columns<ZC_F32>(p, tensors, threads, st);
-  else if (dtype == ZC_F16) launch_columns<ZC_F16>(p, tensors, threads, st);
-  else launch_columns<ZC_BF16>(p, tensors, threads, st);
-  ZC_LAUNCH_CHECK();
+  bool stats = false;                  // (plain tokenwise: no channel statistics)
+  for (int t = 0; t < tensors; ++t) stats |= p.t[t].scheme != ZC_SCHEME_TOKEN;
+  ColPlan c = {0, 1};
+  if (stats) {
+    c = col_plan(p.t, out, tensors, dtype, joint_pack);
+    if (dtype == ZC_F32) launch_columns<ZC_F32>(p, tensors, c, st);
+    else if (dtype == ZC_F16) launch_columns<ZC_F16>(p, tensors, c, st);
+    else launch_columns<ZC_BF16>(p, tensors, c, st);
+    ZC_LAUNCH_CHECK();
+  }
+  if (!stats || c.split > 1) {
+    hipLaunchKernelGGL(k_column_params, dim3((unsigned)ceil_div64(p.t[0].W, 256), (unsigned)(2 * tensors), (unsigned)p.t[0].B), dim3(256), 0, st, p, c.split);
+    ZC_LAUNCH_CHECK();
+  }
   return ZC_OK;
 }
 

@@ -92,7 +92,10 @@ def test_sizes_and_workspaces():
     assert lib.zc_arena_bytes(2, 8, 128, 64, 2) == 2 * 8 * 128 * 64 // 4
     assert lib.zc_arena_slots(1638, 1) % zb.ZC_SLOT_ALIGN == 0 and lib.zc_arena_slots(1638, 1) >= 1638
     assert lib.zc_arena_slots(100, 2) >= 128
-    assert lib.zc_quantize_pack_workspace(1, 8, 4096, 128) >= 2 * 1024 * 16 + (4096 // 16) * 1024 * 8
+    # parameters [B, 2, W] of 16 bytes; few channels: also minima [B, 2, ranges, W] of 8 bytes (here 8 ranges of 512 tokens)
+    assert lib.zc_quantize_pack_workspace(16, 40, 4096, 128) == 16 * 2 * 5120 * 16
+    assert lib.zc_quantize_pack_workspace(1, 8, 4096, 128) == 2 * 1024 * 16 + 2 * 8 * 1024 * 8
+    assert lib.zc_quantize_pack_kv_workspace(16, 40, 4096, 128) == 2 * 16 * 2 * 5120 * 16
     assert lib.zc_probe_saliency_workspace(1, 32, 4096, 410) >= 4 * (32 * 410 + 32 * 4096)
     assert lib.zc_decode_attention_workspace(1, 32, 128) >= 32 * 130 * 4
     assert lib.zc_select_salient_workspace(1, 4096) == 0
@@ -152,7 +155,7 @@ def test_quantize_rejects_bad_arguments_before_launch():
     assert call(p, k=40, n=40) == -1                 # k + n_reg > L
     assert call(p, sal=None) == -1
     assert call(p, w=None) == -3
-    assert call(p, wsz=64) == -3
+    assert call(p, wsz=lib.zc_quantize_pack_workspace(1, 8, 64, 128) - 1) == -3
     p2, _t2 = _packed(zb.ZC_LAYOUT_TGROUP, cap=64)
     p2.n_hi = 64
     assert call(p2) == -4                            # hi arena full

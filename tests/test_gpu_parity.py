@@ -853,9 +853,12 @@ def test_decode_timeline_mode_of_the_benchmark():
     (1, 1, 64, 5120, torch.float32), (1, 1, 64, 5121, torch.float32),
     (64, 3, 64, 37, torch.bfloat16),                                        # sixteen across, the last group half empty
     (4, 40, 128, 640, torch.float16), (4, 40, 128, 641, torch.bfloat16),    # sixteen across, then eight
-    (4, 40, 128, 161, torch.float32), (2, 16, 128, 1300, torch.bfloat16)])
+    (4, 40, 128, 161, torch.float32), (2, 16, 128, 1300, torch.bfloat16),
+    (2, 1, 128, 33001, torch.bfloat16), (1, 2, 64, 9000, torch.float32),    # token ranges: the last one shorter, those of the other subset empty
+    (1, 5, 64, 12289, torch.float16)])
 def test_quantize_column_sweep_edges(B, H, D, n_reg, dtype):
-    """Channelwise codes at the limits of what stays in registers, alone and beside values."""
+    """Channelwise codes at the limits of what stays in registers, alone and beside values; statistics
+    whole and by token ranges; the plain tokenwise scheme, which has none."""
     from tests.pipeline_check import compare_subset, packed_to_chunks
     k = 7
     L = k + n_reg
@@ -865,16 +868,17 @@ def test_quantize_column_sweep_edges(B, H, D, n_reg, dtype):
     sal, reg = (t.sort(dim=1).values.to(torch.int32) for t in (perm[:, :k], perm[:, k:]))
     cap = zb.load().zc_arena_slots(L, 1)
     packs = [zb.PackedTensor(B, H, D, cap, cap, 4, 2, s, layout, max_chunks=1, device=DEV)
-             for s, layout in (("channel", zb.ZC_LAYOUT_ROW), ("channel", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP))]
+             for s, layout in (("channel", zb.ZC_LAYOUT_ROW), ("channel", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP), ("token", zb.ZC_LAYOUT_TGROUP))]
     Xg = X.to(DEV)
     zb.zc_quantize_pack(Xg, sal.to(DEV), reg.to(DEV), packs[0])
     zb.zc_quantize_pack_kv(Xg, Xg, sal.to(DEV), reg.to(DEV), packs[1], packs[2])
+    zb.zc_quantize_pack(Xg, sal.to(DEV), reg.to(DEV), packs[3])
     torch.cuda.synchronize()
     for name in ("codes_hi", "codes_lo", "pos_hi", "pos_lo", "chan_scale", "chan_zero", "chunk_table"):
         assert torch.equal(getattr(packs[0], name), getattr(packs[1], name)), name
     total = mism = 0
     for b in sorted({0, B - 1}):
-        for P, scheme in ((packs[0], "channel"), (packs[2], "cst")):
+        for P, scheme in ((packs[0], "channel"), (packs[2], "cst"), (packs[3], "token")):
             got = packed_to_chunks(P, [b])[0]
             ref = zo.compress_tensor(X[b:b + 1].double().numpy(), sal[b:b + 1].numpy(), reg[b:b + 1].numpy(), 4, 2, scheme)
             for name, x, y in (("hi", got.hi, ref.hi), ("lo", got.lo, ref.lo)):
