@@ -10,6 +10,8 @@
 //                        of the next compression.
 // None of them is on the per-step hot path (a probe step is one step in ten, a
 // re-compression one in a hundred), but each is bound by memory or latency like the step itself.
+#include <type_traits>
+
 #include "zc_common.hpp"
 
 namespace zc {
@@ -273,12 +275,75 @@ __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
 // rows as its loop - the obvious split - leaves the chip to n_out / 256 workgroups that wait for
 // one load after the other: 94 us for 10 rows of 32 heads and 4096 columns (5.2 MB).  Here a
 // workgroup takes COLS columns and gives every head a lane group of its own: the head's P rows
-// are requested back to back (kRowBatch at a time), the per-head sums meet in LDS and are added
+// are requested back to back (eight at a time), the per-head sums meet in LDS and are added
 // head by head, so the summation order - rows within a head, then heads - and with it every
-// score, is the one of that loop.
+// score, is the one of that loop.  Where the columns alone fill the chip the loop stays the better
+// one (and few heads leave the lane groups without work): 10 rows of 2 heads and 16 x 33000 columns
+// 13 against 39 us, of 8 heads 37 against 47; of 32 heads and 16 x 4000 columns 36 against 17.
 constexpr int kRowThreads = 1024;
 constexpr int kRowHeads = 64;      // heads whose sums LDS holds at once
-constexpr int kRowBatch = 8;       // rows of a head requested at once
+
+// The sum over a head's rows (column i of them starts at src), a batch of rows requested before any is added.
+__device__ inline float rows_sum(const float* __restrict__ src, const int32_t* __restrict__ row_len, int P, int64_t row_pitch, int i) {
+  float col = 0.f;
+  int j = 0;
+  auto rows_of = [&](auto n_c) {
+    constexpr int N = decltype(n_c)::value;
+    float v[N];
+#pragma unroll
+    for (int jj = 0; jj < N; ++jj) v[jj] = src[(int64_t)(j + jj) * row_pitch];
+#pragma unroll
+    for (int jj = 0; jj < N; ++jj)
+      if (row_len[j + jj] > i) col += v[jj];
+    j += N;
+  };
+  while (j + 8 <= P) rows_of(std::integral_constant<int, 8>{});
+  if (P & 4) rows_of(std::integral_constant<int, 4>{});
+  if (P & 2) rows_of(std::integral_constant<int, 2>{});
+  if (P & 1) rows_of(std::integral_constant<int, 1>{});
+  return col;
+}
+
+__device__ inline float rows_score(float total, const int32_t* __restrict__ row_len, int P, int Hq, int i, int normalize) {
+  int cnt = 0;
+  for (int j = 0; j < P; ++j) cnt += row_len[j] > i ? 1 : 0;
+  float s = total / (float)Hq;
+  if (normalize) s = cnt > 0 ? s / (float)cnt : 0.f;
+  return s;
+}
+
+// A thread per column, for calls that fill the chip with columns.  FOURS: four rows or more.
+template <bool FOURS>
+__global__ __launch_bounds__(256) void k_rows_saliency_columns(const float* __restrict__ rows, const int32_t* __restrict__ row_len,
+                                                               int P, int Hq, int64_t row_stride, int n_out, int normalize,
+                                                               float* __restrict__ scores) {
+  const int i = blockIdx.x * 256 + threadIdx.x, b = blockIdx.y, B = gridDim.y;
+  if (i >= n_out) return;
+  const int64_t row_pitch = (int64_t)B * Hq * row_stride;
+  const float* src = rows + (int64_t)b * Hq * row_stride + i;
+  float total = 0.f;
+  for (int h = 0; h < Hq; ++h, src += row_stride) {
+    // (pointers that advance, and the rows past the fours one by one: the address arithmetic of
+    // rows_sum would be most of a short call)
+    const float* p = src;
+    float col = 0.f;
+    int j = 0;
+    if constexpr (FOURS) {
+      for (; j + 4 <= P; j += 4) {
+        float v[4];
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) { v[jj] = *p; p += row_pitch; }
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+          if (row_len[j + jj] > i) col += v[jj];
+      }
+    }
+    for (; j < P; ++j, p += row_pitch)
+      if (row_len[j] > i) col += *p;
+    total += col;
+  }
+  scores[(int64_t)b * n_out + i] = rows_score(total, row_len, P, Hq, i, normalize);
+}
 
 template <int COLS>
 __global__ __launch_bounds__(kRowThreads) void k_rows_saliency(const float* __restrict__ rows, const int32_t* __restrict__ row_len,
@@ -296,31 +361,14 @@ __global__ __launch_bounds__(kRowThreads) void k_rows_saliency(const float* __re
   float total = 0.f;
   for (int h0 = 0; h0 < Hq; h0 += kRowHeads) {
     const int hn = min(kRowHeads, Hq - h0);
-    for (int h = g; h < hn; h += NG) {
-      const float* src = rows + ((int64_t)b * Hq + h0 + h) * row_stride + ic;
-      float col = 0.f;
-      for (int j0 = 0; j0 < P; j0 += kRowBatch) {
-        float v[kRowBatch];
-#pragma unroll
-        for (int jj = 0; jj < kRowBatch; ++jj) v[jj] = src[(int64_t)min(j0 + jj, P - 1) * row_pitch];
-#pragma unroll
-        for (int jj = 0; jj < kRowBatch; ++jj)
-          if (j0 + jj < P && row_len[j0 + jj] > i) col += v[jj];
-      }
-      part[h][cx] = col;
-    }
+    for (int h = g; h < hn; h += NG)
+      part[h][cx] = rows_sum(rows + ((int64_t)b * Hq + h0 + h) * row_stride + ic, row_len, P, row_pitch, i);
     __syncthreads();
     if (g == 0)
       for (int h = 0; h < hn; ++h) total += part[h][cx];
     if (h0 + kRowHeads < Hq) __syncthreads();        // (the sums have been read before they are overwritten)
   }
-  if (g == 0 && i < n_out) {
-    int cnt = 0;
-    for (int j = 0; j < P; ++j) cnt += row_len[j] > i ? 1 : 0;
-    float s = total / (float)Hq;
-    if (normalize) s = cnt > 0 ? s / (float)cnt : 0.f;
-    scores[(int64_t)b * n_out + i] = s;
-  }
+  if (g == 0 && i < n_out) scores[(int64_t)b * n_out + i] = rows_score(total, row_len, P, Hq, i, normalize);
 }
 
 // ---- zc_dequantize_cache -------------------------------------------------------------------
@@ -579,12 +627,21 @@ extern "C" int zc_rows_saliency(const float* rows, const int32_t* row_len, int32
   if ((reinterpret_cast<uintptr_t>(rows) & 3) || (reinterpret_cast<uintptr_t>(scores) & 3) || (reinterpret_cast<uintptr_t>(row_len) & 3))
     return ZC_ERR_INVALID_ARG;
   if (n_out == 0) return ZC_OK;
+  hipStream_t st = (hipStream_t)stream;
+  // a thread per column (the line by measurement: 64 workgroups of 256 columns per head, up to 16
+  // heads; with up to three rows, whose loop is short, 9 per head, and always up to four heads)
+  const int64_t by_column = ceil_div64(n_out, 256) * B;
+  if (P < 4 ? by_column >= 9 * Hq || Hq <= 4 : by_column >= 64 * Hq && Hq <= 16) {
+    hipLaunchKernelGGL((P < 4 ? k_rows_saliency_columns<false> : k_rows_saliency_columns<true>), dim3((unsigned)ceil_div64(n_out, 256), (unsigned)B),
+                       dim3(256), 0, st, rows, row_len, (int)P, (int)Hq, row_stride, (int)n_out, normalize ? 1 : 0, scores);
+    ZC_LAUNCH_CHECK();
+    return ZC_OK;
+  }
   // 32 columns (whole 128-byte lines) a workgroup while 64 would leave compute units without one
   const bool narrow = ceil_div64(n_out, 64) * B < 256;
   const int64_t tiles = ceil_div64(n_out, narrow ? 32 : 64);
   const int64_t per_z = tiles < (1 << 21) ? tiles : 1 << 21;        // (a grid counts the threads of a dimension in 32 bits)
   const dim3 grid((unsigned)per_z, (unsigned)B, (unsigned)ceil_div64(tiles, per_z));
-  hipStream_t st = (hipStream_t)stream;
   if (narrow)
     hipLaunchKernelGGL(k_rows_saliency<32>, grid, dim3(kRowThreads), 0, st, rows, row_len, (int)P, (int)Hq, row_stride, (int)n_out,
                        normalize ? 1 : 0, scores);

@@ -219,9 +219,10 @@ def test_decode_probs_over_many_chunks_and_schemes():
         assert np.all(got[:, :, Ltot:] == 0.0)
 
 
-@pytest.mark.parametrize("P,B,Hq,N,n_out", [(1, 1, 1, 40, 1), (9, 2, 40, 100, 33), (8, 1, 70, 64, 64), (17, 3, 64, 131, 65), (10, 300, 2, 70, 70)])
+@pytest.mark.parametrize("P,B,Hq,N,n_out", [(1, 1, 1, 40, 1), (9, 2, 40, 100, 33), (8, 1, 70, 64, 64), (17, 3, 64, 131, 65), (10, 300, 2, 70, 70),
+                                           (3, 12, 1, 300, 257), (15, 128, 1, 260, 256)])
 def test_rows_saliency_shapes(P, B, Hq, N, n_out):
-    """Columns around the edges of a workgroup's tile (32 and 64 columns), more heads than are
+    """Columns around the edges of a workgroup's tile (32, 64 and 256 columns), more heads than are
     summed at once, row counts around a batch of rows; cells past a row's length hold NaN."""
     g = torch.Generator().manual_seed(P * 1000 + Hq)
     rows = torch.rand(P, B, Hq, N, generator=g)
