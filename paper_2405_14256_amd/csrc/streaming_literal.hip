@@ -17,7 +17,7 @@
 namespace zc {
 
 // ---- zc_decode_probs -----------------------------------------------------------------------
-constexpr int kProbSegs = 16;     // segments (chunk x subset, and the tail) one launch takes
+constexpr int kProbSegs = 64;     // segments (chunk x subset, and the tail) one launch takes
 constexpr int kProbTile = 16;     // cache slots (or tail tokens) of one matrix-core tile
 constexpr int kTailSub = 2;       // `sub` of the tail's segment
 
@@ -256,8 +256,11 @@ template <int DT, int D>
 __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
   const int hk = blockIdx.y, b = blockIdx.z;
   const int wave = threadIdx.x >> 6;
-  int si = 0;
-  while (si + 1 < a.n_segs && (int)blockIdx.x >= a.seg[si + 1].first_block) ++si;
+  // the workgroup's segment: the last that starts at or before it (a lane per segment: one by
+  // one, the segments of a cache of many chunks would be a chain of as many loads)
+  const int lane = threadIdx.x & 63;
+  const bool before = lane < a.n_segs && (int)blockIdx.x >= a.seg[lane].first_block;
+  const int si = __builtin_popcountll(__builtin_amdgcn_ballot_w64(before)) - 1;
   const int begin = a.seg[si].begin, len = a.seg[si].len, sub = a.seg[si].sub;
   const bool is_tail = sub == kTailSub;
   const int tile0 = ((int)blockIdx.x - a.seg[si].first_block) * 4 * a.tpw + wave, ntiles = ceil_div(len, kProbTile);

@@ -356,13 +356,13 @@ def test_decode_probs_tiles_and_code_widths(B, Hq, Hkv, d, dtype, bits, L, T):
     width, launches of one and of several tiles a wave, more segments than one launch takes."""
     g = torch.Generator().manual_seed(L)
     lib = zb.load()
-    sizes = [L] + [3] * 9
-    ks = [L // 3] + [1] * 9
+    sizes = [L] + [3] * 33
+    ks = [L // 3] + [1] * 33
     K = torch.randn(B, Hkv, sum(sizes) + T, d, generator=g).to(dtype).to(DEV)
     q = torch.randn(B, Hq, d, generator=g).to(dtype).to(DEV)
     for scheme in ("channel", "token"):
-        p = zb.PackedTensor(B, Hkv, d, lib.zc_arena_slots(sum(ks), 10), lib.zc_arena_slots(sum(sizes) - sum(ks), 10), *bits, scheme,
-                            zb.ZC_LAYOUT_ROW, max_chunks=10, device=DEV)
+        p = zb.PackedTensor(B, Hkv, d, lib.zc_arena_slots(sum(ks), 34), lib.zc_arena_slots(sum(sizes) - sum(ks), 34), *bits, scheme,
+                            zb.ZC_LAYOUT_ROW, max_chunks=34, device=DEV)
         n0 = 0
         for n, k in zip(sizes, ks):
             sal, reg = zb.zc_select_salient(torch.rand(B, n, generator=g).to(DEV), k)
