@@ -442,6 +442,8 @@ __global__ __launch_bounds__(small_threads(DT, D)) void k_probe_small(ProbeArgs 
   const int col = col0 + r;
   const int koff = col < a.Lk ? (int)((uint32_t)col * k_rowb) + kh * 16 : kOutOfRange;     // (columns past the end: zeros)
   float sum = 0.f;
+  int cnt_col = 0;                                   // (per-head scores: probe rows that see this lane's column)
+  if (a.per_head) cnt_col = a.P - lower_bound_pos(spos, a.P, col);
   // consecutive heads to a wave: one load of K serves those that share it
   const int per = ceil_div(a.Hq, NW), h_end = min((w + 1) * per, a.Hq);
   u32x4 kf[T::NKC];
@@ -459,11 +461,18 @@ __global__ __launch_bounds__(small_threads(DT, D)) void k_probe_small(ProbeArgs 
 #pragma unroll
     for (int kc = 0; kc < T::NKC; ++kc)
       mma_chunk<DT>(acc, __builtin_amdgcn_raw_buffer_load_b128(rs_q, qoff + kc * 32, 0, 0), kf[kc]);
+    float head_sum = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int p = acc_row(v, kh), pc = min(p, a.P - 1);
       const float e = __builtin_amdgcn_exp2f(fmaf(acc[v], a.scale_log2, -slse[h * a.P + pc]));
-      sum += (p < a.P && col <= spos[pc]) ? e : 0.f;
+      head_sum += (p < a.P && col <= spos[pc]) ? e : 0.f;
+    }
+    sum += head_sum;
+    if (a.per_head) {
+      head_sum += __shfl_xor(head_sum, 32);
+      if (kh == 0 && col < a.Lk)
+        a.per_head[((int64_t)b * a.Hq + h) * a.Lk + col] = !a.normalize ? head_sum : (cnt_col > 0 ? head_sum / (float)cnt_col : 0.f);
     }
   }
   sum += __shfl_xor(sum, 32);
@@ -575,9 +584,9 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.nsplit = probe_splits(q->B, q->H, P, k->L);
   if ((int64_t)ceil_div64(P, kLseRows) * q->H * q->B * a.nsplit > 0x7fffffff || (int64_t)ceil_div64(k->L, 128) * q->H * q->B > 0x7fffffff)
     return ZC_ERR_UNSUPPORTED;
-  a.per_head = scores_per_head ? scores_per_head : ws_ph;
   a.normalize = normalize ? 1 : 0;
-  a.small = !scores_per_head && probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));
+  a.small = probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));
+  a.per_head = scores_per_head || a.small ? scores_per_head : ws_ph;       // (few rows: only where the caller asks for them)
 
   hipStream_t st = (hipStream_t)stream;
   const bool need_lse = lse_ext == nullptr;

@@ -915,17 +915,19 @@ def test_quantize_of_the_largest_batches():
     (1, 8, 8, 64, 256, 26, torch.float32), (1, 1, 1, 64, 1, 1, torch.bfloat16), (2, 18, 6, 64, 33, 32, torch.float16),
     (3, 17, 17, 64, 100, 10, torch.bfloat16), (1, 12, 4, 128, 65, 31, torch.float32), (130, 24, 8, 128, 31, 9, torch.float16)])
 def test_probe_few_rows(B, Hq, Hkv, d, Lk, P, dtype):
-    """At most 32 probe rows (one launch for sums and mean) against the oracle and against the
-    general path, which per-head scores ask for: heads that do not divide over the waves, a
-    row block that is full and one that is not, columns one past a block."""
+    """At most 32 probe rows (one launch for sums and mean) against the oracle, the same scores with
+    and without per-head ones: heads that do not divide over the waves, a row block that is full
+    and one that is not, columns one past a block."""
     g = torch.Generator().manual_seed(Lk + P)
     Q = torch.randn(B, Hq, Lk, d, generator=g).to(dtype)
     K = torch.randn(B, Hkv, Lk, d, generator=g).to(dtype)
     pos = torch.randperm(Lk, generator=g)[:P].sort().values.to(torch.int32)
     few = zb.zc_probe_saliency(Q.to(DEV), K.to(DEV), pos.to(DEV))
     ph = torch.empty(B, Hq, Lk, dtype=torch.float32, device=DEV)
-    general = zb.zc_probe_saliency(Q.to(DEV), K.to(DEV), pos.to(DEV), scores_per_head=ph)
-    # the same products and exponentials, added in another order: at most P * Hq terms of one sign
-    assert float((few - general).abs().max()) <= 1e-6 * float(general.abs().max())
+    assert torch.equal(zb.zc_probe_saliency(Q.to(DEV), K.to(DEV), pos.to(DEV), scores_per_head=ph), few)
+    # the same sums, added in another order: at most P * Hq terms of one sign
+    assert float((few - ph.double().mean(1)).abs().max()) <= 1e-6 * float(few.abs().max())
+    total = zb.zc_probe_accumulated(Q.to(DEV), K.to(DEV), pos.to(DEV), scores_per_head=ph)
+    assert float((total - ph.double().mean(1)).abs().max()) <= 1e-6 * float(total.abs().max())
     ref, _ = zo.saliency_scores(Q[:1].double().numpy(), K[:1].double().numpy(), pos.numpy())
     assert np.abs(few[:1].cpu().double().numpy() - ref).max() <= 1e-4 * np.abs(ref).max()
