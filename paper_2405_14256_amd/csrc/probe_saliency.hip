@@ -529,13 +529,16 @@ static int probe_splits(int64_t B, int64_t Hq, int64_t P, int64_t Lk) {
 }
 // Whether few probe rows are served by one launch: a block of 32, and no more bytes per
 // workgroup than its CU's loads bring in within the time the other path's two launches take
-// (8 heads of 64 channels, 256 tokens, 26 rows, fp32, 119 KB: 8 against 11 us; 2 x 16 heads of
-// 128 channels, 300 tokens, 30 rows, 16 bit, 254 KB: 10.5 against 9.7); twice that where
-// the columns fill half the chip (16 x 32 heads, 256 tokens, 26 rows, 344 KB: 14.9 against 18.9).
+// (8 heads of 64 channels, 256 tokens, 26 rows, fp32, 119 KB: 8 against 11 us; 32 heads of 128
+// channels over 8, 64 tokens, 4 rows, 16 bit, 163 KB: 9.9 against 9.1); three times that
+// where the columns fill the chip (16 x 32 heads, 256 tokens, 26 rows, 344 KB: 14.9 against
+// 18.9).  Fewer than 16 heads leave waves without work, which shows over many columns (16 x 8
+// heads of 64 channels, 20000 tokens, 32 rows: 160 against 129 us; 16 x 1 head, 96 against 36).
 static bool probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P, int64_t row_bytes) {
   if (P > kSmallRows || Hq * P > kSmallTable) return false;
   const int64_t segments = Hkv > 16 ? Hkv : (Hq < 16 ? Hq : 16);        // K loads: by waves and KV heads
-  const int64_t limit = B * ceil_div64(Lk, 32) >= 128 ? 384 * 1024 : 192 * 1024;
+  if (Hq < 16 && Lk > 1024) return false;
+  const int64_t limit = B * ceil_div64(Lk, 32) >= 256 ? 384 * 1024 : 128 * 1024;
   return (segments * 32 + Hq * P) * row_bytes <= limit;
 }
 static size_t lse_bytes(int64_t B, int64_t Hq, int64_t P) { return (size_t)align_up64(B * Hq * P * (kMaxProbeSplit * (int64_t)sizeof(float2) + 4), 256); }
