@@ -194,6 +194,7 @@ PyObject* prefill(PyObject*, Args a, Py_ssize_t n) {
 PyObject* select(PyObject*, Args a, Py_ssize_t n) {
   return guarded(kSelect, n, 5, [&]() -> int {
     const at::Tensor& s = tensor_of(a[0]);
+    if (s.dim() != 2) { PyErr_Format(PyExc_ValueError, "scores must be [B, L], got %d dimensions", (int)s.dim()); throw Bad(); }
     const int64_t B = s.size(0), L = s.size(1), k = int_of(a[1]);
     const auto* sp = static_cast<const float*>(s.data_ptr());
     auto *sal = ptr_as<int32_t>(a[2]), *reg = ptr_as<int32_t>(a[3]);

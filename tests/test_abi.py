@@ -6,6 +6,7 @@ import re
 
 import numpy as np
 import pytest
+import torch
 
 from paper_2405_14256_amd import binding as zb
 
@@ -112,6 +113,13 @@ def test_select_rejects_bad_arguments_before_launch():
     assert lib.zc_select_salient(0x1000, 1, 16, -1, 0x1000, 0x2000, None, None, 0, None) == -1
     assert lib.zc_select_salient(0x1001, 1, 16, 4, 0x1000, 0x2000, None, None, 0, None) == -1   # misaligned
     assert lib.zc_select_salient(0x1000, 0, 16, 4, 0x1000, 0x2000, None, None, 0, None) == 0    # empty batch: no-op
+
+
+def test_select_refuses_scores_that_are_not_a_matrix():
+    idx = torch.zeros(2, 1, dtype=torch.int32), torch.zeros(2, 2, dtype=torch.int32)
+    for scores in (torch.zeros(2, 3, 4), torch.zeros(6), torch.zeros(())):
+        with pytest.raises(ValueError):
+            zb.zc_select_salient(scores, 1, *idx)
 
 
 def test_probe_rejects_bad_arguments_before_launch():
