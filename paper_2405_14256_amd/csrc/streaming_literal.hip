@@ -52,6 +52,16 @@ struct ProbsArgs {
 };
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+// Four elements of a parameter or position array, which the validation does not hold to 16
+// bytes (the instruction is the same, alignment to 4 is what it needs).
+typedef float f4a __attribute__((ext_vector_type(4), aligned(4)));
+typedef int i4a __attribute__((ext_vector_type(4), aligned(4)));
+__device__ inline float4 load4(const float* p) { const f4a t = *reinterpret_cast<const f4a*>(p); return make_float4(t.x, t.y, t.z, t.w); }
+__device__ inline int4 load4(const int32_t* p) { const i4a t = *reinterpret_cast<const i4a*>(p); return make_int4(t.x, t.y, t.z, t.w); }
+__device__ inline void load8(const float* p, float (&v)[8]) {
+  const float4 a = load4(p), b = load4(p + 4);
+  v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
+}
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
@@ -128,12 +138,12 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
     } else {
       in.w[0] = *reinterpret_cast<const uint32_t*>(row);
     }
-    in.pos = *reinterpret_cast<const int4*>(pos_src + tile * kProbTile);
+    in.pos = load4(pos_src + tile * kProbTile);
     in.ts = make_float4(1.f, 1.f, 1.f, 1.f);
     in.tz = make_float4(0.f, 0.f, 0.f, 0.f);
     if (a.k_tok) {
-      in.ts = *reinterpret_cast<const float4*>(ts_src + tile * kProbTile);
-      in.tz = *reinterpret_cast<const float4*>(tz_src + tile * kProbTile);
+      in.ts = load4(ts_src + tile * kProbTile);
+      in.tz = load4(tz_src + tile * kProbTile);
     }
   };
   In in;
@@ -154,8 +164,8 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
     for (int c8 = 0; c8 < NK; c8 += 8) {
       float v[8], cs[8], cz[8];
       load8<DT>(a.q, qoff + c8, v);
-      load8<ZC_F32>(a.k_cs, coff + c8, cs);
-      load8<ZC_F32>(a.k_cz, coff + c8, cz);
+      load8(a.k_cs + coff + c8, cs);
+      load8(a.k_cz + coff + c8, cz);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         const float x = v[i] * cs[i] * scale;
@@ -463,8 +473,8 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
   const int c = vec * 8;
   const int64_t bh = (int64_t)b * a.H + h;
   float cs[8], cz[8];
-  load8<ZC_F32>(a.chan_scale, chan0 + h * a.D + c, cs);
-  load8<ZC_F32>(a.chan_zero, chan0 + h * a.D + c, cz);
+  load8(a.chan_scale + chan0 + h * a.D + c, cs);
+  load8(a.chan_zero + chan0 + h * a.D + c, cz);
   const int64_t obase = (int64_t)b * a.o_sB + (int64_t)h * a.o_sH + c;
   auto expand = [&](int position, float ts, float tz, auto code_of) {
     if (position < 0 || position >= a.out_L) return;
@@ -502,11 +512,11 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
     const uint4 lo = reinterpret_cast<const uint4*>(src)[0], hi = reinterpret_cast<const uint4*>(src)[1];
     uint32_t w[8] = {lo.x, lo.y, lo.z, lo.w, hi.x, hi.y, hi.z, hi.w};
     const int64_t ti = (int64_t)b * cap + sg.begin + rel;
-    const int4 pos4 = *reinterpret_cast<const int4*>(a.pos[sub] + ti);
+    const int4 pos4 = load4(a.pos[sub] + ti);
     float4 ts4 = make_float4(1.f, 1.f, 1.f, 1.f), tz4 = make_float4(0.f, 0.f, 0.f, 0.f);
     if (a.tokwise) {
-      ts4 = *reinterpret_cast<const float4*>(a.tok_scale[sub] + ti);
-      tz4 = *reinterpret_cast<const float4*>(a.tok_zero[sub] + ti);
+      ts4 = load4(a.tok_scale[sub] + ti);
+      tz4 = load4(a.tok_zero[sub] + ti);
     }
     const int pos[4] = {pos4.x, pos4.y, pos4.z, pos4.w};
     const float ts[4] = {ts4.x, ts4.y, ts4.z, ts4.w}, tz[4] = {tz4.x, tz4.y, tz4.z, tz4.w};

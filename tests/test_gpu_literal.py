@@ -407,3 +407,35 @@ def test_decode_probs_error_against_64_bits(bits, dtype):
         want = torch.exp(logits - lse.double()[..., None])
         err = float(((row.double() - want) / want).square().mean().sqrt())
         assert err <= 2.0 ** -21 * float(logits.square().mean().sqrt()), (scheme, err, float(logits.square().mean().sqrt()) * 2.0 ** -20)
+
+
+@pytest.mark.parametrize("scheme,layout", [("channel", zb.ZC_LAYOUT_ROW), ("token", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP)])
+def test_parameter_arrays_aligned_to_their_elements_only(scheme, layout):
+    """Positions, token and channel parameters one element past a 16-byte boundary, which the
+    validation admits: the same rows and probabilities."""
+    B, H, d, L, k = 2, 3, 128, 150, 50
+    g = torch.Generator().manual_seed(8)
+    x = torch.randn(B, H, L, d, generator=g).to(torch.bfloat16).to(DEV)
+    p = zb.PackedTensor(B, H, d, 64, 128, 4, 2, scheme, layout, max_chunks=1, device=DEV)
+    sal, reg = zb.zc_select_salient(torch.rand(B, L, generator=g).to(DEV), k)
+    zb.zc_quantize_pack(x, sal, reg, p)
+    q = torch.randn(B, 2 * H, d, generator=g).to(torch.bfloat16).to(DEV)
+    lse = torch.zeros(B, 2 * H, device=DEV)
+
+    def results():
+        out = [torch.zeros_like(x)]
+        zb.zc_dequantize_cache(p, out[0])
+        if layout == zb.ZC_LAYOUT_ROW:
+            out.append(torch.zeros(B, 2 * H, L, device=DEV))
+            zb.zc_decode_probs(q, p, None, 0, L, lse, out[1])
+        return out
+    want, keep = results(), []
+    for name in ("tok_scale_hi", "tok_zero_hi", "tok_scale_lo", "tok_zero_lo", "pos_hi", "pos_lo", "chan_scale", "chan_zero"):
+        t = getattr(p, name)
+        moved = torch.empty(t.numel() + 1, dtype=t.dtype, device=DEV)[1:]
+        moved.copy_(t.flatten())
+        keep.append(moved)
+        setattr(p.c, name, moved.data_ptr())
+        assert moved.data_ptr() % 16 == 4
+    for a, b in zip(want, results()):
+        assert torch.equal(a, b)
