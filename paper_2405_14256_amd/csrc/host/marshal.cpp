@@ -104,29 +104,39 @@ struct Packed {
 // ---- scratch ---------------------------------------------------------------------------------
 // One buffer per device, kind of call and stream (calls on different streams may run
 // concurrently and must not share scratch memory), used by every call of that kind on that
-// stream, in stream order.  A buffer is replaced by one at least half as large again, and the old
-// one is kept: a captured graph may hold its address.  (So what a stream keeps is below three
-// times its largest request.)  All of this runs under the interpreter lock.
+// stream, in stream order.  A buffer is replaced by one at least half as large again and goes
+// back to torch's allocator, which reuses it in the order of the stream - unless a call that used
+// it was captured: the graph holds its address, and it is kept.  (So a stream holds less than one and a
+// half times its largest request, and what its graphs were captured with.)  All of this runs
+// under the interpreter lock.
 enum Kind { kScratchProbe, kScratchQuantize, kScratchQuantizeKV, kScratchDecode };
-struct Scratch { at::Tensor t; void* ptr = nullptr; size_t bytes = 0; std::vector<at::Tensor> old; };
+struct Scratch { at::Tensor t; void* ptr = nullptr; size_t bytes = 0; bool captured = false; };
 std::map<std::tuple<int, int, void*>, Scratch>* g_scratch;
+std::vector<at::Tensor>* g_captured;      // replaced buffers that graphs may hold
 
-const Scratch& scratch(size_t need, const at::Tensor& like, Kind kind, void* stream) {
-  Scratch& s = (*g_scratch)[std::make_tuple((int)like.device().index(), (int)kind, stream)];
+// The reference keeps the buffer during the call, whose launch runs without the lock.
+Scratch scratch(size_t need, const at::Tensor& like, Kind kind, hipStream_t stream) {
+  Scratch& s = (*g_scratch)[std::make_tuple((int)like.device().index(), (int)kind, (void*)stream)];
   if (!s.ptr || s.bytes < need) {
     size_t n = need < 256 ? 256 : need;
-    if (s.ptr) {
-      if (n < s.bytes + s.bytes / 2) n = s.bytes + s.bytes / 2;
-      s.old.push_back(s.t);
-    }
-    s.t = at::zeros({(int64_t)n}, like.options().dtype(at::kByte));
-    s.ptr = s.t.data_ptr();
+    if (s.ptr && n < s.bytes + s.bytes / 2) n = s.bytes + s.bytes / 2;
+    at::Tensor t = at::zeros({(int64_t)n}, like.options().dtype(at::kByte));
+    if (s.captured) g_captured->push_back(s.t);
+    s.ptr = t.data_ptr();
+    s.t = std::move(t);
     s.bytes = n;
+    s.captured = false;
   }
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(stream, &status) != hipSuccess) {
+    (void)hipGetLastError();
+    s.captured = true;                     // (the default stream beside a capture: taken for one)
+  }
+  s.captured |= status != hipStreamCaptureStatusNone;
   return s;
 }
 
-void* current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
+hipStream_t current_stream() { return c10::hip::getCurrentHIPStream().stream(); }
 
 // Runs a launch without the interpreter lock (it may wait for room in the stream's queue).
 template <class F> int unlocked(F&& f) {
@@ -166,8 +176,8 @@ PyObject* probe(PyObject*, Args a, Py_ssize_t n) {
     const auto* lse = ptr_as<const float>(a[6]);
     auto* scores = ptr_as<float>(a[7]);
     auto* per_head = ptr_as<float>(a[8]);
-    void* st = current_stream();
-    const Scratch& ws = scratch(ZC_FN(kProbeWs, zc_probe_saliency_workspace)(q.B, q.H, k.L, P), tensor_of(a[1]), kScratchProbe, st);
+    const hipStream_t st = current_stream();
+    const Scratch ws = scratch(ZC_FN(kProbeWs, zc_probe_saliency_workspace)(q.B, q.H, k.L, P), tensor_of(a[1]), kScratchProbe, st);
     void* wp = ws.ptr;
     const size_t wn = ws.bytes;
     const auto fn = ZC_FN(acc ? kAccumulated : kProbe, zc_probe_saliency);
@@ -184,7 +194,7 @@ PyObject* prefill(PyObject*, Args a, Py_ssize_t n) {
     const int32_t P = a[6] == Py_None ? 0 : (int32_t)tensor_of(a[6]).numel();
     const auto* pos = P ? ptr_as<const int32_t>(a[6]) : nullptr;
     auto* lse_probe = P ? ptr_as<float>(a[7]) : nullptr;
-    void* st = current_stream();
+    const hipStream_t st = current_stream();
     const auto fn = ZC_FN(kPrefill, zc_prefill_attention);
     return unlocked([&] { return fn(&q, &k, &v, scale, &o, lse, pos, P, lse_probe, st); });
   });
@@ -199,7 +209,7 @@ PyObject* select(PyObject*, Args a, Py_ssize_t n) {
     const auto* sp = static_cast<const float*>(s.data_ptr());
     auto *sal = ptr_as<int32_t>(a[2]), *reg = ptr_as<int32_t>(a[3]);
     auto* mask = ptr_as<uint8_t>(a[4]);
-    void* st = current_stream();
+    const hipStream_t st = current_stream();
     const auto fn = ZC_FN(kSelect, zc_select_salient);
     return unlocked([&] { return fn(sp, B, L, k, sal, reg, mask, nullptr, 0, st); });
   });
@@ -222,8 +232,8 @@ PyObject* quantize(PyObject*, Args a, Py_ssize_t n) {
     const Lists l = lists_of(a[1], a[2]);
     const Packed p(a[3]);
     const int64_t off = int_of(a[4]);
-    void* st = current_stream();
-    const Scratch& ws = scratch(ZC_FN(kQuantizeWs, zc_quantize_pack_workspace)(x.B, x.H, l.k + l.n_reg, x.D), tensor_of(a[0]),
+    const hipStream_t st = current_stream();
+    const Scratch ws = scratch(ZC_FN(kQuantizeWs, zc_quantize_pack_workspace)(x.B, x.H, l.k + l.n_reg, x.D), tensor_of(a[0]),
                                 kScratchQuantize, st);
     void* wp = ws.ptr;
     const size_t wn = ws.bytes;
@@ -239,8 +249,8 @@ PyObject* quantize_kv(PyObject*, Args a, Py_ssize_t n) {
     const Lists l = lists_of(a[2], a[3]);
     const Packed pk(a[4]), pv(a[5]);
     const int64_t off = int_of(a[6]);
-    void* st = current_stream();
-    const Scratch& ws = scratch(ZC_FN(kQuantizeKVWs, zc_quantize_pack_kv_workspace)(xk.B, xk.H, l.k + l.n_reg, xk.D),
+    const hipStream_t st = current_stream();
+    const Scratch ws = scratch(ZC_FN(kQuantizeKVWs, zc_quantize_pack_kv_workspace)(xk.B, xk.H, l.k + l.n_reg, xk.D),
                                 tensor_of(a[0]), kScratchQuantizeKV, st);
     void* wp = ws.ptr;
     const size_t wn = ws.bytes;
@@ -262,12 +272,12 @@ PyObject* decode(PyObject*, Args a, Py_ssize_t n) {
     const float scale = float_of(a[7]);
     void* out = tensor_of(a[8]).data_ptr();
     auto* lse = ptr_as<float>(a[9]);
-    void* st = current_stream();
+    const hipStream_t st = current_stream();
     if (use_static) {
       const auto fn = ZC_FN(kDecodeStatic, zc_decode_attention_static);
       return unlocked([&] { return fn(&q, pk.get(), pv.get(), tkp, tvp, T, scale, out, lse, st); });
     }
-    const Scratch& ws = scratch(ZC_FN(kDecodeWs, zc_decode_attention_workspace)(q.B, q.H, q.D), tensor_of(a[1]), kScratchDecode, st);
+    const Scratch ws = scratch(ZC_FN(kDecodeWs, zc_decode_attention_workspace)(q.B, q.H, q.D), tensor_of(a[1]), kScratchDecode, st);
     void* wp = ws.ptr;
     const size_t wn = ws.bytes;
     const auto fn = ZC_FN(kDecode, zc_decode_attention);
@@ -293,7 +303,7 @@ PyObject* probs(PyObject*, Args a, Py_ssize_t n) {
     auto* po = static_cast<float*>(out.data_ptr());
     const int64_t N = out.size(2);
     const float scale = float_of(a[7]);
-    void* st = current_stream();
+    const hipStream_t st = current_stream();
     const auto fn = ZC_FN(kProbs, zc_decode_probs);
     return unlocked([&] { return fn(&q, pk.get(), tkp, T, pos0, scale, lse, po, N, st); });
   });
@@ -313,7 +323,7 @@ PyObject* rows_saliency(PyObject*, Args a, Py_ssize_t n) {
     const int64_t B = rows.size(1), H = rows.size(2), N = rows.size(3), n_out = int_of(a[2]);
     const int normalize = PyObject_IsTrue(a[3]) != 0;
     auto* sp = static_cast<float*>(tensor_of(a[4]).data_ptr());
-    void* st = current_stream();
+    const hipStream_t st = current_stream();
     const auto fn = ZC_FN(kRows, zc_rows_saliency);
     return unlocked([&] { return fn(rp, lp, P, B, H, N, n_out, normalize, sp, st); });
   });
@@ -324,7 +334,7 @@ PyObject* dequantize(PyObject*, Args a, Py_ssize_t n) {
   return guarded(kDequantize, n, 2, [&]() -> int {
     const Packed p(a[0]);
     const zc_tensor4 o = describe(a[1]);
-    void* st = current_stream();
+    const hipStream_t st = current_stream();
     const auto fn = ZC_FN(kDequantize, zc_dequantize_cache);
     return unlocked([&] { return fn(p.get(), &o, st); });
   });
@@ -366,6 +376,7 @@ PyModuleDef kModule = {PyModuleDef_HEAD_INIT, "_zc_host", nullptr, -1, kMethods,
 }  // namespace
 
 PyMODINIT_FUNC PyInit__zc_host() {
-  g_scratch = new std::map<std::tuple<int, int, void*>, Scratch>();   // (never freed: tensors must not outlive the allocator at exit)
+  g_scratch = new std::map<std::tuple<int, int, void*>, Scratch>();   // (neither is freed: tensors must not outlive the allocator at exit)
+  g_captured = new std::vector<at::Tensor>();
   return PyModule_Create(&kModule);
 }

@@ -931,3 +931,53 @@ def test_probe_few_rows(B, Hq, Hkv, d, Lk, P, dtype):
     assert float((total - ph.double().mean(1)).abs().max()) <= 1e-6 * float(total.abs().max())
     ref, _ = zo.saliency_scores(Q[:1].double().numpy(), K[:1].double().numpy(), pos.numpy())
     assert np.abs(few[:1].cpu().double().numpy() - ref).max() <= 1e-4 * np.abs(ref).max()
+
+
+def _score(x, pos, out):
+    return zb.zc_probe_saliency(x, x, pos, scores=out, scores_per_head=None)
+
+
+def test_outgrown_scratch_goes_back_to_the_allocator():
+    """Requests that outgrow the buffer one after the other: what a stream holds stays below one and
+    a half times the largest."""
+    lib = zb.load()
+    pos = torch.arange(40, dtype=torch.int32, device=DEV)
+    x = torch.randn(1, 64, 40000, 64, device=DEV).to(torch.bfloat16)
+    out = torch.empty(1, 40000, device=DEV)
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        torch.cuda.synchronize()
+        base, need = torch.cuda.memory_allocated(), 0
+        while True:
+            L = 1000 if need == 0 else int(L * 1.2)
+            if L > 40000:
+                break
+            need = lib.zc_probe_saliency_workspace(1, 64, L, 40)
+            _score(x[:, :, :L], pos, out[:, :L])
+            assert torch.cuda.memory_allocated() - base <= 1.5 * need + 1024
+        torch.cuda.synchronize()
+
+
+def test_scratch_of_a_captured_call_outlives_its_replacement():
+    """A graph's scratch is not handed out after a larger call has replaced it: tensors allocated
+    since keep their values over a replay, and the replay its scores."""
+    pos = torch.arange(40, dtype=torch.int32, device=DEV)
+    x = torch.randn(1, 32, 9000, 64, device=DEV).to(torch.bfloat16)
+    small, out, big = x[:, :, :3000].contiguous(), torch.empty(1, 3000, device=DEV), torch.empty(1, 9000, device=DEV)
+    s = torch.cuda.Stream()
+    s.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(s):
+        want = _score(small, pos, out).clone()
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            _score(small, pos, out)
+        _score(x, pos, big)                                  # replaces the buffer
+        need = zb.load().zc_probe_saliency_workspace(1, 32, 3000, 40)
+        fill = [torch.full((need,), 7, dtype=torch.uint8, device=DEV) for _ in range(4)]
+        for _ in range(3):
+            out.zero_()
+            graph.replay()
+            s.synchronize()
+            assert torch.equal(out, want)
+            assert all(bool((f == 7).all()) for f in fill)
