@@ -232,8 +232,10 @@ int zc_quantize_pack(const zc_tensor4* x, const int32_t* salient_idx, int64_t k,
 /* ---- the four quantizer calls of Algorithm 2 at once ------------------------------------
  * Keys and values of one cache compressed by the same launches: exactly what two
  * zc_quantize_pack calls (xk into outK, then xv into outV, same index lists and offset)
- * leave behind, bit for bit, in half the launches (three, when outK is CHANNEL / ROW, outV is
- * CST / TGROUP and a token row has at most 2048 channels; four or five otherwise).  xk and xv
+ * leave behind, bit for bit, in half the launches or fewer (two, when outK is CHANNEL / ROW, outV is
+ * CST / TGROUP and a token row has at most 2048 channels or the keys' tokens fit the registers of
+ * one sweep; three at most otherwise; one more where long subsets of few channels go by token
+ * ranges).  xk and xv
  * must agree in shape and dtype; outK and outV are two different descriptors.  Workspace:
  * zc_quantize_pack_kv_workspace(B, H, k + n_reg, D).  Errors as for zc_quantize_pack; when
  * one is returned neither descriptor has been changed. */

@@ -6,7 +6,7 @@
 namespace zc {
 
 constexpr int kTailUnit = 16;    // tail tokens per work unit of the MFMA decode kernel (a multiple of 16)
-constexpr int kMaxSplits = 128;
+constexpr int kMaxSplits = 32;   // most workgroups per (batch, KV head): the reduce kernel has a lane per split
 constexpr int kTailSplits = 8;    // 4 * kTailSplits: most waves per (batch, KV head) that share the tail
 constexpr int kStagedRun = 16;   // packed waves with fewer cost units than this get the staged operand inputs
 constexpr int kSegCost = 3;        // cost, in blocks, charged for starting a segment (query operand)
@@ -39,11 +39,11 @@ struct DecArgs {
   int64_t tk_sB, tk_sH, tk_sL, tv_sB, tv_sH, tv_sL;
   int tail_len;
   float scale_log2;
-  int S, n_units;  // workgroups per (batch, KV head); length of the packed cache's cost line
+  int S;           // workgroups per (batch, KV head)
   int n_pw, n_tw;  // waves per (batch, KV head) that share the packed cache / the tail; n_pw + n_tw = 4 S
   int tw_full, tw_rem;   // n_tw = tw_full * S + tw_rem: tail waves per workgroup, and workgroups with one more
   int tail_alone;        // 1: instead, the last n_tw workgroups hold one tail wave each and no packed wave
-  int pw_q, pw_r;        // n_units = pw_q * n_pw + pw_r: cost units per packed wave, and waves with one more
+  int pw_q, pw_r;        // cost units of the packed cache = pw_q * n_pw + pw_r: units per packed wave, and waves with one more
   int tu_q, tu_r;        // tail units = tu_q * n_tw + tu_r, likewise
   int n_cu;        // compute units of the device
   float* part_m;   // [B, Hq, S]

@@ -139,7 +139,6 @@ static int decode_entry(const zc_tensor4* q, const zc_packed* Kp, const zc_packe
   a.tv_sB = tail_len ? tail_v->sB : 0; a.tv_sH = tail_len ? tail_v->sH : 0; a.tv_sL = tail_len ? tail_v->sL : 0;
   a.tail_len = (int)tail_len;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
-  a.n_units = (int)units;
   {
     // compute units of the current device (asked once per process and device id)
     static int cu_of_device[64] = {0};

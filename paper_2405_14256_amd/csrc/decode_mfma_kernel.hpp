@@ -78,7 +78,6 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 constexpr float kLoScale = 2048.f;          // residual operand is scaled by 2^11
 constexpr float kLoInv = 1.f / 2048.f;
-constexpr int kCombineMax = 32;             // most workgroups per (batch, KV head) on this path
 
 __device__ inline f4 mfma16(u4 a, u4 b, f4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
@@ -394,7 +393,7 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
   const int pw = p_alone ? 4 * s + wave
                          : 4 * s - p_tw_full * s - max(0, s - (p_S - p_tw_rem)) + wave;    // index among the packed waves
   // (unit j of the line belongs to packed wave j / q for the first r * (q + 1) units, where the
-  // host has divided n_units = q * n_pw + r: the first r waves take one unit more; no division here)
+  // host has divided the line: units = q * n_pw + r: the first r waves take one unit more; no division here)
   const int u0 = tail_wave ? 0 : p_pw_q * pw + min(pw, p_pw_r);
   const int u1 = tail_wave ? 0 : p_pw_q * (pw + 1) + min(pw + 1, p_pw_r);
 
@@ -1293,13 +1292,13 @@ __global__ __launch_bounds__(256, MINB) void k_decode_mfma(DecArgs a) {
 // past the last one are out of range of the buffer: zeros, with weight 0), and the weights 2^(m - M) come from one
 // exponential over the lanes, handed round as scalars.  (With a branch per split - which
 // loads exist depends on S - the loads took 1.6 us to issue and land, against 0.8 us here.)
-// NMAX: the most splits this instance handles (8, 16, 24 or kCombineMax: the smallest that holds S -
+// NMAX: the most splits this instance handles (8, 16, 24 or kMaxSplits: the smallest that holds S -
 // an output partial that does not exist still costs its load and its two instructions).
 template <int DT, int D, int NMAX>
 __global__ __launch_bounds__(D) void k_decode_reduce(const float* __restrict__ part_m, const float* __restrict__ part_z,
                                                       const float* __restrict__ part_o, int S,
                                                       void* __restrict__ out, float* __restrict__ lse_out) {
-  static_assert(NMAX <= kCombineMax && kCombineMax <= 64, "one lane per split");
+  static_assert(NMAX <= kMaxSplits && kMaxSplits <= 64, "one lane per split");
   const int64_t hq = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;  // b * Hq + h
   const int c = threadIdx.x, lane = c & 63;
   const int last = S - 1;
@@ -1370,8 +1369,8 @@ static int launch_decode_mfma_dt(const DecArgs& a, hipStream_t st) {
   ZC_LAUNCH_CHECK();
   if (a.S > 1) {
 #define ZC_R(DD, NM) hipLaunchKernelGGL((k_decode_reduce<DT, DD, NM>), dim3(a.Hq, a.B), dim3(DD), 0, st, a.part_m, a.part_z, a.part_o, a.S, a.out, a.lse_out)
-    if (a.D == 128) { if (a.S <= 8) ZC_R(128, 8); else if (a.S <= 16) ZC_R(128, 16); else if (a.S <= 24) ZC_R(128, 24); else ZC_R(128, kCombineMax); }
-    else { if (a.S <= 8) ZC_R(64, 8); else if (a.S <= 16) ZC_R(64, 16); else if (a.S <= 24) ZC_R(64, 24); else ZC_R(64, kCombineMax); }
+    if (a.D == 128) { if (a.S <= 8) ZC_R(128, 8); else if (a.S <= 16) ZC_R(128, 16); else if (a.S <= 24) ZC_R(128, 24); else ZC_R(128, kMaxSplits); }
+    else { if (a.S <= 8) ZC_R(64, 8); else if (a.S <= 16) ZC_R(64, 16); else if (a.S <= 24) ZC_R(64, 24); else ZC_R(64, kMaxSplits); }
 #undef ZC_R
     ZC_LAUNCH_CHECK();
   }

@@ -35,7 +35,7 @@ def test_tiny_other_schemes(k_scheme, v_scheme):
 
 @pytest.mark.parametrize("bits_hi,bits_lo", [(8, 4), (8, 8), (4, 4), (2, 2), (8, 2)])
 def test_other_bit_widths(bits_hi, bits_lo):
-    # 8-bit subsets take the generic decode kernel, equal widths the matrix-core one
+    # 8-bit subsets take the decode instances with centred codes, 2- and 4-bit ones the others
     run_pipeline_check(scaled(WORKLOADS["tiny"], bits_hi=bits_hi, bits_lo=bits_lo), decode_steps=3, verbose=True)
     w = scaled(WORKLOADS["llama3_8b_4k"], L=700, decode_steps=2, bits_hi=bits_hi, bits_lo=bits_lo)
     run_pipeline_check(w, verbose=True)
