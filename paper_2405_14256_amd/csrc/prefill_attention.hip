@@ -52,7 +52,10 @@ __device__ inline uint32_t pack_pair(float lo, float hi) {
 __device__ inline void prefill_block(const PrefillArgs& a, int rows, int* b, int* hq, int* q0) {
   const int nqb = ceil_div(a.L, rows), heads = a.B * a.Hq;
   int id = blockIdx.x, head, qb;
-  if (heads & 7) {
+  if (nqb == 1) {                      // (short prompts: a division costs as much as their products)
+    qb = 0;
+    head = heads & 7 ? id : (id & 7) * (heads >> 3) + (id >> 3);
+  } else if (heads & 7) {
     qb = id / heads;
     head = id % heads;
   } else {
@@ -63,8 +66,13 @@ __device__ inline void prefill_block(const PrefillArgs& a, int rows, int* b, int
     head = (id & 7) * hpx + g * a.group + rem % size;
   }
   *q0 = (nqb - 1 - qb) * rows;
-  *b = head / a.Hq;
-  *hq = head % a.Hq;
+  if (a.B == 1) {
+    *b = 0;
+    *hq = head;
+  } else {
+    *b = head / a.Hq;
+    *hq = head % a.Hq;
+  }
 }
 
 // Chunk slot permutation of a V tile row: the transposing load reads 64 bytes of four
