@@ -238,8 +238,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
 // cycles (d = 128) and about 300 cycles of vector instructions, so the two have to run at the
 // same time.  The logits of half h + 1 are multiplied while the exponentials of half h are
 // taken, and the operands of each product are requested one phase before.  32 heads of 32768
-// rows, bf16: 8.80 -> 7.92 ms (1.11 PFLOP/s; a large library product reaches 1.21); 2 x 32
-// heads of 3001 rows, fp16: 220 -> 173 us; 16 heads of 4096 rows of 64 channels: 89 -> 57 us.
+// rows, bf16: 8.80 -> 7.74 ms (1.14 PFLOP/s; a large library product reaches 1.21); 2 x 32
+// heads of 3001 rows, fp16: 220 -> 171 us; 16 heads of 4096 rows of 64 channels: 89 -> 60 us.
 // Scheduling barriers between the slices of the first product, or a raised wave priority
 // around the second, cost 3 to 5 %.
 //
@@ -513,12 +513,19 @@ static int launch_prefill(PrefillArgs a, hipStream_t st) {
     else if (share >= 3100) hipLaunchKernelGGL((k_prefill_attention32<D, 2>), blocks(32, 128), dim3(128), 0, st, a);
     else hipLaunchKernelGGL((k_prefill_attention32<D, 4>), blocks(32, 64), dim3(256), 0, st, a);
   } else {
-    // Eight waves per workgroup read a K and V tile once for 256 rows; four where that leaves
-    // the chip fewer than two workgroups a CU, whose lengths then cannot even out (16 heads of
-    // 4096 rows of 64 channels, 256 against 512 workgroups: 68 against 51 us; 32 heads of 128
-    // channels, 512 against 1024: 133 against 144 us).
-    if (ceil_div(a.L, 256) * heads >= 512) hipLaunchKernelGGL((k_prefill_attention16<DT, D, 8>), blocks(256, 32), dim3(512), 0, st, a);
-    else hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), blocks(128, 64), dim3(256), 0, st, a);
+    // Four waves per workgroup, 128 rows: twice the workgroups to even the lengths out.  Eight read a
+    // K and V tile once for 256 rows, which only shows over long rows of 128 channels (32 heads
+    // of 32768 rows, bf16 7738 against 7796 us, fp16 8204 against 8303; of 16384 rows 1992 / 1997 and
+    // 2112 / 2127; but of 8192 rows 543 / 528, of 4096 rows at batch 2 289 / 276, 16 heads of 12000
+    // rows of 64 channels 376 / 346).
+    if constexpr (D == 128) {
+      if (a.L >= 16384 && ceil_div(a.L, 256) * heads >= 512) {
+        hipLaunchKernelGGL((k_prefill_attention16<DT, D, 8>), blocks(256, 32), dim3(512), 0, st, a);
+        ZC_LAUNCH_CHECK();
+        return ZC_OK;
+      }
+    }
+    hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), blocks(128, 64), dim3(256), 0, st, a);
   }
   ZC_LAUNCH_CHECK();
   return ZC_OK;

@@ -107,8 +107,8 @@ def test_probe_saliency_from_the_prefill_normalisers():
 @pytest.mark.parametrize("B,Hq,Hkv,d,L,rise", [
     (1, 2, 1, 128, 1, 0.0), (1, 3, 3, 64, 31, 0.0), (1, 4, 2, 128, 33, 0.0), (1, 2, 2, 64, 64, 0.0), (1, 8, 2, 128, 65, 0.0),
     (2, 12, 4, 128, 257, 0.0),              # heads that do not divide over the XCDs
-    (8, 64, 64, 64, 97, 0.0),               # 512 workgroups: eight waves each, fewer rows than waves
-    (4, 32, 8, 128, 1025, 0.0), (4, 32, 4, 64, 1057, 0.0),      # the same with many tiles, one row past a block and one wave more
+    (8, 64, 64, 64, 97, 0.0),               # fewer rows than waves
+    (4, 32, 8, 128, 1025, 0.0), (4, 32, 4, 64, 1057, 0.0),      # many tiles, one row past a block and one wave more
     (1, 4, 2, 128, 700, 40.0), (4, 32, 8, 128, 1025, 40.0),     # logits that climb by 2^40 and more: the reference of a row moves
 ])
 def test_prefill_tiles_and_reference(dtype, B, Hq, Hkv, d, L, rise):
@@ -149,3 +149,25 @@ def test_prefill_fp32_key_splits(B, Hq, Hkv, d, L):
         # a logit of magnitude 2^5 is off by a few of its units 2^-19, a weight by as much relatively, |V| stays below 2^3
         assert np.abs(out[b, h].double().cpu().numpy() - O_o[0, 0]).max() <= 1e-4
         assert np.abs(lse[b, h].double().cpu().numpy() - lse_o[0, 0]).max() <= 1e-4
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+def test_prefill_long_rows(dtype):
+    """Eight waves a workgroup (rows of 128 channels from 16384 on): the first and last rows and those
+    around a block's edge, against float64; one row past a block."""
+    Hq, Hkv, d, L = 8, 2, 128, 16385
+    g = torch.Generator().manual_seed(5)
+    Q, K, V = (torch.randn(1, H, L, d, generator=g).to(dtype).to(DEV) for H in (Hq, Hkv, Hkv))
+    out, lse, _ = zb.zc_prefill_attention(Q, K, V)
+    u = 2.0 ** (-8 if dtype == torch.bfloat16 else -11)
+    rows = torch.cat([torch.arange(0, 70), torch.arange(8180, 8200), torch.arange(L - 300, L)]).to(DEV)
+    for h in (0, 5):
+        k, v = K[0, h // 4].double(), V[0, h // 4].double()
+        logits = Q[0, h, rows].double() @ k.T / d ** 0.5
+        logits.masked_fill_(torch.arange(L, device=DEV)[None] > rows[:, None], float("-inf"))
+        want_lse = torch.logsumexp(logits, -1)
+        want = torch.exp(logits - want_lse[:, None]) @ v
+        vmax = float(v.abs().max())
+        # each weight is rounded once to the type (unit u), and so is the result: both are at most u / 2 of max |V|
+        assert float((out[0, h, rows].double() - want).abs().max()) <= u * vmax + 1e-5 * vmax
+        assert float((lse[0, h, rows].double() - want_lse).abs().max()) <= 1e-4
