@@ -788,7 +788,10 @@ static int qp_prepare(const zc_tensor4* x, const int32_t* salient_idx, int64_t k
 // tensors with too few workgroups to hide the packing behind each other's loads, where one
 // packing launch serves both (one prompt of 4096 tokens, 8 heads: 26.1 against 27.5 us); and
 // except for wide 16-bit rows of both that fit in slices of 16 channels only, a quarter of a
-// cache line (12000 tokens of 32 heads of 128 channels: 105 against 121 us; of 64: 216 and 279).
+// cache line (12000 tokens of 32 heads of 128 channels: 105 against 121 us; of 64: 216 and 279) -
+// above 512 channels where that also takes workgroups of 1024 threads (8192 tokens of 8 heads, 8
+// prompts: 134 against 146 us; of 16 heads, 2 prompts: 73 and 95; but of 2 heads, 8 prompts, 61 and
+// 50, and 4096 tokens of 8 heads, 8 prompts, in workgroups of 512: 69 and 66).
 struct ColPlan { int threads, split; };
 static ColPlan col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int dtype, bool joint_pack) {
   const int64_t n = a[0].n[0] > a[0].n[1] ? a[0].n[0] : a[0].n[1], rows = kColRows(dtype);
@@ -799,7 +802,8 @@ static ColPlan col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int
   int v = vl, th = threads;
   while (v > 2 && n > rows * th / v) v /= 2;
   if (n > rows * th / v) th = 1024;
-  const bool fits = n <= rows * th / v && !(joint_pack && wgs(v) < 256) && !(tensors == 2 && dtype != ZC_F32 && v == 2 && a[0].NV > 256);
+  const bool strips = tensors == 2 && dtype != ZC_F32 && v == 2 && a[0].NV > (th == 1024 ? 64 : 256);
+  const bool fits = n <= rows * th / v && !(joint_pack && wgs(v) < 256) && !strips;
   bool any = false;
   for (int t = 0; t < tensors; ++t) {
     a[t].resident = fits && out[t]->scheme == ZC_SCHEME_CHANNEL && out[t]->layout == ZC_LAYOUT_ROW;
