@@ -856,6 +856,7 @@ def test_decode_timeline_mode_of_the_benchmark():
     (4, 40, 128, 161, torch.float32), (2, 16, 128, 1300, torch.bfloat16),
     (64, 8, 128, 25, torch.bfloat16), (64, 8, 128, 60, torch.float16), (128, 8, 64, 64, torch.float32), (1, 1, 64, 255, torch.bfloat16),   # few tokens: small workgroups, and one more
     (1, 17, 128, 5125, torch.bfloat16), (1, 17, 128, 3000, torch.float32),  # rows of more than 256 vectors that only fit in slices of 16 channels
+    (4, 4, 128, 5121, torch.bfloat16), (4, 5, 128, 5121, torch.float16),    # the same with 1024 threads: 64 vectors stay, more do not
     (2, 1, 128, 33001, torch.bfloat16), (1, 2, 64, 9000, torch.float32),    # token ranges: the last one shorter, those of the other subset empty
     (1, 5, 64, 12289, torch.float16)])
 def test_quantize_column_sweep_edges(B, H, D, n_reg, dtype):
