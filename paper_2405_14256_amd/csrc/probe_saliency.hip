@@ -3,16 +3,13 @@
 //
 // The probe rows of A = Softmax(Q_probe K^T / sqrt(d)) are never stored.  Two
 // matrix-core sweeps recompute the logits instead:
-//   k_probe_lse     one workgroup per 128 probe rows and column range (the columns a
-//                   row block can see are cut into up to 8 ranges: to fill the chip
-//                   when the launch is small, and to even out row blocks that see
-//                   very different numbers of columns): the probe rows sit in
-//                   registers as matrix operands, 64-column K tiles stream through
-//                   LDS (global -> LDS transfers, the next tile's in flight), logits
-//                   come out of the MFMA as D[column][row] so that every lane owns
-//                   one probe row and keeps its running (reference, sum) in two
-//                   registers; writes the pair per row and column range
-//                   (k_probe_lse_merge joins the ranges).
+//   k_probe_lse     one workgroup per 128 probe rows and column range (the row blocks of a
+//                   head share its workgroups by the columns they can see): the probe rows
+//                   sit in registers as matrix operands, 64-column K tiles stream through
+//                   LDS (global -> LDS transfers, the next tile's in flight), logits come
+//                   out of the MFMA as D[column][row] so that every lane owns one probe row
+//                   and keeps its running (reference, sum) in two registers; writes the
+//                   pair per row and column range (k_probe_lse_merge joins the ranges).
 //   k_probe_colsum  one workgroup per 128 key columns: K fragments stay in
 //                   registers, 64-row probe tiles stream through LDS with their
 //                   positions and log-sum-exps, logits come out as D[row][column] so
@@ -24,11 +21,19 @@
 // probe that can see it and a row tile stops at its last row's position.
 // Inputs in fp16 / bf16 use the 32x32x16 MFMA, fp32 inputs the 32x32x2 fp32 MFMA
 // (no rounding of the operands); accumulation and softmax are fp32.
+// Both sweeps are bound by instruction issue: a wave's 32 x 64 logits take 16 matrix
+// instructions and 32 triples (fma, exponential, add) a lane, which barely overlap, 0.6 us of
+// a SIMD at the clock the chip holds, however many waves it has.  Small prompts are bound by
+// how the work falls on the CUs and by the waves' start: 32 heads of 128 channels over 8, 4096
+// tokens, 410 probe rows, bf16: 58.3 -> 44.1 us with operands brought in as whole rows, four
+// workgroups a CU and row blocks sharing workgroups by the columns they see (sweep 1 26 -> 24 us,
+// sweep 2 31.6 -> 19); 16384 tokens 390 -> 380.
 #include "mfma_tiles.hpp"
 
 namespace zc {
 
-constexpr int kMaxProbeSplit = 8;
+constexpr int kProbeParts = 8;       // column ranges of a block of probe rows the workspace is sized for
+constexpr int kMaxProbeParts = 12;   // most (what else they need is borrowed from the per-head scores, which come later)
 
 struct ProbeArgs {
   const void* q;
@@ -40,18 +45,83 @@ struct ProbeArgs {
   float scale_log2;
   const float* lse_in;   // natural log, [B, Hq, P]; null: use lse2
   float* lse2;           // [B, Hq, P] log-sum-exp in log2 units: sweep 1's result
-  float2* lse_part;      // [B, Hq, P, nsplit] (running maximum in log2 units, sum) when nsplit > 1
-  int nsplit;            // column ranges a row block's sweep 1 is split into
+  float2* lse_part;      // [B, Hq, P, max_parts] (running maximum in log2 units, sum) of the column ranges
+  int max_parts;         // even: a row's pairs are read two at a time
+  int head_wgs;          // workgroups of a head in sweep 1 (one per row block: no column ranges)
   float* per_head;       // [B, Hq, Lk]
   int small;             // 1: few probe rows, sweep 2 and the mean in one launch
   int normalize;         // 1: divide a column's sum by the number of probes that see it (Eq. 8); 0: Eq. 7
 };
 
+// Two 32x32 results of one row of operands in LDS (row: the address of its chunk kh; chunk
+// 2 kc + kh sits at slot (2 kc + kh) ^ swz, one exclusive or away) and two in registers.  An
+// operand is requested two steps ahead: left to itself the compiler, short of registers, waits
+// for each in front of the instructions that use it.
+template <int DT, int NKC>
+__device__ inline void product_pair(v16f (&acc)[2], uint32_t row, const u32x4 (&f)[2][NKC]) {
+  using lds_u32x4 = __attribute__((address_space(3))) const u32x4;
+  constexpr int kDsRead = 0x100, kMfma = 0x8, MPC = DT == ZC_F32 ? 8 : 2;     // matrix instructions of a step
+#pragma unroll
+  for (int i = 0; i < 16; ++i) { acc[0][i] = 0.f; acc[1][i] = 0.f; }
+  u32x4 a[2];
+  a[0] = *reinterpret_cast<lds_u32x4*>(row);
+  a[1] = *reinterpret_cast<lds_u32x4*>(row ^ 32);
+  __builtin_amdgcn_sched_group_barrier(kDsRead, 2, 0);
+#pragma unroll
+  for (int kc = 0; kc < NKC; ++kc) {
+    const u32x4 af = a[kc & 1];
+    mma_chunk<DT>(acc[0], af, f[0][kc]);
+    mma_chunk<DT>(acc[1], af, f[1][kc]);
+    __builtin_amdgcn_sched_group_barrier(kMfma, MPC, 0);
+    if (kc + 2 < NKC) {
+      a[kc & 1] = *reinterpret_cast<lds_u32x4*>(row ^ ((kc + 2) << 5));
+      __builtin_amdgcn_sched_group_barrier(kDsRead, 1, 0);
+    }
+  }
+}
+
+// A copy the compiler knows nothing of: what is computed from it is computed where it is used, not
+// kept in a register across a loop.
+__device__ inline int opaque(int x) { asm volatile("" : "+v"(x)); return x; }
+
 constexpr int kLseRows = 128;                  // probe rows per workgroup of sweep 1
 constexpr int kLseCols = 64;                   // columns per K tile of sweep 1
 
+// The row blocks of a head share its a.head_wgs workgroups in proportion to the column tiles their
+// rows can see (a block near the end of a prompt sees ten times those of one near its start; a
+// short last block counts in full: it has fewer waves, but each takes as long), each at least
+// one and at most a.max_parts.  Lane i of a wave holds block i.
+struct LseShare { int block, part, parts, tiles; };      // block < 0: a workgroup without work
+__device__ inline LseShare lse_share(const ProbeArgs& a, int nrb, int j) {
+  LseShare s;
+  if (nrb > 64) {                                        // (more than 8192 probe rows: even ranges)
+    s.parts = min(a.head_wgs / nrb, a.max_parts);
+    s.block = j / s.parts; s.part = j % s.parts;
+    if (s.block >= nrb) s.block = -1;
+    else s.tiles = min(a.probe_pos[min(a.P, (s.block + 1) * kLseRows) - 1], a.Lk - 1) / kLseCols + 1;
+    return s;
+  }
+  const int i = threadIdx.x & 63, rows = a.P - i * kLseRows;
+  int tiles = 0;
+  if (rows > 0) tiles = min(a.probe_pos[min(a.P, (i + 1) * kLseRows) - 1], a.Lk - 1) / kLseCols + 1;
+  // one each, what is left by the cumulated tiles (the last block's: all of them, whatever the rounding)
+  const int upto = wave_inclusive_sum(tiles), from = upto - tiles, total = __builtin_amdgcn_readlane(upto, 63);
+  const float rate = (float)(a.head_wgs - nrb) / (float)total;
+  const int s1 = upto == total ? a.head_wgs - nrb : min((int)((float)upto * rate), a.head_wgs - nrb), s0 = (int)((float)from * rate);
+  const int share = rows > 0 ? min(1 + max(s1 - s0, 0), a.max_parts) : 0;
+  const int end = wave_inclusive_sum(share);
+  const uint64_t past = __ballot(j < end);               // the blocks that end behind workgroup j
+  s.block = past ? __builtin_ctzll(past) : -1;
+  if (s.block < 0) return s;
+  s.parts = __builtin_amdgcn_readlane(share, s.block);
+  s.part = j - (__builtin_amdgcn_readlane(end, s.block) - s.parts);
+  s.tiles = __builtin_amdgcn_readlane(tiles, s.block);
+  return s;
+}
+
+// Four workgroups to a CU (128 registers, 35 KB of LDS) for rows of up to 256 bytes.
 template <int DT, int D>
-__global__ __launch_bounds__(256, 2) void k_probe_lse(ProbeArgs a) {
+__global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_probe_lse(ProbeArgs a) {
   using T = Tile<DT, D>;
   constexpr int TILE_B = kLseCols * T::ROWB;
   constexpr int NI = kLseCols / T::RPI / 4;     // transfers per wave and K tile
@@ -59,11 +129,13 @@ __global__ __launch_bounds__(256, 2) void k_probe_lse(ProbeArgs a) {
   __shared__ int spos[kLseRows];
   __shared__ float sm[2][kLseRows], sz[2][kLseRows];
 
-  // logical order: probe-row block fastest, then column range, then query head, then batch
+  // logical order: workgroup of a head fastest, then query head, then batch
   const int nrb = ceil_div(a.P, kLseRows);
   int j = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int rb0 = (j % nrb) * kLseRows; j /= nrb;
-  const int split = j % a.nsplit; j /= a.nsplit;
+  const LseShare share = lse_share(a, nrb, j % a.head_wgs);
+  if (share.block < 0) return;
+  j /= a.head_wgs;
+  const int rb0 = share.block * kLseRows;
   const int hq = j % a.Hq, b = j / a.Hq, hk = hq / a.G;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -74,20 +146,19 @@ __global__ __launch_bounds__(256, 2) void k_probe_lse(ProbeArgs a) {
   const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.Lk - 1) * k_rowb + T::ROWB, kBufFlags);
   const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.Lq - 1) * q_rowb + T::ROWB, kBufFlags);
 
-  // the block's last row decides how many column tiles it sees
   const int nvalid = min(kLseRows, a.P - rb0);
-  const int pmax = min(a.probe_pos[rb0 + nvalid - 1], a.Lk - 1);
-  const int ntiles = pmax / kLseCols + 1;
   // this workgroup's share of the column tiles
-  const int per = ceil_div(ntiles, a.nsplit);
-  const int t_begin = split * per, t_end = min(t_begin + per, ntiles);
+  const int per = ceil_div(share.tiles, share.parts);
+  const int t_begin = share.part * per, t_end = min(t_begin + per, share.tiles);
 
   // A K tile goes global -> LDS directly, every wave a quarter of its transfers;
   // the per-lane part of the addresses is fixed, the tile adds a scalar.
   const uint32_t ks_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&Ks[0][0];
-  int kvoff[NI];
+  // (where the swizzle repeats from one of a wave's transfers to the next, so does the rest)
+  constexpr bool SAME = 4 * T::RPI / T::RP256 % T::SW == 0;
+  int kvoff[SAME ? 1 : NI];
 #pragma unroll
-  for (int jj = 0; jj < NI; ++jj) {
+  for (int jj = 0; jj < (SAME ? 1 : NI); ++jj) {
     const int row = (w + 4 * jj) * T::RPI + lane / T::CPR;
     kvoff[jj] = (int)(row * k_rowb) + (((lane % T::CPR) ^ T::swz(row)) << 4);
   }
@@ -96,41 +167,55 @@ __global__ __launch_bounds__(256, 2) void k_probe_lse(ProbeArgs a) {
   auto issue = [&](int t, int buf) {
     const int toff = (int)((uint32_t)t * kLseCols * k_rowb);
 #pragma unroll
-    for (int jj = 0; jj < NI; ++jj) dma16<0>(ks_lds + buf * TILE_B + (w + 4 * jj) * 1024, rs_k, kvoff[jj] + toff, 0);
+    for (int jj = 0; jj < NI; ++jj) dma16<0>(ks_lds + buf * TILE_B + (w + 4 * jj) * 1024, rs_k, SAME ? kvoff[0] + (toff + (int)(4 * jj * T::RPI * k_rowb)) : kvoff[SAME ? 0 : jj] + toff, 0);
   };
-  if (t_begin < t_end) issue(t_begin, 0);
-
-  // the probe rows of this wave, straight into operand registers
+  // The probe rows of this block come through the two tile buffers into operand registers: whole
+  // rows to a transfer (read straight into operand layout, 32 bytes of every cache line at a
+  // time, they took 6 us of a 27 us launch).
+  int last[2];                                   // last column a lane's row sees, less the lane's first in a tile (< 0: none)
+  {
+    int row[2 * NI];
+#pragma unroll
+    for (int jj = 0; jj < 2 * NI; ++jj) {
+      const int p = min(rb0 + (w + 4 * jj) * T::RPI + lane / T::CPR, a.P - 1);
+      row[jj] = a.probe_rows ? a.probe_rows[p] : a.probe_pos[p];
+    }
+    const int my_pos = a.probe_pos[min(rb0 + (tid & (kLseRows - 1)), a.P - 1)];
+#pragma unroll
+    for (int jj = 0; jj < 2 * NI; ++jj) {
+      const int i = (w + 4 * jj) * T::RPI + lane / T::CPR;
+      dma16<0>(ks_lds + (w + 4 * jj) * 1024, rs_q, i < nvalid ? (int)((uint32_t)row[jj] * q_rowb) + (((lane % T::CPR) ^ T::swz(i)) << 4) : kOutOfRange, 0);
+    }
+    if (tid < kLseRows) spos[tid] = tid < nvalid ? my_pos : -1;
+  }
+  wait_all_loads();
+  __syncthreads();
+  using lds_u32x4 = __attribute__((address_space(3))) const u32x4;
   u32x4 qf[2][T::NKC];
-  int myp[2];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
-    const int p = rb0 + rh * 64 + rb * 32 + r;
-    int voff = kOutOfRange;
-    myp[rb] = -1;
-    if (p < a.P) {
-      myp[rb] = a.probe_pos[p];
-      voff = (int)((uint32_t)(a.probe_rows ? a.probe_rows[p] : myp[rb]) * q_rowb) + kh * 16;
-    }
+    const int i = rh * 64 + rb * 32 + r;
+    last[rb] = spos[i] < 0 ? -1 : spos[i] - 4 * kh;
 #pragma unroll
-    for (int kc = 0; kc < T::NKC; ++kc) qf[rb][kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_q, voff + kc * 32, 0, 0);
+    for (int kc = 0; kc < T::NKC; ++kc) qf[rb][kc] = *reinterpret_cast<lds_u32x4*>(ks_lds + T::slot(i, 2 * kc + kh));
   }
-  if (tid < kLseRows) spos[tid] = (rb0 + tid < a.P) ? a.probe_pos[rb0 + tid] : -1;
   __syncthreads();
+  if (t_begin < t_end) issue(t_begin, 0);
   // rows are sorted by position: a block's first row bounds what is fully visible,
   // its last real row what is visible at all
-  int pos_last = -1;
-  if (rb0 + rh * 64 < a.P) pos_last = spos[min(rh * 64 + 63, nvalid - 1)];
+  // (scalars: read from LDS they would each hold a register)
+  const auto pos_at = [&](int i) { return __builtin_amdgcn_readfirstlane(spos[i]); };
+  const int pos_last = rb0 + rh * 64 < a.P ? pos_at(min(rh * 64 + 63, nvalid - 1)) : -1;
   // the same per 32-row block: its first row's position (-1: no row) and its last real row's
   int pfirst[2], plast[2];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
     const int base = rh * 64 + rb * 32;
-    pfirst[rb] = spos[base];
-    plast[rb] = rb0 + base < a.P ? spos[min(base + 31, nvalid - 1)] : -1;
+    pfirst[rb] = pos_at(base);
+    plast[rb] = rb0 + base < a.P ? pos_at(min(base + 31, nvalid - 1)) : -1;
   }
   float m[2] = {-INFINITY, -INFINITY}, z[2] = {0.f, 0.f};
-  const int krow = ch * 32 + r;                  // this lane's column inside a tile
+  const uint32_t abase = ks_lds + T::slot(ch * 32 + r, kh);
 
   for (int t = t_begin; t < t_end; ++t) {
     const int cur = (t - t_begin) & 1;
@@ -139,128 +224,129 @@ __global__ __launch_bounds__(256, 2) void k_probe_lse(ProbeArgs a) {
     if (t + 1 < t_end) issue(t + 1, cur ^ 1);
     if (t * kLseCols > pos_last) continue;       // nothing of this tile is visible to the wave's rows
     v16f acc[2];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) { acc[0][i] = 0.f; acc[1][i] = 0.f; }
-#pragma unroll
-    for (int kc = 0; kc < T::NKC; ++kc) {
-      const u32x4 af = *reinterpret_cast<const u32x4*>(&Ks[cur][T::slot(krow, 2 * kc + kh)]);
-      mma_chunk<DT>(acc[0], af, qf[0][kc]);
-      mma_chunk<DT>(acc[1], af, qf[1][kc]);
-    }
+    product_pair<DT, T::NKC>(acc, abase + cur * TILE_B, qf);
+    __builtin_amdgcn_sched_barrier(0);           // (here and below: what follows would be moved up, into registers there are not)
     const int colb = t * kLseCols + ch * 32;     // this wave's 32 columns of the tile
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       if (colb > plast[rb]) continue;            // none of them visible to this block's rows
-      if (colb + 31 <= pfirst[rb]) {
-        // Every logit of the tile counts.  The reference point m of a row only has to keep
-        // exp2 in range, not to be the maximum: it is taken from the row's first tile
-        // and moved only when a tile's sum shows that some logit lies 2^60 above it
-        // (the log-sum-exp m + log2(z) does not depend on the choice).
-        bool redo = __builtin_amdgcn_ballot_w64(m[rb] == -INFINITY) != 0;
-        if (!redo) {
-          float sum = 0.f;
+      // The reference point m of a row only has to keep exp2 in range, not to be the maximum: it
+      // is taken from the first columns the row sees and moved only when a tile's sum shows that
+      // some logit lies 2^60 above it (the log-sum-exp m + log2(z) does not depend on the choice).
+      const bool whole = colb + 31 <= pfirst[rb];            // every row of the block sees every column
+      const int vis = last[rb] - colb;                       // of its columns (acc_row(v, 0)) a lane sees those up to vis
+      bool set = __builtin_amdgcn_ballot_w64(m[rb] == -INFINITY && vis >= 0) != 0;
+#pragma unroll 1
+      for (int pass = 0; pass < 2; ++pass) {
+        if (set) {
+          const int seen = opaque(vis);                      // (or the compiler takes this maximum, and below the comparisons, every time)
+          float tmax = -INFINITY;
 #pragma unroll
-          for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(fmaf(acc[rb][v], a.scale_log2, -m[rb]));
-          redo = __builtin_amdgcn_ballot_w64(!(sum < 0x1p60f)) != 0;
-          if (!redo) z[rb] += sum;
-        }
-        if (redo) {
-          float tmax = fmaxf(acc[rb][0], acc[rb][1]);
-#pragma unroll
-          for (int v = 2; v < 16; v += 2) tmax = fmaxf(fmaxf(tmax, acc[rb][v]), acc[rb][v + 1]);
+          for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, acc_row(v, 0) <= seen ? acc[rb][v] : -INFINITY);
           const float m_new = fmaxf(m[rb], tmax * a.scale_log2);
-          float sum = 0.f;
-#pragma unroll
-          for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(fmaf(acc[rb][v], a.scale_log2, -m_new));
-          z[rb] = z[rb] * __builtin_amdgcn_exp2f(m[rb] - m_new) + sum;
+          if (m_new > -INFINITY) z[rb] *= __builtin_amdgcn_exp2f(m[rb] - m_new);
           m[rb] = m_new;
         }
-      } else {
-        float sv[16];
-        float tmax = -INFINITY;
+        float sum = 0.f;
+        if (whole) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int col = colb + acc_row(v, kh);
-          const float sc = (col <= myp[rb]) ? acc[rb][v] * a.scale_log2 : -INFINITY;
-          sv[v] = sc;
-          tmax = fmaxf(tmax, sc);
-        }
-        const float m_new = fmaxf(m[rb], tmax);
-        if (m_new > -INFINITY) {
-          float sum = 0.f;
+          for (int v = 0; v < 16; ++v) {
+            sum += __builtin_amdgcn_exp2f(fmaf(acc[rb][v], a.scale_log2, -m[rb]));
+            if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+          }
+        } else {
+          const int seen = opaque(vis);
+          const float ref = __int_as_float(opaque(__float_as_int(m[rb])));     // (or it joins the two loops, and holds all 16 terms)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) sum += __builtin_amdgcn_exp2f(sv[v] - m_new);
-          z[rb] = z[rb] * __builtin_amdgcn_exp2f(m[rb] - m_new) + sum;
-          m[rb] = m_new;
+          for (int v = 0; v < 16; ++v) {
+            const float e = __builtin_amdgcn_exp2f(fmaf(acc[rb][v], a.scale_log2, -ref));
+            sum += acc_row(v, 0) <= seen ? e : 0.f;
+            if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+          }
         }
+        if (set || __builtin_amdgcn_ballot_w64(!(sum < 0x1p60f)) == 0) {
+          z[rb] += sum;
+          break;
+        }
+        set = true;
       }
     }
   }
   // merge the two half-waves, then the two column halves
+  const int t1 = opaque(tid), r1 = t1 & 31;
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
-    const float mo = __shfl_xor(m[rb], 32), zo = __shfl_xor(z[rb], 32);
-    const float M = fmaxf(m[rb], mo);
+    const auto mh = __builtin_amdgcn_permlane32_swap(__float_as_uint(m[rb]), __float_as_uint(m[rb]), false, false);
+    const auto zh = __builtin_amdgcn_permlane32_swap(__float_as_uint(z[rb]), __float_as_uint(z[rb]), false, false);
+    const float m0 = __uint_as_float(mh[0]), m1 = __uint_as_float(mh[1]), M = fmaxf(m0, m1);
     float Z = 0.f;
-    if (M > -INFINITY) Z = z[rb] * exp2f(m[rb] - M) + zo * exp2f(mo - M);
-    if (kh == 0) { sm[ch][rh * 64 + rb * 32 + r] = M; sz[ch][rh * 64 + rb * 32 + r] = Z; }
+    if (M > -INFINITY) Z = __uint_as_float(zh[0]) * exp2f(m0 - M) + __uint_as_float(zh[1]) * exp2f(m1 - M);
+    if ((t1 & 32) == 0) { sm[ch][rh * 64 + rb * 32 + r1] = M; sz[ch][rh * 64 + rb * 32 + r1] = Z; }
   }
   __syncthreads();
-  if (tid < kLseRows && rb0 + tid < a.P) {
-    const float M = fmaxf(sm[0][tid], sm[1][tid]);
+  if (t1 < kLseRows && rb0 + t1 < a.P) {
+    const float M = fmaxf(sm[0][t1], sm[1][t1]);
     float Z = 0.f;
-    if (M > -INFINITY) Z = sz[0][tid] * exp2f(sm[0][tid] - M) + sz[1][tid] * exp2f(sm[1][tid] - M);
-    const int64_t row = ((int64_t)b * a.Hq + hq) * a.P + rb0 + tid;
-    if (a.nsplit == 1) a.lse2[row] = M + log2f(Z);
-    else a.lse_part[row * a.nsplit + split] = make_float2(M, Z);
+    if (M > -INFINITY) Z = sz[0][t1] * exp2f(sm[0][t1] - M) + sz[1][t1] * exp2f(sm[1][t1] - M);
+    const int64_t row = ((int64_t)b * a.Hq + hq) * a.P + rb0 + t1;
+    if (a.head_wgs == nrb) {
+      a.lse2[row] = M + log2f(Z);
+    } else {
+      float2* dst = a.lse_part + row * a.max_parts;
+      dst[share.part] = make_float2(M, Z);
+      if (share.part == share.parts - 1)                 // the ranges this block does not have
+        for (int p = share.parts; p < a.max_parts; ++p) dst[p] = make_float2(-INFINITY, 0.f);
+    }
   }
 }
 
 // Merges the (maximum, sum) pairs of a probe row's column ranges.
-__global__ void k_probe_lse_merge(const float2* __restrict__ part, float* __restrict__ lse2, int64_t rows, int nsplit) {
+__global__ void k_probe_lse_merge(const float2* __restrict__ part, float* __restrict__ lse2, int64_t rows, int max_parts) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= rows) return;
-  float2 v[kMaxProbeSplit];
+  float4 v[kMaxProbeParts / 2];                          // two pairs each
 #pragma unroll
-  for (int sp = 0; sp < kMaxProbeSplit; ++sp) v[sp] = sp < nsplit ? part[i * nsplit + sp] : make_float2(-INFINITY, 0.f);
+  for (int sp = 0; sp < kMaxProbeParts / 2; ++sp) {
+    v[sp] = reinterpret_cast<const float4*>(part + i * max_parts)[min(sp, max_parts / 2 - 1)];
+    if (2 * sp >= max_parts) v[sp] = make_float4(-INFINITY, 0.f, -INFINITY, 0.f);
+  }
   float M = -INFINITY;
 #pragma unroll
-  for (int sp = 0; sp < kMaxProbeSplit; ++sp) M = fmaxf(M, v[sp].x);
+  for (int sp = 0; sp < kMaxProbeParts / 2; ++sp) M = fmaxf(M, fmaxf(v[sp].x, v[sp].z));
   float Z = 0.f;
 #pragma unroll
-  for (int sp = 0; sp < kMaxProbeSplit; ++sp)
+  for (int sp = 0; sp < kMaxProbeParts / 2; ++sp) {
     if (v[sp].x > -INFINITY) Z += v[sp].y * exp2f(v[sp].x - M);
+    if (v[sp].z > -INFINITY) Z += v[sp].w * exp2f(v[sp].z - M);
+  }
   lse2[i] = M + log2f(Z);
 }
 
-__device__ inline int lower_bound_pos(const int32_t* pos, int n, int key) {
-  int lo = 0, hi = n;
-  while (lo < hi) {
-    const int mid = (lo + hi) >> 1;
-    if (pos[mid] < key) lo = mid + 1; else hi = mid;
-  }
-  return lo;
-}
-
-constexpr int kPosTable = 4096;     // probe positions kept in LDS (larger sets are read from memory)
-
+// Four workgroups to a CU (128 registers, 37 KB of LDS) for rows of up to 256 bytes, so that four
+// independent waves a SIMD overlap matrix and vector work and 1024 workgroups start at once.
 template <int DT, int D>
-__global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 2) void k_probe_colsum(ProbeArgs a) {
+__global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_probe_colsum(ProbeArgs a) {
   using T = Tile<DT, D>;
   constexpr int QT = 64;                        // probe rows per tile
   constexpr int TILE_B = QT * T::ROWB;
   constexpr int NI = QT / T::RPI / 4;           // transfers per wave and tile
   __shared__ __align__(16) uint8_t Qs[2][TILE_B];
-  __shared__ int32_t lpos[kPosTable];
-  __shared__ __align__(16) int spos[2][QT];
-  __shared__ __align__(16) float slse[2][QT];
+  __shared__ __align__(16) int spos[3][QT];     // positions, rows of q and log-sum-exps of three tiles
+  __shared__ __align__(16) int srow[3][QT];
+  __shared__ __align__(16) float slse[3][QT];
   __shared__ float scol[2][128];
+  __shared__ int bins[128];                     // probes at each of this workgroup's columns
+  __shared__ __align__(16) int before[4];       // probes in front of them, by wave
 
-  // logical order: column tile fastest, then query head, then batch
+  // logical order: column tile fastest, then query head, then batch; the tiles of every other
+  // head backwards, so that a CU's workgroups, 32 apart in an XCD's range, do not all see the
+  // many rows of a prompt's first columns or all the few of its last
   const int nct = ceil_div(a.Lk, 128);
   int j = xcd_contiguous(blockIdx.x, gridDim.x);
-  const int col0 = (j % nct) * 128; j /= nct;
+  int ct = j % nct; j /= nct;
   const int hq = j % a.Hq, b = j / a.Hq, hk = hq / a.G;
+  if (hq & 1) ct = nct - 1 - ct;
+  const int col0 = ct * 128;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rbw = w >> 1, cbp = w & 1;
@@ -271,121 +357,150 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 2) void k_pro
   const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.Lk - 1) * k_rowb + T::ROWB, kBufFlags);
   const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.Lq - 1) * q_rowb + T::ROWB, kBufFlags);
   const auto rs_pos = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.probe_pos), 0, (uint32_t)a.P * 4u, kBufFlags);
+  const auto rs_row = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.probe_rows ? a.probe_rows : a.probe_pos), 0, (uint32_t)a.P * 4u, kBufFlags);
   const float* lse_src = (a.lse_in ? a.lse_in : a.lse2) + lrow;
   const auto rs_lse = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(lse_src), 0, (uint32_t)a.P * 4u, kBufFlags);
 
-  // this wave's K columns, straight into operand registers (columns past the end: zeros)
+  // One pass over the probe positions: how many lie in front of these columns (the first probe
+  // that sees them, as positions ascend) and how many at each of them.
+  // Meanwhile the K columns come through the two tile buffers (whole rows to a transfer, as in
+  // sweep 1; columns past the end: zeros).
+  const uint32_t qs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&Qs[0][0];
+  if (tid < 128) bins[tid] = 0;
+  __syncthreads();
+  {
+#pragma unroll
+    for (int jj = 0; jj < 2 * NI; ++jj) {
+      const int i = (w + 4 * jj) * T::RPI + lane / T::CPR, col = col0 + i;
+      dma16<0>(qs_lds + (w + 4 * jj) * 1024, rs_k, col < a.Lk ? (int)((uint32_t)col * k_rowb) + (((lane % T::CPR) ^ T::swz(i)) << 4) : kOutOfRange, 0);
+    }
+    int n = 0;
+    for (int i0 = tid; i0 < a.P; i0 += 4 * 256) {
+      int pos[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) pos[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_pos, (i0 + u * 256) * 4, 0, 0);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const bool real = i0 + u * 256 < a.P;
+        n += real && pos[u] < col0 ? 1 : 0;
+        if (real && (uint32_t)(pos[u] - col0) < 128u) atomicAdd(&bins[pos[u] - col0], 1);
+      }
+    }
+    n = wave_inclusive_sum(n);
+    if (lane == 63) before[w] = n;
+  }
+  wait_all_loads();
+  __syncthreads();
+  using lds_u32x4 = __attribute__((address_space(3))) const u32x4;
   u32x4 kf[2][T::NKC];
 #pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
-    const int col = col0 + (cbp * 2 + cb) * 32 + r;
-    const int voff = col < a.Lk ? (int)((uint32_t)col * k_rowb) + kh * 16 : kOutOfRange;
+  for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-    for (int kc = 0; kc < T::NKC; ++kc) kf[cb][kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_k, voff + kc * 32, 0, 0);
-  }
-  // the probe positions go to LDS, so that the binary searches and the row addresses
-  // of this workgroup do not go to memory
-  const bool pos_in_lds = a.P <= kPosTable;
-  if (pos_in_lds) {
-    for (int i = tid; i < a.P; i += 256) lpos[i] = a.probe_pos[i];
-    __syncthreads();
-  }
-  const bool rows_in_lds = pos_in_lds && !a.probe_rows;              // the rows of q are the positions themselves
-  const auto lds_tab = (__attribute__((address_space(3))) const int32_t*)lpos;
-  const auto g_rows = (__attribute__((address_space(1))) const int32_t*)a.probe_rows;
-  const auto g_pos = (__attribute__((address_space(1))) const int32_t*)a.probe_pos;
-  const int pstart = pos_in_lds ? lower_bound_pos(lpos, a.P, col0) : lower_bound_pos(a.probe_pos, a.P, col0);
+    for (int kc = 0; kc < T::NKC; ++kc) kf[cb][kc] = *reinterpret_cast<lds_u32x4*>(qs_lds + T::slot((cbp * 2 + cb) * 32 + r, 2 * kc + kh));
+  const int pstart = __builtin_amdgcn_readfirstlane(before[0] + before[1] + before[2] + before[3]);
   float colsum[2] = {0.f, 0.f};
 
-  // A tile of 64 probe rows goes global -> LDS directly, every wave a quarter of its
-  // transfers; wave 0 also brings the rows' positions and log-sum-exps.
-  const uint32_t qs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&Qs[0][0];
+  // Wave 0 brings what a tile of 64 probe rows is looked up by two tiles ahead (0 past the last
+  // probe: row 0 of q, which the mask drops); the tile itself goes global -> LDS directly one
+  // ahead, every wave a quarter of its transfers.
   const uint32_t spos_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&spos[0][0];
+  const uint32_t srow_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&srow[0][0];
   const uint32_t slse_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)&slse[0][0];
-  auto issue = [&](int pr, int buf) {
-    // the rows of q this lane fetches: from the LDS table, or from memory (uniform branches
-    // over pointers of known address space: never a read through a generic pointer); the
-    // reads from memory are waited for here, where their values are needed anyway, so that
-    // the compiler carries no load of its own into the rest of the loop (see wait_all_loads)
-    uint32_t qrow[NI];
-    if (rows_in_lds) {
-#pragma unroll
-      for (int jj = 0; jj < NI; ++jj) qrow[jj] = (uint32_t)lds_tab[min(pr + (w + 4 * jj) * T::RPI + lane / T::CPR, a.P - 1)];
-    } else {
-#pragma unroll
-      for (int jj = 0; jj < NI; ++jj) {
-        const int pc = min(pr + (w + 4 * jj) * T::RPI + lane / T::CPR, a.P - 1);
-        qrow[jj] = a.probe_rows ? (uint32_t)g_rows[pc] : (uint32_t)g_pos[pc];
-      }
-      wait_all_loads();
-    }
+  auto look_up = [&](int pr, int slot) {
+    const int voff = (pr + (opaque(tid) & 63)) * 4;
+    dma4(spos_lds + slot * (QT * 4), rs_pos, voff, 0);
+    dma4(srow_lds + slot * (QT * 4), rs_row, voff, 0);
+    dma4(slse_lds + slot * (QT * 4), rs_lse, voff, 0);
+  };
+  const auto to_log2 = [&](int slot) { if (a.lse_in) slse[slot][opaque(tid) & 63] *= kLog2e; };     // an external log-sum-exp is in natural units
+  auto issue = [&](int slot, int buf) {
 #pragma unroll
     for (int jj = 0; jj < NI; ++jj) {
       const int row = (w + 4 * jj) * T::RPI + lane / T::CPR;
-      const int p = pr + row;
-      const int voff = p < a.P ? (int)(qrow[jj] * q_rowb) + (((lane % T::CPR) ^ T::swz(row)) << 4) : kOutOfRange;
-      dma16<0>(qs_lds + buf * TILE_B + (w + 4 * jj) * 1024, rs_q, voff, 0);
-    }
-    if (w == 0) {
-      dma4(spos_lds + buf * (QT * 4), rs_pos, (pr + lane) * 4, 0);
-      dma4(slse_lds + buf * (QT * 4), rs_lse, (pr + lane) * 4, 0);
+      dma16<0>(qs_lds + buf * TILE_B + (w + 4 * jj) * 1024, rs_q, opaque((int)((uint32_t)srow[slot][row] * q_rowb)) + (((lane % T::CPR) ^ T::swz(row)) << 4), 0);
     }
   };
-  if (pstart < a.P) issue(pstart, 0);
-  const int qrow_l = rbw * 32 + r;               // this lane's row inside a tile
+  if (pstart < a.P) {
+    if (w == 0) {
+      look_up(pstart, 0);
+      look_up(pstart + QT, 1);
+      wait_all_loads();
+      to_log2(0);
+    }
+    __syncthreads();
+    issue(0, 0);
+  }
+  const uint32_t abase = qs_lds + T::slot(rbw * 32 + r, kh);
 
+  int slot = 0, cur = 0;
   for (int pr = pstart; pr < a.P; pr += QT) {
-    const int cur = ((pr - pstart) / QT) & 1;
     wait_all_loads();    // this wave's transfers of the tile have landed ...
     __syncthreads();     // ... and everyone's; nobody still reads the other buffer
-    if (pr + QT < a.P) issue(pr + QT, cur ^ 1);
-    float rl[16];
-#pragma unroll
-    for (int v = 0; v < 16; ++v) rl[v] = slse[cur][rbw * 32 + acc_row(v, kh)];
-    if (a.lse_in) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v) rl[v] *= kLog2e;       // an external log-sum-exp is in natural units
-    }
-    v16f acc[2];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) { acc[0][i] = 0.f; acc[1][i] = 0.f; }
-#pragma unroll
-    for (int kc = 0; kc < T::NKC; ++kc) {
-      const u32x4 af = *reinterpret_cast<const u32x4*>(&Qs[cur][T::slot(qrow_l, 2 * kc + kh)]);
-      mma_chunk<DT>(acc[0], af, kf[0][kc]);
-      mma_chunk<DT>(acc[1], af, kf[1][kc]);
-    }
-    // a tile of 64 real rows whose first position is past this workgroup's last
-    // column needs no mask
-    const bool tile_full = pr + QT <= a.P && col0 + 127 <= spos[cur][0];
-#pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-      const int col = col0 + (cbp * 2 + cb) * 32 + r;
-      if (tile_full) {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) colsum[cb] += __builtin_amdgcn_exp2f(fmaf(acc[cb][v], a.scale_log2, -rl[v]));
-      } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const float e = __builtin_amdgcn_exp2f(fmaf(acc[cb][v], a.scale_log2, -rl[v]));
-          const int row = rbw * 32 + acc_row(v, kh);
-          const bool seen = col <= spos[cur][row] && pr + row < a.P;    // (rows past the last probe arrive as zeros)
-          colsum[cb] += seen ? e : 0.f;
-        }
+    const int next = slot == 2 ? 0 : slot + 1;
+    if (pr + QT < a.P) {
+      issue(next, cur ^ 1);
+      if (w == 0) {
+        to_log2(next);
+        look_up(pr + 2 * QT, next == 2 ? 0 : next + 1);
       }
     }
+    v16f acc[2];
+    product_pair<DT, T::NKC>(acc, abase + cur * TILE_B, kf);
+    __builtin_amdgcn_sched_barrier(0);           // (what follows would be moved up, into registers there are not)
+    // a tile of 64 real rows whose first position is past this workgroup's last
+    // column needs no mask
+    const bool tile_full = pr + QT <= a.P && col0 + 127 <= __builtin_amdgcn_readfirstlane(spos[slot][0]);
+    const float4* rl4 = reinterpret_cast<const float4*>(&slse[slot][rbw * 32 + 4 * kh]);     // rows 8 g + 4 kh ..
+    if (tile_full) {
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 t = rl4[2 * g];
+        const float rl[4] = {t.x, t.y, t.z, t.w};
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) colsum[cb] += __builtin_amdgcn_exp2f(fmaf(acc[cb][4 * g + v], a.scale_log2, -rl[v]));
+      }
+    } else {
+      const int4* ps4 = reinterpret_cast<const int4*>(&spos[slot][rbw * 32 + 4 * kh]);
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const float4 t = rl4[2 * g];
+        const int4 s = ps4[2 * g];
+        const float rl[4] = {t.x, t.y, t.z, t.w};
+        const int row0 = pr + rbw * 32 + 4 * kh + 8 * g;
+        const int ps[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          const int col = col0 + (cbp * 2 + cb) * 32 + r;
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const float e = __builtin_amdgcn_exp2f(fmaf(acc[cb][4 * g + v], a.scale_log2, -rl[v]));
+            colsum[cb] += col <= ps[v] && row0 + v < a.P ? e : 0.f;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    slot = next;
+    cur ^= 1;
   }
+  const int t1 = opaque(tid), l1 = t1 & 63;
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
-    colsum[cb] += __shfl_xor(colsum[cb], 32);
-    if (kh == 0) scol[rbw][(cbp * 2 + cb) * 32 + r] = colsum[cb];
+    const auto halves = __builtin_amdgcn_permlane32_swap(__float_as_uint(colsum[cb]), __float_as_uint(colsum[cb]), false, false);
+    colsum[cb] = __uint_as_float(halves[0]) + __uint_as_float(halves[1]);
+    if (l1 < 32) scol[rbw][(cbp * 2 + cb) * 32 + l1] = colsum[cb];
   }
   __syncthreads();
-  if (tid < 128 && col0 + tid < a.Lk) {
-    const int col = col0 + tid;
-    const float total = scol[0][tid] + scol[1][tid];
-    const int cnt = a.P - (pos_in_lds ? lower_bound_pos(lpos, a.P, col) : lower_bound_pos(a.probe_pos, a.P, col));
-    a.per_head[((int64_t)b * a.Hq + hq) * a.Lk + col] = !a.normalize ? total : (cnt > 0 ? total / (float)cnt : 0.f);
+  if (t1 < 128) {
+    // probes at a column of this workgroup before this thread's: a scan over two waves
+    const int own = bins[t1];
+    int lower = pstart + wave_inclusive_sum(own) - own;
+    if (w == 1) lower += __builtin_amdgcn_readlane(wave_inclusive_sum(bins[l1]), 63);
+    const int col = col0 + t1, cnt = a.P - lower;
+    const float total = scol[0][t1] + scol[1][t1];
+    if (col < a.Lk) a.per_head[((int64_t)b * a.Hq + hq) * a.Lk + col] = !a.normalize ? total : (cnt > 0 ? total / (float)cnt : 0.f);
   }
 }
 
@@ -400,7 +515,13 @@ __global__ __launch_bounds__(256) void k_probe_mean(const float* __restrict__ pe
   float s = 0.f;
   if (i < Lk) {
     const int h1 = min(Hq, (gy + 1) * per);
-    for (int h = gy * per; h < h1; ++h) s += per_head[((int64_t)b * Hq + h) * Lk + i];
+    for (int h = gy * per; h < h1; h += 8) {           // (eight heads requested at once, added in order)
+      float v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = per_head[((int64_t)b * Hq + min(h + u, h1 - 1)) * Lk + i];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) s += h + u < h1 ? v[u] : 0.f;
+    }
   }
   part[gy][cx] = s;
   __syncthreads();
@@ -413,6 +534,15 @@ __global__ __launch_bounds__(256) void k_probe_mean(const float* __restrict__ pe
 // operand registers (each is used once, LDS would only add a trip).  Bound by what the loads of
 // one CU bring in, 32 cache lines an instruction: 8 heads of 64 channels, 256 tokens, 26 rows,
 // fp32: 8 us, 11 as two launches with a 64-row tile per head.
+__device__ inline int lower_bound_pos(const int32_t* pos, int n, int key) {
+  int lo = 0, hi = n;
+  while (lo < hi) {
+    const int mid = (lo + hi) >> 1;
+    if (pos[mid] < key) lo = mid + 1; else hi = mid;
+  }
+  return lo;
+}
+
 constexpr int kSmallRows = 32;        // most probe rows
 constexpr int kSmallTable = 4096;     // most log-sum-exps of a batch element (heads x rows)
 constexpr int small_threads(int dt, int d) { return dt == ZC_F32 && d == 128 ? 512 : 1024; }
@@ -491,11 +621,11 @@ __global__ __launch_bounds__(small_threads(DT, D)) void k_probe_small(ProbeArgs 
 template <int DT, int D>
 static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStream_t st) {
   if (need_lse) {
-    hipLaunchKernelGGL((k_probe_lse<DT, D>), dim3((unsigned)((int64_t)ceil_div(a.P, kLseRows) * a.Hq * a.B * a.nsplit)), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_probe_lse<DT, D>), dim3((unsigned)((int64_t)a.head_wgs * a.Hq * a.B)), dim3(256), 0, st, a);
     ZC_LAUNCH_CHECK();
-    if (a.nsplit > 1) {
+    if (a.head_wgs > ceil_div(a.P, kLseRows)) {
       const int64_t rows = (int64_t)a.B * a.Hq * a.P;
-      hipLaunchKernelGGL(k_probe_lse_merge, dim3((unsigned)ceil_div64(rows, 256)), dim3(256), 0, st, a.lse_part, a.lse2, rows, a.nsplit);
+      hipLaunchKernelGGL(k_probe_lse_merge, dim3((unsigned)ceil_div64(rows, 256)), dim3(256), 0, st, a.lse_part, a.lse2, rows, a.max_parts);
       ZC_LAUNCH_CHECK();
     }
   }
@@ -515,17 +645,16 @@ static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStr
 
 using namespace zc;
 
-// Column ranges per row block of sweep 1.  Enough workgroups to fill the chip once (three fit
-// a CU); and, however many there are, up to four ranges of at least 16 tiles each: a row block
-// near the end of a long prompt sees ten times the columns of one near the start, and whole
-// row blocks as units leave the chip half empty while the long ones finish.
-static int probe_splits(int64_t B, int64_t Hq, int64_t P, int64_t Lk) {
-  const int64_t wgs = B * Hq * ceil_div64(P, kLseRows);
-  const int64_t fill = 768 / wgs;
+// Workgroups of a head in sweep 1, which its row blocks share (k_probe_lse): enough to fill the
+// chip once (four fit a CU); and, however many blocks there are, four to a block on average
+// where the columns give each at least 16 tiles, so that the last workgroups to finish are short.
+static int64_t probe_head_wgs(int64_t B, int64_t Hq, int64_t P, int64_t Lk, int max_parts) {
+  const int64_t nrb = ceil_div64(P, kLseRows), fill = 1024 / (B * Hq);
   int64_t even = ceil_div64(Lk, kLseCols) / 16;
   if (even > 4) even = 4;
-  const int64_t ns = fill > even ? fill : even;
-  return (int)(ns < 1 ? 1 : (ns > kMaxProbeSplit ? kMaxProbeSplit : ns));
+  int64_t n = fill > even * nrb ? fill : even * nrb;
+  if (nrb > 64) n = n / nrb * nrb;
+  return n < nrb ? nrb : (n > nrb * max_parts ? nrb * max_parts : n);
 }
 // Whether few probe rows are served by one launch: a block of 32, and no more bytes per
 // workgroup than its CU's loads bring in within the time the other path's two launches take
@@ -541,7 +670,7 @@ static bool probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P,
   const int64_t limit = B * ceil_div64(Lk, 32) >= 256 ? 384 * 1024 : 128 * 1024;
   return (segments * 32 + Hq * P) * row_bytes <= limit;
 }
-static size_t lse_bytes(int64_t B, int64_t Hq, int64_t P) { return (size_t)align_up64(B * Hq * P * (kMaxProbeSplit * (int64_t)sizeof(float2) + 4), 256); }
+static size_t lse_bytes(int64_t B, int64_t Hq, int64_t P) { return (size_t)align_up64(B * Hq * P * (kProbeParts * (int64_t)sizeof(float2) + 4), 256); }
 
 extern "C" size_t zc_probe_saliency_workspace(int64_t B, int64_t Hq, int64_t Lk, int64_t P) {
   if (B <= 0 || Hq <= 0 || Lk <= 0 || P <= 0) return 0;
@@ -582,10 +711,15 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   float* ws_ph = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + lse_bytes(q->B, q->H, P));
   a.lse_in = lse_ext;
-  a.lse_part = reinterpret_cast<float2*>(ws);
-  a.lse2 = reinterpret_cast<float*>(a.lse_part + (int64_t)q->B * q->H * P * kMaxProbeSplit);
-  a.nsplit = probe_splits(q->B, q->H, P, k->L);
-  if ((int64_t)ceil_div64(P, kLseRows) * q->H * q->B * a.nsplit > 0x7fffffff || (int64_t)ceil_div64(k->L, 128) * q->H * q->B > 0x7fffffff)
+  // [log-sum-exps][column ranges' pairs, up to the end of the workspace: the per-head scores, at
+  // their place in it, are written when the pairs have been read]
+  const int64_t rows = q->B * q->H * P, lse2_bytes = align_up64(rows * 4, 16), fit = ((int64_t)need - lse2_bytes) / (rows * (int64_t)sizeof(float2));
+  a.lse2 = reinterpret_cast<float*>(ws);
+  a.lse_part = reinterpret_cast<float2*>(reinterpret_cast<uint8_t*>(ws) + lse2_bytes);
+  a.max_parts = (int)(fit < kMaxProbeParts ? fit : kMaxProbeParts) & ~1;
+  const int64_t head_wgs = probe_head_wgs(q->B, q->H, P, k->L, a.max_parts);
+  a.head_wgs = (int)head_wgs;
+  if (head_wgs * q->H * q->B > 0x7fffffff || (int64_t)ceil_div64(k->L, 128) * q->H * q->B > 0x7fffffff)
     return ZC_ERR_UNSUPPORTED;
   a.normalize = normalize ? 1 : 0;
   a.small = probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));

@@ -52,18 +52,6 @@ __device__ inline void pick_bin(const int* hist, int* wave_tot, int need, int ti
   __syncthreads();
 }
 
-// Inclusive sum over the 64 lanes of a wave (row shifts inside the rows of 16 lanes, then
-// lane 15 of a row to the next row, lane 31 to the upper half).
-__device__ inline int wave_inclusive_sum(int v) {
-  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);    // row_shr:1
-  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);    // row_shr:2
-  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);    // row_shr:4
-  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);    // row_shr:8
-  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);   // row_bcast:15 into rows 1 and 3
-  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);   // row_bcast:31 into rows 2 and 3
-  return v;
-}
-
 constexpr int kSelCand = 1024;                 // candidates one wave finishes the search on
 constexpr int kSelBufFlags = 0x00020000;       // buffer descriptor: raw 32-bit data, no swizzle
 constexpr int kSelDropped = (int)0xFFFFF000u;  // a store offset past the end of every output: the store is dropped

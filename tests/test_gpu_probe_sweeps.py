@@ -1,0 +1,68 @@
+"""Probe saliency: how the row blocks of the first sweep share a head's workgroups, tile edges of both sweeps."""
+import pytest
+import torch
+
+from paper_2405_14256_amd import binding as zb
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda"
+
+
+def reference(q, k, rows, pos, lse=None):
+    """Eq. 9 + Eq. 8 in float64 on the GPU, a head at a time."""
+    B, Hq, _, d = q.shape
+    G, Lk = Hq // k.shape[1], k.shape[2]
+    seen = pos[:, None] >= torch.arange(Lk, device=DEV)[None]
+    count = seen.sum(0).double()
+    scores = torch.zeros(B, Lk, dtype=torch.float64, device=DEV)
+    for b in range(B):
+        for h in range(Hq):
+            x = q[b, h, rows].double() @ k[b, h // G].double().T / d ** 0.5
+            x = x.masked_fill(~seen, float("-inf"))
+            norm = torch.logsumexp(x, -1) if lse is None else lse[b, h].double()
+            scores[b] += torch.exp(x - norm[:, None]).sum(0) / count.clamp(min=1)
+    return scores / Hq
+
+
+# (B, Hq, Hkv, d, L, dtype, probe positions): one row block and several ranges, blocks that see
+# from one tile to all of them, a block of one row, rows below a tile's width, more ranges than a
+# block may have, more than 64 blocks, both halves of a tile masked, the last tile ragged
+def spread(L, P):
+    return torch.linspace(0, L - 1, P).round().long().unique()
+
+
+CASES = [
+    (1, 1, 1, 128, 33000, torch.bfloat16, lambda L: spread(L, 40)),
+    (1, 8, 2, 128, 4097, torch.bfloat16, lambda L: spread(L, 385)),
+    (2, 6, 3, 64, 2111, torch.float16, lambda L: spread(L, 129)),
+    (1, 4, 4, 64, 1025, torch.float32, lambda L: torch.cat([torch.arange(200), torch.tensor([1024])])),
+    (1, 2, 1, 128, 777, torch.float32, lambda L: torch.arange(L - 300, L)),
+    (3, 5, 5, 128, 191, torch.float16, lambda L: torch.arange(60, 190)),
+    (1, 1, 1, 64, 8400, torch.bfloat16, lambda L: torch.arange(L - 8300, L)),
+    (1, 40, 40, 64, 130, torch.bfloat16, lambda L: torch.arange(L)),
+]
+
+
+@pytest.mark.parametrize("external", [False, True])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_scores_of_row_blocks_and_ranges(case, external):
+    B, Hq, Hkv, d, L, dtype, probes = CASES[case]
+    g = torch.Generator(device=DEV).manual_seed(case)
+    pos = probes(L).to(DEV)
+    P = pos.numel()
+    q = (torch.randn(B, Hq, P, d, generator=g, device=DEV) + 0.25).to(dtype)     # rows in an order of their own
+    rows = torch.randperm(P, generator=g, device=DEV)
+    k = torch.randn(B, Hkv, L, d, generator=g, device=DEV)
+    k[..., ::31] *= 15.0
+    k = k.to(dtype)
+    lse = 40.0 + torch.randn(B, Hq, P, generator=g, device=DEV) if external else None
+    want = reference(q, k, rows, pos, lse)
+    per_head = torch.empty(B, Hq, L, device=DEV)
+    for ph in (None, per_head):
+        got = zb.zc_probe_saliency(q, k, pos.int(), probe_rows=rows.int(), lse_ext=lse, scores_per_head=ph)
+        # A logit is an fp32 sum of up to 128 exact products: off by a few 2^-24 of the sum of their
+        # magnitudes, at most about 2^8 here, so a probability by up to 2^-13 and, with errors of
+        # either sign over many rows and heads, far less; measured 2e-6 at most.
+        rel = ((got.double() - want).abs() / want.clamp(min=1e-30)).max().item()
+        assert rel < 3e-5, (rel, ph is not None)
+    assert torch.allclose(per_head.mean(1), got, rtol=1e-5, atol=0)
