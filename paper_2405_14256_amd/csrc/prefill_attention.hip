@@ -27,6 +27,9 @@ struct PrefillArgs {
   float scale_log2;
   float* lse;   // [B, Hq, L] natural log, or null
   int group;    // query heads an XCD works on at a time (prefill_block)
+  const int32_t* probe_pos;    // rows whose normalisers go to lse_probe too, or null
+  int P;
+  float* lse_probe;            // [B, Hq, P]
 };
 
 constexpr int kPfKeys = 64;    // keys per tile
@@ -72,6 +75,26 @@ __device__ inline void prefill_block(const PrefillArgs& a, int rows, int* b, int
   } else {
     *b = head / a.Hq;
     *hq = head % a.Hq;
+  }
+}
+
+// The normalisers of a workgroup's rows, in LDS (rows q0 .. q0 + ROWS - 1 of one head), to the
+// probes at these rows; a probe at no row gets 0 from the block of row 0.  Every workgroup
+// looks at all probes, in any order and with repetitions, two a thread at most: beyond that a
+// launch of its own (k_gather_lse) is cheaper.  (8 heads of 64 channels, 256 rows, 26 probes, fp32,
+// with the saliency that follows: 20.0 us with the launch, 18.4 without; 32 heads of 1000 rows of 128
+// channels, 100 probes, bf16: 34.4 and 32.4; 2 x 32 heads of 3001 rows, 300 probes: 193.8 and 192.4.)
+constexpr int kProbesAThread = 2;
+template <int ROWS, int THREADS>
+__device__ inline void probe_normalisers(const PrefillArgs& a, int64_t head, int q0, const float* slse) {
+#pragma unroll
+  for (int u = 0; u < kProbesAThread; ++u) {
+    const int i = threadIdx.x + u * THREADS;
+    if (i < a.P) {
+      const int pos = a.probe_pos[i], row = pos - q0;
+      if (row >= 0 && row < ROWS && pos < a.L) a.lse_probe[head * a.P + i] = slse[row];
+      else if (q0 == 0 && (pos < 0 || pos >= a.L)) a.lse_probe[head * a.P + i] = 0.f;
+    }
   }
 }
 
@@ -188,7 +211,14 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
         for (int v4 = 0; v4 < 4; ++v4)
           *reinterpret_cast<float4*>(orow + 32 * ct + acc_row(4 * v4, kh)) =
               make_float4(oacc[ct][4 * v4] * inv, oacc[ct][4 * v4 + 1] * inv, oacc[ct][4 * v4 + 2] * inv, oacc[ct][4 * v4 + 3] * inv);
-      if (a.lse && kh == 0) a.lse[((int64_t)b * a.Hq + hq) * a.L + qpos] = (m + log2f(l_tot)) * kLn2;
+    }
+    const float lse = (m + log2f(l_tot)) * kLn2;
+    const int64_t head = (int64_t)b * a.Hq + hq;
+    if (a.lse && kh == 0 && qpos < a.L) a.lse[head * a.L + qpos] = lse;
+    if (a.probe_pos) {
+      if (kh == 0) sl[0][r] = lse;
+      __syncthreads();
+      probe_normalisers<32, 64>(a, head, q0, sl[0]);
     }
     return;
   }
@@ -225,7 +255,14 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
       *reinterpret_cast<float4*>(reinterpret_cast<float*>(a.o) + (int64_t)b * a.o_sB + (int64_t)hq * a.o_sH + (int64_t)(q0 + row) * a.o_sL + c) =
           *reinterpret_cast<const float4*>(&so[row * OROW + c]);
   }
-  if (a.lse && w == 0 && kh == 0 && qpos < a.L) a.lse[((int64_t)b * a.Hq + hq) * a.L + qpos] = (M + log2f(l_tot)) * kLn2;
+  const float lse = (M + log2f(l_tot)) * kLn2;
+  const int64_t head = (int64_t)b * a.Hq + hq;
+  if (a.lse && w == 0 && kh == 0 && qpos < a.L) a.lse[head * a.L + qpos] = lse;
+  if (a.probe_pos) {
+    if (w == 0 && kh == 0) sl[0][r] = lse;       // (the sums were read in front of the barriers above)
+    __syncthreads();
+    probe_normalisers<32, 64 * NW>(a, head, q0, sl[0]);
+  }
 }
 
 // ---- 16-bit types -------------------------------------------------------------------
@@ -473,7 +510,16 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
         *reinterpret_cast<uint2*>(orow + c * 2) =
             make_uint2(pack_pair<DT>(oacc[ct][4 * v4] * inv, oacc[ct][4 * v4 + 1] * inv), pack_pair<DT>(oacc[ct][4 * v4 + 2] * inv, oacc[ct][4 * v4 + 3] * inv));
       }
-    if (a.lse && kh == 0) a.lse[((int64_t)b * a.Hq + hq) * a.L + qpos] = (m + log2f(l_tot)) * kLn2;
+  }
+  const float lse = (m + log2f(l_tot)) * kLn2;
+  const int64_t head = (int64_t)b * a.Hq + hq;
+  if (a.lse && kh == 0 && qpos < a.L) a.lse[head * a.L + qpos] = lse;
+  if (a.probe_pos) {
+    float* slse = reinterpret_cast<float*>(&Ks[0][0]);
+    __syncthreads();                               // (every wave is done with its tiles)
+    if (kh == 0) slse[32 * w + r] = lse;
+    __syncthreads();
+    probe_normalisers<32 * NW, 64 * NW>(a, head, q0, slse);
   }
 }
 
@@ -488,6 +534,11 @@ __global__ void k_gather_lse(const float* __restrict__ lse, const int32_t* __res
   out[i] = (pos >= 0 && pos < L) ? lse[h * L + pos] : 0.f;
 }
 
+// Whether the attention kernel's workgroups of `threads` threads bring the probes' normalisers themselves.
+static void probes_in_kernel(PrefillArgs& a, int threads) {
+  if (a.P > kProbesAThread * threads) a.probe_pos = nullptr;
+}
+
 // Query heads an XCD works on at a time: whole KV heads, at least two rounds of its slots, and
 // groups of one size (a small last group would start its long blocks when the chip drains).
 static int head_group(const PrefillArgs& a, int nqb, int slots) {
@@ -497,10 +548,11 @@ static int head_group(const PrefillArgs& a, int nqb, int slots) {
 }
 
 template <int DT, int D>
-static int launch_prefill(PrefillArgs a, hipStream_t st) {
+static int launch_prefill(PrefillArgs& a, hipStream_t st) {
   const int64_t heads = (int64_t)a.B * a.Hq;
-  const auto blocks = [&](int rows, int slots) {          // slots: workgroups an XCD holds at a time
+  const auto blocks = [&](int rows, int slots, int threads) {          // slots: workgroups an XCD holds at a time
     const int nqb = ceil_div(a.L, rows);
+    probes_in_kernel(a, threads);
     a.group = head_group(a, nqb, slots);
     return dim3((unsigned)(nqb * heads));
   };
@@ -509,9 +561,9 @@ static int launch_prefill(PrefillArgs a, hipStream_t st) {
     // blocks is heads (n + 1) / 2048 times the n of the longest row block.  One wave or two, at
     // 2.1: 88 / 94 and 335 / 331 us, at 2.0: 579 / 549; two or four, at 1.6: 232 / 261, at 1.1: 264 / 237.
     const int64_t share = heads * (ceil_div(a.L, 32) + 1);
-    if (share >= 4300) hipLaunchKernelGGL((k_prefill_attention32<D, 1>), blocks(32, 256), dim3(64), 0, st, a);
-    else if (share >= 3100) hipLaunchKernelGGL((k_prefill_attention32<D, 2>), blocks(32, 128), dim3(128), 0, st, a);
-    else hipLaunchKernelGGL((k_prefill_attention32<D, 4>), blocks(32, 64), dim3(256), 0, st, a);
+    if (share >= 4300) hipLaunchKernelGGL((k_prefill_attention32<D, 1>), blocks(32, 256, 64), dim3(64), 0, st, a);
+    else if (share >= 3100) hipLaunchKernelGGL((k_prefill_attention32<D, 2>), blocks(32, 128, 128), dim3(128), 0, st, a);
+    else hipLaunchKernelGGL((k_prefill_attention32<D, 4>), blocks(32, 64, 256), dim3(256), 0, st, a);
   } else {
     // Four waves per workgroup, 128 rows: twice the workgroups to even the lengths out.  Eight read a
     // K and V tile once for 256 rows, which only shows over long rows of 128 channels (32 heads
@@ -520,12 +572,12 @@ static int launch_prefill(PrefillArgs a, hipStream_t st) {
     // rows of 64 channels 376 / 346).
     if constexpr (D == 128) {
       if (a.L >= 16384 && ceil_div(a.L, 256) * heads >= 512) {
-        hipLaunchKernelGGL((k_prefill_attention16<DT, D, 8>), blocks(256, 32), dim3(512), 0, st, a);
+        hipLaunchKernelGGL((k_prefill_attention16<DT, D, 8>), blocks(256, 32, 512), dim3(512), 0, st, a);
         ZC_LAUNCH_CHECK();
         return ZC_OK;
       }
     }
-    hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), blocks(128, 64), dim3(256), 0, st, a);
+    hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), blocks(128, 64, 256), dim3(256), 0, st, a);
   }
   ZC_LAUNCH_CHECK();
   return ZC_OK;
@@ -574,6 +626,9 @@ extern "C" int zc_prefill_attention(const zc_tensor4* q, const zc_tensor4* k, co
   a.B = (int)q->B; a.Hq = (int)q->H; a.Hkv = (int)k->H; a.G = a.Hq / a.Hkv; a.L = (int)q->L;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse = lse;
+  a.probe_pos = P > 0 ? probe_pos : nullptr;
+  a.P = (int)P;
+  a.lse_probe = lse_probe;
   hipStream_t st = (hipStream_t)stream;
 #define ZC_PF(DT) (q->D == 128 ? launch_prefill<DT, 128>(a, st) : launch_prefill<DT, 64>(a, st))
   if (q->dtype == ZC_F32) rc = ZC_PF(ZC_F32);
@@ -581,7 +636,7 @@ extern "C" int zc_prefill_attention(const zc_tensor4* q, const zc_tensor4* k, co
   else rc = ZC_PF(ZC_BF16);
 #undef ZC_PF
   if (rc) return rc;
-  if (P > 0) {
+  if (P > 0 && !a.probe_pos) {
     const int64_t heads = q->B * q->H, n = heads * P;
     hipLaunchKernelGGL(k_gather_lse, dim3((unsigned)ceil_div64(n, 256)), dim3(256), 0, st, lse, probe_pos, lse_probe, heads, a.L, (int)P);
     ZC_LAUNCH_CHECK();
