@@ -3,9 +3,9 @@
 // on the order-preserving uint32 image of the scores finds the k-th largest
 // key and how many tokens equal to it are taken (lowest indices first); one
 // ordered compaction pass then writes both index lists in ascending order.
-// Rows of up to 34816 tokens are read from memory once and kept in LDS
-// (k_select_cached); longer rows are re-read from memory by every pass
-// (k_select_stream).
+// Rows of up to 16384 tokens are kept in registers (k_select_small), of up to
+// 34816 in LDS (k_select_cached); longer rows are re-read from memory by every
+// pass (k_select_stream).
 #include <type_traits>
 
 #include "zc_common.hpp"
@@ -349,6 +349,191 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
   }
 }
 
+// ---- rows of up to kSelSmallMax tokens: keys in registers ------------------------------------
+// Nothing here is bound by memory or arithmetic: a row is one workgroup's chain of barriers, LDS
+// round trips and instruction fetches (code is cold at every launch, about half a microsecond a
+// KB).  So the kernel is short (1.8 KB for 256 tokens, 3.7 for 4096) and a workgroup no larger
+// than its row: up to four keys a thread (8 and 16 where 1024 threads need them) in coalesced
+// loads (a wave's run is 64 KPT consecutive tokens, lane l holds tokens 64 u + l of it), digits
+// that give a thread two bins, so that one pass usually leaves few enough candidates for a
+// bisection with ballots, and the positions in both lists from ballots, stored as they are.
+// us per launch, k_select_cached -> here, k = 0.4 L: 100 tokens 6.7 -> 3.3; 1000: 7.0 -> 4.0; 2048:
+// 7.5 -> 4.4; 4096: 8.6 -> 5.5; 8192: 10.5 -> 7.3; 16384: 14.5 -> 12.7.  At 32768 tokens 32 keys a
+// thread are 20 KB of code: 21.9 against 20.3, so the longer rows stay there.
+
+constexpr int kSelSmallMax = 16384;            // four keys a thread, 1024 threads
+constexpr int kKthMax = 256;                   // candidates of the bisection, at most
+
+// The need-th largest of a wave's keys, N a lane, that agree in every bit at and above `lo` with
+// `prefix`; unused places hold 0 (below every probed threshold).  Returns the key; `need` becomes
+// how many keys equal to it are taken.  Every lane of the wave gets the same answer.
+template <int N>
+__device__ inline uint32_t kth_of_wave(const uint32_t (&c)[N], uint32_t prefix, int lo, int& need) {
+  uint32_t t = prefix;
+  auto count_ge = [&](uint32_t v) {
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < N; ++u) n += __popcll(__ballot(c[u] >= v));
+    return n;
+  };
+#pragma unroll 1
+  for (int bit = lo - 1; bit >= 0; --bit) {
+    const uint32_t probe = t | (1u << bit);
+    if (count_ge(probe) >= need) t = probe;
+  }
+  if (t != 0xffffffffu) need -= count_ge(t + 1u);
+  return t;
+}
+
+__device__ inline uint32_t wave_or(uint32_t x) {        // OR over the wave (the steps of wave_inclusive_sum)
+  int v = (int)x;
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false);
+  v |= __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false);
+  return (uint32_t)__builtin_amdgcn_readlane(v, 63);
+}
+
+__device__ inline int lanes_below(uint64_t mask) {      // set bits below this lane
+  return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
+}
+
+// One wave (THREADS == 64): no LDS, no barrier, the bisection over all keys.
+template <int THREADS, int KPT>
+__global__ __launch_bounds__(THREADS) void k_select_small(
+    const float* __restrict__ scores, int L, int k, int32_t* __restrict__ salient,
+    int32_t* __restrict__ regular, uint8_t* __restrict__ mask) {
+  constexpr bool ONE_WAVE = THREADS == 64;
+  constexpr int NWAVE = THREADS / 64, RUN = 64 * KPT;
+  constexpr int BINS = 2 * THREADS, DIGIT = __builtin_ctz(BINS);    // two bins a thread
+  __shared__ int hist[ONE_WAVE ? 1 : BINS];
+  __shared__ uint32_t cand[ONE_WAVE ? 1 : kKthMax];
+  __shared__ int s_wave[NWAVE], s_bin, s_need, s_cnt, s_ncand;
+  __shared__ uint32_t s_diff[NWAVE];
+
+  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
+  const int wave = ONE_WAVE ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* sc = scores + (int64_t)b * L;
+  const int i0 = wave * RUN + lane;
+  uint32_t key[KPT], diff = 0u;
+  const uint32_t key0 = float_key(sc[0]);
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) key[u] = float_key(sc[min(i0 + 64 * u, L - 1)]);
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) diff |= key[u] ^ key0;           // (a repeated last token adds nothing)
+#pragma unroll
+  for (int u = 0; u < KPT; ++u)
+    if (i0 + 64 * u >= L) key[u] = 0u;
+
+  // Tokens with key > thr are salient; of those equal to it, the first `need` by index.
+  uint32_t thr;
+  int need = k;
+  if (k <= 0) { thr = 0xffffffffu; need = 0; }
+  else if (k >= L) { thr = 0u; need = L; }                     // (every valid token is above or equal)
+  else {
+    // the bits in which two keys of the row differ
+    diff = wave_or(diff);
+    if constexpr (!ONE_WAVE) {
+      if (lane == 0) s_diff[wave] = diff;
+      for (int i = tid; i < BINS; i += THREADS) hist[i] = 0;
+      if (tid == 0) s_ncand = 0;
+      __syncthreads();
+      diff = wave_or(s_diff[lane & (NWAVE - 1)]);
+    }
+    int lo = diff ? 32 - __clz(diff) : 0;                      // the low `lo` bits are undecided
+    thr = lo >= 32 ? 0u : __builtin_amdgcn_readfirstlane(key0) & (0xffffffffu << lo);
+    if constexpr (ONE_WAVE) {
+      thr = kth_of_wave(key, thr, lo, need);
+    } else {
+      int in_bin = L;
+#pragma unroll 1
+      while (lo > 0 && in_bin > kKthMax) {
+        const int top = lo;
+        lo = max(top - DIGIT, 0);
+        const uint64_t pre = (uint64_t)thr >> top;             // (top may be 32)
+#pragma unroll
+        for (int u = 0; u < KPT; ++u)
+          if (i0 + 64 * u < L && ((uint64_t)key[u] >> top) == pre) atomicAdd(&hist[(key[u] >> lo) & ((1u << (top - lo)) - 1u)], 1);
+        __syncthreads();
+        // keys above each bin: thread t owns bins BINS - 1 - 2 t and the one below it
+        const int2 h = reinterpret_cast<const int2*>(hist)[BINS / 2 - 1 - tid];
+        const int incl = wave_inclusive_sum(h.x + h.y);
+        if (lane == 63) s_wave[wave] = incl;
+        __syncthreads();
+        // (cleared for the next pass, which the next barrier separates from it)
+        reinterpret_cast<int2*>(hist)[BINS / 2 - 1 - tid] = make_int2(0, 0);
+        int before = lane < wave ? s_wave[lane] : 0;
+        before = __builtin_amdgcn_readlane(wave_inclusive_sum(before), 63);
+        const int a0 = before + incl - h.x - h.y, a1 = a0 + h.y;      // keys above the upper bin, above the lower
+        if (a0 < need && need <= a1 + h.x) {                   // exactly one thread
+          const bool upper = need <= a1;
+          s_bin = BINS - 1 - 2 * tid - (upper ? 0 : 1);
+          s_need = need - (upper ? a0 : a1);
+          s_cnt = upper ? h.y : h.x;
+        }
+        __syncthreads();
+        thr |= (uint32_t)__builtin_amdgcn_readfirstlane(s_bin) << lo;
+        need = __builtin_amdgcn_readfirstlane(s_need);
+        in_bin = __builtin_amdgcn_readfirstlane(s_cnt);
+      }
+      if (lo > 0) {                                            // the keys of the bin: candidates of the bisection
+#pragma unroll
+        for (int u = 0; u < KPT; ++u)
+          if (i0 + 64 * u < L && (key[u] >> lo) == (thr >> lo)) cand[atomicAdd(&s_ncand, 1)] = key[u];
+        __syncthreads();
+        // (by every wave for itself: no barrier)
+        if (in_bin <= 64) {
+          const uint32_t c[1] = {lane < in_bin ? cand[lane] : 0u};
+          thr = kth_of_wave(c, thr, lo, need);
+        } else {
+          uint32_t c[kKthMax / 64];
+#pragma unroll
+          for (int u = 0; u < kKthMax / 64; ++u) c[u] = 64 * u + lane < in_bin ? cand[64 * u + lane] : 0u;
+          thr = kth_of_wave(c, thr, lo, need);
+        }
+      }
+    }
+  }
+
+  // ---- positions in both lists --------------------------------------------------------------
+  uint64_t gt[KPT], eq[KPT];
+  int ngt = 0, neq = 0;
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) {
+    const bool valid = i0 + 64 * u < L;
+    gt[u] = __ballot(valid && key[u] > thr);
+    eq[u] = __ballot(valid && key[u] == thr);
+    ngt += __popcll(gt[u]);
+    neq += __popcll(eq[u]);
+  }
+  int run_gt = 0, run_eq = 0;                                  // salient candidates before this wave's run
+  if constexpr (!ONE_WAVE) {
+    if (lane == 0) s_wave[wave] = (int)((uint32_t)ngt | (uint32_t)neq << 16);
+    __syncthreads();
+    const int before = __builtin_amdgcn_readlane(wave_inclusive_sum(lane < wave ? s_wave[lane] : 0), 63);
+    run_gt = before & 0xffff;
+    run_eq = (uint32_t)before >> 16;
+  }
+  int32_t* sal = salient + (int64_t)b * k;
+  int32_t* reg = regular + (int64_t)b * (L - k);
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) {
+    const int i = i0 + 64 * u;
+    const int eq_before = run_eq + lanes_below(eq[u]);
+    const bool is_sal = (gt[u] >> lane & 1) || ((eq[u] >> lane & 1) && eq_before < need);
+    const int p = run_gt + lanes_below(gt[u]) + min(eq_before, need);
+    if (i < L) {
+      int32_t* dst = is_sal ? sal + p : reg + (i - p);
+      *dst = i;
+      if (mask) mask[(int64_t)b * L + i] = is_sal ? 1 : 0;
+    }
+    run_gt += __popcll(gt[u]);
+    run_eq += __popcll(eq[u]);
+  }
+}
+
 // Rows too long for LDS: every pass reads the scores from memory.  (Keeping a thread's keys
 // in registers instead, with every loop unrolled, was slower at every size - 17 us against
 // 10 us for a row of 4096: the straight-line code is fetched cold at every launch.)
@@ -466,7 +651,17 @@ extern "C" int zc_select_salient(const float* scores, int64_t B, int64_t L, int6
   if ((reinterpret_cast<uintptr_t>(scores) & 3) || (reinterpret_cast<uintptr_t>(salient_idx) & 3) ||
       (reinterpret_cast<uintptr_t>(regular_idx) & 3))
     return ZC_ERR_INVALID_ARG;
-  if (L <= zc::kSelMaxCached) {
+  if (L <= zc::kSelSmallMax) {
+    const auto launch = [&](auto kernel, unsigned threads) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)B), dim3(threads), 0, (hipStream_t)stream, scores, (int)L, (int)k, salient_idx, regular_idx, mask);
+    };
+    if (L <= 64 * 4) launch(zc::k_select_small<64, 4>, 64);
+    else if (L <= 256 * 4) launch(zc::k_select_small<256, 4>, 256);
+    else if (L <= 512 * 4) launch(zc::k_select_small<512, 4>, 512);
+    else if (L <= 1024 * 4) launch(zc::k_select_small<1024, 4>, 1024);
+    else if (L <= 1024 * 8) launch(zc::k_select_small<1024, 8>, 1024);
+    else launch(zc::k_select_small<1024, 16>, 1024);
+  } else if (L <= zc::kSelMaxCached) {
     const size_t lds = (size_t)((L + 255) & ~(int64_t)255) * sizeof(uint32_t);
     // rows start on 16-byte boundaries when the array does and L is a multiple of four (or B is 1)
     const bool vec = (reinterpret_cast<uintptr_t>(scores) & 15) == 0 && (B == 1 || (L & 3) == 0);

@@ -1,0 +1,39 @@
+"""zc_select_salient on rows around the sizes at which its workgroup changes, against the oracle:
+exact index lists and mask.  Rows that need one digit pass, two (hundreds of keys that share the
+first digit), all of them (more equal keys than the bisection holds, straddling the k-th place),
+and none (one value)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import zipcache_oracle as zo
+
+pytestmark = pytest.mark.gpu
+
+
+def _row(kind, n, rng):
+    if kind == "spread":
+        return np.exp(rng.standard_normal(n)).astype(np.float32) / n
+    if kind == "one_digit":                 # neighbours in the last bits of one float, one outlier
+        x = (np.float32(1.0).view(np.uint32) + rng.integers(0, 700, n).astype(np.uint32)).view(np.float32)
+        x[n // 2] = 1e9
+        return x
+    if kind == "ties":
+        return np.where(rng.random(n) < 0.8, np.float32(0.25), rng.standard_normal(n).astype(np.float32))
+    return np.full(n, -0.5, np.float32)
+
+
+@pytest.mark.parametrize("L", [2, 63, 256, 257, 1024, 1025, 2048, 2049, 4096, 4097, 8192, 8193, 16384, 16385])
+def test_select_rows(L):
+    from paper_2405_14256_amd import binding as zb
+    rng = np.random.default_rng(L)
+    x = np.stack([_row(kind, L, rng) for kind in ("spread", "one_digit", "ties", "const", "spread")])
+    for k in sorted({0, 1, L // 3, L // 2, L - 1, L}):
+        mask = torch.full((x.shape[0], L), 7, dtype=torch.uint8, device="cuda")
+        sal, reg = zb.zc_select_salient(torch.from_numpy(x).cuda(), k, mask=mask)
+        for b in range(x.shape[0]):
+            s_o, r_o = zo.select_salient(x[b].astype(np.float64), k)
+            assert np.array_equal(sal[b].cpu().numpy(), s_o) and np.array_equal(reg[b].cpu().numpy(), r_o), (L, k, b)
+            m = np.zeros(L, np.uint8)
+            m[s_o] = 1
+            assert np.array_equal(mask[b].cpu().numpy(), m), (L, k, b)
