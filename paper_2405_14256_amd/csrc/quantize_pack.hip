@@ -9,7 +9,8 @@
 //                       and, for channelwise ROW codes that stay resident, the codes.
 //                       Long subsets of few channels are cut into token ranges, whose
 //                       minima k_column_params joins in a launch between the two.
-//   2. k_quant_pack     a team of waves (one thread per 8 channels) owns one to
+//   2. k_pack_kv        (the paper's schemes and layouts) a few channels and tokens a thread;
+//      k_quant_pack     (the others, and wide values) a team of waves (one thread per 8 channels) owns one to
 //                       four word groups of a TGROUP block - the 32 / bits tokens
 //                       whose codes share 32-bit words - and walks them in
 //                       batches of 8 tokens, requesting batch i + 1 before it
@@ -42,8 +43,8 @@ struct QPArgs {
   int32_t* pos[2];
   float* chan_scale;           // this chunk: [2, B, W]
   float* chan_zero;
-  float4* params;              // workspace [B, 2, W]: CHANNEL {1/R, z, R, -}, CST {1/c, -, -, -}; behind it the column
-                               // sweep's [B, 2, split, W] (minimum, minimum of -x) where it goes by token ranges
+  float* params;               // workspace [B, 2, 3, W]: CHANNEL 1/R, z, R; CST 1/c, -, -; behind it (4 B W floats a subset on)
+                               // the column sweep's [B, 2, split, W] (minimum, minimum of -x) where it goes by token ranges
   int32_t* chunk_row;          // device chunk_table row to fill
   int64_t pos_offset;
   int units[2];                // quantize sweep: word groups per subset (4 per TGROUP block)
@@ -57,27 +58,36 @@ constexpr int kStatBatch = 8;       // token rows requested at once where they d
 constexpr int kSplitLanes = 16, kSplitThreads = 512;      // shape of the split column sweep's workgroups
 constexpr int kSplitRows = 16;      // least rows a thread of it takes
 
-__device__ inline float2* range_minima(const QPArgs& a) { return reinterpret_cast<float2*>(a.params + (int64_t)a.B * 2 * a.W); }
+__device__ inline float2* range_minima(const QPArgs& a) { return reinterpret_cast<float2*>(a.params + (int64_t)a.B * 2 * a.W * 4); }
+
+// Parameters of (batch element, subset), value v (0..2) of channel w.
+__device__ inline float* param_row(const QPArgs& a, int b, int sub, int v) { return a.params + ((int64_t)(b * 2 + sub) * 3 + v) * a.W; }
+__device__ inline void store_params(const QPArgs& a, int b, int sub, int w, float3 p) {
+  param_row(a, b, sub, 0)[w] = p.x;
+  if (a.scheme != ZC_SCHEME_CHANNEL) return;
+  param_row(a, b, sub, 1)[w] = p.y;
+  param_row(a, b, sub, 2)[w] = p.z;
+}
 
 struct QPPair { QPArgs t[2]; };   // keys and values of one cache, compressed by the same launches
 
 // What the quantizer needs of a channel whose values span [lo, hi]; n tokens (0: defaults).
-__device__ inline float4 channel_params(int scheme, int n, float qmax, float lo, float hi, float* cs, float* cz) {
+__device__ inline float3 channel_params(int scheme, int n, float qmax, float lo, float hi, float* cs, float* cz) {
   *cs = 1.f; *cz = 0.f;
   if (n > 0 && scheme == ZC_SCHEME_CST) {
     float c = sqrtf(fmaxf(fabsf(lo), fabsf(hi)));       // Eq. 6
     if (c == 0.f) c = 1.f;
     *cs = c;
-    return make_float4(1.f / c, 0.f, 1.f, 0.f);
+    return make_float3(1.f / c, 0.f, 1.f);
   }
   if (n > 0 && scheme == ZC_SCHEME_CHANNEL) {
     float R = hi - lo;                                     // Eq. 5: s = R / (2^k - 1)
     if (R == 0.f) R = qmax;                                // max == min: s := 1
     *cs = R / qmax;
     *cz = -rintf(refined_ratio(lo, qmax, R, 1.f / R));
-    return make_float4(1.f / R, *cz, R, 0.f);
+    return make_float3(1.f / R, *cz, R);
   }
-  return make_float4(1.f, 0.f, 1.f, 0.f);
+  return make_float3(1.f, 0.f, 1.f);
 }
 
 // ---- minima of N values over a wave at once -----------------------------------------
@@ -305,11 +315,11 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
       return;
     }
     float cs, cz;
-    const float4 pr = channel_params(a.scheme, n, (float)((1 << a.bits[sub]) - 1), lo, -neg, &cs, &cz);
+    const float3 pr = channel_params(a.scheme, n, (float)((1 << a.bits[sub]) - 1), lo, -neg, &cs, &cz);
     const int64_t o = (int64_t)(sub * a.B + b) * a.W + wc;
     a.chan_scale[o] = cs;
     a.chan_zero[o] = cz;
-    if (!a.resident) a.params[(int64_t)(b * 2 + sub) * a.W + wc] = pr;
+    if (!a.resident) store_params(a, b, sub, wc, pr);
     prm[0][tid] = pr.x; prm[1][tid] = pr.y; prm[2][tid] = pr.z;
   }
   if constexpr (SPLIT) return;
@@ -364,11 +374,11 @@ __global__ __launch_bounds__(256) void k_column_params(QPPair p, int split) {
     }
   }
   float cs, cz;
-  const float4 pr = channel_params(a.scheme, a.n[sub], (float)((1 << a.bits[sub]) - 1), lo, -neg, &cs, &cz);
+  const float3 pr = channel_params(a.scheme, a.n[sub], (float)((1 << a.bits[sub]) - 1), lo, -neg, &cs, &cz);
   const int64_t o = (int64_t)(sub * a.B + b) * a.W + w;
   a.chan_scale[o] = cs;
   a.chan_zero[o] = cz;
-  a.params[(int64_t)(b * 2 + sub) * a.W + w] = pr;
+  store_params(a, b, sub, w, pr);
   if (sub == 0 && b == 0 && w == 0) {
     a.chunk_row[0] = a.begin[0]; a.chunk_row[1] = a.n[0];
     a.chunk_row[2] = a.begin[1]; a.chunk_row[3] = a.n[1];
@@ -418,11 +428,10 @@ __device__ inline void quant_units(const QPArgs& a, int sub, int g0, int ng, int
   const int64_t row_bytes = a.sL * ESZ;
   float p0[8], p1[8], p2[8];
   {
-    const float4* pp = a.params + (int64_t)(b * 2 + sub) * a.W + w;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float4 t = pp[i];
-      p0[i] = t.x; p1[i] = t.y; p2[i] = t.z;
+    load8<ZC_F32>(param_row(a, b, sub, 0), w, p0);
+    if constexpr (!TOKWISE) {
+      load8<ZC_F32>(param_row(a, b, sub, 1), w, p1);
+      load8<ZC_F32>(param_row(a, b, sub, 2), w, p2);
     }
   }
   __syncthreads();
@@ -660,31 +669,189 @@ __global__ __launch_bounds__(MAXT) void k_quant_pack(QPArgs a) {
   else quant_units<DT, 8, LAYOUT, TOKWISE, EXACT, PIPE>(a, sub, g0, ng, b, red, sidx);
 }
 
-// Keys (channelwise, ROW layout) and values (channel-separable tokenwise, TGROUP layout) of one
-// cache in one launch, for token rows of at most 256 channel vectors (one workgroup width serves
-// both): grid.x = workgroups of the keys, then of the values.
+// ---- the paper's configuration: channelwise keys in ROW layout, channel-separable tokenwise
+// values in TGROUP layout -------------------------------------------------------------------------
+// Bound by latency for one prompt: the sweep above holds 8 tokens x 8 channels a thread in straight
+// code, 5 KB for each of two alternating batches, which is fetched cold at every launch.  Here a thread
+// takes 4 channels of a word group's 8 or 16 values, all requested at once, or 8 channels of 4 keys in
+// a rolled loop: 1 to 4 KB, and twice the waves.  us per joint call (column sweep included), before ->
+// here: 100 tokens of 8 heads of 128 channels, bf16: 12.1 -> 9.4; 1000: 13.2 -> 10.3; 4096: 16.3 -> 14.9;
+// 32768: 70.3 -> 57.4; 2 x 32768 of 16 heads, fp16: 260 -> 253; 4 x 16384 of them, fp32: 452 -> 427.
+// (fp32 rows of 1280 and 1536 channels lose: one prompt of 4096 tokens 28.7 -> 30.7, 30.5 -> 31.7.)  Keys
+// alone, which need no more than their own rows, come here at any width: 2 x 9000 tokens of 40 heads with
+// their values 210 -> 193.  Values wider than a workgroup takes go through quant_units.
+constexpr int kPackThreads = 512, kPackCpt = 4;     // values: most threads of a workgroup, channels of a thread
+
+// 4 consecutive elements.
 template <int DT>
-__global__ __launch_bounds__(256) void k_quant_pack_kv(QPPair p) {
-  constexpr bool PIPE = (DT != ZC_F32);
-  __shared__ float red[2][16][16];
-  __shared__ int32_t sidx[64];
-  const int b = blockIdx.y;
-  const int nk = p.t[0].wgs[0] + p.t[0].wgs[1];
-  const int which = (int)blockIdx.x >= nk ? 1 : 0;
-  const QPArgs& a = which ? p.t[1] : p.t[0];
-  int wg = blockIdx.x - which * nk;
-  const int sub = wg >= a.wgs[0] ? 1 : 0;
-  if (sub) wg -= a.wgs[0];
-  const int g0 = wg * a.upw, ng = a.upw;
-  const int bits = a.bits[sub];
-  if (which == 0) {
-    if (bits == 4) quant_units<DT, 4, ZC_LAYOUT_ROW, false, false, PIPE>(a, sub, g0, ng, b, red, sidx);
-    else if (bits == 2) quant_units<DT, 2, ZC_LAYOUT_ROW, false, false, PIPE>(a, sub, g0, ng, b, red, sidx);
-    else quant_units<DT, 8, ZC_LAYOUT_ROW, false, false, PIPE>(a, sub, g0, ng, b, red, sidx);
+__device__ inline void load4(const void* p, float (&v)[4]) {
+  if constexpr (DT == ZC_F32) {
+    const float4 t = *reinterpret_cast<const float4*>(p);
+    v[0] = t.x; v[1] = t.y; v[2] = t.z; v[3] = t.w;
   } else {
-    if (bits == 4) quant_units<DT, 4, ZC_LAYOUT_TGROUP, true, false, PIPE>(a, sub, g0, ng, b, red, sidx);
-    else if (bits == 2) quant_units<DT, 2, ZC_LAYOUT_TGROUP, true, false, PIPE>(a, sub, g0, ng, b, red, sidx);
-    else quant_units<DT, 8, ZC_LAYOUT_TGROUP, true, false, PIPE>(a, sub, g0, ng, b, red, sidx);
+    const uint2 t = *reinterpret_cast<const uint2*>(p);
+    v[0] = half_bits_to_float<DT>(t.x & 0xffffu);
+    v[1] = half_bits_to_float<DT>(t.x >> 16);
+    v[2] = half_bits_to_float<DT>(t.y & 0xffffu);
+    v[3] = half_bits_to_float<DT>(t.y >> 16);
+  }
+}
+
+// Values (TGROUP layout, channel-separable tokenwise): one word group, a thread per 4 channels.
+template <int DT, int BITS>
+__device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, float (*red)[kPackThreads / 64][16]) {
+  constexpr int E = 32 / BITS, TBAT = E < 8 ? E : 8, NBAT = E / TBAT, TB = 4 * E;
+  constexpr int FPG = 16 / BITS, NG = TBAT / FPG, ESZ = DT == ZC_F32 ? 4 : 2;
+  constexpr float QMAX = (float)((1 << BITS) - 1);
+  const int n = a.n[sub], blk = unit >> 2, kg = unit & 3;
+  const int32_t* idx = a.idx[sub] + (int64_t)b * n;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
+  const bool valid = kPackCpt * tid < a.W;
+  const int w = valid ? kPackCpt * tid : 0, h = w / a.D, c = w - h * a.D;
+  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
+  auto rel_of = [&](int e) { return blk * TB + 16 * tile_of_field_group(BITS, e >> 2) + 4 * kg + (e & 3); };   // token e of the group
+
+  float x[E][kPackCpt], inv_c[kPackCpt];
+#pragma unroll
+  for (int e = 0; e < E; ++e) load4<DT>(base + (int64_t)idx[min(rel_of(e), n - 1)] * a.sL * ESZ, x[e]);
+  load4<ZC_F32>(param_row(a, b, sub, 0) + w, inv_c);
+  // bookkeeping of the group's tokens by lanes 0 .. E - 1 of the first wave
+  const int my_rel = rel_of(lane < E ? lane : 0);
+  const bool mine = tid < E && my_rel < n;
+  const int64_t my_o = (int64_t)b * a.cap[sub] + a.begin[sub] + my_rel;
+  if (mine && a.pos[sub]) a.pos[sub][my_o] = (int32_t)(idx[my_rel] + a.pos_offset);
+
+  // ranges: (min, -max) of TBAT tokens at a time over the wave, all of the group over the waves
+#pragma unroll
+  for (int q = 0; q < NBAT; ++q) {
+    float mm[TBAT];
+#pragma unroll
+    for (int t = 0; t < TBAT; ++t) {
+      float (&v)[kPackCpt] = x[q * TBAT + t];
+#pragma unroll
+      for (int i = 0; i < kPackCpt; ++i) v[i] *= inv_c[i];
+      mm[t] = swap_min_rows(fminf(fminf(v[0], v[1]), fminf(v[2], v[3])), fminf(fminf(-v[0], -v[1]), fminf(-v[2], -v[3])));
+    }
+    const float wmin = wave_min_rest<2 * TBAT>(mm);
+    if ((lane & 3) == 0) {
+      const int vi = value_of_lane<2 * TBAT>(lane);
+      red[q][wave][vi < TBAT ? vi : 8 + vi - TBAT] = wmin;
+    }
+  }
+  __syncthreads();
+  float si[NBAT], z[NBAT];
+#pragma unroll
+  for (int q = 0; q < NBAT; ++q) {
+    float r = INFINITY;
+    for (int v = lane >> 4; v < nwaves; v += 4) r = fminf(r, red[q][v][lane & 15]);
+    r = swap_min_rows(r, r);
+    r = swap_min_halves(r, r);
+    // lanes 0..7 of a row hold the minima, 8..15 the negated maxima: all get both
+    const float other = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(r), 0x128, 0xF, 0xF, true));   // row_ror:8
+    const float tmin = lane & 8 ? other : r, tmax = -(lane & 8 ? r : other);
+    float R = tmax - tmin;
+    if (R == 0.f) R = QMAX;                        // max == min: s := 1
+    const float y = __builtin_amdgcn_rcpf(R);
+    z[q] = -rintf(refined_ratio(tmin, QMAX, R, y));   // tie-exact: a whole row depends on it
+    si[q] = QMAX * y;
+    if (mine && (lane >> 3) == q) {                // (lane e < E: batch e / 8; with fewer than 8 tokens, batch 0)
+      a.tok_scale[sub][my_o] = R * (1.f / QMAX);
+      a.tok_zero[sub][my_o] = z[q];
+    }
+  }
+  if (!valid) return;
+  uint32_t words[kPackCpt] = {};
+#pragma unroll
+  for (int q = 0; q < NBAT; ++q)
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      float acc[kPackCpt] = {};
+#pragma unroll
+      for (int f = 0; f < FPG; ++f) {
+        const int t = g * FPG + f, e = q * TBAT + t;
+        const float st = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(si[q]), t));
+        const float zt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(z[q]), t));
+        const float mult = rel_of(e) < n ? (float)(1 << (BITS * f)) : 0.f;
+#pragma unroll
+        for (int i = 0; i < kPackCpt; ++i) acc[i] = fmaf(__builtin_amdgcn_fmed3f(rintf(x[e][i] * st) + zt, 0.f, QMAX), mult, acc[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < kPackCpt; ++i) words[i] |= (uint32_t)acc[i] << (BITS * (q * TBAT + g * FPG));
+    }
+  const int64_t gblk = a.begin[sub] / TB + blk, nblk = a.cap[sub] / TB;
+  uint32_t* dst = reinterpret_cast<uint32_t*>(a.codes[sub]) + ((((int64_t)b * a.H + h) * nblk + gblk) * 4 + kg) * a.D + c;
+  *reinterpret_cast<uint4*>(dst) = make_uint4(words[0], words[1], words[2], words[3]);
+}
+
+constexpr int kPackTokens = 4;         // keys: tokens of a thread
+
+// Keys (ROW layout, channelwise): a thread per 8 channels of kPackTokens tokens.
+template <int DT, int BITS>
+__device__ inline void pack_keys(const QPArgs& a, int sub, int wg, int b) {
+  constexpr int RAW = DT == ZC_F32 ? 2 : 1, ESZ = DT == ZC_F32 ? 4 : 2;
+  const int n = a.n[sub];
+  const uint32_t i = (uint32_t)wg * blockDim.x + threadIdx.x, quad = i / (uint32_t)a.NV;
+  const int t0 = (int)quad * kPackTokens, w = (int)(i - quad * a.NV) * 8, h = w / a.D, c = w - h * a.D;
+  if (t0 >= n) return;
+  const int32_t* idx = a.idx[sub] + (int64_t)b * n;
+  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
+  int32_t tok[kPackTokens];
+#pragma unroll
+  for (int t = 0; t < kPackTokens; ++t) tok[t] = idx[min(t0 + t, n - 1)];
+  uint4 raw[kPackTokens][RAW];
+#pragma unroll
+  for (int t = 0; t < kPackTokens; ++t)
+#pragma unroll
+    for (int r = 0; r < RAW; ++r) raw[t][r] = *reinterpret_cast<const uint4*>(base + (int64_t)tok[t] * a.sL * ESZ + 16 * r);
+  float p0[8], p1[8], p2[8];
+  load8<ZC_F32>(param_row(a, b, sub, 0), w, p0);
+  load8<ZC_F32>(param_row(a, b, sub, 1), w, p1);
+  load8<ZC_F32>(param_row(a, b, sub, 2), w, p2);
+  if (w == 0 && a.pos[sub]) {
+#pragma unroll
+    for (int t = 0; t < kPackTokens; ++t)
+      if (t0 + t < n) a.pos[sub][(int64_t)b * a.cap[sub] + a.begin[sub] + t0 + t] = (int32_t)(tok[t] + a.pos_offset);
+  }
+  const int rowb = a.D * BITS / 8;
+  uint8_t* dst = a.codes[sub] + (((int64_t)b * a.H + h) * a.cap[sub] + a.begin[sub] + t0) * rowb + c * BITS / 8;
+  const int left = min(kPackTokens, n - t0);
+#pragma unroll 1
+  for (int t = 0; t < left; ++t) {                 // (rolled: the registers move up instead of the code being repeated)
+    float v[8];
+    widen8<DT>(raw[0], v);
+    store_row_codes<DT, BITS>(dst, v, p0, p1, p2);
+    dst += rowb;
+#pragma unroll
+    for (int u = 0; u + 1 < kPackTokens; ++u)
+#pragma unroll
+      for (int r = 0; r < RAW; ++r) raw[u][r] = raw[u + 1][r];
+  }
+}
+
+// grid.x: workgroups of the keys' subsets, then word groups of the values' (a count of 0: no such tensor).
+template <int DT>
+__global__ __launch_bounds__(kPackThreads) void k_pack_kv(QPPair p, int4 wgs) {
+  __shared__ float red[2][kPackThreads / 64][16];
+  const int b = blockIdx.y;
+  int wg = blockIdx.x;
+  const int nk = wgs.x + wgs.y;
+  if (wg < nk) {
+    const QPArgs& a = p.t[0];
+    const int sub = wg >= wgs.x ? 1 : 0;
+    if (sub) wg -= wgs.x;
+    const int bits = a.bits[sub];
+    if (bits == 4) pack_keys<DT, 4>(a, sub, wg, b);
+    else if (bits == 2) pack_keys<DT, 2>(a, sub, wg, b);
+    else pack_keys<DT, 8>(a, sub, wg, b);
+  } else {
+    const QPArgs& a = p.t[1];
+    wg -= nk;
+    const int sub = wg >= wgs.z ? 1 : 0;
+    if (sub) wg -= wgs.z;
+    const int bits = a.bits[sub];
+    if (bits == 4) pack_values<DT, 4>(a, sub, wg, b, red);
+    else if (bits == 2) pack_values<DT, 2>(a, sub, wg, b, red);
+    else pack_values<DT, 8>(a, sub, wg, b, red);
   }
 }
 
@@ -723,7 +890,7 @@ static int64_t col_splits(int64_t B, int64_t NV, int64_t n, int tensors) {
 extern "C" size_t zc_quantize_pack_workspace(int64_t B, int64_t H, int64_t L, int64_t D) {
   if (B <= 0 || H <= 0 || D <= 0 || L < 0) return 0;
   const int64_t W = H * D, split = col_splits(B, W / 8, L, 1);
-  return (size_t)align_up64(B * 2 * W * (int64_t)sizeof(float4), 256) + (split > 1 ? (size_t)B * 2 * split * W * sizeof(float2) : 0);
+  return (size_t)align_up64(B * 2 * W * 4 * (int64_t)sizeof(float), 256) + (split > 1 ? (size_t)B * 2 * split * W * sizeof(float2) : 0);
 }
 
 // Validation and kernel arguments of one tensor's compression call.
@@ -760,7 +927,7 @@ static int qp_prepare(const zc_tensor4* x, const int32_t* salient_idx, int64_t k
   const int64_t chunk_off = (int64_t)out->n_chunks * 2 * x->B * W;
   a.chan_scale = out->chan_scale + chunk_off;
   a.chan_zero = out->chan_zero + chunk_off;
-  a.params = reinterpret_cast<float4*>(ws);
+  a.params = reinterpret_cast<float*>(ws);
   a.chunk_row = out->chunk_table + 4 * out->n_chunks;
   a.pos_offset = pos_offset;
   a.scheme = out->scheme;
@@ -882,6 +1049,28 @@ static int qp_launch_pack(const QPArgs& a, int dtype, int layout, hipStream_t st
   return ZC_OK;
 }
 
+// Tensors k_pack_kv takes: keys of any width, values whose rows fit a workgroup.
+static bool pack_kv_keys(const QPArgs& a, int layout) { return a.scheme == ZC_SCHEME_CHANNEL && layout == ZC_LAYOUT_ROW; }
+static bool pack_kv_values(const QPArgs& a, int layout) {
+  return a.scheme == ZC_SCHEME_CST && layout == ZC_LAYOUT_TGROUP && a.W <= kPackCpt * kPackThreads;
+}
+static int launch_pack_kv(const QPPair& p, bool keys, bool values, int dtype, hipStream_t st) {
+  const int threads = values ? (int)align_up64(p.t[1].W / kPackCpt, 64) : 256;
+  int4 wgs = make_int4(0, 0, 0, 0);
+  if (keys) {
+    wgs.x = (int)ceil_div64(ceil_div64(p.t[0].n[0], kPackTokens) * p.t[0].NV, threads);
+    wgs.y = (int)ceil_div64(ceil_div64(p.t[0].n[1], kPackTokens) * p.t[0].NV, threads);
+  }
+  if (values) { wgs.z = p.t[1].units[0]; wgs.w = p.t[1].units[1]; }
+  const dim3 grid((unsigned)(wgs.x + wgs.y + wgs.z + wgs.w), (unsigned)p.t[0].B), block(threads);
+  if (grid.x == 0) return ZC_OK;
+  if (dtype == ZC_F32) hipLaunchKernelGGL(k_pack_kv<ZC_F32>, grid, block, 0, st, p, wgs);
+  else if (dtype == ZC_F16) hipLaunchKernelGGL(k_pack_kv<ZC_F16>, grid, block, 0, st, p, wgs);
+  else hipLaunchKernelGGL(k_pack_kv<ZC_BF16>, grid, block, 0, st, p, wgs);
+  ZC_LAUNCH_CHECK();
+  return ZC_OK;
+}
+
 extern "C" int zc_quantize_pack(const zc_tensor4* x, const int32_t* salient_idx, int64_t k,
                                 const int32_t* regular_idx, int64_t n_reg, int64_t pos_offset,
                                 zc_packed* out, void* ws, size_t ws_bytes, void* stream) {
@@ -889,11 +1078,12 @@ extern "C" int zc_quantize_pack(const zc_tensor4* x, const int32_t* salient_idx,
   QPArgs& a = p.t[0];
   int rc = qp_prepare(x, salient_idx, k, regular_idx, n_reg, pos_offset, out, ws, ws_bytes, a);
   if (rc) return rc;
-  p.t[1] = a;
   hipStream_t st = (hipStream_t)stream;
   const zc_packed* const outs[1] = {out};
   rc = qp_launch_columns(p, outs, 1, x->dtype, false, st);
-  if (!rc && !a.resident) rc = qp_launch_pack(a, x->dtype, out->layout, st);
+  p.t[1] = a;
+  const bool keys = pack_kv_keys(a, out->layout), values = pack_kv_values(a, out->layout);
+  if (!rc && !a.resident) rc = keys || values ? launch_pack_kv(p, keys, values, x->dtype, st) : qp_launch_pack(a, x->dtype, out->layout, st);
   if (rc) return rc;
   qp_commit(out, k, n_reg);
   return ZC_OK;
@@ -919,27 +1109,15 @@ extern "C" int zc_quantize_pack_kv(const zc_tensor4* xk, const zc_tensor4* xv, c
   const QPArgs& a = p.t[0];
   const int dt = xk->dtype;
   // ---- statistics and parameters of both; codes of resident keys ---------------------------
-  // One packing launch can serve both tensors in the paper's configuration (channelwise keys in
-  // ROW layout, channel-separable tokenwise values in TGROUP layout) when a token row fits one
-  // workgroup of 256 threads.
-  const bool joint = outK->scheme == ZC_SCHEME_CHANNEL && outK->layout == ZC_LAYOUT_ROW &&
-                     outV->scheme == ZC_SCHEME_CST && outV->layout == ZC_LAYOUT_TGROUP && a.NV <= 256;
+  const bool keys = pack_kv_keys(a, outK->layout), values = pack_kv_values(p.t[1], outV->layout);
   const zc_packed* const outs[2] = {outK, outV};
-  rc = qp_launch_columns(p, outs, 2, dt, joint, st);
+  rc = qp_launch_columns(p, outs, 2, dt, keys && values, st);
   if (rc) return rc;
   // ---- quantize + pack what is not packed yet ------------------------------------------------
-  const int nwg = a.wgs[0] + a.wgs[1] + p.t[1].wgs[0] + p.t[1].wgs[1];
-  if (joint && !a.resident && nwg > 0) {
-    dim3 grid((unsigned)nwg, (unsigned)a.B), block((unsigned)align_up64(a.NV, 64));
-    if (dt == ZC_F32) hipLaunchKernelGGL(k_quant_pack_kv<ZC_F32>, grid, block, 0, st, p);
-    else if (dt == ZC_F16) hipLaunchKernelGGL(k_quant_pack_kv<ZC_F16>, grid, block, 0, st, p);
-    else hipLaunchKernelGGL(k_quant_pack_kv<ZC_BF16>, grid, block, 0, st, p);
-    ZC_LAUNCH_CHECK();
-  } else {
-    if (!p.t[0].resident) rc = qp_launch_pack(p.t[0], dt, outK->layout, st);
-    if (!rc && !p.t[1].resident) rc = qp_launch_pack(p.t[1], dt, outV->layout, st);
-    if (rc) return rc;
-  }
+  if (!p.t[0].resident && !keys) rc = qp_launch_pack(p.t[0], dt, outK->layout, st);
+  if (!rc && !p.t[1].resident && !values) rc = qp_launch_pack(p.t[1], dt, outV->layout, st);
+  if (!rc) rc = launch_pack_kv(p, keys && !p.t[0].resident, values, dt, st);
+  if (rc) return rc;
   qp_commit(outK, k, n_reg);
   qp_commit(outV, k, n_reg);
   return ZC_OK;
