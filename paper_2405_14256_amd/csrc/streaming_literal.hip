@@ -411,6 +411,8 @@ struct DequantArgs {
   DequantSeg seg[kDqSegs];
 };
 
+constexpr int64_t kDqFourSlots = 1 << 20;   // vectors of a launch from which a thread takes four slots
+
 // s x in fp16, rounded once: multiplication and conversion are one instruction (v_fma_mixlo_f16,
 // from the contraction; the empty assembly keeps two of them from being combined into products
 // in fp32 and a packed conversion).  Rounded to fp32 in between, a product that lies next to an
@@ -450,14 +452,17 @@ __device__ inline void store8(void* base, int64_t off, const float (&v)[8]) {
 // thread expands whole packed words and stores rows 16 bytes (32 for fp32) at a time - one
 // element per thread and a launch per segment took 8.6 us for each of the two subsets of 4096
 // tokens with 8 heads of 128 channels:
-//   ROW     a thread per 8 channels of a slot (1 to 2 words);
+//   ROW     a thread per 8 channels of a slot (1 to 2 words), or of four consecutive slots where that
+//           still fills the chip: the channel parameters are 64 bytes a thread, four times what it
+//           stores per slot (4 x 4096 tokens of 40 heads of 128 channels, fp16: 45.9 -> 32.7 us; 2 x 32768
+//           of 8 heads, bf16: 44.6 -> 25.9; but one prompt of 1000 of them 4.0 -> 4.7);
 //   TGROUP  a thread per 8 channels and field group of a word group (the same bit field range of 8
 //           words: the codes of 4 consecutive slots), one store per slot; a thread per whole word
 //           group (8 to 16 stores) left half the chip without one.
 // Consecutive threads take consecutive channels of a row.
 // The two subsets of a chunk share one launch: workgroup ranges per segment travel in the arguments.
 // Chunks go one after the other: where two hold the same position, the later one's row stays.
-template <int DT, int BITS>
+template <int DT, int BITS, int RS>
 __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg sg, int unit, int b) {
   constexpr int E = 32 / BITS, TB = 4 * E;
   constexpr uint32_t CM = (1u << BITS) - 1u;
@@ -467,7 +472,7 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
   const int64_t chan0 = ((int64_t)(sg.chunk * 2 + sub) * a.B + b) * a.W;
   const int vec = unit & (VPR - 1), rest = unit / VPR;    // rest: (head, slot) or (head, field group)
   const bool row_layout = a.layout == ZC_LAYOUT_ROW;
-  const int per_head = row_layout ? sg.len : ceil_div(sg.len, TB) * E;
+  const int per_head = row_layout ? ceil_div(sg.len, RS) : ceil_div(sg.len, TB) * E;
   const int h = rest / per_head, r = rest % per_head;
   if (h >= a.H) return;
   const int c = vec * 8;
@@ -493,15 +498,27 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
     }
   };
   if (row_layout) {
-    const int64_t slot = (int64_t)sg.begin + r, ti = (int64_t)b * cap + slot;
-    const uint8_t* src = a.codes[sub] + (bh * cap + slot) * (a.D * BITS / 8) + c * BITS / 8;
-    uint32_t w[2] = {0u, 0u};
-    if constexpr (BITS == 8) { const uint2 t = *reinterpret_cast<const uint2*>(src); w[0] = t.x; w[1] = t.y; }
-    else if constexpr (BITS == 4) w[0] = *reinterpret_cast<const uint32_t*>(src);
-    else w[0] = *reinterpret_cast<const uint16_t*>(src);
-    float ts = 1.f, tz = 0.f;
-    if (a.tokwise) { ts = a.tok_scale[sub][ti]; tz = a.tok_zero[sub][ti]; }
-    expand(a.pos[sub][ti], ts, tz, [&](int i) { return (w[i / E] >> (BITS * (i % E))) & CM; });
+    constexpr int NW = BITS == 8 ? 2 : 1;
+    const int rel = r * RS, n = min(RS, sg.len - rel);
+    const int64_t slot = (int64_t)sg.begin + rel, ti = (int64_t)b * cap + slot;
+    const int rowb = a.D * BITS / 8;
+    const uint8_t* src = a.codes[sub] + (bh * cap + slot) * rowb + c * BITS / 8;
+    uint32_t w[RS][NW];
+    int pos[RS];
+    float ts[RS], tz[RS];
+#pragma unroll
+    for (int e = 0; e < RS; ++e) {           // (a slot past the end repeats the last one and is not stored)
+      const int at = RS == 1 ? 0 : min(e, n - 1);
+      if constexpr (BITS == 8) { const uint2 t = *reinterpret_cast<const uint2*>(src + at * rowb); w[e][0] = t.x; w[e][1] = t.y; }
+      else if constexpr (BITS == 4) w[e][0] = *reinterpret_cast<const uint32_t*>(src + at * rowb);
+      else w[e][0] = *reinterpret_cast<const uint16_t*>(src + at * rowb);
+      pos[e] = a.pos[sub][ti + at];
+      ts[e] = 1.f; tz[e] = 0.f;
+      if (a.tokwise) { ts[e] = a.tok_scale[sub][ti + at]; tz[e] = a.tok_zero[sub][ti + at]; }
+    }
+#pragma unroll
+    for (int e = 0; e < RS; ++e)
+      if (RS == 1 || e < n) expand(pos[e], ts[e], tz[e], [&](int i) { return (w[e][i / E] >> (BITS * (i % E))) & CM; });
   } else {
     // field group jf of word group kg of block blk: slots rel .. rel + 3 (inside the block, so inside the arena)
     const int jf = r % (E / 4), kg = (r / (E / 4)) & 3, blk = r / E;
@@ -529,16 +546,16 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
 }
 
 // grid (workgroups of all segments, B)
-template <int DT>
+template <int DT, int RS>
 __global__ __launch_bounds__(kDqThreads) void k_dequantize_cache(DequantArgs a) {
   int si = 0;
   while (si + 1 < a.n_segs && (int)blockIdx.x >= a.seg[si + 1].first_block) ++si;
   const DequantSeg sg = a.seg[si];
   const int unit = ((int)blockIdx.x - sg.first_block) * kDqThreads + threadIdx.x;
   const int bits = a.bits[sg.sub];
-  if (bits == 4) dequantize_segment<DT, 4>(a, sg, unit, blockIdx.y);
-  else if (bits == 2) dequantize_segment<DT, 2>(a, sg, unit, blockIdx.y);
-  else dequantize_segment<DT, 8>(a, sg, unit, blockIdx.y);
+  if (bits == 4) dequantize_segment<DT, 4, RS>(a, sg, unit, blockIdx.y);
+  else if (bits == 2) dequantize_segment<DT, 2, RS>(a, sg, unit, blockIdx.y);
+  else dequantize_segment<DT, 8, RS>(a, sg, unit, blockIdx.y);
 }
 
 }  // namespace zc
@@ -687,14 +704,15 @@ extern "C" int zc_dequantize_cache(const zc_packed* p, const zc_tensor4* out, vo
   a.bits[0] = p->bits_hi; a.bits[1] = p->bits_lo;
   a.cap[0] = p->cap_hi; a.cap[1] = p->cap_lo;
   a.out = out->ptr; a.o_sB = out->sB; a.o_sH = out->sH; a.o_sL = out->sL; a.out_L = (int)out->L;
-  int64_t blocks = 0;
+  int64_t blocks = 0, row_slots = 1;
   a.n_segs = 0;
   auto flush = [&]() -> int {
     if (a.n_segs == 0) return ZC_OK;
     const dim3 grid((unsigned)blocks, (unsigned)p->B);
-    if (out->dtype == ZC_F32) hipLaunchKernelGGL(k_dequantize_cache<ZC_F32>, grid, dim3(kDqThreads), 0, st, a);
-    else if (out->dtype == ZC_F16) hipLaunchKernelGGL(k_dequantize_cache<ZC_F16>, grid, dim3(kDqThreads), 0, st, a);
-    else hipLaunchKernelGGL(k_dequantize_cache<ZC_BF16>, grid, dim3(kDqThreads), 0, st, a);
+    const auto launch = [&](auto one, auto four) { hipLaunchKernelGGL(row_slots == 4 ? four : one, grid, dim3(kDqThreads), 0, st, a); };
+    if (out->dtype == ZC_F32) launch(k_dequantize_cache<ZC_F32, 1>, k_dequantize_cache<ZC_F32, 4>);
+    else if (out->dtype == ZC_F16) launch(k_dequantize_cache<ZC_F16, 1>, k_dequantize_cache<ZC_F16, 4>);
+    else launch(k_dequantize_cache<ZC_BF16, 1>, k_dequantize_cache<ZC_BF16, 4>);
     ZC_LAUNCH_CHECK();
     a.n_segs = 0;
     blocks = 0;
@@ -707,12 +725,13 @@ extern "C" int zc_dequantize_cache(const zc_packed* p, const zc_tensor4* out, vo
   for (int chunk = 0; chunk < p->n_chunks; ++chunk) {
     rc = flush();                // (the chunk before this one)
     if (rc) return rc;
+    const int32_t* row = p->chunk_table_host + 4 * chunk;
+    row_slots = ((int64_t)row[1] + row[3]) * p->H * vpr * p->B >= kDqFourSlots ? 4 : 1;
     for (int which = 0; which < 2; ++which) {
-      const int32_t* row = p->chunk_table_host + 4 * chunk;
       for (int64_t done = 0, len = row[2 * which + 1]; done < len; done += most) {
         const int64_t part = len - done < most ? len - done : most;
         // a unit is 8 channels of a slot (ROW) or of 4 slots (TGROUP: 32 / bits such groups per block of 4 * 32 / bits slots)
-        const int64_t per_head = p->layout == ZC_LAYOUT_ROW ? part : ceil_div64(part, 4 * (32 / a.bits[which])) * (32 / a.bits[which]);
+        const int64_t per_head = p->layout == ZC_LAYOUT_ROW ? ceil_div64(part, row_slots) : ceil_div64(part, 4 * (32 / a.bits[which])) * (32 / a.bits[which]);
         const int64_t n = ceil_div64(per_head * p->H * vpr, kDqThreads);
         if (a.n_segs == kDqSegs || blocks + n > kDqBlocks) {
           rc = flush();

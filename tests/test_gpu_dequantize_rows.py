@@ -1,0 +1,24 @@
+"""zc_dequantize_cache of ROW layout around the size from which a thread expands four slots: ragged
+last quads, every bit width, token scales and none, exactly the unpacked cache in token order."""
+import pytest
+import torch
+
+from paper_2405_14256_amd import binding as zb
+from tests.test_gpu_literal import _unpacked
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L", [4095, 4096, 4099, 4102])          # 2^20 vectors at 4096 tokens
+@pytest.mark.parametrize("bits_hi,bits_lo,k,scheme,dtype", [(4, 2, 1633, "channel", torch.bfloat16), (8, 4, 1, "channel", torch.float16),
+                                                            (2, 8, 0, "token", torch.float32)])
+def test_dequantize_row_quads(L, bits_hi, bits_lo, k, scheme, dtype):
+    B, H, d = 2, 8, 128
+    g = torch.Generator().manual_seed(L)
+    x = torch.randn(B, H, L, d, generator=g).to(dtype).to("cuda")
+    p = zb.PackedTensor(B, H, d, 1664, 4160, bits_hi, bits_lo, scheme, zb.ZC_LAYOUT_ROW, max_chunks=1, device="cuda")
+    sal, reg = zb.zc_select_salient(torch.rand(B, L, generator=g).cuda(), k)
+    zb.zc_quantize_pack(x, sal, reg, p)
+    out = torch.zeros_like(x)
+    zb.zc_dequantize_cache(p, out)
+    assert torch.equal(out, _unpacked(p, L, dtype))
