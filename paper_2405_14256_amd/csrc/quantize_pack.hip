@@ -153,6 +153,22 @@ __device__ inline float wave_min_rest(float (&v)[N / 2]) {
   return dpp_min_quad(r);
 }
 
+// x s rounded to an integer, plus 1.5 * 2^23 (exact for |x s| < 2^22); x s itself is rounded first.
+constexpr float kRoundMagic = 12582912.f;
+constexpr uint32_t kTameZero = 0x4a000000u;        // 2^21: zero points up to here keep every sum in range
+__device__ inline float rounded_sum(float x, float s) {
+#pragma clang fp contract(off)
+  const float q = x * s;
+  return q + kRoundMagic;
+}
+
+template <int BITS>
+__device__ inline uint32_t shift_add(uint32_t acc, uint32_t x) {          // (written out: the compiler makes shifts and three-way sums of a chain)
+  uint32_t r;
+  asm("v_lshl_add_u32 %0, %1, %2, %3" : "=v"(r) : "v"(acc), "n"(BITS), "v"(x));
+  return r;
+}
+
 __device__ inline int tile_of_field_group(int bits, int jf) {
   // Slot tile (16 slots) addressed by field group jf of a TGROUP word.
   return (bits == 2) ? ((jf & 1) * 2 + (jf >> 1)) : jf;
@@ -436,6 +452,8 @@ __device__ inline void quant_units(const QPArgs& a, int sub, int g0, int ng, int
   }
   __syncthreads();
 
+  float neg_zero = -0.f;                             // (opaque: a known one would turn the fma back into a product)
+  asm("" : "+s"(neg_zero));
   struct Batch { uint4 raw[TBAT][RAW]; };
   // batch q of the workgroup: word group g0 + q / NBAT, tokens (q % NBAT) * TBAT + t of it
   auto slot_of = [&](int q, int t) {                 // slot inside the block
@@ -490,9 +508,18 @@ __device__ inline void quant_units(const QPArgs& a, int sub, int g0, int ng, int
 
     float xs[TBAT][8];                               // tokenwise: x' = x / c; channelwise: x
     float sinv[TBAT], zt[TBAT];
+    float silane = 0.f, zlane = 0.f, low = 0.f, high = 0.f;      // of token (lane & 7): 1/s, z, the bounds of its rounded sums
+    bool wild = false;                               // some token's zero point is out of their range
     float rt[TBAT], yt[TBAT];                        // EXACT (the plain tokenwise scheme) only: range and its reciprocal
 #pragma unroll
     for (int t = 0; t < TBAT; ++t) {
+      if constexpr (TOKWISE && DT == ZC_F16) {        // widened by the multiplication: v_fma_mix_f32 with an addend of -0
+        typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+        const h8v hx = __builtin_bit_cast(h8v, bt.raw[t][0]);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xs[t][i] = fmaf((float)hx[i], p0[i], neg_zero);
+        continue;
+      }
       widen(bt, t, xs[t]);
       if constexpr (TOKWISE) {
 #pragma unroll
@@ -533,6 +560,10 @@ __device__ inline void quant_units(const QPArgs& a, int sub, int g0, int ng, int
       const float y = __builtin_amdgcn_rcpf(R);
       const float z = -rintf(refined_ratio(tmin, QMAX, R, y));   // tie-exact: a whole row depends on it
       const float si = QMAX * y;
+      silane = si; zlane = z;
+      low = kRoundMagic - z;
+      high = my_rel < n ? low + QMAX : low;
+      wild = __ballot(lane < TBAT && (__float_as_uint(z) & 0x7fffffffu) > kTameZero) != 0;
       if (my_live) {
         a.tok_scale[sub][my_o] = R * (1.f / QMAX);
         a.tok_zero[sub][my_o] = z;
@@ -595,6 +626,50 @@ __device__ inline void quant_units(const QPArgs& a, int sub, int g0, int ng, int
       }
     }
     if constexpr (LAYOUT == ZC_LAYOUT_TGROUP) {
+      if constexpr (TOKWISE && !EXACT) {
+        // Adding 1.5 * 2^23 rounds to the integers (half to even); clamped there to [-z, QMAX - z],
+        // the sum's low bits are the code plus those of 1.5 * 2^23 - z, which come off once per word:
+        // four instructions a code instead of five, and no conversion.  (A dead token's range is empty.)
+        // Values of 16 x 4096 tokens of 40 heads, fp16, column sweep included: 320.6 -> 313.7 us.
+        uint32_t word_part[8];
+        float lo_t[TBAT], hi_t[TBAT];
+        uint32_t off = 0u;
+#pragma unroll
+        for (int t = 0; t < TBAT; ++t) {
+          const uint32_t u = (uint32_t)__builtin_amdgcn_readlane(__float_as_int(low), t);
+          lo_t[t] = __uint_as_float(u);
+          hi_t[t] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(high), t));
+          off += u << (BITS * t);
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          uint32_t acc = 0u;
+#pragma unroll
+          for (int t = TBAT - 1; t >= 0; --t)
+            acc = shift_add<BITS>(acc, __float_as_uint(__builtin_amdgcn_fmed3f(rounded_sum(xs[t][i], sinv[t]), lo_t[t], hi_t[t])));
+          word_part[i] = acc - off;
+        }
+        if (wild) {
+          // A zero point out of that range (a row whose spread is a 10^-6 of its values, an infinity):
+          // the batch again from memory, in a rolled loop that needs few registers.
+#pragma unroll
+          for (int i = 0; i < 8; ++i) word_part[i] = 0u;
+#pragma unroll 1
+          for (int t = 0; t < TBAT; ++t) {
+            const int pos = sidx[slot_of(q, t)];
+            if (pos < 0) continue;
+            float v[8];
+            load8<DT>(xbase + (int64_t)pos * row_bytes, 0, v);
+            const float st = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(silane), t));
+            const float zt = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(zlane), t));
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+              word_part[i] |= (uint32_t)__builtin_amdgcn_fmed3f(rintf(v[i] * p0[i] * st) + zt, 0.f, QMAX) << (BITS * t);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) words[i] |= word_part[i] << (BITS * bi * TBAT);
+      } else {
       // channel i: the batch's tokens, 16 bits (FPG tokens) at a time; dead tokens add nothing
       constexpr int NG = TBAT / FPG > 0 ? TBAT / FPG : 1;
       constexpr int TPG = TBAT < FPG ? TBAT : FPG;   // tokens per 16-bit group
@@ -617,6 +692,7 @@ __device__ inline void quant_units(const QPArgs& a, int sub, int g0, int ng, int
           }
           words[i] |= (uint32_t)acc << (BITS * (bi * TBAT + g * TPG));
         }
+      }
       }
       if (bi == NBAT - 1) {
         const int64_t nblk = a.cap[sub] / TB;
@@ -857,9 +933,11 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_kv(QPPair p, int4 wgs) {
 
 template <int DT, int LAYOUT, int MAXT>
 static void launch_qp_l(const QPArgs& a, bool tokwise, dim3 grid, dim3 block, hipStream_t st) {
-  if (!tokwise) hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, false, false, MAXT>), grid, block, 0, st, a);
-  else if (a.scheme == ZC_SCHEME_TOKEN) hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, true, true, MAXT>), grid, block, 0, st, a);
-  else hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, true, false, MAXT>), grid, block, 0, st, a);
+  // (what k_pack_kv takes does not come here: channelwise ROW tensors, narrow channel-separable TGROUP ones)
+  if (!tokwise) {
+    if constexpr (LAYOUT == ZC_LAYOUT_TGROUP && MAXT == 256) hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, false, false, MAXT>), grid, block, 0, st, a);
+  } else if (a.scheme == ZC_SCHEME_TOKEN) hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, true, true, MAXT>), grid, block, 0, st, a);
+  else if constexpr (LAYOUT == ZC_LAYOUT_ROW || MAXT > 256) hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, true, false, MAXT>), grid, block, 0, st, a);
 }
 template <int DT, int MAXT>
 static void launch_qp_t(const QPArgs& a, int layout, bool tokwise, dim3 grid, dim3 block, hipStream_t st) {

@@ -39,3 +39,31 @@ def test_pack_edges(H, D, bits_hi, bits_lo):
                 mism += r["n_mismatch"]
             assert torch.equal(P.pos_hi[:, :k].cpu(), sal) and torch.equal(P.pos_lo[:, :n].cpu(), reg)
     assert mism <= 1e-4 * total, (mism, total)
+
+
+@pytest.mark.parametrize("H,bits_hi,bits_lo", [(17, 4, 2), (40, 8, 4)])
+def test_wide_rows_whose_zero_points_leave_the_rounding_range(H, bits_hi, bits_lo):
+    """Rows of ones in which one channel is 2^-24 less: zero points of 10^8, beyond what the sums with
+    1.5 * 2^23 hold.  The codes follow from the stored z as clamp(rint(x / s) + z) in fp32; the
+    quotients are exact (s is a power of two over 2^bits - 1), so there is no tolerance."""
+    import numpy as np
+    from paper_2405_14256_amd import binding as zb
+    from tests import packfmt
+    D, L, k, cap = 128, 75, 33, 64
+    X = torch.ones(1, H, L, D)
+    rows = [0, 7, 32, 33, 74]
+    for t in rows:
+        X[0, t % H, t, 5] = 1.0 - 2.0 ** -24
+    sal, reg = torch.arange(0, k, dtype=torch.int32)[None], torch.arange(k, L, dtype=torch.int32)[None]
+    P = zb.PackedTensor(1, H, D, cap, cap, bits_hi, bits_lo, "cst", zb.ZC_LAYOUT_TGROUP, max_chunks=1, device="cuda")
+    zb.zc_quantize_pack(X.cuda(), sal.cuda(), reg.cuda(), P)
+    torch.cuda.synchronize()
+    for idx, bits, codes, z in ((sal[0], bits_hi, P.codes_hi, P.tok_zero_hi), (reg[0], bits_lo, P.codes_lo, P.tok_zero_lo)):
+        got = packfmt.decode_tgroup(codes.cpu().numpy(), 1, H, D, cap, bits)[0]           # [H, cap, D]
+        z = z.cpu().numpy()[0]
+        qmax = np.float32(2 ** bits - 1)
+        for j, t in enumerate(idx.tolist()):
+            inv_s = qmax * np.float32(2.0 ** 24) if t in rows else np.float32(1.0)
+            assert (abs(z[j]) > 2.0 ** 21) == (t in rows)
+            want = np.clip(np.rint(X[0, :, t].numpy() * inv_s) + z[j], 0, qmax)
+            assert np.array_equal(got[:, j], want), (bits, t)
