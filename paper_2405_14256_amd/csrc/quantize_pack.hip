@@ -1031,7 +1031,9 @@ static int qp_prepare(const zc_tensor4* x, const int32_t* salient_idx, int64_t k
 // The widest rows that leave a workgroup per CU; narrower ones where a resident subset only
 // then fits the registers.  Keys are resident wherever they fit - except in a call for both
 // tensors with too few workgroups to hide the packing behind each other's loads, where one
-// packing launch serves both (one prompt of 4096 tokens, 8 heads: 26.1 against 27.5 us); and
+// packing launch serves both (one prompt of 4096 tokens, 8 heads: 26.1 against 27.5 us; of 16-bit
+// tensors also at a workgroup per CU: 4 such prompts 34.9 against 39.2, 16 of 1000 tokens 31.4 and
+// 35.5, but 5 of 4096 43.1 and 41.0; 16 of 1000 tokens of 4 heads in fp32 28.3 and 27.6); and
 // except for wide 16-bit rows of both that fit in slices of 16 channels only, a quarter of a
 // cache line (12000 tokens of 32 heads of 128 channels: 105 against 121 us; of 64: 216 and 279) -
 // above 512 channels where that also takes workgroups of 1024 threads (8192 tokens of 8 heads, 8
@@ -1048,7 +1050,7 @@ static ColPlan col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int
   while (v > 2 && n > rows * th / v) v /= 2;
   if (n > rows * th / v) th = 1024;
   const bool strips = tensors == 2 && dtype != ZC_F32 && v == 2 && a[0].NV > (th == 1024 ? 64 : 256);
-  const bool fits = n <= rows * th / v && !(joint_pack && wgs(v) < 256) && !strips;
+  const bool fits = n <= rows * th / v && !(joint_pack && wgs(v) < (dtype == ZC_F32 ? 256 : 257)) && !strips;
   bool any = false;
   for (int t = 0; t < tensors; ++t) {
     a[t].resident = fits && out[t]->scheme == ZC_SCHEME_CHANNEL && out[t]->layout == ZC_LAYOUT_ROW;
