@@ -588,7 +588,7 @@ __device__ inline void quant_units(const QPArgs& a, int sub, int g0, int ng, int
       else if constexpr (DT == ZC_F32) return rintf(refined_ratio(xv, QMAX, rt[t], yt[t])) + zt[t];
       else return rintf(refined_div(xv * QMAX, rt[t], yt[t])) + zt[t];      // x * qmax is exact
     };
-    if (!vvalid) return;
+    if (!vvalid) return;                             // (a row is whole heads of 64 or 128 channels: lanes 0..7, read below, stay or go together)
 #pragma unroll
     for (int t = 0; t < TBAT; ++t) {
       // Eq. 5: round(x / s) first, then + z, then clip
@@ -835,7 +835,7 @@ __device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, fl
       a.tok_zero[sub][my_o] = z[q];
     }
   }
-  if (!valid) return;
+  if (!valid) return;                                // (a row is whole heads of 64 or 128 channels: lanes 0..7, read below, stay or go together)
   uint32_t words[kPackCpt] = {};
 #pragma unroll
   for (int q = 0; q < NBAT; ++q)
