@@ -931,24 +931,34 @@ __global__ __launch_bounds__(kPackThreads) void k_pack_kv(QPPair p, int4 wgs) {
   }
 }
 
+// (what k_pack_kv takes does not come here, see pack_route: no instances for channelwise ROW tensors and
+// narrow channel-separable TGROUP ones)
 template <int DT, int LAYOUT, int MAXT>
-static void launch_qp_l(const QPArgs& a, bool tokwise, dim3 grid, dim3 block, hipStream_t st) {
-  // (what k_pack_kv takes does not come here: channelwise ROW tensors, narrow channel-separable TGROUP ones)
+static int launch_qp_l(const QPArgs& a, bool tokwise, dim3 grid, dim3 block, hipStream_t st) {
   if (!tokwise) {
-    if constexpr (LAYOUT == ZC_LAYOUT_TGROUP && MAXT == 256) hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, false, false, MAXT>), grid, block, 0, st, a);
-  } else if (a.scheme == ZC_SCHEME_TOKEN) hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, true, true, MAXT>), grid, block, 0, st, a);
-  else if constexpr (LAYOUT == ZC_LAYOUT_ROW || MAXT > 256) hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, true, false, MAXT>), grid, block, 0, st, a);
+    if constexpr (LAYOUT == ZC_LAYOUT_TGROUP && MAXT == 256) {
+      hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, false, false, MAXT>), grid, block, 0, st, a);
+      return ZC_OK;
+    }
+  } else if (a.scheme == ZC_SCHEME_TOKEN) {
+    hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, true, true, MAXT>), grid, block, 0, st, a);
+    return ZC_OK;
+  } else if constexpr (LAYOUT == ZC_LAYOUT_ROW || MAXT > 256) {
+    hipLaunchKernelGGL((k_quant_pack<DT, LAYOUT, true, false, MAXT>), grid, block, 0, st, a);
+    return ZC_OK;
+  }
+  return ZC_ERR_UNSUPPORTED;
 }
 template <int DT, int MAXT>
-static void launch_qp_t(const QPArgs& a, int layout, bool tokwise, dim3 grid, dim3 block, hipStream_t st) {
-  if (layout == ZC_LAYOUT_ROW) launch_qp_l<DT, ZC_LAYOUT_ROW, MAXT>(a, tokwise, grid, block, st);
-  else launch_qp_l<DT, ZC_LAYOUT_TGROUP, MAXT>(a, tokwise, grid, block, st);
+static int launch_qp_t(const QPArgs& a, int layout, bool tokwise, dim3 grid, dim3 block, hipStream_t st) {
+  if (layout == ZC_LAYOUT_ROW) return launch_qp_l<DT, ZC_LAYOUT_ROW, MAXT>(a, tokwise, grid, block, st);
+  return launch_qp_l<DT, ZC_LAYOUT_TGROUP, MAXT>(a, tokwise, grid, block, st);
 }
 template <int DT>
-static void launch_qp(const QPArgs& a, int layout, bool tokwise, dim3 grid, dim3 block, hipStream_t st) {
-  if (block.x <= 256) launch_qp_t<DT, 256>(a, layout, tokwise, grid, block, st);
-  else if (block.x <= 768) launch_qp_t<DT, 768>(a, layout, tokwise, grid, block, st);
-  else launch_qp_t<DT, 1024>(a, layout, tokwise, grid, block, st);
+static int launch_qp(const QPArgs& a, int layout, bool tokwise, dim3 grid, dim3 block, hipStream_t st) {
+  if (block.x <= 256) return launch_qp_t<DT, 256>(a, layout, tokwise, grid, block, st);
+  if (block.x <= 768) return launch_qp_t<DT, 768>(a, layout, tokwise, grid, block, st);
+  return launch_qp_t<DT, 1024>(a, layout, tokwise, grid, block, st);
 }
 
 }  // namespace zc
@@ -1122,17 +1132,27 @@ static int qp_launch_pack(const QPArgs& a, int dtype, int layout, hipStream_t st
   int zchunks = 1;
   if (!tokwise && TXq > 256) { zchunks = (int)ceil_div64(a.NV, 256); TXq = 256; }
   dim3 grid((unsigned)(a.wgs[0] + a.wgs[1]), (unsigned)a.B, (unsigned)zchunks), block(TXq);
-  if (dtype == ZC_F32) launch_qp<ZC_F32>(a, layout, tokwise, grid, block, st);
-  else if (dtype == ZC_F16) launch_qp<ZC_F16>(a, layout, tokwise, grid, block, st);
-  else launch_qp<ZC_BF16>(a, layout, tokwise, grid, block, st);
+  int rc;
+  if (dtype == ZC_F32) rc = launch_qp<ZC_F32>(a, layout, tokwise, grid, block, st);
+  else if (dtype == ZC_F16) rc = launch_qp<ZC_F16>(a, layout, tokwise, grid, block, st);
+  else rc = launch_qp<ZC_BF16>(a, layout, tokwise, grid, block, st);
+  if (rc) return rc;
   ZC_LAUNCH_CHECK();
   return ZC_OK;
 }
 
-// Tensors k_pack_kv takes: keys of any width, values whose rows fit a workgroup.
-static bool pack_kv_keys(const QPArgs& a, int layout) { return a.scheme == ZC_SCHEME_CHANNEL && layout == ZC_LAYOUT_ROW; }
-static bool pack_kv_values(const QPArgs& a, int layout) {
-  return a.scheme == ZC_SCHEME_CST && layout == ZC_LAYOUT_TGROUP && a.W <= kPackCpt * kPackThreads;
+// The kernel that packs a tensor which does not stay resident, whichever place it has in a call:
+// k_pack_kv takes keys (channelwise, ROW layout) of any width and values (channel-separable,
+// TGROUP layout) whose rows fit a workgroup, k_quant_pack the others.
+enum class PackRoute { Keys, Values, General };
+static PackRoute pack_route(const QPArgs& a, int layout) {
+  if (a.scheme == ZC_SCHEME_CHANNEL && layout == ZC_LAYOUT_ROW) return PackRoute::Keys;
+  if (a.scheme == ZC_SCHEME_CST && layout == ZC_LAYOUT_TGROUP && a.W <= kPackCpt * kPackThreads) return PackRoute::Values;
+  return PackRoute::General;
+}
+// Keys in the first place and values in the second share a launch.
+static bool pack_joint(const QPPair& p, const zc_packed* const* out, int tensors) {
+  return tensors == 2 && pack_route(p.t[0], out[0]->layout) == PackRoute::Keys && pack_route(p.t[1], out[1]->layout) == PackRoute::Values;
 }
 static int launch_pack_kv(const QPPair& p, bool keys, bool values, int dtype, hipStream_t st) {
   const int threads = values ? (int)align_up64(p.t[1].W / kPackCpt, 64) : 256;
@@ -1151,6 +1171,20 @@ static int launch_pack_kv(const QPPair& p, bool keys, bool values, int dtype, hi
   return ZC_OK;
 }
 
+// Codes of what the column sweep has not packed.
+static int qp_launch_packs(const QPPair& p, const zc_packed* const* out, int tensors, int dtype, hipStream_t st) {
+  if (pack_joint(p, out, tensors)) return launch_pack_kv(p, !p.t[0].resident, true, dtype, st);
+  for (int t = 0; t < tensors; ++t) {
+    const QPArgs& a = p.t[t];
+    if (a.resident) continue;
+    const PackRoute route = pack_route(a, out[t]->layout);
+    const int rc = route == PackRoute::General ? qp_launch_pack(a, dtype, out[t]->layout, st)
+                                               : launch_pack_kv({{a, a}}, route == PackRoute::Keys, route == PackRoute::Values, dtype, st);
+    if (rc) return rc;
+  }
+  return ZC_OK;
+}
+
 extern "C" int zc_quantize_pack(const zc_tensor4* x, const int32_t* salient_idx, int64_t k,
                                 const int32_t* regular_idx, int64_t n_reg, int64_t pos_offset,
                                 zc_packed* out, void* ws, size_t ws_bytes, void* stream) {
@@ -1161,9 +1195,7 @@ extern "C" int zc_quantize_pack(const zc_tensor4* x, const int32_t* salient_idx,
   hipStream_t st = (hipStream_t)stream;
   const zc_packed* const outs[1] = {out};
   rc = qp_launch_columns(p, outs, 1, x->dtype, false, st);
-  p.t[1] = a;
-  const bool keys = pack_kv_keys(a, out->layout), values = pack_kv_values(a, out->layout);
-  if (!rc && !a.resident) rc = keys || values ? launch_pack_kv(p, keys, values, x->dtype, st) : qp_launch_pack(a, x->dtype, out->layout, st);
+  if (!rc) rc = qp_launch_packs(p, outs, 1, x->dtype, st);
   if (rc) return rc;
   qp_commit(out, k, n_reg);
   return ZC_OK;
@@ -1186,17 +1218,11 @@ extern "C" int zc_quantize_pack_kv(const zc_tensor4* xk, const zc_tensor4* xv, c
   rc = qp_prepare(xv, salient_idx, k, regular_idx, n_reg, pos_offset, outV, reinterpret_cast<uint8_t*>(ws) + half, half, p.t[1]);
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
-  const QPArgs& a = p.t[0];
   const int dt = xk->dtype;
-  // ---- statistics and parameters of both; codes of resident keys ---------------------------
-  const bool keys = pack_kv_keys(a, outK->layout), values = pack_kv_values(p.t[1], outV->layout);
   const zc_packed* const outs[2] = {outK, outV};
-  rc = qp_launch_columns(p, outs, 2, dt, keys && values, st);
-  if (rc) return rc;
-  // ---- quantize + pack what is not packed yet ------------------------------------------------
-  if (!p.t[0].resident && !keys) rc = qp_launch_pack(p.t[0], dt, outK->layout, st);
-  if (!rc && !p.t[1].resident && !values) rc = qp_launch_pack(p.t[1], dt, outV->layout, st);
-  if (!rc) rc = launch_pack_kv(p, keys && !p.t[0].resident, values, dt, st);
+  // statistics and parameters of both and codes of resident keys, then what is not packed yet
+  rc = qp_launch_columns(p, outs, 2, dt, pack_joint(p, outs, 2), st);
+  if (!rc) rc = qp_launch_packs(p, outs, 2, dt, st);
   if (rc) return rc;
   qp_commit(outK, k, n_reg);
   qp_commit(outV, k, n_reg);
