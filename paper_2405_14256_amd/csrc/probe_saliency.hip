@@ -236,6 +236,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
       const bool whole = colb + 31 <= pfirst[rb];            // every row of the block sees every column
       const int vis = last[rb] - colb;                       // of its columns (acc_row(v, 0)) a lane sees those up to vis
       bool set = __builtin_amdgcn_ballot_w64(m[rb] == -INFINITY && vis >= 0) != 0;
+      float base = m[rb];                                    // what the logits are taken relative to
 #pragma unroll 1
       for (int pass = 0; pass < 2; ++pass) {
         if (set) {
@@ -246,17 +247,18 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
           const float m_new = fmaxf(m[rb], tmax * a.scale_log2);
           if (m_new > -INFINITY) z[rb] *= __builtin_amdgcn_exp2f(m[rb] - m_new);
           m[rb] = m_new;
+          base = m_new > -INFINITY ? m_new : 0.f;            // (every visible logit -inf so far: their terms are 0, not exp2(-inf + inf))
         }
         float sum = 0.f;
         if (whole) {
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
-            sum += __builtin_amdgcn_exp2f(fmaf(acc[rb][v], a.scale_log2, -m[rb]));
+            sum += __builtin_amdgcn_exp2f(fmaf(acc[rb][v], a.scale_log2, -base));
             if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
           }
         } else {
           const int seen = opaque(vis);
-          const float ref = __int_as_float(opaque(__float_as_int(m[rb])));     // (or it joins the two loops, and holds all 16 terms)
+          const float ref = __int_as_float(opaque(__float_as_int(base)));     // (or it joins the two loops, and holds all 16 terms)
 #pragma unroll
           for (int v = 0; v < 16; ++v) {
             const float e = __builtin_amdgcn_exp2f(fmaf(acc[rb][v], a.scale_log2, -ref));

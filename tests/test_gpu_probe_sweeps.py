@@ -66,3 +66,27 @@ def test_scores_of_row_blocks_and_ranges(case, external):
         rel = ((got.double() - want).abs() / want.clamp(min=1e-30)).max().item()
         assert rel < 3e-5, (rel, ph is not None)
     assert torch.allclose(per_head.mean(1), got, rtol=1e-5, atol=0)
+
+
+# Masked keys: columns whose logits are -inf, in tiles that a row sees in part, in whole tiles and as
+# all of the columns that a row's lane sees of its first tiles.
+@pytest.mark.parametrize("d,dtype,P", [(64, torch.float32, 40), (128, torch.bfloat16, 96), (64, torch.float16, 26)])
+def test_scores_with_logits_of_minus_infinity(d, dtype, P):
+    B, Hq, Hkv, L = 1, 4, 2, 300
+    g = torch.Generator(device=DEV).manual_seed(P)
+    pos = torch.cat([torch.arange(5, 12), torch.tensor([44, 70]), spread(L, 400)[-(P - 9):]]).unique().to(DEV)
+    q = torch.randn(B, Hq, pos.numel(), d, generator=g, device=DEV)
+    q[..., 3] = 1.0
+    k = torch.randn(B, Hkv, L, d, generator=g, device=DEV)
+    k[:, :, [0, 1, 2, 3, 8, 64, 65, 66, 67, 128]] = 0.0
+    k[:, :, [0, 1, 2, 3, 8, 64, 65, 66, 67, 128], 3] = float("-inf")
+    k[:, :, 32:64] = 0.0
+    k[:, :, 32:64, 3] = float("-inf")
+    q, k = q.to(dtype), k.to(dtype)
+    rows = torch.arange(pos.numel(), device=DEV)
+    got = zb.zc_probe_saliency(q, k, pos.int(), probe_rows=rows.int())
+    want = reference(q, k, rows, pos)
+    hidden = torch.isinf(k[0, 0, :, 3])
+    assert bool((got[:, hidden] == 0).all()) and bool(torch.isfinite(got).all())
+    rel = ((got.double() - want).abs() / want.clamp(min=1e-30))[:, ~hidden].max().item()
+    assert rel < 3e-5, rel                       # (the bound of the test above)
