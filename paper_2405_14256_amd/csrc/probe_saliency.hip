@@ -89,7 +89,7 @@ constexpr int kLseCols = 64;                   // columns per K tile of sweep 1
 
 // The row blocks of a head share its a.head_wgs workgroups in proportion to the column tiles their
 // rows can see (a block near the end of a prompt sees ten times those of one near its start; a
-// short last block counts in full: it has fewer waves, but each takes as long), each at least
+// short last block counts in full: it has fewer waves, but each multiplies 64 rows), each at least
 // one and at most a.max_parts.  Lane i of a wave holds block i.
 struct LseShare { int block, part, parts, tiles; };      // block < 0: a workgroup without work
 __device__ inline LseShare lse_share(const ProbeArgs& a, int nrb, int j) {
@@ -192,9 +192,14 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
   __syncthreads();
   using lds_u32x4 = __attribute__((address_space(3))) const u32x4;
   u32x4 qf[2][T::NKC];
+  // (a row past the last probe has logits of 0 and starts with a reference: without one its terms of
+  // a whole tile would be infinite and the wave would evaluate every such tile twice: 32 heads over 8
+  // of 128 channels, 16384 tokens, 40 probes, bf16: 63.9 -> 55.2 us, 64 probes 54.4)
+  float m[2];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
     const int i = rh * 64 + rb * 32 + r;
+    m[rb] = spos[i] < 0 ? 0.f : -INFINITY;
     last[rb] = spos[i] < 0 ? -1 : spos[i] - 4 * kh;
 #pragma unroll
     for (int kc = 0; kc < T::NKC; ++kc) qf[rb][kc] = *reinterpret_cast<lds_u32x4*>(ks_lds + T::slot(i, 2 * kc + kh));
@@ -214,7 +219,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
     pfirst[rb] = pos_at(base);
     plast[rb] = rb0 + base < a.P ? pos_at(min(base + 31, nvalid - 1)) : -1;
   }
-  float m[2] = {-INFINITY, -INFINITY}, z[2] = {0.f, 0.f};
+  float z[2] = {0.f, 0.f};
   const uint32_t abase = ks_lds + T::slot(ch * 32 + r, kh);
 
   for (int t = t_begin; t < t_end; ++t) {
