@@ -54,9 +54,11 @@ struct ProbeArgs {
 };
 
 // Two 32x32 results of one row of operands in LDS (row: the address of its chunk kh; chunk
-// 2 kc + kh sits at slot (2 kc + kh) ^ swz, one exclusive or away) and two in registers.  An
+// 2 kc + kh sits at slot (2 kc + kh) ^ swz, one exclusive or away: on the address itself, so the
+// tiles start at a multiple of a row's size, kTileAlign) and two in registers.  An
 // operand is requested two steps ahead: left to itself the compiler, short of registers, waits
 // for each in front of the instructions that use it.
+constexpr int kTileAlign = 512;                // the longest row
 template <int DT, int NKC>
 __device__ inline void product_pair(v16f (&acc)[2], uint32_t row, const u32x4 (&f)[2][NKC]) {
   using lds_u32x4 = __attribute__((address_space(3))) const u32x4;
@@ -125,7 +127,8 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
   using T = Tile<DT, D>;
   constexpr int TILE_B = kLseCols * T::ROWB;
   constexpr int NI = kLseCols / T::RPI / 4;     // transfers per wave and K tile
-  __shared__ __align__(16) uint8_t Ks[2][TILE_B];
+  __shared__ __align__(kTileAlign) uint8_t Ks[2][TILE_B];
+  static_assert(__alignof__(Ks) % T::ROWB == 0 && TILE_B % T::ROWB == 0, "product_pair forms addresses by exclusive or");
   __shared__ int spos[kLseRows];
   __shared__ float sm[2][kLseRows], sz[2][kLseRows];
 
@@ -337,7 +340,8 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   constexpr int QT = 64;                        // probe rows per tile
   constexpr int TILE_B = QT * T::ROWB;
   constexpr int NI = QT / T::RPI / 4;           // transfers per wave and tile
-  __shared__ __align__(16) uint8_t Qs[2][TILE_B];
+  __shared__ __align__(kTileAlign) uint8_t Qs[2][TILE_B];
+  static_assert(__alignof__(Qs) % T::ROWB == 0 && TILE_B % T::ROWB == 0, "product_pair forms addresses by exclusive or");
   __shared__ __align__(16) int spos[3][QT];     // positions, rows of q and log-sum-exps of three tiles
   __shared__ __align__(16) int srow[3][QT];
   __shared__ __align__(16) float slse[3][QT];
