@@ -863,11 +863,11 @@ constexpr int kPackTokens = 4;         // keys: tokens of a thread
 
 // Keys (ROW layout, channelwise): a thread per 8 channels of kPackTokens tokens.
 template <int DT, int BITS>
-__device__ inline void pack_keys(const QPArgs& a, int sub, int wg, int b) {
+__device__ inline void pack_keys(const QPArgs& a, int sub, int wg, int b, int first_quad) {
   constexpr int RAW = DT == ZC_F32 ? 2 : 1, ESZ = DT == ZC_F32 ? 4 : 2;
   const int n = a.n[sub];
   const uint32_t i = (uint32_t)wg * blockDim.x + threadIdx.x, quad = i / (uint32_t)a.NV;
-  const int t0 = (int)quad * kPackTokens, w = (int)(i - quad * a.NV) * 8, h = w / a.D, c = w - h * a.D;
+  const int t0 = (first_quad + (int)quad) * kPackTokens, w = (int)(i - quad * a.NV) * 8, h = w / a.D, c = w - h * a.D;
   if (t0 >= n) return;
   const int32_t* idx = a.idx[sub] + (int64_t)b * n;
   const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
@@ -904,26 +904,32 @@ __device__ inline void pack_keys(const QPArgs& a, int sub, int wg, int b) {
   }
 }
 
-// grid.x: workgroups of the keys' subsets, then word groups of the values' (a count of 0: no such tensor).
+// What a launch of k_pack_kv packs: workgroups of the keys' subsets, then word groups of the values'
+// (a count of 0: no such tensor); where it does not start at a subset's first token, from which
+// group of kPackTokens tokens or word group on.
+struct PackRange { int wgs[4]; int first; };
+
+// grid (sum of r.wgs, B)
 template <int DT>
-__global__ __launch_bounds__(kPackThreads) void k_pack_kv(QPPair p, int4 wgs) {
+__global__ __launch_bounds__(kPackThreads) void k_pack_kv(QPPair p, PackRange r) {
   __shared__ float red[2][kPackThreads / 64][16];
   const int b = blockIdx.y;
   int wg = blockIdx.x;
-  const int nk = wgs.x + wgs.y;
+  const int nk = r.wgs[0] + r.wgs[1];
   if (wg < nk) {
     const QPArgs& a = p.t[0];
-    const int sub = wg >= wgs.x ? 1 : 0;
-    if (sub) wg -= wgs.x;
+    const int sub = wg >= r.wgs[0] ? 1 : 0;
+    if (sub) wg -= r.wgs[0];
     const int bits = a.bits[sub];
-    if (bits == 4) pack_keys<DT, 4>(a, sub, wg, b);
-    else if (bits == 2) pack_keys<DT, 2>(a, sub, wg, b);
-    else pack_keys<DT, 8>(a, sub, wg, b);
+    if (bits == 4) pack_keys<DT, 4>(a, sub, wg, b, r.first);
+    else if (bits == 2) pack_keys<DT, 2>(a, sub, wg, b, r.first);
+    else pack_keys<DT, 8>(a, sub, wg, b, r.first);
   } else {
     const QPArgs& a = p.t[1];
     wg -= nk;
-    const int sub = wg >= wgs.z ? 1 : 0;
-    if (sub) wg -= wgs.z;
+    const int sub = wg >= r.wgs[2] ? 1 : 0;
+    if (sub) wg -= r.wgs[2];
+    wg += r.first;
     const int bits = a.bits[sub];
     if (bits == 4) pack_values<DT, 4>(a, sub, wg, b, red);
     else if (bits == 2) pack_values<DT, 2>(a, sub, wg, b, red);
@@ -1156,18 +1162,32 @@ static bool pack_joint(const QPPair& p, const zc_packed* const* out, int tensors
 }
 static int launch_pack_kv(const QPPair& p, bool keys, bool values, int dtype, hipStream_t st) {
   const int threads = values ? (int)align_up64(p.t[1].W / kPackCpt, 64) : 256;
-  int4 wgs = make_int4(0, 0, 0, 0);
-  if (keys) {
-    wgs.x = (int)ceil_div64(ceil_div64(p.t[0].n[0], kPackTokens) * p.t[0].NV, threads);
-    wgs.y = (int)ceil_div64(ceil_div64(p.t[0].n[1], kPackTokens) * p.t[0].NV, threads);
+  const auto launch = [&](const PackRange& r) -> int {
+    const dim3 grid((unsigned)(r.wgs[0] + r.wgs[1] + r.wgs[2] + r.wgs[3]), (unsigned)p.t[0].B), block(threads);
+    if (dtype == ZC_F32) hipLaunchKernelGGL(k_pack_kv<ZC_F32>, grid, block, 0, st, p, r);
+    else if (dtype == ZC_F16) hipLaunchKernelGGL(k_pack_kv<ZC_F16>, grid, block, 0, st, p, r);
+    else hipLaunchKernelGGL(k_pack_kv<ZC_BF16>, grid, block, 0, st, p, r);
+    ZC_LAUNCH_CHECK();
+    return ZC_OK;
+  };
+  int64_t wgs[4] = {0, 0, 0, 0}, total = 0;
+  for (int sub = 0; sub < 2; ++sub) {
+    if (keys) wgs[sub] = ceil_div64(ceil_div64(p.t[0].n[sub], kPackTokens) * p.t[0].NV, threads);
+    if (values) wgs[2 + sub] = p.t[1].units[sub];
   }
-  if (values) { wgs.z = p.t[1].units[0]; wgs.w = p.t[1].units[1]; }
-  const dim3 grid((unsigned)(wgs.x + wgs.y + wgs.z + wgs.w), (unsigned)p.t[0].B), block(threads);
-  if (grid.x == 0) return ZC_OK;
-  if (dtype == ZC_F32) hipLaunchKernelGGL(k_pack_kv<ZC_F32>, grid, block, 0, st, p, wgs);
-  else if (dtype == ZC_F16) hipLaunchKernelGGL(k_pack_kv<ZC_F16>, grid, block, 0, st, p, wgs);
-  else hipLaunchKernelGGL(k_pack_kv<ZC_BF16>, grid, block, 0, st, p, wgs);
-  ZC_LAUNCH_CHECK();
+  for (int64_t n : wgs) total += n;
+  if (total == 0) return ZC_OK;
+  const int64_t most = 0xffffffffll / threads;             // (a grid counts the threads of a dimension in 32 bits)
+  if (total <= most) return launch({{(int)wgs[0], (int)wgs[1], (int)wgs[2], (int)wgs[3]}, 0});
+  // more than that: a subset at a time, in pieces of whole groups of tokens
+  const int64_t piece = most / p.t[0].NV * p.t[0].NV;
+  for (int seg = 0; seg < 4; ++seg)
+    for (int64_t done = 0; done < wgs[seg]; done += piece) {
+      PackRange r = {{0, 0, 0, 0}, (int)(seg < 2 ? done * threads / p.t[0].NV : done)};
+      r.wgs[seg] = (int)(wgs[seg] - done < piece ? wgs[seg] - done : piece);
+      const int rc = launch(r);
+      if (rc) return rc;
+    }
   return ZC_OK;
 }
 

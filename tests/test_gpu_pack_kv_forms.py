@@ -60,3 +60,42 @@ def test_every_pair_of_forms(first, second, B, H, D, k, n, dtype, bits):
                                          (20, 128, 2600, torch.float16)])
 def test_channelwise_rows_in_second_place(first, H, D, n, dtype):
     _compare(first, ("channel", zb.ZC_LAYOUT_ROW), 1, H, D, 40, n, dtype)
+
+
+def _largest(form, H, n, bits, dtype):
+    """`n` tokens of which a few are not zero, packed; the same few (and a zero one) in a call of their own."""
+    D = 64
+    x = torch.zeros(1, 1, n, D, dtype=dtype, device=DEV)
+    rows = [0, 5, n // 2, n - 4096, n - 4095, n - 1]
+    for r in rows:
+        x[0, 0, r] = torch.arange(D, device=DEV) - 9 * (r % 3)
+    rows.append(1)
+    few = torch.cat([x[:, :, r:r + 1] for r in rows], 2)
+    none = torch.empty(1, 0, dtype=torch.int32, device=DEV)
+    out = []
+    for t in (x, few):
+        p = zb.PackedTensor(1, H, D, 0, t.shape[2], 8, bits, *form, max_chunks=1, device=DEV)
+        zb.zc_quantize_pack(t.expand(1, H, -1, D), none, torch.arange(t.shape[2], dtype=torch.int32, device=DEV)[None], p)
+        out.append(p)
+    assert torch.equal(out[0].pos_lo[0, rows].cpu(), torch.tensor(rows, dtype=torch.int32))
+    return rows, out
+
+
+def test_values_of_more_threads_than_a_launch_counts():
+    """A word group of four 8-bit codes takes a wave of k_pack_kv, so that 2^28 tokens reach 2^32 threads."""
+    rows, (many, few) = _largest(("cst", zb.ZC_LAYOUT_TGROUP), 1, (1 << 28) + 4096, 8, torch.float16)
+
+    def codes(p, slot):                               # blocks of 16 slots, 4 words of 64 channels, 4 slots a word
+        return (p.codes_lo.view(torch.int32).view(-1, 4, 64)[slot // 16, slot % 16 // 4] >> (8 * (slot % 4))) & 0xff
+    for i, r in enumerate(rows):
+        assert torch.equal(many.tok_scale_lo[0, r], few.tok_scale_lo[0, i]) and torch.equal(many.tok_zero_lo[0, r], few.tok_zero_lo[0, i]), r
+        assert torch.equal(codes(many, r), codes(few, i)), r
+
+
+def test_keys_of_more_threads_than_a_launch_counts():
+    """Four tokens of 8192 channels take 1024 threads, so that 2^24 tokens reach 2^32 (all heads read one)."""
+    rows, (many, few) = _largest(("channel", zb.ZC_LAYOUT_ROW), 128, (1 << 24) + 4096, 2, torch.bfloat16)
+    assert torch.equal(many.chan_scale, few.chan_scale) and torch.equal(many.chan_zero, few.chan_zero)
+    a, b = many.codes_lo.view(128, -1, 16), few.codes_lo.view(128, -1, 16)
+    for i, r in enumerate(rows):
+        assert torch.equal(a[:, r], b[:, i]), r
