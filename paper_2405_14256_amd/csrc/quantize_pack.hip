@@ -753,7 +753,10 @@ __global__ __launch_bounds__(MAXT) void k_quant_pack(QPArgs a) {
 // a rolled loop: 1 to 4 KB, and twice the waves.  us per joint call (column sweep included), before ->
 // here: 100 tokens of 8 heads of 128 channels, bf16: 12.1 -> 9.4; 1000: 13.2 -> 10.3; 4096: 16.3 -> 14.9;
 // 32768: 70.3 -> 57.4; 2 x 32768 of 16 heads, fp16: 260 -> 253; 4 x 16384 of them, fp32: 452 -> 427.
-// (fp32 rows of 1280 and 1536 channels lose: one prompt of 4096 tokens 28.7 -> 30.7, 30.5 -> 31.7.)  Keys
+// In fp32, workgroups of five and six waves (1088 to 1536 channels) need five waves a SIMD, so 96
+// registers, for three or four of them a CU: 4 x 4096 tokens of 1280 channels 60.6 -> 60.5 (63.8 with
+// four a SIMD), of 1536 68.6 -> 69.0; one prompt 28.8 -> 27.4 and 30.6 -> 30.3; but values alone of 4 x 4096
+// tokens of 1536 channels lose 2 to 4 % (42.7 -> 43.4, at 8 and 4 bits 44.2 -> 46.0).  Keys
 // alone, which need no more than their own rows, come here at any width: 2 x 9000 tokens of 40 heads with
 // their values 210 -> 193.  Values wider than a workgroup takes go through quant_units.
 constexpr int kPackThreads = 512, kPackCpt = 4;     // values: most threads of a workgroup, channels of a thread
@@ -794,8 +797,8 @@ __device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, fl
   // bookkeeping of the group's tokens by lanes 0 .. E - 1 of the first wave
   const int my_rel = rel_of(lane < E ? lane : 0);
   const bool mine = tid < E && my_rel < n;
-  const int64_t my_o = (int64_t)b * a.cap[sub] + a.begin[sub] + my_rel;
-  if (mine && a.pos[sub]) a.pos[sub][my_o] = (int32_t)(idx[my_rel] + a.pos_offset);
+  const int64_t o0 = (int64_t)b * a.cap[sub] + a.begin[sub];
+  if (mine && a.pos[sub]) (a.pos[sub] + o0)[my_rel] = (int32_t)(idx[my_rel] + a.pos_offset);
 
   // ranges: (min, -max) of TBAT tokens at a time over the wave, all of the group over the waves
 #pragma unroll
@@ -831,8 +834,8 @@ __device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, fl
     z[q] = -rintf(refined_ratio(tmin, QMAX, R, y));   // tie-exact: a whole row depends on it
     si[q] = QMAX * y;
     if (mine && (lane >> 3) == q) {                // (lane e < E: batch e / 8; with fewer than 8 tokens, batch 0)
-      a.tok_scale[sub][my_o] = R * (1.f / QMAX);
-      a.tok_zero[sub][my_o] = z[q];
+      (a.tok_scale[sub] + o0)[my_rel] = R * (1.f / QMAX);
+      (a.tok_zero[sub] + o0)[my_rel] = z[q];
     }
   }
   if (!valid) return;                                // (a row is whole heads of 64 or 128 channels: lanes 0..7, read below, stay or go together)
@@ -854,8 +857,12 @@ __device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, fl
 #pragma unroll
       for (int i = 0; i < kPackCpt; ++i) words[i] |= (uint32_t)acc[i] << (BITS * (q * TBAT + g * FPG));
     }
+  int w1 = threadIdx.x;                              // (the channel again, not held in registers meanwhile)
+  asm volatile("" : "+v"(w1));
+  w1 *= kPackCpt;
+  const int h1 = w1 >> (a.D == 128 ? 7 : 6), c1 = w1 & (a.D - 1);
   const int64_t gblk = a.begin[sub] / TB + blk, nblk = a.cap[sub] / TB;
-  uint32_t* dst = reinterpret_cast<uint32_t*>(a.codes[sub]) + ((((int64_t)b * a.H + h) * nblk + gblk) * 4 + kg) * a.D + c;
+  uint32_t* dst = reinterpret_cast<uint32_t*>(a.codes[sub]) + ((((int64_t)b * a.H + h1) * nblk + gblk) * 4 + kg) * a.D + c1;
   *reinterpret_cast<uint4*>(dst) = make_uint4(words[0], words[1], words[2], words[3]);
 }
 
@@ -911,7 +918,7 @@ struct PackRange { int wgs[4]; int first; };
 
 // grid (sum of r.wgs, B)
 template <int DT>
-__global__ __launch_bounds__(kPackThreads) void k_pack_kv(QPPair p, PackRange r) {
+__global__ __launch_bounds__(kPackThreads, 5) void k_pack_kv(QPPair p, PackRange r) {
   __shared__ float red[2][kPackThreads / 64][16];
   const int b = blockIdx.y;
   int wg = blockIdx.x;
