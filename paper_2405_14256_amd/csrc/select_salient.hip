@@ -4,8 +4,8 @@
 // key and how many tokens equal to it are taken (lowest indices first); one
 // ordered compaction pass then writes both index lists in ascending order.
 // Rows of up to 16384 tokens are kept in registers (k_select_small), of up to
-// 34816 in LDS (k_select_cached); longer rows are re-read from memory by every
-// pass (k_select_stream).
+// 34816, and many rows of more than 4096, in LDS (k_select_cached); longer rows
+// are re-read from memory by every pass (k_select_stream).
 #include <type_traits>
 
 #include "zc_common.hpp"
@@ -352,17 +352,29 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
 // ---- rows of up to kSelSmallMax tokens: keys in registers ------------------------------------
 // Nothing here is bound by memory or arithmetic: a row is one workgroup's chain of barriers, LDS
 // round trips and instruction fetches (code is cold at every launch, about half a microsecond a
-// KB).  So the kernel is short (1.8 KB for 256 tokens, 3.7 for 4096) and a workgroup no larger
+// KB).  So the kernel is short (1.8 KB for 256 tokens, 5 for 4096, of which rows without many keys
+// in one digit execute 3.7) and a workgroup no larger
 // than its row: up to four keys a thread (8 and 16 where 1024 threads need them) in coalesced
 // loads (a wave's run is 64 KPT consecutive tokens, lane l holds tokens 64 u + l of it), digits
 // that give a thread two bins, so that one pass usually leaves few enough candidates for a
 // bisection with ballots, and the positions in both lists from ballots, stored as they are.
-// us per launch, k_select_cached -> here, k = 0.4 L: 100 tokens 6.7 -> 3.3; 1000: 7.0 -> 4.0; 2048:
-// 7.5 -> 4.4; 4096: 8.6 -> 5.5; 8192: 10.5 -> 7.3; 16384: 14.5 -> 12.7.  At 32768 tokens 32 keys a
-// thread are 20 KB of code: 21.9 against 20.3, so the longer rows stay there.
+// us per launch, k_select_cached -> here, k = 0.4 L: 100 tokens 6.7 -> 3.3; 1000: 6.9 -> 4.0; 2048:
+// 7.4 -> 4.5; 4096: 8.5 -> 5.6; 8192: 10.4 -> 7.4; 16384: 14.3 -> 12.5; with nine tenths of the scores
+// equal 4096: 9.3 -> 5.1; 16384: 16.2 -> 11.6.  At 32768 tokens 32 keys a thread are 20 KB of code: 21.9
+// against 20.3, so the longer rows stay there.  So do rows of more than 4096 tokens once there are
+// more of them than the chip runs at a time and the threads are not full: of more than 8192 from 257
+// rows on, while two workgroups of k_select_cached share a CU's LDS (512 rows of 9000: 17.6 against
+// 21.9, of 15600: 24.8 and 28.5, but of 15900: 34.2 and 29.1; 256 rows of 12000: 14.3 and 12.6); of fewer
+// from 769 on (4096 of 6000: 89 and 97; 1024: 26.1 and 27.1; 768 of 5000: 21.2 and 20.0).
 
-constexpr int kSelSmallMax = 16384;            // four keys a thread, 1024 threads
+constexpr int kSelSmallMax = 16384;            // 16 keys a thread, 1024 threads
+constexpr int kSelPairMax = 15616;             // tokens of which k_select_cached fits a CU twice
+static bool select_small(int64_t B, int64_t L) {
+  if (L <= 4096) return true;
+  return L <= kSelSmallMax && !(L <= kSelPairMax && B > (L > 8192 ? 256 : 768));
+}
 constexpr int kKthMax = 256;                   // candidates of the bisection, at most
+constexpr int kSharedDigits = 7;               // lanes of 64 that may share a digit with the lane before them
 
 // The need-th largest of a wave's keys, N a lane, that agree in every bit at and above `lo` with
 // `prefix`; unused places hold 0 (below every probed threshold).  Returns the key; `need` becomes
@@ -373,7 +385,7 @@ __device__ inline uint32_t kth_of_wave(const uint32_t (&c)[N], uint32_t prefix, 
   auto count_ge = [&](uint32_t v) {
     int n = 0;
 #pragma unroll
-    for (int u = 0; u < N; ++u) n += __popcll(__ballot(c[u] >= v));
+    for (int u = 0; u < N; ++u) n += __builtin_popcountll(__builtin_amdgcn_ballot_w64(c[u] >= v));
     return n;
   };
 #pragma unroll 1
@@ -400,18 +412,58 @@ __device__ inline int lanes_below(uint64_t mask) {      // set bits below this l
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0));
 }
 
+// One more in hist[digit] for every key of a wave that matches the prefix.  Adds of a wave to one
+// word go one after the other, and a row may hold one value thousands of times (columns that no
+// probe sees) or many keys that share a digit.  SHARED: where lanes next to each other share one
+// (looked for in their first keys only), the wave's keys of that digit are counted by ballots and
+// added at once.  Nine tenths of equal scores, together with skipping the bits that all candidates
+// share: 4096 tokens 14.0 -> 5.1 us, 16384 46.4 -> 11.6; the look costs 0.1 us (4096 tokens 5.5 -> 5.6).
+template <bool SHARED, int KPT>
+__device__ inline void count_digits(int* hist, const uint32_t (&key)[KPT], int lane, uint32_t prefix, uint32_t above, int lo, uint32_t dmask) {
+  const int mine = (int)((key[0] >> lo) & dmask);
+  uint64_t shared = 0;
+  if constexpr (SHARED) {
+    const uint64_t in = __builtin_amdgcn_ballot_w64((key[0] & above) == prefix);
+    const int left = __builtin_amdgcn_update_dpp(-1, mine, 0x111, 0xF, 0xF, false);            // row_shr:1
+    shared = __builtin_amdgcn_ballot_w64(left == mine) & in & in << 1;
+  }
+  if (__builtin_expect(__builtin_popcountll(shared) <= kSharedDigits, 1)) {
+#pragma unroll
+    for (int u = 0; u < KPT; ++u)
+      if ((key[u] & above) == prefix) atomicAdd(&hist[(key[u] >> lo) & dmask], 1);
+    return;
+  }
+  // (the two digits found first: of others there are few each)
+  const int one = __builtin_amdgcn_readlane(mine, __builtin_ctzll(shared));
+  shared &= ~__builtin_amdgcn_ballot_w64(mine == one);
+  const int two = shared ? __builtin_amdgcn_readlane(mine, __builtin_ctzll(shared)) : -2;
+  int n1 = 0, n2 = 0;
+#pragma unroll
+  for (int u = 0; u < KPT; ++u) {
+    const int d = (key[u] & above) == prefix ? (int)((key[u] >> lo) & dmask) : -1;
+    n1 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(d == one));
+    n2 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(d == two));
+    if (d >= 0 && d != one && d != two) atomicAdd(&hist[d], 1);
+  }
+  if (lane == 0) {
+    atomicAdd(&hist[one], n1);
+    if (two >= 0) atomicAdd(&hist[two], n2);
+  }
+}
+
 // One wave (THREADS == 64): no LDS, no barrier, the bisection over all keys.
 template <int THREADS, int KPT>
 __global__ __launch_bounds__(THREADS) void k_select_small(
     const float* __restrict__ scores, int L, int k, int32_t* __restrict__ salient,
     int32_t* __restrict__ regular, uint8_t* __restrict__ mask) {
   constexpr bool ONE_WAVE = THREADS == 64;
+  constexpr bool MANY = THREADS > 256;           // (in four waves the adds are few: that code would cost more than they do)
   constexpr int NWAVE = THREADS / 64, RUN = 64 * KPT;
   constexpr int BINS = 2 * THREADS, DIGIT = __builtin_ctz(BINS);    // two bins a thread
-  __shared__ int hist[ONE_WAVE ? 1 : BINS];
+  __shared__ __align__(16) int hist[ONE_WAVE ? 1 : BINS];
   __shared__ uint32_t cand[ONE_WAVE ? 1 : kKthMax];
   __shared__ int s_wave[NWAVE], s_bin, s_need, s_cnt, s_ncand;
-  __shared__ uint32_t s_diff[NWAVE];
+  __shared__ uint32_t s_diff[NWAVE], s_same[NWAVE];
 
   const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63;
   const int wave = ONE_WAVE ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -437,7 +489,7 @@ __global__ __launch_bounds__(THREADS) void k_select_small(
     diff = wave_or(diff);
     if constexpr (!ONE_WAVE) {
       if (lane == 0) s_diff[wave] = diff;
-      for (int i = tid; i < BINS; i += THREADS) hist[i] = 0;
+      reinterpret_cast<int2*>(hist)[tid] = make_int2(0, 0);
       if (tid == 0) s_ncand = 0;
       __syncthreads();
       diff = wave_or(s_diff[lane & (NWAVE - 1)]);
@@ -449,13 +501,30 @@ __global__ __launch_bounds__(THREADS) void k_select_small(
     } else {
       int in_bin = L;
 #pragma unroll 1
-      while (lo > 0 && in_bin > kKthMax) {
+      for (bool first = true; lo > 0 && in_bin > kKthMax; first = false) {
+        if (MANY && __builtin_expect(!first, 0)) {
+          // Many keys in one digit: equal ones, or close ones beside one far away.  The bits that all of
+          // them share are decided.
+          uint32_t ones = 0u, zeros = 0u;
+          const uint32_t above = 0xffffffffu << lo;            // (lo < 32 after a pass)
+#pragma unroll
+          for (int u = 0; u < KPT; ++u)
+            if ((key[u] & above) == thr) { ones |= key[u]; zeros |= ~key[u]; }
+          ones = wave_or(ones);
+          zeros = wave_or(zeros);
+          if (lane == 0) { s_diff[wave] = ones; s_same[wave] = zeros; }
+          __syncthreads();
+          ones = wave_or(s_diff[lane & (NWAVE - 1)]);
+          zeros = wave_or(s_same[lane & (NWAVE - 1)]);
+          const uint32_t differ = ones & zeros & ~above;
+          lo = differ ? 32 - __clz(differ) : 0;
+          thr = ones & (0xffffffffu << lo);
+          if (lo == 0) break;
+        }
         const int top = lo;
         lo = max(top - DIGIT, 0);
-        const uint64_t pre = (uint64_t)thr >> top;             // (top may be 32)
-#pragma unroll
-        for (int u = 0; u < KPT; ++u)
-          if (i0 + 64 * u < L && ((uint64_t)key[u] >> top) == pre) atomicAdd(&hist[(key[u] >> lo) & ((1u << (top - lo)) - 1u)], 1);
+        // (a pad's key of 0 lies below every number's; it matches a prefix of zeros and adds to digit 0)
+        count_digits<MANY>(hist, key, lane, thr, top >= 32 ? 0u : 0xffffffffu << top, lo, (1u << (top - lo)) - 1u);
         __syncthreads();
         // keys above each bin: thread t owns bins BINS - 1 - 2 t and the one below it
         const int2 h = reinterpret_cast<const int2*>(hist)[BINS / 2 - 1 - tid];
@@ -481,7 +550,7 @@ __global__ __launch_bounds__(THREADS) void k_select_small(
       if (lo > 0) {                                            // the keys of the bin: candidates of the bisection
 #pragma unroll
         for (int u = 0; u < KPT; ++u)
-          if (i0 + 64 * u < L && (key[u] >> lo) == (thr >> lo)) cand[atomicAdd(&s_ncand, 1)] = key[u];
+          if ((key[u] & 0xffffffffu << lo) == thr) cand[atomicAdd(&s_ncand, 1)] = key[u];
         __syncthreads();
         // (by every wave for itself: no barrier)
         if (in_bin <= 64) {
@@ -500,13 +569,14 @@ __global__ __launch_bounds__(THREADS) void k_select_small(
   // ---- positions in both lists --------------------------------------------------------------
   uint64_t gt[KPT], eq[KPT];
   int ngt = 0, neq = 0;
+  asm volatile("" : "+s"(L));                                  // (or the comparisons with it are kept from the start on)
 #pragma unroll
   for (int u = 0; u < KPT; ++u) {
     const bool valid = i0 + 64 * u < L;
-    gt[u] = __ballot(valid && key[u] > thr);
-    eq[u] = __ballot(valid && key[u] == thr);
-    ngt += __popcll(gt[u]);
-    neq += __popcll(eq[u]);
+    gt[u] = __builtin_amdgcn_ballot_w64(valid && key[u] > thr);
+    eq[u] = __builtin_amdgcn_ballot_w64(valid && key[u] == thr);
+    ngt += __builtin_popcountll(gt[u]);
+    neq += __builtin_popcountll(eq[u]);
   }
   int run_gt = 0, run_eq = 0;                                  // salient candidates before this wave's run
   if constexpr (!ONE_WAVE) {
@@ -529,14 +599,12 @@ __global__ __launch_bounds__(THREADS) void k_select_small(
       *dst = i;
       if (mask) mask[(int64_t)b * L + i] = is_sal ? 1 : 0;
     }
-    run_gt += __popcll(gt[u]);
-    run_eq += __popcll(eq[u]);
+    run_gt += __builtin_popcountll(gt[u]);
+    run_eq += __builtin_popcountll(eq[u]);
   }
 }
 
-// Rows too long for LDS: every pass reads the scores from memory.  (Keeping a thread's keys
-// in registers instead, with every loop unrolled, was slower at every size - 17 us against
-// 10 us for a row of 4096: the straight-line code is fetched cold at every launch.)
+// Rows too long for LDS: every pass reads the scores from memory.
 __global__ __launch_bounds__(kSelThreads) void k_select_stream(
     const float* __restrict__ scores, int L, int k, int32_t* __restrict__ salient,
     int32_t* __restrict__ regular, uint8_t* __restrict__ mask) {
@@ -651,7 +719,7 @@ extern "C" int zc_select_salient(const float* scores, int64_t B, int64_t L, int6
   if ((reinterpret_cast<uintptr_t>(scores) & 3) || (reinterpret_cast<uintptr_t>(salient_idx) & 3) ||
       (reinterpret_cast<uintptr_t>(regular_idx) & 3))
     return ZC_ERR_INVALID_ARG;
-  if (L <= zc::kSelSmallMax) {
+  if (zc::select_small(B, L)) {
     const auto launch = [&](auto kernel, unsigned threads) {
       hipLaunchKernelGGL(kernel, dim3((unsigned)B), dim3(threads), 0, (hipStream_t)stream, scores, (int)L, (int)k, salient_idx, regular_idx, mask);
     };

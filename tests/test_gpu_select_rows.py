@@ -37,3 +37,34 @@ def test_select_rows(L):
             m = np.zeros(L, np.uint8)
             m[s_o] = 1
             assert np.array_equal(mask[b].cpu().numpy(), m), (L, k, b)
+
+
+def _check(x, k):
+    from paper_2405_14256_amd import binding as zb
+    sal, reg = zb.zc_select_salient(x, k)
+    first = torch.sort(x, dim=1, descending=True, stable=True).indices            # equal scores: lower index first
+    assert torch.equal(sal.long(), first[:, :k].sort(dim=1).values) and torch.equal(reg.long(), first[:, k:].sort(dim=1).values)
+
+
+@pytest.mark.parametrize("L", [700, 1500, 3001, 5000, 12001, 16383])
+def test_select_rows_of_few_values(L):
+    """Rows in which most keys share a digit: one or two values, values of either sign (no bit is shared:
+    pads look like keys of the lowest digit), close values beside one far away, and almost only -inf."""
+    g = torch.Generator(device="cuda").manual_seed(L)
+    u, v = torch.rand(2, L, generator=g, device="cuda"), torch.randn(L, generator=g, device="cuda")
+    lowest = torch.finfo(torch.float32).min
+    rows = [torch.where(u[0] < 0.9, torch.zeros_like(v), v.exp()), torch.where(u[0] < 0.45, torch.zeros_like(v), torch.where(u[0] < 0.9, torch.ones_like(v), v)),
+            torch.where(u[0] < 0.9, -torch.ones_like(v), torch.ones_like(v)), v, 1.0 + 1e-5 * u[1], torch.where(u[0] < 0.97, torch.full_like(v, float("-inf")), v),
+            torch.where(u[0] < 0.5, torch.full_like(v, float("-inf")), torch.full_like(v, lowest)), torch.where(u[0] < 0.97, torch.full_like(v, float("inf")), v)]
+    rows[4][L // 2] = 1e9
+    x = torch.stack(rows)
+    for k in (1, 37, L // 20, L // 3, L // 2, L - L // 20, L - 1):
+        _check(x, k)
+
+
+@pytest.mark.parametrize("B,L", [(257, 8193), (257, 15616), (257, 15617), (769, 4097), (769, 8192), (256, 9000)])
+def test_select_many_rows(B, L):
+    g = torch.Generator(device="cuda").manual_seed(B)
+    x = torch.randn(B, L, generator=g, device="cuda").exp()
+    x[::3] = (x[::3] * 8).floor()
+    _check(x, L // 3)
