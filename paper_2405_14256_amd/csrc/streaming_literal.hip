@@ -455,7 +455,7 @@ __device__ inline void store8(void* base, int64_t off, const float (&v)[8]) {
 //   ROW     a thread per 8 channels of a slot (1 to 2 words), or of four consecutive slots where that
 //           still fills the chip: the channel parameters are 64 bytes a thread, four times what it
 //           stores per slot (4 x 4096 tokens of 40 heads of 128 channels, fp16: 45.9 -> 32.7 us; 2 x 32768
-//           of 8 heads, bf16: 44.6 -> 25.9; but one prompt of 1000 of them 4.0 -> 4.7);
+//           of 8 heads, bf16: 44.6 -> 25.9; but one prompt of 1000 of them 3.4 -> 4.0);
 //   TGROUP  a thread per 8 channels and field group of a word group (the same bit field range of 8
 //           words: the codes of 4 consecutive slots), one store per slot; a thread per whole word
 //           group (8 to 16 stores) left half the chip without one.
@@ -497,7 +497,17 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
       store8<DT>(a.out, off, v);
     }
   };
-  if (row_layout) {
+  if (row_layout && RS == 1) {
+    const int64_t slot = (int64_t)sg.begin + r, ti = (int64_t)b * cap + slot;
+    const uint8_t* src = a.codes[sub] + (bh * cap + slot) * (a.D * BITS / 8) + c * BITS / 8;
+    uint32_t w[2] = {0u, 0u};
+    if constexpr (BITS == 8) { const uint2 t = *reinterpret_cast<const uint2*>(src); w[0] = t.x; w[1] = t.y; }
+    else if constexpr (BITS == 4) w[0] = *reinterpret_cast<const uint32_t*>(src);
+    else w[0] = *reinterpret_cast<const uint16_t*>(src);
+    float ts = 1.f, tz = 0.f;
+    if (a.tokwise) { ts = a.tok_scale[sub][ti]; tz = a.tok_zero[sub][ti]; }
+    expand(a.pos[sub][ti], ts, tz, [&](int i) { return (w[i / E] >> (BITS * (i % E))) & CM; });
+  } else if (row_layout) {
     constexpr int NW = BITS == 8 ? 2 : 1;
     const int rel = r * RS, n = min(RS, sg.len - rel);
     const int64_t slot = (int64_t)sg.begin + rel, ti = (int64_t)b * cap + slot;
@@ -508,7 +518,7 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
     float ts[RS], tz[RS];
 #pragma unroll
     for (int e = 0; e < RS; ++e) {           // (a slot past the end repeats the last one and is not stored)
-      const int at = RS == 1 ? 0 : min(e, n - 1);
+      const int at = min(e, n - 1);
       if constexpr (BITS == 8) { const uint2 t = *reinterpret_cast<const uint2*>(src + at * rowb); w[e][0] = t.x; w[e][1] = t.y; }
       else if constexpr (BITS == 4) w[e][0] = *reinterpret_cast<const uint32_t*>(src + at * rowb);
       else w[e][0] = *reinterpret_cast<const uint16_t*>(src + at * rowb);
@@ -518,7 +528,7 @@ __device__ inline void dequantize_segment(const DequantArgs& a, const DequantSeg
     }
 #pragma unroll
     for (int e = 0; e < RS; ++e)
-      if (RS == 1 || e < n) expand(pos[e], ts[e], tz[e], [&](int i) { return (w[e][i / E] >> (BITS * (i % E))) & CM; });
+      if (e < n) expand(pos[e], ts[e], tz[e], [&](int i) { return (w[e][i / E] >> (BITS * (i % E))) & CM; });
   } else {
     // field group jf of word group kg of block blk: slots rel .. rel + 3 (inside the block, so inside the arena)
     const int jf = r % (E / 4), kg = (r / (E / 4)) & 3, blk = r / E;
@@ -726,7 +736,7 @@ extern "C" int zc_dequantize_cache(const zc_packed* p, const zc_tensor4* out, vo
     rc = flush();                // (the chunk before this one)
     if (rc) return rc;
     const int32_t* row = p->chunk_table_host + 4 * chunk;
-    row_slots = ((int64_t)row[1] + row[3]) * p->H * vpr * p->B >= kDqFourSlots ? 4 : 1;
+    row_slots = p->layout == ZC_LAYOUT_ROW && ((int64_t)row[1] + row[3]) * p->H * vpr * p->B >= kDqFourSlots ? 4 : 1;
     for (int which = 0; which < 2; ++which) {
       for (int64_t done = 0, len = row[2 * which + 1]; done < len; done += most) {
         const int64_t part = len - done < most ? len - done : most;
