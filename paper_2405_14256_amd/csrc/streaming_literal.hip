@@ -411,7 +411,10 @@ struct DequantArgs {
   DequantSeg seg[kDqSegs];
 };
 
-constexpr int64_t kDqFourSlots = 1 << 20;   // vectors of a launch from which a thread takes four slots
+// Vectors of a ROW launch from which a thread takes four slots (us with one and four: 2^18 of bf16 4.0 and
+// 4.3, 3/8 of 2^20 4.5 and 4.7, 2^19 5.25 and 5.05, 3/4 6.8 and 5.8, 2^20 7.9 and 6.6; fp16 5.5 and 5.45, 7.0
+// and 6.2, 8.2 and 7.1 from 2^19 on; fp32, bound by its stores, within 2 % of each other from 2^18 on).
+constexpr int64_t kDqFourSlots = 1 << 19;
 
 // s x in fp16, rounded once: multiplication and conversion are one instruction (v_fma_mixlo_f16,
 // from the contraction; the empty assembly keeps two of them from being combined into products

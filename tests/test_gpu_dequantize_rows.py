@@ -1,4 +1,4 @@
-"""zc_dequantize_cache of ROW layout around the size from which a thread expands four slots: ragged
+"""zc_dequantize_cache of ROW layout around the size from which a thread expands four slots, and above it: ragged
 last quads, every bit width, token scales and none, exactly the unpacked cache in token order."""
 import pytest
 import torch
@@ -22,3 +22,9 @@ def test_dequantize_row_quads(L, bits_hi, bits_lo, k, scheme, dtype):
     out = torch.zeros_like(x)
     zb.zc_dequantize_cache(p, out)
     assert torch.equal(out, _unpacked(p, L, dtype))
+
+
+@pytest.mark.parametrize("L", [2047, 2048, 2051])                 # 2^19 vectors at 2048 tokens
+@pytest.mark.parametrize("bits_hi,bits_lo,k,scheme,dtype", [(4, 2, 821, "channel", torch.float16), (8, 4, 1023, "token", torch.bfloat16)])
+def test_dequantize_row_quads_from_half_that_size(L, bits_hi, bits_lo, k, scheme, dtype):
+    test_dequantize_row_quads(L, bits_hi, bits_lo, k, scheme, dtype)
