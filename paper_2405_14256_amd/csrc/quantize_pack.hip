@@ -17,8 +17,8 @@
 //                       reduces and quantizes batch i: per-token range by DPP wave
 //                       reduction (+ LDS across the team's waves) for the tokenwise
 //                       schemes, tie-exact x (2^k-1) / R for the zero points and the
-//                       channelwise codes, round half to even, + z, clamp, pack along
-//                       channels (ROW layout) or along tokens (TGROUP layout).
+//                       plain tokenwise and channelwise codes, round half to even, + z,
+//                       clamp, pack along channels (ROW layout) or along tokens (TGROUP).
 // Every sweep reads 16 bytes per lane with consecutive lanes on consecutive
 // addresses of a (token, head) row; the second sweep of a tensor that fits the
 // 256 MB Infinity Cache does not reach HBM.
@@ -589,39 +589,33 @@ __device__ inline void quant_units(const QPArgs& a, int sub, int g0, int ng, int
       else return rintf(refined_div(xv * QMAX, rt[t], yt[t])) + zt[t];      // x * qmax is exact
     };
     if (!vvalid) return;                             // (a row is whole heads of 64 or 128 channels: lanes 0..7, read below, stay or go together)
+    if constexpr (LAYOUT == ZC_LAYOUT_ROW) {
+      static_assert(TOKWISE, "channelwise codes in ROW layout are k_pack_kv's");
 #pragma unroll
-    for (int t = 0; t < TBAT; ++t) {
-      // Eq. 5: round(x / s) first, then + z, then clip
-      float code[8];
+      for (int t = 0; t < TBAT; ++t) {
+        // Eq. 5: round(x / s) first, then + z, then clip
+        float code[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        float qv;
-        if constexpr (TOKWISE) qv = tok_code(xs[t][i], t);
-        else if constexpr (DT == ZC_F32) qv = rintf(refined_ratio(xs[t][i], QMAX, p2[i], p0[i])) + p1[i];
-        else qv = rintf(refined_div(xs[t][i] * QMAX, p2[i], p0[i])) + p1[i];   // x * qmax is exact
-        code[i] = __builtin_amdgcn_fmed3f(qv, 0.f, QMAX);
-      }
-      if constexpr (LAYOUT == ZC_LAYOUT_ROW) {
-        if (tv[t]) {
-          // the 8 codes of this token, 16 bits at a time
-          constexpr int NG = 8 / FPG;                // 16-bit groups of the 8 codes (>= 1: bits >= 2)
-          uint32_t half[NG];
+        for (int i = 0; i < 8; ++i) code[i] = __builtin_amdgcn_fmed3f(tok_code(xs[t][i], t), 0.f, QMAX);
+        if (!tv[t]) continue;
+        // the 8 codes of this token, 16 bits at a time
+        constexpr int NG = 8 / FPG;                  // 16-bit groups of the 8 codes (>= 1: bits >= 2)
+        uint32_t half[NG];
 #pragma unroll
-          for (int g = 0; g < NG; ++g) {
-            float acc = 0.f;
+        for (int g = 0; g < NG; ++g) {
+          float acc = 0.f;
 #pragma unroll
-            for (int f = 0; f < FPG; ++f) acc = fmaf(code[g * FPG + f], (float)(1 << (BITS * f)), acc);
-            half[g] = (uint32_t)acc;
-          }
-          const int64_t slot = a.begin[sub] + blk * TB + slot_of(q, t);
-          uint8_t* row = a.codes[sub] + (((int64_t)b * a.H + h) * a.cap[sub] + slot) * (a.D * BITS / 8) + c * BITS / 8;
-          if constexpr (BITS == 8) {
-            *reinterpret_cast<uint2*>(row) = make_uint2(half[0] | (half[1] << 16), half[2] | (half[3] << 16));
-          } else if constexpr (BITS == 4) {
-            *reinterpret_cast<uint32_t*>(row) = half[0] | (half[1] << 16);
-          } else {
-            *reinterpret_cast<uint16_t*>(row) = (uint16_t)half[0];
-          }
+          for (int f = 0; f < FPG; ++f) acc = fmaf(code[g * FPG + f], (float)(1 << (BITS * f)), acc);
+          half[g] = (uint32_t)acc;
+        }
+        const int64_t slot = a.begin[sub] + blk * TB + slot_of(q, t);
+        uint8_t* row = a.codes[sub] + (((int64_t)b * a.H + h) * a.cap[sub] + slot) * (a.D * BITS / 8) + c * BITS / 8;
+        if constexpr (BITS == 8) {
+          *reinterpret_cast<uint2*>(row) = make_uint2(half[0] | (half[1] << 16), half[2] | (half[3] << 16));
+        } else if constexpr (BITS == 4) {
+          *reinterpret_cast<uint32_t*>(row) = half[0] | (half[1] << 16);
+        } else {
+          *reinterpret_cast<uint16_t*>(row) = (uint16_t)half[0];
         }
       }
     }
@@ -1062,6 +1056,7 @@ static int qp_prepare(const zc_tensor4* x, const int32_t* salient_idx, int64_t k
 // above 512 channels where that also takes workgroups of 1024 threads (8192 tokens of 8 heads, 8
 // prompts: 134 against 146 us; of 16 heads, 2 prompts: 73 and 95; but of 2 heads, 8 prompts, 61 and
 // 50, and 4096 tokens of 8 heads, 8 prompts, in workgroups of 512: 69 and 66).
+constexpr int64_t kCUs = 256;
 struct ColPlan { int threads, split; };
 static ColPlan col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int dtype, bool joint_pack) {
   const int64_t n = a[0].n[0] > a[0].n[1] ? a[0].n[0] : a[0].n[1], rows = kColRows(dtype);
@@ -1073,7 +1068,8 @@ static ColPlan col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int
   while (v > 2 && n > rows * th / v) v /= 2;
   if (n > rows * th / v) th = 1024;
   const bool strips = tensors == 2 && dtype != ZC_F32 && v == 2 && a[0].NV > (th == 1024 ? 64 : 256);
-  const bool fits = n <= rows * th / v && !(joint_pack && wgs(v) < (dtype == ZC_F32 ? 256 : 257)) && !strips;
+  const bool few_wgs = dtype == ZC_F32 ? wgs(v) < kCUs : wgs(v) <= kCUs;
+  const bool fits = n <= rows * th / v && !(joint_pack && few_wgs) && !strips;
   bool any = false;
   for (int t = 0; t < tensors; ++t) {
     a[t].resident = fits && out[t]->scheme == ZC_SCHEME_CHANNEL && out[t]->layout == ZC_LAYOUT_ROW;
