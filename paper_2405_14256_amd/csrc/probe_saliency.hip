@@ -252,7 +252,9 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
           float tmax = -INFINITY;
 #pragma unroll
           for (int v = 0; v < 16; ++v) tmax = fmaxf(tmax, acc_row(v, 0) <= seen ? acc[rb][v] : -INFINITY);
-          const float m_new = fmaxf(m[rb], tmax * a.scale_log2);
+          // (no visible column: as it was, whatever a negative scale makes of -inf; with one the reference is the smallest
+          // visible logit, which serves as well.  Scaling every term instead takes 12 more registers.)
+          const float m_new = seen >= 0 ? fmaxf(m[rb], tmax * a.scale_log2) : m[rb];
           if (m_new > -INFINITY) z[rb] *= __builtin_amdgcn_exp2f(m[rb] - m_new);
           m[rb] = m_new;
           base = m_new > -INFINITY ? m_new : 0.f;            // (every visible logit -inf so far: their terms are 0, not exp2(-inf + inf))

@@ -90,3 +90,20 @@ def test_scores_with_logits_of_minus_infinity(d, dtype, P):
     assert bool((got[:, hidden] == 0).all()) and bool(torch.isfinite(got).all())
     rel = ((got.double() - want).abs() / want.clamp(min=1e-30))[:, ~hidden].max().item()
     assert rel < 3e-5, rel                       # (the bound of the test above)
+
+
+# A row's reference is a maximum of scaled logits: columns a lane does not see stay out of it for a negative scale too.
+@pytest.mark.parametrize("case", [1, 2, 3, 4])
+def test_scores_of_a_negative_scale(case):
+    B, Hq, Hkv, d, L, dtype, probes = CASES[case]
+    g = torch.Generator(device=DEV).manual_seed(case)
+    pos = probes(L).to(DEV)
+    q = torch.randn(B, Hq, pos.numel(), d, generator=g, device=DEV).to(dtype)
+    k = torch.randn(B, Hkv, L, d, generator=g, device=DEV).to(dtype)
+    rows = torch.arange(pos.numel(), dtype=torch.int32, device=DEV)
+    got = zb.zc_probe_saliency(q, k, pos.int(), probe_rows=rows, sm_scale=-0.25)
+    want = reference(q.double() * (-0.25 * d ** 0.5), k, rows.long(), pos)
+    # (the bound of the first test: a logit's terms sum up to 0.25 * 128 * E|q k| = 21, below its 2^8; a matrix
+    # instruction drops bits of products without regard to sign, so the scores of -q and 0.25 are not the same bits)
+    rel = ((got.double() - want).abs() / want.clamp(min=1e-30)).max().item()
+    assert rel < 3e-5, rel
