@@ -96,23 +96,33 @@ constexpr int kLseCols = 64;                   // columns per K tile of sweep 1
 struct LseShare { int block, part, parts, tiles; };      // block < 0: a workgroup without work
 __device__ inline LseShare lse_share(const ProbeArgs& a, int nrb, int j) {
   LseShare s;
+  const auto tiles_of = [&](int block) { return min(a.probe_pos[min(a.P, (block + 1) * kLseRows) - 1], a.Lk - 1) / kLseCols + 1; };
+  if (nrb == 1 || a.head_wgs == nrb) {                   // nothing to share
+    s.block = nrb == 1 ? 0 : j;
+    s.part = j - s.block;
+    s.parts = nrb == 1 ? a.head_wgs : 1;
+    s.tiles = __builtin_amdgcn_readfirstlane(tiles_of(s.block));
+    return s;
+  }
   if (nrb > 64) {                                        // (more than 8192 probe rows: even ranges)
     s.parts = min(a.head_wgs / nrb, a.max_parts);
     s.block = j / s.parts; s.part = j % s.parts;
     if (s.block >= nrb) s.block = -1;
-    else s.tiles = min(a.probe_pos[min(a.P, (s.block + 1) * kLseRows) - 1], a.Lk - 1) / kLseCols + 1;
+    else s.tiles = tiles_of(s.block);
     return s;
   }
-  const int i = threadIdx.x & 63, rows = a.P - i * kLseRows;
-  int tiles = 0;
-  if (rows > 0) tiles = min(a.probe_pos[min(a.P, (i + 1) * kLseRows) - 1], a.Lk - 1) / kLseCols + 1;
-  // one each, what is left by the cumulated tiles (the last block's: all of them, whatever the rounding)
+  const int i = threadIdx.x & 63, tiles = i < nrb ? tiles_of(i) : 0;
+  // One each, what is left by the cumulated tiles (the last block's: all of them, whatever the rounding).
+  // Cut to whole numbers with a quarter added: without it two blocks that see 31 and 32 columns share
+  // four workgroups as one and three (16 x 32 heads over 8 of 128 channels, the last 200 of 2000 rows, fp32:
+  // 1585 us, 1110 with two each), with a half one more goes too early where shares grow (2 x 900 rows,
+  // all of them probes, bf16: 43.5 and 45.8).  The best of 64 tried shares cost 0.4 us more than it gave.
   const int upto = wave_inclusive_sum(tiles), from = upto - tiles, total = __builtin_amdgcn_readlane(upto, 63);
   const float rate = (float)(a.head_wgs - nrb) / (float)total;
-  const int s1 = upto == total ? a.head_wgs - nrb : min((int)((float)upto * rate), a.head_wgs - nrb), s0 = (int)((float)from * rate);
-  const int share = rows > 0 ? min(1 + max(s1 - s0, 0), a.max_parts) : 0;
+  const auto shared_by = [&](int t) { return t == total ? a.head_wgs - nrb : min((int)fmaf((float)t, rate, 0.25f), a.head_wgs - nrb); };
+  const int share = i < nrb ? min(1 + max(shared_by(upto) - shared_by(from), 0), a.max_parts) : 0;
   const int end = wave_inclusive_sum(share);
-  const uint64_t past = __ballot(j < end);               // the blocks that end behind workgroup j
+  const uint64_t past = __builtin_amdgcn_ballot_w64(j < end);   // the blocks that end behind workgroup j
   s.block = past ? __builtin_ctzll(past) : -1;
   if (s.block < 0) return s;
   s.parts = __builtin_amdgcn_readlane(share, s.block);

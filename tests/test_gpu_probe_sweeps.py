@@ -40,6 +40,7 @@ CASES = [
     (3, 5, 5, 128, 191, torch.float16, lambda L: torch.arange(60, 190)),
     (1, 1, 1, 64, 8400, torch.bfloat16, lambda L: torch.arange(L - 8300, L)),
     (1, 40, 40, 64, 130, torch.bfloat16, lambda L: torch.arange(L)),
+    (1, 16, 4, 128, 2000, torch.float32, lambda L: torch.arange(L - 200, L)),        # two blocks that see all but the same columns
 ]
 
 
