@@ -671,17 +671,23 @@ using namespace zc;
 // Workgroups of a head in sweep 1, which its row blocks share (k_probe_lse): enough to fill the
 // chip once (four fit a CU); and, however many blocks there are, four to a block on average
 // where the columns give each at least 16 tiles, so that the last workgroups to finish are short.
-static int64_t probe_head_wgs(int64_t B, int64_t Hq, int64_t P, int64_t Lk, int max_parts) {
-  const int64_t nrb = ceil_div64(P, kLseRows), fill = 1024 / (B * Hq);
-  int64_t even = ceil_div64(Lk, kLseCols) / 16;
-  if (even > 4) even = 4;
+static int64_t probe_head_wgs(int64_t B, int64_t Hq, int64_t P, int64_t Lk, int max_parts, bool fp32) {
+  const int64_t heads = B * Hq, nrb = ceil_div64(P, kLseRows), tiles = ceil_div64(Lk, kLseCols);
+  // A second range of a single block is a launch more, to merge them: none for prompts of up to four tiles
+  // (fp32, where a tile takes twice as long: from 128 heads on), and above 384 heads none to fill the chip.
+  // 24 x 8 heads of 64 channels, 130 tokens, 13 probes, one range and three, bf16: 10.0 and 12.7 us, fp32: 15.8
+  // and 18.8 (4 x 8 heads, the last 13: 18.0 and 15.6); 64 x 8 heads, 300 tokens, 30 probes, one and two: 22.7
+  // and 25.2; 16 x 32 heads over 8 of 128, 500 tokens, 50 probes: 26.7 and 28.6.
+  if (nrb == 1 && tiles <= 4 && (!fp32 || heads >= 128)) return 1;
+  const int64_t fill = nrb == 1 && heads > 384 ? 1 : 1024 / heads;
+  const int64_t even = tiles / 16 < 4 ? tiles / 16 : 4;
   int64_t n = fill > even * nrb ? fill : even * nrb;
   if (nrb > 64) n = n / nrb * nrb;
   n = n < nrb ? nrb : (n > nrb * max_parts ? nrb * max_parts : n);
   // A single block: no more ranges than whole tiles make.  The ranges without one cost their start and
   // a place on a CU, which in fp32, bound by the matrix cores of the CUs that got two, is half the
   // time: 32 heads over 8 of 128 channels, 1000 tokens, 64 probes: 34.4 us with 12 ranges, 26.7 with 8.
-  if (nrb == 1) n = ceil_div64(ceil_div64(Lk, kLseCols), ceil_div64(ceil_div64(Lk, kLseCols), n));
+  if (nrb == 1) n = ceil_div64(tiles, ceil_div64(tiles, n));
   return n;
 }
 // Whether few probe rows are served by one launch: a block of 32, and no more bytes per
@@ -745,7 +751,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.lse2 = reinterpret_cast<float*>(ws);
   a.lse_part = reinterpret_cast<float2*>(reinterpret_cast<uint8_t*>(ws) + lse2_bytes);
   a.max_parts = (int)(fit < kMaxProbeParts ? fit : kMaxProbeParts) & ~1;
-  const int64_t head_wgs = probe_head_wgs(q->B, q->H, P, k->L, a.max_parts);
+  const int64_t head_wgs = probe_head_wgs(q->B, q->H, P, k->L, a.max_parts, q->dtype == ZC_F32);
   a.head_wgs = (int)head_wgs;
   if (head_wgs * q->H * q->B > 0x7fffffff || (int64_t)ceil_div64(k->L, 128) * q->H * q->B > 0x7fffffff)
     return ZC_ERR_UNSUPPORTED;

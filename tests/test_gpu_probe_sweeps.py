@@ -41,6 +41,8 @@ CASES = [
     (1, 1, 1, 64, 8400, torch.bfloat16, lambda L: torch.arange(L - 8300, L)),
     (1, 40, 40, 64, 130, torch.bfloat16, lambda L: torch.arange(L)),
     (1, 16, 4, 128, 2000, torch.float32, lambda L: torch.arange(L - 200, L)),        # two blocks that see all but the same columns
+    (2, 200, 200, 64, 300, torch.bfloat16, lambda L: spread(L, 30)),                  # a single block of more heads than get two ranges
+    (1, 130, 130, 64, 200, torch.float32, lambda L: spread(L, 33)),                   # of four tiles at most: one range
 ]
 
 
