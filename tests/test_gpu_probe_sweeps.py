@@ -43,6 +43,7 @@ CASES = [
     (1, 16, 4, 128, 2000, torch.float32, lambda L: torch.arange(L - 200, L)),        # two blocks that see all but the same columns
     (2, 200, 200, 64, 300, torch.bfloat16, lambda L: spread(L, 30)),                  # a single block of more heads than get two ranges
     (1, 130, 130, 64, 200, torch.float32, lambda L: spread(L, 33)),                   # of four tiles at most: one range
+    (1, 8, 2, 128, 4500, torch.float32, lambda L: spread(L, 450)),                    # whole rounds of workgroups a CU
 ]
 
 
