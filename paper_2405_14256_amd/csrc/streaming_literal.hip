@@ -413,8 +413,10 @@ struct DequantArgs {
 
 // Vectors of a ROW launch from which a thread takes four slots (us with one and four: 2^18 of bf16 4.0 and
 // 4.3, 3/8 of 2^20 4.5 and 4.7, 2^19 5.25 and 5.05, 3/4 6.8 and 5.8, 2^20 7.9 and 6.6; fp16 5.5 and 5.45, 7.0
-// and 6.2, 8.2 and 7.1 from 2^19 on; fp32, bound by its stores, within 2 % of each other from 2^18 on).
-constexpr int64_t kDqFourSlots = 1 << 19;
+// and 6.2, 8.2 and 7.1 from 2^19 on; fp32, bound by its stores: 8 prompts of 4096 tokens of a head of 128 channels
+// (2^19) 7.25 and 7.65, 32 of 200 of 8 heads 9.5 and 9.9, 4 of 4096 of 4 heads (2^20) 10.9 and 11.0, one of 5000 of
+// 17 heads (1.3 x 2^20) 12.9 and 12.7, of 8000 of 16 heads (2^21) 16.7 and 16.2).
+static constexpr int64_t four_slots_from(int dtype) { return dtype == ZC_F32 ? 5 << 18 : 1 << 19; }
 
 // s x in fp16, rounded once: multiplication and conversion are one instruction (v_fma_mixlo_f16,
 // from the contraction; the empty assembly keeps two of them from being combined into products
@@ -739,7 +741,7 @@ extern "C" int zc_dequantize_cache(const zc_packed* p, const zc_tensor4* out, vo
     rc = flush();                // (the chunk before this one)
     if (rc) return rc;
     const int32_t* row = p->chunk_table_host + 4 * chunk;
-    row_slots = p->layout == ZC_LAYOUT_ROW && ((int64_t)row[1] + row[3]) * p->H * vpr * p->B >= kDqFourSlots ? 4 : 1;
+    row_slots = p->layout == ZC_LAYOUT_ROW && ((int64_t)row[1] + row[3]) * p->H * vpr * p->B >= four_slots_from(out->dtype) ? 4 : 1;
     for (int which = 0; which < 2; ++which) {
       for (int64_t done = 0, len = row[2 * which + 1]; done < len; done += most) {
         const int64_t part = len - done < most ? len - done : most;
