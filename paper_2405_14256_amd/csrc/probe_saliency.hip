@@ -686,8 +686,8 @@ static int64_t probe_head_wgs(int64_t B, int64_t Hq, int64_t P, int64_t Lk, int 
   if (fp32) {
     // Bound by the matrix cores of the CUs with one workgroup more than others: whole rounds of two a CU, or
     // of one, unless that takes more than a third of the ranges away.  16 heads over 4 of 128 channels, 5000 tokens,
-    // 500 probes, 768 and 512 workgroups: 163 and 137 us; 8 heads over 2, 9000 and 900: 250 and 216; 4 heads, 20000
-    // and 1000, 384 and 256: 324 and 301; but 36 x 8 heads, 700 tokens, 70 probes, 864 and 288: 138 and 157.
+    // 500 probes, 768 and 512 workgroups: 163 and 137 us; 8 heads over 2, 9000 and 900: 250 and 215; 4 heads, 20000
+    // and 1000, 384 and 256: 327 and 303; but 36 x 8 heads, 700 tokens, 70 probes, 864 and 288: 138 and 157.
     const int64_t unit = n * heads >= 512 ? 512 : 256, whole = n * heads / unit * unit / heads;
     if (3 * whole >= 2 * n) n = whole;
   }
