@@ -9,7 +9,8 @@
 //                   LDS (global -> LDS transfers, the next tile's in flight), logits come
 //                   out of the MFMA as D[column][row] so that every lane owns one probe row
 //                   and keeps its running (reference, sum) in two registers; writes the
-//                   pair per row and column range (k_probe_lse_merge joins the ranges).
+//                   pair per row and column range (sweep 2 joins the ranges of few probes,
+//                   k_probe_lse_merge those of others).
 //   k_probe_colsum  one workgroup per 128 key columns: K fragments stay in
 //                   registers, 64-row probe tiles stream through LDS with their
 //                   positions and log-sum-exps, logits come out as D[row][column] so
@@ -27,13 +28,19 @@
 // how the work falls on the CUs and by the waves' start: 32 heads of 128 channels over 8, 4096
 // tokens, 410 probe rows, bf16: 58.3 -> 44.1 us with operands brought in as whole rows, four
 // workgroups a CU and row blocks sharing workgroups by the columns they see (sweep 1 26 -> 24 us,
-// sweep 2 31.6 -> 19); 16384 tokens 390 -> 380.
+// sweep 2 31.6 -> 19); 16384 tokens 390 -> 380.  Then 43.3 -> 38.5 by keeping the waves of a full chip at the
+// same number of tiles to go (priority_by_tiles: 42.8 -> 39.6 in sweeps that a launch still joined), a mix of row
+// blocks on every CU, 32 rows a wave for a last block of at most 64, what the probes are looked up by in LDS
+// from one trip to memory, and sweep 2 joining the pairs of sweep 1; 16 x 40 heads, 4096 tokens: 645 -> 614;
+// 8 heads of 64 channels, 700 tokens: 13.7 -> 12.1; 16 x 16 heads of 128, 500 tokens, fp32: 78.7 -> 61.7.
 #include "mfma_tiles.hpp"
 
 namespace zc {
 
 constexpr int kProbeParts = 8;       // column ranges of a block of probe rows the workspace is sized for
 constexpr int kMaxProbeParts = 12;   // most (what else they need is borrowed from the per-head scores, which come later)
+
+constexpr int kProbeTable = 512;     // most probes whose positions, rows and log-sum-exps a workgroup keeps in LDS
 
 struct ProbeArgs {
   const void* q;
@@ -45,26 +52,37 @@ struct ProbeArgs {
   float scale_log2;
   const float* lse_in;   // natural log, [B, Hq, P]; null: use lse2
   float* lse2;           // [B, Hq, P] log-sum-exp in log2 units: sweep 1's result
-  float2* lse_part;      // [B, Hq, P, max_parts] (running maximum in log2 units, sum) of the column ranges
-  int max_parts;         // even: a row's pairs are read two at a time
+  float2* lse_part;      // [B, Hq, max_parts, P] (reference in log2 units, sum) of the column ranges
+  int max_parts;
+  int join;              // 1: sweep 2 joins a row's pairs itself (lse2 is not written); 0: k_probe_lse_merge does
   int head_wgs;          // workgroups of a head in sweep 1 (one per row block: no column ranges)
   float* per_head;       // [B, Hq, Lk]
+  // the waves of sweep 1 / sweep 2 are kept at about the same number of tiles to go from so many tiles / probe rows before
+  // their ends on (0: not at all)
+  int even1, even2;
   int small;             // 1: few probe rows, sweep 2 and the mean in one launch
   int normalize;         // 1: divide a column's sum by the number of probes that see it (Eq. 8); 0: Eq. 7
 };
 
-// Two 32x32 results of one row of operands in LDS (row: the address of its chunk kh; chunk
+// A copy the compiler knows nothing of: what is computed from it is computed where it is used, not
+// kept in a register across a loop.
+__device__ inline int opaque(int x) { asm volatile("" : "+v"(x)); return x; }
+
+// N 32x32 results of one row of operands in LDS (row: the address of its chunk kh; chunk
 // 2 kc + kh sits at slot (2 kc + kh) ^ swz, one exclusive or away: on the address itself, so the
-// tiles start at a multiple of a row's size, kTileAlign) and two in registers.  An
+// tiles start at a multiple of a row's size, kTileAlign) and N in registers.  An
 // operand is requested two steps ahead: left to itself the compiler, short of registers, waits
 // for each in front of the instructions that use it.
 constexpr int kTileAlign = 512;                // the longest row
-template <int DT, int NKC>
-__device__ inline void product_pair(v16f (&acc)[2], uint32_t row, const u32x4 (&f)[2][NKC]) {
+template <int DT, int N, int NKC>
+__device__ inline void products(v16f (&acc)[2], uint32_t row, const u32x4 (&f)[2][NKC]) {
   using lds_u32x4 = __attribute__((address_space(3))) const u32x4;
-  constexpr int kDsRead = 0x100, kMfma = 0x8, MPC = DT == ZC_F32 ? 8 : 2;     // matrix instructions of a step
+  constexpr int kDsRead = 0x100, kMfma = 0x8, MPC = DT == ZC_F32 ? 4 * N : N;     // matrix instructions of a step
+  row = (uint32_t)opaque((int)row);              // (or the addresses of two instances are formed in front of both)
 #pragma unroll
-  for (int i = 0; i < 16; ++i) { acc[0][i] = 0.f; acc[1][i] = 0.f; }
+  for (int n = 0; n < N; ++n)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[n][i] = 0.f;
   u32x4 a[2];
   a[0] = *reinterpret_cast<lds_u32x4*>(row);
   a[1] = *reinterpret_cast<lds_u32x4*>(row ^ 32);
@@ -72,8 +90,8 @@ __device__ inline void product_pair(v16f (&acc)[2], uint32_t row, const u32x4 (&
 #pragma unroll
   for (int kc = 0; kc < NKC; ++kc) {
     const u32x4 af = a[kc & 1];
-    mma_chunk<DT>(acc[0], af, f[0][kc]);
-    mma_chunk<DT>(acc[1], af, f[1][kc]);
+#pragma unroll
+    for (int n = 0; n < N; ++n) mma_chunk<DT>(acc[n], af, f[n][kc]);
     __builtin_amdgcn_sched_group_barrier(kMfma, MPC, 0);
     if (kc + 2 < NKC) {
       a[kc & 1] = *reinterpret_cast<lds_u32x4*>(row ^ ((kc + 2) << 5));
@@ -82,16 +100,48 @@ __device__ inline void product_pair(v16f (&acc)[2], uint32_t row, const u32x4 (&
   }
 }
 
-// A copy the compiler knows nothing of: what is computed from it is computed where it is used, not
-// kept in a register across a loop.
-__device__ inline int opaque(int x) { asm volatile("" : "+v"(x)); return x; }
+// The (reference, sum) pairs of a probe row's column ranges, and the log-sum-exp of all of them.
+struct RowPairs {
+  float2 v[kMaxProbeParts];
+  __device__ void load(const ProbeArgs& a, int64_t head, int row) {
+    const float2* src = a.lse_part + head * a.max_parts * a.P + row;
+#pragma unroll
+    for (int sp = 0; sp < kMaxProbeParts; ++sp)
+      if (sp < a.max_parts) v[sp] = src[(int64_t)sp * a.P];
+  }
+  __device__ float joined(const ProbeArgs& a) {
+    float M = -INFINITY;
+#pragma unroll
+    for (int sp = 0; sp < kMaxProbeParts; ++sp) {
+      if (sp >= a.max_parts) v[sp] = make_float2(-INFINITY, 0.f);
+      M = fmaxf(M, v[sp].x);
+    }
+    float Z = 0.f;
+#pragma unroll
+    for (int sp = 0; sp < kMaxProbeParts; ++sp)
+      Z += v[sp].x > -INFINITY ? v[sp].y * __builtin_amdgcn_exp2f(v[sp].x - M) : 0.f;
+    return M + log2f(Z);
+  }
+};
+
+// Waves with more tiles to go first: of equal waves a SIMD serves the oldest, so that the youngest is left with
+// most of its tiles when the others have ended, alone and waiting for each (32 heads, 4096 tokens, 410 probes:
+// the median wave of sweep 1 ended at 14.7 us, the last at 23.1).  Where all workgroups run at once: of several
+// rounds the ends should be spread, so that the starts of the next are (even_waves).
+constexpr int kEvenTiles = 5;                  // with so many to go a wave leaves the highest priority
+__device__ inline void priority_by_tiles(int left) {
+  if (left > kEvenTiles) __builtin_amdgcn_s_setprio(3);
+  else if (left >= 4) __builtin_amdgcn_s_setprio(2);
+  else if (left >= 2) __builtin_amdgcn_s_setprio(1);
+  else __builtin_amdgcn_s_setprio(0);
+}
 
 constexpr int kLseRows = 128;                  // probe rows per workgroup of sweep 1
 constexpr int kLseCols = 64;                   // columns per K tile of sweep 1
 
 // The row blocks of a head share its a.head_wgs workgroups in proportion to the column tiles their
 // rows can see (a block near the end of a prompt sees ten times those of one near its start; a
-// short last block counts in full: it has fewer waves, but each multiplies 64 rows), each at least
+// last block of at most 64 rows counts half: its waves multiply 32 rows each), each at least
 // one and at most a.max_parts.  Lane i of a wave holds block i.
 struct LseShare { int block, part, parts, tiles; };      // block < 0: a workgroup without work
 __device__ inline LseShare lse_share(const ProbeArgs& a, int nrb, int j) {
@@ -112,12 +162,13 @@ __device__ inline LseShare lse_share(const ProbeArgs& a, int nrb, int j) {
     return s;
   }
   const int i = threadIdx.x & 63, tiles = i < nrb ? tiles_of(i) : 0;
+  const int weight = a.P - i * kLseRows <= kLseRows / 2 ? (tiles + 1) / 2 : tiles;
   // One each, what is left by the cumulated tiles (the last block's: all of them, whatever the rounding).
   // Cut to whole numbers with a quarter added: without it two blocks that see 31 and 32 columns share
   // four workgroups as one and three (16 x 32 heads over 8 of 128 channels, the last 200 of 2000 rows, fp32:
   // 1585 us, 1110 with two each), with a half one more goes too early where shares grow (2 x 900 rows,
   // all of them probes, bf16: 43.5 and 45.8).  The best of 64 tried shares cost 0.4 us more than it gave.
-  const int upto = wave_inclusive_sum(tiles), from = upto - tiles, total = __builtin_amdgcn_readlane(upto, 63);
+  const int upto = wave_inclusive_sum(weight), from = upto - weight, total = __builtin_amdgcn_readlane(upto, 63);
   const float rate = (float)(a.head_wgs - nrb) / (float)total;
   const auto shared_by = [&](int t) { return t == total ? a.head_wgs - nrb : min((int)fmaf((float)t, rate, 0.25f), a.head_wgs - nrb); };
   const int share = i < nrb ? min(1 + max(shared_by(upto) - shared_by(from), 0), a.max_parts) : 0;
@@ -138,21 +189,25 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
   constexpr int TILE_B = kLseCols * T::ROWB;
   constexpr int NI = kLseCols / T::RPI / 4;     // transfers per wave and K tile
   __shared__ __align__(kTileAlign) uint8_t Ks[2][TILE_B];
-  static_assert(__alignof__(Ks) % T::ROWB == 0 && TILE_B % T::ROWB == 0, "product_pair forms addresses by exclusive or");
+  static_assert(__alignof__(Ks) % T::ROWB == 0 && TILE_B % T::ROWB == 0, "products forms addresses by exclusive or");
   __shared__ int spos[kLseRows];
   __shared__ float sm[2][kLseRows], sz[2][kLseRows];
 
   // logical order: workgroup of a head fastest, then query head, then batch
   const int nrb = ceil_div(a.P, kLseRows);
   int j = xcd_contiguous(blockIdx.x, gridDim.x);
-  const LseShare share = lse_share(a, nrb, j % a.head_wgs);
+  // An XCD deals its workgroups to 32 CUs in turn, so that a CU of a full chip would hold the same ranges of
+  // four heads, all of them near the end of the prompt or all of few rows: from one round of 32 to the next
+  // the heads begin a quarter further on.
+  const int head = j / a.head_wgs, turn = gridDim.x >= 768 && gridDim.x <= 1024 ? (head * a.head_wgs >> 5) * (min(a.head_wgs, 32) >> 2) : 0;
+  const LseShare share = lse_share(a, nrb, (j + turn) % a.head_wgs);
   if (share.block < 0) return;
-  j /= a.head_wgs;
+  j = head;
   const int rb0 = share.block * kLseRows;
   const int hq = j % a.Hq, b = j / a.Hq, hk = hq / a.G;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int rh = w >> 1, ch = w & 1;            // this wave: rows rh * 64 .. + 63, columns ch * 32 .. + 31 of a tile
+  const int rh = w >> 1, ch = w & 1;            // this wave: rows row0 .. + 63, columns ch * 32 .. + 31 of a tile
   const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)hq * a.q_sH) * T::EB;
   const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)hk * a.k_sH) * T::EB;
   const uint32_t k_rowb = (uint32_t)(a.k_sL * T::EB), q_rowb = (uint32_t)(a.q_sL * T::EB);
@@ -160,6 +215,8 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
   const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.Lq - 1) * q_rowb + T::ROWB, kBufFlags);
 
   const int nvalid = min(kLseRows, a.P - rb0);
+  const bool two = nvalid > kLseRows / 2;       // (of a block of at most 64 rows 32 a wave)
+  const int row0 = rh * (two ? 64 : 32);
   // this workgroup's share of the column tiles
   const int per = ceil_div(share.tiles, share.parts);
   const int t_begin = share.part * per, t_end = min(t_begin + per, share.tiles);
@@ -188,11 +245,9 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
   int last[2];                                   // last column a lane's row sees, less the lane's first in a tile (< 0: none)
   {
     int row[2 * NI];
+    const int32_t* rows = a.probe_rows ? a.probe_rows : a.probe_pos;
 #pragma unroll
-    for (int jj = 0; jj < 2 * NI; ++jj) {
-      const int p = min(rb0 + (w + 4 * jj) * T::RPI + lane / T::CPR, a.P - 1);
-      row[jj] = a.probe_rows ? a.probe_rows[p] : a.probe_pos[p];
-    }
+    for (int jj = 0; jj < 2 * NI; ++jj) row[jj] = rows[min(rb0 + (w + 4 * jj) * T::RPI + lane / T::CPR, a.P - 1)];
     const int my_pos = a.probe_pos[min(rb0 + (tid & (kLseRows - 1)), a.P - 1)];
 #pragma unroll
     for (int jj = 0; jj < 2 * NI; ++jj) {
@@ -211,7 +266,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
   float m[2];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
-    const int i = rh * 64 + rb * 32 + r;
+    const int i = row0 + rb * 32 + r;
     m[rb] = spos[i] < 0 ? 0.f : -INFINITY;
     last[rb] = spos[i] < 0 ? -1 : spos[i] - 4 * kh;
 #pragma unroll
@@ -223,26 +278,29 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
   // its last real row what is visible at all
   // (scalars: read from LDS they would each hold a register)
   const auto pos_at = [&](int i) { return __builtin_amdgcn_readfirstlane(spos[i]); };
-  const int pos_last = rb0 + rh * 64 < a.P ? pos_at(min(rh * 64 + 63, nvalid - 1)) : -1;
   // the same per 32-row block: its first row's position (-1: no row) and its last real row's
   int pfirst[2], plast[2];
 #pragma unroll
   for (int rb = 0; rb < 2; ++rb) {
-    const int base = rh * 64 + rb * 32;
+    const int base = row0 + rb * 32;
     pfirst[rb] = pos_at(base);
-    plast[rb] = rb0 + base < a.P ? pos_at(min(base + 31, nvalid - 1)) : -1;
+    plast[rb] = base < nvalid && (two || rb == 0) ? pos_at(min(base + 31, nvalid - 1)) : -1;
   }
+  const int pos_last = max(plast[0], plast[1]);
   float z[2] = {0.f, 0.f};
   const uint32_t abase = ks_lds + T::slot(ch * 32 + r, kh);
 
+  if (a.even1) priority_by_tiles(t_end - t_begin);
   for (int t = t_begin; t < t_end; ++t) {
     const int cur = (t - t_begin) & 1;
     wait_all_loads();    // this wave's transfers of tile t have landed ...
     __syncthreads();     // ... and everyone's; nobody still reads the other buffer
     if (t + 1 < t_end) issue(t + 1, cur ^ 1);
+    if (t_end - t <= a.even1) priority_by_tiles(t_end - t);
     if (t * kLseCols > pos_last) continue;       // nothing of this tile is visible to the wave's rows
     v16f acc[2];
-    product_pair<DT, T::NKC>(acc, abase + cur * TILE_B, qf);
+    if (two) products<DT, 2>(acc, abase + cur * TILE_B, qf);
+    else products<DT, 1>(acc, abase + cur * TILE_B, qf);
     __builtin_amdgcn_sched_barrier(0);           // (here and below: what follows would be moved up, into registers there are not)
     const int colb = t * kLseCols + ch * 32;     // this wave's 32 columns of the tile
 #pragma unroll
@@ -303,7 +361,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
     const float m0 = __uint_as_float(mh[0]), m1 = __uint_as_float(mh[1]), M = fmaxf(m0, m1);
     float Z = 0.f;
     if (M > -INFINITY) Z = __uint_as_float(zh[0]) * exp2f(m0 - M) + __uint_as_float(zh[1]) * exp2f(m1 - M);
-    if ((t1 & 32) == 0) { sm[ch][rh * 64 + rb * 32 + r1] = M; sz[ch][rh * 64 + rb * 32 + r1] = Z; }
+    if ((t1 & 32) == 0 && (two || rb == 0)) { sm[ch][row0 + rb * 32 + r1] = M; sz[ch][row0 + rb * 32 + r1] = Z; }
   }
   __syncthreads();
   if (t1 < kLseRows && rb0 + t1 < a.P) {
@@ -314,34 +372,24 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
     if (a.head_wgs == nrb) {
       a.lse2[row] = M + log2f(Z);
     } else {
-      float2* dst = a.lse_part + row * a.max_parts;
-      dst[share.part] = make_float2(M, Z);
+      float2* dst = a.lse_part + ((int64_t)b * a.Hq + hq) * a.max_parts * a.P + rb0 + t1;
+      dst[(int64_t)share.part * a.P] = make_float2(M, Z);
       if (share.part == share.parts - 1)                 // the ranges this block does not have
-        for (int p = share.parts; p < a.max_parts; ++p) dst[p] = make_float2(-INFINITY, 0.f);
+        for (int p = share.parts; p < a.max_parts; ++p) dst[(int64_t)p * a.P] = make_float2(-INFINITY, 0.f);
     }
   }
 }
 
-// Merges the (maximum, sum) pairs of a probe row's column ranges.
-__global__ void k_probe_lse_merge(const float2* __restrict__ part, float* __restrict__ lse2, int64_t rows, int max_parts) {
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= rows) return;
-  float4 v[kMaxProbeParts / 2];                          // two pairs each
-#pragma unroll
-  for (int sp = 0; sp < kMaxProbeParts / 2; ++sp) {
-    v[sp] = reinterpret_cast<const float4*>(part + i * max_parts)[min(sp, max_parts / 2 - 1)];
-    if (2 * sp >= max_parts) v[sp] = make_float4(-INFINITY, 0.f, -INFINITY, 0.f);
+// Merges the (reference, sum) pairs of the probe rows' column ranges, a thread per row of a head.
+// grid (ceil(P / 64), heads)
+__global__ __launch_bounds__(64) void k_probe_lse_merge(ProbeArgs a) {
+  const int row = blockIdx.x * 64 + threadIdx.x;
+  for (int64_t head = blockIdx.y; head < (int64_t)a.B * a.Hq; head += gridDim.y) {
+    if (row >= a.P) return;
+    RowPairs v;
+    v.load(a, head, row);
+    a.lse2[head * a.P + row] = v.joined(a);
   }
-  float M = -INFINITY;
-#pragma unroll
-  for (int sp = 0; sp < kMaxProbeParts / 2; ++sp) M = fmaxf(M, fmaxf(v[sp].x, v[sp].z));
-  float Z = 0.f;
-#pragma unroll
-  for (int sp = 0; sp < kMaxProbeParts / 2; ++sp) {
-    if (v[sp].x > -INFINITY) Z += v[sp].y * exp2f(v[sp].x - M);
-    if (v[sp].z > -INFINITY) Z += v[sp].w * exp2f(v[sp].z - M);
-  }
-  lse2[i] = M + log2f(Z);
 }
 
 // Four workgroups to a CU (128 registers, 37 KB of LDS) for rows of up to 256 bytes, so that four
@@ -353,11 +401,13 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   constexpr int TILE_B = QT * T::ROWB;
   constexpr int NI = QT / T::RPI / 4;           // transfers per wave and tile
   __shared__ __align__(kTileAlign) uint8_t Qs[2][TILE_B];
-  static_assert(__alignof__(Qs) % T::ROWB == 0 && TILE_B % T::ROWB == 0, "product_pair forms addresses by exclusive or");
-  __shared__ __align__(16) int spos[3][QT];     // positions, rows of q and log-sum-exps of three tiles
-  __shared__ __align__(16) int srow[3][QT];
-  __shared__ __align__(16) float slse[3][QT];
-  __shared__ float scol[2][128];
+  static_assert(__alignof__(Qs) % T::ROWB == 0 && TILE_B % T::ROWB == 0, "products forms addresses by exclusive or");
+  // positions (-1: no probe), offsets of their rows in q and log-sum-exps (log2 units) of the probes from pstart on: entry j at
+  // j modulo the table
+  __shared__ __align__(16) int spos[kProbeTable];
+  __shared__ __align__(16) int srow[kProbeTable];
+  __shared__ __align__(16) float slse[kProbeTable];
+  float (*scol)[128] = reinterpret_cast<float (*)[128]>(&Qs[0][0]);     // (in the place of the tiles, at the end)
   __shared__ int bins[128];                     // probes at each of this workgroup's columns
   __shared__ __align__(16) int before[4];       // probes in front of them, by wave
 
@@ -389,8 +439,11 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   // Meanwhile the K columns come through the two tile buffers (whole rows to a transfer, as in
   // sweep 1; columns past the end: zeros).
   const uint32_t qs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&Qs[0][0];
+  const bool table = a.P <= kProbeTable;
+  constexpr int NT = kProbeTable / 256;
+  int tpos[NT], trow[NT];
+  float tlse[NT];
   if (tid < 128) bins[tid] = 0;
-  __syncthreads();
   {
 #pragma unroll
     for (int jj = 0; jj < 2 * NI; ++jj) {
@@ -398,15 +451,38 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
       dma16<0>(qs_lds + (w + 4 * jj) * 1024, rs_k, col < a.Lk ? (int)((uint32_t)col * k_rowb) + (((lane % T::CPR) ^ T::swz(i)) << 4) : kOutOfRange, 0);
     }
     int n = 0;
-    for (int i0 = tid; i0 < a.P; i0 += 4 * 256) {
-      int pos[4];
+    const auto count = [&](bool real, int pos) {
+      n += real && pos < col0 ? 1 : 0;
+      if (real && (uint32_t)(pos - col0) < 128u) atomicAdd(&bins[pos - col0], 1);
+    };
+    if (table) {
+      // few probes: all that is to be looked up of them comes with the positions
+      RowPairs pairs[NT];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) pos[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_pos, (i0 + u * 256) * 4, 0, 0);
+      for (int u = 0; u < NT; ++u)
+        if (u * 256 < a.P) {
+          const int i = u * 256 + tid;
+          tpos[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_pos, i * 4, 0, 0);
+          trow[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_row, i * 4, 0, 0);
+          if (__builtin_expect(a.join, 0)) pairs[u].load(a, (int64_t)b * a.Hq + hq, min(i, a.P - 1));
+          else tlse[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_lse, i * 4, 0, 0));
+        }
+      __syncthreads();                           // (the bins are empty)
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        const bool real = i0 + u * 256 < a.P;
-        n += real && pos[u] < col0 ? 1 : 0;
-        if (real && (uint32_t)(pos[u] - col0) < 128u) atomicAdd(&bins[pos[u] - col0], 1);
+      for (int u = 0; u < NT; ++u)
+        if (u * 256 < a.P) {
+          count(u * 256 + tid < a.P, tpos[u]);
+          if (__builtin_expect(a.join, 0)) tlse[u] = pairs[u].joined(a);
+          else if (a.lse_in) tlse[u] *= kLog2e;  // an external log-sum-exp is in natural units
+        }
+    } else {
+      __syncthreads();
+      for (int i0 = tid; i0 < a.P; i0 += 4 * 256) {
+        int pos[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) pos[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_pos, (i0 + u * 256) * 4, 0, 0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) count(i0 + u * 256 < a.P, pos[u]);
       }
     }
     n = wave_inclusive_sum(n);
@@ -423,91 +499,125 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   const int pstart = __builtin_amdgcn_readfirstlane(before[0] + before[1] + before[2] + before[3]);
   float colsum[2] = {0.f, 0.f};
 
-  // Wave 0 brings what a tile of 64 probe rows is looked up by two tiles ahead (0 past the last
-  // probe: row 0 of q, which the mask drops); the tile itself goes global -> LDS directly one
+  // What a tile of 64 probe rows is looked up by: all of it is in LDS where the probes are few; otherwise one half of
+  // the table is filled while the tiles of the other are worked on, every wave a quarter of it.  (Past the
+  // last probe: row 0 of q, which a position of -1 masks.)  The tile itself goes global -> LDS directly one
   // ahead, every wave a quarter of its transfers.
-  const uint32_t spos_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&spos[0][0];
-  const uint32_t srow_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&srow[0][0];
-  const uint32_t slse_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)&slse[0][0];
-  auto look_up = [&](int pr, int slot) {
-    const int voff = (pr + (opaque(tid) & 63)) * 4;
-    dma4(spos_lds + slot * (QT * 4), rs_pos, voff, 0);
-    dma4(srow_lds + slot * (QT * 4), rs_row, voff, 0);
-    dma4(slse_lds + slot * (QT * 4), rs_lse, voff, 0);
+  const uint32_t spos_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&spos[0];
+  const uint32_t srow_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&srow[0];
+  const uint32_t slse_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) float*)&slse[0];
+  constexpr int kHalf = kProbeTable / 2;
+  static_assert(kHalf == 256 && kHalf == 4 * QT, "an entry a thread; four tiles");
+  auto fetch = [&](int entry) {                  // entries entry .. + kHalf - 1, this wave's 64 of them
+    const int voff = (pstart + entry + opaque(tid)) * 4;
+    const uint32_t to = ((entry & kHalf) + w * 64) * 4;
+    dma4(spos_lds + to, rs_pos, voff, 0);
+    dma4(srow_lds + to, rs_row, voff, 0);
+    dma4(slse_lds + to, rs_lse, voff, 0);
   };
-  const auto to_log2 = [&](int slot) { if (a.lse_in) slse[slot][opaque(tid) & 63] *= kLog2e; };     // an external log-sum-exp is in natural units
-  auto issue = [&](int slot, int buf) {
+  const auto fetched = [&](int entry) {          // when this wave's have landed
+    const int e = (entry & kHalf) + opaque(tid);
+    srow[e] = (int)((uint32_t)srow[e] * q_rowb);
+    if (a.lse_in) slse[e] *= kLog2e;             // an external log-sum-exp is in natural units
+    if (pstart + entry + opaque(tid) >= a.P) spos[e] = -1;
+  };
+  auto issue = [&](int at, int buf) {
+    int from[NI];                                // (read together: the transfers keep their order)
+#pragma unroll
+    for (int jj = 0; jj < NI; ++jj) from[jj] = srow[at + (w + 4 * jj) * T::RPI + lane / T::CPR];
 #pragma unroll
     for (int jj = 0; jj < NI; ++jj) {
       const int row = (w + 4 * jj) * T::RPI + lane / T::CPR;
-      dma16<0>(qs_lds + buf * TILE_B + (w + 4 * jj) * 1024, rs_q, opaque((int)((uint32_t)srow[slot][row] * q_rowb)) + (((lane % T::CPR) ^ T::swz(row)) << 4), 0);
+      dma16<0>(qs_lds + buf * TILE_B + (w + 4 * jj) * 1024, rs_q, opaque(from[jj]) + (((lane % T::CPR) ^ T::swz(row)) << 4), 0);
     }
   };
   if (pstart < a.P) {
-    if (w == 0) {
-      look_up(pstart, 0);
-      look_up(pstart + QT, 1);
+    if (table) {
+#pragma unroll
+      for (int u = 0; u < NT; ++u) {
+        const int at = u * 256 + tid - pstart;
+        if (u * 256 + tid < a.P && at >= 0) { spos[at] = tpos[u]; srow[at] = (int)((uint32_t)trow[u] * q_rowb); slse[at] = tlse[u]; }
+      }
+      const int at = a.P - pstart + tid;         // (to the end of the last tile)
+      if (tid < QT && at < kProbeTable) { spos[at] = -1; srow[at] = 0; slse[at] = 0.f; }
+    } else {
+      fetch(0);
+      fetch(kHalf);
       wait_all_loads();
-      to_log2(0);
+      fetched(0);
+      fetched(kHalf);
     }
     __syncthreads();
     issue(0, 0);
   }
   const uint32_t abase = qs_lds + T::slot(rbw * 32 + r, kh);
+  const int wcol0 = col0 + cbp * 64;             // this wave's columns: wcol0 .. + 63; of a tile, its rows rbw * 32 .. + 31
+  const int pend = a.P - rbw * 32;
 
-  int slot = 0, cur = 0;
+  if (a.even2) priority_by_tiles((a.P - pstart + QT - 1) / QT);
+  int at = 0, cur = 0;
+  int until = table ? 0x7fffffff : kHalf / QT;   // tiles to the next step of filling the table
+  bool ahead = false;                            // the newest loads are those of a fetch
   for (int pr = pstart; pr < a.P; pr += QT) {
-    wait_all_loads();    // this wave's transfers of the tile have landed ...
-    __syncthreads();     // ... and everyone's; nobody still reads the other buffer
-    const int next = slot == 2 ? 0 : slot + 1;
-    if (pr + QT < a.P) {
-      issue(next, cur ^ 1);
-      if (w == 0) {
-        to_log2(next);
-        look_up(pr + 2 * QT, next == 2 ? 0 : next + 1);
+    if (ahead) __builtin_amdgcn_s_waitcnt(0x0F73);       // vmcnt(3)
+    else wait_all_loads();   // this wave's transfers of the tile have landed ...
+    __syncthreads();         // ... and everyone's; nobody still reads the other buffer
+    ahead = false;
+    const int next = (at + QT) & (kProbeTable - 1);
+    if (pr + QT < a.P) issue(next, cur ^ 1);
+    if (a.P - pr <= a.even2) priority_by_tiles((a.P - pr + QT - 1) / QT);
+    if (until == 0) {                            // the first tile of a half: the other one is free; the third: it is full
+      const int entry = pr - pstart;
+      if (entry & (2 * QT)) fetched(entry - 2 * QT + kHalf);
+      else {
+        fetch(entry + kHalf);
+        ahead = true;
       }
+      until = 2;
     }
-    v16f acc[2];
-    product_pair<DT, T::NKC>(acc, abase + cur * TILE_B, kf);
-    __builtin_amdgcn_sched_barrier(0);           // (what follows would be moved up, into registers there are not)
-    // a tile of 64 real rows whose first position is past this workgroup's last
-    // column needs no mask
-    const bool tile_full = pr + QT <= a.P && col0 + 127 <= __builtin_amdgcn_readfirstlane(spos[slot][0]);
-    const float4* rl4 = reinterpret_cast<const float4*>(&slse[slot][rbw * 32 + 4 * kh]);     // rows 8 g + 4 kh ..
-    if (tile_full) {
+    --until;
+    if (pr < pend) {                             // (no probe in the wave's rows of a last tile)
+      v16f acc[2];
+      products<DT, 2>(acc, abase + cur * TILE_B, kf);
+      __builtin_amdgcn_sched_barrier(0);         // (what follows would be moved up, into registers there are not)
+      const float4* rl4 = reinterpret_cast<const float4*>(&slse[at + rbw * 32 + 4 * kh]);     // rows 8 g + 4 kh ..
+      // 32 real rows whose first position is past the wave's last column need no mask
+      if (pr + 32 <= pend && wcol0 + 63 <= __builtin_amdgcn_readfirstlane(spos[at + rbw * 32])) {
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 t = rl4[2 * g];
-        const float rl[4] = {t.x, t.y, t.z, t.w};
+        for (int g = 0; g < 4; ++g) {
+          const float4 t = rl4[2 * g];
+          const float rl[4] = {t.x, t.y, t.z, t.w};
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
+          for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-          for (int v = 0; v < 4; ++v) colsum[cb] += __builtin_amdgcn_exp2f(fmaf(acc[cb][4 * g + v], a.scale_log2, -rl[v]));
-      }
-    } else {
-      const int4* ps4 = reinterpret_cast<const int4*>(&spos[slot][rbw * 32 + 4 * kh]);
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const float4 t = rl4[2 * g];
-        const int4 s = ps4[2 * g];
-        const float rl[4] = {t.x, t.y, t.z, t.w};
-        const int row0 = pr + rbw * 32 + 4 * kh + 8 * g;
-        const int ps[4] = {s.x, s.y, s.z, s.w};
-#pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-          const int col = col0 + (cbp * 2 + cb) * 32 + r;
-#pragma unroll
-          for (int v = 0; v < 4; ++v) {
-            const float e = __builtin_amdgcn_exp2f(fmaf(acc[cb][4 * g + v], a.scale_log2, -rl[v]));
-            colsum[cb] += col <= ps[v] && row0 + v < a.P ? e : 0.f;
-          }
+            for (int v = 0; v < 4; ++v) colsum[cb] += __builtin_amdgcn_exp2f(fmaf(acc[cb][4 * g + v], a.scale_log2, -rl[v]));
         }
-        __builtin_amdgcn_sched_barrier(0);
+      } else {
+        const int4* ps4 = reinterpret_cast<const int4*>(&spos[at + rbw * 32 + 4 * kh]);
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+          const float4 t = rl4[2 * g];
+          const int4 s = ps4[2 * g];
+          const float rl[4] = {t.x, t.y, t.z, t.w};
+          const int ps[4] = {s.x, s.y, s.z, s.w};
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb) {
+            const int col = wcol0 + cb * 32 + r;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+              const float e = __builtin_amdgcn_exp2f(fmaf(acc[cb][4 * g + v], a.scale_log2, -rl[v]));
+              colsum[cb] += col <= ps[v] ? e : 0.f;
+            }
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
       }
     }
-    slot = next;
+    at = next;
     cur ^= 1;
   }
+  wait_all_loads();                              // (a fetch behind the last probe: nothing may land in LDS that is another workgroup's)
+  __syncthreads();
   const int t1 = opaque(tid), l1 = t1 & 63;
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb) {
@@ -646,9 +756,9 @@ static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStr
   if (need_lse) {
     hipLaunchKernelGGL((k_probe_lse<DT, D>), dim3((unsigned)((int64_t)a.head_wgs * a.Hq * a.B)), dim3(256), 0, st, a);
     ZC_LAUNCH_CHECK();
-    if (a.head_wgs > ceil_div(a.P, kLseRows)) {
-      const int64_t rows = (int64_t)a.B * a.Hq * a.P;
-      hipLaunchKernelGGL(k_probe_lse_merge, dim3((unsigned)ceil_div64(rows, 256)), dim3(256), 0, st, a.lse_part, a.lse2, rows, a.max_parts);
+    if (a.head_wgs > ceil_div(a.P, kLseRows) && !a.join) {
+      const int64_t heads = (int64_t)a.B * a.Hq;
+      hipLaunchKernelGGL(k_probe_lse_merge, dim3((unsigned)ceil_div(a.P, 64), (unsigned)(heads < 65535 ? heads : 65535)), dim3(64), 0, st, a);
       ZC_LAUNCH_CHECK();
     }
   }
@@ -699,6 +809,16 @@ static int64_t probe_head_wgs(int64_t B, int64_t Hq, int64_t P, int64_t Lk, int 
   if (nrb == 1) n = ceil_div64(tiles, ceil_div64(tiles, n));
   return n;
 }
+// Whether a sweep's waves are kept at about the same number of tiles to go: where a CU holds several of its
+// workgroups, all of them at once, of at least four tiles each.  us, without and with: 32 heads of 128 channels, 4096
+// tokens, 410 probes (1024 workgroups), sweep 2: 19.7 and 18.5; 12 heads of 64, 5000 tokens (480): 13.2 and 12.8; but
+// 24 heads, 9000 tokens, fp32 (1704 on 512 places): 344 and 374; 4 x 16 heads of 64, 900 tokens, two tiles: 8.50
+// and 8.61.  Sweep 1, whose workgroups all have as many tiles, from three a CU on: 4 heads, 20000 tokens, 1000
+// probes (384): 32.2 and 34.0.
+static bool even_waves(int64_t wgs, double tiles, const zc_tensor4* q) {
+  const int64_t places = q->dtype == ZC_F32 && q->D == 128 ? 512 : 1024;
+  return wgs > 256 && wgs <= places && tiles >= 4.0;
+}
 // Whether few probe rows are served by one launch: a block of 32, and no more bytes per
 // workgroup than its CU's loads bring in within the time the other path's two launches take
 // (8 heads of 64 channels, 256 tokens, 26 rows, fp32, 119 KB: 8 against 11 us; 32 heads of 128
@@ -715,9 +835,18 @@ static bool probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P,
 }
 static size_t lse_bytes(int64_t B, int64_t Hq, int64_t P) { return (size_t)align_up64(B * Hq * P * (kProbeParts * (int64_t)sizeof(float2) + 4), 256); }
 
+// What a call needs at least; and what it takes on top where sweep 2 joins the pairs of the column ranges, which then
+// lie beside the per-head scores it writes meanwhile: few probes, and one round of workgroups (of several
+// rounds each reads the pairs again: 16 x 40 heads of 128 channels, 4096 tokens, 410 probes: 352 us and a launch of
+// 8.4, joined 398; 32 heads: 19.2 and 4.6, joined 21.4).
+static size_t probe_least_bytes(int64_t B, int64_t Hq, int64_t Lk, int64_t P) { return lse_bytes(B, Hq, P) + (size_t)B * Hq * Lk * 4; }
+static size_t join_bytes(int64_t B, int64_t Hq, int64_t Lk, int64_t P) {
+  return P > kProbeTable || ceil_div64(Lk, 128) * Hq * B > 1024 ? 0 : (size_t)align_up64(B * Hq * P * (kMaxProbeParts - kProbeParts) * (int64_t)sizeof(float2), 256);
+}
+
 extern "C" size_t zc_probe_saliency_workspace(int64_t B, int64_t Hq, int64_t Lk, int64_t P) {
   if (B <= 0 || Hq <= 0 || Lk <= 0 || P <= 0) return 0;
-  return lse_bytes(B, Hq, P) + (size_t)B * Hq * Lk * 4;
+  return probe_least_bytes(B, Hq, Lk, P) + join_bytes(B, Hq, Lk, P);
 }
 
 static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
@@ -742,7 +871,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
     // offsets must not wrap either)
     if (q->L * q->sL * eb >= 0xFFFFF000ll || (k->L + 128) * k->sL * eb >= 0xFFFFF000ll || (int64_t)P * 4 >= 0xFFFFF000ll) return ZC_ERR_UNSUPPORTED;
   }
-  const size_t need = zc_probe_saliency_workspace(q->B, q->H, k->L, P);
+  const size_t need = probe_least_bytes(q->B, q->H, k->L, P), extra = join_bytes(q->B, q->H, k->L, P);
   if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 15)) return ZC_ERR_WORKSPACE;
 
   ProbeArgs a;
@@ -752,20 +881,25 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.B = (int)q->B; a.Hq = (int)q->H; a.Hkv = (int)k->H; a.G = a.Hq / a.Hkv; a.Lk = (int)k->L; a.Lq = (int)q->L; a.P = P;
   a.probe_rows = probe_rows; a.probe_pos = probe_pos;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
-  float* ws_ph = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + lse_bytes(q->B, q->H, P));
   a.lse_in = lse_ext;
+  a.small = probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));
+  a.join = !lse_ext && !a.small && extra > 0 && ws_bytes >= need + extra;
+  float* ws_ph = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + lse_bytes(q->B, q->H, P) + (a.join ? extra : 0));
   // [log-sum-exps][column ranges' pairs, up to the end of the workspace: the per-head scores, at
-  // their place in it, are written when the pairs have been read]
+  // their place in it, are written when the pairs have been read]; joined by sweep 2 [pairs][per-head scores]
   const int64_t rows = q->B * q->H * P, lse2_bytes = align_up64(rows * 4, 16), fit = ((int64_t)need - lse2_bytes) / (rows * (int64_t)sizeof(float2));
   a.lse2 = reinterpret_cast<float*>(ws);
-  a.lse_part = reinterpret_cast<float2*>(reinterpret_cast<uint8_t*>(ws) + lse2_bytes);
-  a.max_parts = (int)(fit < kMaxProbeParts ? fit : kMaxProbeParts) & ~1;
+  a.lse_part = reinterpret_cast<float2*>(reinterpret_cast<uint8_t*>(ws) + (a.join ? 0 : lse2_bytes));
+  a.max_parts = (int)(a.join || fit > kMaxProbeParts ? kMaxProbeParts : fit);
   const int64_t head_wgs = probe_head_wgs(q->B, q->H, P, k->L, a.max_parts, q->dtype == ZC_F32);
   a.head_wgs = (int)head_wgs;
+  if (head_wgs <= ceil_div64(P, kLseRows)) a.join = 0;     // (one range a row block: its log-sum-exps are in lse2)
   if (head_wgs * q->H * q->B > 0x7fffffff || (int64_t)ceil_div64(k->L, 128) * q->H * q->B > 0x7fffffff)
     return ZC_ERR_UNSUPPORTED;
+  const int64_t wgs1 = head_wgs * q->H * q->B, wgs2 = ceil_div64(k->L, 128) * q->H * q->B;
+  a.even1 = wgs1 >= 768 && even_waves(wgs1, (double)(ceil_div64(P, kLseRows) * ceil_div64(k->L, kLseCols)) / (double)head_wgs, q) ? kEvenTiles : 0;
+  a.even2 = even_waves(wgs2, P / 64.0, q) ? kEvenTiles * 64 : 0;
   a.normalize = normalize ? 1 : 0;
-  a.small = probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));
   a.per_head = scores_per_head || a.small ? scores_per_head : ws_ph;       // (few rows: only where the caller asks for them)
 
   hipStream_t st = (hipStream_t)stream;

@@ -1,4 +1,6 @@
 """Probe saliency: how the row blocks of the first sweep share a head's workgroups, tile edges of both sweeps."""
+import ctypes as C
+
 import pytest
 import torch
 
@@ -44,6 +46,16 @@ CASES = [
     (2, 200, 200, 64, 300, torch.bfloat16, lambda L: spread(L, 30)),                  # a single block of more heads than get two ranges
     (1, 130, 130, 64, 200, torch.float32, lambda L: spread(L, 33)),                   # of four tiles at most: one range
     (1, 8, 2, 128, 4500, torch.float32, lambda L: spread(L, 450)),                    # whole rounds of workgroups a CU
+    # last blocks of up to 32, of 33 to 64 and of 65 rows; the most probes looked up from LDS at once and one more, some in
+    # front of the last columns, some behind the first; heads enough for a full chip of blocks of different lengths
+    (1, 4, 2, 128, 1500, torch.bfloat16, lambda L: spread(L, 160)),
+    (1, 4, 2, 64, 1500, torch.float32, lambda L: spread(L, 161)),
+    (1, 4, 2, 128, 1500, torch.float16, lambda L: spread(L, 192)),
+    (2, 4, 2, 64, 1500, torch.bfloat16, lambda L: spread(L, 193)),
+    (1, 2, 1, 128, 3000, torch.bfloat16, lambda L: spread(L, 512)),
+    (1, 2, 1, 128, 3000, torch.float32, lambda L: spread(L, 513)),
+    (1, 2, 2, 64, 2600, torch.bfloat16, lambda L: torch.arange(L - 1100, L)),
+    (1, 32, 8, 128, 2100, torch.bfloat16, lambda L: torch.cat([spread(L - 110, 110), torch.arange(L - 110, L)]).unique()),
 ]
 
 
@@ -111,3 +123,29 @@ def test_scores_of_a_negative_scale(case):
     # instruction drops bits of products without regard to sign, so the scores of -q and 0.25 are not the same bits)
     rel = ((got.double() - want).abs() / want.clamp(min=1e-30)).max().item()
     assert rel < 3e-5, rel
+
+
+# A workspace of the least size: the pairs of the column ranges have no place beside the per-head scores, and are joined in front of sweep 2.
+@pytest.mark.parametrize("case", [1, 2, 12, 16])
+def test_scores_in_the_least_workspace(case):
+    B, Hq, Hkv, d, L, dtype, probes = CASES[case]
+    g = torch.Generator(device=DEV).manual_seed(case)
+    pos = probes(L).int().to(DEV)
+    P = pos.numel()
+    q = torch.randn(B, Hq, L, d, generator=g, device=DEV).to(dtype)
+    k = torch.randn(B, Hkv, L, d, generator=g, device=DEV).to(dtype)
+    want = zb.zc_probe_saliency(q, k, pos)
+    least = -(-B * Hq * P * 68 // 256) * 256 + B * Hq * L * 4          # a log-sum-exp and eight pairs a row, the per-head scores
+    lib = zb.load()
+    assert least < lib.zc_probe_saliency_workspace(B, Hq, L, P)
+    ws = torch.full((least + 64,), 0xff, dtype=torch.uint8, device=DEV)
+    got = torch.empty_like(want)
+    code = {torch.float32: zb.ZC_F32, torch.float16: zb.ZC_F16, torch.bfloat16: zb.ZC_BF16}[dtype]
+    views = [zb.zc_tensor4(t.data_ptr(), code, 0, *t.shape, *t.stride()[:3]) for t in (q, k)]
+    call = lambda n: lib.zc_probe_saliency(C.byref(views[0]), C.byref(views[1]), None, pos.data_ptr(), P, 0.0, None,
+                                           got.data_ptr(), None, ws.data_ptr(), n, torch.cuda.current_stream().cuda_stream)
+    assert call(least - 1) == -3
+    assert call(least) == 0
+    assert bool((ws[least:] == 0xff).all())
+    # (the ranges may be cut elsewhere: sums of the same terms in another order, each sum off by a few 2^-24)
+    assert torch.allclose(got, want, rtol=1e-5, atol=0)
