@@ -60,6 +60,7 @@ struct ProbeArgs {
   // the waves of sweep 1 / sweep 2 are kept at about the same number of tiles to go from so many tiles / probe rows before
   // their ends on (0: not at all)
   int even1, even2;
+  int group;             // sweep 2: query heads whose columns an XCD takes from the first on together (0: a head after the other)
   int small;             // 1: few probe rows, sweep 2 and the mean in one launch
   int normalize;         // 1: divide a column's sum by the number of probes that see it (Eq. 8); 0: Eq. 7
 };
@@ -411,14 +412,27 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   __shared__ int bins[128];                     // probes at each of this workgroup's columns
   __shared__ __align__(16) int before[4];       // probes in front of them, by wave
 
-  // logical order: column tile fastest, then query head, then batch; the tiles of every other
-  // head backwards, so that a CU's workgroups, 32 apart in an XCD's range, do not all see the
-  // many rows of a prompt's first columns or all the few of its last
+  // Logical order: the first columns, which the most probes see, of all heads of a group, then the next ones: the
+  // last workgroups to start are the shortest, and a CU's workgroups, 32 apart in an XCD's range, see few
+  // rows and many.  Where the heads divide over the 8 XCDs every XCD has its own, in groups of two rounds of
+  // its places, so that the workgroups in flight read few heads' rows through its L2.  Otherwise head after
+  // head, every other one backwards.  us given normalisers, head after head and so: 2 x 32 heads, 3001 tokens
+  // 23.4 and 22.7; 24 heads, 9000 tokens 52.4 and 47.1; 32 heads, 32768 tokens 665 and 632; 16 x 16 heads of 64,
+  // 2000 tokens 30.9 and 27.9; 32 heads, 4096 tokens 18.7 and 18.0, fp32 111 and 98; up to a
+  // workgroup a CU the divisions only cost time (16 x 8 heads of 64, 400 tokens 7.1 and 7.3).
   const int nct = ceil_div(a.Lk, 128);
-  int j = xcd_contiguous(blockIdx.x, gridDim.x);
-  int ct = j % nct; j /= nct;
+  int j, ct;
+  if (a.group) {
+    const int hpx = (a.B * a.Hq) >> 3, rank = blockIdx.x >> 3, g = rank / (a.group * nct), rem = rank - g * (a.group * nct);
+    const int size = min(a.group, hpx - g * a.group);
+    ct = rem / size;
+    j = (blockIdx.x & 7) * hpx + g * a.group + rem - ct * size;
+  } else {
+    j = xcd_contiguous(blockIdx.x, gridDim.x);
+    ct = j % nct; j /= nct;
+    if ((j % a.Hq) & 1) ct = nct - 1 - ct;
+  }
   const int hq = j % a.Hq, b = j / a.Hq, hk = hq / a.G;
-  if (hq & 1) ct = nct - 1 - ct;
   const int col0 = ct * 128;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -899,6 +913,10 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   const int64_t wgs1 = head_wgs * q->H * q->B, wgs2 = ceil_div64(k->L, 128) * q->H * q->B;
   a.even1 = wgs1 >= 768 && even_waves(wgs1, (double)(ceil_div64(P, kLseRows) * ceil_div64(k->L, kLseCols)) / (double)head_wgs, q) ? kEvenTiles : 0;
   a.even2 = even_waves(wgs2, P / 64.0, q) ? kEvenTiles * 64 : 0;
+  {
+    const int64_t nct = ceil_div64(k->L, 128), heads = q->B * q->H, hpx = heads / 8, least = ceil_div64(256, nct), groups = hpx / least;
+    a.group = heads % 8 == 0 && wgs2 > 256 ? (int)(groups > 1 ? ceil_div64(hpx, groups) : hpx) : 0;
+  }
   a.normalize = normalize ? 1 : 0;
   a.per_head = scores_per_head || a.small ? scores_per_head : ws_ph;       // (few rows: only where the caller asks for them)
 
