@@ -184,6 +184,7 @@ __device__ inline int tile_of_field_group(int bits, int jf) {
 // 379 us, 517 as three launches that read the keys twice), by the latency of its two rounds
 // of loads where it is not (one prompt of 4096 tokens, 1024 channels: 8 us for both tensors'
 // statistics and parameters, 14 as two launches).
+constexpr int64_t kPartBytes = 0xFFFFF000ll;                       // codes of a batch element: least size that a 32-bit offset does not reach
 constexpr int kColRows(int dt) { return dt == ZC_F32 ? 10 : 20; }   // rows a thread can hold
 
 template <int DT>
@@ -203,7 +204,7 @@ __device__ inline void widen8(const uint4 (&raw)[DT == ZC_F32 ? 2 : 1], float (&
 
 // The 8 codes of one token row, packed (ROW layout).
 template <int DT, int BITS>
-__device__ inline void store_row_codes(uint8_t* row, const float (&x)[8], const float (&p0)[8], const float (&p1)[8], const float (&p2)[8]) {
+__device__ inline void row_codes(uint32_t (&code)[BITS == 8 ? 2 : 1], const float (&x)[8], const float (&p0)[8], const float (&p1)[8], const float (&p2)[8]) {
   constexpr float QMAX = (float)((1 << BITS) - 1);
   constexpr int FPG = 16 / BITS, NG = 8 / FPG;       // code fields per 16-bit group, groups
   uint32_t half[NG];
@@ -220,9 +221,113 @@ __device__ inline void store_row_codes(uint8_t* row, const float (&x)[8], const 
     }
     half[g] = (uint32_t)acc;
   }
-  if constexpr (BITS == 8) *reinterpret_cast<uint2*>(row) = make_uint2(half[0] | (half[1] << 16), half[2] | (half[3] << 16));
-  else if constexpr (BITS == 4) *reinterpret_cast<uint32_t*>(row) = half[0] | (half[1] << 16);
-  else *reinterpret_cast<uint16_t*>(row) = (uint16_t)half[0];
+#pragma unroll
+  for (int g = 0; g < NG; g += 2) code[g / 2] = half[g] | (g + 1 < NG ? half[g + 1] << 16 : 0u);
+}
+template <int DT, int BITS>
+__device__ inline void store_row_codes(uint8_t* row, const float (&x)[8], const float (&p0)[8], const float (&p1)[8], const float (&p2)[8]) {
+  uint32_t code[BITS == 8 ? 2 : 1];
+  row_codes<DT, BITS>(code, x, p0, p1, p2);
+  if constexpr (BITS == 8) *reinterpret_cast<uint2*>(row) = make_uint2(code[0], code[1]);
+  else if constexpr (BITS == 4) *reinterpret_cast<uint32_t*>(row) = code[0];
+  else *reinterpret_cast<uint16_t*>(row) = (uint16_t)code[0];
+}
+
+// ---- 2-bit codes of 16-bit keys by thresholds ------------------------------------------------
+// A channel's codes ascend with its values, so a 2-bit code is the number of three thresholds a value reaches:
+// the least 16-bit numbers whose code is 1, 2 and 3.  Two values at a time, a code takes 4 (fp16: the sign
+// of x - t, which is exact) or 5 (bf16: saturating differences of the order-preserving integers)
+// instructions instead of 9.
+constexpr float kTameRange = 0x1p60f, kTameOffset = 0x1p20f;      // ranges and zero points beyond: the general path
+
+// Order-preserving integer of a 16-bit float's bits, and back.
+__device__ inline int ordered16(int bits) {
+  const int s = (int)(int16_t)bits;
+  return s ^ ((s >> 15) & 0x7fff);
+}
+
+// Threshold of code j (1 .. 3) of a channel with zero point z, range R and y = 1 / R, as an ordered integer.
+template <int DT>
+__device__ inline int code_threshold(int j, float z, float R, float y) {
+  const int inf = DT == ZC_F16 ? 0x7c00 : 0x7f80;
+  const float at = ((float)j - 0.5f - z) * (R * (1.f / 3.f));     // where the rounding turns to j: the threshold is next to it
+  int bits;
+  if constexpr (DT == ZC_F16) {
+    bits = (int)__builtin_bit_cast(uint16_t, (_Float16)at);
+  } else {
+    bits = (int)__builtin_bit_cast(uint16_t, (__bf16)at);
+  }
+  const int g = ordered16(bits);
+  int t = min(g + 2, inf);
+#pragma unroll
+  for (int d = 1; d >= -1; --d) {
+    const int k = min(max(g + d, -inf - 1), inf);
+    const float x = half_bits_to_float<DT>((uint32_t)ordered16(k) & 0xffffu);
+    if (k == inf || rintf(refined_div(x * 3.f, R, y)) + z >= (float)j) t = k;
+  }
+  return t;
+}
+
+// Whether two 16-bit values at a time lie below their thresholds: the sign bits of both halves.  (fp16: t holds
+// the negated thresholds; bf16: ordered integers of both.)
+template <int DT>
+__device__ inline uint32_t below16(uint32_t x, uint32_t t) {
+  if constexpr (DT == ZC_F16) {
+    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, x) + __builtin_bit_cast(h2, t));
+  } else {
+    typedef short s2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(s2, x), __builtin_bit_cast(s2, t)));
+  }
+}
+
+// Bits of a where mask is set, of b elsewhere; the exclusive or of three.  (Written out: of constant masks the
+// compiler makes ands and ors.)
+__device__ inline uint32_t select_bits(uint32_t mask, uint32_t a, uint32_t b) { return __builtin_amdgcn_bitop3_b32(mask, a, b, 0xca); }
+__device__ inline uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96); }
+struct CodeMasks { uint32_t top, pair, quad; };          // of the bits 15; 14 and 15 of both halves; 2, 3, 6, 7, 10, 11, 14 and 15
+__device__ inline CodeMasks code_masks() {
+  CodeMasks m = {0x80008000u, 0xc000c000u, 0xccccu};
+  asm("" : "+s"(m.top), "+s"(m.pair), "+s"(m.quad));
+  return m;
+}
+
+// The 8 codes of one token row's channels, two bits each; t[j]: the thresholds of code j + 1, two to a word.
+template <int DT>
+__device__ inline uint16_t threshold_codes(const uint4& raw, const uint4 (&t)[3], const CodeMasks& m) {
+  const uint32_t x4[4] = {raw.x, raw.y, raw.z, raw.w};
+  uint32_t w = 0u;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const auto word = [&](const uint4& v) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; };
+    uint32_t x = x4[i];
+    if constexpr (DT == ZC_BF16) {
+      typedef short s2 __attribute__((ext_vector_type(2)));
+      x ^= __builtin_bit_cast(uint32_t, __builtin_bit_cast(s2, x) >> (short)15) & 0x7fff7fffu;
+    }
+    const uint32_t b1 = below16<DT>(x, word(t[0])), b2 = below16<DT>(x, word(t[1])), b3 = below16<DT>(x, word(t[2]));
+    // the complement of a code: high bit "below 2", low bit the parity of the thresholds it is below
+    const uint32_t c = select_bits(m.top, b2, xor3(b1, b2, b3) >> 1);
+    w = i == 0 ? c : select_bits(m.pair, c, w >> 4);     // even channels' in the low half, four bits apart, odd ones' in the high half
+  }
+  return (uint16_t)__builtin_amdgcn_bitop3_b32(m.quad, w >> 16, w >> 2, 0x35);      // (the complement of select_bits)
+}
+
+// sum + 0 x for the 8 values of x: a NaN if one of them is.
+template <int DT>
+__device__ inline float plus_zero_times(float sum, const uint4& x, uint32_t zero) {
+  const uint32_t x4[4] = {x.x, x.y, x.z, x.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if constexpr (DT == ZC_F16) {
+      typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+      sum = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, x4[i]), __builtin_bit_cast(h2, zero), sum, false);
+    } else {
+      typedef __bf16 b2 __attribute__((ext_vector_type(2)));
+      sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, x4[i]), __builtin_bit_cast(b2, zero), sum, false);
+    }
+  }
+  return sum;
 }
 
 template <int DT, int THREADS, bool SPLIT = false>       // SPLIT: `split` token ranges per subset, only their minima
@@ -231,6 +336,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
   constexpr int NR = kColRows(DT), NWAVE = THREADS / 64;
   __shared__ __align__(16) float red[NWAVE][2][128];
   __shared__ __align__(16) float prm[3][128];
+  __shared__ __align__(16) uint16_t thr[3][128];         // thresholds of 2-bit codes
+  __shared__ int wild;                                   // some channel has none
 
   // logical order: channel group fastest, then subset, tensor, batch element: the workgroups
   // that share a token row's cache lines run on one XCD at about the same time
@@ -244,6 +351,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
   const QPArgs& a = which ? p.t[1] : p.t[0];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int x = tid & (vl - 1), y = tid / vl, step = THREADS / vl;
+  const int y0 = __builtin_amdgcn_readfirstlane(y);             // the wave's first row
   const int n = a.scheme == ZC_SCHEME_TOKEN ? 0 : a.n[sub];     // (plain tokenwise: no channel statistics)
   const int vec = min(grp * vl + x, a.NV - 1);                  // (lanes past the row repeat its last vector)
   const int w = vec * 8, h = w / a.D, c = w % a.D;
@@ -267,17 +375,20 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
     int32_t tok[NR];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (r * step < n) tok[r] = idx[min(r * step + y, n - 1)];
+      if (r * step + y0 < n) tok[r] = idx[min(r * step + y, n - 1)];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (r * step < n) {
+      if (r * step + y0 < n) {
         const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)tok[r] * row_bytes);
 #pragma unroll
         for (int q = 0; q < RAW; ++q) raw[r][q] = src[q];
       }
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (r * step < n) reduce(raw[r]);
+      if (r * step + y0 < n) reduce(raw[r]);
+    // (all rows are here; the compiler, which does not see that a row that was requested has been reduced, would wait for
+    // each again where it is packed - and with it for the codes stored before)
+    __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0)
   } else {
     int first = 0, n1 = n;
     if constexpr (SPLIT) {
@@ -317,6 +428,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
 #pragma unroll
       for (int j = 0; j < 4; ++j) u[j] = fminf(u[j], __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(u[j]), 0x122, 0xF, 0xF, true)));   // row_ror:2
     }
+    if (tid == 0) wild = 0;
     if ((lane & 15) < vl)
       *reinterpret_cast<float4*>(&red[wave][lane >> 5][(lane & 15) * 8 + 4 * ((lane >> 4) & 1)]) = make_float4(u[0], u[1], u[2], u[3]);
   }
@@ -337,6 +449,16 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
     a.chan_zero[o] = cz;
     if (!a.resident) store_params(a, b, sub, wc, pr);
     prm[0][tid] = pr.x; prm[1][tid] = pr.y; prm[2][tid] = pr.z;
+    if (DT == ZC_F16 && a.resident && a.bits[sub] == 2) {
+      if (!(pr.z > 1.f / kTameRange && pr.z < kTameRange && fabsf(pr.y) <= kTameOffset)) wild = 1;
+      else {
+#pragma unroll 1
+        for (int j = 0; j < 3; ++j) {
+          const int t = code_threshold<DT>(j + 1, pr.y, pr.z, pr.x);
+          thr[j][tid] = (uint16_t)(DT == ZC_F16 ? ordered16(t) ^ 0x8000 : t);
+        }
+      }
+    }
   }
   if constexpr (SPLIT) return;
   if (grp == 0 && sub == 0 && b == 0 && tid == 0) {
@@ -349,23 +471,55 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
   if (grp == 0 && a.pos[sub])
     for (int t = tid; t < n; t += THREADS) a.pos[sub][(int64_t)b * a.cap[sub] + a.begin[sub] + t] = (int32_t)(idx[t] + a.pos_offset);
   if (grp * vl + x >= a.NV) return;
+  const int bits = a.bits[sub];
+  // Codes of a row through a buffer descriptor over this batch element's, from the chunk's first slot on: rows past the
+  // end are out of range (no branch), and the offset takes 32 bits.
+  const int rowb = a.D * bits / 8;
+  const uint32_t room = (uint32_t)(((int64_t)a.H * a.cap[sub] - a.begin[sub]) * rowb);      // (below kPartBytes: col_plan)
+  const uint32_t at = (uint32_t)(((int64_t)h * a.cap[sub] + y) * rowb) + c * bits / 8;
+  const auto rs_dst = __builtin_amdgcn_make_buffer_rsrc(a.codes[sub] + ((int64_t)b * a.H * a.cap[sub] + a.begin[sub]) * rowb, 0, room, 0x00020000);
+  const auto offset_of = [&](int r) { return r * step + y < n ? (int)(at + (uint32_t)(r * step * rowb)) : (int)(uint32_t)kPartBytes; };
+  if constexpr (DT == ZC_F16) {
+    if (bits == 2 && !wild) {
+      const CodeMasks m = code_masks();
+      uint4 t[3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) t[j] = *reinterpret_cast<const uint4*>(&thr[j][x * 8]);
+      uint32_t zero = 0u;
+      asm("" : "+v"(zero));
+      float nan = 0.f;
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+        if (r * step + y0 < n) {
+          __builtin_amdgcn_raw_buffer_store_b16((short)threshold_codes<DT>(raw[r][0], t, m), rs_dst, offset_of(r), 0, 0);
+          nan = plus_zero_times<DT>(nan, raw[r][0], zero);
+        }
+      if (__builtin_amdgcn_ballot_w64((__float_as_uint(nan) & 0x7fffffffu) != 0u) == 0) return;      // (a NaN's code is what the general path makes of it)
+    }
+  }
   float p0[8], p1[8], p2[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) { p0[i] = prm[0][x * 8 + i]; p1[i] = prm[1][x * 8 + i]; p2[i] = prm[2][x * 8 + i]; }
   auto pack = [&](auto bits_c) {
     constexpr int BITS = decltype(bits_c)::value;
-    const int rowb = a.D * BITS / 8;
-    uint8_t* dst = a.codes[sub] + (((int64_t)b * a.H + h) * a.cap[sub] + a.begin[sub] + y) * rowb + c * BITS / 8;
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
-      if (r * step + y < n) {
+      if (r * step + y0 < n) {
         float v[8];
+        uint32_t code[BITS == 8 ? 2 : 1];
         widen8<DT>(raw[r], v);
-        store_row_codes<DT, BITS>(dst + (int64_t)(r * step) * rowb, v, p0, p1, p2);
+        row_codes<DT, BITS>(code, v, p0, p1, p2);
+        if constexpr (BITS == 8) {
+          typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+          __builtin_amdgcn_raw_buffer_store_b64(u2{code[0], code[1]}, rs_dst, offset_of(r), 0, 0);
+        } else if constexpr (BITS == 4) {
+          __builtin_amdgcn_raw_buffer_store_b32(code[0], rs_dst, offset_of(r), 0, 0);
+        } else {
+          __builtin_amdgcn_raw_buffer_store_b16((short)code[0], rs_dst, offset_of(r), 0, 0);
+        }
       }
     }
   };
-  const int bits = a.bits[sub];
   if (bits == 4) pack(std::integral_constant<int, 4>{});
   else if (bits == 2) pack(std::integral_constant<int, 2>{});
   else pack(std::integral_constant<int, 8>{});
@@ -1072,7 +1226,8 @@ static ColPlan col_plan(QPArgs* a, const zc_packed* const* out, int tensors, int
   const bool fits = n <= rows * th / v && !(joint_pack && few_wgs) && !strips;
   bool any = false;
   for (int t = 0; t < tensors; ++t) {
-    a[t].resident = fits && out[t]->scheme == ZC_SCHEME_CHANNEL && out[t]->layout == ZC_LAYOUT_ROW;
+    const auto near = [&](int sub) { return a[t].H * a[t].cap[sub] * a[t].D * a[t].bits[sub] / 8 < kPartBytes; };
+    a[t].resident = fits && out[t]->scheme == ZC_SCHEME_CHANNEL && out[t]->layout == ZC_LAYOUT_ROW && near(0) && near(1);
     any |= a[t].resident != 0;
   }
   for (int t = 0; t < tensors; ++t) a[t].vl = any ? v : vl;
