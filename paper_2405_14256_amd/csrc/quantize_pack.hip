@@ -233,12 +233,13 @@ __device__ inline void store_row_codes(uint8_t* row, const float (&x)[8], const 
   else *reinterpret_cast<uint16_t*>(row) = (uint16_t)code[0];
 }
 
-// ---- 2-bit codes of 16-bit keys by thresholds ------------------------------------------------
+// ---- 2-bit codes of fp16 keys by thresholds ------------------------------------------------
 // A channel's codes ascend with its values, so a 2-bit code is the number of three thresholds a value reaches:
-// the least 16-bit numbers whose code is 1, 2 and 3.  Two values at a time, a code takes 4 (fp16: the sign
-// of x - t, which is exact) or 5 (bf16: saturating differences of the order-preserving integers)
-// instructions instead of 9.
+// the least fp16 numbers whose code is 1, 2 and 3.  Two values at a time (the sign of x - t, which is exact), a code
+// takes 4 instructions instead of 9.  (bf16 would take 5, with saturating differences of order-preserving integers: no
+// faster where the chip is full, and finding the thresholds costs 0.6 us where it is not.)
 constexpr float kTameRange = 0x1p60f, kTameOffset = 0x1p20f;      // ranges and zero points beyond: the general path
+typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
 // Order-preserving integer of a 16-bit float's bits, and back.
 __device__ inline int ordered16(int bits) {
@@ -246,39 +247,19 @@ __device__ inline int ordered16(int bits) {
   return s ^ ((s >> 15) & 0x7fff);
 }
 
-// Threshold of code j (1 .. 3) of a channel with zero point z, range R and y = 1 / R, as an ordered integer.
-template <int DT>
-__device__ inline int code_threshold(int j, float z, float R, float y) {
-  const int inf = DT == ZC_F16 ? 0x7c00 : 0x7f80;
+// Negated threshold (bits) of code j (1 .. 3) of a channel with zero point z, range R and y = 1 / R.
+__device__ inline uint16_t negated_threshold(int j, float z, float R, float y) {
+  constexpr int inf = 0x7c00;
   const float at = ((float)j - 0.5f - z) * (R * (1.f / 3.f));     // where the rounding turns to j: the threshold is next to it
-  int bits;
-  if constexpr (DT == ZC_F16) {
-    bits = (int)__builtin_bit_cast(uint16_t, (_Float16)at);
-  } else {
-    bits = (int)__builtin_bit_cast(uint16_t, (__bf16)at);
-  }
-  const int g = ordered16(bits);
+  const int g = ordered16((int)__builtin_bit_cast(uint16_t, (_Float16)at));
   int t = min(g + 2, inf);
 #pragma unroll
   for (int d = 1; d >= -1; --d) {
     const int k = min(max(g + d, -inf - 1), inf);
-    const float x = half_bits_to_float<DT>((uint32_t)ordered16(k) & 0xffffu);
+    const float x = f16_bits_to_float((uint32_t)ordered16(k) & 0xffffu);
     if (k == inf || rintf(refined_div(x * 3.f, R, y)) + z >= (float)j) t = k;
   }
-  return t;
-}
-
-// Whether two 16-bit values at a time lie below their thresholds: the sign bits of both halves.  (fp16: t holds
-// the negated thresholds; bf16: ordered integers of both.)
-template <int DT>
-__device__ inline uint32_t below16(uint32_t x, uint32_t t) {
-  if constexpr (DT == ZC_F16) {
-    typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(h2, x) + __builtin_bit_cast(h2, t));
-  } else {
-    typedef short s2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_elementwise_sub_sat(__builtin_bit_cast(s2, x), __builtin_bit_cast(s2, t)));
-  }
+  return (uint16_t)(ordered16(t) ^ 0x8000);
 }
 
 // Bits of a where mask is set, of b elsewhere; the exclusive or of three.  (Written out: of constant masks the
@@ -292,20 +273,17 @@ __device__ inline CodeMasks code_masks() {
   return m;
 }
 
-// The 8 codes of one token row's channels, two bits each; t[j]: the thresholds of code j + 1, two to a word.
-template <int DT>
+// The 8 codes of one token row's channels, two bits each; t[j]: the negated thresholds of code j + 1, two to a word.
 __device__ inline uint16_t threshold_codes(const uint4& raw, const uint4 (&t)[3], const CodeMasks& m) {
   const uint32_t x4[4] = {raw.x, raw.y, raw.z, raw.w};
   uint32_t w = 0u;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
-    const auto word = [&](const uint4& v) { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; };
-    uint32_t x = x4[i];
-    if constexpr (DT == ZC_BF16) {
-      typedef short s2 __attribute__((ext_vector_type(2)));
-      x ^= __builtin_bit_cast(uint32_t, __builtin_bit_cast(s2, x) >> (short)15) & 0x7fff7fffu;
-    }
-    const uint32_t b1 = below16<DT>(x, word(t[0])), b2 = below16<DT>(x, word(t[1])), b3 = below16<DT>(x, word(t[2]));
+    const auto below = [&](const uint4& v) {             // sign bits: below the threshold
+      const uint32_t word = i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w;
+      return __builtin_bit_cast(uint32_t, __builtin_bit_cast(half2v, x4[i]) + __builtin_bit_cast(half2v, word));
+    };
+    const uint32_t b1 = below(t[0]), b2 = below(t[1]), b3 = below(t[2]);
     // the complement of a code: high bit "below 2", low bit the parity of the thresholds it is below
     const uint32_t c = select_bits(m.top, b2, xor3(b1, b2, b3) >> 1);
     w = i == 0 ? c : select_bits(m.pair, c, w >> 4);     // even channels' in the low half, four bits apart, odd ones' in the high half
@@ -314,19 +292,10 @@ __device__ inline uint16_t threshold_codes(const uint4& raw, const uint4 (&t)[3]
 }
 
 // sum + 0 x for the 8 values of x: a NaN if one of them is.
-template <int DT>
 __device__ inline float plus_zero_times(float sum, const uint4& x, uint32_t zero) {
   const uint32_t x4[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if constexpr (DT == ZC_F16) {
-      typedef _Float16 h2 __attribute__((ext_vector_type(2)));
-      sum = __builtin_amdgcn_fdot2(__builtin_bit_cast(h2, x4[i]), __builtin_bit_cast(h2, zero), sum, false);
-    } else {
-      typedef __bf16 b2 __attribute__((ext_vector_type(2)));
-      sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, x4[i]), __builtin_bit_cast(b2, zero), sum, false);
-    }
-  }
+  for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, x4[i]), __builtin_bit_cast(half2v, zero), sum, false);
   return sum;
 }
 
@@ -453,10 +422,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
       if (!(pr.z > 1.f / kTameRange && pr.z < kTameRange && fabsf(pr.y) <= kTameOffset)) wild = 1;
       else {
 #pragma unroll 1
-        for (int j = 0; j < 3; ++j) {
-          const int t = code_threshold<DT>(j + 1, pr.y, pr.z, pr.x);
-          thr[j][tid] = (uint16_t)(DT == ZC_F16 ? ordered16(t) ^ 0x8000 : t);
-        }
+        for (int j = 0; j < 3; ++j) thr[j][tid] = negated_threshold(j + 1, pr.y, pr.z, pr.x);
       }
     }
   }
@@ -491,8 +457,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
 #pragma unroll
       for (int r = 0; r < NR; ++r)
         if (r * step + y0 < n) {
-          __builtin_amdgcn_raw_buffer_store_b16((short)threshold_codes<DT>(raw[r][0], t, m), rs_dst, offset_of(r), 0, 0);
-          nan = plus_zero_times<DT>(nan, raw[r][0], zero);
+          __builtin_amdgcn_raw_buffer_store_b16((short)threshold_codes(raw[r][0], t, m), rs_dst, offset_of(r), 0, 0);
+          nan = plus_zero_times(nan, raw[r][0], zero);
         }
       if (__builtin_amdgcn_ballot_w64((__float_as_uint(nan) & 0x7fffffffu) != 0u) == 0) return;      // (a NaN's code is what the general path makes of it)
     }
