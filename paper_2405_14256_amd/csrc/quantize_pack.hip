@@ -365,14 +365,21 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
       first = part * per;
       n1 = min(n, first + per);
     }
+    int32_t tok[kStatBatch];                     // of the next batch: looked up while the one before is on its way
+    const auto look_up = [&](int t0) {
+#pragma unroll
+      for (int r = 0; r < kStatBatch; ++r) tok[r] = idx[min(t0 + r * step + y, n1 - 1)];
+    };
+    if (first < n1) look_up(first);
     for (int t0 = first; t0 < n1; t0 += kStatBatch * step) {
       uint4 rw[kStatBatch][RAW];
 #pragma unroll
       for (int r = 0; r < kStatBatch; ++r) {
-        const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)idx[min(t0 + r * step + y, n1 - 1)] * row_bytes);
+        const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)tok[r] * row_bytes);
 #pragma unroll
         for (int q = 0; q < RAW; ++q) rw[r][q] = src[q];
       }
+      if (t0 + kStatBatch * step < n1) look_up(t0 + kStatBatch * step);
 #pragma unroll
       for (int r = 0; r < kStatBatch; ++r) reduce(rw[r]);
     }
