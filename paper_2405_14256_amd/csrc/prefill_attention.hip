@@ -33,6 +33,7 @@ struct PrefillArgs {
 };
 
 constexpr int kPfKeys = 64;    // keys per tile
+typedef float v4f __attribute__((ext_vector_type(4)));
 
 template <int DT>
 __device__ inline uint32_t pack_pair(float lo, float hi) {
@@ -262,6 +263,160 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
     if (w == 0 && kh == 0) sl[0][r] = lse;       // (the sums were read in front of the barriers above)
     __syncthreads();
     probe_normalisers<32, 64 * NW>(a, head, q0, sl[0]);
+  }
+}
+
+// The same for calls that leave most of the chip idle: 16 rows a workgroup, in 16 x 16 matrix instructions (the
+// same rate), eight waves, and their outputs joined at once from a place of their own each.  Bound by the chain of a
+// wave's trip to memory, its 32 cycles for every 1024 products and the join: 8 heads of 64 channels, 256 rows 11.0 -> 7.9 us,
+// 64 rows 6.9 -> 5.2; of 128 channels 16.8 -> 12.2 and 9.5 -> 6.7.
+// Operand layouts of the 16 x 16 x 4 instruction: lane (g = lane / 16, i = lane % 16) holds element [i][k = g] of an
+// operand and elements [4 g + v][i] of the result; the order of a product's k index is free.
+template <int D>
+__global__ __launch_bounds__(512, 1) void k_prefill_attention32_few(PrefillArgs a) {
+  constexpr int NW = 8, NKC = D / 16, CT = D / 16;
+  constexpr int OROW = D + 4;                    // floats of a row in the joining stage
+  __shared__ __align__(16) float so[NW][16 * OROW];
+  __shared__ float sm[NW][16], sl[NW][16];
+
+  int hq, b, q0;
+  prefill_block(a, 16, &b, &hq, &q0);
+  const int hk = hq / a.G;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 15, g = lane >> 4;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)hq * a.q_sH) * 4;
+  const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)hk * a.k_sH) * 4;
+  const uint8_t* vb = reinterpret_cast<const uint8_t*>(a.v) + ((int64_t)b * a.v_sB + (int64_t)hk * a.v_sH) * 4;
+  const uint32_t q_rowb = (uint32_t)(a.q_sL * 4), k_rowb = (uint32_t)(a.k_sL * 4), v_rowb = (uint32_t)(a.v_sL * 4);
+  const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.L - 1) * q_rowb + D * 4, kBufFlags);
+  const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.L - 1) * k_rowb + D * 4, kBufFlags);
+  const auto rs_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(vb), 0, (uint32_t)(a.L - 1) * v_rowb + D * 4, kBufFlags);
+  const int qpos = q0 + r;
+
+  // (rows past the end, of any tensor, arrive as zeros)
+  u32x4 qf[NKC];
+  {
+    const int voff = qpos < a.L ? (int)((uint32_t)qpos * q_rowb) + g * 16 : kOutOfRange;
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) qf[kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_q, voff + kc * 64, 0, 0);
+  }
+  v4f oacc[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) oacc[ct] = v4f{};
+  float m = -INFINITY, l = 0.f;       // running maximum (log2 units) and this lane group's share of the sum
+
+  const int nblk = q0 / 32 + 1;                  // blocks of 32 keys the rows see: the last holds the diagonal
+  for (int blk = w; blk < nblk; blk += NW) {
+    const int key0 = blk * 32;
+    u32x4 kf[2][NKC];
+    float vf[2][4][CT];                          // [key tile][accumulator of the logits]: key 16 t + 4 g + v, channel 16 ct + r
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const int koff = (int)((uint32_t)(key0 + 16 * t + r) * k_rowb) + g * 16;
+#pragma unroll
+      for (int kc = 0; kc < NKC; ++kc) kf[t][kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_k, koff + kc * 64, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int voff = (int)((uint32_t)(key0 + 16 * t + 4 * g + v) * v_rowb) + r * 4;
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) vf[t][v][ct] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_v, voff + ct * 64, 0, 0));
+      }
+    v4f s[2] = {v4f{}, v4f{}};
+#pragma unroll
+    for (int kc = 0; kc < NKC; ++kc) {
+      // (the elements one by one on purpose, see mma_chunk)
+#pragma unroll
+      for (int t = 0; t < 2; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kf[t][kc].x), __uint_as_float(qf[kc].x), s[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kf[t][kc].y), __uint_as_float(qf[kc].y), s[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kf[t][kc].z), __uint_as_float(qf[kc].z), s[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < 2; ++t) s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kf[t][kc].w), __uint_as_float(qf[kc].w), s[t], 0, 0, 0);
+    }
+    if (blk == nblk - 1) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (key0 + 16 * t + 4 * g + v > qpos) s[t][v] = -INFINITY;
+    }
+    // (as in k_prefill_attention32: the maximum over the raw products, the scale with the subtraction)
+    float tmax = fmaxf(fmaxf(fmaxf(s[0][0], s[0][1]), fmaxf(s[0][2], s[0][3])), fmaxf(fmaxf(s[1][0], s[1][1]), fmaxf(s[1][2], s[1][3])));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 16));
+    tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
+    const float m_new = fmaxf(m, tmax * a.scale_log2);
+    if (__builtin_amdgcn_ballot_w64(m_new > m)) {
+      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+      l *= alpha;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) oacc[ct][i] *= alpha;
+      m = m_new;
+    }
+    float psum = 0.f;
+    const float ref = m == -INFINITY ? 0.f : m;  // (a wave whose logits are all -inf so far: its weights are 0)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        s[t][v] = __builtin_amdgcn_exp2f(fmaf(s[t][v], a.scale_log2, -ref));
+        psum += s[t][v];
+      }
+    l += psum;
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int v = 0; v < 4; ++v)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) oacc[ct] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[t][v][ct], s[t][v], oacc[ct], 0, 0, 0);
+  }
+
+  // ---- join the waves: a common reference and sum, then the outputs of all of them at once ----
+  // (a wave without keys has m = -inf, l = 0 and zeros; wave 0 always has the block of key 0)
+  float l_wave = l + __shfl_xor(l, 16);
+  l_wave += __shfl_xor(l_wave, 32);
+  if (g == 0) { sm[w][r] = m; sl[w][r] = l_wave; }
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) *reinterpret_cast<v4f*>(&so[w][r * OROW + 16 * ct + 4 * g]) = oacc[ct];      // four consecutive channels
+  __syncthreads();
+  const int used = min(NW, nblk);
+  for (int i = tid; i < 16 * (D / 4); i += 64 * NW) {
+    const int row = i / (D / 4), c = (i % (D / 4)) * 4;
+    float pm[NW], M = -INFINITY, total = 0.f;
+#pragma unroll
+    for (int v = 0; v < NW; ++v) { pm[v] = sm[v][row]; M = fmaxf(M, pm[v]); }
+#pragma unroll
+    for (int v = 0; v < NW; ++v) {
+      pm[v] = pm[v] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(pm[v] - M);
+      total = fmaf(sl[v][row], pm[v], total);
+    }
+    v4f o = v4f{};
+#pragma unroll
+    for (int v = 0; v < NW; ++v)
+      if (v < used) o += *reinterpret_cast<const v4f*>(&so[v][row * OROW + c]) * (pm[v] / total);
+    const int64_t head = (int64_t)b * a.Hq + hq;
+    if (q0 + row < a.L) {
+      *reinterpret_cast<v4f*>(reinterpret_cast<float*>(a.o) + (int64_t)b * a.o_sB + (int64_t)hq * a.o_sH + (int64_t)(q0 + row) * a.o_sL + c) = o;
+      if (c == 0 && a.lse) a.lse[head * a.L + q0 + row] = (M + log2f(total)) * kLn2;
+    }
+  }
+  if (a.probe_pos) {
+    __syncthreads();                             // (every wave has read the sums)
+    if (tid < 16) {
+      float M = -INFINITY, total = 0.f;
+#pragma unroll
+      for (int v = 0; v < NW; ++v) M = fmaxf(M, sm[v][tid]);
+#pragma unroll
+      for (int v = 0; v < NW; ++v) total = fmaf(sl[v][tid], sm[v][tid] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sm[v][tid] - M), total);
+      so[0][tid] = (M + log2f(total)) * kLn2;
+    }
+    __syncthreads();
+    probe_normalisers<16, 64 * NW>(a, (int64_t)b * a.Hq + hq, q0, so[0]);
   }
 }
 
@@ -561,7 +716,14 @@ static int launch_prefill(PrefillArgs& a, hipStream_t st) {
     // blocks is heads (n + 1) / 2048 times the n of the longest row block.  One wave or two, at
     // 2.1: 88 / 94 and 335 / 331 us, at 2.0: 579 / 549; two or four, at 1.6: 232 / 261, at 1.1: 264 / 237.
     const int64_t share = heads * (ceil_div(a.L, 32) + 1);
-    if (share >= 4300) hipLaunchKernelGGL((k_prefill_attention32<D, 1>), blocks(32, 256, 64), dim3(64), 0, st, a);
+    // 16 rows a workgroup of eight waves while all of them run at once (two a CU for 64 channels, one for 128), of long rows
+    // also in two rounds.  us, four waves of 32 rows and this: 8 heads of 64 channels, 256 rows (128 workgroups) 11.0
+    // and 7.9; 16 x 8 heads, 64 rows (512) 7.1 and 6.8, 100 rows (896) 9.7 and 11.8; 8 heads, 2048 rows (1024) 61.3 and 54.2;
+    // 128 channels: 32 heads, 100 rows (224) 11.1 and 7.5; 4 x 16 heads, 100 rows (448) 11.4 and 12.3; 8 heads, 1000 rows
+    // (504) 43.3 and 34.8; 12 heads, 1500 rows (1128) 86.9 and 98.4.
+    const int64_t few = heads * ceil_div(a.L, 16), places = D == 64 ? 512 : 256;
+    if (few <= places || (few <= 2 * places && a.L >= 512)) hipLaunchKernelGGL(k_prefill_attention32_few<D>, blocks(16, 32, 512), dim3(512), 0, st, a);
+    else if (share >= 4300) hipLaunchKernelGGL((k_prefill_attention32<D, 1>), blocks(32, 256, 64), dim3(64), 0, st, a);
     else if (share >= 3100) hipLaunchKernelGGL((k_prefill_attention32<D, 2>), blocks(32, 128, 128), dim3(128), 0, st, a);
     else hipLaunchKernelGGL((k_prefill_attention32<D, 4>), blocks(32, 64, 256), dim3(256), 0, st, a);
   } else {
