@@ -173,6 +173,15 @@ static int decode_entry(const zc_tensor4* q, const zc_packed* Kp, const zc_packe
         if (best == 0 || cost < best_cost) { best = c; best_cost = cost; }
       }
       S = (int)best;
+      // One workgroup per CU instead of two: a wave alone on its SIMD issues nearly twice as fast, and the reduction has
+      // half the partials.  Better while each has at most 17 units, of caches with 8-bit codes 45 (from 18 on where
+      // a head has fewer than six).  us per call, two and one: 16 heads of 128 channels, 183 units at 4 and 2 bits (11 each) 9.7 and 8.8,
+      // 276 (17) 10.5 and 9.8; 64 heads, 276 (69) 17.2 and 17.5; of 64 channels, 16 heads, 526 (33) 9.2 and 9.4; at 8 and 4 bits,
+      // 32 heads, 353 (44) 18.5 and 16.5, 128 heads, 58 (29) 15.6 and 13.9, 110 (55) 20.0 and 20.4; 64 heads of 64, 58 (15) 8.7 and 9.1,
+      // 40 heads, 110 (18) 11.7 and 10.6.
+      const int64_t one = a.n_cu / heads, each = one > 0 ? ceil_div64(units, one) : 0;
+      const bool wide = Kp->bits_hi == 8 || Kp->bits_lo == 8;
+      if (one > 0 && one < best && (wide ? each <= 45 && (each >= 18 || one >= 6) : each <= 17)) S = (int)one;
     }
     // Tail: waves of its own.  One unit (16 tokens) per wave while the launch stays
     // below one workgroup per CU; else a share of the waves in proportion to its cost

@@ -849,18 +849,27 @@ static bool probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P,
 }
 static size_t lse_bytes(int64_t B, int64_t Hq, int64_t P) { return (size_t)align_up64(B * Hq * P * (kProbeParts * (int64_t)sizeof(float2) + 4), 256); }
 
-// What a call needs at least; and what it takes on top where sweep 2 joins the pairs of the column ranges, which then
-// lie beside the per-head scores it writes meanwhile: few probes, and one round of workgroups (of several
-// rounds each reads the pairs again: 16 x 40 heads of 128 channels, 4096 tokens, 410 probes: 352 us and a launch of
-// 8.4, joined 398; 32 heads: 19.2 and 4.6, joined 21.4).
+// What a call needs at least; and what it takes on top for the pairs of the column ranges to lie beside the per-head
+// scores, so that sweep 2 can join them while it writes these: where the probes are few and its workgroups one round
+// (of several rounds each reads the pairs again: 16 x 40 heads of 128 channels, 4096 tokens, 410 probes: 352 us
+// and a launch of 8.4, joined 398; 32 heads: 19.2 and 4.6, joined 21.4).  Nothing for up to 64 probes, whose
+// ranges are then at most the kProbeParts there is room for - except in fp32 where that makes the ranges two tiles
+// instead of one (8 heads of 64 channels, 700 tokens, 70 probes: 17.9 us with 11 ranges, 20.2 with 6; a launch more: 19.5).
 static size_t probe_least_bytes(int64_t B, int64_t Hq, int64_t Lk, int64_t P) { return lse_bytes(B, Hq, P) + (size_t)B * Hq * Lk * 4; }
-static size_t join_bytes(int64_t B, int64_t Hq, int64_t Lk, int64_t P) {
-  return P > kProbeTable || ceil_div64(Lk, 128) * Hq * B > 1024 ? 0 : (size_t)align_up64(B * Hq * P * (kMaxProbeParts - kProbeParts) * (int64_t)sizeof(float2), 256);
+constexpr int64_t kJoinWgs = 1024;
+static size_t join_bytes(int64_t B, int64_t Hq, int64_t P) {
+  const int64_t heads = B * Hq < kJoinWgs ? B * Hq : kJoinWgs, rows = P < kProbeTable ? P : kProbeTable;
+  return P <= kLseRows / 2 ? 0 : (size_t)align_up64(heads * rows * (kMaxProbeParts - kProbeParts) * (int64_t)sizeof(float2), 256);
+}
+static bool probe_join(int64_t B, int64_t Hq, int64_t Lk, int64_t P, bool fp32) {
+  const int64_t tiles = ceil_div64(Lk, kLseCols);
+  if (fp32 && P <= kLseRows / 2 && tiles > kProbeParts && tiles <= kMaxProbeParts) return false;
+  return P <= kProbeTable && ceil_div64(Lk, 128) * Hq * B <= kJoinWgs;
 }
 
 extern "C" size_t zc_probe_saliency_workspace(int64_t B, int64_t Hq, int64_t Lk, int64_t P) {
   if (B <= 0 || Hq <= 0 || Lk <= 0 || P <= 0) return 0;
-  return probe_least_bytes(B, Hq, Lk, P) + join_bytes(B, Hq, Lk, P);
+  return probe_least_bytes(B, Hq, Lk, P) + join_bytes(B, Hq, P);
 }
 
 static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
@@ -885,7 +894,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
     // offsets must not wrap either)
     if (q->L * q->sL * eb >= 0xFFFFF000ll || (k->L + 128) * k->sL * eb >= 0xFFFFF000ll || (int64_t)P * 4 >= 0xFFFFF000ll) return ZC_ERR_UNSUPPORTED;
   }
-  const size_t need = probe_least_bytes(q->B, q->H, k->L, P), extra = join_bytes(q->B, q->H, k->L, P);
+  const size_t need = probe_least_bytes(q->B, q->H, k->L, P), extra = join_bytes(q->B, q->H, P);
   if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 15)) return ZC_ERR_WORKSPACE;
 
   ProbeArgs a;
@@ -897,14 +906,14 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse_in = lse_ext;
   a.small = probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));
-  a.join = !lse_ext && !a.small && extra > 0 && ws_bytes >= need + extra;
+  a.join = !lse_ext && !a.small && probe_join(q->B, q->H, k->L, P, q->dtype == ZC_F32) && ws_bytes >= need + extra;
   float* ws_ph = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + lse_bytes(q->B, q->H, P) + (a.join ? extra : 0));
   // [log-sum-exps][column ranges' pairs, up to the end of the workspace: the per-head scores, at
   // their place in it, are written when the pairs have been read]; joined by sweep 2 [pairs][per-head scores]
   const int64_t rows = q->B * q->H * P, lse2_bytes = align_up64(rows * 4, 16), fit = ((int64_t)need - lse2_bytes) / (rows * (int64_t)sizeof(float2));
   a.lse2 = reinterpret_cast<float*>(ws);
   a.lse_part = reinterpret_cast<float2*>(reinterpret_cast<uint8_t*>(ws) + (a.join ? 0 : lse2_bytes));
-  a.max_parts = (int)(a.join || fit > kMaxProbeParts ? kMaxProbeParts : fit);
+  a.max_parts = (int)(a.join ? (extra > 0 ? kMaxProbeParts : kProbeParts) : fit < kMaxProbeParts ? fit : kMaxProbeParts);
   const int64_t head_wgs = probe_head_wgs(q->B, q->H, P, k->L, a.max_parts, q->dtype == ZC_F32);
   a.head_wgs = (int)head_wgs;
   if (head_wgs <= ceil_div64(P, kLseRows)) a.join = 0;     // (one range a row block: its log-sum-exps are in lse2)
