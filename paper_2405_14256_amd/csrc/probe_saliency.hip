@@ -853,17 +853,16 @@ static size_t lse_bytes(int64_t B, int64_t Hq, int64_t P) { return (size_t)align
 // scores, so that sweep 2 can join them while it writes these: where the probes are few and its workgroups one round
 // (of several rounds each reads the pairs again: 16 x 40 heads of 128 channels, 4096 tokens, 410 probes: 352 us
 // and a launch of 8.4, joined 398; 32 heads: 19.2 and 4.6, joined 21.4).  Nothing for up to 64 probes, whose
-// ranges are then at most the kProbeParts there is room for - except in fp32 where that makes the ranges two tiles
-// instead of one (8 heads of 64 channels, 700 tokens, 70 probes: 17.9 us with 11 ranges, 20.2 with 6; a launch more: 19.5).
+// ranges are then at most the kProbeParts there is room for: where that makes them of two tiles instead of one it is
+// still the better way (fp32, 64 probes of 640 tokens, us per call with a launch of its own over 10 ranges and joined:
+// 32 heads of 128 channels 23.4 and 20.8, 4 x 16 of 64 22.9 and 20.6; only 4 heads lose, 700 tokens: 20.6 and 20.9).
 static size_t probe_least_bytes(int64_t B, int64_t Hq, int64_t Lk, int64_t P) { return lse_bytes(B, Hq, P) + (size_t)B * Hq * Lk * 4; }
 constexpr int64_t kJoinWgs = 1024;
 static size_t join_bytes(int64_t B, int64_t Hq, int64_t P) {
   const int64_t heads = B * Hq < kJoinWgs ? B * Hq : kJoinWgs, rows = P < kProbeTable ? P : kProbeTable;
   return P <= kLseRows / 2 ? 0 : (size_t)align_up64(heads * rows * (kMaxProbeParts - kProbeParts) * (int64_t)sizeof(float2), 256);
 }
-static bool probe_join(int64_t B, int64_t Hq, int64_t Lk, int64_t P, bool fp32) {
-  const int64_t tiles = ceil_div64(Lk, kLseCols);
-  if (fp32 && P <= kLseRows / 2 && tiles > kProbeParts && tiles <= kMaxProbeParts) return false;
+static bool probe_join(int64_t B, int64_t Hq, int64_t Lk, int64_t P) {
   return P <= kProbeTable && ceil_div64(Lk, 128) * Hq * B <= kJoinWgs;
 }
 
@@ -906,7 +905,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse_in = lse_ext;
   a.small = probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));
-  a.join = !lse_ext && !a.small && probe_join(q->B, q->H, k->L, P, q->dtype == ZC_F32) && ws_bytes >= need + extra;
+  a.join = !lse_ext && !a.small && probe_join(q->B, q->H, k->L, P) && ws_bytes >= need + extra;
   float* ws_ph = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + lse_bytes(q->B, q->H, P) + (a.join ? extra : 0));
   // [log-sum-exps][column ranges' pairs, up to the end of the workspace: the per-head scores, at
   // their place in it, are written when the pairs have been read]; joined by sweep 2 [pairs][per-head scores]
