@@ -58,3 +58,38 @@ def test_decode_with_8_bit_codes(bits, dtype, d, B, Hkv, G, q_scale, v_scale):
         err = float((out.double() - want).norm() / want.norm())
         tol = {torch.float32: 1e-6 + 4e-7 * spread, torch.float16: 2.3e-4 if v_scale >= 1 else 3.3e-4, torch.bfloat16: 2e-3}[dtype]
         assert err <= tol, (k_scheme, v_scheme, err, spread)
+
+
+@pytest.mark.parametrize("B,Hkv,L,bits", [(2, 8, 8000, (4, 2)), (2, 8, 8400, (4, 2)),                                      # 17 units a workgroup of one per CU, 18
+                                          (4, 8, 7901, (8, 4)), (4, 8, 8300, (8, 4)),                                      # 44, 46
+                                          (8, 8, 700, (8, 4)), (8, 8, 2000, (8, 4)),                                       # few for four a head, enough
+                                          (3, 12, 1300, (4, 4)), (100, 3, 300, (4, 2))])                                   # seven a head; more heads than CUs
+def test_decode_with_one_or_two_workgroups_a_cu(B, Hkv, L, bits):
+    """Either side of the rule by which a launch takes one workgroup per compute unit: every sequence
+    of a batch of equal ones has the answer that it has alone, but for the order of the partial sums."""
+    d, G, T = 128, 2, 37
+    g = torch.Generator().manual_seed(L)
+    lib = zb.load()
+    X = torch.randn(2, 1, Hkv, L + T, d, generator=g).to(DEV)
+    q = torch.randn(1, Hkv * G, d, generator=g).to(DEV)
+    scores = torch.rand(1, L, generator=g).to(DEV)
+    k = L // 5
+    res = []
+    for n in (1, B):
+        K, V = (x.expand(n, -1, -1, -1).contiguous() for x in X)
+        sal, reg = zb.zc_select_salient(scores.expand(n, -1).contiguous(), k)
+        mk = lambda s, layout: zb.PackedTensor(n, Hkv, d, lib.zc_arena_slots(k, 1), lib.zc_arena_slots(L - k, 1), *bits, s, layout, max_chunks=1, device=DEV)
+        Kp, Vp = mk("channel", zb.ZC_LAYOUT_ROW), mk("cst", zb.ZC_LAYOUT_TGROUP)
+        zb.zc_quantize_pack(K[:, :, :L], sal, reg, Kp)
+        zb.zc_quantize_pack(V[:, :, :L], sal, reg, Vp)
+        lse = torch.empty(n, Hkv * G, dtype=torch.float32, device=DEV)
+        out = zb.zc_decode_attention(q.expand(n, -1, -1).contiguous(), Kp, Vp, K[:, :, L:], V[:, :, L:], T, lse_out=lse)
+        res.append((out, lse))
+    (one, lse1), (out, lse) = res
+    assert torch.equal(out, out[:1].expand_as(out)) and torch.equal(lse, lse[:1].expand_as(lse))
+    # A sum of L weights of at most a few units in chains of L / 32 and more: each term is off by 2^-24 of the
+    # sum so far, which adds up like a random walk - 2^-24 sqrt(L) - times what the values' spread leaves.
+    # Either order has this error; four times both is 2^-21 sqrt(L) of the largest output.
+    tol = 2.0 ** -21 * L ** 0.5
+    assert float((lse - lse1).abs().max()) <= tol
+    assert float((out - one).abs().max()) <= tol * max(1.0, float(one.abs().max()))

@@ -99,3 +99,46 @@ def test_keys_of_more_threads_than_a_launch_counts():
     a, b = many.codes_lo.view(128, -1, 16), few.codes_lo.view(128, -1, 16)
     for i, r in enumerate(rows):
         assert torch.equal(a[:, r], b[:, i]), r
+
+
+@pytest.mark.parametrize("kind", ["tame", "nan", "wild"])
+@pytest.mark.parametrize("n", [1, 2, 63, 517, 2600])
+def test_two_bit_fp16_keys_by_thresholds(n, kind):
+    """2-bit codes of fp16 keys that stay in registers, found by three thresholds a channel, against those
+    of the kernel that divides every value (another layout, so another path): the same codes where
+    values are ties of the rounding and one number beside them, equal, zeros of both signs, subnormal,
+    the largest, far from zero in a narrow range, a NaN, or of a range without thresholds."""
+    from tests.pipeline_check import packed_to_chunks
+    H, D = 3, 64
+    g = torch.Generator().manual_seed(n)
+    X = torch.randn(1, H, n, D, generator=g)
+    steps = torch.randint(0, 7, (H, n), generator=g).float()
+    at = lambda ch, x: X[0, :, :, ch].copy_(x)
+    for i, scale in enumerate((1.0, 0.75, 3.1, 2.0 ** -14, 2.0 ** -22, 9000.0)):
+        at(i, scale * steps / 2)                                                            # every half step: ties
+        at(8 + i, (scale * steps / 2).half().view(torch.int16).add((steps % 3 - 1).short() * (steps > 0)).view(torch.float16).float())
+        at(16 + i, scale * (steps / 2 - 1.7))                                               # a zero point between
+    at(24, torch.full((H, n), 0.3))
+    at(25, torch.zeros(H, n))
+    at(26, torch.where(steps > 3, 0.0, -0.0))
+    at(27, torch.where(steps > 3, 65504.0, -65504.0))
+    at(28, 1000.0 + steps / 2)
+    at(29, -3.0 - steps * 2.0 ** -8)
+    at(30, 2.0 ** -24 * (steps - 3))
+    X = X.to(torch.float16)
+    if kind == "nan":
+        X[0, 0, n // 2, 5] = X[0, 2, 0, 63] = float("nan")
+    if kind == "wild":
+        X[0, 1, n // 2, 33] = float("inf")
+        X[0, 2, 0, 12] = -float("inf")
+    X = X.to(DEV)
+    idx = torch.arange(n, dtype=torch.int32, device=DEV)[None]
+    none = idx[:, :0]
+    got = []
+    for layout in (zb.ZC_LAYOUT_ROW, zb.ZC_LAYOUT_TGROUP):
+        p = _packed(("channel", layout), 1, H, D, 64, zb.load().zc_arena_slots(n, 1), (4, 2))
+        zb.zc_quantize_pack(X, none, idx, p)
+        got.append((torch.as_tensor(packed_to_chunks(p, [0])[0].lo.codes), p.chan_scale.clone(), p.chan_zero.clone()))
+    (row, *params), (tgroup, *want) = got
+    assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(params, want))
+    assert torch.equal(row, tgroup), (row != tgroup).nonzero()[:8]
