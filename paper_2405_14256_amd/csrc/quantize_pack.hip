@@ -342,19 +342,21 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
   // rows past the end repeat the last one (minima do not care).
   if (!SPLIT && a.resident) {
     int32_t tok[NR];
+    // (every wave has a first row, if only the last one again: a channel of nothing but NaN has NaN for its range)
+    const auto has = [&](int r) { return r == 0 ? n > 0 : r * step + y0 < n; };
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (r * step + y0 < n) tok[r] = idx[min(r * step + y, n - 1)];
+      if (has(r)) tok[r] = idx[min(r * step + y, n - 1)];
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (r * step + y0 < n) {
+      if (has(r)) {
         const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)tok[r] * row_bytes);
 #pragma unroll
         for (int q = 0; q < RAW; ++q) raw[r][q] = src[q];
       }
 #pragma unroll
     for (int r = 0; r < NR; ++r)
-      if (r * step + y0 < n) reduce(raw[r]);
+      if (has(r)) reduce(raw[r]);
     // (all rows are here; the compiler, which does not see that a row that was requested has been reduced, would wait for
     // each again where it is packed - and with it for the codes stored before)
     __builtin_amdgcn_s_waitcnt(0x0F70);                        // vmcnt(0)
