@@ -156,7 +156,7 @@ static int decode_entry(const zc_tensor4* q, const zc_packed* Kp, const zc_packe
   a.pw_q = a.pw_r = a.tu_q = a.tu_r = 0;
   {
     const int64_t heads = q->B * Kp->H;
-    const int64_t tail_units = ceil_div64(tail_len, kTailUnit);
+    const int64_t tail_units = ceil_div64(tail_len, kTailUnit), tail_cost = tail_units > 0 ? 2 * tail_units + kSegCost : 0;
     // Packed cache.  About eight cost units per workgroup is the finest useful split;
     // the reduce kernel reads at most 32 partials per head.
     int64_t want = ceil_div64(units, 8);
@@ -173,15 +173,18 @@ static int decode_entry(const zc_tensor4* q, const zc_packed* Kp, const zc_packe
         if (best == 0 || cost < best_cost) { best = c; best_cost = cost; }
       }
       S = (int)best;
-      // One workgroup per CU instead of two: a wave alone on its SIMD issues nearly twice as fast, and the reduction has
-      // half the partials.  Better while each has at most 17 units, of caches with 8-bit codes 45 (from 18 on where
-      // a head has fewer than six).  us per call, two and one: 16 heads of 128 channels, 183 units at 4 and 2 bits (11 each) 9.7 and 8.8,
-      // 276 (17) 10.5 and 9.8; 64 heads, 276 (69) 17.2 and 17.5; of 64 channels, 16 heads, 526 (33) 9.2 and 9.4; at 8 and 4 bits,
-      // 32 heads, 353 (44) 18.5 and 16.5, 128 heads, 58 (29) 15.6 and 13.9, 110 (55) 20.0 and 20.4; 64 heads of 64, 58 (15) 8.7 and 9.1,
-      // 40 heads, 110 (18) 11.7 and 10.6.
-      const int64_t one = a.n_cu / heads, each = one > 0 ? ceil_div64(units, one) : 0;
-      const bool wide = Kp->bits_hi == 8 || Kp->bits_lo == 8;
-      if (one > 0 && one < best && (wide ? each <= 45 && (each >= 18 || one >= 6) : each <= 17)) S = (int)one;
+      // One workgroup per CU instead of two: a wave alone on its SIMD issues faster, and half the partials to reduce are
+      // worth two units (a workgroup that is alone with its head writes the result itself: the launch that reduces is
+      // worth twelve); but a unit takes it kLone / 32 of what one takes each of two (the last row: alone with its head), and `one`
+      // may leave CUs idle.  us per call with 57 tokens of tail, two and one: 64 heads of 128 channels at 4 and 2 bits,
+      // 14 units each 10.7 and 10.1, 20 units 11.0 and 10.8, 28 (takes two) 12.2 and 12.7; 16 heads of 64, 12 units 8.3 and 7.7, 20
+      // (two) 8.9 and 8.8, 32 (two) 9.7 and 10.0; 32 heads of 128 at 8 and 4 bits, 36 units 17.9 and 15.5, 110 (two) 30.0 and 30.2; of
+      // 64, 14 units 9.2 and 8.7, 50 (two) 13.8 and 14.7; 86 heads of 64, where one leaves a third of the CUs idle, 24 units (two)
+      // 10.0 and 10.4; 12 heads of 64, where two are on half the CUs only, 44 units 14.2 and 13.2.
+      constexpr int64_t kLone[3][3] = {{21, 20, 19}, {19, 17, 16}, {23, 22, 20}};      // 64 channels, 128; none, one or both code widths 8 bits
+      const int64_t one = a.n_cu / heads, gain = one == 1 ? 12 : 2;
+      const int64_t lone = kLone[one == 1 ? 2 : q->D == 128][(Kp->bits_hi == 8) + (Kp->bits_lo == 8)];
+      if (one > 0 && one < best && lone * ceil_div64(units + tail_cost, one) <= 32 * (gain + ceil_div64(units + tail_cost, best))) S = (int)one;
     }
     // Tail: waves of its own.  One unit (16 tokens) per wave while the launch stays
     // below one workgroup per CU; else a share of the waves in proportion to its cost
@@ -193,7 +196,6 @@ static int decode_entry(const zc_tensor4* q, const zc_packed* Kp, const zc_packe
         n_tw = tail_units;
         extra_waves = true;
       } else {
-        const int64_t tail_cost = 2 * tail_units + kSegCost;
         n_tw = (4 * S * tail_cost + (units + tail_cost) / 2) / (units + tail_cost);
         if (n_tw < 1) n_tw = 1;
         if (n_tw > 4 * S - 1) n_tw = 4 * S - 1;

@@ -60,14 +60,39 @@ def test_decode_with_8_bit_codes(bits, dtype, d, B, Hkv, G, q_scale, v_scale):
         assert err <= tol, (k_scheme, v_scheme, err, spread)
 
 
-@pytest.mark.parametrize("B,Hkv,L,bits", [(2, 8, 8000, (4, 2)), (2, 8, 8400, (4, 2)),                                      # 17 units a workgroup of one per CU, 18
-                                          (4, 8, 7901, (8, 4)), (4, 8, 8300, (8, 4)),                                      # 44, 46
-                                          (8, 8, 700, (8, 4)), (8, 8, 2000, (8, 4)),                                       # few for four a head, enough
-                                          (3, 12, 1300, (4, 4)), (100, 3, 300, (4, 2))])                                   # seven a head; more heads than CUs
-def test_decode_with_one_or_two_workgroups_a_cu(B, Hkv, L, bits):
+def workgroups_of_a_head(B, Hkv, d, sizes, T, bits, cus=256):
+    """What a launch chooses from for a cache of one chunk: (cost units of a head, its workgroups where a CU has two, where it
+    has one, whether the latter are taken), or None where all workgroups of the finest split fit one per CU."""
+    ceil = lambda a, b: -(-a // b)
+    units = sum(ceil(n, 16 if b == 8 else 32) + 3 for n, b in zip(sizes, bits) if n)
+    heads, finest = B * Hkv, min(ceil(units, 8), 32)
+    if heads * finest <= cus:
+        return None
+    two = min(range(1, finest + 1), key=lambda c: ceil(heads * c, 2 * cus) * (48 + ceil(units, c)))
+    one, tail = cus // heads, 2 * ceil(T, 16) + 3
+    lone = ((21, 20, 19), (19, 17, 16), (23, 22, 20))[2 if one == 1 else d == 128][bits.count(8)]
+    gain = 12 if one == 1 else 2
+    return units, two, one, 0 < one < two and lone * ceil(units + tail, one) <= 32 * (gain + ceil(units + tail, two))
+
+
+# Pairs on either side of the rule, at both head widths and every number of 8-bit widths; a head with two workgroups, where one
+# of a CU leaves a third of the chip idle; a head to a workgroup; 12 heads, which two only give half the CUs; too few units to ask;
+# more heads than CUs
+@pytest.mark.parametrize("B,Hkv,d,L,bits,one", [
+    (2, 8, 128, 10300, (4, 2), True), (2, 8, 128, 12800, (4, 2), False), (8, 8, 128, 2200, (4, 4), True), (8, 8, 128, 2900, (4, 4), False),
+    (2, 8, 64, 7600, (4, 2), True), (2, 8, 64, 10400, (2, 4), False), (4, 8, 128, 13400, (8, 4), True), (4, 8, 128, 20000, (8, 4), False),
+    (4, 8, 64, 3000, (8, 2), True), (4, 8, 64, 3600, (2, 8), False), (8, 8, 64, 1300, (8, 8), True), (8, 8, 64, 1500, (8, 8), False),
+    (16, 8, 128, 3000, (8, 8), True), (10, 9, 64, 400, (8, 4), True), (10, 9, 64, 700, (8, 4), False), (43, 2, 128, 800, (2, 2), True),
+    (43, 2, 128, 1000, (2, 2), False), (25, 8, 64, 1100, (4, 2), True), (25, 8, 64, 1700, (4, 2), False), (31, 8, 128, 900, (8, 8), True),
+    (43, 4, 128, 1500, (8, 8), False), (1, 12, 64, 9000, (2, 8), True), (3, 12, 128, 1300, (4, 4), None), (100, 3, 128, 300, (4, 2), False),
+    (2, 8, 128, 8000, (4, 2), True), (2, 8, 128, 8400, (4, 2), True), (4, 8, 128, 7901, (8, 4), True), (4, 8, 128, 8300, (8, 4), True),
+    (8, 8, 128, 700, (8, 4), True), (8, 8, 128, 2000, (8, 4), True)])
+def test_decode_with_one_or_two_workgroups_a_cu(B, Hkv, d, L, bits, one):
     """Either side of the rule by which a launch takes one workgroup per compute unit: every sequence
     of a batch of equal ones has the answer that it has alone, but for the order of the partial sums."""
-    d, G, T = 128, 2, 37
+    G, T = 2, 37
+    rule = workgroups_of_a_head(B, Hkv, d, (L // 5, L - L // 5), T, bits)
+    assert one == (rule and rule[3]), rule
     g = torch.Generator().manual_seed(L)
     lib = zb.load()
     X = torch.randn(2, 1, Hkv, L + T, d, generator=g).to(DEV)
@@ -85,11 +110,11 @@ def test_decode_with_one_or_two_workgroups_a_cu(B, Hkv, L, bits):
         lse = torch.empty(n, Hkv * G, dtype=torch.float32, device=DEV)
         out = zb.zc_decode_attention(q.expand(n, -1, -1).contiguous(), Kp, Vp, K[:, :, L:], V[:, :, L:], T, lse_out=lse)
         res.append((out, lse))
-    (one, lse1), (out, lse) = res
+    (alone, lse1), (out, lse) = res
     assert torch.equal(out, out[:1].expand_as(out)) and torch.equal(lse, lse[:1].expand_as(lse))
     # A sum of L weights of at most a few units in chains of L / 32 and more: each term is off by 2^-24 of the
     # sum so far, which adds up like a random walk - 2^-24 sqrt(L) - times what the values' spread leaves.
     # Either order has this error; four times both is 2^-21 sqrt(L) of the largest output.
     tol = 2.0 ** -21 * L ** 0.5
     assert float((lse - lse1).abs().max()) <= tol
-    assert float((out - one).abs().max()) <= tol * max(1.0, float(one.abs().max()))
+    assert float((out - alone).abs().max()) <= tol * max(1.0, float(alone.abs().max()))
