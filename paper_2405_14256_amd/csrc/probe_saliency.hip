@@ -393,9 +393,15 @@ __global__ __launch_bounds__(64) void k_probe_lse_merge(ProbeArgs a) {
   }
 }
 
-// Four workgroups to a CU (128 registers, 37 KB of LDS) for rows of up to 256 bytes, so that four
+// Four workgroups to a CU (128 registers, 38.5 KB of LDS) for rows of up to 256 bytes, so that four
 // independent waves a SIMD overlap matrix and vector work and 1024 workgroups start at once.
-template <int DT, int D>
+// An instance each for up to kProbeTable probes, for such whose pairs it joins, and for more: as branches of one
+// kernel they were 10.8 KB of cold code instead of 6.8 to 8.8, and a lone wave paid their scalar tests in every tile.  us given
+// normalisers, one kernel and three: 32 heads of 128 channels, 4096 tokens, 64 probes 9.6 and 9.0, 410 18.0 and 16.9; all rows of a
+// head of 64 channels as probes, 8192 rows 104 and 94, 8 heads of 2048 30.6 and 28.3 (tiles behind the first open one are no longer
+// asked for their first position either).
+enum class Probes { Few, FewJoined, Many };
+template <int DT, int D, Probes PROBES>
 __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_probe_colsum(ProbeArgs a) {
   using T = Tile<DT, D>;
   constexpr int QT = 64;                        // probe rows per tile
@@ -411,6 +417,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   float (*scol)[128] = reinterpret_cast<float (*)[128]>(&Qs[0][0]);     // (in the place of the tiles, at the end)
   __shared__ int bins[128];                     // probes at each of this workgroup's columns
   __shared__ __align__(16) int before[4];       // probes in front of them, by wave
+  static_assert(T::ROWB > 256 || (sizeof(Qs) + sizeof(spos) + sizeof(srow) + sizeof(slse) + sizeof(bins) + sizeof(before) + 2047) / 2048 * 8 <= 160, "four workgroups to a CU");
 
   // Logical order: the first columns, which the most probes see, of all heads of a group, then the next ones: the
   // last workgroups to start are the shortest, and a CU's workgroups, 32 apart in an XCD's range, see few
@@ -419,7 +426,9 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   // head, every other one backwards.  us given normalisers, head after head and so: 2 x 32 heads, 3001 tokens
   // 23.4 and 22.7; 24 heads, 9000 tokens 52.4 and 47.1; 32 heads, 32768 tokens 665 and 632; 16 x 16 heads of 64,
   // 2000 tokens 30.9 and 27.9; 32 heads, 4096 tokens 18.7 and 18.0, fp32 111 and 98; up to a
-  // workgroup a CU the divisions only cost time (16 x 8 heads of 64, 400 tokens 7.1 and 7.3).
+  // workgroup a CU the divisions only cost time (16 x 8 heads of 64, 400 tokens 7.1 and 7.3), and of up to 64
+  // probes in 16 bits every workgroup has as much to do (32 heads, 8192 tokens 12.8 and 13.2; in fp32 the matrix cores do less
+  // where 32 rows see the columns: 16 x 16 heads, 500 tokens, both sweeps 62.7 and 61.2).
   const int nct = ceil_div(a.Lk, 128);
   int j, ct;
   if (a.group) {
@@ -453,7 +462,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   // Meanwhile the K columns come through the two tile buffers (whole rows to a transfer, as in
   // sweep 1; columns past the end: zeros).
   const uint32_t qs_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&Qs[0][0];
-  const bool table = a.P <= kProbeTable;
+  constexpr bool table = PROBES != Probes::Many, join = PROBES == Probes::FewJoined;
   constexpr int NT = kProbeTable / 256;
   int tpos[NT], trow[NT];
   float tlse[NT];
@@ -469,7 +478,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
       n += real && pos < col0 ? 1 : 0;
       if (real && (uint32_t)(pos - col0) < 128u) atomicAdd(&bins[pos - col0], 1);
     };
-    if (table) {
+    if constexpr (table) {
       // few probes: all that is to be looked up of them comes with the positions
       RowPairs pairs[NT];
 #pragma unroll
@@ -478,7 +487,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
           const int i = u * 256 + tid;
           tpos[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_pos, i * 4, 0, 0);
           trow[u] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_row, i * 4, 0, 0);
-          if (__builtin_expect(a.join, 0)) pairs[u].load(a, (int64_t)b * a.Hq + hq, min(i, a.P - 1));
+          if constexpr (join) pairs[u].load(a, (int64_t)b * a.Hq + hq, min(i, a.P - 1));
           else tlse[u] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs_lse, i * 4, 0, 0));
         }
       __syncthreads();                           // (the bins are empty)
@@ -486,7 +495,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
       for (int u = 0; u < NT; ++u)
         if (u * 256 < a.P) {
           count(u * 256 + tid < a.P, tpos[u]);
-          if (__builtin_expect(a.join, 0)) tlse[u] = pairs[u].joined(a);
+          if constexpr (join) tlse[u] = pairs[u].joined(a);
           else if (a.lse_in) tlse[u] *= kLog2e;  // an external log-sum-exp is in natural units
         }
     } else {
@@ -514,7 +523,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   float colsum[2] = {0.f, 0.f};
 
   // What a tile of 64 probe rows is looked up by: all of it is in LDS where the probes are few; otherwise one half of
-  // the table is filled while the tiles of the other are worked on, every wave a quarter of it.  (Past the
+  // the table is filled under the first tile of the other, every wave a quarter of it.  (Past the
   // last probe: row 0 of q, which a position of -1 masks.)  The tile itself goes global -> LDS directly one
   // ahead, every wave a quarter of its transfers.
   const uint32_t spos_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) int*)&spos[0];
@@ -546,7 +555,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
     }
   };
   if (pstart < a.P) {
-    if (table) {
+    if constexpr (table) {
 #pragma unroll
       for (int u = 0; u < NT; ++u) {
         const int at = u * 256 + tid - pstart;
@@ -568,35 +577,32 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   const int wcol0 = col0 + cbp * 64;             // this wave's columns: wcol0 .. + 63; of a tile, its rows rbw * 32 .. + 31
   const int pend = a.P - rbw * 32;
 
+  const int even_from = a.even2 ? a.P - a.even2 : 0x7fffffff;
   if (a.even2) priority_by_tiles((a.P - pstart + QT - 1) / QT);
   int at = 0, cur = 0;
-  int until = table ? 0x7fffffff : kHalf / QT;   // tiles to the next step of filling the table
-  bool ahead = false;                            // the newest loads are those of a fetch
+  int refill = pstart + kHalf;                   // the first tile of a half: the other one is free; the second: it is full
+  bool open = false;                             // (positions ascend: what is visible stays visible)
   for (int pr = pstart; pr < a.P; pr += QT) {
-    if (ahead) __builtin_amdgcn_s_waitcnt(0x0F73);       // vmcnt(3)
-    else wait_all_loads();   // this wave's transfers of the tile have landed ...
-    __syncthreads();         // ... and everyone's; nobody still reads the other buffer
-    ahead = false;
-    const int next = (at + QT) & (kProbeTable - 1);
-    if (pr + QT < a.P) issue(next, cur ^ 1);
-    if (a.P - pr <= a.even2) priority_by_tiles((a.P - pr + QT - 1) / QT);
-    if (until == 0) {                            // the first tile of a half: the other one is free; the third: it is full
-      const int entry = pr - pstart;
-      if (entry & (2 * QT)) fetched(entry - 2 * QT + kHalf);
-      else {
-        fetch(entry + kHalf);
-        ahead = true;
+    wait_all_loads();    // this wave's transfers of the tile have landed ...
+    __syncthreads();     // ... and everyone's; nobody still reads the other buffer
+    if constexpr (!table) {
+      if (__builtin_expect(pr == refill, 0)) {
+        const int entry = pr - pstart;
+        if (entry & QT) { fetched(entry - QT + kHalf); refill += kHalf - QT; }
+        else { fetch(entry + kHalf); refill += QT; }
       }
-      until = 2;
     }
-    --until;
-    if (pr < pend) {                             // (no probe in the wave's rows of a last tile)
+    const int next = (at + QT) & (kProbeTable - 1);
+    if (__builtin_expect(pr + QT < a.P, 1)) issue(next, cur ^ 1);
+    if (__builtin_expect(pr >= even_from, 0)) priority_by_tiles((a.P - pr + QT - 1) / QT);
+    if (__builtin_expect(pr < pend, 1)) {        // (no probe in the wave's rows of a last tile)
       v16f acc[2];
       products<DT, 2>(acc, abase + cur * TILE_B, kf);
       __builtin_amdgcn_sched_barrier(0);         // (what follows would be moved up, into registers there are not)
       const float4* rl4 = reinterpret_cast<const float4*>(&slse[at + rbw * 32 + 4 * kh]);     // rows 8 g + 4 kh ..
       // 32 real rows whose first position is past the wave's last column need no mask
-      if (pr + 32 <= pend && wcol0 + 63 <= __builtin_amdgcn_readfirstlane(spos[at + rbw * 32])) {
+      if (!open) open = wcol0 + 63 <= __builtin_amdgcn_readfirstlane(spos[at + rbw * 32]);
+      if (open && pr + 32 <= pend) {
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const float4 t = rl4[2 * g];
@@ -781,7 +787,10 @@ static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStr
     ZC_LAUNCH_CHECK();
     return ZC_OK;
   }
-  hipLaunchKernelGGL((k_probe_colsum<DT, D>), dim3((unsigned)((int64_t)ceil_div(a.Lk, 128) * a.Hq * a.B)), dim3(256), 0, st, a);
+  const dim3 grid2((unsigned)((int64_t)ceil_div(a.Lk, 128) * a.Hq * a.B));
+  if (a.P > kProbeTable) hipLaunchKernelGGL((k_probe_colsum<DT, D, Probes::Many>), grid2, dim3(256), 0, st, a);
+  else if (a.join) hipLaunchKernelGGL((k_probe_colsum<DT, D, Probes::FewJoined>), grid2, dim3(256), 0, st, a);
+  else hipLaunchKernelGGL((k_probe_colsum<DT, D, Probes::Few>), grid2, dim3(256), 0, st, a);
   ZC_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_probe_mean, dim3(ceil_div(a.Lk, 64), a.B), dim3(64, 4), 0, st, a.per_head, scores, a.Hq, a.Lk);
   ZC_LAUNCH_CHECK();
@@ -923,7 +932,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.even2 = even_waves(wgs2, P / 64.0, q) ? kEvenTiles * 64 : 0;
   {
     const int64_t nct = ceil_div64(k->L, 128), heads = q->B * q->H, hpx = heads / 8, least = ceil_div64(256, nct), groups = hpx / least;
-    a.group = heads % 8 == 0 && wgs2 > 256 ? (int)(groups > 1 ? ceil_div64(hpx, groups) : hpx) : 0;
+    a.group = heads % 8 == 0 && wgs2 > 256 && (P > 64 || q->dtype == ZC_F32) ? (int)(groups > 1 ? ceil_div64(hpx, groups) : hpx) : 0;
   }
   a.normalize = normalize ? 1 : 0;
   a.per_head = scores_per_head || a.small ? scores_per_head : ws_ph;       // (few rows: only where the caller asks for them)

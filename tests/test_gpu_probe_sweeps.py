@@ -56,6 +56,11 @@ CASES = [
     (1, 2, 1, 128, 3000, torch.float32, lambda L: spread(L, 513)),
     (1, 2, 2, 64, 2600, torch.bfloat16, lambda L: torch.arange(L - 1100, L)),
     (1, 32, 8, 128, 2100, torch.bfloat16, lambda L: torch.cat([spread(L - 110, 110), torch.arange(L - 110, L)]).unique()),
+    # more probes than are looked up at once: two halves of the table and a row, three, six and the last tile ragged, one that sees
+    # the first columns only
+    (1, 2, 1, 64, 2000, torch.float16, lambda L: torch.arange(L - 769, L)),
+    (1, 3, 3, 128, 1600, torch.bfloat16, lambda L: torch.arange(1538)),
+    (1, 2, 2, 64, 3000, torch.float32, lambda L: torch.cat([torch.arange(90), spread(L, 700)]).unique()),
 ]
 
 
