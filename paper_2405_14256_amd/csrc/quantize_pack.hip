@@ -71,7 +71,24 @@ __device__ inline void store_params(const QPArgs& a, int b, int sub, int w, floa
 
 struct QPPair { QPArgs t[2]; };   // keys and values of one cache, compressed by the same launches
 
-// What the quantizer needs of a channel whose values span [lo, hi]; n tokens (0: defaults).
+// The bits of x as a number of their own: this file is compiled as if there were no NaN, and a test of a float's
+// bits that only a NaN passes would be taken for the one it amounts to.
+__device__ inline uint32_t bits_of(float x) {
+  uint32_t b = __float_as_uint(x);
+  asm("" : "+v"(b));
+  return b;
+}
+// All bits (a NaN's) if no number was among a channel's values - its minimum and that of -x are then where they began, or
+// NaN - else none.  (Without branches: they would be cold code in a chain that all workgroups of a small launch wait for.)
+__device__ inline uint32_t no_number(float lo, float neg) {
+  const uint32_t inf = 0x7f800000u, a = bits_of(lo), b = bits_of(neg);
+  uint32_t m = ((a & 0x7fffffffu) > inf) | ((b & 0x7fffffffu) > inf) | ((a == inf) & (b == inf)) ? ~0u : 0u;
+  asm("" : "+v"(m));
+  return m;
+}
+
+// What the quantizer needs of a channel whose values span [lo, hi]; n tokens (0: defaults).  Channelwise, one without any
+// number has NaN for its parameters.
 __device__ inline float3 channel_params(int scheme, int n, float qmax, float lo, float hi, float* cs, float* cz) {
   *cs = 1.f; *cz = 0.f;
   if (n > 0 && scheme == ZC_SCHEME_CST) {
@@ -83,9 +100,11 @@ __device__ inline float3 channel_params(int scheme, int n, float qmax, float lo,
   if (n > 0 && scheme == ZC_SCHEME_CHANNEL) {
     float R = hi - lo;                                     // Eq. 5: s = R / (2^k - 1)
     if (R == 0.f) R = qmax;                                // max == min: s := 1
-    *cs = R / qmax;
-    *cz = -rintf(refined_ratio(lo, qmax, R, 1.f / R));
-    return make_float3(1.f / R, *cz, R);
+    const uint32_t none = no_number(lo, -hi);
+    const auto or_nan = [&](float x) { return __uint_as_float(__float_as_uint(x) | none); };
+    *cs = or_nan(R / qmax);
+    *cz = or_nan(-rintf(refined_ratio(lo, qmax, R, 1.f / R)));
+    return make_float3(or_nan(1.f / R), *cz, or_nan(R));
   }
   return make_float3(1.f, 0.f, 1.f);
 }
@@ -238,7 +257,11 @@ __device__ inline void store_row_codes(uint8_t* row, const float (&x)[8], const 
 // the least fp16 numbers whose code is 1, 2 and 3.  Two values at a time (the sign of x - t, which is exact), a code
 // takes 4 instructions instead of 9.  (bf16 would take 5, with saturating differences of order-preserving integers: no
 // faster where the chip is full, and finding the thresholds costs 0.6 us where it is not.)
-constexpr float kTameRange = 0x1p60f, kTameOffset = 0x1p20f;      // ranges and zero points beyond: the general path
+// Ranges from 2^60 on or up to 2^-60 and zero points above 2^20, NaN among them (bits of larger ones are larger): the general path.
+__device__ inline bool has_thresholds(float z, float R) {
+  const uint32_t r = bits_of(R);
+  return r > 0x21800000u && r < 0x5d800000u && (bits_of(z) & 0x7fffffffu) <= 0x49800000u;
+}
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
 // Order-preserving integer of a 16-bit float's bits, and back.
@@ -291,11 +314,12 @@ __device__ inline uint16_t threshold_codes(const uint4& raw, const uint4 (&t)[3]
   return (uint16_t)__builtin_amdgcn_bitop3_b32(m.quad, w >> 16, w >> 2, 0x35);      // (the complement of select_bits)
 }
 
-// sum + 0 x for the 8 values of x: a NaN if one of them is.
-__device__ inline float plus_zero_times(float sum, const uint4& x, uint32_t zero) {
+// sum + 0 x for the 8 values of x, two at a time: not zero where one of them is a NaN.  (Written out: the compiler may drop
+// arithmetic that only a NaN gets through.)
+__device__ inline uint32_t plus_zero_times(uint32_t sum, const uint4& x) {
   const uint32_t x4[4] = {x.x, x.y, x.z, x.w};
 #pragma unroll
-  for (int i = 0; i < 4; ++i) sum = __builtin_amdgcn_fdot2(__builtin_bit_cast(half2v, x4[i]), __builtin_bit_cast(half2v, zero), sum, false);
+  for (int i = 0; i < 4; ++i) asm("v_pk_fma_f16 %0, %1, 0, %0" : "+v"(sum) : "v"(x4[i]));
   return sum;
 }
 
@@ -342,7 +366,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
   // rows past the end repeat the last one (minima do not care).
   if (!SPLIT && a.resident) {
     int32_t tok[NR];
-    // (every wave has a first row, if only the last one again: a channel of nothing but NaN has NaN for its range)
+    // (every wave takes a first row, if only the last one again: no branch in front of it)
     const auto has = [&](int r) { return r == 0 ? n > 0 : r * step + y0 < n; };
 #pragma unroll
     for (int r = 0; r < NR; ++r)
@@ -412,6 +436,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
   }
   __syncthreads();
   const int wc = grp * vl * 8 + tid;                            // channel of this thread in the parameter step
+  const bool by_thresholds = DT == ZC_F16 && a.resident && a.bits[sub] == 2;
   if (tid < vl * 8 && wc < a.W) {
     float lo = red[0][0][tid], neg = red[0][1][tid];
 #pragma unroll
@@ -427,8 +452,8 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
     a.chan_zero[o] = cz;
     if (!a.resident) store_params(a, b, sub, wc, pr);
     prm[0][tid] = pr.x; prm[1][tid] = pr.y; prm[2][tid] = pr.z;
-    if (DT == ZC_F16 && a.resident && a.bits[sub] == 2) {
-      if (!(pr.z > 1.f / kTameRange && pr.z < kTameRange && fabsf(pr.y) <= kTameOffset)) wild = 1;
+    if (by_thresholds) {
+      if (!has_thresholds(pr.y, pr.z)) wild = 1;
       else {
 #pragma unroll 1
         for (int j = 0; j < 3; ++j) thr[j][tid] = negated_threshold(j + 1, pr.y, pr.z, pr.x);
@@ -455,21 +480,19 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
   const auto rs_dst = __builtin_amdgcn_make_buffer_rsrc(a.codes[sub] + ((int64_t)b * a.H * a.cap[sub] + a.begin[sub]) * rowb, 0, room, 0x00020000);
   const auto offset_of = [&](int r) { return r * step + y < n ? (int)(at + (uint32_t)(r * step * rowb)) : (int)(uint32_t)kPartBytes; };
   if constexpr (DT == ZC_F16) {
-    if (bits == 2 && !wild) {
+    if (by_thresholds && !wild) {
       const CodeMasks m = code_masks();
       uint4 t[3];
 #pragma unroll
       for (int j = 0; j < 3; ++j) t[j] = *reinterpret_cast<const uint4*>(&thr[j][x * 8]);
-      uint32_t zero = 0u;
-      asm("" : "+v"(zero));
-      float nan = 0.f;
+      uint32_t nan = 0u;
 #pragma unroll
       for (int r = 0; r < NR; ++r)
         if (r * step + y0 < n) {
           __builtin_amdgcn_raw_buffer_store_b16((short)threshold_codes(raw[r][0], t, m), rs_dst, offset_of(r), 0, 0);
-          nan = plus_zero_times(nan, raw[r][0], zero);
+          nan = plus_zero_times(nan, raw[r][0]);
         }
-      if (__builtin_amdgcn_ballot_w64((__float_as_uint(nan) & 0x7fffffffu) != 0u) == 0) return;      // (a NaN's code is what the general path makes of it)
+      if (__builtin_amdgcn_ballot_w64((nan & 0x7fff7fffu) != 0u) == 0) return;      // (a NaN's code is what the general path makes of it)
     }
   }
   float p0[8], p1[8], p2[8];
