@@ -264,6 +264,10 @@ __device__ inline bool has_thresholds(float z, float R) {
 }
 typedef _Float16 half2v __attribute__((ext_vector_type(2)));
 
+// Finding them is a chain of its own, which a thread with more rows than so many makes up for.  us for keys, dividing and by thresholds: 8 x
+// 100 tokens of 8 heads of 128 channels 5.36 and 5.98, 4 x 1000 7.4 and 7.9 (4 to 6 rows), 4 x 2000 9.78 and 9.77 (9), 2 x 3000 of 32 heads
+// 23.1 and 21.7, 4096 of 40 heads 26.8 and 24.7.
+constexpr int kThresholdRows = 8;
 // Order-preserving integer of a 16-bit float's bits, and back.
 __device__ inline int ordered16(int bits) {
   const int s = (int)(int16_t)bits;
@@ -436,7 +440,7 @@ __global__ __launch_bounds__(THREADS, 4) void k_columns(QPPair p, int tensors, i
   }
   __syncthreads();
   const int wc = grp * vl * 8 + tid;                            // channel of this thread in the parameter step
-  const bool by_thresholds = DT == ZC_F16 && a.resident && a.bits[sub] == 2;
+  const bool by_thresholds = DT == ZC_F16 && a.resident && a.bits[sub] == 2 && n > kThresholdRows * step;
   if (tid < vl * 8 && wc < a.W) {
     float lo = red[0][0][tid], neg = red[0][1][tid];
 #pragma unroll

@@ -102,12 +102,13 @@ def test_keys_of_more_threads_than_a_launch_counts():
 
 
 @pytest.mark.parametrize("kind", ["tame", "nan", "wild"])
-@pytest.mark.parametrize("n", [1, 2, 63, 517, 2600])
+@pytest.mark.parametrize("n", [1, 2, 63, 517, 2600, 4096, 4097, 7003])
 def test_two_bit_fp16_keys_by_thresholds(n, kind):
     """2-bit codes of fp16 keys that stay in registers, found by three thresholds a channel, against those
     of the kernel that divides every value (another layout, so another path): the same codes where
     values are ties of the rounding and one number beside them, equal, zeros of both signs, subnormal,
-    the largest, far from zero in a narrow range, a NaN, or of a range without thresholds."""
+    the largest, far from zero in a narrow range, a NaN, or of a range without thresholds.  (Up to
+    8 rows a thread divide too: 4096 tokens are the most that do, 4097 the fewest that do not.)"""
     from tests.pipeline_check import packed_to_chunks
     H, D = 3, 64
     g = torch.Generator().manual_seed(n)
