@@ -78,14 +78,6 @@ __device__ inline uint32_t bits_of(float x) {
   asm("" : "+v"(b));
   return b;
 }
-// All bits (a NaN's) if no number was among a channel's values - its minimum and that of -x are then where they began, or
-// NaN - else none.  (Without branches: they would be cold code in a chain that all workgroups of a small launch wait for.)
-__device__ inline uint32_t no_number(float lo, float neg) {
-  const uint32_t inf = 0x7f800000u, a = bits_of(lo), b = bits_of(neg);
-  uint32_t m = ((a & 0x7fffffffu) > inf) | ((b & 0x7fffffffu) > inf) | ((a == inf) & (b == inf)) ? ~0u : 0u;
-  asm("" : "+v"(m));
-  return m;
-}
 
 // What the quantizer needs of a channel whose values span [lo, hi]; n tokens (0: defaults).  Channelwise, one without any
 // number has NaN for its parameters.
@@ -98,9 +90,12 @@ __device__ inline float3 channel_params(int scheme, int n, float qmax, float lo,
     return make_float3(1.f / c, 0.f, 1.f);
   }
   if (n > 0 && scheme == ZC_SCHEME_CHANNEL) {
-    float R = hi - lo;                                     // Eq. 5: s = R / (2^k - 1)
+    float R = hi - lo + 0.f;                               // Eq. 5: s = R / (2^k - 1)  (never -0)
+    // Without a number the minimum and that of -x are where they began, or NaN: the range is -inf or NaN, and all bits are set.  (No
+    // branch: it would be cold code in a chain that all workgroups of a small launch wait for.)
+    uint32_t none = bits_of(R) > 0x7f800000u ? ~0u : 0u;
+    asm("" : "+v"(none));
     if (R == 0.f) R = qmax;                                // max == min: s := 1
-    const uint32_t none = no_number(lo, -hi);
     const auto or_nan = [&](float x) { return __uint_as_float(__float_as_uint(x) | none); };
     *cs = or_nan(R / qmax);
     *cz = or_nan(-rintf(refined_ratio(lo, qmax, R, 1.f / R)));
