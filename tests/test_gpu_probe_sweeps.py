@@ -154,3 +154,28 @@ def test_scores_in_the_least_workspace(case):
     assert bool((ws[least:] == 0xff).all())
     # (the ranges may be cut elsewhere: sums of the same terms in another order, each sum off by a few 2^-24)
     assert torch.allclose(got, want, rtol=1e-5, atol=0)
+
+
+# Heads that share an XCD's places in groups (a multiple of 8 heads, and so many tokens that fewer than an XCD's heads fill its
+# places): groups of 2 and 2; 3 and 2; 3, 3 and 1; 4 and 3 of a batch element each; 3 and 2 on the border of two batch elements
+@pytest.mark.parametrize("B,Hq,Hkv,d,L,P,dtype", [(1, 32, 8, 64, 16400, 200, torch.bfloat16), (1, 40, 40, 64, 16400, 130, torch.float16),
+                                                  (1, 56, 8, 64, 16500, 70, torch.bfloat16), (7, 8, 4, 64, 12900, 600, torch.bfloat16),
+                                                  (2, 20, 20, 64, 16385, 80, torch.float32)])
+def test_every_column_of_every_head_of_a_group(B, Hq, Hkv, d, L, P, dtype):
+    tiles, per_xcd = -(-L // 128), B * Hq // 8
+    least = -(-256 // tiles)
+    assert B * Hq % 8 == 0 and per_xcd // least > 1              # several groups
+    g = torch.Generator(device=DEV).manual_seed(L)
+    pos = spread(L, P).to(DEV)
+    P = pos.numel()
+    q = torch.randn(B, Hq, P, d, generator=g, device=DEV).to(dtype)
+    k = torch.randn(B, Hkv, L, d, generator=g, device=DEV).to(dtype)
+    rows = torch.arange(P, device=DEV)
+    per_head = torch.full((B, Hq, L), float("nan"), device=DEV)
+    scores = torch.full((B, L), float("nan"), device=DEV)
+    zb.zc_probe_saliency(q, k, pos.int(), probe_rows=rows.int(), scores=scores, scores_per_head=per_head)
+    for h in range(Hq):
+        want = reference(q[:, h:h + 1], k[:, h * Hkv // Hq][:, None], rows, pos)
+        rel = ((per_head[:, h].double() - want).abs() / want.clamp(min=1e-30)).max().item()
+        assert rel < 3e-5, (h, rel)                              # (the bound of test_scores_of_row_blocks_and_ranges)
+    assert torch.allclose(per_head.mean(1), scores, rtol=1e-5, atol=0)
