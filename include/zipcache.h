@@ -44,7 +44,7 @@
  *     the library cannot check this.
  *   - Value ranges (not checked: the data lives on the device).  All inputs must be
  *     finite - no NaN, no infinity (the quantizer takes minima and maxima without
- *     regard to NaN).  zc_decode_attention feeds the matrix cores fp16 operands:
+ *     regard to NaN; a channel of nothing but NaN has NaN for its channelwise parameters).  zc_decode_attention feeds the matrix cores fp16 operands:
  *     every |q[c] * chan_scale[c] * sm_scale| of the keys' channel scales must stay
  *     below 700 and every token scale of the values below 1000 (an fp16 overflow
  *     there turns the output into NaN); activations of the models the paper
@@ -71,7 +71,7 @@ typedef enum {
   ZC_OK = 0,
   ZC_ERR_INVALID_ARG = -1, /* null / misaligned pointer, bad size or stride  */
   ZC_ERR_UNSUPPORTED = -2, /* dtype, head dim, bit width, scheme, size limit  */
-  ZC_ERR_WORKSPACE = -3,   /* workspace smaller than the *_workspace() size  */
+  ZC_ERR_WORKSPACE = -3,   /* workspace smaller than the call needs: never one of *_workspace() bytes */
   ZC_ERR_CAPACITY = -4,    /* arena or chunk table of a zc_packed is full    */
   ZC_ERR_HIP = -5,         /* the HIP runtime refused a launch               */
   ZC_ERR_STATIC_LIMIT = -6 /* needs more scratch than ZC_STATIC_SCRATCH_BYTES */
@@ -165,7 +165,11 @@ typedef struct zc_packed {
  *   sum_{p : probe_pos[p] >= i} A[p, i] / #{p : probe_pos[p] >= i}
  * (0 where no probe sees column i).  scores_per_head (device float
  * [B, Hq, Lk]) receives the per-head values when not NULL.
- * The result is deterministic: no floating-point atomics are used. */
+ * The result is deterministic: no floating-point atomics are used.
+ * A workspace of zc_probe_saliency_workspace() bytes suffices for any call of these sizes.  For
+ * P > 64 one that lacks up to 32 * min(B * Hq, 1024) * min(P, 512) of them (rounded up to 256) is
+ * taken as well; without lse_ext the partial sums of a row may then be added in another order,
+ * so scores are the same bits only for workspaces on the same side of the full size. */
 size_t zc_probe_saliency_workspace(int64_t B, int64_t Hq, int64_t Lk, int64_t P);
 int zc_probe_saliency(const zc_tensor4* q, const zc_tensor4* k,
                       const int32_t* probe_rows, const int32_t* probe_pos, int32_t P,
