@@ -164,3 +164,22 @@ def test_keys_of_a_channel_of_nan(n, layout, dtype):
     for a in (p.chan_scale, p.chan_zero):
         low = a.flatten()[-H * D:].cpu()                    # (the subset of few bits is the second)
         assert torch.equal(low.isnan(), nan) and not bool(low.isinf().any())
+
+
+@pytest.mark.parametrize("cap", [524224, 524288])
+def test_keys_on_either_side_of_4_gigabytes(cap):
+    """Codes of a batch element just below and at 2^32 bytes: the first still have 32-bit offsets in the column
+    sweep, the second take the way of keys that do not stay in registers; either has the codes of a small arena."""
+    H, D, n = 64, 128, 90
+    X = torch.randn(1, H, 2 * n, D, generator=torch.Generator().manual_seed(cap)).to(torch.bfloat16).to(DEV)
+    idx = torch.arange(n, dtype=torch.int32, device=DEV)[None]
+    got = []
+    for c in (cap, 256):
+        p = zb.PackedTensor(1, H, D, 64, c, 2, 8, "channel", zb.ZC_LAYOUT_ROW, max_chunks=2, device=DEV)
+        for x in (X[:, :, :n], X[:, :, n:]):                    # (the second chunk begins at slot 128)
+            zb.zc_quantize_pack(x, idx[:, :0], idx, p)
+        rows = p.codes_lo.view(H, c, D)
+        assert not bool(rows[:, n:128].any()) and not bool(rows[:, 128 + n:256].any())
+        got.append((torch.cat([rows[:, :n], rows[:, 128:128 + n]], 1).clone(), p.chan_scale[:2].clone(), p.chan_zero[:2].clone()))
+        del p, rows
+    assert all(torch.equal(a, b) for a, b in zip(*got))
