@@ -717,12 +717,16 @@ static int launch_prefill(PrefillArgs& a, hipStream_t st) {
     // 2.1: 88 / 94 and 335 / 331 us, at 2.0: 579 / 549; two or four, at 1.6: 232 / 261, at 1.1: 264 / 237.
     const int64_t share = heads * (ceil_div(a.L, 32) + 1);
     // 16 rows a workgroup of eight waves while all of them run at once (two a CU for 64 channels, one for 128), of long rows
-    // also in two rounds.  us, four waves of 32 rows and this: 8 heads of 64 channels, 256 rows (128 workgroups) 11.0
-    // and 7.9; 16 x 8 heads, 64 rows (512) 7.1 and 6.8, 100 rows (896) 9.7 and 11.8; 8 heads, 2048 rows (1024) 61.3 and 54.2;
-    // 128 channels: 32 heads, 100 rows (224) 11.1 and 7.5; 4 x 16 heads, 100 rows (448) 11.4 and 12.3; 8 heads, 1000 rows
-    // (504) 43.3 and 34.8; 12 heads, 1500 rows (1128) 86.9 and 98.4.
+    // also in two rounds: of 64 channels for few heads only, as workgroups of 32 rows need one round there and are about as many as fit.
+    // us, four waves of 32 rows and this: 8 heads of 64 channels, 256 rows (128 workgroups) 11.0
+    // and 7.9; 16 x 8 heads, 64 rows (512) 7.1 and 6.8, 100 rows (896) 9.7 and 11.8; 8 heads, 2047 rows (1024) 60.8 and 53.9; 14 heads, 1168 rows
+    // (1022) 39.5 and 37.7; 16 heads, 974 rows (976) 34.0 and 32.9, 1022 rows (1024) 34.4 and 36.2; 20 heads, 602 rows (760) 23.1 and 22.4;
+    // 24 heads, 557 rows (840) 22.5 and 22.8, 637 rows (960) 24.6 and 25.7; 32 heads, 512 rows (1024) 20.9 and 25.2;
+    // 128 channels: 32 heads, 100 rows (224) 11.1 and 7.5; 4 x 16 heads, 100 rows (448) 11.4 and 12.3; 16 heads, 512 rows (512) 27.7 and
+    // 25.0; 8 heads, 1023 rows (512) 47.5 and 34.8; 12 heads, 1500 rows (1128) 86.9 and 98.4.
     const int64_t few = heads * ceil_div(a.L, 16), places = D == 64 ? 512 : 256;
-    if (few <= places || (few <= 2 * places && a.L >= 512)) hipLaunchKernelGGL(k_prefill_attention32_few<D>, blocks(16, 32, 512), dim3(512), 0, st, a);
+    const bool two_rounds = few <= 2 * places && a.L >= 512 && (D == 128 || heads <= 14 || (heads <= 20 && few <= 1000));
+    if (few <= places || two_rounds) hipLaunchKernelGGL(k_prefill_attention32_few<D>, blocks(16, 32, 512), dim3(512), 0, st, a);
     else if (share >= 4300) hipLaunchKernelGGL((k_prefill_attention32<D, 1>), blocks(32, 256, 64), dim3(64), 0, st, a);
     else if (share >= 3100) hipLaunchKernelGGL((k_prefill_attention32<D, 2>), blocks(32, 128, 128), dim3(128), 0, st, a);
     else hipLaunchKernelGGL((k_prefill_attention32<D, 4>), blocks(32, 64, 256), dim3(256), 0, st, a);
@@ -776,7 +780,7 @@ extern "C" int zc_prefill_attention(const zc_tensor4* q, const zc_tensor4* k, co
         (v->L + 128) * v->sL * eb >= 0xFFFFF000ll)
       return ZC_ERR_UNSUPPORTED;
   }
-  const int64_t grid = ceil_div64(q->L, 32) * q->H * q->B;         // (the smallest row blocks)
+  const int64_t grid = ceil_div64(q->L, 32) * q->H * q->B;         // (the smallest row blocks but for those of 16 rows, at most 1024)
   if (grid > 0x7fffffff) return ZC_ERR_UNSUPPORTED;
 
   PrefillArgs a;

@@ -41,11 +41,12 @@ def causal_reference(q, k, v):
     return torch.matmul(torch.softmax(x, -1), v.double().repeat_interleave(G, 1)), torch.logsumexp(x, -1)
 
 
-# fp32 calls by the 16-row kernel (at most 512 workgroups for 64 channels, 256 for 128; twice that from 512 rows on) - edges of its
-# row and key blocks, one to nine key blocks for eight waves - and, last of each width, just past its rule
+# fp32 calls by the 16-row kernel (at most 512 workgroups for 64 channels, 256 for 128; twice that from 512 rows on, for 64 channels up
+# to 14 heads, or 1000 workgroups up to 20) - edges of its row and key blocks, one to nine key blocks for eight waves - and just past its rule
 @pytest.mark.parametrize("d,B,Hq,Hkv,L", [
     (64, 1, 1, 1, 1), (64, 1, 3, 1, 15), (64, 2, 4, 2, 16), (64, 1, 5, 5, 17), (64, 1, 8, 2, 31), (64, 1, 8, 8, 33), (64, 3, 2, 1, 255),
     (64, 1, 4, 4, 257), (64, 1, 8, 8, 289), (64, 2, 16, 16, 256), (64, 2, 16, 16, 257), (64, 1, 8, 8, 2048), (64, 1, 8, 4, 2049),
+    (64, 1, 14, 7, 1168), (64, 1, 14, 7, 1169), (64, 2, 8, 4, 992), (64, 1, 16, 4, 993), (64, 1, 20, 4, 800), (64, 1, 21, 7, 512), (64, 4, 8, 8, 512),
     (128, 1, 2, 1, 7), (128, 1, 4, 2, 47), (128, 1, 16, 4, 256), (128, 1, 16, 4, 257), (128, 1, 8, 2, 1000), (128, 1, 8, 2, 1025)])
 def test_fp32_calls_of_few_rows(d, B, Hq, Hkv, L):
     g = torch.Generator(device=DEV).manual_seed(L + d)
