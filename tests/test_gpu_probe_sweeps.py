@@ -61,6 +61,10 @@ CASES = [
     (1, 2, 1, 64, 2000, torch.float16, lambda L: torch.arange(L - 769, L)),
     (1, 3, 3, 128, 1600, torch.bfloat16, lambda L: torch.arange(1538)),
     (1, 2, 2, 64, 3000, torch.float32, lambda L: torch.cat([torch.arange(90), spread(L, 700)]).unique()),
+    # few probes over several ranges, joined by a launch; as many ranges as two at a time leave of nine
+    (10, 16, 4, 64, 352, torch.bfloat16, lambda L: spread(L, 18)),
+    (3, 8, 8, 64, 900, torch.float16, lambda L: spread(L, 31)),
+    (1, 2, 1, 64, 900, torch.bfloat16, lambda L: spread(L, 300)),
 ]
 
 
@@ -131,7 +135,7 @@ def test_scores_of_a_negative_scale(case):
 
 
 # A workspace of the least size: the pairs of the column ranges have no place beside the per-head scores, and are joined in front of sweep 2.
-@pytest.mark.parametrize("case", [1, 2, 12, 16])
+@pytest.mark.parametrize("case", [1, 2, 12, 16, len(CASES) - 1])
 def test_scores_in_the_least_workspace(case):
     B, Hq, Hkv, d, L, dtype, probes = CASES[case]
     g = torch.Generator(device=DEV).manual_seed(case)
