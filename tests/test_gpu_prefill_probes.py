@@ -8,10 +8,11 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda"
 
 
-# (dtype, d, B, Hq, Hkv, L, P): up to two probes a thread come from the kernel - workgroups of 64, 128 and
-# 256 threads (fp32, by heads and length), 256 and 512 (16 bit) - one more takes the other launch
+# (dtype, d, B, Hq, Hkv, L, P): up to two probes a thread come from the kernel - workgroups of 512, 256, 128 and
+# 64 threads (fp32, by heads and length), 256 and 512 (16 bit) - one more takes the other launch
 @pytest.mark.parametrize("dtype,d,B,Hq,Hkv,L", [(torch.float32, 64, 1, 3, 1, 97), (torch.float32, 64, 2, 160, 160, 250),
-                                                (torch.float32, 128, 1, 128, 32, 800), (torch.float16, 128, 2, 4, 2, 391),
+                                                (torch.float32, 128, 1, 128, 32, 800), (torch.float32, 64, 2, 200, 200, 350),
+                                                (torch.float16, 128, 2, 4, 2, 391),
                                                 (torch.bfloat16, 64, 1, 8, 8, 33), (torch.bfloat16, 128, 1, 8, 1, 16400)])
 @pytest.mark.parametrize("P", [1, 128, 129, 256, 257, 512, 513, 1024, 1025])
 def test_probe_normalisers_are_the_rows(dtype, d, B, Hq, Hkv, L, P):
