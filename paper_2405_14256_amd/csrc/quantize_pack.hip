@@ -2,7 +2,8 @@
 // tensor (Eq. 5, Eq. 6, Algorithm 1; the four quantizer calls of Algorithm 2).
 //
 // Channel statistics of a subset must be complete before any of its tokens can
-// be quantized, so the work is two launches, one where the rows fit registers:
+// be quantized, so the work is two launches, one where the rows fit registers or
+// the subsets are so short that every workgroup takes its statistics itself (k_short_kv):
 //   1. k_columns        a workgroup owns a few channels of one subset: their minima
 //                       and maxima over all its tokens, the parameters that follow
 //                       (Eq. 5's R = max - min, 1/R and z, or Eq. 6's c and 1/c)
@@ -921,27 +922,29 @@ __device__ inline void load4(const void* p, float (&v)[4]) {
   }
 }
 
-// Values (TGROUP layout, channel-separable tokenwise): one word group, a thread per 4 channels.
+// Token e of a word group of values: its index in the subset.
+template <int BITS>
+__device__ inline int value_token(int unit, int e) {
+  constexpr int TB = 4 * (32 / BITS);
+  return (unit >> 2) * TB + 16 * tile_of_field_group(BITS, e >> 2) + 4 * (unit & 3) + (e & 3);
+}
+
+// Ranges, token parameters, codes and positions of a word group of values (TGROUP layout, channel-separable tokenwise) whose rows x
+// are there, 4 channels a thread; tx: of the waves (nwaves) that share the row.  red: theirs.  All threads of the workgroup come here.
 template <int DT, int BITS>
-__device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, float (*red)[kPackThreads / 64][16]) {
+__device__ inline void finish_values(const QPArgs& a, int sub, int unit, int b, float (&x)[32 / BITS][kPackCpt], const float (&inv_c)[kPackCpt],
+                                     int tx, int wave, int nwaves, float (*red)[kPackThreads / 64][16]) {
   constexpr int E = 32 / BITS, TBAT = E < 8 ? E : 8, NBAT = E / TBAT, TB = 4 * E;
-  constexpr int FPG = 16 / BITS, NG = TBAT / FPG, ESZ = DT == ZC_F32 ? 4 : 2;
+  constexpr int FPG = 16 / BITS, NG = TBAT / FPG;
   constexpr float QMAX = (float)((1 << BITS) - 1);
   const int n = a.n[sub], blk = unit >> 2, kg = unit & 3;
   const int32_t* idx = a.idx[sub] + (int64_t)b * n;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
-  const bool valid = kPackCpt * tid < a.W;
-  const int w = valid ? kPackCpt * tid : 0, h = w / a.D, c = w - h * a.D;
-  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
-  auto rel_of = [&](int e) { return blk * TB + 16 * tile_of_field_group(BITS, e >> 2) + 4 * kg + (e & 3); };   // token e of the group
-
-  float x[E][kPackCpt], inv_c[kPackCpt];
-#pragma unroll
-  for (int e = 0; e < E; ++e) load4<DT>(base + (int64_t)idx[min(rel_of(e), n - 1)] * a.sL * ESZ, x[e]);
-  load4<ZC_F32>(param_row(a, b, sub, 0) + w, inv_c);
+  const int lane = tx & 63;
+  const bool valid = kPackCpt * tx < a.W;
+  auto rel_of = [&](int e) { return value_token<BITS>(unit, e); };
   // bookkeeping of the group's tokens by lanes 0 .. E - 1 of the first wave
   const int my_rel = rel_of(lane < E ? lane : 0);
-  const bool mine = tid < E && my_rel < n;
+  const bool mine = tx < E && my_rel < n;
   const int64_t o0 = (int64_t)b * a.cap[sub] + a.begin[sub];
   if (mine && a.pos[sub]) (a.pos[sub] + o0)[my_rel] = (int32_t)(idx[my_rel] + a.pos_offset);
 
@@ -1002,13 +1005,28 @@ __device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, fl
 #pragma unroll
       for (int i = 0; i < kPackCpt; ++i) words[i] |= (uint32_t)acc[i] << (BITS * (q * TBAT + g * FPG));
     }
-  int w1 = threadIdx.x;                              // (the channel again, not held in registers meanwhile)
+  int w1 = tx;                                       // (the channel again, not held in registers meanwhile)
   asm volatile("" : "+v"(w1));
   w1 *= kPackCpt;
   const int h1 = w1 >> (a.D == 128 ? 7 : 6), c1 = w1 & (a.D - 1);
   const int64_t gblk = a.begin[sub] / TB + blk, nblk = a.cap[sub] / TB;
   uint32_t* dst = reinterpret_cast<uint32_t*>(a.codes[sub]) + ((((int64_t)b * a.H + h1) * nblk + gblk) * 4 + kg) * a.D + c1;
   *reinterpret_cast<uint4*>(dst) = make_uint4(words[0], words[1], words[2], words[3]);
+}
+
+// Values whose channels' parameters are known: one word group a workgroup.
+template <int DT, int BITS>
+__device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, float (*red)[kPackThreads / 64][16]) {
+  constexpr int E = 32 / BITS, ESZ = DT == ZC_F32 ? 4 : 2;
+  const int n = a.n[sub], tid = threadIdx.x;
+  const int32_t* idx = a.idx[sub] + (int64_t)b * n;
+  const int w = kPackCpt * tid < a.W ? kPackCpt * tid : 0, h = w / a.D, c = w - h * a.D;
+  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
+  float x[E][kPackCpt], inv_c[kPackCpt];
+#pragma unroll
+  for (int e = 0; e < E; ++e) load4<DT>(base + (int64_t)idx[min(value_token<BITS>(unit, e), n - 1)] * a.sL * ESZ, x[e]);
+  load4<ZC_F32>(param_row(a, b, sub, 0) + w, inv_c);
+  finish_values<DT, BITS>(a, sub, unit, b, x, inv_c, tid, tid >> 6, blockDim.x >> 6, red);
 }
 
 constexpr int kPackTokens = 4;         // keys: tokens of a thread
@@ -1086,6 +1104,249 @@ __global__ __launch_bounds__(kPackThreads, 5) void k_pack_kv(QPPair p, PackRange
     if (bits == 4) pack_values<DT, 4>(a, sub, wg, b, red);
     else if (bits == 2) pack_values<DT, 2>(a, sub, wg, b, red);
     else pack_values<DT, 8>(a, sub, wg, b, red);
+  }
+}
+
+// ---- short chunks: one launch ------------------------------------------------------------------
+// A flushed window, or a short prompt: both launches above are little more than a launch and a few trips to memory each.
+// Here a workgroup that needs the statistics of a subset's channels takes them itself, from all of the subset's tokens: up to
+// 180 KB out of an L2, which costs less than the second launch and the parameters' way through memory.
+//   keys    16 lanes across a row of 128 channels, their rows in registers until the parameters are there
+//   values  a team of W / 4 threads per word group, 256 threads or one team a workgroup; its token list comes to LDS in one trip, the rows of
+//           its own tokens are requested first, then all of them, 16 bytes a lane, whose largest magnitudes meet in LDS
+// Bound by the chain of those trips and, from 100 KB on, by the vector issue of the repeated statistics (16-bit magnitudes are
+// compared as integers, two at a time: 1 instruction a value; four teams and 1024 threads a workgroup, which repeat them
+// less, took 12.5 us for 64 tokens of 1024 channels).  us per joint call, bf16, as two launches and here: 64 tokens
+// of 4 heads of 64 channels 7.9 and 6.5, of 8 heads of 128 8.3 and 6.9, 16 prompts of them 11.5 and 7.5; 100 tokens 8.4 and 7.4, 11.6 and 10.0.
+constexpr int kShortTokens = 128;                       // most tokens of a subset
+constexpr int kShortLanes = 16, kShortRows = 8;         // keys: lanes across a row, most rows of a thread
+struct ShortPlan {
+  int key_wgs, value_wgs[2];        // of a subset (0: no such tensor)
+  int team, teams;                  // values: threads of a team, teams of a workgroup
+  int lanes, rows;                  // values, statistics: lanes across a row, rows at a time
+};
+
+template <int DT, int BITS>
+__device__ inline void short_keys_codes(const QPArgs& a, int sub, int b, int h, int c, int x, int y, int step, int n,
+                                        const uint4 (&raw)[kShortRows][DT == ZC_F32 ? 2 : 1], const float (*prm)[128]) {
+  float p0[8], p1[8], p2[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) { p0[i] = prm[0][x * 8 + i]; p1[i] = prm[1][x * 8 + i]; p2[i] = prm[2][x * 8 + i]; }
+  const int rowb = a.D * BITS / 8;
+  uint8_t* dst = a.codes[sub] + (((int64_t)b * a.H + h) * a.cap[sub] + a.begin[sub] + y) * rowb + c * BITS / 8;
+#pragma unroll
+  for (int r = 0; r < kShortRows; ++r) {
+    if (r * step >= n) break;
+    if (r * step + y < n) {
+      float v[8];
+      widen8<DT>(raw[r], v);
+      store_row_codes<DT, BITS>(dst + (int64_t)r * step * rowb, v, p0, p1, p2);
+    }
+  }
+}
+
+template <int DT>
+__device__ inline void short_keys(const QPArgs& a, int sub, int grp, int b, float (*red)[2][128], float (*prm)[128]) {
+  constexpr int RAW = DT == ZC_F32 ? 2 : 1, ESZ = DT == ZC_F32 ? 4 : 2;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = blockDim.x >> 6;
+  const int x = tid & (kShortLanes - 1), y = tid / kShortLanes, step = blockDim.x / kShortLanes;
+  const int n = a.n[sub];
+  const int vec = min(grp * kShortLanes + x, a.NV - 1);         // (lanes past the row repeat its last vector)
+  const int w = vec * 8, h = w / a.D, c = w % a.D;
+  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
+  const int32_t* idx = a.idx[sub] + (int64_t)b * n;
+  uint4 raw[kShortRows][RAW];
+  float mn[8], mneg[8];                                         // minimum, minimum of -x
+#pragma unroll
+  for (int i = 0; i < 8; ++i) { mn[i] = INFINITY; mneg[i] = INFINITY; }
+  int32_t tok[kShortRows];
+#pragma unroll
+  for (int r = 0; r < kShortRows; ++r)
+    if (r * step < n) tok[r] = idx[min(r * step + y, n - 1)];   // (rows past the end repeat the last one)
+#pragma unroll
+  for (int r = 0; r < kShortRows; ++r)
+    if (r * step < n) {
+      const uint4* src = reinterpret_cast<const uint4*>(base + (int64_t)tok[r] * a.sL * ESZ);
+#pragma unroll
+      for (int q = 0; q < RAW; ++q) raw[r][q] = src[q];
+    }
+  if (grp == 0 && a.pos[sub] && x == 0) {
+#pragma unroll
+    for (int r = 0; r < kShortRows; ++r)
+      if (r * step + y < n) a.pos[sub][(int64_t)b * a.cap[sub] + a.begin[sub] + r * step + y] = (int32_t)(tok[r] + a.pos_offset);
+  }
+#pragma unroll
+  for (int r = 0; r < kShortRows; ++r)
+    if (r * step < n) {
+      float v[8];
+      widen8<DT>(raw[r], v);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) { mn[i] = fminf(mn[i], v[i]); mneg[i] = fminf(mneg[i], -v[i]); }
+    }
+  {                                                             // over the four rows of a wave, as in k_columns
+    float u[4];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) mn[j] = swap_min_halves(mn[j], mneg[j]);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) u[j] = swap_min_rows(mn[j], mn[j + 4]);
+    *reinterpret_cast<float4*>(&red[wave][lane >> 5][(lane & 15) * 8 + 4 * ((lane >> 4) & 1)]) = make_float4(u[0], u[1], u[2], u[3]);
+  }
+  __syncthreads();
+  const int wc = grp * kShortLanes * 8 + tid;
+  if (tid < kShortLanes * 8 && wc < a.W) {
+    float lo = INFINITY, neg = INFINITY;
+    for (int v = 0; v < nwaves; ++v) { lo = fminf(lo, red[v][0][tid]); neg = fminf(neg, red[v][1][tid]); }
+    float cs, cz;
+    const float3 pr = channel_params(ZC_SCHEME_CHANNEL, n, (float)((1 << a.bits[sub]) - 1), lo, -neg, &cs, &cz);
+    const int64_t o = (int64_t)(sub * a.B + b) * a.W + wc;
+    a.chan_scale[o] = cs;
+    a.chan_zero[o] = cz;
+    prm[0][tid] = pr.x; prm[1][tid] = pr.y; prm[2][tid] = pr.z;
+  }
+  __syncthreads();
+  if (grp * kShortLanes + x >= a.NV) return;
+  const int bits = a.bits[sub];
+  if (bits == 4) short_keys_codes<DT, 4>(a, sub, b, h, c, x, y, step, n, raw, prm);
+  else if (bits == 2) short_keys_codes<DT, 2>(a, sub, b, h, c, x, y, step, n, raw, prm);
+  else short_keys_codes<DT, 8>(a, sub, b, h, c, x, y, step, n, raw, prm);
+}
+
+// The larger magnitude of the 16-bit numbers in each half (bits: a NaN's are above infinity's).
+__device__ inline uint32_t larger_magnitudes(uint32_t m, uint32_t x) {
+  typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2, m), __builtin_bit_cast(u16x2, x & 0x7fff7fffu)));
+}
+
+template <int DT, int BITS>
+__device__ inline void short_values(const QPArgs& a, int sub, int wg, int b, const ShortPlan& s, uint4* stage, int32_t* sidx,
+                                    float (*red)[2][kPackThreads / 64][16]) {
+  constexpr int E = 32 / BITS, ESZ = DT == ZC_F32 ? 4 : 2, CPL = 16 / ESZ;      // CPL: channels of a lane in the statistics
+  constexpr int BATCH = DT == ZC_F32 ? 8 : 12;        // rows requested at once
+  const int n = a.n[sub], tid = threadIdx.x;
+  const int32_t* idx = a.idx[sub] + (int64_t)b * n;
+  const int64_t row_bytes = a.sL * ESZ;
+  const char* xb = reinterpret_cast<const char*>(a.x) + (int64_t)b * a.sB * ESZ;
+  const int nwaves = s.team >> 6, team = __builtin_amdgcn_readfirstlane(tid >> 6) / nwaves;
+  const int tx = tid - team * s.team, unit = wg * s.teams + team;
+  const int w = kPackCpt * tx < a.W ? kPackCpt * tx : 0;
+  const char* own_base = xb + ((int64_t)(w / a.D) * a.sH + w % a.D) * ESZ;
+  typedef typename std::conditional<DT == ZC_F32, uint4, uint2>::type Row;
+  for (int t = tid; t < n; t += blockDim.x) sidx[t] = idx[t];       // (one trip for every look-up below)
+  __syncthreads();
+  Row own[E];
+  if (n > 0) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) own[e] = *reinterpret_cast<const Row*>(own_base + (int64_t)sidx[min(value_token<BITS>(unit, e), n - 1)] * row_bytes);
+  }
+  // statistics: s.rows tokens at a time, a lane per 16 bytes of a row
+  const int sy = tid / s.lanes, sw = (tid - sy * s.lanes) * CPL;
+  uint4 most = make_uint4(0u, 0u, 0u, 0u);
+  float4 lo4 = make_float4(INFINITY, INFINITY, INFINITY, INFINITY), neg4 = lo4;
+  if (sy < s.rows) {
+    const char* base = xb + ((int64_t)(sw / a.D) * a.sH + sw % a.D) * ESZ;
+    for (int t0 = sy; t0 < n; t0 += BATCH * s.rows) {
+      uint4 rw[BATCH];
+#pragma unroll
+      for (int r = 0; r < BATCH; ++r) rw[r] = *reinterpret_cast<const uint4*>(base + (int64_t)sidx[min(t0 + r * s.rows, n - 1)] * row_bytes);
+#pragma unroll
+      for (int r = 0; r < BATCH; ++r) {
+        if constexpr (DT == ZC_F32) {
+          const float4 v = __builtin_bit_cast(float4, rw[r]);
+          lo4.x = fminf(lo4.x, v.x); lo4.y = fminf(lo4.y, v.y); lo4.z = fminf(lo4.z, v.z); lo4.w = fminf(lo4.w, v.w);
+          neg4.x = fminf(neg4.x, -v.x); neg4.y = fminf(neg4.y, -v.y); neg4.z = fminf(neg4.z, -v.z); neg4.w = fminf(neg4.w, -v.w);
+        } else {
+          most.x = larger_magnitudes(most.x, rw[r].x); most.y = larger_magnitudes(most.y, rw[r].y);
+          most.z = larger_magnitudes(most.z, rw[r].z); most.w = larger_magnitudes(most.w, rw[r].w);
+        }
+      }
+    }
+    uint4* mine = stage + sy * s.lanes + (sw / CPL);
+    if constexpr (DT == ZC_F32) {
+      mine[0] = __builtin_bit_cast(uint4, lo4);
+      mine[kPackThreads] = __builtin_bit_cast(uint4, neg4);
+    } else {
+      mine[0] = most;
+    }
+  }
+  __syncthreads();
+  float lo[kPackCpt], neg[kPackCpt];
+  if constexpr (DT == ZC_F32) {
+#pragma unroll
+    for (int i = 0; i < kPackCpt; ++i) { lo[i] = INFINITY; neg[i] = INFINITY; }
+#pragma unroll 2
+    for (int t = 0; t < s.rows; ++t) {
+      const float4 l = __builtin_bit_cast(float4, stage[t * s.lanes + w / CPL]), g = __builtin_bit_cast(float4, stage[kPackThreads + t * s.lanes + w / CPL]);
+      lo[0] = fminf(lo[0], l.x); lo[1] = fminf(lo[1], l.y); lo[2] = fminf(lo[2], l.z); lo[3] = fminf(lo[3], l.w);
+      neg[0] = fminf(neg[0], g.x); neg[1] = fminf(neg[1], g.y); neg[2] = fminf(neg[2], g.z); neg[3] = fminf(neg[3], g.w);
+    }
+  } else {
+    uint2 m = make_uint2(0u, 0u);
+#pragma unroll 2
+    for (int t = 0; t < s.rows; ++t) {
+      const uint2 v = reinterpret_cast<const uint2*>(stage)[(t * s.lanes * CPL + w) / kPackCpt];
+      m.x = larger_magnitudes(m.x, v.x); m.y = larger_magnitudes(m.y, v.y);
+    }
+    const uint32_t mag[kPackCpt] = {m.x & 0xffffu, m.x >> 16, m.y & 0xffffu, m.y >> 16};
+    bool nan = false;
+#pragma unroll
+    for (int i = 0; i < kPackCpt; ++i) {
+      neg[i] = -half_bits_to_float<DT>(mag[i]);
+      lo[i] = neg[i];
+      nan |= mag[i] > (DT == ZC_F16 ? 0x7c00u : 0x7f80u);
+    }
+    if (nan) {                                       // a NaN is none of the channel's numbers: its statistics again, without it
+#pragma unroll
+      for (int i = 0; i < kPackCpt; ++i) { lo[i] = INFINITY; neg[i] = INFINITY; }
+#pragma unroll 1
+      for (int t = 0; t < n; ++t) {
+        float v[kPackCpt];
+        load4<DT>(own_base + (int64_t)idx[t] * row_bytes, v);
+#pragma unroll
+        for (int i = 0; i < kPackCpt; ++i) { lo[i] = fminf(lo[i], v[i]); neg[i] = fminf(neg[i], -v[i]); }
+      }
+    }
+  }
+  float cs[kPackCpt], inv_c[kPackCpt], cz;
+#pragma unroll
+  for (int i = 0; i < kPackCpt; ++i) inv_c[i] = channel_params(ZC_SCHEME_CST, n, 0.f, lo[i], -neg[i], &cs[i], &cz).x;
+  if (unit == 0 && kPackCpt * tx < a.W) {
+    const int64_t o = (int64_t)(sub * a.B + b) * a.W + w;
+    *reinterpret_cast<float4*>(a.chan_scale + o) = make_float4(cs[0], cs[1], cs[2], cs[3]);
+    *reinterpret_cast<float4*>(a.chan_zero + o) = make_float4(0.f, 0.f, 0.f, 0.f);
+  }
+  if (n == 0) return;
+  float x[E][kPackCpt];
+#pragma unroll
+  for (int e = 0; e < E; ++e) load4<DT>(&own[e], x[e]);
+  finish_values<DT, BITS>(a, sub, unit, b, x, inv_c, tx, tx >> 6, nwaves, red[team]);
+}
+
+// grid (2 s.key_wgs + s.value_wgs, B); s.team * s.teams threads
+template <int DT>
+__global__ __launch_bounds__(kPackThreads) void k_short_kv(QPPair p, ShortPlan s) {
+  __shared__ __align__(16) uint4 stage[2 * kPackThreads];
+  __shared__ float red[4][2][kPackThreads / 64][16];
+  __shared__ __align__(16) float prm[3][128];
+  __shared__ int32_t sidx[kShortTokens];
+  const int b = blockIdx.y;
+  int wg = blockIdx.x;
+  if (b == 0 && wg == 0 && threadIdx.x < 2) {
+    const QPArgs& a = p.t[threadIdx.x];                 // (of one tensor: both are it)
+    a.chunk_row[0] = a.begin[0]; a.chunk_row[1] = a.n[0];
+    a.chunk_row[2] = a.begin[1]; a.chunk_row[3] = a.n[1];
+  }
+  if (wg < 2 * s.key_wgs) {
+    const int sub = wg >= s.key_wgs ? 1 : 0;
+    short_keys<DT>(p.t[0], sub, wg - sub * s.key_wgs, b, reinterpret_cast<float (*)[2][128]>(stage), prm);
+  } else {
+    const QPArgs& a = p.t[1];
+    wg -= 2 * s.key_wgs;
+    const int sub = wg >= s.value_wgs[0] ? 1 : 0;
+    if (sub) wg -= s.value_wgs[0];
+    const int bits = a.bits[sub];
+    if (bits == 4) short_values<DT, 4>(a, sub, wg, b, s, stage, sidx, red);
+    else if (bits == 2) short_values<DT, 2>(a, sub, wg, b, s, stage, sidx, red);
+    else short_values<DT, 8>(a, sub, wg, b, s, stage, sidx, red);
   }
 }
 
@@ -1349,6 +1610,44 @@ static int launch_pack_kv(const QPPair& p, bool keys, bool values, int dtype, hi
   return ZC_OK;
 }
 
+// Whether a call's tensors are short enough for k_short_kv, and its shape.  The line lies where reading the longer subset once a
+// workgroup costs as much as the launch.  us as two launches and as one, one prompt and 16, bf16: 8 heads of 128
+// channels, 70 tokens in it (143 KB) 8.4 / 11.6 and 7.4 / 10.0, 90 (184 KB) 8.5 / 11.7 and 7.9 / 11.4, 105 (215 KB) 8.4 / 12.6 and 8.5 / 14.0;
+// 16 heads, 45 tokens (184 KB) 9.4 / 13.1 and 8.6 / 13.3; fp32: 8 heads of 64, 70 tokens (143 KB) 8.2 / 9.7 and 7.4 / 7.7;
+// 8 heads of 128, 45 (184 KB) 8.4 / 10.9 and 7.7 / 9.3; 12 heads of 64, 70 (215 KB) 8.3 / 11.1 and 8.7 / 11.6, and, with 58 rows a
+// thread (178 KB), 8.2 and 8.3: no more than 48.
+// Keys alone are one launch either way: few rows a thread, or workgroups enough (k_columns starts more): 45 tokens
+// 4.9 and 4.3 us, 70 the same, 84 4.9 and 5.2 (16 prompts of 16 heads 7.7 and 6.2).
+constexpr int64_t kShortBytes = 180 * 1024, kShortReads = 48;
+static bool short_plan(const QPPair& p, const zc_packed* const* out, int tensors, int dtype, ShortPlan& s) {
+  const QPArgs& a = p.t[0];
+  const PackRoute route = pack_route(a, out[0]->layout);
+  if (tensors == 2 ? !pack_joint(p, out, 2) : route == PackRoute::General) return false;
+  const bool keys = route == PackRoute::Keys, values = tensors == 2 || !keys;
+  const int64_t n = a.n[0] > a.n[1] ? a.n[0] : a.n[1], row_bytes = (int64_t)a.W * (dtype == ZC_F32 ? 4 : 2);
+  s.key_wgs = keys ? (int)ceil_div64(a.NV, kShortLanes) : 0;
+  if (n > kShortTokens) return false;
+  if (values ? n * row_bytes > kShortBytes : n > 72 && 2 * s.key_wgs * (int64_t)a.B < 128) return false;
+  s.team = values ? (int)align_up64(a.W / kPackCpt, 64) : 256;
+  s.teams = s.team <= 64 ? 4 : s.team <= 128 ? 2 : 1;
+  s.lanes = (int)(row_bytes / 16);
+  s.rows = values ? s.team * s.teams / s.lanes : 0;
+  if ((keys && n > kShortRows * (s.team * s.teams / kShortLanes)) || (values && n > kShortReads * s.rows)) return false;
+  for (int sub = 0; sub < 2; ++sub) {
+    const int wgs = (int)ceil_div64(a.units[sub], s.teams);
+    s.value_wgs[sub] = !values ? 0 : wgs > 0 ? wgs : 1;                // (an empty subset's parameters are written too)
+  }
+  return true;
+}
+static int launch_short(const QPPair& p, int dtype, const ShortPlan& s, hipStream_t st) {
+  const dim3 grid((unsigned)(2 * s.key_wgs + s.value_wgs[0] + s.value_wgs[1]), (unsigned)p.t[0].B), block((unsigned)(s.team * s.teams));
+  if (dtype == ZC_F32) hipLaunchKernelGGL(k_short_kv<ZC_F32>, grid, block, 0, st, p, s);
+  else if (dtype == ZC_F16) hipLaunchKernelGGL(k_short_kv<ZC_F16>, grid, block, 0, st, p, s);
+  else hipLaunchKernelGGL(k_short_kv<ZC_BF16>, grid, block, 0, st, p, s);
+  ZC_LAUNCH_CHECK();
+  return ZC_OK;
+}
+
 // Codes of what the column sweep has not packed.
 static int qp_launch_packs(const QPPair& p, const zc_packed* const* out, int tensors, int dtype, hipStream_t st) {
   if (pack_joint(p, out, tensors)) return launch_pack_kv(p, !p.t[0].resident, true, dtype, st);
@@ -1363,6 +1662,16 @@ static int qp_launch_packs(const QPPair& p, const zc_packed* const* out, int ten
   return ZC_OK;
 }
 
+// Parameters and codes of a call's tensors.
+static int qp_launch(QPPair& p, const zc_packed* const* out, int tensors, int dtype, hipStream_t st) {
+  if (tensors == 1) p.t[1] = p.t[0];
+  ShortPlan s;
+  if (short_plan(p, out, tensors, dtype, s)) return launch_short(p, dtype, s, st);
+  // statistics and parameters of both and codes of resident keys, then what is not packed yet
+  const int rc = qp_launch_columns(p, out, tensors, dtype, tensors == 2 && pack_joint(p, out, 2), st);
+  return rc ? rc : qp_launch_packs(p, out, tensors, dtype, st);
+}
+
 extern "C" int zc_quantize_pack(const zc_tensor4* x, const int32_t* salient_idx, int64_t k,
                                 const int32_t* regular_idx, int64_t n_reg, int64_t pos_offset,
                                 zc_packed* out, void* ws, size_t ws_bytes, void* stream) {
@@ -1372,8 +1681,7 @@ extern "C" int zc_quantize_pack(const zc_tensor4* x, const int32_t* salient_idx,
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
   const zc_packed* const outs[1] = {out};
-  rc = qp_launch_columns(p, outs, 1, x->dtype, false, st);
-  if (!rc) rc = qp_launch_packs(p, outs, 1, x->dtype, st);
+  rc = qp_launch(p, outs, 1, x->dtype, st);
   if (rc) return rc;
   qp_commit(out, k, n_reg);
   return ZC_OK;
@@ -1398,9 +1706,7 @@ extern "C" int zc_quantize_pack_kv(const zc_tensor4* xk, const zc_tensor4* xv, c
   hipStream_t st = (hipStream_t)stream;
   const int dt = xk->dtype;
   const zc_packed* const outs[2] = {outK, outV};
-  // statistics and parameters of both and codes of resident keys, then what is not packed yet
-  rc = qp_launch_columns(p, outs, 2, dt, pack_joint(p, outs, 2), st);
-  if (!rc) rc = qp_launch_packs(p, outs, 2, dt, st);
+  rc = qp_launch(p, outs, 2, dt, st);
   if (rc) return rc;
   qp_commit(outK, k, n_reg);
   qp_commit(outV, k, n_reg);

@@ -62,6 +62,56 @@ def test_channelwise_rows_in_second_place(first, H, D, n, dtype):
     _compare(first, ("channel", zb.ZC_LAYOUT_ROW), 1, H, D, 40, n, dtype)
 
 
+@pytest.mark.parametrize("special", [False, True])
+@pytest.mark.parametrize("H,D,dtype,k,bits", [
+    (1, 64, torch.bfloat16, 1, (4, 2)), (1, 64, torch.float32, 128, (2, 4)),          # rows of half the lanes keys take
+    (3, 64, torch.float16, 17, (8, 2)), (4, 64, torch.bfloat16, 128, (4, 2)),         # four teams a workgroup
+    (5, 64, torch.float32, 33, (2, 8)), (8, 64, torch.float16, 65, (4, 2)),           # two
+    (12, 64, torch.bfloat16, 96, (4, 2)), (12, 64, torch.float16, 97, (2, 4)),        # eight keys a thread, and one too many
+    (8, 128, torch.bfloat16, 90, (2, 4)), (8, 128, torch.float16, 91, (4, 2)),        # the most bytes, and one token more
+    (8, 128, torch.float32, 45, (4, 2)), (16, 128, torch.bfloat16, 45, (2, 8)), (16, 128, torch.float32, 22, (4, 2)),
+])
+def test_short_subsets_as_beside_long_ones(H, D, dtype, k, bits, special):
+    """A subset short enough for the one-launch kernel, alone, and the same beside one too long for it, which takes the
+    kernels of longer calls: all that belongs to the short one bit for bit, in joint and single calls, from token-major
+    tensors; the other, empty one has its default parameters.  (special: zeros, infinities, NaN, a channel of nothing else.)"""
+    B, n = 3, 131
+    g = torch.Generator(device=DEV).manual_seed(H + k)
+    X, Y = ((3 * torch.randn(B, k + n, H, D, generator=g, device=DEV)).to(dtype).permute(0, 2, 1, 3) for _ in range(2))
+    order = torch.stack([torch.randperm(k + n, generator=g, device=DEV) for _ in range(B)]).int()
+    sal, reg = (t.sort(dim=1).values.contiguous() for t in (order[:, :k], order[:, k:]))
+    if special:
+        first, last = sal[1, 0].item(), sal[1, -1].item()
+        for T in (X, Y):
+            T[0, 0, :, 1] = 0.0
+            T[0, 0, :, 2] = -0.0
+            T[1, 0, first, 3] = float("inf")
+            T[1, 0, last, 4] = -float("inf")
+            T[1, H - 1, first, D - 1] = float("nan")
+            T[2, H - 1, :, D - 2] = float("nan")
+    forms = [("channel", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP)]
+    want, got, one = ([_packed(f, B, H, D, k, n, bits) for f in forms] for _ in range(3))
+    none = reg[:, :0]
+    zb.zc_quantize_pack_kv(X, Y, sal, reg, *want, pos_offset=7)
+    zb.zc_quantize_pack_kv(X, Y, sal, none, *got, pos_offset=7)
+    zb.zc_quantize_pack(X, sal, none, one[0], pos_offset=7)
+    zb.zc_quantize_pack(Y, sal, none, one[1], pos_offset=7)
+    raw = lambda t: t.contiguous().view(torch.uint8)
+    for w, *others in zip(want, got, one):
+        for o in others:
+            for name in ("codes_hi", "tok_scale_hi", "tok_zero_hi", "pos_hi"):
+                a, b = getattr(w, name), getattr(o, name)
+                if a is not None and name.startswith(("tok", "pos")):
+                    a, b = a[:, :k], b[:, :k]
+                assert a is None or torch.equal(raw(a), raw(b)), (w.scheme, name)
+            for name, default in (("chan_scale", 1.0), ("chan_zero", 0.0)):
+                a, b = getattr(w, name).flatten(), getattr(o, name).flatten()
+                half = a.numel() // 2
+                assert torch.equal(raw(a[:half]), raw(b[:half])), (w.scheme, name)
+                assert bool((b[half:] == default).all()), (w.scheme, name)
+            assert o.chunk_table.flatten()[:4].tolist() == [0, k, 0, 0] and o.chunks == [(0, k, 0, 0)]
+
+
 def _largest(form, H, n, bits, dtype):
     """`n` tokens of which a few are not zero, packed; the same few (and a zero one) in a call of their own."""
     D = 64
