@@ -61,7 +61,8 @@ struct ProbeArgs {
   // their ends on (0: not at all)
   int even1, even2;
   int group;             // sweep 2: query heads whose columns an XCD takes from the first on together (0: a head after the other)
-  int small;             // 1: few probe rows, sweep 2 and the mean in one launch
+  int few_cols;          // few probe rows, sweep 2 and the mean in one launch: of so many times 16 columns a workgroup (0: not)
+  int few_blocks;        // of so many blocks of 16 probe rows a wave
   int normalize;         // 1: divide a column's sum by the number of probes that see it (Eq. 8); 0: Eq. 7
 };
 
@@ -690,11 +691,13 @@ __global__ __launch_bounds__(256) void k_probe_mean(const float* __restrict__ pe
 }
 
 // ---- few probe rows ----------------------------------------------------------------------
-// Sweep 2 and the mean over heads in one launch: a workgroup owns 32 columns of a batch element
-// for all heads, a wave a run of consecutive heads; rows and columns go straight from memory to
-// operand registers (each is used once, LDS would only add a trip).  Bound by what the loads of
-// one CU bring in, 32 cache lines an instruction: 8 heads of 64 channels, 256 tokens, 26 rows,
-// fp32: 8 us, 11 as two launches with a 64-row tile per head.
+// Sweep 2 and the mean over heads in one launch: a workgroup owns 16 NC columns of a batch element for all heads, a wave a
+// run of blocks of 16 probe rows, head after head; rows and columns go straight from memory to operand registers (each is
+// used once, and bringing them to LDS in whole lines was no faster: a CU gets about 37 KB a us from beyond its L2 either
+// way).  Bound by that and by the chain of the two trips, so 16 columns where the workgroups find a CU each; 32, which read the
+// probe rows half as often, where they do not.  us, two launches and this (32 columns and 32 rows a wave before): 8 heads of 64
+// channels, bf16, 100 tokens, 10 rows 5.8 and 3.7 (4.5); 256 tokens, 26 rows, fp32 7.8 and 6.4 (7.3); 16 heads of 128, 100 tokens, fp32 10.0 and
+// 8.9; 8 x 32 heads over 8, 1000 tokens, 10 rows, bf16 13.0 and 10.0 (10.8); 16 of them, fp32 92 and 38.
 __device__ inline int lower_bound_pos(const int32_t* pos, int n, int key) {
   int lo = 0, hi = n;
   while (lo < hi) {
@@ -704,75 +707,144 @@ __device__ inline int lower_bound_pos(const int32_t* pos, int n, int key) {
   return lo;
 }
 
-constexpr int kSmallRows = 32;        // most probe rows
-constexpr int kSmallTable = 4096;     // most log-sum-exps of a batch element (heads x rows)
-constexpr int small_threads(int dt, int d) { return dt == ZC_F32 && d == 128 ? 512 : 1024; }
+constexpr int kFewRows = 32;          // most probe rows
+constexpr int kFewTable = 4096;       // most log-sum-exps of a batch element (heads x rows)
+// Whether a wave of 32 columns takes two blocks of a head together (for long fp32 rows there are no registers).
+constexpr bool few_both(int64_t P, bool fp32, int64_t D) { return P > 16 && !(fp32 && D == 128); }
+typedef float v4f __attribute__((ext_vector_type(4)));
+// 16 x 16 result over one 16-byte chunk a lane (lane: row or column lane % 16, k chunk lane / 16).
+template <int DT>
+__device__ inline void mma16(v4f& acc, u32x4 a, u32x4 b) {
+  if constexpr (DT == ZC_BF16) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+  } else if constexpr (DT == ZC_F16) {
+    acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), acc, 0, 0, 0);
+  } else {
+    // (the elements one by one on purpose, see mma_chunk)
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
+  }
+}
 
-template <int DT, int D>
-__global__ __launch_bounds__(small_threads(DT, D)) void k_probe_small(ProbeArgs a, float* __restrict__ scores) {
+// BOTH: a wave takes the two blocks of a head together.
+template <int DT, int D, int NC, bool BOTH, bool PER_HEAD>
+__global__ __launch_bounds__(1024) void k_probe_few(ProbeArgs a, float* __restrict__ scores) {
   using T = Tile<DT, D>;
-  constexpr int NT = small_threads(DT, D), NW = NT / 64;
-  __shared__ float slse[kSmallTable];
-  __shared__ int spos[kSmallRows], srow[kSmallRows];
-  __shared__ float part[NW][32];
-  const int b = blockIdx.y, col0 = blockIdx.x * 32;
-  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
+  constexpr int NK = T::ROWB / 64;                   // 16-byte chunks of a lane in a row
+  constexpr bool AHEAD = !BOTH && NK * (NC + 2) <= 24;        // the next block's rows are requested in front of a block's products
+  __shared__ float slse[kFewTable];
+  __shared__ int spos[kFewRows], srow[kFewRows];
+  __shared__ float part[16][16 * NC];
+  const int b = blockIdx.y, col0 = blockIdx.x * 16 * NC;
+  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4, nw = blockDim.x >> 6;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t k_rowb = (uint32_t)(a.k_sL * T::EB), q_rowb = (uint32_t)(a.q_sL * T::EB);
+  // consecutive blocks of 16 probe rows, head after head, to a wave: one load of K serves those that share it
+  const int rt = (a.P + 15) >> 4, u0 = w * a.few_blocks, u1 = min(u0 + a.few_blocks, a.Hq * rt);
+  u32x4 kf[NC][NK], qf[AHEAD || BOTH ? 2 : 1][NK];
+  auto load_k = [&](int h) {
+    const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)(h / a.G) * a.k_sH) * T::EB;
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.Lk - 1) * k_rowb + T::ROWB, kBufFlags);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int col = col0 + 16 * c + i;             // (columns past the end: zeros)
+      const int off = col < a.Lk ? (int)((uint32_t)col * k_rowb) + g * 16 : kOutOfRange;
+#pragma unroll
+      for (int kc = 0; kc < NK; ++kc) kf[c][kc] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + kc * 64, 0, 0);
+    }
+  };
+  auto load_q = [&](int u, u32x4 (&f)[NK]) {
+    const int h = rt == 1 ? u : u >> 1, p = (rt == 1 ? 0 : (u & 1) * 16) + i;
+    const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)h * a.q_sH) * T::EB;
+    const auto rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.Lq - 1) * q_rowb + T::ROWB, kBufFlags);
+    const int off = p < a.P ? (int)((uint32_t)srow[p] * q_rowb) + g * 16 : kOutOfRange;
+#pragma unroll
+    for (int kc = 0; kc < NK; ++kc) f[kc] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + kc * 64, 0, 0);
+  };
+  if (u0 < u1) load_k(rt == 1 ? u0 : u0 >> 1);       // (needs nothing of the probes)
   const int ntab = a.Hq * a.P;
   const float* lse_src = (a.lse_in ? a.lse_in : a.lse2) + (int64_t)b * ntab;
   const float unit = a.lse_in ? kLog2e : 1.f;        // an external log-sum-exp is in natural units
-  for (int i = tid; i < ntab; i += NT) slse[i] = lse_src[i] * unit;
   if (tid < a.P) {
     const int pos = a.probe_pos[tid];
     spos[tid] = pos;
     srow[tid] = a.probe_rows ? a.probe_rows[tid] : pos;
   }
+  for (int t = tid; t < ntab; t += blockDim.x) slse[t] = lse_src[t] * unit;
   __syncthreads();
-
-  const uint32_t k_rowb = (uint32_t)(a.k_sL * T::EB), q_rowb = (uint32_t)(a.q_sL * T::EB);
-  const int col = col0 + r;
-  const int koff = col < a.Lk ? (int)((uint32_t)col * k_rowb) + kh * 16 : kOutOfRange;     // (columns past the end: zeros)
-  float sum = 0.f;
-  int cnt_col = 0;                                   // (per-head scores: probe rows that see this lane's column)
-  if (a.per_head) cnt_col = a.P - lower_bound_pos(spos, a.P, col);
-  // consecutive heads to a wave: one load of K serves those that share it
-  const int per = ceil_div(a.Hq, NW), h_end = min((w + 1) * per, a.Hq);
-  u32x4 kf[T::NKC];
-  for (int h = w * per; h < h_end; ++h) {
-    const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)h * a.q_sH) * T::EB;
-    const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)(h / a.G) * a.k_sH) * T::EB;
-    const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.Lq - 1) * q_rowb + T::ROWB, kBufFlags);
-    const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.Lk - 1) * k_rowb + T::ROWB, kBufFlags);
-    if (h == w * per || h % a.G == 0) {
+  float sum[NC], all[NC];                            // all: PER_HEAD, the heads so far
 #pragma unroll
-      for (int kc = 0; kc < T::NKC; ++kc) kf[kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_k, koff + kc * 32, 0, 0);
+  for (int c = 0; c < NC; ++c) sum[c] = all[c] = 0.f;
+  auto block = [&](int u, const u32x4 (&f)[NK]) {
+    const int h = rt == 1 ? u : u >> 1, p0 = (rt == 1 ? 0 : (u & 1) * 16) + 4 * g;
+    v4f acc[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) acc[c] = v4f{};
+#pragma unroll
+    for (int kc = 0; kc < NK; ++kc)                  // (the columns' chains of products side by side)
+#pragma unroll
+      for (int c = 0; c < NC; ++c) mma16<DT>(acc[c], f[kc], kf[c][kc]);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+      const int col = col0 + 16 * c + i;
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int p = p0 + v, pc = min(p, a.P - 1);
+        const float e = __builtin_amdgcn_exp2f(fmaf(acc[c][v], a.scale_log2, -slse[h * a.P + pc]));
+        sum[c] += (p < a.P && col <= spos[pc]) ? e : 0.f;
+      }
     }
-    const int qoff = r < a.P ? (int)((uint32_t)srow[r] * q_rowb) + kh * 16 : kOutOfRange;
-    v16f acc = {};
+    if constexpr (PER_HEAD) {
+      if (rt == 1 || (u & 1)) {                      // a head's last block (its first is this wave's too)
 #pragma unroll
-    for (int kc = 0; kc < T::NKC; ++kc)
-      mma_chunk<DT>(acc, __builtin_amdgcn_raw_buffer_load_b128(rs_q, qoff + kc * 32, 0, 0), kf[kc]);
-    float head_sum = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const int p = acc_row(v, kh), pc = min(p, a.P - 1);
-      const float e = __builtin_amdgcn_exp2f(fmaf(acc[v], a.scale_log2, -slse[h * a.P + pc]));
-      head_sum += (p < a.P && col <= spos[pc]) ? e : 0.f;
+        for (int c = 0; c < NC; ++c) {
+          const float total = (sum[c] + __shfl_xor(sum[c], 16)) + __shfl_xor(sum[c] + __shfl_xor(sum[c], 16), 32);
+          const int col = col0 + 16 * c + i, cnt = a.P - lower_bound_pos(spos, a.P, col);
+          if (g == 0 && col < a.Lk)
+            a.per_head[((int64_t)b * a.Hq + h) * a.Lk + col] = !a.normalize ? total : (cnt > 0 ? total / (float)cnt : 0.f);
+          all[c] += sum[c];
+          sum[c] = 0.f;
+        }
+      }
     }
-    sum += head_sum;
-    if (a.per_head) {
-      head_sum += __shfl_xor(head_sum, 32);
-      if (kh == 0 && col < a.Lk)
-        a.per_head[((int64_t)b * a.Hq + h) * a.Lk + col] = !a.normalize ? head_sum : (cnt_col > 0 ? head_sum / (float)cnt_col : 0.f);
+  };
+  if constexpr (BOTH) {
+    for (int u = u0; u < u1; u += 2) {
+      load_q(u, qf[0]);
+      load_q(u + 1, qf[1]);
+      block(u, qf[0]);
+      block(u + 1, qf[1]);
+      if (u + 2 < u1 && (u + 2) % (2 * a.G) == 0) load_k((u + 2) >> 1);
+    }
+  } else {
+    if (u0 < u1) load_q(u0, qf[0]);
+    for (int u = u0; u < u1; ++u) {
+      if constexpr (AHEAD) { if (u + 1 < u1) load_q(u + 1, qf[1]); }
+      block(u, qf[0]);
+      if (u + 1 < u1) {
+        if ((u + 1) % (a.G * rt) == 0) load_k(rt == 1 ? u + 1 : (u + 1) >> 1);
+        if constexpr (AHEAD) {
+#pragma unroll
+          for (int kc = 0; kc < NK; ++kc) qf[0][kc] = qf[1][kc];
+        } else {
+          load_q(u + 1, qf[0]);
+        }
+      }
     }
   }
-  sum += __shfl_xor(sum, 32);
-  if (kh == 0) part[w][r] = sum;
-  __syncthreads();
-  if (tid < 32 && col0 + tid < a.Lk) {
-    float total = 0.f;
 #pragma unroll
-    for (int v = 0; v < NW; ++v) total += part[v][tid];
+  for (int c = 0; c < NC; ++c) {
+    if constexpr (PER_HEAD) sum[c] = all[c];
+    sum[c] += __shfl_xor(sum[c], 16);
+    sum[c] += __shfl_xor(sum[c], 32);
+    if (g == 0) part[w][16 * c + i] = sum[c];
+  }
+  __syncthreads();
+  if (tid < 16 * NC && col0 + tid < a.Lk) {
+    float total = 0.f;
+    for (int v = 0; v < nw; ++v) total += part[v][tid];
     const int cnt = a.P - lower_bound_pos(spos, a.P, col0 + tid);
     if (a.normalize) total = cnt > 0 ? total / (float)cnt : 0.f;
     scores[(int64_t)b * a.Lk + col0 + tid] = total / (float)a.Hq;
@@ -790,8 +862,12 @@ static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStr
       ZC_LAUNCH_CHECK();
     }
   }
-  if (a.small) {
-    hipLaunchKernelGGL((k_probe_small<DT, D>), dim3((unsigned)ceil_div(a.Lk, 32), (unsigned)a.B), dim3(small_threads(DT, D)), 0, st, a, scores);
+  if (a.few_cols) {
+    const dim3 grid((unsigned)ceil_div(a.Lk, 16 * a.few_cols), (unsigned)a.B), block(64 * ceil_div(a.Hq * ceil_div(a.P, 16), a.few_blocks));
+    if (a.per_head) hipLaunchKernelGGL((k_probe_few<DT, D, 1, false, true>), grid, block, 0, st, a, scores);
+    else if (a.few_cols == 1) hipLaunchKernelGGL((k_probe_few<DT, D, 1, false, false>), grid, block, 0, st, a, scores);
+    else if (few_both(a.P, DT == ZC_F32, D)) hipLaunchKernelGGL((k_probe_few<DT, D, 2, few_both(kFewRows, DT == ZC_F32, D), false>), grid, block, 0, st, a, scores);
+    else hipLaunchKernelGGL((k_probe_few<DT, D, 2, false, false>), grid, block, 0, st, a, scores);
     ZC_LAUNCH_CHECK();
     return ZC_OK;
   }
@@ -850,19 +926,37 @@ static bool even_waves(int64_t wgs, double tiles, const zc_tensor4* q) {
   const int64_t places = q->dtype == ZC_F32 && q->D == 128 ? 512 : 1024;
   return wgs > 256 && wgs <= places && tiles >= 4.0;
 }
-// Whether few probe rows are served by one launch: a block of 32, and no more bytes per
-// workgroup than its CU's loads bring in within the time the other path's two launches take
-// (8 heads of 64 channels, 256 tokens, 26 rows, fp32, 119 KB: 8 against 11 us; 32 heads of 128
-// channels over 8, 64 tokens, 4 rows, 16 bit, 163 KB: 9.9 against 9.1); three times that
-// where the columns fill the chip (16 x 32 heads, 256 tokens, 26 rows, 344 KB: 14.9 against
-// 18.9).  Fewer than 16 heads leave waves without work, which shows over many columns (16 x 8
-// heads of 64 channels, 20000 tokens, 32 rows: 160 against 129 us; 16 x 1 head, 96 against 36).
-static bool probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P, int64_t row_bytes) {
-  if (P > kSmallRows || Hq * P > kSmallTable) return false;
-  const int64_t segments = Hkv > 16 ? Hkv : (Hq < 16 ? Hq : 16);        // K loads: by waves and KV heads
-  if (Hq < 16 && Lk > 1024) return false;
-  const int64_t limit = B * ceil_div64(Lk, 32) >= 256 ? 384 * 1024 : 128 * 1024;
-  return (segments * 32 + Hq * P) * row_bytes <= limit;
+// Whether few probe rows are served by one launch (k_probe_few), with how many times 16 columns a workgroup and blocks of 16 rows a
+// wave, by what the ways cost in us.  One launch: the trips of its start, those of a wave's further blocks, and, a round of
+// a workgroup per CU, the bytes each reads (K once a wave), of which a CU gets 37 KB a us, all of them together in several
+// rounds 22 (fp32) and 28.  Two: workgroups of a head's 128 columns, of which
+// fp32 has one a CU and 16-bit types four.  us, two launches and one, measured and as priced: bf16, 8 heads of 64 channels, 100 tokens, 10
+// rows 5.8 / 3.7 and 5.9 / 3.7; 16 heads over 4, 300 tokens, 30 rows 5.9 / 5.6 and 5.9 / 5.7; 32 heads over 8 of 128 channels, 100 tokens
+// 6.2 / 7.4 and 6.2 / 7.9; 16 x 32 over 8, 1000 tokens 22.5 / 18.4 (32 columns) and 21.9 / 18.9; fp32, 12 heads of 64,
+// 256 tokens, 26 rows 7.9 / 7.5 and 8.1 / 7.8; 16 of 128, 100 tokens 10.0 / 8.9 and 10 / 8.5; 24 over 8, 64 tokens, 7 rows 9.9 / 10.3 and 10 / 10.2.
+struct FewPlan { int cols, blocks; };
+static FewPlan probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P, int64_t D, bool fp32, bool per_head) {
+  FewPlan plan = {0, 0};
+  if (P > kFewRows || Hq * P > kFewTable) return plan;
+  const int64_t row_bytes = D * (fp32 ? 4 : 2), rt = ceil_div64(P, 16);
+  const double wgs = (double)(ceil_div64(Lk, 128) * Hq * B) / 256.0;
+  double best, further;
+  if (fp32) {
+    best = (D == 64 ? 7.9 : 10.0) + (wgs > 1.0 ? (D == 64 ? 2.4 : 5.3) * (wgs - 1.0) : 0.0);
+    further = D == 64 ? 1.5 : 2.3;
+  } else {
+    best = (D == 64 ? 5.8 : 6.1) + 0.5 * (wgs < 4.0 ? wgs : 4.0) + (wgs > 4.0 ? (D == 64 ? 0.85 : 1.15) * (wgs - 4.0) : 0.0);
+    further = D == 64 ? 0.2 : 1.1;
+  }
+  for (int64_t nc = 1; nc <= (per_head ? 1 : 2); ++nc)
+    for (int64_t share = per_head || (nc == 2 && few_both(P, fp32, D)) ? rt : 1; share <= (nc == 2 && !few_both(P, fp32, D) ? 1 : rt); ++share) {
+      const int64_t blocks = ceil_div64(Hq * rt, 16 * share) * share, waves = ceil_div64(Hq * rt, blocks), segments = Hkv > waves ? Hkv : waves;
+      const int64_t n = B * ceil_div64(Lk, 16 * nc), rounds = ceil_div64(n, 256);
+      const double rate = rounds == 1 ? 37.0 : fp32 ? 22.0 : 28.0;
+      const double t = 3.0 + further * (double)(blocks - 1) + (double)(rounds * (segments * 16 * nc + Hq * P) * row_bytes) / (1e3 * rate);
+      if (t < best) { best = t; plan = {(int)nc, (int)blocks}; }
+    }
+  return plan;
 }
 static size_t lse_bytes(int64_t B, int64_t Hq, int64_t P) { return (size_t)align_up64(B * Hq * P * (kProbeParts * (int64_t)sizeof(float2) + 4), 256); }
 
@@ -921,8 +1015,10 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.probe_rows = probe_rows; a.probe_pos = probe_pos;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse_in = lse_ext;
-  a.small = probe_few(q->B, q->H, k->H, k->L, P, q->D * (q->dtype == ZC_F32 ? 4 : 2));
-  a.join = !lse_ext && !a.small && probe_join(q->B, q->H, k->L, P) && ws_bytes >= need + extra;
+  const FewPlan few = probe_few(q->B, q->H, k->H, k->L, P, q->D, q->dtype == ZC_F32, scores_per_head != nullptr);
+  a.few_cols = few.cols;
+  a.few_blocks = few.blocks;
+  a.join = !lse_ext && !a.few_cols && probe_join(q->B, q->H, k->L, P) && ws_bytes >= need + extra;
   float* ws_ph = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + lse_bytes(q->B, q->H, P) + (a.join ? extra : 0));
   // [log-sum-exps][column ranges' pairs, up to the end of the workspace: the per-head scores, at
   // their place in it, are written when the pairs have been read]; joined by sweep 2 [pairs][per-head scores]
@@ -943,7 +1039,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
     a.group = heads % 8 == 0 && wgs2 > 256 && (P > 64 || q->dtype == ZC_F32) ? (int)(groups > 1 ? ceil_div64(hpx, groups) : hpx) : 0;
   }
   a.normalize = normalize ? 1 : 0;
-  a.per_head = scores_per_head || a.small ? scores_per_head : ws_ph;       // (few rows: only where the caller asks for them)
+  a.per_head = scores_per_head || a.few_cols ? scores_per_head : ws_ph;       // (few rows: only where the caller asks for them)
 
   hipStream_t st = (hipStream_t)stream;
   const bool need_lse = lse_ext == nullptr;

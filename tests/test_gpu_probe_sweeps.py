@@ -183,3 +183,47 @@ def test_every_column_of_every_head_of_a_group(B, Hq, Hkv, d, L, P, dtype):
         rel = ((per_head[:, h].double() - want).abs() / want.clamp(min=1e-30)).max().item()
         assert rel < 3e-5, (h, rel)                              # (the bound of test_scores_of_row_blocks_and_ranges)
     assert torch.allclose(per_head.mean(1), scores, rtol=1e-5, atol=0)
+
+
+# Few probes, sweep 2 and the mean in one launch: 1, 15 to 17, 31 and 32 rows (blocks of 16, halves of a head's two by waves of
+# their own and by one), fewer heads than waves, one wave more and heads that do not divide by them, columns of less than a
+# tile, of whole tiles and one more, 16 a workgroup and (enough of them for more than a round) 32, every probe at one position,
+# probes in front of most columns
+FEW = [
+    (1, 1, 1, 64, 1, torch.float16, lambda L: torch.arange(1)),
+    (3, 8, 8, 64, 16, torch.float32, lambda L: torch.arange(1, 16)),
+    (2, 8, 2, 128, 17, torch.bfloat16, lambda L: torch.arange(1, 17)),
+    (2, 8, 8, 64, 100, torch.float16, lambda L: spread(L, 17)),
+    (1, 9, 3, 64, 257, torch.bfloat16, lambda L: spread(L, 31)),
+    (1, 16, 16, 128, 33, torch.float32, lambda L: torch.full((16,), 32)),
+    (2, 17, 1, 64, 95, torch.float32, lambda L: spread(L, 32)),
+    (1, 33, 11, 64, 64, torch.bfloat16, lambda L: torch.arange(5, 37)),
+    (12, 24, 8, 128, 700, torch.float32, lambda L: spread(L, 9)),
+    (16, 16, 4, 64, 1000, torch.bfloat16, lambda L: torch.arange(480, 496)),
+    (9, 8, 4, 128, 1500, torch.float16, lambda L: spread(L, 20)),
+]
+
+
+@pytest.mark.parametrize("external", [False, True])
+@pytest.mark.parametrize("case", range(len(FEW)))
+def test_scores_of_few_probes_in_one_launch(case, external):
+    B, Hq, Hkv, d, L, dtype, probes = FEW[case]
+    g = torch.Generator(device=DEV).manual_seed(case)
+    pos = probes(L).to(DEV)
+    P = pos.numel()
+    q = (torch.randn(B, Hq, P + 3, d, generator=g, device=DEV) + 0.25).to(dtype)
+    rows = torch.randperm(P + 3, generator=g, device=DEV)[:P]
+    k = torch.randn(B, L, Hkv, d, generator=g, device=DEV)                       # a token's heads side by side
+    k[..., ::31] *= 15.0
+    k = k.to(dtype).transpose(1, 2)
+    lse = 40.0 + torch.randn(B, Hq, P, generator=g, device=DEV) if external else None
+    want = reference(q, k, rows, pos, lse)
+    per_head = torch.full((B, Hq, L), float("nan"), device=DEV)
+    got = [zb.zc_probe_saliency(q, k, pos.int(), probe_rows=rows.int(), lse_ext=lse, scores_per_head=ph) for ph in (None, per_head)]
+    for s in got:
+        rel = ((s.double() - want).abs() / want.clamp(min=1e-30)).max().item()
+        assert rel < 3e-5, rel                                                   # (the bound of test_scores_of_row_blocks_and_ranges)
+    assert torch.allclose(per_head.mean(1), got[1], rtol=1e-5, atol=0)
+    summed = zb.zc_probe_accumulated(q, k, pos.int(), probe_rows=rows.int(), lse_ext=lse)
+    seen = (pos[:, None] >= torch.arange(L, device=DEV)[None]).sum(0).clamp(min=1)
+    assert torch.allclose(summed / seen, got[0], rtol=1e-5, atol=0)
