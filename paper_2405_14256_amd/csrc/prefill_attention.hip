@@ -678,6 +678,283 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
   }
 }
 
+// The same for calls that leave much of the chip idle: KS of a workgroup's four waves share 32 rows, each with every KS-th
+// 32 keys, a reference, a sum and an output of its own, joined in LDS at the end; a tile is 32 KS keys, of which a wave takes
+// one step.  Bound by the chain of a row block's steps, which a wave alone on its SIMD takes 0.6 us for (128 channels), and by the
+// start and the join.  us, one wave a row and here: 16 heads over 4 of 64 channels, 1000 rows 16.2 -> 9.1 (four), 2000 28.0 ->
+// 19.4 (two); 8 of 64, 700 rows 11.7 -> 7.3; 32 over 8 of 128, 120 rows 7.0 -> 5.9, 300 9.7 -> 8.6, 1000 23.7 -> 19.5; 16 of 128, 2000 rows
+// 39.5 -> 30.9; but 2000 rows of 32 heads of 128, a full chip, 49.1 -> 51.0.
+template <int DT, int D, int KS>
+__global__ __launch_bounds__(256, KS == 4 && D == 128 ? 1 : 2) void k_prefill_attention16_keys(PrefillArgs a) {
+  using T = Tile<DT, D>;
+  constexpr int NW = 4, ROWS = 32 * NW / KS, KEYS = 32 * KS;
+  constexpr int TILE_B = KEYS * T::ROWB;
+  constexpr int NI = KEYS / T::RPI / NW;      // transfers per wave, tile and tensor
+  constexpr int CT = D / 32;                     // 32-channel tiles of the output
+  constexpr int EPS = 16 / T::NKC;               // logits per slice
+  constexpr int VS = T::NKC / 4;                 // the slice that requests the first V operand
+  static_assert(NI >= 1, "a wave moves whole transfers");
+  __shared__ __align__(1024) uint8_t tiles[4 * TILE_B];                // K, K, V, V; then the waves' outputs
+  __shared__ float sum[NW][2][64];
+  __shared__ float slse[ROWS];
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+  int hq, b, q0;
+  prefill_block(a, ROWS, &b, &hq, &q0);
+  const int hk = hq / a.G;
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint8_t* qb = reinterpret_cast<const uint8_t*>(a.q) + ((int64_t)b * a.q_sB + (int64_t)hq * a.q_sH) * 2;
+  const uint8_t* kb = reinterpret_cast<const uint8_t*>(a.k) + ((int64_t)b * a.k_sB + (int64_t)hk * a.k_sH) * 2;
+  const uint8_t* vb = reinterpret_cast<const uint8_t*>(a.v) + ((int64_t)b * a.v_sB + (int64_t)hk * a.v_sH) * 2;
+  const uint32_t q_rowb = (uint32_t)(a.q_sL * 2), k_rowb = (uint32_t)(a.k_sL * 2), v_rowb = (uint32_t)(a.v_sL * 2);
+  const auto rs_q = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(qb), 0, (uint32_t)(a.L - 1) * q_rowb + T::ROWB, kBufFlags);
+  const auto rs_k = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(kb), 0, (uint32_t)(a.L - 1) * k_rowb + T::ROWB, kBufFlags);
+  const auto rs_v = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(vb), 0, (uint32_t)(a.L - 1) * v_rowb + T::ROWB, kBufFlags);
+
+  const int kg = w % KS;                                              // this wave's 32 keys of every tile
+  const int ntiles = (min(q0 + ROWS, a.L) - 1) / KEYS + 1;            // key tiles the workgroup can see
+  const int wq0 = q0 + 32 * (w / KS);                                 // first row of this wave
+  const int qpos = wq0 + r;                                           // this lane's row
+  const int nh = wq0 < a.L ? wq0 / 32 + 1 : 0;                        // blocks of 32 keys its rows can see: the last is the diagonal
+  const int nt = (nh + KS - 1 - kg) / KS;                             // tiles of which its keys are among them
+  const bool diagonal = (nh - 1) % KS == kg;                          // the last of them is the diagonal
+
+  const uint32_t ks_lds = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)&tiles[0];
+  const uint32_t vs_lds = ks_lds + 2 * TILE_B;
+  int kvoff[NI], vvoff[NI];
+#pragma unroll
+  for (int jj = 0; jj < NI; ++jj) {
+    const int row = (w + NW * jj) * T::RPI + lane / T::CPR;
+    kvoff[jj] = (int)(row * k_rowb) + (((lane % T::CPR) ^ T::swz(row)) << 4);
+    vvoff[jj] = (int)(row * v_rowb) + (((lane % T::CPR) ^ v_swizzle<D>(row)) << 4);
+  }
+  // (the tile's offset is part of the per-lane offset, which the range check sees: rows
+  // past the end arrive as zeros)
+  auto k_issue = [&](int t) {
+    const int toff = (int)((uint32_t)t * KEYS * k_rowb);
+#pragma unroll
+    for (int jj = 0; jj < NI; ++jj) dma16<0>(ks_lds + (t & 1) * TILE_B + (w + NW * jj) * 1024, rs_k, kvoff[jj] + toff, 0);
+  };
+  auto v_issue = [&](int t) {
+    const int toff = (int)((uint32_t)t * KEYS * v_rowb);
+#pragma unroll
+    for (int jj = 0; jj < NI; ++jj) dma16<0>(vs_lds + (t & 1) * TILE_B + (w + NW * jj) * 1024, rs_v, vvoff[jj] + toff, 0);
+  };
+
+  k_issue(0);
+  v_issue(0);
+  if (ntiles > 1) k_issue(1);
+  // this wave's query rows, straight into operand registers (rows past the end: zeros)
+  u32x4 qf[T::NKC];
+  {
+    const int voff = qpos < a.L ? (int)((uint32_t)qpos * q_rowb) + kh * 16 : kOutOfRange;
+#pragma unroll
+    for (int kc = 0; kc < T::NKC; ++kc) qf[kc] = __builtin_amdgcn_raw_buffer_load_b128(rs_q, voff + kc * 32, 0, 0);
+  }
+
+  // ---- operands from LDS -----------------------------------------------------------------
+  struct KFrag { u32x4 x[T::NKC]; };
+  // (LDS addresses: one register per lane and chunk pattern, tile and half in the offset of
+  // the instruction; the empty assembly keeps the compiler from holding a register for each)
+  typedef __attribute__((address_space(3))) const uint8_t* lds_ptr;
+  uint32_t kaddr = ks_lds + T::slot(r, kh);           // chunk 2 kc + kh sits at kaddr ^ (32 kc)
+  asm volatile("" : "+v"(kaddr));
+  auto k_read = [&](KFrag& f) {
+#pragma unroll
+    for (int kc = 0; kc < T::NKC; ++kc) f.x[kc] = *(__attribute__((address_space(3))) const u32x4*)((lds_ptr)(uintptr_t)(kaddr ^ (32 * kc)));
+  };
+  // The transposing load: in every 16 lanes, lanes 4 i .. 4 i + 3 name the 16 channels of key
+  // i, and lane c receives channel c of the four keys.  A lane's 8 k-indices of operand chunk
+  // s are the keys its logit accumulators 8 s .. 8 s + 7 stand for: 16 s + 4 kh + {0 .. 3} and
+  // 16 s + 8 + 4 kh + {0 .. 3}.
+  const int vkey = 4 * kh + ((lane & 15) >> 2);
+  const int vsub = ((lane >> 4) & 1) * 2 + ((lane & 3) >> 1);         // 16-byte chunk inside a 32-channel tile
+  uint32_t vaddr[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) {
+    vaddr[ct] = vs_lds + vkey * T::ROWB + (((4 * ct + vsub) ^ v_swizzle<D>(vkey)) << 4) + (lane & 1) * 8;
+    asm volatile("" : "+v"(vaddr[ct]));
+  }
+  auto v_read = [&](int s, int ct, u32x4& f) {
+    // (the swizzle depends on the key's lowest two bits only)
+    const lds_ptr base = (lds_ptr)(uintptr_t)vaddr[ct] + 16 * s * T::ROWB;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)base);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(base + 8 * T::ROWB));
+    const uint2 l2 = __builtin_bit_cast(uint2, lo), h2 = __builtin_bit_cast(uint2, hi);
+    f.x = l2.x; f.y = l2.y; f.z = h2.x; f.w = h2.y;
+  };
+
+  v16f oacc[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[ct][i] = 0.f;
+  float m = -INFINITY, l = 0.f;       // the row's running maximum (log2 units) and this half-wave's share of the sum
+  KFrag kf;
+  v16f s0, s1;
+
+  kaddr += kg * 32 * T::ROWB;                        // (every address: of this wave's keys)
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) vaddr[ct] += kg * 32 * T::ROWB;
+  wait_all_loads();
+  __syncthreads();
+  k_read(kf);
+  s0 = v16f{};
+#pragma unroll
+  for (int kc = 0; kc < T::NKC; ++kc) mma_chunk<DT>(s0, kf.x[kc], qf[kc]);
+  kaddr += TILE_B;                                   // the K operands of a step are those of the next tile
+
+  // Largest logit (log2 units) of a half in either half-wave.  (The maximum is taken over the raw
+  // products - the scale is positive - and the scale enters the weights with the subtraction of
+  // the reference: one fused multiply-add per logit.)
+  auto half_max = [&](const v16f& sc) {
+    float t = sc[0];
+#pragma unroll
+    for (int v = 1; v < 16; ++v) t = fmaxf(t, sc[v]);
+    const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(t), __float_as_uint(t), false, false);
+    return fmaxf(__uint_as_float(both[0]), __uint_as_float(both[1])) * a.scale_log2;
+  };
+  float tmax = half_max(s0);                         // of the half whose weights are taken next
+
+  // One step: weights of the logits sc, output += V^T P; unless it is the wave's LAST, the logits of its keys of the next tile
+  // meanwhile, and their maximum.
+  auto step = [&](auto last_c, v16f& sc, v16f& sn) {
+    constexpr bool LAST = decltype(last_c)::value;
+    u32x4 vf[2][CT];
+    if constexpr (LAST) {
+      if (diagonal) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (acc_row(v, kh) > r) sc[v] = -INFINITY;
+        tmax = half_max(sc);
+      }
+    } else {
+      k_read(kf);
+    }
+    const float m_new = fmaxf(m, tmax);
+    if (__builtin_amdgcn_ballot_w64(m_new > m)) {
+      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+      l *= alpha;
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[ct][i] *= alpha;
+      m = m_new;
+    }
+    uint32_t pw[8];                                  // the weights, two to a word
+    float psum = 0.f;
+    const float nm = m == -INFINITY ? 0.f : -m;      // (a wave whose logits are all -inf so far: its weights are 0)
+    if constexpr (!LAST) sn = v16f{};
+#pragma unroll
+    for (int kc = 0; kc < T::NKC; ++kc) {
+      if constexpr (!LAST) mma_chunk<DT>(sn, kf.x[kc], qf[kc]);
+      if (kc >= VS && kc < VS + CT) v_read(0, kc - VS, vf[0][kc - VS]);     // (into registers kf has left)
+#pragma unroll
+      for (int e = kc * EPS; e < (kc + 1) * EPS; e += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[e], a.scale_log2, nm));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[e + 1], a.scale_log2, nm));
+        psum += p0;
+        psum += p1;
+        pw[e >> 1] = pack_pair<DT>(p0, p1);
+      }
+    }
+    l += psum;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) v_read(1, ct, vf[1][ct]);
+    u32x4 pb[2];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) { pb[s].x = pw[4 * s]; pb[s].y = pw[4 * s + 1]; pb[s].z = pw[4 * s + 2]; pb[s].w = pw[4 * s + 3]; }
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) mma_chunk<DT>(oacc[ct], vf[s][ct], pb[s]);
+    if constexpr (!LAST) tmax = half_max(sn);        // (beside the second product, which leaves the vector units idle)
+  };
+  // Tile t's barrier: K(t + 1) and V(t) are complete in LDS, and nobody still reads K(t) or V(t - 1), whose buffers are filled next.
+  auto top = [&](int t) {
+    wait_all_loads();
+    __syncthreads();
+    if (t + 1 < ntiles) v_issue(t + 1);
+    if (t + 2 < ntiles) k_issue(t + 2);
+  };
+  int turn = TILE_B;
+  auto next_buffers = [&]() {                        // tile t + 1: V from the other buffer, K (of t + 2) too
+    kaddr -= turn;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) vaddr[ct] += turn;
+    turn = -turn;
+  };
+  int t = 0;
+  for (; t + 2 < nt; t += 2) {
+    top(t);
+    step(std::false_type{}, s0, s1);
+    next_buffers();
+    top(t + 1);
+    step(std::false_type{}, s1, s0);
+    next_buffers();
+  }
+  if (t + 1 < nt) {
+    top(t++);
+    step(std::false_type{}, s0, s1);
+    next_buffers();
+    s0 = s1;
+  }
+  if (nt > 0) {
+    top(t++);
+    step(std::true_type{}, s0, s1);
+  }
+  for (; t < ntiles; ++t) top(t);                    // the other waves' tiles: their transfers and barriers
+
+  // ---- join the waves of a row: all outputs to LDS, each wave finishes an equal part of the channels ----
+  // (a wave without keys has m = -inf, l = 0 and zeros; the first wave has key 0)
+  constexpr int PART = CT * 4 / KS;                  // groups of four channels of a lane
+  float4* stage = reinterpret_cast<float4*>(tiles);
+  const float l_wave = l + __shfl_xor(l, 32);
+  __syncthreads();                                   // (every wave is done with its tiles)
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4)
+      stage[((w * CT + ct) * 4 + v4) * 64 + lane] = make_float4(oacc[ct][4 * v4], oacc[ct][4 * v4 + 1], oacc[ct][4 * v4 + 2], oacc[ct][4 * v4 + 3]);
+  sum[w][0][lane] = m;
+  sum[w][1][lane] = l_wave;
+  __syncthreads();
+  const int w0 = w - kg;                             // the row's waves: w0 .. w0 + KS - 1
+  float M = -INFINITY, l_tot = 0.f, f[KS];
+#pragma unroll
+  for (int v = 0; v < KS; ++v) { f[v] = sum[w0 + v][0][lane]; M = fmaxf(M, f[v]); }
+#pragma unroll
+  for (int v = 0; v < KS; ++v) {
+    f[v] = f[v] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(f[v] - M);
+    l_tot = fmaf(sum[w0 + v][1][lane], f[v], l_tot);
+  }
+  if (qpos < a.L) {
+    const float inv = 1.f / l_tot;
+    uint8_t* orow = reinterpret_cast<uint8_t*>(a.o) + ((int64_t)b * a.o_sB + (int64_t)hq * a.o_sH + (int64_t)qpos * a.o_sL) * 2;
+#pragma unroll
+    for (int u = 0; u < PART; ++u) {
+      const int part = kg * PART + u;                // group part % 4 of channel tile part / 4
+      float4 o = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+      for (int v = 0; v < KS; ++v) {
+        const float4 p = stage[((w0 + v) * CT * 4 + part) * 64 + lane];
+        o.x = fmaf(p.x, f[v], o.x); o.y = fmaf(p.y, f[v], o.y); o.z = fmaf(p.z, f[v], o.z); o.w = fmaf(p.w, f[v], o.w);
+      }
+      const int c = 32 * (part >> 2) + 8 * (part & 3) + 4 * kh;                // (acc_row: four consecutive channels)
+      *reinterpret_cast<uint2*>(orow + c * 2) = make_uint2(pack_pair<DT>(o.x * inv, o.y * inv), pack_pair<DT>(o.z * inv, o.w * inv));
+    }
+  }
+  const float lse = (M + log2f(l_tot)) * kLn2;
+  const int64_t head = (int64_t)b * a.Hq + hq;
+  if (a.lse && kg == 0 && kh == 0 && qpos < a.L) a.lse[head * a.L + qpos] = lse;
+  if (a.probe_pos) {
+    if (kg == 0 && kh == 0) slse[wq0 - q0 + r] = lse;
+    __syncthreads();
+    probe_normalisers<ROWS, 64 * NW>(a, head, q0, slse);
+  }
+}
+
 // lse_probe[b, h, p] = lse[b, h, probe_pos[p]]
 __global__ void k_gather_lse(const float* __restrict__ lse, const int32_t* __restrict__ probe_pos, float* __restrict__ out,
                              int64_t heads, int L, int P) {
@@ -700,6 +977,30 @@ static int head_group(const PrefillArgs& a, int nqb, int slots) {
   const int hpx = (a.B * a.Hq) >> 3, least = a.G * ceil_div(2 * slots, nqb * a.G);
   const int groups = hpx / least;
   return groups > 1 ? a.G * ceil_div(hpx, groups * a.G) : hpx > 0 ? hpx : 1;
+}
+
+// Waves that share a row's keys in a 16-bit call: 1, 2 or 4, by what each way costs in us: a workgroup's start, then the steps of the
+// longest row block or a SIMD's share of all steps, and what further workgroups a CU add.  Fitted to 400 calls of 1 to 640
+// heads and 64 to 9000 rows, timed all three ways (rms 4 to 8 %; calls below 4000 heads x row blocks of 32); one wave unless another way is 8 % cheaper by
+// that: all 400 are within 2 % of one wave or faster, 1.18 times in the geometric mean (1.19 with the best way each).
+static int key_split(int64_t heads, int64_t L, int D) {
+  struct Way { double start, step, share, more; int split, places; };
+  const Way ways[2][3] = {{{3.45, 0.40, 0.356, 3.27, 1, 1}, {3.90, 0.455, 0.362, 1.52, 2, 1}, {4.06, 0.525, 0.451, 1.58, 4, 1}},
+                          {{4.98, 0.58, 0.560, 5.90, 1, 1}, {4.80, 0.755, 0.638, 3.13, 2, 1}, {5.16, 0.833, 1.100, 3.70, 4, 0}}};
+  const int64_t blocks = ceil_div64(L, 32);
+  const double all = (double)heads * (double)blocks * (double)(blocks + 1) / 2048.0;     // steps of a SIMD
+  int best = 1;
+  double least = 0.0;
+  for (const Way& w : ways[D == 128]) {
+    const int64_t n = heads * ceil_div64(blocks, 4 / w.split);
+    // (one workgroup a CU: whole rounds; two: about as they come)
+    const double further = w.places ? (double)n / 256.0 - 1.0 : (double)(ceil_div64(n, 256) - 1);
+    const double chain = w.step * (double)ceil_div64(blocks, w.split), shared = w.share * all;
+    const double t = w.start + (chain > shared ? chain : shared) + (further > 0.0 ? w.more * further : 0.0);
+    if (w.split == 1) least = 0.92 * t;
+    else if (t < least) { least = t; best = w.split; }
+  }
+  return best;
 }
 
 template <int DT, int D>
@@ -743,7 +1044,10 @@ static int launch_prefill(PrefillArgs& a, hipStream_t st) {
         return ZC_OK;
       }
     }
-    hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), blocks(128, 64, 256), dim3(256), 0, st, a);
+    const int split = key_split(heads, a.L, D);
+    if (split == 4) hipLaunchKernelGGL((k_prefill_attention16_keys<DT, D, 4>), blocks(32, D == 128 ? 32 : 64, 256), dim3(256), 0, st, a);
+    else if (split == 2) hipLaunchKernelGGL((k_prefill_attention16_keys<DT, D, 2>), blocks(64, 64, 256), dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_prefill_attention16<DT, D, 4>), blocks(128, 64, 256), dim3(256), 0, st, a);
   }
   ZC_LAUNCH_CHECK();
   return ZC_OK;

@@ -171,3 +171,39 @@ def test_prefill_long_rows(dtype):
         # each weight is rounded once to the type (unit u), and so is the result: both are at most u / 2 of max |V|
         assert float((out[0, h, rows].double() - want).abs().max()) <= u * vmax + 1e-5 * vmax
         assert float((lse[0, h, rows].double() - want_lse).abs().max()) <= 1e-4
+
+
+# Waves that share a row's keys, two and four of them: less than a block of 32 keys, a block and one more, a wave without
+# keys, tiles of 64 and of 128 keys whole and one more, rows past the end of a workgroup's second block, several tiles, token-major
+# tensors, more workgroups than places, key blocks in which every logit is -inf (not the first 32, which every row sees of)
+SPLIT = [(1, 3, 1, 64, 31), (2, 4, 4, 64, 33), (1, 8, 2, 128, 64), (3, 4, 1, 128, 65), (1, 5, 5, 64, 97), (1, 8, 8, 64, 128), (2, 8, 4, 128, 129),
+         (1, 8, 2, 64, 257), (1, 16, 4, 64, 700), (1, 2, 1, 128, 1500), (4, 8, 2, 128, 301), (2, 24, 8, 128, 481), (1, 32, 8, 128, 840),
+         (2, 16, 16, 64, 1201), (1, 8, 8, 64, 3003)]
+
+
+@pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
+@pytest.mark.parametrize("case", SPLIT)
+def test_rows_whose_keys_waves_share(case, dtype):
+    B, Hq, Hkv, d, L = case
+    g = torch.Generator(device=DEV).manual_seed(L)
+    Q, K, V = (torch.randn(B, L, h, d, generator=g, device=DEV).to(dtype).transpose(1, 2) for h in (Hq, Hkv, Hkv))
+    Q = Q.clone(memory_format=torch.preserve_format)
+    Q[..., 1] = 1.0
+    if L > 300:
+        K[:, :, 64:96, 1] = K[:, :, 160:224, 1] = -float("inf")
+    pos = torch.randint(0, L, (min(L, 40),), generator=g, device=DEV).sort().values.int()
+    out, lse, lse_p = zb.zc_prefill_attention(Q, K, V, probe_pos=pos)
+    assert torch.equal(lse_p, lse[:, :, pos.long()])
+    # a weight and the result are rounded to the type (8 and 11 significant bits: by 2^-8 and 2^-11 of their size; weights in fp16
+    # from 2^-14 on down by 2^-25), a logit, of up to 2^6, is an fp32 sum of 128 products: 2^-18 at most
+    u, low = (2.0 ** -8, 0.0) if dtype == torch.bfloat16 else (2.0 ** -11, 2.0 ** -25)
+    hidden = torch.ones(L, L, dtype=torch.bool, device=DEV).triu(1)
+    for b in range(B):
+        for h in range(Hq):
+            k, v = K[b, h * Hkv // Hq].double(), V[b, h * Hkv // Hq].double()
+            x = (Q[b, h].double() @ k.T / d ** 0.5).masked_fill(hidden, -float("inf"))
+            p = torch.softmax(x, -1)
+            want, size = p @ v, p @ v.abs()
+            bound = (1.01 * u + 2.0 ** -17) * (size + want.abs()) + low * v.abs().sum(0)
+            assert bool(((out[b, h].double() - want).abs() <= bound).all()), (b, h)
+            assert (lse[b, h].double() - torch.logsumexp(x, -1)).abs().max().item() <= 1e-4
