@@ -46,7 +46,7 @@ struct ProbsArgs {
   const float* lse;         // [B, Hq] natural log
   float* probs;             // [B, Hq, N]
   int N;
-  int tpw;                  // tiles per wave
+  int tpw;                  // units (tail: tiles) per wave
   int n_segs;
   ProbsSeg seg[kProbSegs];
 };
@@ -76,11 +76,13 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 // largest element to [1, 2): 22 bits, whatever the scale of the query.  A lane's quarter row
 // (channels kg D / 4 ...) is contiguous in the ROW layout and goes from memory straight to its
 // registers.  The tail's few tokens take v_mfma_f32_16x16x4_f32 instead (no rounding of K).
-// Measured, us per call: on the vector ALUs with q' in LDS / with fp32 matrix instructions for
-// the packed tokens too / now:
-//   4096 tokens, 8 KV heads of 4 query heads      13.6 /   8.5 /  6.8
-//   the same, batch 8                             47.9 /  33.0 / 16.6
-//   2000 tokens, 40 KV heads of 1, batch 16      103.3 / 124.1 / 57.3
+// Tiles go two at a time: what a tile's 16 slots take after the products (the logit, its exponential, the store) only the
+// lanes of the value columns need, so a second tile's slots take the residual columns' lanes there, and positions and
+// parameters are requested once for both.  Measured, us per call: on the vector ALUs with q' in LDS / with fp32 matrix
+// instructions for the packed tokens too / a tile at a time / now:
+//   4096 tokens, 8 KV heads of 4 query heads      13.6 /   8.5 /  6.3 /  5.9
+//   8000 tokens, the same, batch 8                   - /     - / 23.7 / 18.9
+//   2000 tokens, 40 KV heads of 1, batch 16      103.3 / 124.1 / 50.2 / 36.3
 constexpr float kProbLo = 2048.f;
 
 // Codes of a quarter row (NK = D / 4 channels) as fp16 operand registers, two codes each: register
@@ -107,54 +109,71 @@ __device__ constexpr int channel_of(int i, int half) {
   return i / (E / 2) * E + i % (E / 2) + half * (E / 2);
 }
 
-template <int DT, int D, int BITS>
-__device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chunk, int sub, int begin, int len, int tile0, int ntiles) {
+// s x in fp16, rounded once: multiplication and conversion are one instruction (v_fma_mixlo_f16,
+// from the contraction; the empty assembly keeps two of them from being combined into products
+// in fp32 and a packed conversion).  Rounded to fp32 in between, a product that lies next to an
+// fp16 midpoint lands on it, and where cache rows are de-quantized there are such: s is R / (2^k - 1) for a 16-bit number R, so
+// some levels are short fractions of R.  A channel's extreme that moves by one unit in this
+// way can move the zero point it is compressed with next.
+__device__ inline uint16_t mul_to_half(float s, float x) {
+#pragma clang fp contract(fast)
+  uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)(s * x));
+  asm("" : "+v"(h));
+  return h;
+}
+
+// Slots of a segment, TILES tiles at a time; of two, the second one's results are in the odd lanes of a column pair, which the first
+// one leaves idle once value and residual are added up.
+template <int DT, int D, int BITS, bool TOK, int TILES>
+__device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chunk, int sub, int begin, int len, int unit0, int nunits) {
   constexpr int NK = D / 4, KS = D / 32;              // channels per lane and tile; matrix instructions per tile
-  constexpr int NW = NK * BITS / 32, ROWB = D * BITS / 8;
+  constexpr int NW = NK * BITS / 32, ROWB = D * BITS / 8, UNIT = TILES * kProbTile;
   const int lane = threadIdx.x & 63, n = lane & 15, kg = lane >> 4;
   const int g = n >> 1, part = n & 1;                 // head and part (value, residual) of this lane's column
   const bool nvalid = g < a.G;
   const int64_t cap = sub ? a.cap[1] : a.cap[0];
-  const uint8_t* kc = (sub ? a.kc[1] : a.kc[0]) + (((int64_t)b * a.Hkv + hk) * cap + begin) * ROWB + kg * (ROWB / 4);
-  const int64_t tok0 = (int64_t)b * cap + begin + 4 * kg;
+  const uint8_t* kc = (sub ? a.kc[1] : a.kc[0]) + (((int64_t)b * a.Hkv + hk) * cap + begin + n) * ROWB + kg * (ROWB / 4);
+  const int slot0 = (TILES == 2 ? kProbTile * part : 0) + 4 * kg;        // of a unit: the four slots whose results this lane has
+  const int64_t tok0 = (int64_t)b * cap + begin + slot0;
   const int32_t* pos_src = (sub ? a.pos[1] : a.pos[0]) + tok0;
   const float *ts_src = nullptr, *tz_src = nullptr;
-  if (a.k_tok) { ts_src = (sub ? a.k_ts[1] : a.k_ts[0]) + tok0; tz_src = (sub ? a.k_tz[1] : a.k_tz[0]) + tok0; }
+  if constexpr (TOK) { ts_src = (sub ? a.k_ts[1] : a.k_ts[0]) + tok0; tz_src = (sub ? a.k_tz[1] : a.k_tz[0]) + tok0; }
 
-  // a tile's inputs of this lane: the quarter row of slot n, positions and token parameters of slots 4 kg ..
+  // a unit's inputs of this lane: the quarter rows of slots n and 16 + n, positions and token parameters of its four slots
   // (slots past the segment's end lie inside the same 64-slot unit of the arena)
-  struct In { uint32_t w[NW]; int4 pos; float4 ts, tz; };
-  auto load = [&](int tile, In& in) {
-    const uint8_t* row = kc + (int64_t)(tile * kProbTile + n) * ROWB;
-    if constexpr (NW >= 4) {
+  struct In { uint32_t w[TILES][NW]; int4 pos; float4 ts, tz; };
+  auto load = [&](int unit, In& in) {
 #pragma unroll
-      for (int i = 0; i < NW; i += 4) {
-        const uint4 t = *reinterpret_cast<const uint4*>(row + 4 * i);
-        in.w[i] = t.x; in.w[i + 1] = t.y; in.w[i + 2] = t.z; in.w[i + 3] = t.w;
+    for (int t = 0; t < TILES; ++t) {
+      const uint8_t* row = kc + ((int64_t)unit * UNIT + t * kProbTile) * ROWB;
+      if constexpr (NW >= 4) {
+#pragma unroll
+        for (int i = 0; i < NW; i += 4) {
+          const uint4 x = *reinterpret_cast<const uint4*>(row + 4 * i);
+          in.w[t][i] = x.x; in.w[t][i + 1] = x.y; in.w[t][i + 2] = x.z; in.w[t][i + 3] = x.w;
+        }
+      } else if constexpr (NW == 2) {
+        const uint2 x = *reinterpret_cast<const uint2*>(row);
+        in.w[t][0] = x.x; in.w[t][1] = x.y;
+      } else {
+        in.w[t][0] = *reinterpret_cast<const uint32_t*>(row);
       }
-    } else if constexpr (NW == 2) {
-      const uint2 t = *reinterpret_cast<const uint2*>(row);
-      in.w[0] = t.x; in.w[1] = t.y;
-    } else {
-      in.w[0] = *reinterpret_cast<const uint32_t*>(row);
     }
-    in.pos = load4(pos_src + tile * kProbTile);
-    in.ts = make_float4(1.f, 1.f, 1.f, 1.f);
-    in.tz = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (a.k_tok) {
-      in.ts = load4(ts_src + tile * kProbTile);
-      in.tz = load4(tz_src + tile * kProbTile);
+    in.pos = load4(pos_src + unit * UNIT);
+    if constexpr (TOK) {
+      in.ts = load4(ts_src + unit * UNIT);
+      in.tz = load4(tz_src + unit * UNIT);
     }
   };
   In in;
-  load(tile0, in);
+  load(unit0, in);
 
   // q' = q * channel scale * sm_scale * log2(e) of head g (unused columns: 0), its two channel sums
   const int64_t hq = (int64_t)b * a.Hq + hk * a.G + (nvalid ? g : 0);
   const float lse2 = a.lse[hq] * kLog2e;
   u4 qB[KS];
   float aq = 0.f, bq = 0.f, unscale;
-  const float tok_bias = a.k_tok ? code_bias<BITS>() : 0.f, chan_bias = code_bias<BITS>() - tok_bias;   // off the zero points in use, which are integers
+  constexpr float tok_bias = TOK ? code_bias<BITS>() : 0.f, chan_bias = code_bias<BITS>() - tok_bias;   // off the zero points in use, which are integers
   {
     const int64_t qoff = (int64_t)b * a.q_sB + (int64_t)(hk * a.G + (nvalid ? g : 0)) * a.q_sH + kg * NK;
     const int64_t coff = ((int64_t)(chunk * 2 + sub) * a.B + b) * (a.Hkv * D) + hk * D + kg * NK;
@@ -188,43 +207,56 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
       uint32_t r[4];
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        uint32_t bits2 = 0;
+        uint32_t value = 0, rest = 0;
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-          const float x = qp[channel_of<BITS>(4 * ks + i, half)] * up;
-          const _Float16 hi = (_Float16)x;
-          const _Float16 y = part ? (_Float16)((x - (float)hi) * kProbLo) : hi;
-          bits2 |= (uint32_t)__builtin_bit_cast(uint16_t, y) << (16 * half);
+        for (int half = 0; half < 2; ++half) {        // (products with powers of two: each rounded once, to fp16)
+          const float x = qp[channel_of<BITS>(4 * ks + i, half)];
+          const uint16_t hi = mul_to_half(up, x);
+          const float left = fmaf(x, up, -(float)__builtin_bit_cast(_Float16, hi));
+          value |= (uint32_t)hi << (16 * half);
+          rest |= (uint32_t)mul_to_half(kProbLo, left) << (16 * half);
         }
-        r[i] = bits2;
+        r[i] = part ? rest : value;
       }
       qB[ks] = u4{r[0], r[1], r[2], r[3]};
     }
   }
   float* out = a.probs + hq * a.N;
-  const bool store_col = nvalid && part == 0;
+  const bool store = nvalid && (TILES == 2 || part == 0);
 
   for (int i = 0; i < a.tpw; ++i) {
-    const int tile = tile0 + 4 * i;
-    if (tile >= ntiles) break;
-    uint32_t r[NK / 2];
-    codes_to_half<BITS, NK>(in.w, r);
+    const int unit = unit0 + 4 * i;
+    if (unit >= nunits) break;
+    uint32_t r[TILES][NK / 2];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) codes_to_half<BITS, NK>(in.w[t], r[t]);
     const int pos[4] = {in.pos.x, in.pos.y, in.pos.z, in.pos.w};
-    const float ts[4] = {in.ts.x, in.ts.y, in.ts.z, in.ts.w}, tz[4] = {in.tz.x, in.tz.y, in.tz.z, in.tz.w};
-    if (i + 1 < a.tpw && tile + 4 < ntiles) load(tile + 4, in);      // the next tile's inputs are in flight meanwhile
-    f4 acc = f4{0.f, 0.f, 0.f, 0.f};
+    float ts[4], tz[4];
+    if constexpr (TOK) {
+      ts[0] = in.ts.x; ts[1] = in.ts.y; ts[2] = in.ts.z; ts[3] = in.ts.w;
+      tz[0] = in.tz.x; tz[1] = in.tz.y; tz[2] = in.tz.z; tz[3] = in.tz.w;
+    }
+    load(min(unit + 4, nunits - 1), in);              // the next unit's inputs are in flight meanwhile (no branch: it would copy them)
+    f4 acc[TILES];
+#pragma unroll
+    for (int t = 0; t < TILES; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int ks = 0; ks < KS; ++ks)
-      acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, u4{r[4 * ks], r[4 * ks + 1], r[4 * ks + 2], r[4 * ks + 3]}),
-                                                   __builtin_bit_cast(h8, qB[ks]), acc, 0, 0, 0);
-    const float own[4] = {acc.x, acc.y, acc.z, acc.w};
+#pragma unroll
+      for (int t = 0; t < TILES; ++t)
+        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, u4{r[t][4 * ks], r[t][4 * ks + 1], r[t][4 * ks + 2], r[t][4 * ks + 3]}),
+                                                        __builtin_bit_cast(h8, qB[ks]), acc[t], 0, 0, 0);
+    const float first[4] = {acc[0].x, acc[0].y, acc[0].z, acc[0].w}, second[4] = {acc[TILES - 1].x, acc[TILES - 1].y, acc[TILES - 1].z, acc[TILES - 1].w};
+    const auto neighbour = [](float x) { return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), 0xB1, 0xF, 0xF, true)); };
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-      const float lo = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(own[v]), 0xB1, 0xF, 0xF, true));   // the neighbour lane's
-      const float dot = fmaf(lo, 1.f / kProbLo, own[v]) * unscale;
-      const float logit2 = ts[v] * (dot - (tz[v] - tok_bias) * aq - bq);
+      const float near_first = neighbour(first[v]), near_second = neighbour(second[v]);      // (by all lanes, not under the selects)
+      const bool odd = TILES == 2 && part;
+      const float value = odd ? near_second : first[v], rest = odd ? second[v] : near_first;
+      const float dot = fmaf(rest, 1.f / kProbLo, value) * unscale;
+      const float logit2 = TOK ? ts[v] * (dot - (tz[v] - tok_bias) * aq - bq) : dot - bq;
       const float p = exp2f(logit2 - lse2);
-      if (store_col && tile * kProbTile + 4 * kg + v < len && pos[v] >= 0 && pos[v] < a.N) out[pos[v]] = p;
+      if (store && unit * UNIT + slot0 + v < len && pos[v] >= 0 && pos[v] < a.N) out[pos[v]] = p;
     }
   }
 }
@@ -261,8 +293,8 @@ __device__ inline void probs_tail(const ProbsArgs& a, int b, int hk, int len, in
   }
 }
 
-// grid (workgroups of all segments, Hkv, B); a wave takes a.tpw tiles of its segment
-template <int DT, int D>
+// grid (workgroups of all segments, Hkv, B); a wave takes a.tpw units of its segment.  TOK: keys with token parameters.
+template <int DT, int D, bool TOK, int TILES>
 __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
   const int hk = blockIdx.y, b = blockIdx.z;
   const int wave = threadIdx.x >> 6;
@@ -273,13 +305,13 @@ __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
   const int si = __builtin_popcountll(__builtin_amdgcn_ballot_w64(before)) - 1;
   const int begin = a.seg[si].begin, len = a.seg[si].len, sub = a.seg[si].sub;
   const bool is_tail = sub == kTailSub;
-  const int tile0 = ((int)blockIdx.x - a.seg[si].first_block) * 4 * a.tpw + wave, ntiles = ceil_div(len, kProbTile);
+  const int first = ((int)blockIdx.x - a.seg[si].first_block) * 4 * a.tpw + wave, count = ceil_div(len, is_tail ? kProbTile : TILES * kProbTile);
   const int bits = is_tail ? 0 : sub ? a.bits[1] : a.bits[0];
-  if (tile0 >= ntiles) return;
-  if (is_tail) probs_tail<DT, D>(a, b, hk, len, tile0, ntiles);
-  else if (bits == 4) probs_segment<DT, D, 4>(a, b, hk, a.seg[si].chunk, sub, begin, len, tile0, ntiles);
-  else if (bits == 2) probs_segment<DT, D, 2>(a, b, hk, a.seg[si].chunk, sub, begin, len, tile0, ntiles);
-  else probs_segment<DT, D, 8>(a, b, hk, a.seg[si].chunk, sub, begin, len, tile0, ntiles);
+  if (first >= count) return;
+  if (is_tail) probs_tail<DT, D>(a, b, hk, len, first, count);
+  else if (bits == 4) probs_segment<DT, D, 4, TOK, TILES>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
+  else if (bits == 2) probs_segment<DT, D, 2, TOK, TILES>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
+  else probs_segment<DT, D, 8, TOK, TILES>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
 }
 
 // scores[b, i] = mean_h ( sum_{j : row_len[j] > i} rows[j, b, h, i] ) / #{j : row_len[j] > i}
@@ -417,19 +449,6 @@ struct DequantArgs {
 // (2^19) 7.25 and 7.65, 32 of 200 of 8 heads 9.5 and 9.9, 4 of 4096 of 4 heads (2^20) 10.9 and 11.0, one of 5000 of
 // 17 heads (1.3 x 2^20) 12.9 and 12.7, of 8000 of 16 heads (2^21) 16.7 and 16.2).
 static constexpr int64_t four_slots_from(int dtype) { return dtype == ZC_F32 ? 5 << 18 : 1 << 19; }
-
-// s x in fp16, rounded once: multiplication and conversion are one instruction (v_fma_mixlo_f16,
-// from the contraction; the empty assembly keeps two of them from being combined into products
-// in fp32 and a packed conversion).  Rounded to fp32 in between, a product that lies next to an
-// fp16 midpoint lands on it, and there are such: s is R / (2^k - 1) for a 16-bit number R, so
-// some levels are short fractions of R.  A channel's extreme that moves by one unit in this
-// way can move the zero point it is compressed with next.
-__device__ inline uint16_t mul_to_half(float s, float x) {
-#pragma clang fp contract(fast)
-  uint16_t h = __builtin_bit_cast(uint16_t, (_Float16)(s * x));
-  asm("" : "+v"(h));
-  return h;
-}
 
 // Eight consecutive elements rounded to DT and stored (16-byte aligned).
 template <int DT>
@@ -618,11 +637,16 @@ extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const z
   a.tail_pos0 = (int)tail_pos0;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse = lse; a.probs = probs_out; a.N = (int)N;
-  // one tile a wave while the launch is below two workgroups per CU (latency), up to eight when
-  // the chip is full anyway and a wave's start (the query operand) would weigh as much as its tile
+  int unit = kProbTile;
+  // A tile a wave while every SIMD has a wave at most (latency); else two at a time, one unit a wave while the launch is below two
+  // waves a SIMD, up to six when the chip is full anyway and a wave's start (the query operand) would weigh as much as its
+  // units.  us by one and by two tiles at a time: 784 tiles (700 tokens of 16 KV heads of 128 channels) 4.3 and 4.5, 1100 (1400 of 12 heads of
+  // 64) 4.2 and 3.8, 2100 (4096 of 8) 6.5 and 5.9; 16 x 40 heads of 2000 tokens by up to 2, 4, 6 and 8 units a wave 46.0, 38.9, 36.2 and 44.9.
   {
-    const int64_t t = tiles * a.Hkv * a.B / 2048;
-    a.tpw = (int)(t < 1 ? 1 : t > 8 ? 8 : t);
+    const int64_t all = tiles * a.Hkv * a.B;
+    if (all > 960) unit = 2 * kProbTile;
+    const int64_t t = all / (unit / kProbTile) / 2048;
+    a.tpw = (int)(t < 1 ? 1 : t > 6 ? 6 : t);
   }
   hipStream_t st = (hipStream_t)stream;
   int64_t blocks = 0;
@@ -630,15 +654,20 @@ extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const z
   auto flush = [&]() -> int {
     if (a.n_segs == 0) return ZC_OK;
     const dim3 grid((unsigned)blocks, (unsigned)a.Hkv, (unsigned)a.B);
-#define ZC_PR(DT)                                                                              \
-  do {                                                                                         \
-    if (q->D == 128) hipLaunchKernelGGL((k_decode_probs<DT, 128>), grid, dim3(256), 0, st, a); \
-    else hipLaunchKernelGGL((k_decode_probs<DT, 64>), grid, dim3(256), 0, st, a);              \
+    const auto launch = [&](auto one, auto two) { hipLaunchKernelGGL(unit == kProbTile ? one : two, grid, dim3(256), 0, st, a); };
+#define ZC_PRD(DT, D, TOK) launch(k_decode_probs<DT, D, TOK, 1>, k_decode_probs<DT, D, TOK, 2>)
+#define ZC_PR(DT)                                      \
+  do {                                                 \
+    if (a.k_tok && q->D == 128) ZC_PRD(DT, 128, true); \
+    else if (a.k_tok) ZC_PRD(DT, 64, true);            \
+    else if (q->D == 128) ZC_PRD(DT, 128, false);      \
+    else ZC_PRD(DT, 64, false);                        \
   } while (0)
     if (q->dtype == ZC_F32) ZC_PR(ZC_F32);
     else if (q->dtype == ZC_F16) ZC_PR(ZC_F16);
     else ZC_PR(ZC_BF16);
 #undef ZC_PR
+#undef ZC_PRD
     ZC_LAUNCH_CHECK();
     a.n_segs = 0;
     blocks = 0;
@@ -651,7 +680,7 @@ extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const z
       if (rcf) return rcf;
     }
     a.seg[a.n_segs++] = {begin, (int)len, (int)blocks, chunk, sub};
-    blocks += ceil_div64(ceil_div64(len, kProbTile), 4 * a.tpw);
+    blocks += ceil_div64(ceil_div64(len, sub == kTailSub ? kProbTile : unit), 4 * a.tpw);
     return ZC_OK;
   };
   for (int ci = 0; ci < Kp->n_chunks; ++ci)

@@ -381,6 +381,39 @@ def test_decode_probs_tiles_and_code_widths(B, Hq, Hkv, d, dtype, bits, L, T):
         assert bool((row[:, :, n0 + T:] == -1.0).all())
 
 
+# Two tiles at a time (more than 960 of them): segments that end inside the first and the second tile of a pair, at either's
+# end and one after, head widths, groups and code widths, one and several pairs a wave
+@pytest.mark.parametrize("B,Hq,Hkv,d,dtype,bits,sizes,T", [
+    (8, 16, 8, 64, torch.bfloat16, (4, 8), [(40, 160), (17, 31), (15, 33)], 5), (8, 64, 8, 128, torch.float16, (8, 4), [(48, 97), (16, 64), (65, 32)], 17),
+    (5, 9, 9, 64, torch.float32, (2, 4), [(511, 1024)], 32), (16, 24, 12, 64, torch.float16, (4, 4), [(1600, 3201), (20, 80)], 0)])
+def test_decode_probs_pairs_of_tiles(B, Hq, Hkv, d, dtype, bits, sizes, T):
+    g = torch.Generator().manual_seed(Hq)
+    lib = zb.load()
+    n_packed = sum(k + n for k, n in sizes)
+    assert B * Hkv * sum(-(-k // 16) + -(-n // 16) for k, n in sizes) > 960
+    K = torch.randn(B, Hkv, n_packed + T, d, generator=g).to(dtype).to(DEV)
+    q = torch.randn(B, Hq, d, generator=g).to(dtype).to(DEV)
+    for scheme in ("channel", "token"):
+        p = zb.PackedTensor(B, Hkv, d, lib.zc_arena_slots(sum(k for k, _ in sizes), 3), lib.zc_arena_slots(sum(n for _, n in sizes), 3), *bits, scheme,
+                            zb.ZC_LAYOUT_ROW, max_chunks=3, device=DEV)
+        n0 = 0
+        for k, n in sizes:
+            sal, reg = zb.zc_select_salient(torch.rand(B, k + n, generator=g).to(DEV), k)
+            zb.zc_quantize_pack(K[:, :, n0:n0 + k + n], sal, reg, p, pos_offset=n0)
+            n0 += k + n
+        Kh = K.float()
+        zb.zc_dequantize_cache(p, Kh)
+        logits = torch.cat([torch.matmul(q.double().view(B, Hkv, Hq // Hkv, d), k.double().transpose(-1, -2).contiguous()).view(B, Hq, -1)
+                            for k in Kh.split(512, 2)], -1) / d ** 0.5
+        lse = torch.logsumexp(logits, -1)
+        row = torch.full((B, Hq, n0 + T + 2), -1.0, dtype=torch.float32, device=DEV)
+        zb.zc_decode_probs(q, p, K[:, :, n0:] if T else None, T, n0, lse.float(), row)
+        want = torch.exp(logits - lse[..., None])
+        # (the bound of test_decode_probs_tiles_and_code_widths; a chunk of fifteen tokens and more has no channel of a narrow range)
+        assert float(((row[:, :, :n0 + T].double() - want) / want).abs().max()) <= 300 * 2.0 ** -23
+        assert bool((row[:, :, n0 + T:] == -1.0).all())
+
+
 @pytest.mark.parametrize("dtype", [torch.float32, torch.float16, torch.bfloat16])
 @pytest.mark.parametrize("bits", [(8, 8), (8, 4)])
 def test_decode_probs_error_against_64_bits(bits, dtype):
