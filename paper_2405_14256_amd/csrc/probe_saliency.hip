@@ -123,13 +123,14 @@ struct RowPairs {
     float M = -INFINITY;
 #pragma unroll
     for (int sp = 0; sp < kMaxProbeParts; ++sp) {
-      if (sp >= max_parts) v[sp] = make_float2(-INFINITY, 0.f);
+      if (sp >= kProbeParts && sp >= max_parts) v[sp] = make_float2(-INFINITY, 0.f);
       M = fmaxf(M, v[sp].x);
     }
+    // (a range without a reference: 0 times 2^-inf)
+    const float base = M > -INFINITY ? M : 0.f;
     float Z = 0.f;
 #pragma unroll
-    for (int sp = 0; sp < kMaxProbeParts; ++sp)
-      Z += v[sp].x > -INFINITY ? v[sp].y * __builtin_amdgcn_exp2f(v[sp].x - M) : 0.f;
+    for (int sp = 0; sp < kMaxProbeParts; ++sp) Z = fmaf(v[sp].y, __builtin_amdgcn_exp2f(v[sp].x - base), Z);
     return M + log2f(Z);
   }
 };
@@ -255,14 +256,15 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
   int last[2];                                   // last column a lane's row sees, less the lane's first in a tile (< 0: none)
   {
     int row[2 * NI];
-    const int32_t* rows = a.probe_rows ? a.probe_rows : a.probe_pos;
+    const auto rs_row = __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(a.probe_rows ? a.probe_rows : a.probe_pos), 0, (uint32_t)a.P * 4u, kBufFlags);
+    const int i0 = w * T::RPI + lane / T::CPR;
 #pragma unroll
-    for (int jj = 0; jj < 2 * NI; ++jj) row[jj] = rows[min(rb0 + (w + 4 * jj) * T::RPI + lane / T::CPR, a.P - 1)];
+    for (int jj = 0; jj < 2 * NI; ++jj) row[jj] = (int)__builtin_amdgcn_raw_buffer_load_b32(rs_row, (rb0 + i0) * 4 + 16 * jj * T::RPI, 0, 0);
     const int my_pos = a.probe_pos[min(rb0 + (tid & (kLseRows - 1)), a.P - 1)];
 #pragma unroll
     for (int jj = 0; jj < 2 * NI; ++jj) {
-      const int i = (w + 4 * jj) * T::RPI + lane / T::CPR;
-      dma16<0>(ks_lds + (w + 4 * jj) * 1024, rs_q, i < nvalid ? (int)((uint32_t)row[jj] * q_rowb) + (((lane % T::CPR) ^ T::swz(i)) << 4) : kOutOfRange, 0);
+      const int off = opaque((int)((uint32_t)row[jj] * q_rowb) + (((lane % T::CPR) ^ T::swz(SAME ? i0 : i0 + 4 * jj * T::RPI)) << 4));
+      dma16<0>(ks_lds + (w + 4 * jj) * 1024, rs_q, i0 + 4 * jj * T::RPI < nvalid ? off : kOutOfRange, 0);
     }
     if (tid < kLseRows) spos[tid] = tid < nvalid ? my_pos : -1;
   }
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
     m[rb] = spos[i] < 0 ? 0.f : -INFINITY;
     last[rb] = spos[i] < 0 ? -1 : spos[i] - 4 * kh;
 #pragma unroll
-    for (int kc = 0; kc < T::NKC; ++kc) qf[rb][kc] = *reinterpret_cast<lds_u32x4*>(ks_lds + T::slot(i, 2 * kc + kh));
+    for (int kc = 0; kc < T::NKC; ++kc) qf[rb][kc] = *reinterpret_cast<lds_u32x4*>((ks_lds + T::slot(row0 + r, kh) ^ (kc << 5)) + rb * 32 * T::ROWB);
   }
   __syncthreads();
   if (t_begin < t_end) issue(t_begin, 0);
@@ -297,6 +299,8 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
     plast[rb] = base < nvalid && (two || rb == 0) ? pos_at(min(base + 31, nvalid - 1)) : -1;
   }
   const int pos_last = max(plast[0], plast[1]);
+  const bool both = plast[1] >= 0;
+  bool ready = false;                            // no row without a reference
   float z[2] = {0.f, 0.f};
   const uint32_t abase = ks_lds + T::slot(ch * 32 + r, kh);
 
@@ -309,10 +313,31 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
     if (t_end - t <= a.even1) priority_by_tiles(t_end - t);
     if (t * kLseCols > pos_last) continue;       // nothing of this tile is visible to the wave's rows
     v16f acc[2];
-    if (two) products<DT, 2>(acc, abase + cur * TILE_B, qf);
+    if (both) products<DT, 2>(acc, abase + cur * TILE_B, qf);
     else products<DT, 1>(acc, abase + cur * TILE_B, qf);
     __builtin_amdgcn_sched_barrier(0);           // (here and below: what follows would be moved up, into registers there are not)
     const int colb = t * kLseCols + ch * 32;     // this wave's 32 columns of the tile
+    // Every row has its reference and sees every column: nothing but the terms (what the general case asks of every block
+    // was 22 of a wave-tile's 151 vector instructions: all rows of 32 heads of 128 channels, 32768 tokens, 3276 probes,
+    // both sweeps 1271 -> 1216 us).
+    if (ready && colb + 31 <= pfirst[0]) {
+      float sum[2] = {0.f, 0.f};
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) {
+        if (rb == 1 && !both) break;
+        sum[rb] = __builtin_amdgcn_exp2f(fmaf(acc[rb][0], a.scale_log2, -m[rb]));
+#pragma unroll
+        for (int v = 1; v < 16; ++v) {
+          sum[rb] += __builtin_amdgcn_exp2f(fmaf(acc[rb][v], a.scale_log2, -m[rb]));
+          if (v % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+      if (__builtin_amdgcn_ballot_w64(!(sum[0] + sum[1] < 0x1p60f)) == 0) {
+        z[0] += sum[0];
+        z[1] += sum[1];
+        continue;
+      }
+    }
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb) {
       if (colb > plast[rb]) continue;            // none of them visible to this block's rows
@@ -361,6 +386,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
         set = true;
       }
     }
+    if (!ready) ready = __builtin_amdgcn_ballot_w64(m[0] == -INFINITY || (both && m[1] == -INFINITY)) == 0;
   }
   // merge the two half-waves, then the two column halves
   const int t1 = opaque(tid), r1 = t1 & 31;
@@ -477,10 +503,13 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   float tlse[NT];
   if (tid < 128) bins[tid] = 0;
   {
+    constexpr bool SAME = 4 * T::RPI / T::RP256 % T::SW == 0;      // (the swizzle repeats from one of a wave's transfers to the next)
+    const int i0 = w * T::RPI + lane / T::CPR;
+    int off = (int)((uint32_t)(col0 + i0) * k_rowb);
 #pragma unroll
     for (int jj = 0; jj < 2 * NI; ++jj) {
-      const int i = (w + 4 * jj) * T::RPI + lane / T::CPR, col = col0 + i;
-      dma16<0>(qs_lds + (w + 4 * jj) * 1024, rs_k, col < a.Lk ? (int)((uint32_t)col * k_rowb) + (((lane % T::CPR) ^ T::swz(i)) << 4) : kOutOfRange, 0);
+      dma16<0>(qs_lds + (w + 4 * jj) * 1024, rs_k, off + (((lane % T::CPR) ^ T::swz(SAME ? i0 : i0 + 4 * jj * T::RPI)) << 4), 0);
+      off += (int)(4 * T::RPI * k_rowb);
     }
     int n = 0;
     const auto count = [&](bool real, int pos) {
@@ -504,8 +533,10 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
       for (int u = 0; u < NT; ++u)
         if (u * 256 < a.P) {
           count(u * 256 + tid < a.P, tpos[u]);
-          if constexpr (join) tlse[u] = pairs[u].joined(a.max_parts);
-          else if (a.lse_in) tlse[u] *= kLog2e;  // an external log-sum-exp is in natural units
+          if constexpr (join) {                  // (but of probes that all lie in front of these columns)
+            if (__builtin_amdgcn_ballot_w64(u * 256 + tid < a.P && tpos[u] >= col0)) tlse[u] = pairs[u].joined(a.max_parts);
+          }
+          if (!join && a.lse_in) tlse[u] *= kLog2e;      // an external log-sum-exp is in natural units
         }
     } else {
       __syncthreads();
@@ -527,7 +558,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
 #pragma unroll
   for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-    for (int kc = 0; kc < T::NKC; ++kc) kf[cb][kc] = *reinterpret_cast<lds_u32x4*>(qs_lds + T::slot((cbp * 2 + cb) * 32 + r, 2 * kc + kh));
+    for (int kc = 0; kc < T::NKC; ++kc) kf[cb][kc] = *reinterpret_cast<lds_u32x4*>((qs_lds + T::slot(cbp * 64 + r, kh) ^ (kc << 5)) + cb * 32 * T::ROWB);
   const int pstart = __builtin_amdgcn_readfirstlane(before[0] + before[1] + before[2] + before[3]);
   float colsum[2] = {0.f, 0.f};
 

@@ -117,6 +117,27 @@ def test_scores_with_logits_of_minus_infinity(d, dtype, P):
     assert rel < 3e-5, rel                       # (the bound of the test above)
 
 
+# Columns 2^72 above all before them, in a tile that every row sees and in one that some rows see: the rows' references move
+# while only terms are summed.  Blocks of one, two and both halves of a wave's rows.
+@pytest.mark.parametrize("d,dtype,P", [(128, torch.bfloat16, 33), (64, torch.float16, 97), (128, torch.float32, 160), (128, torch.float16, 192)])
+def test_scores_whose_references_move(d, dtype, P):
+    B, Hq, Hkv, L = 1, 4, 2, 1500
+    g = torch.Generator(device=DEV).manual_seed(P)
+    pos = torch.cat([spread(800, 20) + 400, torch.arange(L - (P - 20), L)]).unique().to(DEV)
+    q = torch.randn(B, Hq, pos.numel(), d, generator=g, device=DEV)
+    q[..., 3] = 1.0
+    k = torch.randn(B, Hkv, L, d, generator=g, device=DEV)
+    k[..., 3] = 0.0
+    k[:, :, [333, 777], 3] = torch.tensor([50.0, 100.0], device=DEV) * d ** 0.5
+    q, k = q.to(dtype), k.to(dtype)
+    rows = torch.arange(pos.numel(), device=DEV)
+    got = zb.zc_probe_saliency(q, k, pos.int(), probe_rows=rows.int())
+    want = reference(q, k, rows, pos)
+    # (the bound of the first test: the terms of a logit sum up to less than 2^8)
+    rel = ((got.double() - want).abs() / want.clamp(min=1e-30)).max().item()
+    assert rel < 3e-5, rel
+
+
 # A row's reference is a maximum of scaled logits: columns a lane does not see stay out of it for a negative scale too.
 @pytest.mark.parametrize("case", [1, 2, 3, 4])
 def test_scores_of_a_negative_scale(case):
