@@ -924,27 +924,39 @@ __device__ inline void load4(const void* p, float (&v)[4]) {
 
 // Token e of a word group of values: its index in the subset.
 template <int BITS>
-__device__ inline int value_token(int unit, int e) {
+__device__ inline int value_token(int blk, int kg, int e) {       // (the word group's block, its group in it)
   constexpr int TB = 4 * (32 / BITS);
-  return (unit >> 2) * TB + 16 * tile_of_field_group(BITS, e >> 2) + 4 * (unit & 3) + (e & 3);
+  return blk * TB + 16 * tile_of_field_group(BITS, e >> 2) + 4 * kg + (e & 3);
 }
 
-// Ranges, token parameters, codes and positions of a word group of values (TGROUP layout, channel-separable tokenwise) whose rows x
-// are there, 4 channels a thread; tx: of the waves (nwaves) that share the row.  red: theirs.  All threads of the workgroup come here.
-template <int DT, int BITS>
-__device__ inline void finish_values(const QPArgs& a, int sub, int unit, int b, float (&x)[32 / BITS][kPackCpt], const float (&inv_c)[kPackCpt],
-                                     int tx, int wave, int nwaves, float (*red)[kPackThreads / 64][16]) {
+// Values (TGROUP layout, channel-separable tokenwise): one word group, a thread per 4 channels.  TEAM: of `threads` threads of a
+// workgroup from `first` on, red theirs, all of which come here; rows(x, inv_c) hands over the rows and the channels' parameters.
+struct OwnRows {};
+template <int DT, int BITS, typename ROWS = OwnRows>
+__device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, float (*red)[kPackThreads / 64][16], int first = 0, int threads = 0, const ROWS& rows = ROWS()) {
+  constexpr bool TEAM = !std::is_same<ROWS, OwnRows>::value;
   constexpr int E = 32 / BITS, TBAT = E < 8 ? E : 8, NBAT = E / TBAT, TB = 4 * E;
-  constexpr int FPG = 16 / BITS, NG = TBAT / FPG;
+  constexpr int FPG = 16 / BITS, NG = TBAT / FPG, ESZ = DT == ZC_F32 ? 4 : 2;
   constexpr float QMAX = (float)((1 << BITS) - 1);
   const int n = a.n[sub], blk = unit >> 2, kg = unit & 3;
   const int32_t* idx = a.idx[sub] + (int64_t)b * n;
-  const int lane = tx & 63;
-  const bool valid = kPackCpt * tx < a.W;
-  auto rel_of = [&](int e) { return value_token<BITS>(unit, e); };
+  const int tid = TEAM ? threadIdx.x - first : threadIdx.x, lane = tid & 63, wave = tid >> 6, nwaves = TEAM ? threads >> 6 : blockDim.x >> 6;
+  const bool valid = kPackCpt * tid < a.W;
+  const int w = valid ? kPackCpt * tid : 0, h = w / a.D, c = w - h * a.D;
+  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
+  auto rel_of = [&](int e) { return value_token<BITS>(blk, kg, e); };
+
+  float x[E][kPackCpt], inv_c[kPackCpt];
+  if constexpr (TEAM) {
+    rows(x, inv_c);
+  } else {
+#pragma unroll
+    for (int e = 0; e < E; ++e) load4<DT>(base + (int64_t)idx[min(rel_of(e), n - 1)] * a.sL * ESZ, x[e]);
+    load4<ZC_F32>(param_row(a, b, sub, 0) + w, inv_c);
+  }
   // bookkeeping of the group's tokens by lanes 0 .. E - 1 of the first wave
   const int my_rel = rel_of(lane < E ? lane : 0);
-  const bool mine = tx < E && my_rel < n;
+  const bool mine = tid < E && my_rel < n;
   const int64_t o0 = (int64_t)b * a.cap[sub] + a.begin[sub];
   if (mine && a.pos[sub]) (a.pos[sub] + o0)[my_rel] = (int32_t)(idx[my_rel] + a.pos_offset);
 
@@ -1005,28 +1017,13 @@ __device__ inline void finish_values(const QPArgs& a, int sub, int unit, int b, 
 #pragma unroll
       for (int i = 0; i < kPackCpt; ++i) words[i] |= (uint32_t)acc[i] << (BITS * (q * TBAT + g * FPG));
     }
-  int w1 = tx;                                       // (the channel again, not held in registers meanwhile)
+  int w1 = TEAM ? tid : threadIdx.x;                              // (the channel again, not held in registers meanwhile)
   asm volatile("" : "+v"(w1));
   w1 *= kPackCpt;
   const int h1 = w1 >> (a.D == 128 ? 7 : 6), c1 = w1 & (a.D - 1);
   const int64_t gblk = a.begin[sub] / TB + blk, nblk = a.cap[sub] / TB;
   uint32_t* dst = reinterpret_cast<uint32_t*>(a.codes[sub]) + ((((int64_t)b * a.H + h1) * nblk + gblk) * 4 + kg) * a.D + c1;
   *reinterpret_cast<uint4*>(dst) = make_uint4(words[0], words[1], words[2], words[3]);
-}
-
-// Values whose channels' parameters are known: one word group a workgroup.
-template <int DT, int BITS>
-__device__ inline void pack_values(const QPArgs& a, int sub, int unit, int b, float (*red)[kPackThreads / 64][16]) {
-  constexpr int E = 32 / BITS, ESZ = DT == ZC_F32 ? 4 : 2;
-  const int n = a.n[sub], tid = threadIdx.x;
-  const int32_t* idx = a.idx[sub] + (int64_t)b * n;
-  const int w = kPackCpt * tid < a.W ? kPackCpt * tid : 0, h = w / a.D, c = w - h * a.D;
-  const char* base = reinterpret_cast<const char*>(a.x) + ((int64_t)b * a.sB + (int64_t)h * a.sH + c) * ESZ;
-  float x[E][kPackCpt], inv_c[kPackCpt];
-#pragma unroll
-  for (int e = 0; e < E; ++e) load4<DT>(base + (int64_t)idx[min(value_token<BITS>(unit, e), n - 1)] * a.sL * ESZ, x[e]);
-  load4<ZC_F32>(param_row(a, b, sub, 0) + w, inv_c);
-  finish_values<DT, BITS>(a, sub, unit, b, x, inv_c, tid, tid >> 6, blockDim.x >> 6, red);
 }
 
 constexpr int kPackTokens = 4;         // keys: tokens of a thread
@@ -1236,7 +1233,7 @@ __device__ inline void short_values(const QPArgs& a, int sub, int wg, int b, con
   Row own[E];
   if (n > 0) {
 #pragma unroll
-    for (int e = 0; e < E; ++e) own[e] = *reinterpret_cast<const Row*>(own_base + (int64_t)sidx[min(value_token<BITS>(unit, e), n - 1)] * row_bytes);
+    for (int e = 0; e < E; ++e) own[e] = *reinterpret_cast<const Row*>(own_base + (int64_t)sidx[min(value_token<BITS>(unit >> 2, unit & 3, e), n - 1)] * row_bytes);
   }
   // statistics: s.rows tokens at a time, a lane per 16 bytes of a row
   const int sy = tid / s.lanes, sw = (tid - sy * s.lanes) * CPL;
@@ -1315,10 +1312,13 @@ __device__ inline void short_values(const QPArgs& a, int sub, int wg, int b, con
     *reinterpret_cast<float4*>(a.chan_zero + o) = make_float4(0.f, 0.f, 0.f, 0.f);
   }
   if (n == 0) return;
-  float x[E][kPackCpt];
+  const auto rows = [&](float (&x)[E][kPackCpt], float (&inv)[kPackCpt]) {
 #pragma unroll
-  for (int e = 0; e < E; ++e) load4<DT>(&own[e], x[e]);
-  finish_values<DT, BITS>(a, sub, unit, b, x, inv_c, tx, tx >> 6, nwaves, red[team]);
+    for (int e = 0; e < E; ++e) load4<DT>(&own[e], x[e]);
+#pragma unroll
+    for (int i = 0; i < kPackCpt; ++i) inv[i] = inv_c[i];
+  };
+  pack_values<DT, BITS>(a, sub, unit, b, red[team], team * s.team, s.team, rows);
 }
 
 // grid (2 s.key_wgs + s.value_wgs, B); s.team * s.teams threads
