@@ -759,7 +759,8 @@ __device__ inline void mma16(v4f& acc, u32x4 a, u32x4 b) {
   }
 }
 
-// BOTH: a wave takes the two blocks of a head together.
+// BOTH: a wave takes the two blocks of a head together.  PER_HEAD: the heads' own sums too, beside the same sum over all, which
+// scores do not depend on.
 template <int DT, int D, int NC, bool BOTH, bool PER_HEAD>
 __global__ __launch_bounds__(1024) void k_probe_few(ProbeArgs a, float* __restrict__ scores) {
   using T = Tile<DT, D>;
@@ -768,6 +769,7 @@ __global__ __launch_bounds__(1024) void k_probe_few(ProbeArgs a, float* __restri
   __shared__ float slse[kFewTable];
   __shared__ int spos[kFewRows], srow[kFewRows];
   __shared__ float part[16][16 * NC];
+  __shared__ float second[PER_HEAD ? 16 : 1][16 * NC];          // of a head whose first block is the wave before's
   const int b = blockIdx.y, col0 = blockIdx.x * 16 * NC;
   const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, g = lane >> 4, nw = blockDim.x >> 6;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -805,9 +807,19 @@ __global__ __launch_bounds__(1024) void k_probe_few(ProbeArgs a, float* __restri
   }
   for (int t = tid; t < ntab; t += blockDim.x) slse[t] = lse_src[t] * unit;
   __syncthreads();
-  float sum[NC], all[NC];                            // all: PER_HEAD, the heads so far
+  float sum[NC], head[NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) sum[c] = all[c] = 0.f;
+  for (int c = 0; c < NC; ++c) sum[c] = head[c] = 0.f;
+  const int head_col = col0 + 16 * (g % NC) + i;     // per-head scores: the column that a lane of the first NC blocks stores
+  const int seen_by = !PER_HEAD ? 0 : a.normalize ? a.P - lower_bound_pos(spos, a.P, head_col) : 1;
+  auto store_head = [&](int h, const float (&total)[NC]) {
+    const float t = total[g % NC == NC - 1 ? NC - 1 : 0];
+    if (g < NC && head_col < a.Lk) a.per_head[((int64_t)b * a.Hq + h) * a.Lk + head_col] = seen_by > 0 ? t / (float)seen_by : 0.f;
+  };
+  auto over_rows = [](float x) {
+    x += __shfl_xor(x, 16);
+    return x + __shfl_xor(x, 32);
+  };
   auto block = [&](int u, const u32x4 (&f)[NK]) {
     const int h = rt == 1 ? u : u >> 1, p0 = (rt == 1 ? 0 : (u & 1) * 16) + 4 * g;
     v4f acc[NC];
@@ -823,21 +835,21 @@ __global__ __launch_bounds__(1024) void k_probe_few(ProbeArgs a, float* __restri
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int p = p0 + v, pc = min(p, a.P - 1);
-        const float e = __builtin_amdgcn_exp2f(fmaf(acc[c][v], a.scale_log2, -slse[h * a.P + pc]));
-        sum[c] += (p < a.P && col <= spos[pc]) ? e : 0.f;
+        const float e = __builtin_amdgcn_exp2f(fmaf(acc[c][v], a.scale_log2, -slse[h * a.P + pc])), seen = (p < a.P && col <= spos[pc]) ? e : 0.f;
+        sum[c] += seen;
+        if constexpr (PER_HEAD) head[c] += seen;
       }
     }
     if constexpr (PER_HEAD) {
-      if (rt == 1 || (u & 1)) {                      // a head's last block (its first is this wave's too)
+      if (rt == 1 || (u & 1)) {                      // a head's last block
+        float total[NC];
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
-          const float total = (sum[c] + __shfl_xor(sum[c], 16)) + __shfl_xor(sum[c] + __shfl_xor(sum[c], 16), 32);
-          const int col = col0 + 16 * c + i, cnt = a.P - lower_bound_pos(spos, a.P, col);
-          if (g == 0 && col < a.Lk)
-            a.per_head[((int64_t)b * a.Hq + h) * a.Lk + col] = !a.normalize ? total : (cnt > 0 ? total / (float)cnt : 0.f);
-          all[c] += sum[c];
-          sum[c] = 0.f;
+          total[c] = over_rows(head[c]);
+          head[c] = 0.f;
+          if (rt == 2 && u == u0 && g == 0) second[w][16 * c + i] = total[c];
         }
+        if (rt == 1 || u > u0) store_head(h, total);
       }
     }
   };
@@ -867,12 +879,18 @@ __global__ __launch_bounds__(1024) void k_probe_few(ProbeArgs a, float* __restri
   }
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
-    if constexpr (PER_HEAD) sum[c] = all[c];
-    sum[c] += __shfl_xor(sum[c], 16);
-    sum[c] += __shfl_xor(sum[c], 32);
+    sum[c] = over_rows(sum[c]);
     if (g == 0) part[w][16 * c + i] = sum[c];
   }
   __syncthreads();
+  if constexpr (PER_HEAD) {
+    if (rt == 2 && (u1 & 1) && u0 < u1) {            // this wave ends with a head's first block (an even number in all: there is a wave after it)
+      float total[NC];
+#pragma unroll
+      for (int c = 0; c < NC; ++c) total[c] = over_rows(head[c]) + second[w + 1][16 * c + i];
+      store_head(u1 >> 1, total);
+    }
+  }
   if (tid < 16 * NC && col0 + tid < a.Lk) {
     float total = 0.f;
     for (int v = 0; v < nw; ++v) total += part[v][tid];
@@ -895,10 +913,11 @@ static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStr
   }
   if (a.few_cols) {
     const dim3 grid((unsigned)ceil_div(a.Lk, 16 * a.few_cols), (unsigned)a.B), block(64 * ceil_div(a.Hq * ceil_div(a.P, 16), a.few_blocks));
-    if (a.per_head) hipLaunchKernelGGL((k_probe_few<DT, D, 1, false, true>), grid, block, 0, st, a, scores);
-    else if (a.few_cols == 1) hipLaunchKernelGGL((k_probe_few<DT, D, 1, false, false>), grid, block, 0, st, a, scores);
-    else if (few_both(a.P, DT == ZC_F32, D)) hipLaunchKernelGGL((k_probe_few<DT, D, 2, few_both(kFewRows, DT == ZC_F32, D), false>), grid, block, 0, st, a, scores);
-    else hipLaunchKernelGGL((k_probe_few<DT, D, 2, false, false>), grid, block, 0, st, a, scores);
+    constexpr bool both = few_both(kFewRows, DT == ZC_F32, D);
+    const auto launch = [&](auto plain, auto per_head) { hipLaunchKernelGGL(a.per_head ? per_head : plain, grid, block, 0, st, a, scores); };
+    if (a.few_cols == 1) launch(k_probe_few<DT, D, 1, false, false>, k_probe_few<DT, D, 1, false, true>);
+    else if (few_both(a.P, DT == ZC_F32, D)) launch(k_probe_few<DT, D, 2, both, false>, k_probe_few<DT, D, 2, both, true>);
+    else launch(k_probe_few<DT, D, 2, false, false>, k_probe_few<DT, D, 2, false, true>);
     ZC_LAUNCH_CHECK();
     return ZC_OK;
   }
@@ -966,7 +985,7 @@ static bool even_waves(int64_t wgs, double tiles, const zc_tensor4* q) {
 // 6.2 / 7.4 and 6.2 / 7.9; 16 x 32 over 8, 1000 tokens 22.5 / 18.4 (32 columns) and 21.9 / 18.9; fp32, 12 heads of 64,
 // 256 tokens, 26 rows 7.9 / 7.5 and 8.1 / 7.8; 16 of 128, 100 tokens 10.0 / 8.9 and 10 / 8.5; 24 over 8, 64 tokens, 7 rows 9.9 / 10.3 and 10 / 10.2.
 struct FewPlan { int cols, blocks; };
-static FewPlan probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P, int64_t D, bool fp32, bool per_head) {
+static FewPlan probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P, int64_t D, bool fp32) {
   FewPlan plan = {0, 0};
   if (P > kFewRows || Hq * P > kFewTable) return plan;
   const int64_t row_bytes = D * (fp32 ? 4 : 2), rt = ceil_div64(P, 16);
@@ -979,8 +998,8 @@ static FewPlan probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t
     best = (D == 64 ? 5.8 : 6.1) + 0.5 * (wgs < 4.0 ? wgs : 4.0) + (wgs > 4.0 ? (D == 64 ? 0.85 : 1.15) * (wgs - 4.0) : 0.0);
     further = D == 64 ? 0.2 : 1.1;
   }
-  for (int64_t nc = 1; nc <= (per_head ? 1 : 2); ++nc)
-    for (int64_t share = per_head || (nc == 2 && few_both(P, fp32, D)) ? rt : 1; share <= (nc == 2 && !few_both(P, fp32, D) ? 1 : rt); ++share) {
+  for (int64_t nc = 1; nc <= 2; ++nc)
+    for (int64_t share = nc == 2 && few_both(P, fp32, D) ? rt : 1; share <= (nc == 2 && !few_both(P, fp32, D) ? 1 : rt); ++share) {
       const int64_t blocks = ceil_div64(Hq * rt, 16 * share) * share, waves = ceil_div64(Hq * rt, blocks), segments = Hkv > waves ? Hkv : waves;
       const int64_t n = B * ceil_div64(Lk, 16 * nc), rounds = ceil_div64(n, 256);
       const double rate = rounds == 1 ? 37.0 : fp32 ? 22.0 : 28.0;
@@ -1046,7 +1065,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.probe_rows = probe_rows; a.probe_pos = probe_pos;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse_in = lse_ext;
-  const FewPlan few = probe_few(q->B, q->H, k->H, k->L, P, q->D, q->dtype == ZC_F32, scores_per_head != nullptr);
+  const FewPlan few = probe_few(q->B, q->H, k->H, k->L, P, q->D, q->dtype == ZC_F32);
   a.few_cols = few.cols;
   a.few_blocks = few.blocks;
   a.join = !lse_ext && !a.few_cols && probe_join(q->B, q->H, k->L, P) && ws_bytes >= need + extra;

@@ -244,6 +244,7 @@ def test_scores_of_few_probes_in_one_launch(case, external):
     for s in got:
         rel = ((s.double() - want).abs() / want.clamp(min=1e-30)).max().item()
         assert rel < 3e-5, rel                                                   # (the bound of test_scores_of_row_blocks_and_ranges)
+    assert torch.equal(got[0], got[1])
     assert torch.allclose(per_head.mean(1), got[1], rtol=1e-5, atol=0)
     summed = zb.zc_probe_accumulated(q, k, pos.int(), probe_rows=rows.int(), lse_ext=lse)
     seen = (pos[:, None] >= torch.arange(L, device=DEV)[None]).sum(0).clamp(min=1)
