@@ -53,6 +53,14 @@ __device__ inline void pick_bin(const int* hist, int* wave_tot, int need, int ti
 }
 
 constexpr int kSelCand = 1024;                 // candidates one wave finishes the search on
+// Few rows leave most CUs idle while one of them writes a row's lists, 64 entries a store to a few lines each: kSelSlices
+// workgroups then repeat the search for the k-th key, which costs no time, and write an eighth of the lists each (a quarter of up to 4096
+// tokens).  Rows of more than 2048 tokens, while a CU has one such workgroup at most.  us per launch, one workgroup a row and
+// eight, one row and 32 rows, k = 0.4 L: 2500 tokens 5.3 / 5.65 and 5.1 / 5.3; 4096 5.5 / 5.9 and 5.2 / 5.5; 8192 7.2 / 7.7 and 6.5 / 6.8; 16384 12.7 /
+// 13.2 and 10.7 / 11.1; 21108 18.0 / 18.6 and 15.5 / 15.9; 32768 20.7 / 21.4 and 16.5 / 17.1 (15.9 / 16.6 with four loads requested at once).
+constexpr int kSelSlices = 8;
+static bool select_sliced(int64_t B) { return B * kSelSlices <= 256; }
+constexpr int kSelPieces = 136;                // of 256 tokens: kSelMaxCached
 constexpr int kSelBufFlags = 0x00020000;       // buffer descriptor: raw 32-bit data, no swizzle
 constexpr int kSelDropped = (int)0xFFFFF000u;  // a store offset past the end of every output: the store is dropped
 
@@ -72,7 +80,9 @@ constexpr int kSelDropped = (int)0xFFFFF000u;  // a store offset past the end of
 //      are written through buffer descriptors, a store that does not apply (the other list's,
 //      a pad's) being pointed past the end of its buffer, where it is dropped.
 // VEC: the row starts on a 16-byte boundary (16-byte loads of the scores).
-template <bool VEC>
+// SLICED: gridDim.y workgroups share a row: each finds the k-th key for itself (one CU's chain of steps either way) and
+// compacts pieces of 256 tokens of its own, whose counts are kept per piece.
+template <bool VEC, bool SLICED>
 __global__ __launch_bounds__(kSelThreads) void k_select_cached(
     const float* __restrict__ scores, int L, int k, int32_t* __restrict__ salient,
     int32_t* __restrict__ regular, uint8_t* __restrict__ mask) {
@@ -83,6 +93,7 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
   __shared__ uint32_t s_thr;
   __shared__ int s_wave_gt[kSelWaves], s_wave_eq[kSelWaves];
   __shared__ uint32_t s_wave_min[kSelWaves], s_wave_max[kSelWaves];
+  __shared__ int s_piece[SLICED ? kSelPieces : 1];             // low half: keys above the k-th, high half: equal to it
   static_assert(kSelCand * 2 <= kSelRep * kSelRepStride && kSelWaves * 256 <= kSelRep * kSelRepStride,
                 "the candidates and the compaction stages reuse the histogram copies");
 
@@ -96,7 +107,22 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
   for (int i = tid; i < kSelRep * kSelRepStride; i += kSelThreads) hrep[i] = 0;
   if (tid == 0) s_ncand = 0;
   uint32_t kmin = 0xffffffffu, kmax = 0u;
-  for (int c = tid; c < n4; c += kSelThreads) {
+  int c0 = tid;
+  if constexpr (VEC) {                               // four words requested at once (one workgroup a row, 32768 tokens 21.5 -> 20.6 us)
+    for (; c0 + 3 * kSelThreads < L >> 2; c0 += 4 * kSelThreads) {
+      float4 t[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) t[u] = reinterpret_cast<const float4*>(sc)[c0 + u * kSelThreads];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint4 kk = make_uint4(float_key(t[u].x), float_key(t[u].y), float_key(t[u].z), float_key(t[u].w));
+        kmin = min(min(kmin, min(kk.x, kk.y)), min(kk.z, kk.w));
+        kmax = max(max(kmax, max(kk.x, kk.y)), max(kk.z, kk.w));
+        skeys4[c0 + u * kSelThreads] = kk;
+      }
+    }
+  }
+  for (int c = c0; c < n4; c += kSelThreads) {
     const int i = 4 * c;
     uint32_t kk[4] = {0u, 0u, 0u, 0u};
     if (i + 3 < L) {
@@ -192,6 +218,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
   {
     const uint32_t pg = thr_gt >> lo, pe = thr_eq >> lo;
     int cnt = 0;                                    // low half: keys above, high half: keys equal (no bits left)
+    if constexpr (SLICED) { if (tid < kSelPieces) s_piece[tid] = 0; }      // (a wave's own are written after this barrier)
+    if constexpr (SLICED) __syncthreads();
     auto piece = [&](auto whole_c, int base) {
       constexpr bool WHOLE = decltype(whole_c)::value;              // no pad in this piece
       const uint4 kk = skeys4[(base >> 2) + lane];
@@ -214,7 +242,12 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
         at = __builtin_amdgcn_readlane(at, 63) + incl - nin;
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-          if (in[u]) cand[at++] = make_uint2(k4[u], (uint32_t)wave);
+          if (in[u]) cand[at++] = make_uint2(k4[u], SLICED ? (uint32_t)base >> 8 : (uint32_t)wave);
+      }
+      if constexpr (SLICED) {
+        const int all = wave_inclusive_sum(cnt);
+        if (lane == 63) s_piece[base >> 8] = all;
+        cnt = 0;
       }
     };
     for (int base = i0; base < i1; base += 256) {
@@ -222,8 +255,10 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
       else piece(std::false_type{}, base);
     }
     // (a wave's run has at most 34816 / 16 rounded up to 256 = 2304 tokens: the halves cannot carry)
-    cnt = __builtin_amdgcn_readlane(wave_inclusive_sum(cnt), 63);
-    if (lane == 0) { s_wave_gt[wave] = cnt & 0xffff; s_wave_eq[wave] = cnt >> 16; }
+    if constexpr (!SLICED) {
+      cnt = __builtin_amdgcn_readlane(wave_inclusive_sum(cnt), 63);
+      if (lane == 0) { s_wave_gt[wave] = cnt & 0xffff; s_wave_eq[wave] = cnt >> 16; }
+    }
   }
   __syncthreads();
 
@@ -269,7 +304,9 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
       }
       for (int j = lane; j < n; j += 64) {
         const uint2 c = cand[j];
-        if (c.x > pre) atomicAdd(&s_wave_gt[c.y], 1);
+        if constexpr (SLICED) {
+          if (c.x >= pre) atomicAdd(&s_piece[c.y], c.x > pre ? 1 : 0x10000);
+        } else if (c.x > pre) atomicAdd(&s_wave_gt[c.y], 1);
         else if (c.x == pre) atomicAdd(&s_wave_eq[c.y], 1);
       }
       if (lane == 0) { s_thr = pre; s_need = nd; }
@@ -281,7 +318,8 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
 
   // ---- 5. ordered compaction -------------------------------------------------------
   int run_gt = 0, run_eq = 0;
-  for (int w = 0; w < wave; ++w) { run_gt += s_wave_gt[w]; run_eq += s_wave_eq[w]; }
+  if constexpr (!SLICED)
+    for (int w = 0; w < wave; ++w) { run_gt += s_wave_gt[w]; run_eq += s_wave_eq[w]; }
   run_gt = __builtin_amdgcn_readfirstlane(run_gt);
   run_eq = __builtin_amdgcn_readfirstlane(run_eq);
   const auto rs_sal = __builtin_amdgcn_make_buffer_rsrc(salient + (int64_t)b * k, 0, (uint32_t)k * 4u, kSelBufFlags);
@@ -293,7 +331,17 @@ __global__ __launch_bounds__(kSelThreads) void k_select_cached(
   // the tokens of a piece go to a 256-word stage of the wave in list order - the salient ones,
   // then the others - and leave it 64 consecutive words at a time.
   int32_t* stage = hrep + wave * 256;               // (the candidates are no longer needed)
-  for (int base = i0; base < i1; base += 256) {
+  const int first = SLICED ? 256 * (int)(blockIdx.y * kSelWaves + wave) : i0, end = SLICED ? L : i1;
+  const int stride = SLICED ? 256 * kSelWaves * (int)gridDim.y : 256;
+  for (int base = first; base < end; base += stride) {
+    if constexpr (SLICED) {                          // what the pieces before this one hold (halves of 16 bits: no more than 34816 tokens)
+      uint32_t before = 0u;
+#pragma unroll
+      for (int u = 0; u < (kSelPieces + 63) / 64; ++u) before += 64 * u + lane < base >> 8 ? (uint32_t)s_piece[min(64 * u + lane, kSelPieces - 1)] : 0u;
+      before = (uint32_t)__builtin_amdgcn_readlane(wave_inclusive_sum((int)before), 63);
+      run_gt = (int)(before & 0xffffu);
+      run_eq = (int)(before >> 16);
+    }
     const uint4 kk = skeys4[(base >> 2) + lane];
     const int i = base + 4 * lane;
     const uint32_t k4[4] = {kk.x, kk.y, kk.z, kk.w};
@@ -451,8 +499,9 @@ __device__ inline void count_digits(int* hist, const uint32_t (&key)[KPT], int l
   }
 }
 
-// One wave (THREADS == 64): no LDS, no barrier, the bisection over all keys.
-template <int THREADS, int KPT>
+// One wave (THREADS == 64): no LDS, no barrier, the bisection over all keys.  SLICES workgroups (grid.y) share a row: each finds
+// the k-th key for itself and stores KPT / SLICES keys a thread.
+template <int THREADS, int KPT, int SLICES>
 __global__ __launch_bounds__(THREADS) void k_select_small(
     const float* __restrict__ scores, int L, int k, int32_t* __restrict__ salient,
     int32_t* __restrict__ regular, uint8_t* __restrict__ mask) {
@@ -594,7 +643,7 @@ __global__ __launch_bounds__(THREADS) void k_select_small(
     const int eq_before = run_eq + lanes_below(eq[u]);
     const bool is_sal = (gt[u] >> lane & 1) || ((eq[u] >> lane & 1) && eq_before < need);
     const int p = run_gt + lanes_below(gt[u]) + min(eq_before, need);
-    if (i < L) {
+    if (i < L && (SLICES == 1 || u / (KPT / SLICES) == (int)blockIdx.y)) {
       int32_t* dst = is_sal ? sal + p : reg + (i - p);
       *dst = i;
       if (mask) mask[(int64_t)b * L + i] = is_sal ? 1 : 0;
@@ -720,32 +769,33 @@ extern "C" int zc_select_salient(const float* scores, int64_t B, int64_t L, int6
       (reinterpret_cast<uintptr_t>(regular_idx) & 3))
     return ZC_ERR_INVALID_ARG;
   if (zc::select_small(B, L)) {
-    const auto launch = [&](auto kernel, unsigned threads) {
-      hipLaunchKernelGGL(kernel, dim3((unsigned)B), dim3(threads), 0, (hipStream_t)stream, scores, (int)L, (int)k, salient_idx, regular_idx, mask);
+    const auto launch = [&](auto kernel, unsigned threads, unsigned slices = 1) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)B, slices), dim3(threads), 0, (hipStream_t)stream, scores, (int)L, (int)k, salient_idx, regular_idx, mask);
     };
-    if (L <= 64 * 4) launch(zc::k_select_small<64, 4>, 64);
-    else if (L <= 256 * 4) launch(zc::k_select_small<256, 4>, 256);
-    else if (L <= 512 * 4) launch(zc::k_select_small<512, 4>, 512);
-    else if (L <= 1024 * 4) launch(zc::k_select_small<1024, 4>, 1024);
-    else if (L <= 1024 * 8) launch(zc::k_select_small<1024, 8>, 1024);
-    else launch(zc::k_select_small<1024, 16>, 1024);
+    const bool sliced = zc::select_sliced(B);
+    if (L <= 64 * 4) launch(zc::k_select_small<64, 4, 1>, 64);
+    else if (L <= 256 * 4) launch(zc::k_select_small<256, 4, 1>, 256);
+    else if (L <= 512 * 4) launch(zc::k_select_small<512, 4, 1>, 512);
+    else if (L <= 1024 * 4 && sliced) launch(zc::k_select_small<1024, 4, 4>, 1024, 4);
+    else if (L <= 1024 * 4) launch(zc::k_select_small<1024, 4, 1>, 1024);
+    else if (L <= 1024 * 8 && sliced) launch(zc::k_select_small<1024, 8, 8>, 1024, 8);
+    else if (L <= 1024 * 8) launch(zc::k_select_small<1024, 8, 1>, 1024);
+    else if (sliced) launch(zc::k_select_small<1024, 16, 8>, 1024, 8);
+    else launch(zc::k_select_small<1024, 16, 1>, 1024);
   } else if (L <= zc::kSelMaxCached) {
     const size_t lds = (size_t)((L + 255) & ~(int64_t)255) * sizeof(uint32_t);
     // rows start on 16-byte boundaries when the array does and L is a multiple of four (or B is 1)
     const bool vec = (reinterpret_cast<uintptr_t>(scores) & 15) == 0 && (B == 1 || (L & 3) == 0);
-    const void* fn = vec ? reinterpret_cast<const void*>(&zc::k_select_cached<true>)
-                         : reinterpret_cast<const void*>(&zc::k_select_cached<false>);
+    const bool sliced = zc::select_sliced(B);
+    const auto kernel = vec ? (sliced ? &zc::k_select_cached<true, true> : &zc::k_select_cached<true, false>)
+                            : (sliced ? &zc::k_select_cached<false, true> : &zc::k_select_cached<false, false>);
     if (lds > 32 * 1024) {
       // a launch above the default dynamic-LDS limit needs the attribute raised (idempotent)
-      if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(zc::kSelMaxCached * sizeof(uint32_t))) != hipSuccess)
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)(zc::kSelMaxCached * sizeof(uint32_t))) != hipSuccess)
         return ZC_ERR_HIP;
     }
-    if (vec)
-      hipLaunchKernelGGL(zc::k_select_cached<true>, dim3((unsigned)B), dim3(zc::kSelThreads), lds,
-                         (hipStream_t)stream, scores, (int)L, (int)k, salient_idx, regular_idx, mask);
-    else
-      hipLaunchKernelGGL(zc::k_select_cached<false>, dim3((unsigned)B), dim3(zc::kSelThreads), lds,
-                         (hipStream_t)stream, scores, (int)L, (int)k, salient_idx, regular_idx, mask);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)B, sliced ? zc::kSelSlices : 1), dim3(zc::kSelThreads), lds,
+                       (hipStream_t)stream, scores, (int)L, (int)k, salient_idx, regular_idx, mask);
   } else {
     hipLaunchKernelGGL(zc::k_select_stream, dim3((unsigned)B), dim3(zc::kSelThreads), 0,
                        (hipStream_t)stream, scores, (int)L, (int)k, salient_idx, regular_idx, mask);

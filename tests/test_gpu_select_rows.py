@@ -68,3 +68,26 @@ def test_select_many_rows(B, L):
     x = torch.randn(B, L, generator=g, device="cuda").exp()
     x[::3] = (x[::3] * 8).floor()
     _check(x, L // 3)
+
+
+@pytest.mark.parametrize("B,L", [(32, 2049), (33, 2049), (32, 4096), (33, 4095), (32, 4097), (33, 8192), (32, 8193), (33, 16384), (32, 16384),
+                                 (1, 16385), (2, 16640), (4, 21001), (32, 30000), (33, 30000), (3, 34816), (33, 34815), (2, 34817)])
+def test_select_rows_shared_by_workgroups(B, L):
+    """Rows that eight workgroups share (up to 32 of them) and that one takes: spread scores, few values (the k-th place inside
+    thousands of equal ones, over many pieces), one value, and a row of -inf, salient counts down to none of a piece and all of it."""
+    from paper_2405_14256_amd import binding as zb
+    g = torch.Generator(device="cuda").manual_seed(B + L)
+    x = torch.randn(B, L, generator=g, device="cuda").exp()
+    if B > 1:
+        x[1] = (x[1] * 2).floor()
+        x[B - 1] = float("-inf")
+    if B > 3:
+        x[2] = 0.25
+        x[3, : L // 2] += 1e3                   # the first half salient: pieces of either list alone
+    for k in (0, 1, L // 10, L // 2, L - 1, L):
+        mask = torch.full((B, L), 7, dtype=torch.uint8, device="cuda")
+        sal, reg = zb.zc_select_salient(x, k, mask=mask)
+        first = torch.sort(x, dim=1, descending=True, stable=True).indices        # equal scores: lower index first
+        assert torch.equal(sal.long(), first[:, :k].sort(dim=1).values) and torch.equal(reg.long(), first[:, k:].sort(dim=1).values)
+        want = torch.zeros_like(mask).scatter_(1, first[:, :k], torch.ones_like(mask[:, :k]))
+        assert torch.equal(mask, want)
