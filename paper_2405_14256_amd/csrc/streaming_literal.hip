@@ -46,7 +46,7 @@ struct ProbsArgs {
   const float* lse;         // [B, Hq] natural log
   float* probs;             // [B, Hq, N]
   int N;
-  int tpw;                  // units (tail: tiles) per wave
+  int tpw, tail_tpw;        // units per wave (of one tile: 1), the tail's tiles per wave
   int n_segs;
   ProbsSeg seg[kProbSegs];
 };
@@ -224,7 +224,7 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
   float* out = a.probs + hq * a.N;
   const bool store = nvalid && (TILES == 2 || part == 0);
 
-  for (int i = 0; i < a.tpw; ++i) {
+  for (int i = 0; i < (TILES == 1 ? 1 : a.tpw); ++i) {
     const int unit = unit0 + 4 * i;
     if (unit >= nunits) break;
     uint32_t r[TILES][NK / 2];
@@ -236,7 +236,7 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
       ts[0] = in.ts.x; ts[1] = in.ts.y; ts[2] = in.ts.z; ts[3] = in.ts.w;
       tz[0] = in.tz.x; tz[1] = in.tz.y; tz[2] = in.tz.z; tz[3] = in.tz.w;
     }
-    load(min(unit + 4, nunits - 1), in);              // the next unit's inputs are in flight meanwhile (no branch: it would copy them)
+    if constexpr (TILES == 2) load(min(unit + 4, nunits - 1), in);      // the next unit's inputs are in flight meanwhile (no branch: it would copy them)
     f4 acc[TILES];
 #pragma unroll
     for (int t = 0; t < TILES; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
@@ -272,7 +272,7 @@ __device__ inline void probs_tail(const ProbsArgs& a, int b, int hk, int len, in
   const float scale = nvalid ? a.scale_log2 : 0.f;
   const float lse2 = a.lse[hq] * kLog2e;
   float* out = a.probs + hq * a.N + a.tail_pos0;
-  for (int tile = tile0; tile < ntiles && tile < tile0 + 4 * a.tpw; tile += 4) {
+  for (int tile = tile0; tile < ntiles && tile < tile0 + 4 * a.tail_tpw; tile += 4) {
     const int t = min(tile * kProbTile + n, len - 1);
     const int64_t off = (int64_t)b * a.tk_sB + (int64_t)hk * a.tk_sH + (int64_t)t * a.tk_sL + kg * NK;
     f4 acc = f4{0.f, 0.f, 0.f, 0.f};
@@ -293,7 +293,7 @@ __device__ inline void probs_tail(const ProbsArgs& a, int b, int hk, int len, in
   }
 }
 
-// grid (workgroups of all segments, Hkv, B); a wave takes a.tpw units of its segment.  TOK: keys with token parameters.
+// grid (workgroups of all segments, Hkv, B); a wave takes a.tpw units of its segment (a.tail_tpw tiles of the tail).  TOK: keys with token parameters.
 template <int DT, int D, bool TOK, int TILES>
 __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
   const int hk = blockIdx.y, b = blockIdx.z;
@@ -305,7 +305,7 @@ __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
   const int si = __builtin_popcountll(__builtin_amdgcn_ballot_w64(before)) - 1;
   const int begin = a.seg[si].begin, len = a.seg[si].len, sub = a.seg[si].sub;
   const bool is_tail = sub == kTailSub;
-  const int first = ((int)blockIdx.x - a.seg[si].first_block) * 4 * a.tpw + wave, count = ceil_div(len, is_tail ? kProbTile : TILES * kProbTile);
+  const int first = ((int)blockIdx.x - a.seg[si].first_block) * 4 * (is_tail ? a.tail_tpw : a.tpw) + wave, count = ceil_div(len, is_tail ? kProbTile : TILES * kProbTile);
   const int bits = is_tail ? 0 : sub ? a.bits[1] : a.bits[0];
   if (first >= count) return;
   if (is_tail) probs_tail<DT, D>(a, b, hk, len, first, count);
@@ -640,13 +640,33 @@ extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const z
   int unit = kProbTile;
   // A tile a wave while every SIMD has a wave at most (latency); else two at a time, one unit a wave while the launch is below two
   // waves a SIMD, up to six when the chip is full anyway and a wave's start (the query operand) would weigh as much as its
-  // units.  us by one and by two tiles at a time: 784 tiles (700 tokens of 16 KV heads of 128 channels) 4.3 and 4.5, 1100 (1400 of 12 heads of
-  // 64) 4.2 and 3.8, 2100 (4096 of 8) 6.5 and 5.9; 16 x 40 heads of 2000 tokens by up to 2, 4, 6 and 8 units a wave 46.0, 38.9, 36.2 and 44.9.
+  // units.  us by one and by two tiles at a time: 784 packed tiles (700 tokens of 16 KV heads of 128 channels) 4.3 and 4.5, 928 (928 of 16)
+  // 5.7 and 4.8, 1100 (1400 of 12 heads of 64) 4.2 and 3.8, 2100 (4096 of 8) 6.5 and 5.9; up to 1400 not of 8-bit codes (930: 3720 of 4 heads,
+  // 4.8 and 5.35) nor of segments so short that little less than the same workgroups are left (1360: 5 x 16 heads of 256, 5.6 and 6.1); 16 x 40 heads of 2000 tokens by up to 2, 4, 6
+  // and 8 units a wave 46.0, 38.9, 36.2 and 44.9.
+  // One unit more a wave where that spares a fifth of the workgroups or the second round: of several rounds, a workgroup of a unit or two
+  // costs about what a full one does (one to two units: 8 heads of 13990 tokens 9.65 and 8.0; four to five: 3 x 8 of 11239 13.0 and 11.6;
+  // 8 x 40 heads of 660 tokens and 94 of the tail, fp32, four and three workgroups a head 39.5 and 36.9, with its decode; 4 x 8 heads of 4006 tokens, 1056 workgroups of one unit 11.2, 10.4 when they fit a round).  The tail's tiles go one at a
+  // time, up to eight a wave (16 x 40 heads of 70 tokens and 78, one and three a wave 45.6 and 32.0, with its decode).
   {
-    const int64_t all = tiles * a.Hkv * a.B;
-    if (all > 960) unit = 2 * kProbTile;
-    const int64_t t = all / (unit / kProbTile) / 2048;
-    a.tpw = (int)(t < 1 ? 1 : t > 6 ? 6 : t);
+    const int64_t heads = (int64_t)a.Hkv * a.B, all = tiles * heads, packed = (tiles - ceil_div64(tail_len, kProbTile)) * heads;
+    const int64_t round = q->dtype == ZC_F32 && q->D == 128 ? 768 : 1024;      // (three or four workgroups a CU, by registers)
+    const auto bounded = [](int64_t t, int64_t most) { return (int)(t < 1 ? 1 : t > most ? most : t); };
+    a.tail_tpw = bounded(all / 2048, 8);
+    const auto workgroups = [&](int slots, int tpw) {       // of the packed segments of a head
+      int64_t n = 0;
+      for (int ci = 0; ci < Kp->n_chunks; ++ci)
+        for (int sb = 0; sb < 2; ++sb) n += ceil_div64(ceil_div64(Kp->chunk_table_host[4 * ci + 2 * sb + 1], slots), 4 * tpw);
+      return n;
+    };
+    const int64_t tail_wgs = ceil_div64(ceil_div64(tail_len, kProbTile), 4 * a.tail_tpw);
+    const bool narrow = a.bits[0] <= 4 && a.bits[1] <= 4;
+    if (packed > 1400 || (packed > 860 && narrow && 20 * workgroups(2 * kProbTile, 1) <= 11 * workgroups(kProbTile, 1))) unit = 2 * kProbTile;
+    a.tpw = unit == kProbTile ? 1 : bounded(all / 4096, 6);
+    if (unit > kProbTile && a.tpw < 6) {
+      const int64_t now = workgroups(unit, a.tpw) + tail_wgs, next = workgroups(unit, a.tpw + 1) + tail_wgs;
+      if (((a.tpw >= 2 || now * heads > 640) && 5 * next <= 4 * now) || (now * heads > round && next * heads <= round)) ++a.tpw;
+    }
   }
   hipStream_t st = (hipStream_t)stream;
   int64_t blocks = 0;
@@ -680,7 +700,7 @@ extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const z
       if (rcf) return rcf;
     }
     a.seg[a.n_segs++] = {begin, (int)len, (int)blocks, chunk, sub};
-    blocks += ceil_div64(ceil_div64(len, sub == kTailSub ? kProbTile : unit), 4 * a.tpw);
+    blocks += sub == kTailSub ? ceil_div64(ceil_div64(len, kProbTile), 4 * a.tail_tpw) : ceil_div64(ceil_div64(len, unit), 4 * a.tpw);
     return ZC_OK;
   };
   for (int ci = 0; ci < Kp->n_chunks; ++ci)
