@@ -1,5 +1,6 @@
 // zc_select_salient: exact top-k split of the token scores (Algorithm 2,
-// "Split(., p~, r%)").  One workgroup per batch row: an MSB-first radix select
+// "Split(., p~, r%)").  One workgroup per batch row (of few long rows up to
+// eight, which share the writing: select_sliced): an MSB-first radix select
 // on the order-preserving uint32 image of the scores finds the k-th largest
 // key and how many tokens equal to it are taken (lowest indices first); one
 // ordered compaction pass then writes both index lists in ascending order.
