@@ -1308,8 +1308,9 @@ __device__ inline void short_values(const QPArgs& a, int sub, int wg, int b, con
   for (int i = 0; i < kPackCpt; ++i) inv_c[i] = channel_params(ZC_SCHEME_CST, n, 0.f, lo[i], -neg[i], &cs[i], &cz).x;
   if (unit == 0 && kPackCpt * tx < a.W) {
     const int64_t o = (int64_t)(sub * a.B + b) * a.W + w;
-    *reinterpret_cast<float4*>(a.chan_scale + o) = make_float4(cs[0], cs[1], cs[2], cs[3]);
-    *reinterpret_cast<float4*>(a.chan_zero + o) = make_float4(0.f, 0.f, 0.f, 0.f);
+    typedef float f4a __attribute__((ext_vector_type(4), aligned(4)));         // (the validation does not hold these arrays to 16 bytes)
+    *reinterpret_cast<f4a*>(a.chan_scale + o) = f4a{cs[0], cs[1], cs[2], cs[3]};
+    *reinterpret_cast<f4a*>(a.chan_zero + o) = f4a{0.f, 0.f, 0.f, 0.f};
   }
   if (n == 0) return;
   const auto rows = [&](float (&x)[E][kPackCpt], float (&inv)[kPackCpt]) {

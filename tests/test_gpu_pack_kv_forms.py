@@ -112,6 +112,31 @@ def test_short_subsets_as_beside_long_ones(H, D, dtype, k, bits, special):
             assert o.chunk_table.flatten()[:4].tolist() == [0, k, 0, 0] and o.chunks == [(0, k, 0, 0)]
 
 
+@pytest.mark.parametrize("n", [20, 131])
+@pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
+def test_channel_parameters_at_any_float(dtype, n):
+    """Channel parameters are written where they are put, also at addresses that four bytes divide and sixteen do not (by
+    the kernel of short subsets and those of longer ones): the same bits, and the floats beside them left alone."""
+    B, H, D, k = 2, 3, 64, 5
+    g = torch.Generator(device=DEV).manual_seed(n)
+    X, Y = (torch.randn(B, H, k + n, D, generator=g, device=DEV).to(dtype) for _ in range(2))
+    sal, reg = zb.zc_select_salient(torch.rand(B, k + n, generator=g, device=DEV), k)
+    forms = [("channel", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP)]
+    want = [_packed(f, B, H, D, k, n, (4, 2)) for f in forms]
+    zb.zc_quantize_pack_kv(X, Y, sal, reg, *want)
+    for off in (1, 2, 3):
+        got = [_packed(f, B, H, D, k, n, (4, 2)) for f in forms]
+        wide = [[torch.full((a.numel() + 8,), -7.0, device=DEV) for a in (p.chan_scale, p.chan_zero)] for p in got]
+        for p, (scale, zero) in zip(got, wide):
+            p.c.chan_scale, p.c.chan_zero = scale[off:].data_ptr(), zero[off:].data_ptr()
+        zb.zc_quantize_pack_kv(X, Y, sal, reg, *got)
+        for w, p, arrays in zip(want, got, wide):
+            assert torch.equal(w.codes_hi, p.codes_hi) and torch.equal(w.codes_lo, p.codes_lo)
+            for a, b in zip((w.chan_scale, w.chan_zero), arrays):
+                assert torch.equal(b[off:off + a.numel()], a.flatten())
+                assert bool((b[:off] == -7.0).all()) and bool((b[off + a.numel():] == -7.0).all())
+
+
 def _largest(form, H, n, bits, dtype):
     """`n` tokens of which a few are not zero, packed; the same few (and a zero one) in a call of their own."""
     D = 64
