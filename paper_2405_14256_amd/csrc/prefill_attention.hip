@@ -99,6 +99,10 @@ __device__ inline void probe_normalisers(const PrefillArgs& a, int64_t head, int
   }
 }
 
+// Where a row's reference starts: below every logit, but finite, so that a wave whose logits are all -inf so far has weights of
+// 2^(-inf) = 0 and not of 2^(-inf + inf), and a wave without keys joins with a factor for its zeros that is a number.
+constexpr float kLowest = -3.40282347e38f;
+
 // Chunk slot permutation of a V tile row: the transposing load reads 64 bytes of four
 // consecutive keys per half-wave (32 bytes per 16 lanes); these land in different banks.
 template <int D>
@@ -148,7 +152,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
   v16f oacc[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) oacc[ct] = v16f{};
-  float m = -INFINITY, l = 0.f;       // running maximum (log2 units) and this half-wave's share of the sum
+  float m = kLowest, l = 0.f;       // running maximum (log2 units) and this half-wave's share of the sum
 
   const int nblk = q0 / 32 + 1;                  // blocks of 32 keys the rows see: the last is the diagonal
   for (int blk = w; blk < nblk; blk += NW) {
@@ -180,7 +184,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     const float m_new = fmaxf(m, tmax * a.scale_log2);
     if (__builtin_amdgcn_ballot_w64(m_new > m)) {
-      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
       l *= alpha;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
@@ -224,7 +228,7 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
     return;
   }
   // ---- join the waves: a common reference and sum, then the outputs one wave after the other ----
-  // (a wave without keys has m = -inf, l = 0 and zeros; wave 0 always has the block of key 0)
+  // (a wave without keys has m = kLowest, l = 0 and zeros; wave 0 always has the block of key 0)
   const float l_wave = l + __shfl_xor(l, 32);
   if (kh == 0) { sm[w][r] = m; sl[w][r] = l_wave; }
   __syncthreads();
@@ -233,8 +237,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_prefill_attention32(PrefillArgs 
   for (int v = 1; v < NW; ++v) M = fmaxf(M, sm[v][r]);
   float l_tot = 0.f;
 #pragma unroll
-  for (int v = 0; v < NW; ++v) l_tot += sm[v][r] == -INFINITY ? 0.f : sl[v][r] * __builtin_amdgcn_exp2f(sm[v][r] - M);
-  const float mine = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M) / l_tot;
+  for (int v = 0; v < NW; ++v) l_tot += sl[v][r] * __builtin_amdgcn_exp2f(sm[v][r] - M);
+  const float mine = __builtin_amdgcn_exp2f(m - M) / l_tot;
   const int used = min(NW, nblk);
   for (int v = used - 1; v >= 0; --v) {
     if (w == v) {
@@ -303,7 +307,7 @@ __global__ __launch_bounds__(512, 1) void k_prefill_attention32_few(PrefillArgs 
   v4f oacc[CT];
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) oacc[ct] = v4f{};
-  float m = -INFINITY, l = 0.f;       // running maximum (log2 units) and this lane group's share of the sum
+  float m = kLowest, l = 0.f;       // running maximum (log2 units) and this lane group's share of the sum
 
   const int nblk = q0 / 32 + 1;                  // blocks of 32 keys the rows see: the last holds the diagonal
   for (int blk = w; blk < nblk; blk += NW) {
@@ -350,7 +354,7 @@ __global__ __launch_bounds__(512, 1) void k_prefill_attention32_few(PrefillArgs 
     tmax = fmaxf(tmax, __shfl_xor(tmax, 32));
     const float m_new = fmaxf(m, tmax * a.scale_log2);
     if (__builtin_amdgcn_ballot_w64(m_new > m)) {
-      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
       l *= alpha;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
@@ -359,12 +363,11 @@ __global__ __launch_bounds__(512, 1) void k_prefill_attention32_few(PrefillArgs 
       m = m_new;
     }
     float psum = 0.f;
-    const float ref = m == -INFINITY ? 0.f : m;  // (a wave whose logits are all -inf so far: its weights are 0)
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        s[t][v] = __builtin_amdgcn_exp2f(fmaf(s[t][v], a.scale_log2, -ref));
+        s[t][v] = __builtin_amdgcn_exp2f(fmaf(s[t][v], a.scale_log2, -m));
         psum += s[t][v];
       }
     l += psum;
@@ -377,7 +380,7 @@ __global__ __launch_bounds__(512, 1) void k_prefill_attention32_few(PrefillArgs 
   }
 
   // ---- join the waves: a common reference and sum, then the outputs of all of them at once ----
-  // (a wave without keys has m = -inf, l = 0 and zeros; wave 0 always has the block of key 0)
+  // (a wave without keys has m = kLowest, l = 0 and zeros; wave 0 always has the block of key 0)
   float l_wave = l + __shfl_xor(l, 16);
   l_wave += __shfl_xor(l_wave, 32);
   if (g == 0) { sm[w][r] = m; sl[w][r] = l_wave; }
@@ -387,12 +390,12 @@ __global__ __launch_bounds__(512, 1) void k_prefill_attention32_few(PrefillArgs 
   const int used = min(NW, nblk);
   for (int i = tid; i < 16 * (D / 4); i += 64 * NW) {
     const int row = i / (D / 4), c = (i % (D / 4)) * 4;
-    float pm[NW], M = -INFINITY, total = 0.f;
+    float pm[NW], M = kLowest, total = 0.f;
 #pragma unroll
     for (int v = 0; v < NW; ++v) { pm[v] = sm[v][row]; M = fmaxf(M, pm[v]); }
 #pragma unroll
     for (int v = 0; v < NW; ++v) {
-      pm[v] = pm[v] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(pm[v] - M);
+      pm[v] = __builtin_amdgcn_exp2f(pm[v] - M);
       total = fmaf(sl[v][row], pm[v], total);
     }
     v4f o = v4f{};
@@ -408,11 +411,11 @@ __global__ __launch_bounds__(512, 1) void k_prefill_attention32_few(PrefillArgs 
   if (a.probe_pos) {
     __syncthreads();                             // (every wave has read the sums)
     if (tid < 16) {
-      float M = -INFINITY, total = 0.f;
+      float M = kLowest, total = 0.f;
 #pragma unroll
       for (int v = 0; v < NW; ++v) M = fmaxf(M, sm[v][tid]);
 #pragma unroll
-      for (int v = 0; v < NW; ++v) total = fmaf(sl[v][tid], sm[v][tid] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(sm[v][tid] - M), total);
+      for (int v = 0; v < NW; ++v) total = fmaf(sl[v][tid], __builtin_amdgcn_exp2f(sm[v][tid] - M), total);
       so[0][tid] = (M + log2f(total)) * kLn2;
     }
     __syncthreads();
@@ -541,7 +544,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[ct][i] = 0.f;
-  float m = -INFINITY, l = 0.f;       // the row's running maximum (log2 units) and this half-wave's share of the sum
+  float m = kLowest, l = 0.f;       // the row's running maximum (log2 units) and this half-wave's share of the sum
   KFrag kf;
   v16f s0, s1;
 
@@ -580,7 +583,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
     }
     const float m_new = fmaxf(m, tmax);
     if (__builtin_amdgcn_ballot_w64(m_new > m)) {
-      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
       l *= alpha;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
@@ -590,7 +593,7 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
     }
     uint32_t pw[8];                                  // the weights, two to a word
     float psum = 0.f;
-    const float nm = -m;                             // (finite: key 0 is visible to every row)
+    const float nm = -m;
     if constexpr (!LAST) sn = v16f{};
 #pragma unroll
     for (int kc = 0; kc < T::NKC; ++kc) {
@@ -790,7 +793,7 @@ __global__ __launch_bounds__(256, KS == 4 && D == 128 ? 1 : 2) void k_prefill_at
   for (int ct = 0; ct < CT; ++ct)
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[ct][i] = 0.f;
-  float m = -INFINITY, l = 0.f;       // the row's running maximum (log2 units) and this half-wave's share of the sum
+  float m = kLowest, l = 0.f;       // the row's running maximum (log2 units) and this half-wave's share of the sum
   KFrag kf;
   v16f s0, s1;
 
@@ -834,7 +837,7 @@ __global__ __launch_bounds__(256, KS == 4 && D == 128 ? 1 : 2) void k_prefill_at
     }
     const float m_new = fmaxf(m, tmax);
     if (__builtin_amdgcn_ballot_w64(m_new > m)) {
-      const float alpha = (m == -INFINITY) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
       l *= alpha;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
@@ -844,7 +847,7 @@ __global__ __launch_bounds__(256, KS == 4 && D == 128 ? 1 : 2) void k_prefill_at
     }
     uint32_t pw[8];                                  // the weights, two to a word
     float psum = 0.f;
-    const float nm = m == -INFINITY ? 0.f : -m;      // (a wave whose logits are all -inf so far: its weights are 0)
+    const float nm = -m;
     if constexpr (!LAST) sn = v16f{};
 #pragma unroll
     for (int kc = 0; kc < T::NKC; ++kc) {
@@ -907,7 +910,7 @@ __global__ __launch_bounds__(256, KS == 4 && D == 128 ? 1 : 2) void k_prefill_at
   for (; t < ntiles; ++t) top(t);                    // the other waves' tiles: their transfers and barriers
 
   // ---- join the waves of a row: all outputs to LDS, each wave finishes an equal part of the channels ----
-  // (a wave without keys has m = -inf, l = 0 and zeros; the first wave has key 0)
+  // (a wave without keys has m = kLowest, l = 0 and zeros; the first wave has key 0)
   constexpr int PART = CT * 4 / KS;                  // groups of four channels of a lane
   float4* stage = reinterpret_cast<float4*>(tiles);
   const float l_wave = l + __shfl_xor(l, 32);
@@ -921,12 +924,12 @@ __global__ __launch_bounds__(256, KS == 4 && D == 128 ? 1 : 2) void k_prefill_at
   sum[w][1][lane] = l_wave;
   __syncthreads();
   const int w0 = w - kg;                             // the row's waves: w0 .. w0 + KS - 1
-  float M = -INFINITY, l_tot = 0.f, f[KS];
+  float M = kLowest, l_tot = 0.f, f[KS];
 #pragma unroll
   for (int v = 0; v < KS; ++v) { f[v] = sum[w0 + v][0][lane]; M = fmaxf(M, f[v]); }
 #pragma unroll
   for (int v = 0; v < KS; ++v) {
-    f[v] = f[v] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(f[v] - M);
+    f[v] = __builtin_amdgcn_exp2f(f[v] - M);
     l_tot = fmaf(sum[w0 + v][1][lane], f[v], l_tot);
   }
   if (qpos < a.L) {

@@ -207,3 +207,31 @@ def test_rows_whose_keys_waves_share(case, dtype):
             bound = (1.01 * u + 2.0 ** -17) * (size + want.abs()) + low * v.abs().sum(0)
             assert bool(((out[b, h].double() - want).abs() <= bound).all()), (b, h)
             assert (lse[b, h].double() - torch.logsumexp(x, -1)).abs().max().item() <= 1e-4
+
+
+# The first 40 keys of every row, more than its first block, have logits of -inf: a reference that starts there is still finite.  One case
+# for each kernel: fp32 by 16 rows, by 32 rows of four, two and one wave, 16-bit types by four, two and one wave a row and by 256 rows
+NO_LOGITS = [(1, 8, 64, 100, torch.float32), (1, 24, 64, 700, torch.float32), (4, 32, 64, 800, torch.float32), (5, 32, 128, 870, torch.float32),
+             (1, 8, 64, 300, torch.bfloat16), (1, 16, 128, 1500, torch.float16), (4, 32, 128, 1500, torch.bfloat16), (8, 32, 64, 700, torch.float16),
+             (1, 8, 128, 16384, torch.float16)]
+
+
+@pytest.mark.parametrize("case", NO_LOGITS)
+def test_rows_whose_first_logits_are_minus_infinity(case):
+    B, H, d, L, dtype = case
+    g = torch.Generator(device=DEV).manual_seed(L)
+    Q, K, V = (torch.randn(B, H, L, d, generator=g, device=DEV).to(dtype) for _ in range(3))
+    Q[..., 1] = 1.0
+    K[:, :, :40, 1] = -float("inf")
+    out, lse, _ = zb.zc_prefill_attention(Q, K, V)
+    rows = torch.tensor([40, 41, 63, 64, 95, 96, L // 2, L - 1], device=DEV)
+    hidden = torch.arange(L, device=DEV)[None] > rows[:, None]
+    u = {torch.float32: 2.0 ** -20, torch.bfloat16: 2.0 ** -8, torch.float16: 2.0 ** -10}[dtype]
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        x = (Q[b, h, rows].double() @ K[b, h].double().T / d ** 0.5).masked_fill(hidden, -float("inf"))
+        v = V[b, h].double()
+        p = torch.softmax(x, -1)
+        # (the weights and the result are rounded to the type; fp32: a logit's and the weights' sums, 2^-20 of their size)
+        assert bool(((out[b, h, rows].double() - p @ v).abs() <= 2 * u * (p @ v.abs()) + 1e-6).all()), (b, h)
+        assert (lse[b, h, rows].double() - torch.logsumexp(x, -1)).abs().max().item() <= 1e-4
+    assert bool(out[:, :, 40:].isfinite().all()) and bool(lse[:, :, 40:].isfinite().all())
