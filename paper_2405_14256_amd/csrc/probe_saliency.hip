@@ -60,6 +60,7 @@ struct ProbeArgs {
   // the waves of sweep 1 / sweep 2 are kept at about the same number of tiles to go from so many tiles / probe rows before
   // their ends on (0: not at all)
   int even1, even2;
+  int whole1;            // sweep 1: whole tiles go past the general case
   int group;             // sweep 2: query heads whose columns an XCD takes from the first on together (0: a head after the other)
   int few_cols;          // few probe rows, sweep 2 and the mean in one launch: of so many times 16 columns a workgroup (0: not)
   int few_blocks;        // of so many blocks of 16 probe rows a wave
@@ -193,8 +194,9 @@ __device__ inline LseShare lse_share(const ProbeArgs& a, int nrb, int j) {
   return s;
 }
 
-// Four workgroups to a CU (128 registers, 35 KB of LDS) for rows of up to 256 bytes.
-template <int DT, int D>
+// Four workgroups to a CU (128 registers, 35 KB of LDS) for rows of up to 256 bytes.  WHOLE: tiles that every row of a wave sees go
+// past the general case (whole_tiles).
+template <int DT, int D, bool WHOLE>
 __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_probe_lse(ProbeArgs a) {
   using T = Tile<DT, D>;
   constexpr int TILE_B = kLseCols * T::ROWB;
@@ -320,7 +322,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
     // Every row has its reference and sees every column: nothing but the terms (what the general case asks of every block
     // was 22 of a wave-tile's 151 vector instructions: all rows of 32 heads of 128 channels, 32768 tokens, 3276 probes,
     // both sweeps 1271 -> 1216 us).
-    if (ready && colb + 31 <= pfirst[0]) {
+    if (WHOLE && ready && colb + 31 <= pfirst[0]) {
       float sum[2] = {0.f, 0.f};
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb) {
@@ -386,7 +388,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 2 : 4) void k_pro
         set = true;
       }
     }
-    if (!ready) ready = __builtin_amdgcn_ballot_w64(m[0] == -INFINITY || (both && m[1] == -INFINITY)) == 0;
+    if (WHOLE && !ready) ready = __builtin_amdgcn_ballot_w64(m[0] == -INFINITY || (both && m[1] == -INFINITY)) == 0;
   }
   // merge the two half-waves, then the two column halves
   const int t1 = opaque(tid), r1 = t1 & 31;
@@ -903,7 +905,9 @@ __global__ __launch_bounds__(1024) void k_probe_few(ProbeArgs a, float* __restri
 template <int DT, int D>
 static int launch_probe(const ProbeArgs& a, bool need_lse, float* scores, hipStream_t st) {
   if (need_lse) {
-    hipLaunchKernelGGL((k_probe_lse<DT, D>), dim3((unsigned)((int64_t)a.head_wgs * a.Hq * a.B)), dim3(256), 0, st, a);
+    const dim3 grid1((unsigned)((int64_t)a.head_wgs * a.Hq * a.B));
+    if (a.whole1) hipLaunchKernelGGL((k_probe_lse<DT, D, true>), grid1, dim3(256), 0, st, a);
+    else hipLaunchKernelGGL((k_probe_lse<DT, D, false>), grid1, dim3(256), 0, st, a);
     ZC_LAUNCH_CHECK();
     if (a.head_wgs > ceil_div(a.P, kLseRows) && !a.join) {
       const int64_t rows = (int64_t)a.B * a.Hq * a.P;
@@ -975,6 +979,17 @@ static int64_t probe_head_wgs(int64_t B, int64_t Hq, int64_t P, int64_t Lk, int 
 static bool even_waves(int64_t wgs, double tiles, const zc_tensor4* q) {
   const int64_t places = q->dtype == ZC_F32 && q->D == 128 ? 512 : 1024;
   return wgs > 256 && wgs <= places && tiles >= 4.0;
+}
+// Whether sweep 1 has the way past the general case for whole tiles.  Where workgroups run once it is mostly more cold code: the
+// rows are spread over the columns, and the start and the tiles seen in part are what a wave does.  us, general case alone and both: 24 heads over 8 of
+// 128 channels, 228 tokens, 22 probes 12.9 and 13.4; 40 heads, 2715 and 272 30.7 and 31.3; 24 over 8, 6000 and 600 (1008 workgroups) 52.5 and 53.7; 8
+// heads of 64, 3300 and 330 (384) 19.3 and 19.8; 16 x 40 heads, 1500 and 150 (1280) 133.5 and 136.6; 16 x 24 of 128, fp32, 2000 and 200 710.5 and 711.8.  It pays in more
+// rounds of rows that see 32 tiles and more, and of a few heads' long row blocks on a chip that is not full: 12 x 32 over 8, 2400 and 240 (1536) 140.2 and
+// 135.9; 40 heads, 9276 and 928 (1280) 178.5 and 167.3; 32 over 8, 32768 and 3276 1278 and 1225; 8 of 64, 4300 and 430 21.1 and 21.6, 5600 and 560 26.8 and 25.9, 7000 and
+// 700 30.2 and 28.2; 12 of 64, 4300 24.45 and 24.5, 5000 26.8 and 26.3; 32 over 8, fp32, 2500 and 250 100.2 and 100.7, 4096 and 410 221.7 and 220.9, 6000 and 600 425.5 and 418.9.
+static bool whole_tiles(int64_t wgs, int64_t head_wgs, int64_t nrb, int64_t tiles, const zc_tensor4* q) {
+  if (q->dtype == ZC_F32) return nrb >= 4 && wgs > (q->D == 128 ? 512 : 1024);
+  return wgs > 1024 ? tiles >= 32 : nrb >= 4 && wgs <= 960 && 10 * nrb * tiles >= 44 * head_wgs;
 }
 // Whether few probe rows are served by one launch (k_probe_few), with how many times 16 columns a workgroup and blocks of 16 rows a
 // wave, by what the ways cost in us.  One launch: the trips of its start, those of a wave's further blocks, and, a round of
@@ -1083,6 +1098,7 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
     return ZC_ERR_UNSUPPORTED;
   const int64_t wgs1 = head_wgs * q->H * q->B, wgs2 = ceil_div64(k->L, 128) * q->H * q->B;
   a.even1 = wgs1 >= 768 && even_waves(wgs1, (double)(ceil_div64(P, kLseRows) * ceil_div64(k->L, kLseCols)) / (double)head_wgs, q) ? kEvenTiles : 0;
+  a.whole1 = whole_tiles(wgs1, head_wgs, ceil_div64(P, kLseRows), ceil_div64(k->L, kLseCols), q) ? 1 : 0;
   a.even2 = even_waves(wgs2, P / 64.0, q) ? kEvenTiles * 64 : 0;
   {
     const int64_t nct = ceil_div64(k->L, 128), heads = q->B * q->H, hpx = heads / 8, least = ceil_div64(256, nct), groups = hpx / least;
