@@ -999,8 +999,11 @@ static bool whole_tiles(int64_t wgs, int64_t head_wgs, int64_t nrb, int64_t tile
 // rows 5.8 / 3.7 and 5.9 / 3.7; 16 heads over 4, 300 tokens, 30 rows 5.9 / 5.6 and 5.9 / 5.7; 32 heads over 8 of 128 channels, 100 tokens
 // 6.2 / 7.4 and 6.2 / 7.9; 16 x 32 over 8, 1000 tokens 22.5 / 18.4 (32 columns) and 21.9 / 18.9; fp32, 12 heads of 64,
 // 256 tokens, 26 rows 7.9 / 7.5 and 8.1 / 7.8; 16 of 128, 100 tokens 10.0 / 8.9 and 10 / 8.5; 24 over 8, 64 tokens, 7 rows 9.9 / 10.3 and 10 / 10.2.
+// Where sweep 1 leaves ranges, the two launches join them on the way and the one needs a launch for that first, 1.8 us more
+// (`ranges`; both sweeps, two and one: 2 x 16 heads over 4 of 64, 281 tokens, 28 rows, fp16 10.8 and 11.9; 2 x 16 of 128, 120 and 12, fp32 17.3 and 18.3;
+// 4 x 16 over 4 of 64, 167 and 16, fp32 13.8 and 14.1; but 3 x 12 of 64, 105 and 10, fp32 14.1 and 12.7).
 struct FewPlan { int cols, blocks; };
-static FewPlan probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P, int64_t D, bool fp32) {
+static FewPlan probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t P, int64_t D, bool fp32, bool ranges) {
   FewPlan plan = {0, 0};
   if (P > kFewRows || Hq * P > kFewTable) return plan;
   const int64_t row_bytes = D * (fp32 ? 4 : 2), rt = ceil_div64(P, 16);
@@ -1018,7 +1021,7 @@ static FewPlan probe_few(int64_t B, int64_t Hq, int64_t Hkv, int64_t Lk, int64_t
       const int64_t blocks = ceil_div64(Hq * rt, 16 * share) * share, waves = ceil_div64(Hq * rt, blocks), segments = Hkv > waves ? Hkv : waves;
       const int64_t n = B * ceil_div64(Lk, 16 * nc), rounds = ceil_div64(n, 256);
       const double rate = rounds == 1 ? 37.0 : fp32 ? 22.0 : 28.0;
-      const double t = 3.0 + further * (double)(blocks - 1) + (double)(rounds * (segments * 16 * nc + Hq * P) * row_bytes) / (1e3 * rate);
+      const double t = (ranges ? 4.8 : 3.0) + further * (double)(blocks - 1) + (double)(rounds * (segments * 16 * nc + Hq * P) * row_bytes) / (1e3 * rate);
       if (t < best) { best = t; plan = {(int)nc, (int)blocks}; }
     }
   return plan;
@@ -1080,10 +1083,12 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
   a.probe_rows = probe_rows; a.probe_pos = probe_pos;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse_in = lse_ext;
-  const FewPlan few = probe_few(q->B, q->H, k->H, k->L, P, q->D, q->dtype == ZC_F32);
+  a.join = !lse_ext && probe_join(q->B, q->H, k->L, P) && ws_bytes >= need + extra;
+  const bool ranges = a.join && probe_head_wgs(q->B, q->H, P, k->L, extra > 0 ? kMaxProbeParts : kProbeParts, q->dtype == ZC_F32) > ceil_div64(P, kLseRows);
+  const FewPlan few = probe_few(q->B, q->H, k->H, k->L, P, q->D, q->dtype == ZC_F32, ranges);
   a.few_cols = few.cols;
   a.few_blocks = few.blocks;
-  a.join = !lse_ext && !a.few_cols && probe_join(q->B, q->H, k->L, P) && ws_bytes >= need + extra;
+  if (a.few_cols) a.join = 0;
   float* ws_ph = reinterpret_cast<float*>(reinterpret_cast<uint8_t*>(ws) + lse_bytes(q->B, q->H, P) + (a.join ? extra : 0));
   // [log-sum-exps][column ranges' pairs, up to the end of the workspace: the per-head scores, at
   // their place in it, are written when the pairs have been read]; joined by sweep 2 [pairs][per-head scores]
