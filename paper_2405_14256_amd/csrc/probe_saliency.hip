@@ -813,8 +813,12 @@ __global__ __launch_bounds__(1024) void k_probe_few(ProbeArgs a, float* __restri
 #pragma unroll
   for (int c = 0; c < NC; ++c) sum[c] = head[c] = 0.f;
   const int head_col = col0 + 16 * (g % NC) + i;     // per-head scores: the column that a lane of the first NC blocks stores
-  const int seen_by = !PER_HEAD ? 0 : a.normalize ? a.P - lower_bound_pos(spos, a.P, head_col) : 1;
+  // (looked up at every store where a register more would spill, 32 columns of 128 fp32 channels: 8 x 32 heads over 8, 1000 tokens, 10 rows 23.1 -> 21.5 us)
+  constexpr bool TIGHT = NK * (NC + 1) >= 24;
+  const auto seen = [&]() { return a.normalize ? a.P - lower_bound_pos(spos, a.P, head_col) : 1; };
+  const int seen_once = PER_HEAD && !TIGHT ? seen() : 0;
   auto store_head = [&](int h, const float (&total)[NC]) {
+    const int seen_by = TIGHT ? seen() : seen_once;
     const float t = total[g % NC == NC - 1 ? NC - 1 : 0];
     if (g < NC && head_col < a.Lk) a.per_head[((int64_t)b * a.Hq + h) * a.Lk + head_col] = seen_by > 0 ? t / (float)seen_by : 0.f;
   };
