@@ -1611,14 +1611,20 @@ static int launch_pack_kv(const QPPair& p, bool keys, bool values, int dtype, hi
   return ZC_OK;
 }
 
-// Whether a call's tensors are short enough for k_short_kv, and its shape.  The line lies where reading the longer subset once a
-// workgroup costs as much as the launch.  us as two launches and as one, one prompt and 16, bf16: 8 heads of 128
-// channels, 70 tokens in it (143 KB) 8.4 / 11.6 and 7.4 / 10.0, 90 (184 KB) 8.5 / 11.7 and 7.9 / 11.4, 105 (215 KB) 8.4 / 12.6 and 8.5 / 14.0;
-// 16 heads, 45 tokens (184 KB) 9.4 / 13.1 and 8.6 / 13.3; fp32: 8 heads of 64, 70 tokens (143 KB) 8.2 / 9.7 and 7.4 / 7.7;
-// 8 heads of 128, 45 (184 KB) 8.4 / 10.9 and 7.7 / 9.3; 12 heads of 64, 70 (215 KB) 8.3 / 11.1 and 8.7 / 11.6, and, with 58 rows a
-// thread (178 KB), 8.2 and 8.3: no more than 48.
-// Keys alone are one launch either way: few rows a thread, or workgroups enough (k_columns starts more): 45 tokens
-// 4.9 and 4.3 us, 70 the same, 84 4.9 and 5.2 (16 prompts of 16 heads 7.7 and 6.2).
+// Whether a call's tensors are short enough for k_short_kv, and its shape.  Of one prompt the line lies where reading the longer
+// subset once a workgroup costs as much as the launch.  us as two launches and as one, bf16: 8 heads of 128
+// channels, 70 tokens in it (143 KB) 8.4 and 7.4, 90 (184 KB) 8.5 and 7.9, 105 (215 KB) 8.4 and 8.5; fp32, 12 heads of 64, 70 (215 KB) 8.3 and 8.7, and,
+// with 58 rows a thread (178 KB), 8.2 and 8.3: no more than 48.
+// Of many prompts it lies in what all workgroups of values read together: the two launches read every byte twice, here it comes out of an L2
+// once for each word group of its subset (divided by the teams).  That costs nothing up to some 26 MB of values alone and 36 of
+// both tensors; beyond, up to as many readings of a byte as the second launch and its start are worth.  us as two launches and as one, both
+// tensors: 8 heads of 128 channels, bf16, 45 tokens in each subset, 16 and 128 prompts (18 and 142 MB, 6 readings) 9.6 and 7.4, 33.8 and 31.7; 90, 16 prompts
+// (59 MB, 10) 12.7 and 16.3; 4 heads, fp16, 90 and 22, 64 (26 MB, 3.6) 19.5 and 11.6; fp32, 8 heads, 45 each, 64 (94 MB, 8) 22.4 and 32.3; 15 each, 256 (126 MB, 4) 45.7 and
+// 38.2; 11 and 45, 256 (4) 54.3 and 74.0; values alone: 8 heads, bf16, 90 each, 256 prompts (943 MB, 10) 57.4 and 120; 4 heads of 64, 120 and 30, 256 (35 MB, 1.8) 19.1 and 11.9; 8 heads of
+// 64, fp32, 60 each, 256 (94 MB, 3) 28.3 and 37.8.  Joint calls of more than 1024 channels gain nothing from half a workgroup a CU on: 16 heads of 128, 30 and 7, 32 prompts 17.1 and 19.1.
+// Keys alone are one launch either way (k_columns starts more workgroups, and in fp32 holds more in flight): bf16, 4 heads of 64, 60 tokens, one prompt
+// 1.05 times faster here, 120 tokens of 64 prompts (256 workgroups) 1.06 slower, of 256 prompts 1.26 faster; fp32, 30 tokens 1.05 faster, 60 1.13
+// slower, 30 of 256 prompts (1024) 1.11 slower.
 constexpr int64_t kShortBytes = 180 * 1024, kShortReads = 48;
 static bool short_plan(const QPPair& p, const zc_packed* const* out, int tensors, int dtype, ShortPlan& s) {
   const QPArgs& a = p.t[0];
@@ -1628,7 +1634,11 @@ static bool short_plan(const QPPair& p, const zc_packed* const* out, int tensors
   const int64_t n = a.n[0] > a.n[1] ? a.n[0] : a.n[1], row_bytes = (int64_t)a.W * (dtype == ZC_F32 ? 4 : 2);
   s.key_wgs = keys ? (int)ceil_div64(a.NV, kShortLanes) : 0;
   if (n > kShortTokens) return false;
-  if (values ? n * row_bytes > kShortBytes : n > 72 && 2 * s.key_wgs * (int64_t)a.B < 128) return false;
+  if (values && n * row_bytes > kShortBytes) return false;
+  if (!values) {
+    const int64_t wgs = 2 * s.key_wgs * (int64_t)a.B;
+    if (dtype == ZC_F32 ? n > 32 || wgs > 512 : n > 60 && wgs < (n > 96 ? 384 : n > 72 ? 256 : 128)) return false;
+  }
   s.team = values ? (int)align_up64(a.W / kPackCpt, 64) : 256;
   s.teams = s.team <= 64 ? 4 : s.team <= 128 ? 2 : 1;
   s.lanes = (int)(row_bytes / 16);
@@ -1637,6 +1647,12 @@ static bool short_plan(const QPPair& p, const zc_packed* const* out, int tensors
   for (int sub = 0; sub < 2; ++sub) {
     const int wgs = (int)ceil_div64(a.units[sub], s.teams);
     s.value_wgs[sub] = !values ? 0 : wgs > 0 ? wgs : 1;                // (an empty subset's parameters are written too)
+  }
+  if (values) {
+    const int64_t row = row_bytes * a.B, read = row * ((int64_t)s.value_wgs[0] * a.n[0] + (int64_t)s.value_wgs[1] * a.n[1]), all = row * (a.n[0] + a.n[1]);
+    const int64_t again = keys ? (dtype == ZC_F32 ? 11 : 22) : 9;      // readings of a byte, in quarters
+    if (read > (keys ? 36 : 26) * 1000000 && 4 * read > again * all) return false;
+    if (keys && a.W > 1024 && (s.value_wgs[0] + s.value_wgs[1]) * (int64_t)a.B >= 128) return false;
   }
   return true;
 }

@@ -112,6 +112,34 @@ def test_short_subsets_as_beside_long_ones(H, D, dtype, k, bits, special):
             assert o.chunk_table.flatten()[:4].tolist() == [0, k, 0, 0] and o.chunks == [(0, k, 0, 0)]
 
 
+@pytest.mark.parametrize("B,H,D,k,n,dtype", [
+    (40, 8, 128, 90, 90, torch.bfloat16), (12, 8, 64, 90, 90, torch.float32), (130, 4, 64, 60, 60, torch.float32),      # past what workgroups may read
+    (64, 4, 128, 22, 90, torch.float16), (64, 8, 128, 11, 45, torch.bfloat16),                                          # past it, of few readings a byte
+    (31, 16, 128, 7, 30, torch.bfloat16), (33, 16, 128, 7, 30, torch.bfloat16),                                         # either side of half a workgroup a CU
+    (64, 4, 64, 97, 97, torch.float16), (96, 4, 64, 97, 97, torch.float16), (129, 4, 64, 32, 32, torch.float32),        # keys alone: 256 and 384 workgroups, 516
+])
+def test_short_subsets_of_many_prompts(B, H, D, k, n, dtype):
+    """Short subsets of a batch, which take the one launch or two by what its workgroups would read together, and each
+    prompt in a call of its own: the same bits, in joint and single calls."""
+    g = torch.Generator(device=DEV).manual_seed(B + n)
+    X, Y = ((3 * torch.randn(B, H, k + n, D, generator=g, device=DEV)).to(dtype) for _ in range(2))
+    sal, reg = zb.zc_select_salient(torch.rand(B, k + n, generator=g, device=DEV), k)
+    forms = [("channel", zb.ZC_LAYOUT_ROW), ("cst", zb.ZC_LAYOUT_TGROUP)]
+    joint, single = ([_packed(f, B, H, D, k, n, (4, 2)) for f in forms] for _ in range(2))
+    zb.zc_quantize_pack_kv(X, Y, sal, reg, *joint, pos_offset=7)
+    for x, p in zip((X, Y), single):
+        zb.zc_quantize_pack(x, sal, reg, p, pos_offset=7)
+    for b in (0, B // 2, B - 1):
+        one = [_packed(f, 1, H, D, k, n, (4, 2)) for f in forms]
+        zb.zc_quantize_pack_kv(X[b:b + 1], Y[b:b + 1], sal[b:b + 1], reg[b:b + 1], *one, pos_offset=7)
+        for which, want in enumerate(one):
+            for p in (joint[which], single[which]):
+                for name in ARRAYS[:-1]:
+                    a, w = getattr(p, name), getattr(want, name)
+                    a = a.view(2, B, H * D)[:, b] if name.startswith("chan") else a.view(B, -1)[b]
+                    assert torch.equal(a.flatten(), w.flatten()), (which, b, name)
+
+
 @pytest.mark.parametrize("n", [20, 131])
 @pytest.mark.parametrize("dtype", [torch.float16, torch.float32])
 def test_channel_parameters_at_any_float(dtype, n):
