@@ -124,7 +124,7 @@ __device__ inline uint16_t mul_to_half(float s, float x) {
 
 // Slots of a segment, TILES tiles at a time; of two, the second one's results are in the odd lanes of a column pair, which the first
 // one leaves idle once value and residual are added up.
-template <int DT, int D, int BITS, bool TOK, int TILES>
+template <int DT, int D, int BITS, bool TOK, int TILES, bool LOOP>
 __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chunk, int sub, int begin, int len, int unit0, int nunits) {
   constexpr int NK = D / 4, KS = D / 32;              // channels per lane and tile; matrix instructions per tile
   constexpr int NW = NK * BITS / 32, ROWB = D * BITS / 8, UNIT = TILES * kProbTile;
@@ -224,7 +224,7 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
   float* out = a.probs + hq * a.N;
   const bool store = nvalid && (TILES == 2 || part == 0);
 
-  for (int i = 0; i < (TILES == 1 ? 1 : a.tpw); ++i) {
+  for (int i = 0; i < (LOOP ? a.tpw : 1); ++i) {
     const int unit = unit0 + 4 * i;
     if (unit >= nunits) break;
     uint32_t r[TILES][NK / 2];
@@ -236,7 +236,7 @@ __device__ inline void probs_segment(const ProbsArgs& a, int b, int hk, int chun
       ts[0] = in.ts.x; ts[1] = in.ts.y; ts[2] = in.ts.z; ts[3] = in.ts.w;
       tz[0] = in.tz.x; tz[1] = in.tz.y; tz[2] = in.tz.z; tz[3] = in.tz.w;
     }
-    if constexpr (TILES == 2) load(min(unit + 4, nunits - 1), in);      // the next unit's inputs are in flight meanwhile (no branch: it would copy them)
+    if constexpr (LOOP) load(min(unit + 4, nunits - 1), in);      // the next unit's inputs are in flight meanwhile (no branch: it would copy them)
     f4 acc[TILES];
 #pragma unroll
     for (int t = 0; t < TILES; ++t) acc[t] = f4{0.f, 0.f, 0.f, 0.f};
@@ -294,7 +294,7 @@ __device__ inline void probs_tail(const ProbsArgs& a, int b, int hk, int len, in
 }
 
 // grid (workgroups of all segments, Hkv, B); a wave takes a.tpw units of its segment (a.tail_tpw tiles of the tail).  TOK: keys with token parameters.
-template <int DT, int D, bool TOK, int TILES>
+template <int DT, int D, bool TOK, int TILES, bool LOOP>
 __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
   const int hk = blockIdx.y, b = blockIdx.z;
   const int wave = threadIdx.x >> 6;
@@ -309,9 +309,9 @@ __global__ __launch_bounds__(256) void k_decode_probs(ProbsArgs a) {
   const int bits = is_tail ? 0 : sub ? a.bits[1] : a.bits[0];
   if (first >= count) return;
   if (is_tail) probs_tail<DT, D>(a, b, hk, len, first, count);
-  else if (bits == 4) probs_segment<DT, D, 4, TOK, TILES>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
-  else if (bits == 2) probs_segment<DT, D, 2, TOK, TILES>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
-  else probs_segment<DT, D, 8, TOK, TILES>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
+  else if (bits == 4) probs_segment<DT, D, 4, TOK, TILES, LOOP>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
+  else if (bits == 2) probs_segment<DT, D, 2, TOK, TILES, LOOP>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
+  else probs_segment<DT, D, 8, TOK, TILES, LOOP>(a, b, hk, a.seg[si].chunk, sub, begin, len, first, count);
 }
 
 // scores[b, i] = mean_h ( sum_{j : row_len[j] > i} rows[j, b, h, i] ) / #{j : row_len[j] > i}
@@ -596,6 +596,56 @@ __global__ __launch_bounds__(kDqThreads) void k_dequantize_cache(DequantArgs a) 
 
 using namespace zc;
 
+// Workgroups a head in the grid: a multiple of eight, or four, gives every XCD the same segments of all heads - the long ones, or
+// the tail's - and one workgroup more without work deals them out; where workgroups are few it only costs (4 a head, 520 to 1500 workgroups: 1.11
+// times faster, up to 520 0.99; multiples of eight, from 1500 on 1.03, up to 1500 0.99).
+static int64_t probs_grid(int64_t blocks, int64_t heads) {
+  const int64_t n = blocks * heads;
+  return blocks + ((blocks == 4 && n > 520) || (blocks % 8 == 0 && n > 1500) ? 1 : 0);
+}
+// Tiles of the packed segments: one at a time, one a wave, while no CU gets a second workgroup (latency); else two at a time
+// (a unit), `tpw` units a wave.  us, one tile and one unit: 8 heads of 2530 tokens (250 and 130 workgroups) 4.5 and 4.7; 16 heads of 1383 (368) 5.5 and 4.65.
+struct ProbsShape { bool pairs; int tpw; };
+// What units a wave cost: the start of a wave (the query operand; a unit is 0.3 of it for 128 channels and 0.4 for 64, in fp32 it is 1.2)
+// and its units, times what the workgroups of the fullest CU take: three (128 channels) or four go at a time, a lone one at 0.55 of that, and of
+// further ones the last count half, as they start when others end.  Grids that give XCDs the same segments pay 8 %.
+// Of 2500 drawn calls timed in all ten shapes the one of least cost is 0.7 % slower than the best in the geometric mean; all are 1.20 times faster than by a tile at
+// a time with up to eight a wave.  us, one tile and 1, 2, 3, 4, 6, 9 units a wave:
+// 9 x 8 heads of 22847 tokens, bits 8 and 4, fp16 105, 69, 52, 46, 43, 57 (2.3 rounds of 4), 43; 13 x 40 of 1552 54, 37, 32, 28, 26, 32, 25; 5 x 40 of 347
+// 10.3, 8.9, 10.0 (4 workgroups a head), 7.8, 7.8; 2 x 8 of 1383 5.5, 4.65, 5.9, 6.6, 7.0.
+static double probs_cost(int64_t blocks, int64_t heads, int64_t units, const zc_tensor4* q) {
+  const int64_t grid = probs_grid(blocks, heads), wgs = grid * heads;
+  const double places = q->D == 128 ? 3.0 : 4.0, x = (double)wgs / 256.0, n = (double)ceil_div64(wgs, 256);
+  const double f = n <= 1.0 ? 0.55 : n <= places ? 0.35 + 0.65 * n / places : 0.5 * (x + n) / places > 1.0 ? 0.5 * (x + n) / places : 1.0;
+  return f * ((q->dtype == ZC_F32 ? 1.2 : 1.0) + (q->D == 128 ? 0.3 : 0.4) * (double)units) * (grid % 8 == 0 || grid == 4 ? 1.08 : 1.0);
+}
+static ProbsShape probs_shape(const zc_packed* Kp, int64_t heads, int64_t tail_wgs, const zc_tensor4* q) {
+  constexpr int kLong = 64;
+  int64_t longs[kLong], one = tail_wgs, rest = tail_wgs, longest = 0;      // workgroups by single tiles; the tail's and those of segments of up to four units
+  int n_longs = 0;
+  for (int ci = 0; ci < Kp->n_chunks; ++ci)
+    for (int sb = 0; sb < 2; ++sb) {
+      const int64_t len = Kp->chunk_table_host[4 * ci + 2 * sb + 1], units = ceil_div64(len, 2 * kProbTile);
+      if (len <= 0) continue;
+      one += ceil_div64(len, 4 * kProbTile);
+      if (units > longest) longest = units;
+      if (units <= 4) ++rest;
+      else if (n_longs < kLong) longs[n_longs++] = units;
+      else longs[kLong - 1] += units;                        // (a price, not the grid)
+    }
+  if (one * heads <= 256) return {false, 1};
+  ProbsShape best = {true, 1};
+  double least = 0.0;
+  for (int tpw = 1; tpw <= 9; ++tpw) {
+    int64_t blocks = rest;
+    for (int i = 0; i < n_longs; ++i) blocks += ceil_div64(longs[i], 4 * tpw);
+    const double cost = probs_cost(blocks, heads, tpw, q);
+    if (tpw == 1 || cost < least) { least = cost; best.tpw = tpw; }
+    if (blocks * heads <= 256 || 4 * tpw >= longest) break;    // (more a wave leaves no fewer to wait for)
+  }
+  return best;
+}
+
 extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const zc_tensor4* tail_k, int64_t tail_len,
                                int64_t tail_pos0, float sm_scale, const float* lse, float* probs_out, int64_t N,
                                void* stream) {
@@ -637,45 +687,21 @@ extern "C" int zc_decode_probs(const zc_tensor4* q, const zc_packed* Kp, const z
   a.tail_pos0 = (int)tail_pos0;
   a.scale_log2 = (sm_scale == 0.f ? 1.0f / sqrtf((float)q->D) : sm_scale) * kLog2e;
   a.lse = lse; a.probs = probs_out; a.N = (int)N;
-  int unit = kProbTile;
-  // A tile a wave while every SIMD has a wave at most (latency); else two at a time, one unit a wave while the launch is below two
-  // waves a SIMD, up to six when the chip is full anyway and a wave's start (the query operand) would weigh as much as its
-  // units.  us by one and by two tiles at a time: 784 packed tiles (700 tokens of 16 KV heads of 128 channels) 4.3 and 4.5, 928 (928 of 16)
-  // 5.7 and 4.8, 1100 (1400 of 12 heads of 64) 4.2 and 3.8, 2100 (4096 of 8) 6.5 and 5.9; up to 1400 not of 8-bit codes (930: 3720 of 4 heads,
-  // 4.8 and 5.35) nor of segments so short that little less than the same workgroups are left (1360: 5 x 16 heads of 256, 5.6 and 6.1); 16 x 40 heads of 2000 tokens by up to 2, 4, 6
-  // and 8 units a wave 46.0, 38.9, 36.2 and 44.9.
-  // One unit more a wave where that spares a fifth of the workgroups or the second round: of several rounds, a workgroup of a unit or two
-  // costs about what a full one does (one to two units: 8 heads of 13990 tokens 9.65 and 8.0; four to five: 3 x 8 of 11239 13.0 and 11.6;
-  // 8 x 40 heads of 660 tokens and 94 of the tail, fp32, four and three workgroups a head 39.5 and 36.9, with its decode; 4 x 8 heads of 4006 tokens, 1056 workgroups of one unit 11.2, 10.4 when they fit a round).  The tail's tiles go one at a
-  // time, up to eight a wave (16 x 40 heads of 70 tokens and 78, one and three a wave 45.6 and 32.0, with its decode).
-  {
-    const int64_t heads = (int64_t)a.Hkv * a.B, all = tiles * heads, packed = (tiles - ceil_div64(tail_len, kProbTile)) * heads;
-    const int64_t round = q->dtype == ZC_F32 && q->D == 128 ? 768 : 1024;      // (three or four workgroups a CU, by registers)
-    const auto bounded = [](int64_t t, int64_t most) { return (int)(t < 1 ? 1 : t > most ? most : t); };
-    a.tail_tpw = bounded(all / 2048, 8);
-    const auto workgroups = [&](int slots, int tpw) {       // of the packed segments of a head
-      int64_t n = 0;
-      for (int ci = 0; ci < Kp->n_chunks; ++ci)
-        for (int sb = 0; sb < 2; ++sb) n += ceil_div64(ceil_div64(Kp->chunk_table_host[4 * ci + 2 * sb + 1], slots), 4 * tpw);
-      return n;
-    };
-    const int64_t tail_wgs = ceil_div64(ceil_div64(tail_len, kProbTile), 4 * a.tail_tpw);
-    const bool narrow = a.bits[0] <= 4 && a.bits[1] <= 4;
-    if (packed > 1400 || (packed > 860 && narrow && 20 * workgroups(2 * kProbTile, 1) <= 11 * workgroups(kProbTile, 1))) unit = 2 * kProbTile;
-    a.tpw = unit == kProbTile ? 1 : bounded(all / 4096, 6);
-    if (unit > kProbTile && a.tpw < 6) {
-      const int64_t now = workgroups(unit, a.tpw) + tail_wgs, next = workgroups(unit, a.tpw + 1) + tail_wgs;
-      if (((a.tpw >= 2 || now * heads > 640) && 5 * next <= 4 * now) || (now * heads > round && next * heads <= round)) ++a.tpw;
-    }
-  }
+  // The tail's tiles go one at a time, up to eight a wave (16 x 40 heads of 70 tokens and 78, one and three a wave 45.6 and 32.0 us, with its
+  // decode); those of the packed segments one or two at a time, as many a wave as costs least.
+  const int64_t heads = (int64_t)a.Hkv * a.B, all = tiles * heads, tail_tiles = ceil_div64(tail_len, kProbTile);
+  a.tail_tpw = (int)(all < 2 * 2048 ? 1 : all >= 8 * 2048 ? 8 : all / 2048);
+  const ProbsShape shape = probs_shape(Kp, heads, ceil_div64(tail_tiles, 4 * a.tail_tpw), q);
+  const int unit = shape.pairs ? 2 * kProbTile : kProbTile;
+  a.tpw = shape.tpw;
   hipStream_t st = (hipStream_t)stream;
   int64_t blocks = 0;
   a.n_segs = 0;
   auto flush = [&]() -> int {
     if (a.n_segs == 0) return ZC_OK;
-    const dim3 grid((unsigned)blocks, (unsigned)a.Hkv, (unsigned)a.B);
-    const auto launch = [&](auto one, auto two) { hipLaunchKernelGGL(unit == kProbTile ? one : two, grid, dim3(256), 0, st, a); };
-#define ZC_PRD(DT, D, TOK) launch(k_decode_probs<DT, D, TOK, 1>, k_decode_probs<DT, D, TOK, 2>)
+    const dim3 grid((unsigned)probs_grid(blocks, heads), (unsigned)a.Hkv, (unsigned)a.B);
+    const auto launch = [&](auto tile, auto pair, auto pairs) { hipLaunchKernelGGL(unit == kProbTile ? tile : a.tpw == 1 ? pair : pairs, grid, dim3(256), 0, st, a); };
+#define ZC_PRD(DT, D, TOK) launch(k_decode_probs<DT, D, TOK, 1, false>, k_decode_probs<DT, D, TOK, 2, false>, k_decode_probs<DT, D, TOK, 2, true>)
 #define ZC_PR(DT)                                      \
   do {                                                 \
     if (a.k_tok && q->D == 128) ZC_PRD(DT, 128, true); \

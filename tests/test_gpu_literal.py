@@ -381,11 +381,13 @@ def test_decode_probs_tiles_and_code_widths(B, Hq, Hkv, d, dtype, bits, L, T):
         assert bool((row[:, :, n0 + T:] == -1.0).all())
 
 
-# Two tiles at a time (more than 1400 of them): segments that end inside the first and the second tile of a pair, at either's
-# end and one after, head widths, groups and code widths, one and several pairs a wave, a tail longer than the segments with several tiles a wave
+# Two tiles at a time (more workgroups than CUs by single tiles): segments that end inside the first and the second tile of a pair, at either's
+# end and one after, head widths, groups and code widths, one and several pairs a wave, a tail longer than the segments with several tiles a wave,
+# and grids of four and of eight workgroups a head and one without work
 @pytest.mark.parametrize("B,Hq,Hkv,d,dtype,bits,sizes,T", [
     (9, 16, 8, 64, torch.bfloat16, (4, 8), [(40, 160), (17, 31), (15, 33)], 5), (16, 40, 40, 128, torch.float32, (4, 2), [(17, 63)], 78), (8, 64, 8, 128, torch.float16, (8, 4), [(48, 97), (16, 64), (65, 32)], 17),
-    (5, 9, 9, 64, torch.float32, (2, 4), [(511, 1024)], 32), (16, 24, 12, 64, torch.float16, (4, 4), [(1600, 3201), (20, 80)], 0)])
+    (5, 9, 9, 64, torch.float32, (2, 4), [(511, 1024)], 32), (16, 24, 12, 64, torch.float16, (4, 4), [(1600, 3201), (20, 80)], 0),
+    (16, 24, 12, 128, torch.float16, (4, 2), [(500, 900)], 33), (22, 12, 12, 64, torch.bfloat16, (4, 2), [(53, 20), (134, 31), (27, 18)], 95)])
 def test_decode_probs_pairs_of_tiles(B, Hq, Hkv, d, dtype, bits, sizes, T):
     g = torch.Generator().manual_seed(Hq)
     lib = zb.load()
