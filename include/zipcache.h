@@ -200,6 +200,9 @@ int zc_probe_accumulated(const zc_tensor4* q, const zc_tensor4* k,
  * zc_probe_saliency scores the same probe rows in one sweep instead of two.
  * fp32 tensors are multiplied on the fp32 matrix pipes, never rounded to 16 bits; the
  * probabilities of 16-bit tensors enter the second product rounded to the tensors' type.
+ * Where heads and rows leave the chip idle a row's keys are shared by waves and their parts
+ * joined in fp32: the last bits of a row's output and normaliser may depend on how many
+ * heads and rows the call has.  A row has a number for its result whatever its first keys' logits, -inf included, unless all are -inf.
  * Needs no workspace; enqueued on `stream`.
  * Errors: ZC_ERR_INVALID_ARG for mismatching shapes or types, ZC_ERR_UNSUPPORTED for a
  * (batch, head) slab of 4 GiB or more. */

@@ -175,10 +175,14 @@ def test_prefill_long_rows(dtype):
 
 # Waves that share a row's keys, two and four of them: less than a block of 32 keys, a block and one more, a wave without
 # keys, tiles of 64 and of 128 keys whole and one more, rows past the end of a workgroup's second block, several tiles, token-major
-# tensors, more workgroups than places, key blocks in which every logit is -inf (not the first 32, which every row sees of)
+# tensors, more workgroups than places, key blocks in which every logit is -inf.  (The first line's first three and the last line's take one wave a row: either
+# side of where the rule draws its line; 640 heads of up to 64 rows two; (4, 8, 2, 128, 301) to (2, 16, 16, 64, 1201) and the last line but one two, the others four)
 SPLIT = [(1, 3, 1, 64, 31), (2, 4, 4, 64, 33), (1, 8, 2, 128, 64), (3, 4, 1, 128, 65), (1, 5, 5, 64, 97), (1, 8, 8, 64, 128), (2, 8, 4, 128, 129),
          (1, 8, 2, 64, 257), (1, 16, 4, 64, 700), (1, 2, 1, 128, 1500), (4, 8, 2, 128, 301), (2, 24, 8, 128, 481), (1, 32, 8, 128, 840),
-         (2, 16, 16, 64, 1201), (1, 8, 8, 64, 3003)]
+         (2, 16, 16, 64, 1201), (1, 8, 8, 64, 3003),
+         (20, 32, 8, 64, 31), (20, 32, 32, 64, 33), (20, 32, 4, 64, 64), (1, 4, 4, 128, 96), (1, 4, 4, 128, 97),
+         (12, 8, 4, 128, 97), (4, 32, 8, 128, 128), (8, 8, 8, 128, 129),
+         (16, 32, 8, 64, 32), (1, 8, 8, 128, 32), (4, 32, 8, 64, 129), (40, 32, 8, 128, 65)]
 
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float16])
