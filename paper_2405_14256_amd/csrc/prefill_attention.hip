@@ -33,6 +33,7 @@ struct PrefillArgs {
 };
 
 constexpr int kPfKeys = 64;    // keys per tile
+constexpr int kMostKeys = 128; // of any kernel's tiles: so many rows past the end of k and v the 32-bit offsets must not wrap
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 template <int DT>
@@ -691,6 +692,7 @@ template <int DT, int D, int KS>
 __global__ __launch_bounds__(256, KS == 4 && D == 128 ? 1 : 2) void k_prefill_attention16_keys(PrefillArgs a) {
   using T = Tile<DT, D>;
   constexpr int NW = 4, ROWS = 32 * NW / KS, KEYS = 32 * KS;
+  static_assert(KEYS <= kMostKeys && kPfKeys <= kMostKeys, "the entry's check of the offsets");
   constexpr int TILE_B = KEYS * T::ROWB;
   constexpr int NI = KEYS / T::RPI / NW;      // transfers per wave, tile and tensor
   constexpr int CT = D / 32;                     // 32-channel tiles of the output
@@ -1086,11 +1088,11 @@ extern "C" int zc_prefill_attention(const zc_tensor4* q, const zc_tensor4* k, co
   if (P < 0 || (P > 0 && (!probe_pos || !lse_probe || !lse))) return ZC_ERR_INVALID_ARG;
   if (q->B > 65535 || q->H > 65535 || q->L > 0x7fffffff - 256) return ZC_ERR_UNSUPPORTED;
   {
-    // one (batch, head) slab of every tensor is addressed with 32-bit byte offsets; a tile may
-    // reach up to 63 rows past the end of k and v, and "nothing" is requested at 0xFFFFF000
+    // one (batch, head) slab of every tensor is addressed with 32-bit byte offsets; a tile of k_prefill_attention16_keys may
+    // reach up to 127 rows past the end of k and v, and "nothing" is requested at 0xFFFFF000
     const int64_t eb = q->dtype == ZC_F32 ? 4 : 2;
-    if (q->L * q->sL * eb >= 0xFFFFF000ll || (k->L + 128) * k->sL * eb >= 0xFFFFF000ll ||
-        (v->L + 128) * v->sL * eb >= 0xFFFFF000ll)
+    if (q->L * q->sL * eb >= 0xFFFFF000ll || (k->L + kMostKeys) * k->sL * eb >= 0xFFFFF000ll ||
+        (v->L + kMostKeys) * v->sL * eb >= 0xFFFFF000ll)
       return ZC_ERR_UNSUPPORTED;
   }
   const int64_t grid = ceil_div64(q->L, 32) * q->H * q->B;         // (the smallest row blocks but for those of 16 rows, at most 1024)

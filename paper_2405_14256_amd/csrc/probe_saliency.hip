@@ -150,6 +150,8 @@ __device__ inline void priority_by_tiles(int left) {
 
 constexpr int kLseRows = 128;                  // probe rows per workgroup of sweep 1
 constexpr int kLseCols = 64;                   // columns per K tile of sweep 1
+constexpr int kBlockCols = 128;                // columns of a workgroup of sweep 2
+static_assert(kLseCols <= kBlockCols, "the entry's check of the offsets past the end of k");
 
 // The row blocks of a head share its a.head_wgs workgroups in proportion to the column tiles their
 // rows can see (a block near the end of a prompt sees ten times those of one near its start; a
@@ -442,6 +444,7 @@ template <int DT, int D, Probes PROBES>
 __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_probe_colsum(ProbeArgs a) {
   using T = Tile<DT, D>;
   constexpr int QT = 64;                        // probe rows per tile
+  static_assert(kBlockCols == 2 * QT, "a block's columns come through the two tile buffers");
   constexpr int TILE_B = QT * T::ROWB;
   constexpr int NI = QT / T::RPI / 4;           // transfers per wave and tile
   __shared__ __align__(kTileAlign) uint8_t Qs[2][TILE_B];
@@ -466,7 +469,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
   // workgroup a CU the divisions only cost time (16 x 8 heads of 64, 400 tokens 7.1 and 7.3), and of up to 64
   // probes in 16 bits every workgroup has as much to do (32 heads, 8192 tokens 12.8 and 13.2; in fp32 the matrix cores do less
   // where 32 rows see the columns: 16 x 16 heads, 500 tokens, both sweeps 62.7 and 61.2).
-  const int nct = ceil_div(a.Lk, 128);
+  const int nct = ceil_div(a.Lk, kBlockCols);
   int j, ct;
   if (a.group) {
     const int hpx = (a.B * a.Hq) >> 3, rank = blockIdx.x >> 3, g = rank / (a.group * nct), rem = rank - g * (a.group * nct);
@@ -479,7 +482,7 @@ __global__ __launch_bounds__(256, (DT == ZC_F32 && D == 128) ? 1 : 4) void k_pro
     if ((j % a.Hq) & 1) ct = nct - 1 - ct;
   }
   const int hq = j % a.Hq, b = j / a.Hq, hk = hq / a.G;
-  const int col0 = ct * 128;
+  const int col0 = ct * kBlockCols;
   const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, kh = lane >> 5;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int rbw = w >> 1, cbp = w & 1;
@@ -1072,9 +1075,9 @@ static int probe_scores(const zc_tensor4* q, const zc_tensor4* k,
     // the kernels address one (batch, head) slab of q and of k with 32-bit byte offsets,
     // and request "nothing" at offset 0xFFFFF000, which must lie past the end of a slab
     const int64_t eb = q->dtype == ZC_F32 ? 4 : 2;
-    // (a K tile may start up to 63 rows before the end of k and reach as far past it: those
+    // (sweep 2 asks for whole blocks of kBlockCols columns, up to 127 rows past the end of k, sweep 1 for whole tiles of 64: those
     // offsets must not wrap either)
-    if (q->L * q->sL * eb >= 0xFFFFF000ll || (k->L + 128) * k->sL * eb >= 0xFFFFF000ll || (int64_t)P * 4 >= 0xFFFFF000ll) return ZC_ERR_UNSUPPORTED;
+    if (q->L * q->sL * eb >= 0xFFFFF000ll || (k->L + kBlockCols) * k->sL * eb >= 0xFFFFF000ll || (int64_t)P * 4 >= 0xFFFFF000ll) return ZC_ERR_UNSUPPORTED;
   }
   const size_t need = probe_least_bytes(q->B, q->H, k->L, P), extra = join_bytes(q->B, q->H, P);
   if (!ws || ws_bytes < need || (reinterpret_cast<uintptr_t>(ws) & 15)) return ZC_ERR_WORKSPACE;
