@@ -205,13 +205,14 @@ def test_keys_of_more_threads_than_a_launch_counts():
 
 
 @pytest.mark.parametrize("kind", ["tame", "nan", "wild"])
-@pytest.mark.parametrize("n", [1, 2, 63, 517, 2600, 4096, 4097, 7003])
+@pytest.mark.parametrize("n", [1, 2, 60, 61, 63, 517, 2600, 4096, 4097, 7003])
 def test_two_bit_fp16_keys_by_thresholds(n, kind):
     """2-bit codes of fp16 keys that stay in registers, found by three thresholds a channel, against those
     of the kernel that divides every value (another layout, so another path): the same codes where
     values are ties of the rounding and one number beside them, equal, zeros of both signs, subnormal,
     the largest, far from zero in a narrow range, a NaN, or of a range without thresholds.  (Up to
-    8 rows a thread divide too: 4096 tokens are the most that do, 4097 the fewest that do not.)"""
+    8 rows a thread divide too: 4096 tokens are the most that do, 4097 the fewest that do not.  Up to 60 take the one launch of
+    short subsets, which divides.)"""
     from tests.pipeline_check import packed_to_chunks
     H, D = 3, 64
     g = torch.Generator().manual_seed(n)
@@ -250,9 +251,10 @@ def test_two_bit_fp16_keys_by_thresholds(n, kind):
 
 @pytest.mark.parametrize("dtype", [torch.float16, torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("layout", [zb.ZC_LAYOUT_ROW, zb.ZC_LAYOUT_TGROUP])
-@pytest.mark.parametrize("n", [1, 9, 130, 1000, 9000, 40000])
+@pytest.mark.parametrize("n", [1, 9, 32, 61, 130, 1000, 9000, 40000])
 def test_keys_of_a_channel_of_nan(n, layout, dtype):
-    """A channel that is all NaN has NaN for its parameters, whether its tokens stay in registers, come in
+    """A channel that is all NaN has NaN for its parameters, whether its tokens stay in registers (of the one launch of
+    short subsets up to 32 in fp32 and 60, of the column sweep from 61 on), come in
     batches or in ranges, whatever part of the workgroup they leave without a row; the other channels have theirs."""
     H, D = 2, 64
     X = torch.randn(1, H, n, D, generator=torch.Generator().manual_seed(n)).to(dtype)
@@ -272,17 +274,18 @@ def test_keys_of_a_channel_of_nan(n, layout, dtype):
 @pytest.mark.parametrize("cap", [524224, 524288])
 def test_keys_on_either_side_of_4_gigabytes(cap):
     """Codes of a batch element just below and at 2^32 bytes: the first still have 32-bit offsets in the column
-    sweep, the second take the way of keys that do not stay in registers; either has the codes of a small arena."""
-    H, D, n = 64, 128, 90
+    sweep, the second take the way of keys that do not stay in registers; either has the codes of a small arena.  (130
+    tokens: more than the one launch of short subsets takes, whose offsets have 64 bits.)"""
+    H, D, n = 64, 128, 130
     X = torch.randn(1, H, 2 * n, D, generator=torch.Generator().manual_seed(cap)).to(torch.bfloat16).to(DEV)
     idx = torch.arange(n, dtype=torch.int32, device=DEV)[None]
     got = []
-    for c in (cap, 256):
+    for c in (cap, 384):
         p = zb.PackedTensor(1, H, D, 64, c, 2, 8, "channel", zb.ZC_LAYOUT_ROW, max_chunks=2, device=DEV)
-        for x in (X[:, :, :n], X[:, :, n:]):                    # (the second chunk begins at slot 128)
+        for x in (X[:, :, :n], X[:, :, n:]):                    # (the second chunk begins at slot 192)
             zb.zc_quantize_pack(x, idx[:, :0], idx, p)
         rows = p.codes_lo.view(H, c, D)
-        assert not bool(rows[:, n:128].any()) and not bool(rows[:, 128 + n:256].any())
-        got.append((torch.cat([rows[:, :n], rows[:, 128:128 + n]], 1).clone(), p.chan_scale[:2].clone(), p.chan_zero[:2].clone()))
+        assert not bool(rows[:, n:192].any()) and not bool(rows[:, 192 + n:384].any())
+        got.append((torch.cat([rows[:, :n], rows[:, 192:192 + n]], 1).clone(), p.chan_scale[:2].clone(), p.chan_zero[:2].clone()))
         del p, rows
     assert all(torch.equal(a, b) for a, b in zip(*got))

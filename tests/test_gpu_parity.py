@@ -855,6 +855,7 @@ def test_decode_timeline_mode_of_the_benchmark():
     (4, 40, 128, 640, torch.float16), (4, 40, 128, 641, torch.bfloat16),    # sixteen across, then eight
     (4, 40, 128, 161, torch.float32), (2, 16, 128, 1300, torch.bfloat16),
     (64, 8, 128, 25, torch.bfloat16), (64, 8, 128, 60, torch.float16), (128, 8, 64, 64, torch.float32), (1, 1, 64, 255, torch.bfloat16),   # few tokens: small workgroups, and one more
+    (8, 3, 64, 70, torch.bfloat16), (7, 8, 128, 100, torch.bfloat16), (7, 8, 128, 129, torch.float16),      # the same where the one launch of short subsets takes 16-bit keys of 60 tokens at most
     (1, 17, 128, 5125, torch.bfloat16), (1, 17, 128, 3000, torch.float32),  # rows of more than 256 vectors that only fit in slices of 16 channels
     (4, 4, 128, 5121, torch.bfloat16), (4, 5, 128, 5121, torch.float16),    # the same with 1024 threads: 64 vectors stay, more do not
     (2, 1, 128, 33001, torch.bfloat16), (1, 2, 64, 9000, torch.float32),    # token ranges: the last one shorter, those of the other subset empty
@@ -916,7 +917,7 @@ def test_quantize_of_the_largest_batches():
     (1, 8, 8, 64, 256, 26, torch.float32), (1, 1, 1, 64, 1, 1, torch.bfloat16), (2, 18, 6, 64, 33, 32, torch.float16),
     (3, 17, 17, 64, 100, 10, torch.bfloat16), (1, 12, 4, 128, 65, 31, torch.float32), (130, 24, 8, 128, 31, 9, torch.float16)])
 def test_probe_few_rows(B, Hq, Hkv, d, Lk, P, dtype):
-    """At most 32 probe rows (one launch for sums and mean) against the oracle, the same scores with
+    """At most 32 probe rows (one launch for sums and mean where that costs least) against the oracle, the same scores with
     and without per-head ones: heads that do not divide over the waves, a row block that is full
     and one that is not, columns one past a block."""
     g = torch.Generator().manual_seed(Lk + P)

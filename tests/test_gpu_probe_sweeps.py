@@ -61,10 +61,13 @@ CASES = [
     (1, 2, 1, 64, 2000, torch.float16, lambda L: torch.arange(L - 769, L)),
     (1, 3, 3, 128, 1600, torch.bfloat16, lambda L: torch.arange(1538)),
     (1, 2, 2, 64, 3000, torch.float32, lambda L: torch.cat([torch.arange(90), spread(L, 700)]).unique()),
-    # few probes over several ranges, joined by a launch; as many ranges as two at a time leave of nine
+    # few probes over several ranges, joined by sweep 2; as many ranges as two at a time leave of nine
     (10, 16, 4, 64, 352, torch.bfloat16, lambda L: spread(L, 18)),
     (3, 8, 8, 64, 900, torch.float16, lambda L: spread(L, 31)),
     (1, 2, 1, 64, 900, torch.bfloat16, lambda L: spread(L, 300)),
+    # ranges joined by a launch: in front of the one launch of few probes, and of a sweep 2 of more than a round of workgroups
+    (3, 12, 12, 64, 105, torch.float32, lambda L: spread(L, 10)),
+    (36, 8, 4, 64, 700, torch.bfloat16, lambda L: spread(L, 70)),
 ]
 
 
@@ -206,7 +209,7 @@ def test_every_column_of_every_head_of_a_group(B, Hq, Hkv, d, L, P, dtype):
     assert torch.allclose(per_head.mean(1), scores, rtol=1e-5, atol=0)
 
 
-# Few probes, sweep 2 and the mean in one launch: 1, 15 to 17, 31 and 32 rows (blocks of 16, halves of a head's two by waves of
+# Few probes, sweep 2 and the mean in one launch (given normalisers; without them two launches may cost less): 1, 15 to 17, 31 and 32 rows (blocks of 16, halves of a head's two by waves of
 # their own and by one), fewer heads than waves, one wave more and heads that do not divide by them, columns of less than a
 # tile, of whole tiles and one more, 16 a workgroup and (enough of them for more than a round) 32, every probe at one position,
 # probes in front of most columns
