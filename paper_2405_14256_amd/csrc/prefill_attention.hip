@@ -584,7 +584,8 @@ __global__ __launch_bounds__(64 * NW, 2) void k_prefill_attention16(PrefillArgs 
     }
     const float m_new = fmaxf(m, tmax);
     if (__builtin_amdgcn_ballot_w64(m_new > m)) {
-      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+      // (0 either way; without the select the schedule differs: 2 x 32 heads, 3001 rows 178.1 -> 177.2 us, but 11 x 32 over 4, 157 rows, with probes 16.6 -> 17.3)
+      const float alpha = (m == kLowest) ? 0.f : __builtin_amdgcn_exp2f(m - m_new);
       l *= alpha;
 #pragma unroll
       for (int ct = 0; ct < CT; ++ct)
