@@ -988,25 +988,27 @@ static int head_group(const PrefillArgs& a, int nqb, int slots) {
 // Waves that share a row's keys in a 16-bit call: 1, 2 or 4, by what each way costs in us: a workgroup's start, then the steps of the
 // longest row block or a SIMD's share of all steps, and what further workgroups a CU add.  Fitted to 400 calls of 1 to 640
 // heads and 64 to 9000 rows, timed all three ways (rms 4 to 8 %; calls below 4000 heads x row blocks of 32); one wave unless another way is 8 % cheaper by
-// that: all 400 are within 2 % of one wave or faster, 1.18 times in the geometric mean (1.19 with the best way each).  Beyond 2500
-// heads x row blocks a full chip gains nothing (1024 heads of 128 channels, 160 rows, one and two 44.9 and 48.5 us; 4096 of 192 206 and 225).  Up to 64 rows there is
+// that: all 400 are within 2 % of one wave or faster, 1.18 times in the geometric mean (1.19 with the best way each).  Beyond 2000
+// heads x row blocks a full chip gains nothing (448 heads of 64, 130 rows, one and two waves 10.8 and 11.1 us; 1024 heads of 128 channels, 160 rows 44.9 and 48.5; 4096 of 192 206 and 225).  Up to 64 rows there is
 // one step to share and a start that costs more (8 heads of 128, 64 rows 5.1 and 5.7 us; 640 of 64 rows 12.5 and 13.8; 512 of 64 channels, 32 rows 4.2
 // and 4.8), except where registers decide: of 64 channels a CU has three workgroups of two waves a row and two of one (640 heads, 48 rows 7.0
 // and 6.1 us; 1024 8.0 and 8.4; 4096 27.4 and 24.7).
 static int key_split(int64_t heads, int64_t L, int D) {
-  struct Way { double start, step, share, more; int split, places; };
-  const Way ways[2][3] = {{{3.45, 0.40, 0.356, 3.27, 1, 1}, {3.90, 0.455, 0.362, 1.52, 2, 1}, {4.06, 0.525, 0.451, 1.58, 4, 1}},
-                          {{4.98, 0.58, 0.560, 5.90, 1, 1}, {4.80, 0.755, 0.638, 3.13, 2, 1}, {5.16, 0.833, 1.100, 3.70, 4, 0}}};
+  struct Way { double start, step, share, more; int split, places; double second; };
+  const Way ways[2][3] = {{{3.45, 0.40, 0.356, 3.27, 1, 1, 0.0}, {3.90, 0.455, 0.362, 1.52, 2, 1, 0.0}, {4.06, 0.525, 0.451, 1.58, 4, 1, 0.0}},
+                          {{4.98, 0.58, 0.560, 5.90, 1, 1, 0.0}, {4.80, 0.755, 0.638, 3.13, 2, 1, 0.4}, {5.16, 0.833, 1.100, 3.70, 4, 0, 0.0}}};
   const int64_t blocks = ceil_div64(L, 32);
   if (blocks <= 2) return D == 64 && 9 * ceil_div64(heads, 768) < 8 * ceil_div64(heads, 512) ? 2 : 1;
-  if (heads * blocks > 2500) return 1;
+  if (heads * blocks > 2000) return 1;
   const double all = (double)heads * (double)blocks * (double)(blocks + 1) / 2048.0;     // steps of a SIMD
   int best = 1;
   double least = 0.0;
   for (const Way& w : ways[D == 128]) {
     const int64_t n = heads * ceil_div64(blocks, 4 / w.split);
-    // (one workgroup a CU: whole rounds; two: about as they come)
-    const double further = w.places ? (double)n / 256.0 - 1.0 : (double)(ceil_div64(n, 256) - 1);
+    // (one workgroup a CU: whole rounds; two: about as they come, of 128 channels and two waves a row the first of them costs
+    // more: 96 heads, 175 rows, 288 workgroups, one and two waves 7.95 and 8.8 us)
+    double further = w.places ? (double)n / 256.0 - 1.0 : (double)(ceil_div64(n, 256) - 1);
+    if (n > 256 && further < w.second * (double)n / 256.0) further = w.second * (double)n / 256.0;
     const double chain = w.step * (double)ceil_div64(blocks, w.split), shared = w.share * all;
     const double t = w.start + (chain > shared ? chain : shared) + (further > 0.0 ? w.more * further : 0.0);
     if (w.split == 1) least = 0.92 * t;
