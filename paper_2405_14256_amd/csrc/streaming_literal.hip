@@ -80,9 +80,9 @@ typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 // lanes of the value columns need, so a second tile's slots take the residual columns' lanes there, and positions and
 // parameters are requested once for both.  Measured, us per call: on the vector ALUs with q' in LDS / with fp32 matrix
 // instructions for the packed tokens too / a tile at a time / now:
-//   4096 tokens, 8 KV heads of 4 query heads      13.6 /   8.5 /  6.3 /  5.9
-//   8000 tokens, the same, batch 8                   - /     - / 23.7 / 18.9
-//   2000 tokens, 40 KV heads of 1, batch 16      103.3 / 124.1 / 50.2 / 36.3
+//   4096 tokens, 8 KV heads of 4 query heads      13.6 /   8.5 /  6.7 /  5.6
+//   8000 tokens, the same, batch 8                   - /     - / 22.9 / 17.3
+//   2000 tokens, 40 KV heads of 1, batch 16      103.3 / 124.1 / 48.7 / 33.9
 constexpr float kProbLo = 2048.f;
 
 // Codes of a quarter row (NK = D / 4 channels) as fp16 operand registers, two codes each: register
@@ -603,13 +603,14 @@ static int64_t probs_grid(int64_t blocks, int64_t heads) {
   const int64_t n = blocks * heads;
   return blocks + ((blocks == 4 && n > 520) || (blocks % 8 == 0 && n > 1500) ? 1 : 0);
 }
-// Tiles of the packed segments: one at a time, one a wave, while no CU gets a second workgroup (latency); else two at a time
-// (a unit), `tpw` units a wave.  us, one tile and one unit: 8 heads of 2530 tokens (250 and 130 workgroups) 4.5 and 4.7; 16 heads of 1383 (368) 5.5 and 4.65.
+// Tiles of the packed segments: one at a time, one a wave, while no CU gets a second workgroup, or two at most where pairs would give it two as
+// well (latency); else two at a time (a unit), `tpw` units a wave.  One tile's time over one unit's, 2500 drawn calls: up to 256 workgroups 0.95 to 0.99, 257
+// to 512 and more than 256 by units 0.95 to 0.98, but up to 256 by units 1.13 to 1.16 (16 heads of 1383, 368 and 192 workgroups, 5.5 and 4.65 us), 513 to 768 1.06 to 1.09.
 struct ProbsShape { bool pairs; int tpw; };
 // What units a wave cost: the start of a wave (the query operand; a unit is 0.3 of it for 128 channels and 0.4 for 64, in fp32 it is 1.2)
 // and its units, times what the workgroups of the fullest CU take: three (128 channels) or four go at a time, a lone one at 0.55 of that, and of
-// further ones the last count half, as they start when others end.  Grids that give XCDs the same segments pay 8 %.
-// Of 2500 drawn calls timed in all ten shapes the one of least cost is 0.7 % slower than the best in the geometric mean; all are 1.20 times faster than by a tile at
+// further ones the last count half, as they start when others end.  Grids that give XCDs the same segments pay 8 %, more than six units, whose ends
+// are coarse, 6 %.  Of 2500 drawn calls timed in all ten shapes the one of least cost is 0.7 % slower than the best in the geometric mean; all are 1.20 times faster than by a tile at
 // a time with up to eight a wave.  us, one tile and 1, 2, 3, 4, 6, 9 units a wave:
 // 9 x 8 heads of 22847 tokens, bits 8 and 4, fp16 105, 69, 52, 46, 43, 57 (2.3 rounds of 4), 43; 13 x 40 of 1552 54, 37, 32, 28, 26, 32, 25; 5 x 40 of 347
 // 10.3, 8.9, 10.0 (4 workgroups a head), 7.8, 7.8; 2 x 8 of 1383 5.5, 4.65, 5.9, 6.6, 7.0.
@@ -617,7 +618,7 @@ static double probs_cost(int64_t blocks, int64_t heads, int64_t units, const zc_
   const int64_t grid = probs_grid(blocks, heads), wgs = grid * heads;
   const double places = q->D == 128 ? 3.0 : 4.0, x = (double)wgs / 256.0, n = (double)ceil_div64(wgs, 256);
   const double f = n <= 1.0 ? 0.55 : n <= places ? 0.35 + 0.65 * n / places : 0.5 * (x + n) / places > 1.0 ? 0.5 * (x + n) / places : 1.0;
-  return f * ((q->dtype == ZC_F32 ? 1.2 : 1.0) + (q->D == 128 ? 0.3 : 0.4) * (double)units) * (grid % 8 == 0 || grid == 4 ? 1.08 : 1.0);
+  return f * ((q->dtype == ZC_F32 ? 1.2 : 1.0) + (q->D == 128 ? 0.3 : 0.4) * (double)units) * (grid % 8 == 0 || grid == 4 ? 1.08 : 1.0) * (units > 6 ? 1.06 : 1.0);
 }
 static ProbsShape probs_shape(const zc_packed* Kp, int64_t heads, int64_t tail_wgs, const zc_tensor4* q) {
   constexpr int kLong = 64;
@@ -633,12 +634,12 @@ static ProbsShape probs_shape(const zc_packed* Kp, int64_t heads, int64_t tail_w
       else if (n_longs < kLong) longs[n_longs++] = units;
       else longs[kLong - 1] += units;                        // (a price, not the grid)
     }
-  if (one * heads <= 256) return {false, 1};
   ProbsShape best = {true, 1};
   double least = 0.0;
   for (int tpw = 1; tpw <= 9; ++tpw) {
     int64_t blocks = rest;
     for (int i = 0; i < n_longs; ++i) blocks += ceil_div64(longs[i], 4 * tpw);
+    if (tpw == 1 && one * heads <= (probs_grid(blocks, heads) * heads > 256 ? 512 : 256)) return {false, 1};
     const double cost = probs_cost(blocks, heads, tpw, q);
     if (tpw == 1 || cost < least) { least = cost; best.tpw = tpw; }
     if (blocks * heads <= 256 || 4 * tpw >= longest) break;    // (more a wave leaves no fewer to wait for)
